@@ -1,4 +1,4 @@
-"""Builds libtsvd.so (the C-ABI library) for gfx950 with hipcc, in-tree."""
+"""Builds libtsvd.so (the C-ABI library) for gfx950 with hipcc, and the torch binding beside it, in-tree."""
 from __future__ import annotations
 
 import os
@@ -8,10 +8,30 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtsvd.so")
+BINDING = os.path.join(HERE, "_tsvd_torch.so")
 SOURCES = ["tsvd_pack.cpp", "tsvd_api.hip", "tsvd_skinny.hip", "tsvd_gemv.hip", "tsvd_mid.hip", "tsvd_dense.hip", "tsvd_gemm.hip", "tsvd_fp6.hip", "tsvd_transition.hip", "tsvd_conv.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-pthread",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument"]
+
+
+def build_binding(verbose: bool = False) -> str:
+    """Compiles csrc/tsvd_torch.cpp (host code on torch's headers) against libtsvd.so."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "tsvd_torch.cpp"), "-o", BINDING,
+           "-L" + HERE, "-ltsvd", "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stderr + "\n")
+        raise RuntimeError("g++ failed building the torch binding")
+    return BINDING
 
 
 def build(verbose: bool = False) -> str:
@@ -54,6 +74,7 @@ def build(verbose: bool = False) -> str:
         if res.returncode != 0:
             sys.stderr.write(filtered(res.stderr) + "\n")
             raise RuntimeError("hipcc failed linking libtsvd.so")
+    build_binding(verbose)
     return LIB
 
 

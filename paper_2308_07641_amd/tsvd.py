@@ -1,6 +1,6 @@
-"""ctypes binding with the same names as the C ABI (include/tsvd.h).
+"""Python binding with the same names as the C ABI (include/tsvd.h).
 
-Argument marshalling only.  If libtsvd.so has not been built the import of this module still
+Argument marshalling only: the forward calls in a small native extension (csrc/tsvd_torch.cpp), the others through ctypes.  If libtsvd.so has not been built the import of this module still
 succeeds (so that the build step can import the package) but every call raises.
 """
 from __future__ import annotations
@@ -18,6 +18,7 @@ TSVD_TOKEN_MAJOR = 1
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libtsvd.so")
 _lib = None
+_binding = None
 
 _vp = ctypes.c_void_p
 _i64 = ctypes.c_int64
@@ -87,6 +88,21 @@ def load_library():
             fn.argtypes = args
         _lib = lib
     return _lib
+
+
+def _load_binding():
+    """Loads the native argument marshalling of the forward calls (csrc/tsvd_torch.cpp); raises if it has not been built."""
+    global _binding
+    load_library()
+    import torch
+    try:
+        from . import _tsvd_torch
+    except ImportError as e:
+        raise RuntimeError("the native binding _tsvd_torch.so is missing or does not load: build it with "
+                           "`python -m paper_2308_07641_amd.build` (or __graft_entry__.build())") from e
+    _tsvd_torch.setup(TsvdError, torch._C._cuda_getCurrentRawStream)
+    _binding = _tsvd_torch
+    return _binding
 
 
 def tsvd_strerror(status: int) -> str:
@@ -218,27 +234,7 @@ def tsvd_forward(h: Handle, x, y=None, workspace=None, stream=None):
     x, y, workspace are torch CUDA tensors used as plain device buffers; the work is
     enqueued on `stream` (default: torch's current stream) and not synchronised.
     """
-    import torch
-    if not x.is_cuda:
-        raise ValueError("x must live on the GPU")
-    x2 = x if x.dim() == 2 else x.unsqueeze(1)
-    if x2.shape[0] != h.N or x2.stride(1) != 1:
-        raise ValueError("x must be [N,B] with unit column stride")
-    B = x2.shape[1]
-    ldx = x2.stride(0) if x2.shape[0] > 1 else max(B, x2.stride(0))
-    if y is None:
-        y = torch.empty((h.M, B), dtype=torch.float32, device=x.device)
-    if y.dtype != torch.float32 or y.shape != (h.M, B) or y.stride(1) != 1 or not y.is_cuda:
-        raise ValueError("y must be a float32 GPU tensor [M,B] with unit column stride")
-    ldy = y.stride(0) if y.shape[0] > 1 else max(B, y.stride(0))
-    ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    _check(load_library().tsvd_forward(h.ptr, x2.data_ptr(), _dtype_code(x2), B, ldx, y.data_ptr(), TSVD_F32, ldy,
-                                       ws_ptr, ws_bytes, stream), "tsvd_forward")
-    return y
+    return (_binding or _load_binding()).forward(h, x, y, workspace, stream)
 
 
 def tsvd_workspace_bytes_ex(h: Handle, B: int, x_dtype: int, x_layout: int) -> int:
@@ -251,65 +247,13 @@ def tsvd_forward_ex(h: Handle, x, x_layout=TSVD_FEATURE_MAJOR, bias=None, y=None
 
     Same conventions as tsvd_forward; bias is a float32 GPU tensor [M] or None.
     """
-    import torch
-    if not x.is_cuda or x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be a 2-d GPU tensor with unit inner stride")
-    token_major = x_layout == TSVD_TOKEN_MAJOR
-    B, feat = (x.shape[0], x.shape[1]) if token_major else (x.shape[1], x.shape[0])
-    if feat != h.N:
-        raise ValueError("x does not have N features")
-    ldx = x.stride(0) if x.shape[0] > 1 else max(x.shape[1], x.stride(0))
-    ydt = torch.bfloat16 if y_dtype == TSVD_BF16 else torch.float32
-    if y is None:
-        y = torch.empty((h.M, B), dtype=ydt, device=x.device)
-    if y.dtype != ydt or y.shape != (h.M, B) or y.stride(1) != 1 or not y.is_cuda:
-        raise ValueError("y must be a GPU tensor [M,B] of the requested type with unit column stride")
-    ldy = y.stride(0) if y.shape[0] > 1 else max(B, y.stride(0))
-    bias_ptr = None
-    if bias is not None:
-        if bias.dtype != torch.float32 or bias.shape != (h.M,) or not bias.is_cuda or not bias.is_contiguous():
-            raise ValueError("bias must be a contiguous float32 GPU tensor [M]")
-        bias_ptr = bias.data_ptr()
-    ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    _check(load_library().tsvd_forward_ex(h.ptr, x.data_ptr(), _dtype_code(x), x_layout, B, ldx, bias_ptr, y.data_ptr(),
-                                          y_dtype, ldy, ws_ptr, ws_bytes, stream), "tsvd_forward_ex")
-    return y
+    return (_binding or _load_binding()).layer(h, x, x_layout, bias, y, y_dtype, TSVD_FEATURE_MAJOR, workspace, stream, 0)
 
 
 def tsvd_forward_io(h: Handle, x, x_layout=TSVD_FEATURE_MAJOR, bias=None, y=None, y_dtype=TSVD_F32, y_layout=TSVD_FEATURE_MAJOR,
                     workspace=None, stream=None):
     """tsvd_forward_ex with the layout of y chosen too: [M,B] (feature-major) or [B,M] (token-major)."""
-    import torch
-    if not x.is_cuda or x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be a 2-d GPU tensor with unit inner stride")
-    B, feat = (x.shape[0], x.shape[1]) if x_layout == TSVD_TOKEN_MAJOR else (x.shape[1], x.shape[0])
-    if feat != h.N:
-        raise ValueError("x does not have N features")
-    ldx = x.stride(0) if x.shape[0] > 1 else max(x.shape[1], x.stride(0))
-    ydt = torch.bfloat16 if y_dtype == TSVD_BF16 else torch.float32
-    yshape = (B, h.M) if y_layout == TSVD_TOKEN_MAJOR else (h.M, B)
-    if y is None:
-        y = torch.empty(yshape, dtype=ydt, device=x.device)
-    if y.dtype != ydt or tuple(y.shape) != yshape or y.stride(1) != 1 or not y.is_cuda:
-        raise ValueError("y must be a GPU tensor of the requested type and layout with unit inner stride")
-    ldy = y.stride(0) if y.shape[0] > 1 else max(y.shape[1], y.stride(0))
-    bias_ptr = None
-    if bias is not None:
-        if bias.dtype != torch.float32 or bias.shape != (h.M,) or not bias.is_cuda or not bias.is_contiguous():
-            raise ValueError("bias must be a contiguous float32 GPU tensor [M]")
-        bias_ptr = bias.data_ptr()
-    ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    _check(load_library().tsvd_forward_io(h.ptr, x.data_ptr(), _dtype_code(x), x_layout, B, ldx, bias_ptr, y.data_ptr(),
-                                          y_dtype, y_layout, ldy, ws_ptr, ws_bytes, stream), "tsvd_forward_io")
-    return y
+    return (_binding or _load_binding()).layer(h, x, x_layout, bias, y, y_dtype, y_layout, workspace, stream, 1)
 
 
 TSVD_NOALLOC_MAX_WORKSPACE = 16 << 20
@@ -317,28 +261,9 @@ TSVD_NOALLOC_MAX_WORKSPACE = 16 << 20
 
 def tsvd_forward_noalloc(h: Handle, x, y, x_layout=TSVD_FEATURE_MAJOR, bias=None, y_dtype=TSVD_F32, stream=None):
     """tsvd_forward_ex on the library's fixed per-GPU workspace; y must be given (nothing is allocated)."""
-    import torch
-    if not x.is_cuda or x.dim() != 2 or x.stride(1) != 1:
-        raise ValueError("x must be a 2-d GPU tensor with unit inner stride")
-    token_major = x_layout == TSVD_TOKEN_MAJOR
-    B, feat = (x.shape[0], x.shape[1]) if token_major else (x.shape[1], x.shape[0])
-    if feat != h.N:
-        raise ValueError("x does not have N features")
-    ldx = x.stride(0) if x.shape[0] > 1 else max(x.shape[1], x.stride(0))
-    ydt = torch.bfloat16 if y_dtype == TSVD_BF16 else torch.float32
-    if y.dtype != ydt or y.shape != (h.M, B) or y.stride(1) != 1 or not y.is_cuda:
+    if y is None:
         raise ValueError("y must be a GPU tensor [M,B] of the requested type with unit column stride")
-    ldy = y.stride(0) if y.shape[0] > 1 else max(B, y.stride(0))
-    bias_ptr = None
-    if bias is not None:
-        if bias.dtype != torch.float32 or bias.shape != (h.M,) or not bias.is_cuda or not bias.is_contiguous():
-            raise ValueError("bias must be a contiguous float32 GPU tensor [M]")
-        bias_ptr = bias.data_ptr()
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
-    _check(load_library().tsvd_forward_noalloc(h.ptr, x.data_ptr(), _dtype_code(x), x_layout, B, ldx, bias_ptr, y.data_ptr(),
-                                               y_dtype, ldy, stream), "tsvd_forward_noalloc")
-    return y
+    return (_binding or _load_binding()).layer(h, x, x_layout, bias, y, y_dtype, TSVD_FEATURE_MAJOR, None, stream, 2)
 
 
 # ---- diagnostic interface (include/tsvd_tuning.h): for the tests and the benchmark only
@@ -474,34 +399,11 @@ def tsvd_transition(W, theta: float, tol: float, max_rank: int, stream=None, q: 
 
 
 # ---- convolution forms (include/tsvd_conv.h)
-class ConvGeometry(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("form", "c_in", "c_out", "k1", "k2", "stride1", "stride2", "pad1", "pad2", "dil1", "dil2", "groups")]
-
-
 def tsvd_conv2d_forward(h: Handle, form: int, c_in: int, c_out: int, k1: int, k2: int, x, stride=(1, 1), pad=(0, 0), dil=(1, 1),
                         bias=None, y_dtype=TSVD_F32, stream=None, groups=1):
     """y [C_out, images, Ho, Wo] = conv2d(x [C_in, images, H, W] bf16) with the kernel in ternary-SVD form `form`
     (groups > 1: form 0 with per-group factors, see include/tsvd_conv.h)."""
-    import torch
-    if not x.is_cuda or x.dtype != torch.bfloat16 or x.dim() != 4 or x.shape[0] != c_in or not x.is_contiguous():
-        raise ValueError("x must be a contiguous bf16 GPU tensor [C_in, images, H, W]")
-    _, images, H, W = x.shape
-    g = ConvGeometry(form, c_in, c_out, k1, k2, stride[0], stride[1], pad[0], pad[1], dil[0], dil[1], groups)
-    lib = load_library()
-    nbytes = int(lib.tsvd_conv2d_workspace_bytes(h.ptr, ctypes.addressof(g), images, H, W))
-    if nbytes == 0:
-        raise ValueError("geometry does not fit the packed matrix (or is invalid)")
-    Ho = (H + 2 * pad[0] - dil[0] * (k1 - 1) - 1) // stride[0] + 1
-    Wo = (W + 2 * pad[1] - dil[1] * (k2 - 1) - 1) // stride[1] + 1
-    ws = torch.empty((nbytes,), dtype=torch.uint8, device=x.device)
-    y = torch.empty((c_out, images, Ho, Wo), dtype=torch.bfloat16 if y_dtype == TSVD_BF16 else torch.float32, device=x.device)
-    bias_ptr = None
-    if bias is not None:
-        _need(bias, torch.float32, (c_out,), "bias")
-        bias_ptr = bias.data_ptr()
-    _check(lib.tsvd_conv2d_forward(h.ptr, ctypes.addressof(g), x.data_ptr(), images, H, W, bias_ptr, y.data_ptr(), y_dtype,
-                                   ws.data_ptr(), nbytes, _stream(x, stream)), "tsvd_conv2d_forward")
-    return y
+    return (_binding or _load_binding()).conv2d(h, form, c_in, c_out, k1, k2, x, stride, pad, dil, bias, y_dtype, stream, groups)
 
 
 def tsvd_free(h: Handle) -> None:
