@@ -50,13 +50,12 @@ tsvd_status tsvd_residual(const double* W_dev, const int8_t* U_dev, int64_t ldu,
                           int64_t M, int64_t K, int64_t N, double* R_dev, double* norm2_dev, void* stream);
 
 /* First step of an iteration of Algorithm 2 for q = 1: the leading singular triple of R [M][N]
- * (the paper calls a full SVD and keeps the leading vectors; only those are needed), by
- * Golub-Kahan-Lanczos bidiagonalisation with full reorthogonalisation in fp64: tens of steps where
- * a power iteration needs thousands on the close singular values of a random matrix.  The small
- * bidiagonal problem is solved on the host, so the call SYNCHRONISES with the stream.  Stops when
- * the residual |R^T u - sigma v| of the pair is below 1e-12 sigma, restarting from the current
- * estimate every 128 steps, or after max_steps steps in total.
- *   u_dev [M], v_dev [N] : unit vectors; sigma_dev [1]; steps_dev optional int32[1].
+ * (the paper calls a full SVD and keeps the leading vectors; only those are needed), in fp64.  Up to min(M, N) = 2048 by
+ * repeated squaring of the Gram matrix on the shorter side until it is numerically of rank one; beyond by
+ * Golub-Kahan-Lanczos bidiagonalisation with full reorthogonalisation (restarted every 128 steps).  Either way the residual
+ * |R^T u - sigma v| of the pair ends below 1e-12 sigma, unless max_steps squarings or Lanczos steps were not enough.  The host
+ * looks at the progress in between, so the call SYNCHRONISES with the stream.
+ *   u_dev [M], v_dev [N] : unit vectors; sigma_dev [1]; steps_dev optional int32[1]: squarings or Lanczos steps taken.
  *   workspace : device, at least tsvd_leading_singular_pair_workspace(M, N) bytes, 256-byte aligned.
  * The sign of the pair (u, v) is arbitrary, as it is for any SVD routine.  M, N <= 8192. */
 size_t tsvd_leading_singular_pair_workspace(int64_t M, int64_t N);
@@ -66,7 +65,7 @@ tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M, int64_t N
 
 /* Algorithm 2 with q = 1, chaining the calls above: until |W - U diag(S) V|_F / |W|_F <= tol or
  * the rank reaches max_rank.  SYNCHRONISES with the stream once per iteration (the exit test
- * reads one number back).
+ * reads one number back; the following iteration is enqueued by then and dropped where the loop ends).
  *   W_dev : [M][N] fp64.   U_dev : [M][max_rank] int8, V_dev : [max_rank][N] int8, S_dev :
  *   [max_rank] fp64: the first *rank_out columns / rows / entries are the result (U has row stride
  *   max_rank).   errors_host : optional host array [max_rank]: relative error after each iteration.

@@ -1,0 +1,38 @@
+// Leading singular pair of an fp64 matrix by repeated squaring of its Gram matrix (tsvd_pair.hip), as the transition
+// (tsvd_transition.hip) uses it.  Everything is enqueued; nothing here waits for the device.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+// What the device reports about the squarings of one pair.
+struct tsvd_pair_state {
+    int last;            // index of the squared matrix that is numerically of rank one, -1 while there is none
+    int missed;          // pairs since the caller cleared it whose squarings ended before that
+};
+
+struct tsvd_pair_plan {
+    int M, N;            // of R
+    int n, np;           // the shorter side, and rounded up to 64
+    double* X[2];        // [np][np] the squared matrices in turn
+    double* v0;          // [N] start vector
+    double* s;           // [n] start vector on the shorter side (v0 itself where that is the columns)
+    tsvd_pair_state* state;
+    double *u, *v;       // [M], [N]: the pair, not normalised
+};
+
+#define TSVD_PAIR_MAX_SQUARINGS 48
+
+// Whether the squarings are the faster method for an M x N matrix (the others take Lanczos steps).
+bool tsvd_pair_squares(int64_t M, int64_t N);
+size_t tsvd_pair_bytes(int64_t M, int64_t N);
+// Lays the plan out in `mem` (tsvd_pair_bytes, 256-byte aligned) and enqueues the start vector.
+void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* plan, hipStream_t stream);
+// Gram matrix of R [M][N] and its squarings `from` .. `to` - 1 (from = 0 computes the Gram matrix first).
+void tsvd_pair_square(const tsvd_pair_plan& plan, const double* R, int from, int to, hipStream_t stream);
+// plan.u and plan.v from the last squared matrix; `count` squarings were enqueued in total.
+void tsvd_pair_vectors(const tsvd_pair_plan& plan, const double* R, int count, hipStream_t stream);
+// Unit vectors, singular value and number of squarings (steps may be null) of the pair in the plan.
+void tsvd_pair_normalise(const tsvd_pair_plan& plan, int count, double* u, double* v, double* sigma, int32_t* steps, hipStream_t stream);
+// R -= sigma u v^T for the pair in the plan.
+void tsvd_pair_deflate(const tsvd_pair_plan& plan, double* R, hipStream_t stream);

@@ -1,0 +1,322 @@
+// Leading singular pair of an fp64 matrix R [M][N] by repeated squaring of its Gram matrix.
+//
+// With A the Gram matrix on the shorter side (R^T R or R R^T, n = min(M, N)), A^(2^p) tends to the projector onto the
+// leading singular direction: p squarings are 2^p power steps.  On the close singular values of a random matrix (gaps of
+// 1e-2 .. 1e-4) that takes 10 .. 18 launches that fill the chip, where Lanczos bidiagonalisation takes 60 .. 100 steps
+// of four launches each, two of them a single workgroup: 76 steps at 44 us against 12 squarings at about 4 us on a
+// [512, 256] matrix.  Rounding: every squaring perturbs its matrix by a few units in the last place of its norm, so the
+// vector is off by rounding over the gap, as with any backward-stable method.
+//
+// The result is X s for the fixed start vector s of the Lanczos process, the projection of the start vector: so the
+// sign is the one with a positive product with the start vector, which is also the sign that process gives (its
+// tridiagonal matrix has positive off-diagonal entries, its leading eigenvector entries of one sign), and in a
+// degenerate leading space both return the same vector.
+#include "tsvd_pair.h"
+
+#include <algorithm>
+
+namespace {
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// Shorter side from which the squarings cost more than the Lanczos steps: a squaring is n^3 multiplications, a Lanczos
+// step two passes over R.
+constexpr int PAIR_MAX_N = 2048;
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// Workgroup (bi, bj), bi <= bj, of Y = c P P^T for P [rows][L]: T x T blocks of 16 x 16, the contraction split over four
+// wavefronts (v_mfma_f64_16x16x4), each 64 indices at a time; the block and its mirror image are stored.
+//
+// The order of the contraction index is free as long as both operands share it: lane group g of a wavefront takes the
+// indices 8 t + 2 g, 8 t + 2 g + 1 of its 64 with load t, so a load is 16 bytes per lane and touches 16 row segments of
+// 64 bytes.  Bound by the latency of the loads and of the chain of MFMAs (64 cycles each): small tiles on many
+// workgroups while n is small (n = 256: 136 workgroups of 16 MFMAs per wavefront), 32 x 32 tiles, which read half as much
+// per product, beyond.
+//
+// GRAM (first launch): P is R by its rows (TR = false) or columns (TR), any pitch; rows beyond n and indices beyond L read
+// as zero, c = 1.  Extra workgroups compute s = R v0 where the shorter side is the rows.
+// Otherwise P = X[step & 1], symmetric, zero beyond n, c = 1 / trace^2: the trace of every X from the second on is
+// sum lambda^2 / (sum lambda)^2 of the one before, 1 - 2 (lambda_2 / lambda_1)^(2^p) near the end.  Once that is within 1e-6 of
+// 1, X itself has the ratio squared, below 2.5e-13, and is the result (the residual |R^T u - sigma v| is that times the gap,
+// against the 1e-12 sigma of the Lanczos process): every workgroup of this and the later launches returns.
+template <int T, bool GRAM, bool TR>
+__global__ void __launch_bounds__(256)
+tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step) {
+    __shared__ __align__(16) double part[4][T * T * 256];
+    __shared__ double red[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
+    const int nb = p.np / (16 * T), tiles = nb * (nb + 1) / 2;
+    if constexpr (GRAM) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = -1;
+        if ((int)blockIdx.x >= tiles) {                     // s = R v0, a wavefront per row
+            const int m = ((int)blockIdx.x - tiles) * 4 + wave;
+            if (m < p.M) {
+                double a = 0.0;
+                for (int k = lane; k < p.N; k += 64) a += R[(size_t)m * p.N + k] * p.v0[k];
+                a = wave_sum(a);
+                if (lane == 0) p.s[m] = a;
+            }
+            return;
+        }
+    }
+    int bj = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+    while (bj * (bj + 1) / 2 > (int)blockIdx.x) --bj;
+    while ((bj + 1) * (bj + 2) / 2 <= (int)blockIdx.x) ++bj;
+    const int bi = (int)blockIdx.x - bj * (bj + 1) / 2;
+
+    const double* P = GRAM ? R : p.X[step & 1];
+    const int L = GRAM ? (TR ? p.M : p.N) : p.np;
+    f64x4 acc[T][T];
+#pragma unroll
+    for (int a = 0; a < T; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const double* arow[T];
+    const double* brow[T];
+#pragma unroll
+    for (int q = 0; q < T; ++q) {
+        const int ra = (bi * T + q) * 16 + i, rb = (bj * T + q) * 16 + i;
+        arow[q] = GRAM ? P + (TR ? (size_t)min(ra, p.n - 1) : (size_t)min(ra, p.n - 1) * p.N) : P + (size_t)ra * p.np;
+        brow[q] = GRAM ? P + (TR ? (size_t)min(rb, p.n - 1) : (size_t)min(rb, p.n - 1) * p.N) : P + (size_t)rb * p.np;
+    }
+    auto load = [&](const double* row, int k) -> f64x2 {     // P[row][k], P[row][k + 1]; GRAM: indices clamped
+        if constexpr (!GRAM) return *reinterpret_cast<const f64x2*>(row + k);
+        const int k0 = min(k, L - 1), k1 = min(k + 1, L - 1);
+        return TR ? f64x2{row[(size_t)k0 * p.N], row[(size_t)k1 * p.N]} : f64x2{row[k0], row[k1]};
+    };
+    // everything a wavefront needs is requested before anything is waited for
+    double tr = 0.0;
+    int done = -1;
+    if constexpr (!GRAM) {
+        done = p.state->last;
+        tr = P[(size_t)min((int)threadIdx.x, p.np - 1) * (p.np + 1)];
+    }
+    for (int k0 = wave * 64; k0 < L; k0 += 256) {
+        f64x2 a[T][8], b[T][8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+                a[q][t] = load(arow[q], k0 + 8 * t + 2 * g);
+                b[q][t] = load(brow[q], k0 + 8 * t + 2 * g);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (GRAM) {                                // rows beyond n and indices beyond L count as zero
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int q = 0; q < T; ++q)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const bool in = k0 + 8 * t + 2 * g + e < L;
+                        if (!in || (bi * T + q) * 16 + i >= p.n) a[q][t][e] = 0.0;
+                        if (!in || (bj * T + q) * 16 + i >= p.n) b[q][t][e] = 0.0;
+                    }
+        } else if (done >= 0) {
+            break;
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int qa = 0; qa < T; ++qa)
+#pragma unroll
+                    for (int qb = 0; qb < T; ++qb)
+                        acc[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[qa][t][e], b[qb][t][e], acc[qa][qb], 0, 0, 0);
+    }
+    double c = 1.0;
+    if constexpr (!GRAM) {
+        if (done >= 0) return;
+        if ((int)threadIdx.x >= p.np) tr = 0.0;
+        for (int d = threadIdx.x + 256; d < p.np; d += 256) tr += P[(size_t)d * (p.np + 1)];
+        tr = wave_sum(tr);
+        if (lane == 0) red[wave] = tr;
+    }
+    // result lane (i, g): column i, rows g + 4 v
+#pragma unroll
+    for (int qa = 0; qa < T; ++qa)
+#pragma unroll
+        for (int qb = 0; qb < T; ++qb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[wave][(qa * T + qb) * 256 + (g + 4 * v) * 16 + i] = acc[qa][qb][v];
+    __syncthreads();
+    if constexpr (!GRAM) {
+        const double trace = (red[0] + red[1]) + (red[2] + red[3]);
+        if (step > 0 && fabs(1.0 - trace) < 1e-6) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = step;
+            return;
+        }
+        c = trace > 0.0 ? 1.0 / (trace * trace) : 0.0;
+    }
+    double* Y = p.X[GRAM ? 0 : (step + 1) & 1];
+    const int r = threadIdx.x >> 4, cc = threadIdx.x & 15;
+#pragma unroll
+    for (int qa = 0; qa < T; ++qa)
+#pragma unroll
+        for (int qb = 0; qb < T; ++qb) {
+            const int at = (qa * T + qb) * 256;
+            const int row = (bi * T + qa) * 16, col = (bj * T + qb) * 16;
+            auto sum = [&](int e) { return ((part[0][at + e] + part[1][at + e]) + (part[2][at + e] + part[3][at + e])) * c; };
+            Y[(size_t)(row + r) * p.np + col + cc] = sum(r * 16 + cc);
+            if (bi != bj) Y[(size_t)(col + r) * p.np + row + cc] = sum(cc * 16 + r);
+        }
+}
+
+// The fixed start vector of the process, with no special symmetry.
+__global__ void __launch_bounds__(256)
+tsvd_pair_start_kernel(double* __restrict__ v0, int N, tsvd_pair_state* state) {
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < N) v0[k] = 1.0 + 0.5 * sin(1.0 + 0.7 * (double)k);
+    if (k == 0) {
+        state->last = -1;
+        state->missed = 0;
+    }
+}
+
+// The vector of the shorter side, a wavefront per row: X s.
+__global__ void __launch_bounds__(256)
+tsvd_pair_short_kernel(tsvd_pair_plan p, int count) {
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int last = p.state->last;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && last < 0) ++p.state->missed;
+    if (row >= p.n) return;
+    const double* X = p.X[(last >= 0 ? last : count) & 1] + (size_t)row * p.np;
+    double a = 0.0;
+    for (int k = lane; k < p.n; k += 64) a += X[k] * p.s[k];
+    a = wave_sum(a);
+    if (lane == 0) (p.N <= p.M ? p.v : p.u)[row] = a;
+}
+
+// The vector of the longer side.  N <= M: u = R v, a wavefront per row.  M < N: v = R^T u, 64 columns per workgroup, the
+// rows in four phases.
+__global__ void __launch_bounds__(256)
+tsvd_pair_long_kernel(tsvd_pair_plan p, const double* __restrict__ R) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (p.N <= p.M) {
+        const int m = blockIdx.x * 4 + wave;
+        if (m >= p.M) return;
+        const double* row = R + (size_t)m * p.N;
+        double a = 0.0;
+        for (int k = lane; k < p.N; k += 64) a += row[k] * p.v[k];
+        a = wave_sum(a);
+        if (lane == 0) p.u[m] = a;
+        return;
+    }
+    __shared__ double red[4][64];
+    const int col = blockIdx.x * 64 + lane;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    if (col < p.N) {
+        int m = wave;
+        for (; m + 12 < p.M; m += 16)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] += R[(size_t)(m + 4 * t) * p.N + col] * p.u[m + 4 * t];
+        for (; m < p.M; m += 4) a[0] += R[(size_t)m * p.N + col] * p.u[m];
+    }
+    red[wave][lane] = (a[0] + a[1]) + (a[2] + a[3]);
+    __syncthreads();
+    if (wave == 0 && col < p.N) p.v[col] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+}
+
+// Sum of squares over the workgroup (256 threads), in every thread.
+__device__ __forceinline__ double norm2(const double* x, int len, double* red) {
+    double a = 0.0;
+    for (int k = threadIdx.x; k < len; k += 256) a += x[k] * x[k];
+    a = wave_sum(a);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Unit vectors and the singular value: |u| / |v| of the raw pair is sigma (u = R v) or 1 / sigma (v = R^T u).
+__global__ void __launch_bounds__(256)
+tsvd_pair_normalise_kernel(tsvd_pair_plan p, int count, double* __restrict__ u, double* __restrict__ v, double* __restrict__ sigma,
+                           int* __restrict__ steps) {
+    __shared__ double red[4];
+    const double un = sqrt(norm2(p.u, p.M, red)), vn = sqrt(norm2(p.v, p.N, red));
+    const double ui = un > 0.0 ? 1.0 / un : 0.0, vi = vn > 0.0 ? 1.0 / vn : 0.0;
+    for (int k = threadIdx.x; k < p.M; k += 256) u[k] = p.u[k] * ui;
+    for (int k = threadIdx.x; k < p.N; k += 256) v[k] = p.v[k] * vi;
+    if (threadIdx.x == 0) {
+        sigma[0] = p.N <= p.M ? un * vi : vn * ui;
+        if (steps) steps[0] = p.state->last >= 0 ? p.state->last : count;
+    }
+}
+
+// R[m][k] -= sigma u[m] v[k] with unit u and v: u_raw v_raw / |the shorter side's raw vector|^2.  A workgroup per row.
+__global__ void __launch_bounds__(256)
+tsvd_pair_deflate_kernel(tsvd_pair_plan p, double* __restrict__ R) {
+    __shared__ double red[4];
+    const double n2 = p.N <= p.M ? norm2(p.v, p.N, red) : norm2(p.u, p.M, red);
+    const double f = n2 > 0.0 ? p.u[blockIdx.x] / n2 : 0.0;
+    double* row = R + (size_t)blockIdx.x * p.N;
+    for (int k = threadIdx.x; k < p.N; k += 256) row[k] -= f * p.v[k];
+}
+
+}  // namespace
+
+bool tsvd_pair_squares(int64_t M, int64_t N) { return std::min(M, N) <= PAIR_MAX_N; }
+
+size_t tsvd_pair_bytes(int64_t M, int64_t N) {
+    const size_t np = (size_t)(std::min(M, N) + 63) / 64 * 64;
+    return 2 * round256(np * np * 8) + 3 * round256((size_t)N * 8) + 2 * round256((size_t)M * 8) + 256;
+}
+
+void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* p, hipStream_t stream) {
+    uint8_t* at = static_cast<uint8_t*>(mem);
+    auto take = [&](size_t doubles) {
+        double* r = reinterpret_cast<double*>(at);
+        at += round256(doubles * 8);
+        return r;
+    };
+    p->M = (int)M; p->N = (int)N; p->n = (int)std::min(M, N); p->np = (p->n + 63) / 64 * 64;
+    p->X[0] = take((size_t)p->np * p->np);
+    p->X[1] = take((size_t)p->np * p->np);
+    p->v0 = take((size_t)N);
+    p->s = N <= M ? p->v0 : take((size_t)M);
+    p->u = take((size_t)M);
+    p->v = take((size_t)N);
+    p->state = reinterpret_cast<tsvd_pair_state*>(at);
+    hipLaunchKernelGGL(tsvd_pair_start_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, p->v0, p->N, p->state);
+}
+
+void tsvd_pair_square(const tsvd_pair_plan& p, const double* R, int from, int to, hipStream_t stream) {
+    const bool big = p.np > 384;
+    const int nb = p.np / (big ? 32 : 16);
+    const unsigned tiles = (unsigned)(nb * (nb + 1) / 2);
+    if (from == 0) {
+        const bool cols = p.N <= p.M;
+        const unsigned grid = tiles + (cols ? 0u : (unsigned)((p.M + 3) / 4));
+        if (big && cols) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, true, true>), dim3(grid), dim3(256), 0, stream, p, R, 0);
+        else if (big) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, true, false>), dim3(grid), dim3(256), 0, stream, p, R, 0);
+        else if (cols) hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, true>), dim3(grid), dim3(256), 0, stream, p, R, 0);
+        else hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, false>), dim3(grid), dim3(256), 0, stream, p, R, 0);
+    }
+    for (int step = from; step < to; ++step) {
+        if (big) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, false, false>), dim3(tiles), dim3(256), 0, stream, p, R, step);
+        else hipLaunchKernelGGL((tsvd_pair_square_kernel<1, false, false>), dim3(tiles), dim3(256), 0, stream, p, R, step);
+    }
+}
+
+void tsvd_pair_vectors(const tsvd_pair_plan& p, const double* R, int count, hipStream_t stream) {
+    hipLaunchKernelGGL(tsvd_pair_short_kernel, dim3((unsigned)((p.n + 3) / 4)), dim3(256), 0, stream, p, count);
+    const unsigned grid = p.N <= p.M ? (unsigned)((p.M + 3) / 4) : (unsigned)((p.N + 63) / 64);
+    hipLaunchKernelGGL(tsvd_pair_long_kernel, dim3(grid), dim3(256), 0, stream, p, R);
+}
+
+void tsvd_pair_normalise(const tsvd_pair_plan& p, int count, double* u, double* v, double* sigma, int32_t* steps, hipStream_t stream) {
+    hipLaunchKernelGGL(tsvd_pair_normalise_kernel, dim3(1), dim3(256), 0, stream, p, count, u, v, sigma, steps);
+}
+
+void tsvd_pair_deflate(const tsvd_pair_plan& p, double* R, hipStream_t stream) {
+    hipLaunchKernelGGL(tsvd_pair_deflate_kernel, dim3((unsigned)p.M), dim3(256), 0, stream, p, R);
+}

@@ -1,17 +1,20 @@
 // Direct transition W -> (U, S, V) on the GPU (paper, section "Direct Transition Algorithm to
 // TSVD form": Algorithm 1, Eq. (3), Algorithm 2).  The algorithm runs once per layer and every
 // step is small at the paper's matrix sizes ([512, 256] in its random-matrix study), so the steps
-// are bound by launch and memory latency, not by arithmetic: each is one launch, the two
-// iterative ones (power iteration, conjugate gradients) are single-workgroup kernels that keep
-// their vectors in LDS and never return to the host inside the iteration.  Everything is fp64:
-// the decisions of Algorithm 1 compare sums against cos(theta) and must not depend on fp32 noise.
+// are bound by launch and memory latency, not by arithmetic: each is one launch.  The leading
+// singular pair comes from squarings of the Gram matrix (tsvd_pair.hip), beyond its sizes from
+// Lanczos steps.  Everything is fp64: the decisions of Algorithm 1 compare sums against cos(theta)
+// and must not depend on fp32 noise.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "../../include/tsvd_transition.h"
+#include "tsvd_pair.h"
 
 #define TERN_MAX_N 8192
 #define FIT_MAX_K 2048
@@ -33,93 +36,170 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
     return r;
 }
 
+// The value of lane ^ J of the wavefront, by cross-lane moves of the vector ALU (about ten cycles; a shuffle through
+// the LDS crossbar takes over a hundred).
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor32(uint32_t x) {
+    if constexpr (J == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);            // quad_perm 1,0,3,2
+    else if constexpr (J == 2) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);       // quad_perm 2,3,0,1
+    else if constexpr (J == 4) return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);   // ^ 7, ^ 3
+    else if constexpr (J == 8) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);      // row_ror 8
+    else if constexpr (J == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (threadIdx.x & 16) ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (threadIdx.x & 32) ? r[0] : r[1];
+    }
+}
+template <int J>
+__device__ __forceinline__ double lane_xor(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)lane_xor32<J>((uint32_t)b) | ((uint64_t)lane_xor32<J>((uint32_t)(b >> 32)) << 32));
+}
+
+// Sum over a wavefront, in every lane.
+__device__ __forceinline__ double wave_sum(double v) {
+    v += lane_xor<32>(v);
+    v += lane_xor<16>(v);
+    v += lane_xor<8>(v);
+    v += lane_xor<4>(v);
+    v += lane_xor<2>(v);
+    v += lane_xor<1>(v);
+    return v;
+}
+
 // ---- Algorithm 1: one workgroup per vector ---------------------------------------------------
-// LDS: magnitudes [npow2] fp64, sorted largest first by a bitonic network (padding sorts last),
-// then prefix sums in the order of the sorted list: thread t adds its chunk of npow2 / 256
-// consecutive entries, thread 0 turns the 256 chunk sums into offsets, every thread walks its
-// chunk again and reports the smallest q whose cosine reaches cos(theta).
-__global__ void __launch_bounds__(256)
-tsvd_ternarize_kernel(const double* __restrict__ x, long long ldx, int n, int npow2, double cos_theta,
-                      int8_t* __restrict__ t, long long ldt, int* __restrict__ status) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    double* keys = reinterpret_cast<double*>(smem);            // [npow2]
-    double* red = keys + npow2;                                 // [256]
-    double* offs = red + 256;                                   // [256]
+// The magnitudes stay in registers, E per thread (position e * threads + thread), and are sorted largest first by a
+// bitonic network: partners less than a wavefront apart meet through cross-lane moves, those in other wavefronts through
+// LDS (6 of the 45 stages at 512 entries), those of one thread in its registers.  Then prefix sums in sorted order (wave
+// scans and the totals of the wavefronts before), and the smallest q whose cosine reaches cos(theta).  Padding
+// (-1) sorts last.  (With the whole list in LDS and 256 threads, every stage behind a barrier, 512 entries took 23 us.)
+struct ternarize_job {
+    const double* x; long long ldx; int n;
+    int8_t* t; long long ldt;
+    int* status;             // [rows], or null
+    int* failed;             // counts the vectors without a neighbour, or null
+};
+struct ternarize_args {
+    ternarize_job job[2];    // blockIdx.y
+    int npow2;
+    double cos_theta;
+};
+#define TERN_THREADS 1024
+template <int E>
+__global__ void __launch_bounds__(TERN_THREADS)
+tsvd_ternarize_kernel(ternarize_args p) {
+    __shared__ double keys[E > 1 ? TERN_THREADS * 2 : TERN_THREADS];
+    __shared__ double tot[2][TERN_THREADS / 64];
     __shared__ int qmin;
-    const int tid = threadIdx.x;
-    const double* xr = x + (size_t)blockIdx.x * ldx;
-    int8_t* tr = t + (size_t)blockIdx.x * ldt;
+    __shared__ double threshold;
+    const ternarize_job& job = p.job[blockIdx.y];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, T = blockDim.x, nw = T >> 6, n = job.n;
+    const double* xr = job.x + (size_t)blockIdx.x * job.ldx;
+    int8_t* tr = job.t + (size_t)blockIdx.x * job.ldt;
     if (tid == 0) qmin = 0x7FFFFFFF;
-    double ss = 0.0;
-    for (int i = tid; i < npow2; i += 256) {
-        const double v = i < n ? xr[i] : 0.0;
-        keys[i] = i < n ? fabs(v) : -1.0;
+    double a[E], ss = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int s = e * T + tid;
+        const double v = s < n ? xr[s] : 0.0;
+        a[e] = s < n ? fabs(v) : -1.0;
         ss += v * v;
     }
-    const double length = sqrt(block_sum256(ss, red));
-    for (int k = 2; k <= npow2; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = tid; i < npow2; i += 256) {
-                const int l = i ^ j;
-                if (l > i) {
-                    const double a = keys[i], b = keys[l];
-                    const bool largest_first = (i & k) == 0;
-                    if (largest_first ? a < b : a > b) {
-                        keys[i] = b;
-                        keys[l] = a;
+    ss = wave_sum(ss);
+    if (lane == 0) tot[0][wave] = ss;
+    __syncthreads();
+    double length = 0.0;
+    for (int w = 0; w < nw; ++w) length += tot[0][w];
+    length = sqrt(length);
+    int flip = 0;
+    auto exchange = [&](int e, int k, int j, double b) {                            // position e T + tid meets the one j away
+        const int s = e * T + tid;
+        a[e] = (((s & k) == 0) == ((s & j) == 0)) ? fmax(a[e], b) : fmin(a[e], b);
+    };
+    for (int k = 2; k <= p.npow2; k <<= 1) {
+        for (int j = k >> 1; j >= 64; j >>= 1) {
+            if (j >= T) {
+#pragma unroll
+                for (int h = E / 2; h > 0; h >>= 1)
+                    if (j == h * T) {
+#pragma unroll
+                        for (int e = 0; e < E; ++e)
+                            if (!(e & h)) {
+                                const bool first = ((e * T + tid) & k) == 0;        // largest first
+                                const double hi = fmax(a[e], a[e | h]), lo = fmin(a[e], a[e | h]);
+                                a[e] = first ? hi : lo;
+                                a[e | h] = first ? lo : hi;
+                            }
                     }
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    double* buf = keys + (E > 1 ? flip * TERN_THREADS : 0);
+                    if (E == 1) __syncthreads();                                    // (the reads of the stage before)
+                    buf[tid] = a[e];
+                    __syncthreads();
+                    exchange(e, k, j, buf[tid ^ j]);
+                    flip ^= 1;
                 }
             }
-            __syncthreads();
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if (k >= 64) exchange(e, k, 32, lane_xor<32>(a[e]));
+            if (k >= 32) exchange(e, k, 16, lane_xor<16>(a[e]));
+            if (k >= 16) exchange(e, k, 8, lane_xor<8>(a[e]));
+            if (k >= 8) exchange(e, k, 4, lane_xor<4>(a[e]));
+            if (k >= 4) exchange(e, k, 2, lane_xor<2>(a[e]));
+            exchange(e, k, 1, lane_xor<1>(a[e]));
         }
     }
-    const int chunk = npow2 >= 256 ? npow2 / 256 : 1;
-    const int first = tid * chunk;
-    double mine = 0.0;
-    if (first < npow2)
-        for (int e = 0; e < chunk; ++e) mine += fmax(keys[first + e], 0.0);
-    red[tid] = mine;
-    __syncthreads();
-    if (tid == 0) {
-        double run = 0.0;
-        for (int c = 0; c < 256; ++c) {
-            offs[c] = run;
-            run += red[c];
+    double carry = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        double run = fmax(a[e], 0.0);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double up = __shfl_up(run, o, 64);
+            if (lane >= o) run += up;
         }
-    }
-    __syncthreads();
-    if (first < npow2 && length > 0.0) {
-        double run = offs[tid];
-        for (int e = 0; e < chunk; ++e) {
-            const double key = keys[first + e];
-            if (key < 0.0) break;                               // padding
-            run += key;
-            const int q = first + e + 1;
-            if (run / (sqrt((double)q) * length) >= cos_theta) {
-                atomicMin(&qmin, q);
-                break;
-            }
+        if (lane == 63) tot[(e + 1) & 1][wave] = run;
+        __syncthreads();
+        double before = carry;
+        for (int w = 0; w < nw; ++w) {
+            if (w < wave) before += tot[(e + 1) & 1][w];
+            carry += tot[(e + 1) & 1][w];
         }
+        run += before;
+        const int q = e * T + tid + 1;
+        if (a[e] >= 0.0 && length > 0.0 && run / (sqrt((double)q) * length) >= p.cos_theta) atomicMin(&qmin, q);
     }
     __syncthreads();
     const int q = qmin;
     const bool found = q != 0x7FFFFFFF;
-    const double threshold = found ? keys[q - 1] : 0.0;
-    for (int i = tid; i < n; i += 256) {
-        const double v = xr[i];
-        tr[i] = (found && fabs(v) >= threshold) ? (v >= 0.0 ? 1 : -1) : 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * T + tid + 1 == q) threshold = a[e];
+    __syncthreads();
+    const double th = threshold;
+    for (int s = tid; s < n; s += T) {
+        const double v = xr[s];
+        tr[s] = (found && fabs(v) >= th) ? (v >= 0.0 ? 1 : -1) : 0;
     }
-    if (tid == 0) status[blockIdx.x] = found ? 0 : 1;
+    if (tid == 0) {
+        if (job.status) job.status[blockIdx.x] = found ? 0 : 1;
+        if (job.failed && !found) atomicAdd(job.failed, 1);
+    }
 }
 
 // ---- Eq. (3), left side: G[k][l] = (sum_m U[m][k] U[m][l]) (sum_n V[k][n] V[l][n]) ------------------
 // One thread per (k, l), l fastest (U[m][l] is then read along rows; V[l][n] is strided but V is
 // small and cached).  Integer sums, exact.
-// only_row >= 0: just row and column `only_row` (the component appended last; grid.y = 1).
 __global__ void __launch_bounds__(256)
 tsvd_gram_kernel(const int8_t* __restrict__ U, long long ldu, const int8_t* __restrict__ V, int M, int K, int N,
-                 double* __restrict__ G, long long ldg, int only_row) {
-    const int l = blockIdx.x * 256 + threadIdx.x, k = only_row >= 0 ? only_row : (int)blockIdx.y;
+                 double* __restrict__ G, long long ldg) {
+    const int l = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
     if (l >= K) return;
     int uu = 0, vv = 0;
     for (int m = 0; m < M; ++m) uu += (int)U[(size_t)m * ldu + k] * (int)U[(size_t)m * ldu + l];
@@ -127,15 +207,14 @@ tsvd_gram_kernel(const int8_t* __restrict__ U, long long ldu, const int8_t* __re
     const int8_t* vl = V + (size_t)l * N;
     for (int n = 0; n < N; ++n) vv += (int)vk[n] * (int)vl[n];
     G[(size_t)k * ldg + l] = (double)uu * (double)vv;
-    if (only_row >= 0) G[(size_t)l * ldg + k] = (double)uu * (double)vv;
 }
 
 // ---- Eq. (3), right side: d[k] = sum_m sum_n U[m][k] W[m][n] V[k][n]; one workgroup per k ----------
 __global__ void __launch_bounds__(256)
 tsvd_rhs_kernel(const int8_t* __restrict__ U, long long ldu, const int8_t* __restrict__ V, const double* __restrict__ W, int M,
-                int N, double* __restrict__ d, int k_first) {
+                int N, double* __restrict__ d) {
     __shared__ double red[256];
-    const int k = k_first + blockIdx.x;
+    const int k = blockIdx.x;
     const int8_t* vk = V + (size_t)k * N;
     double acc = 0.0;
     for (int m = 0; m < M; ++m) {
@@ -150,90 +229,269 @@ tsvd_rhs_kernel(const int8_t* __restrict__ U, long long ldu, const int8_t* __res
     if (threadIdx.x == 0) d[k] = total;
 }
 
+// ---- Eq. (3) inside Algorithm 2: what the components K0 + blockIdx.y (of K by now) add to the system ---------------
+// A wavefront each: idx < K: the entry (idx, new) of the Gram matrix and its mirror, four codes per v_dot4; then, for
+// every row m of W, U[m][new] sum_n W[m][n] V[new][n] into part[new - K0][m] (summed by the solver).  Ut [rank][mp] and
+// V [rank][np] hold one component per row, zero beyond M and N (pitches are multiples of 16).
+__global__ void __launch_bounds__(256)
+tsvd_system_kernel(const int8_t* __restrict__ Ut, int mp, const int8_t* __restrict__ V, int np, const double* __restrict__ W, int M, int N,
+                   int K0, int K, double* __restrict__ G, long long ldg, double* __restrict__ part) {
+    const int idx = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, r = K0 + blockIdx.y;
+    if (idx < K) {
+        auto dot = [&](const int8_t* a, const int8_t* b, int len) {
+            int v = 0;
+            for (int k = lane * 4; k < len; k += 256)
+                v = __builtin_amdgcn_sdot4(*reinterpret_cast<const int*>(a + k), *reinterpret_cast<const int*>(b + k), v, false);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            return v;
+        };
+        const int uu = dot(Ut + (size_t)idx * mp, Ut + (size_t)r * mp, mp), vv = dot(V + (size_t)idx * np, V + (size_t)r * np, np);
+        if (lane == 0) G[(size_t)r * ldg + idx] = G[(size_t)idx * ldg + r] = (double)uu * (double)vv;
+    } else if (idx - K < M) {
+        const int m = idx - K, um = Ut[(size_t)r * mp + m];
+        double a = 0.0;
+        if (um != 0) {
+            const double* wr = W + (size_t)m * N;
+            const int8_t* vr = V + (size_t)r * np;
+            for (int n = lane; n < N; n += 64) a += (double)vr[n] * wr[n];
+            a = wave_sum(a);
+        }
+        if (lane == 0) part[(size_t)blockIdx.y * M + m] = um > 0 ? a : -a;
+    }
+}
+
 // ---- Eq. (3), the solve: conjugate gradients with diagonal scaling, one workgroup -------------
 // G s = d for the symmetric positive semi-definite G of the normal equations, started from s = 0,
 // so for a singular G the iterates stay in its range and converge to the minimum-norm solution
-// (the pseudo-inverse solution).  Vectors live in LDS; G (K^2 fp64) is re-read from L2 each
-// iteration.  Stops at |r| <= 1e-13 |d| or after 20 K iterations.
-__global__ void __launch_bounds__(1024)
-// warm: start from the values found in s instead of zero (any least-squares solution gives the
-// same residual; the loop of Algorithm 2 starts from the previous scales).
-tsvd_pcg_kernel(const double* __restrict__ G, long long ldg, const double* __restrict__ d, int K, double* __restrict__ s, int warm,
-                int* __restrict__ iters) {
-    extern __shared__ __align__(16) unsigned char smem[];
+// (the pseudo-inverse solution).  Stops at |r| <= 1e-13 |d| or after 20 K iterations.
+// s0: start from these `fresh` values (and zeros) instead of zero (any least-squares solution gives the
+// same residual; the loop of Algorithm 2 starts from the previous scales), or null.  The entries of d from
+// `fresh` on are first summed from `part` [K - fresh][M].
+//
+// An iteration waits for barriers and LDS latency, not for arithmetic: a thread owns a row (its entries of every vector;
+// only the direction is shared), rows are read as columns (G is symmetric, so consecutive threads read consecutive
+// words), the two sums of an update go through one reduction (wave sums, then every thread adds the wavefronts' totals),
+// and a system of up to PCG_LDS_K unknowns runs with G in LDS on as few wavefronts as it has rows.  Larger systems
+// re-read G from L2 on 1024 threads, the columns of a row split over 1024 / K groups of threads.
+#define PCG_LDS_K 96
+__device__ __forceinline__ void solve_pcg(unsigned char* smem, const double* __restrict__ G, long long ldg, double* __restrict__ d, int K,
+                                          double* __restrict__ s, const double* __restrict__ s0, int* __restrict__ iters,
+                                          const double* __restrict__ part, int fresh, int M) {
     double* xs = reinterpret_cast<double*>(smem);   // [K] solution
     double* r = xs + K;                             // residual
     double* p = r + K;                              // direction
     double* q = p + K;                              // G p
     double* dg = q + K;                             // 1 / diagonal (1 where the diagonal is 0)
-    double* red = dg + K;                           // [1024]
-    const int tid = threadIdx.x;
-    auto dot = [&](auto f) {                        // sum_k f(k), fixed order, result in every thread
-        double v = 0.0;
-        for (int k = tid; k < K; k += 1024) v += f(k);
-        red[tid] = v;
-        __syncthreads();
-        for (int st = 512; st > 0; st >>= 1) {
-            if (tid < st) red[tid] += red[tid + st];
-            __syncthreads();
+    double* sub = dg + K;                           // [1024] partial products of a row
+    double* Gl = sub + 1024;                        // [K][K], K <= PCG_LDS_K
+    __shared__ double red[2][2][16];
+    const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = T >> 6;
+    int flip = 0;
+    auto sum2 = [&](double a, double b, double& sa, double& sb) {      // sums over the workgroup, fixed order, in every thread
+        a = wave_sum(a);
+        b = wave_sum(b);
+        if (lane == 0) {
+            red[flip][0][wave] = a;
+            red[flip][1][wave] = b;
         }
-        const double out = red[0];
         __syncthreads();
-        return out;
+        sa = sb = 0.0;
+        for (int w = 0; w < nw; ++w) {
+            sa += red[flip][0][w];
+            sb += red[flip][1][w];
+        }
+        flip ^= 1;
     };
-    const int wave = tid >> 6, lane = tid & 63;
-    auto matvec = [&](const double* in, double* out) {          // out = G in: one wavefront per row, lanes along the row
-        for (int k = wave; k < K; k += 16) {
-            const double* row = G + (size_t)k * ldg;
+    double unused;
+    for (int k = fresh; k < K; ++k) {
+        double a = 0.0, total;
+        for (int m = tid; m < M; m += T) a += part[(size_t)(k - fresh) * M + m];
+        sum2(a, 0.0, total, unused);
+        if (tid == 0) d[k] = total;
+    }
+    const bool in_lds = K <= PCG_LDS_K;
+    if (in_lds)
+        for (int e = tid; e < K * K; e += T) Gl[e] = G[(size_t)(e / K) * ldg + e % K];
+    const double* Gm = in_lds ? Gl : G;
+    const size_t ld = in_lds ? (size_t)K : (size_t)ldg;
+    const int rows = (K + 63) & ~63, groups = rows >= T ? 1 : T / rows, grp = tid / rows;
+    auto matvec = [&](const double* in, double* out) {                 // out = G in (owner threads only read their entries of out)
+        if (groups == 1) {
+            for (int k = tid; k < K; k += T) {
+                double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
+                int l = 0;
+                for (; l + 3 < K; l += 4) {
+                    v0 += Gm[(size_t)l * ld + k] * in[l];
+                    v1 += Gm[(size_t)(l + 1) * ld + k] * in[l + 1];
+                    v2 += Gm[(size_t)(l + 2) * ld + k] * in[l + 2];
+                    v3 += Gm[(size_t)(l + 3) * ld + k] * in[l + 3];
+                }
+                for (; l < K; ++l) v0 += Gm[(size_t)l * ld + k] * in[l];
+                out[k] = (v0 + v1) + (v2 + v3);
+            }
+            return;
+        }
+        const int k = tid - grp * rows;
+        if (grp < groups && k < K) {
+            const int l0 = K * grp / groups, l1 = K * (grp + 1) / groups;
+            double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
+            int l = l0;
+            for (; l + 3 < l1; l += 4) {
+                v0 += Gm[(size_t)l * ld + k] * in[l];
+                v1 += Gm[(size_t)(l + 1) * ld + k] * in[l + 1];
+                v2 += Gm[(size_t)(l + 2) * ld + k] * in[l + 2];
+                v3 += Gm[(size_t)(l + 3) * ld + k] * in[l + 3];
+            }
+            for (; l < l1; ++l) v0 += Gm[(size_t)l * ld + k] * in[l];
+            sub[grp * rows + k] = (v0 + v1) + (v2 + v3);
+        }
+        __syncthreads();
+        for (int i = tid; i < K; i += T) {                              // (K < T here)
             double v = 0.0;
-            for (int l = lane; l < K; l += 64) v += row[l] * in[l];
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0) out[k] = v;
+            for (int gq = 0; gq < groups; ++gq) v += sub[gq * rows + i];
+            out[i] = v;
         }
-        __syncthreads();
     };
-    for (int k = tid; k < K; k += 1024) {
-        const double g = G[(size_t)k * ldg + k];
+    for (int k = tid; k < K; k += T) xs[k] = s0 && k < fresh ? s0[k] : 0.0;
+    __syncthreads();                                                   // (d, G and xs complete)
+    if (s0) matvec(xs, q);
+    double a = 0.0, b = 0.0, dd, rz, rr;
+    for (int k = tid; k < K; k += T) {
+        const double g = Gm[(size_t)k * ld + k], dk = d[k];
         dg[k] = g > 0.0 ? 1.0 / g : 1.0;
-        xs[k] = warm ? s[k] : 0.0;
-    }
-    __syncthreads();
-    if (warm) matvec(xs, q);
-    for (int k = tid; k < K; k += 1024) {
-        r[k] = d[k] - (warm ? q[k] : 0.0);
+        r[k] = dk - (s0 ? q[k] : 0.0);
         p[k] = r[k] * dg[k];
+        a += dk * dk;
+        b += r[k] * r[k] * dg[k];
     }
-    __syncthreads();
-    const double dd = dot([&](int k) { return d[k] * d[k]; });
-    double rz = dot([&](int k) { return r[k] * r[k] * dg[k]; });
+    sum2(a, b, dd, rz);
+    a = 0.0;
+    for (int k = tid; k < K; k += T) a += r[k] * r[k];
+    sum2(a, 0.0, rr, unused);
     int it = 0;
-    bool converged = !(dd > 0.0);
+    bool converged = !(dd > 0.0) || rr <= 1e-26 * dd;                  // (a warm start may already fit)
     const int max_it = 20 * K + 20;
-    if (dd > 0.0 && dot([&](int k) { return r[k] * r[k]; }) <= 1e-26 * dd) converged = true;    // (a warm start may already fit)
     while (!converged && it < max_it) {
         matvec(p, q);
-        const double pq = dot([&](int k) { return p[k] * q[k]; });
-        if (!(pq > 0.0)) break;                                 // direction in the null space: done
+        a = 0.0;
+        for (int k = tid; k < K; k += T) a += p[k] * q[k];
+        double pq;
+        sum2(a, 0.0, pq, unused);
+        if (!(pq > 0.0)) break;                                        // direction in the null space: done
         const double alpha = rz / pq;
-        for (int k = tid; k < K; k += 1024) {
+        a = b = 0.0;
+        for (int k = tid; k < K; k += T) {
             xs[k] += alpha * p[k];
-            r[k] -= alpha * q[k];
+            const double rk = r[k] - alpha * q[k];
+            r[k] = rk;
+            a += rk * rk;
+            b += rk * rk * dg[k];
         }
-        __syncthreads();
-        const double rr = dot([&](int k) { return r[k] * r[k]; });
+        double rz_new;
+        sum2(a, b, rr, rz_new);
         ++it;
         if (rr <= 1e-26 * dd) {
             converged = true;
             break;
         }
-        const double rz_new = dot([&](int k) { return r[k] * r[k] * dg[k]; });
         const double beta = rz_new / rz;
         rz = rz_new;
-        for (int k = tid; k < K; k += 1024) p[k] = r[k] * dg[k] + beta * p[k];
+        for (int k = tid; k < K; k += T) p[k] = r[k] * dg[k] + beta * p[k];
         __syncthreads();
     }
-    for (int k = tid; k < K; k += 1024) s[k] = xs[k];
+    for (int k = tid; k < K; k += T) s[k] = xs[k];
     if (tid == 0 && iters) iters[0] = converged ? it : -it;
+}
+__global__ void __launch_bounds__(1024)
+tsvd_pcg_kernel(const double* __restrict__ G, long long ldg, double* __restrict__ d, int K, double* __restrict__ s,
+                const double* __restrict__ s0, int* __restrict__ iters, const double* __restrict__ part, int fresh, int M) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    solve_pcg(smem, G, ldg, d, K, s, s0, iters, part, fresh, M);
+}
+
+// ---- Eq. (3), the solve while Algorithm 2 has at most 64 components: one row of the Cholesky factor more per component ----
+// G = L L^T grows by a row and a column per component, and so do L (a forward substitution) and y = L^-1 d (one entry);
+// only the back substitution L^T s = y runs over everything.  One wavefront, a row per lane: a step of either
+// substitution is a lane broadcast, a multiplication and a multiply-add on an entry of L that was read ahead, so 32
+// components take 64 steps of about 40 cycles where conjugate gradients took some twenty iterations of 2000 (19 us).
+// L [CHOL_K][CHOL_K] and y live in `factor` between the calls.  A pivot below 1e-10 of its diagonal entry (two components
+// that nearly coincide) sets factor's last word, and this and all later calls go through conjugate gradients.
+#define CHOL_K 64
+#define CHOL_DOUBLES (CHOL_K * CHOL_K + CHOL_K + 1)
+#define CHOL_PITCH (CHOL_K + 1)
+__global__ void __launch_bounds__(256)
+tsvd_scales_kernel(const double* __restrict__ G, long long ldg, double* __restrict__ d, int K, double* __restrict__ s,
+                   const double* __restrict__ s0, const double* __restrict__ part, int fresh, int M, double* __restrict__ factor) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    double* Ll = reinterpret_cast<double*>(smem);           // [K][CHOL_PITCH]
+    __shared__ double tot[CHOL_K][4];
+    __shared__ int singular;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double* y = factor + CHOL_K * CHOL_K;
+    double* marked = y + CHOL_K;
+    if (tid == 0) singular = marked[0] != 0.0;
+#pragma unroll 4
+    for (int e = tid; e < fresh * CHOL_K; e += 256) Ll[(e >> 6) * CHOL_PITCH + (e & 63)] = factor[e];
+    for (int k = fresh; k < K; ++k) {
+        double a = 0.0;
+        for (int m = tid; m < M; m += 256) a += part[(size_t)(k - fresh) * M + m];
+        a = wave_sum(a);
+        if (lane == 0) tot[k][wave] = a;
+    }
+    __syncthreads();
+    if (wave == 0 && !singular) {
+        auto broadcast = [](double v, int from) {
+            const uint64_t b = __builtin_bit_cast(uint64_t, v);
+            return __builtin_bit_cast(double, (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)b, from) |
+                                                  ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(b >> 32), from) << 32));
+        };
+        double inv = lane < fresh ? 1.0 / Ll[lane * CHOL_PITCH + lane] : 0.0, yl = lane < fresh ? y[lane] : 0.0;
+        bool bad = false;
+        for (int r = fresh; r < K && !bad; ++r) {
+            const double* row = Ll + min(lane, r) * CHOL_PITCH;
+            double x = lane <= r ? G[(size_t)r * ldg + lane] : 0.0;
+            const double dr = (tot[r][0] + tot[r][1]) + (tot[r][2] + tot[r][3]), grr = broadcast(x, r);
+            for (int j0 = 0; j0 < r; j0 += 8)               // (steps at and beyond r change nothing)
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int j = j0 + t;
+                    const double lj = broadcast(x, j) * broadcast(inv, j), e = row[j];
+                    x = lane < r && lane >= j ? lane == j ? lj : x - e * lj : x;
+                }
+            if (lane >= r) x = 0.0;
+            const double pivot = grr - wave_sum(x * x), dot = wave_sum(x * yl);
+            bad = !(pivot > 1e-10 * grr);
+            const double diag = sqrt(pivot);
+            if (lane == r) {
+                x = diag;
+                inv = 1.0 / diag;
+                yl = (dr - dot) / diag;
+                d[r] = dr;
+            }
+            Ll[r * CHOL_PITCH + lane] = x;
+            factor[r * CHOL_K + lane] = x;
+        }
+        if (bad) {
+            if (lane == 0) {
+                singular = 1;
+                marked[0] = 1.0;
+            }
+        } else {
+            if (lane >= fresh && lane < K) y[lane] = yl;
+            double x = yl;
+            for (int j0 = (K - 1) & ~7; j0 >= 0; j0 -= 8)
+#pragma unroll
+                for (int t = 7; t >= 0; --t) {
+                    const int j = j0 + t;
+                    const double sj = broadcast(x, j) * broadcast(inv, j), e = Ll[min(j, K - 1) * CHOL_PITCH + lane];
+                    x = j < K && lane <= j ? lane == j ? sj : x - e * sj : x;
+                }
+            if (lane < K) s[lane] = x;
+        }
+    }
+    __syncthreads();
+    if (singular) solve_pcg(smem, G, ldg, d, K, s, s0, nullptr, part, fresh, M);
 }
 
 // ---- residual: R = W - U diag(S) V and partial sums of |R|_F^2 ----------------------------------
@@ -258,6 +516,68 @@ tsvd_residual_kernel(const double* __restrict__ W, const int8_t* __restrict__ U,
     }
     const double total = block_sum256(ss, red);
     if (threadIdx.x == 0 && partial) partial[m] = total;
+}
+
+// The same inside Algorithm 2, on the component-major factors Ut [rank][mp], V [rank][np]: grid (ceil(N / 256), ceil(M / 4)),
+// a wavefront per row, four columns per lane (one 4-byte load of V serves them and hits L1 for three of the four
+// wavefronts).  part[m * gridDim.x + blockIdx.x] = sum of squares of that piece, in host memory: the host adds them (a
+// copy back to the host after the launch would cost more than the launch); with them goes what the device has to report.
+struct transition_report {
+    tsvd_pair_state pair;
+    int failed;              // ternarizations without a result
+    int unused;
+};
+__global__ void __launch_bounds__(256)
+tsvd_residual_rows_kernel(const double* __restrict__ W, const int8_t* __restrict__ Ut, int mp, const double* __restrict__ S,
+                          const int8_t* __restrict__ V, int np, int M, int N, int K, double* __restrict__ R, double* __restrict__ part,
+                          const transition_report* __restrict__ seen, transition_report* __restrict__ told) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    double* us = reinterpret_cast<double*>(smem);               // [4][K]
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) told[0] = seen[0];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.y * 4, m = m0 + wave, n = blockIdx.x * 256 + 4 * lane;
+    for (int k = threadIdx.x; k < K; k += 256) {
+        const int w = *reinterpret_cast<const int*>(Ut + (size_t)k * mp + m0);
+        const double sk = S[k];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) us[e * K + k] = (double)(int8_t)(w >> (8 * e)) * sk;
+    }
+    __syncthreads();
+    if (m >= M) return;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const int nc = min(n, np - 4);
+#pragma unroll 8
+    for (int k = 0; k < K; ++k) {
+        const int w = *reinterpret_cast<const int*>(V + (size_t)k * np + nc);
+        const double u = us[wave * K + k];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += u * (double)(int8_t)(w >> (8 * e));
+    }
+    double ss = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (n + e < N) {
+            const double rv = W[(size_t)m * N + n + e] - acc[e];
+            R[(size_t)m * N + n + e] = rv;
+            ss += rv * rv;
+        }
+    ss = wave_sum(ss);
+    if (lane == 0) part[(size_t)m * gridDim.x + blockIdx.x] = ss;
+}
+
+// The result of Algorithm 2 from its component-major scratch: U [M][max_rank] (zero from K on), V [K][N], S [max_rank] (zero from K on).
+__global__ void __launch_bounds__(256)
+tsvd_emit_kernel(const int8_t* __restrict__ Ut, int mp, const int8_t* __restrict__ Vs, int np, const double* __restrict__ Ss, int M, int N, int K,
+                 int max_rank, int8_t* __restrict__ U, int8_t* __restrict__ V, double* __restrict__ S) {
+    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x, all = (size_t)gridDim.x * 256;
+    for (size_t e = t; e < (size_t)M * max_rank; e += all) {
+        const int m = (int)(e / max_rank), k = (int)(e - (size_t)m * max_rank);
+        U[e] = k < K ? Ut[(size_t)k * mp + m] : (int8_t)0;
+    }
+    for (size_t e = t; e < (size_t)K * N; e += all) {
+        const int k = (int)(e / N);
+        V[e] = Vs[(size_t)k * np + (e - (size_t)k * N)];
+    }
+    for (size_t e = t; e < (size_t)max_rank; e += all) S[e] = (int)e < K ? Ss[e] : 0.0;
 }
 
 // Sum of `count` partial values in a fixed order (one workgroup).
@@ -520,15 +840,49 @@ tsvd_deflate_kernel(double* __restrict__ R, int M, int N, const double* __restri
     for (int n = blockIdx.x * 256 + threadIdx.x; n < N; n += gridDim.x * 256) R[(size_t)m * N + n] -= f * v[n];
 }
 
+namespace {
+
+// `rows` vectors per job; the jobs of a launch share the length of the sorting network.
+hipError_t launch_ternarize(const ternarize_job* jobs, int njobs, unsigned rows, double theta, hipStream_t stream) {
+    ternarize_args a;
+    int n = 1;
+    for (int j = 0; j < njobs; ++j) {
+        a.job[j] = jobs[j];
+        n = std::max(n, jobs[j].n);
+    }
+    a.npow2 = std::max(64, pow2_at_least(n));
+    a.cos_theta = std::cos(theta);
+    const dim3 grid(rows, (unsigned)njobs), block((unsigned)std::min(a.npow2, TERN_THREADS));
+    switch (std::max(1, a.npow2 / TERN_THREADS)) {
+        case 1: hipLaunchKernelGGL(tsvd_ternarize_kernel<1>, grid, block, 0, stream, a); break;
+        case 2: hipLaunchKernelGGL(tsvd_ternarize_kernel<2>, grid, block, 0, stream, a); break;
+        case 4: hipLaunchKernelGGL(tsvd_ternarize_kernel<4>, grid, block, 0, stream, a); break;
+        default: hipLaunchKernelGGL(tsvd_ternarize_kernel<8>, grid, block, 0, stream, a); break;
+    }
+    return hipGetLastError();
+}
+
+// The K x K system of Eq. (3), by the Cholesky factor kept in `factor` (if any) while it is small, else by conjugate gradients; the last `fresh_count` entries of d come from part [fresh_count][M].
+void launch_solve(const double* G, long long ldg, double* d, int K, double* s, const double* s0, int* iters, const double* part, int fresh_count,
+                int M, double* factor, hipStream_t stream) {
+    const bool lds = K <= PCG_LDS_K;
+    const size_t bytes = (size_t)5 * K * 8 + 1024 * 8 + (lds ? (size_t)K * K * 8 : 0);
+    if (factor && K <= CHOL_K) {
+        hipLaunchKernelGGL(tsvd_scales_kernel, dim3(1), dim3(256), bytes, stream, G, ldg, d, K, s, s0, part, K - fresh_count, M, factor);
+        return;
+    }
+    hipLaunchKernelGGL(tsvd_pcg_kernel, dim3(1), dim3(lds ? (unsigned)((K + 63) & ~63) : 1024u), bytes, stream, G, ldg, d, K, s, s0, iters, part,
+                       K - fresh_count, M);
+}
+
+}  // namespace
+
 extern "C" tsvd_status tsvd_ternarize(const double* x_dev, int64_t n, int64_t count, int64_t ldx, double theta, int8_t* t_dev,
                                       int64_t ldt, int32_t* status_dev, void* stream) {
     if (!x_dev || !t_dev || !status_dev || n < 1 || n > TERN_MAX_N || count < 1 || count > (1 << 30) || ldx < n || ldt < n)
         return TSVD_EINVAL;
-    const int npow2 = pow2_at_least(n);
-    const size_t lds = (size_t)npow2 * 8 + 2 * 256 * 8;
-    hipLaunchKernelGGL(tsvd_ternarize_kernel, dim3((unsigned)count), dim3(256), lds, static_cast<hipStream_t>(stream), x_dev,
-                       (long long)ldx, (int)n, npow2, std::cos(theta), t_dev, (long long)ldt, status_dev);
-    return hipGetLastError() == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
+    const ternarize_job job = {x_dev, (long long)ldx, (int)n, t_dev, (long long)ldt, status_dev, nullptr};
+    return launch_ternarize(&job, 1, (unsigned)count, theta, static_cast<hipStream_t>(stream)) == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
 }
 
 extern "C" size_t tsvd_fit_scales_workspace(int64_t K) {
@@ -547,10 +901,9 @@ extern "C" tsvd_status tsvd_fit_scales(const int8_t* U_dev, int64_t ldu, const i
     double* G = static_cast<double*>(workspace);
     double* d = reinterpret_cast<double*>(static_cast<uint8_t*>(workspace) + round256((size_t)K * (size_t)K * 8));
     hipLaunchKernelGGL(tsvd_gram_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)K), dim3(256), 0, s, U_dev, (long long)ldu,
-                       V_dev, (int)M, (int)K, (int)N, G, (long long)K, -1);
-    hipLaunchKernelGGL(tsvd_rhs_kernel, dim3((unsigned)K), dim3(256), 0, s, U_dev, (long long)ldu, V_dev, W_dev, (int)M, (int)N, d, 0);
-    const size_t lds = (size_t)5 * K * 8 + 1024 * 8;
-    hipLaunchKernelGGL(tsvd_pcg_kernel, dim3(1), dim3(1024), lds, s, G, (long long)K, d, (int)K, S_dev, 0, iters_dev);
+                       V_dev, (int)M, (int)K, (int)N, G, (long long)K);
+    hipLaunchKernelGGL(tsvd_rhs_kernel, dim3((unsigned)K), dim3(256), 0, s, U_dev, (long long)ldu, V_dev, W_dev, (int)M, (int)N, d);
+    launch_solve(G, (long long)K, d, (int)K, S_dev, nullptr, iters_dev, nullptr, 0, 0, nullptr, s);
     return hipGetLastError() == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
 }
 
@@ -577,6 +930,7 @@ extern "C" tsvd_status tsvd_residual(const double* W_dev, const int8_t* U_dev, i
 
 extern "C" size_t tsvd_leading_singular_pair_workspace(int64_t M, int64_t N) {
     if (M < 1 || N < 1 || M > TERN_MAX_N || N > TERN_MAX_N) return 0;
+    if (tsvd_pair_squares(M, N)) return tsvd_pair_bytes(M, N);
     return round256((size_t)GKL_MAX_STEPS * M * 8) + round256((size_t)(GKL_MAX_STEPS + 1) * N * 8) + 4 * round256(GKL_MAX_STEPS * 8) +
            round256((size_t)M * 8) + round256((size_t)GKL_ROW_SLICES * N * 8);      // raw R v, partial R^T u
 }
@@ -589,6 +943,24 @@ extern "C" tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M
         return TSVD_EINVAL;
     if (workspace_bytes < tsvd_leading_singular_pair_workspace(M, N) || (reinterpret_cast<uintptr_t>(workspace) & 255u))
         return TSVD_EINVAL;
+    if (tsvd_pair_squares(M, N)) {
+        // squarings until the matrix is numerically of rank one; the host looks at the state now and then
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        tsvd_pair_plan plan;
+        tsvd_pair_prepare(M, N, workspace, &plan, s);
+        const int limit = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(1, (int)max_steps));
+        int count = 0;
+        for (tsvd_pair_state state = {-1, 0}; count < limit && state.last < 0;) {
+            const int to = std::min(limit, count == 0 ? 16 : count + 8);
+            tsvd_pair_square(plan, R_dev, count, to, s);
+            count = to;
+            if (hipMemcpyAsync(&state, plan.state, sizeof state, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+                return TSVD_EDEVICE;
+        }
+        tsvd_pair_vectors(plan, R_dev, count, s);
+        tsvd_pair_normalise(plan, count, u_dev, v_dev, sigma_dev, steps_dev, s);
+        return hipGetLastError() == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
+    }
     auto finish_lds = [](int64_t len) { return ((size_t)5 * (size_t)len + GKL_MAX_STEPS + 1 + 1024) * 8; };
     if (finish_lds(std::max(M, N)) > 150 * 1024) return TSVD_EUNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -665,12 +1037,12 @@ extern "C" tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M
 
 hipError_t tsvd_transition_init() {
     hipError_t e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_ternarize_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TERN_MAX_N * 8 + 2 * 256 * 8)) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_pcg_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 5 * FIT_MAX_K * 8 + 1024 * 8)) != hipSuccess) return e;
+                                 std::max(5 * FIT_MAX_K * 8, 5 * PCG_LDS_K * 8 + PCG_LDS_K * PCG_LDS_K * 8) + 1024 * 8)) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_residual_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  FIT_MAX_K * 8)) != hipSuccess) return e;
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_residual_rows_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 4 * FIT_MAX_K * 8)) != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_gkl_finish_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
 }
 
@@ -688,98 +1060,174 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         return TSVD_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     *rank_out = 0;
-    // scratch: R [M][N], u [M], v [N], t_u [M] int8, sigma, |R|^2, status[2], fit workspace
-    const size_t bytes_R = round256((size_t)M * N * 8), bytes_u = round256((size_t)M * 8), bytes_v = round256((size_t)N * 8);
-    const size_t bytes_tu = round256((size_t)M), bytes_misc = 256, bytes_fit = tsvd_fit_scales_workspace(max_rank);
-    const size_t bytes_svd = tsvd_leading_singular_pair_workspace(M, N);
-    const size_t bytes_defl = q > 1 ? bytes_R : 0;             // working copy of the residual for the second .. q-th triple
-    uint8_t* base = nullptr;
-    if (hipMalloc(reinterpret_cast<void**>(&base), bytes_R + bytes_u + bytes_v + bytes_tu + bytes_misc + bytes_fit + bytes_svd + bytes_defl) !=
-        hipSuccess) {
+    const bool squares = tsvd_pair_squares(M, N);
+    const int mp = (int)((M + 15) & ~15), np = (int)((N + 15) & ~15);       // pitches of the component-major factors
+    const int pieces = (int)((N + 255) / 256);                              // pieces of a row of the residual
+    // scratch
+    size_t total = 0;
+    auto reserve = [&](size_t bytes) {
+        const size_t at = total;
+        total += round256(bytes);
+        return at;
+    };
+    const size_t at_R = reserve((size_t)M * N * 8);
+    const size_t at_Rwork = reserve(q > 1 ? (size_t)M * N * 8 : 0);          // working copy for the second .. q-th triple
+    const size_t at_Ut = reserve((size_t)max_rank * mp), at_V = reserve((size_t)max_rank * np);
+    const size_t scale_bytes = round256((size_t)max_rank * 8);
+    const size_t at_S = reserve(3 * scale_bytes), at_d = reserve((size_t)max_rank * 8);
+    const size_t at_G = reserve((size_t)max_rank * max_rank * 8);
+    const size_t at_factor = reserve((size_t)CHOL_DOUBLES * 8);
+    const size_t at_part = reserve((size_t)q * M * 8);
+    const size_t at_report = reserve(sizeof(transition_report));
+    const size_t at_u = reserve((size_t)M * 8), at_v = reserve((size_t)N * 8), at_sigma = reserve(8);
+    const size_t bytes_svd = tsvd_leading_singular_pair_workspace(M, N), at_svd = reserve(bytes_svd);
+    // what the host reads after an iteration (two in turn, written by the device): the report, and the residual's sums of squares
+    const size_t told_bytes = round256(sizeof(transition_report) + (size_t)M * pieces * 8);
+    uint8_t *base = nullptr, *pinned = nullptr;
+    hipEvent_t event[2] = {nullptr, nullptr};
+    auto release = [&] {
+        for (hipEvent_t e : event)
+            if (e) (void)hipEventDestroy(e);
+        if (pinned) (void)hipHostFree(pinned);
+        if (base) (void)hipFree(base);
+    };
+    if (hipMalloc(reinterpret_cast<void**>(&base), total) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&pinned), 2 * told_bytes, hipHostMallocDefault) != hipSuccess ||
+        hipEventCreateWithFlags(&event[0], hipEventDisableTiming) != hipSuccess || hipEventCreateWithFlags(&event[1], hipEventDisableTiming) != hipSuccess) {
+        release();
         (void)hipGetLastError();
         return TSVD_EDEVICE;
     }
-    double* R = reinterpret_cast<double*>(base);
-    double* u = reinterpret_cast<double*>(base + bytes_R);
-    double* v = reinterpret_cast<double*>(base + bytes_R + bytes_u);
-    int8_t* tu = reinterpret_cast<int8_t*>(base + bytes_R + bytes_u + bytes_v);
-    double* misc = reinterpret_cast<double*>(base + bytes_R + bytes_u + bytes_v + bytes_tu);   // [0] sigma, [1] |R|^2
-    int32_t* flags = reinterpret_cast<int32_t*>(misc + 4);                                     // ternarize status x 2
-    uint8_t* fit_ws = base + bytes_R + bytes_u + bytes_v + bytes_tu + bytes_misc;
-    double* G = reinterpret_cast<double*>(fit_ws);                              // [max_rank][max_rank], grown row by row
-    double* dvec = reinterpret_cast<double*>(fit_ws + round256((size_t)max_rank * (size_t)max_rank * 8));
-    void* svd_ws = fit_ws + bytes_fit;
-    double* Rwork = q > 1 ? reinterpret_cast<double*>(fit_ws + bytes_fit + bytes_svd) : nullptr;
+    double* R = reinterpret_cast<double*>(base + at_R);
+    double* Rwork = reinterpret_cast<double*>(base + at_Rwork);
+    int8_t* Ut = reinterpret_cast<int8_t*>(base + at_Ut);                    // [max_rank][mp]
+    int8_t* Vs = reinterpret_cast<int8_t*>(base + at_V);                     // [max_rank][np]
+    double* scales[3];                                                       // of iteration i in [i % 3]; 0: none yet
+    for (int e = 0; e < 3; ++e) scales[e] = reinterpret_cast<double*>(base + at_S + e * scale_bytes);
+    double* dvec = reinterpret_cast<double*>(base + at_d);
+    double* G = reinterpret_cast<double*>(base + at_G);                      // [max_rank][max_rank], grown row by row
+    double* factor = reinterpret_cast<double*>(base + at_factor);
+    double* part = reinterpret_cast<double*>(base + at_part);
+    transition_report* rep = reinterpret_cast<transition_report*>(base + at_report);
+    double* u = reinterpret_cast<double*>(base + at_u);
+    double* v = reinterpret_cast<double*>(base + at_v);
+    double* sigma = reinterpret_cast<double*>(base + at_sigma);
 
     tsvd_status st = TSVD_OK;
     auto ok = [&](hipError_t e) {
         if (e != hipSuccess && st == TSVD_OK) st = TSVD_EDEVICE;
         return e == hipSuccess;
     };
-    // |W|^2 and R = W: the residual of one all-zero component
+    // the residual after iteration i, with K components, and the report of it
+    auto residual = [&](int64_t i, int64_t K) {
+        uint8_t* told = pinned + (i & 1) * told_bytes;
+        hipLaunchKernelGGL(tsvd_residual_rows_kernel, dim3((unsigned)pieces, (unsigned)((M + 3) / 4)), dim3(256), (size_t)4 * K * 8, s, W_dev, Ut, mp,
+                           scales[i % 3], Vs, np, (int)M, (int)N, (int)K, R, reinterpret_cast<double*>(told + sizeof(transition_report)), rep,
+                           reinterpret_cast<transition_report*>(told));
+        ok(hipGetLastError());
+        ok(hipEventRecord(event[i & 1], s));
+    };
+    transition_report seen = {};
+    double rnorm2 = 0.0;
+    auto wait_for = [&](int64_t i) {
+        if (st == TSVD_EDEVICE || !ok(hipEventSynchronize(event[i & 1]))) return false;
+        const uint8_t* told = pinned + (i & 1) * told_bytes;
+        std::memcpy(&seen, told, sizeof seen);
+        const double* sq = reinterpret_cast<const double*>(told + sizeof(transition_report));
+        rnorm2 = 0.0;
+        for (size_t e = 0; e < (size_t)M * pieces; ++e) rnorm2 += sq[e];
+        return true;
+    };
+    ok(hipMemsetAsync(Ut, 0, at_S - at_Ut, s));                              // the padding of the factors
+    ok(hipMemsetAsync(rep, 0, sizeof(transition_report), s));
+    ok(hipMemsetAsync(factor, 0, (size_t)CHOL_DOUBLES * 8, s));
+    tsvd_pair_plan plan;
+    if (squares) {
+        tsvd_pair_prepare(M, N, base + at_svd, &plan, s);
+        plan.state = &rep->pair;
+        u = plan.u;
+        v = plan.v;
+    }
+    residual(0, 0);                                                          // R = W, |W|^2
     double wnorm2 = 0.0;
-    ok(hipMemsetAsync(S_dev, 0, (size_t)max_rank * 8, s));
-    ok(hipMemsetAsync(U_dev, 0, (size_t)M * max_rank, s));
-    ok(hipMemsetAsync(V_dev, 0, (size_t)N, s));
-    if (st == TSVD_OK) st = tsvd_residual(W_dev, U_dev, max_rank, S_dev, V_dev, M, 1, N, R, misc + 1, s);
-    ok(hipMemcpyAsync(&wnorm2, misc + 1, 8, hipMemcpyDeviceToHost, s));
-    ok(hipStreamSynchronize(s));
-    int64_t K = 0;
-    while (st == TSVD_OK && K < max_rank && wnorm2 > 0.0) {
+    if (wait_for(0)) wnorm2 = rnorm2;
+    int squarings = 16;                                                      // enqueued per pair; grows if a pair needs more
+    // Iteration i: components first .. first + take - 1 from the residual of the one before.
+    auto enqueue = [&](int64_t i, int64_t first, int64_t take) {
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
         // that triple removed, ... (the last iteration takes what still fits below max_rank)
-        const int64_t take = std::min<int64_t>(q, max_rank - K);
-        if (take > 1 && !ok(hipMemcpyAsync(Rwork, R, (size_t)M * N * 8, hipMemcpyDeviceToDevice, s))) break;
-        const int64_t K0 = K;
-        for (int64_t j = 0; j < take && st == TSVD_OK; ++j) {
-            const double* src = take > 1 ? Rwork : R;
-            st = tsvd_leading_singular_pair(src, M, N, 4 * GKL_MAX_STEPS, u, v, misc, nullptr, svd_ws, bytes_svd, s);
-            if (st != TSVD_OK) break;
-            if (j + 1 < take) {
-                hipLaunchKernelGGL(tsvd_deflate_kernel, dim3((unsigned)std::min<int64_t>(16, (N + 255) / 256), (unsigned)M), dim3(256), 0, s,
-                                   Rwork, (int)M, (int)N, u, v, misc);
-                if (!ok(hipGetLastError())) break;
-            }
-            // column K of U (row stride max_rank) is written through a contiguous temporary
-            st = tsvd_ternarize(u, M, 1, M, theta, tu, M, flags, s);
-            if (st != TSVD_OK) break;
-            st = tsvd_ternarize(v, N, 1, N, theta, V_dev + (size_t)K * N, N, flags + 1, s);
-            if (st != TSVD_OK) break;
-            int32_t fl[2] = {0, 0};
-            if (!ok(hipMemcpy2DAsync(U_dev + K, (size_t)max_rank, tu, 1, 1, (size_t)M, hipMemcpyDeviceToDevice, s))) break;
-            if (!ok(hipMemcpyAsync(fl, flags, 8, hipMemcpyDeviceToHost, s)) || !ok(hipStreamSynchronize(s))) break;
-            if (fl[0] != 0 || fl[1] != 0) {
-                st = TSVD_EVALUE;                                   // no ternary vector within theta
-                break;
-            }
-            ++K;
+        const double* src = R;
+        if (take > 1) {
+            if (!ok(hipMemcpyAsync(Rwork, R, (size_t)M * N * 8, hipMemcpyDeviceToDevice, s))) return;
+            src = Rwork;
         }
-        if (st != TSVD_OK) {
-            K = K0;            // (the components of an unfinished iteration are dropped: *rank_out stays at the last complete one)
-            break;
+        for (int64_t j = 0; j < take; ++j) {
+            if (squares) {
+                tsvd_pair_square(plan, src, 0, squarings, s);
+                tsvd_pair_vectors(plan, src, squarings, s);
+                if (j + 1 < take) tsvd_pair_deflate(plan, Rwork, s);
+            } else {
+                const tsvd_status ps = tsvd_leading_singular_pair(src, M, N, 4 * GKL_MAX_STEPS, u, v, sigma, nullptr, base + at_svd, bytes_svd, s);
+                if (ps != TSVD_OK) {
+                    st = ps;
+                    return;
+                }
+                if (j + 1 < take)
+                    hipLaunchKernelGGL(tsvd_deflate_kernel, dim3((unsigned)std::min<int64_t>(16, (N + 255) / 256), (unsigned)M), dim3(256), 0, s,
+                                       Rwork, (int)M, (int)N, u, v, sigma);
+            }
+            const ternarize_job jobs[2] = {{u, M, (int)M, Ut + (size_t)(first + j) * mp, mp, nullptr, &rep->failed},
+                                           {v, N, (int)N, Vs + (size_t)(first + j) * np, np, nullptr, &rep->failed}};
+            if (!ok(launch_ternarize(jobs, 2, 1, theta, s))) return;
         }
         // Eq. (3) with what changed only: the new rows / columns of the Gram matrix and entries of the right
-        // side; the solve starts from the previous scales (the new ones at 0, set when S was cleared)
-        for (int64_t r = K0; r < K; ++r) {
-            hipLaunchKernelGGL(tsvd_gram_kernel, dim3((unsigned)((K + 255) / 256), 1), dim3(256), 0, s, U_dev, (long long)max_rank, V_dev,
-                               (int)M, (int)K, (int)N, G, (long long)max_rank, (int)r);
-            hipLaunchKernelGGL(tsvd_rhs_kernel, dim3(1), dim3(256), 0, s, U_dev, (long long)max_rank, V_dev, W_dev, (int)M, (int)N, dvec,
-                               (int)r);
+        // side; the solve starts from the previous scales (the new ones at 0)
+        const int64_t K = first + take;
+        hipLaunchKernelGGL(tsvd_system_kernel, dim3((unsigned)((K + M + 3) / 4), (unsigned)take), dim3(256), 0, s, Ut, mp, Vs, np, W_dev, (int)M, (int)N,
+                           (int)first, (int)K, G, (long long)max_rank, part);
+        launch_solve(G, (long long)max_rank, dvec, (int)K, scales[i % 3], scales[(i + 2) % 3], nullptr, part, (int)take, (int)M, factor, s);
+        residual(i, K);
+    };
+    // One iteration is always enqueued beyond the one the host waits for: it costs nothing where the loop goes on, and
+    // where the loop ends nothing of it is used (its components lie beyond the rank, its scales in a buffer of their own).
+    int64_t K = 0, i = 1, ahead = 0;                                         // ahead: components enqueued
+    int64_t take = std::min<int64_t>(q, max_rank);
+    if (st == TSVD_OK && wnorm2 > 0.0) {
+        enqueue(1, 0, take);
+        ahead = take;
+        while (st == TSVD_OK) {
+            const int64_t next = std::min<int64_t>(q, max_rank - ahead);
+            if (next > 0) enqueue(i + 1, ahead, next);
+            if (st != TSVD_OK || !wait_for(i)) break;
+            if (seen.pair.missed != 0 && squarings < TSVD_PAIR_MAX_SQUARINGS) {
+                // some pair needed more squarings: back to the residual before this iteration, with more of them
+                squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, squarings + 8);
+                if (!ok(hipStreamSynchronize(s)) || !ok(hipMemsetAsync(rep, 0, sizeof(transition_report), s))) break;
+                residual(i - 1, K);
+                enqueue(i, K, take);
+                ahead = K + take;
+                continue;
+            }
+            if (seen.failed != 0) {
+                st = TSVD_EVALUE;           // no ternary vector within theta: the components of an unfinished iteration are dropped
+                break;
+            }
+            const double err = std::sqrt(rnorm2 / wnorm2);
+            if (errors_host)
+                for (int64_t r = K; r < K + take; ++r) errors_host[r] = err;      // (one error per iteration, repeated for its components)
+            K += take;
+            *rank_out = K;
+            if (err <= tol || next <= 0) break;
+            take = next;
+            ahead += next;
+            ++i;
         }
-        hipLaunchKernelGGL(tsvd_pcg_kernel, dim3(1), dim3(1024), (size_t)5 * K * 8 + 1024 * 8, s, G, (long long)max_rank, dvec, (int)K,
-                           S_dev, 1, static_cast<int*>(nullptr));
-        if (!ok(hipGetLastError())) break;
-        st = tsvd_residual(W_dev, U_dev, max_rank, S_dev, V_dev, M, K, N, R, misc + 1, s);
-        if (st != TSVD_OK) break;
-        double rnorm2 = 0.0;
-        if (!ok(hipMemcpyAsync(&rnorm2, misc + 1, 8, hipMemcpyDeviceToHost, s)) || !ok(hipStreamSynchronize(s))) break;
-        const double err = std::sqrt(rnorm2 / wnorm2);
-        if (errors_host)
-            for (int64_t r = K0; r < K; ++r) errors_host[r] = err;      // (one error per iteration, repeated for its components)
-        *rank_out = K;
-        if (err <= tol) break;
     }
+    const int64_t kept = K == 0 ? 0 : st == TSVD_OK ? i : i - 1;              // the last complete iteration
+    if (st == TSVD_OK || st == TSVD_EVALUE)
+        hipLaunchKernelGGL(tsvd_emit_kernel, dim3(256), dim3(256), 0, s, Ut, mp, Vs, np, scales[kept % 3], (int)M, (int)N, (int)*rank_out, (int)max_rank, U_dev, V_dev,
+                           S_dev);
     (void)hipStreamSynchronize(s);
-    (void)hipFree(base);
+    release();
     return st;
 }

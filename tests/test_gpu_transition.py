@@ -101,6 +101,33 @@ def test_leading_singular_pair(tsvd, M, N):
         assert np.max(np.abs(sign * u - ur[:, 0])) < 1e-8 and np.max(np.abs(sign * v - vr[0, :])) < 1e-8
 
 
+@pytest.mark.parametrize("M,N", [(1, 1), (1, 70), (70, 1), (64, 64), (65, 63), (129, 200), (384, 400), (385, 385), (500, 420)])
+def test_leading_singular_pair_by_squarings_at_tile_edges(tsvd, M, N):
+    """Sizes around the tiles of the squaring kernels (16 and 32 rows, padding to 64, the change at 384), both orientations;
+    a rank-one matrix (done after one squaring) and a pair of equal leading singular values (never of rank one: the pair must
+    still be a singular pair)."""
+    rng = np.random.default_rng(100 * M + N)
+    cases = {"laplace": rng.laplace(size=(M, N)), "rank one": np.outer(rng.standard_normal(M), rng.standard_normal(N)),
+             "zero": np.zeros((M, N))}
+    if min(M, N) > 4:
+        A, _ = np.linalg.qr(rng.standard_normal((M, 4)))
+        B, _ = np.linalg.qr(rng.standard_normal((N, 4)))
+        cases["equal"] = (A * np.array([3.0, 3.0, 1.0, 0.5])[None, :]) @ B.T
+    for name, R in cases.items():
+        print(f"case squarings M={M} N={N} {name}", flush=True)
+        u, sigma, v, steps = tsvd.tsvd_leading_singular_pair(_dev(R))
+        u, sigma, v = u.cpu().numpy(), float(sigma.cpu()[0]), v.cpu().numpy()
+        if name == "zero":
+            assert sigma == 0.0 and not u.any() and not v.any()
+            continue
+        top = np.linalg.svd(R, compute_uv=False)[0]
+        assert abs(sigma - top) <= 1e-12 * top
+        assert abs(np.linalg.norm(u) - 1) < 1e-12 and abs(np.linalg.norm(v) - 1) < 1e-12
+        assert np.linalg.norm(R @ v - sigma * u) <= 1e-12 * top and np.linalg.norm(R.T @ u - sigma * v) <= 1e-12 * top
+        start = 1.0 + 0.5 * np.sin(1.0 + 0.7 * np.arange(N))
+        assert v @ start > 0                                                        # the sign is that of the start vector
+
+
 def test_transition_follows_the_oracle_on_separated_spectra(tsvd):
     """Algorithm 2 end to end.  W is built with well separated singular values, so every residual
     has a clear leading pair and both sides must pick the same ternary vectors: U S V, S and the
