@@ -11,6 +11,7 @@
 
 #include "../../include/tsvd.h"
 #include "../../include/tsvd_tuning.h"
+#include "tsvd_batch.h"
 #include "tsvd_kernels.h"
 #include "tsvd_layout.h"
 
@@ -424,15 +425,33 @@ bool use_gemm(const tsvd_handle*, int64_t B, tsvd_dtype x_dtype) {
     return B >= min_b;
 }
 
+// (set for the duration of a tsvd_forward_noalloc call whose planes would not fit the fixed workspace where z in 16 bits does)
+thread_local bool planes_only_by_older_rules = false;
+
+// How a batched call runs that the few-token kernels leave.  copies: x would have to be copied for the kernels that read aligned
+// feature-major rows.
+tsvd_batch_plan batch_plan(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, bool x_token_major, bool copies, bool y_token_major, bool out_bf16) {
+    tsvd_batch_call c = {};
+    c.M = h->hd.M; c.K = h->hd.K; c.N = h->hd.N; c.B = B; c.cus = h->cu_count;
+    c.f32 = x_dtype == TSVD_F32;
+    c.x_token_major = x_token_major; c.y_token_major = y_token_major; c.out_bf16 = out_bf16; c.copies = copies;
+    c.whole = tsvd_stage_mask() == 7;
+    tsvd_batch_plan plan = tsvd_plan_batch(c);
+    if (planes_only_by_older_rules && !c.f32) plan.split = false;
+    return plan;
+}
+
 size_t gemm_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     const int64_t Bp = tsvd_round_up(B, 256);
-    if (x_dtype == TSVD_F32)      // two sets of planes of x, two of z (blocks that hold anything only)
-        return round256(tsvd_gemm_fp6_bytes(256 * ((h->hd.N + 127) / 128), Bp)) + round256(tsvd_gemm_fp6_bytes(256 * ((h->hd.K + 127) / 128), Bp));
+    if (x_dtype == TSVD_F32) return tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, true);
     // partial column maxima [PARTS][Bp] fp32, then Z as fp16 [Kp][Bp]
     size_t bytes = round256((size_t)(TSVD_COLMAX_PARTS + 1) * Bp * 4) + round256((size_t)h->hd.Kp * (size_t)Bp * 2);
     // (the rule is asked as for aligned rows: a caller with unaligned rows then reserves a little too much)
     if (tsvd_gemm_use_fp6(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count, true))      // planes of Z, and of X for stage V
         bytes += round256(tsvd_gemm_fp6_bytes(h->hd.Kp, Bp)) + round256(tsvd_gemm_fp6_bytes(h->hd.Np, Bp));
+    // (asked as for the call that favours planes most)
+    if (use_gemm(h, B, x_dtype) && batch_plan(h, B, x_dtype, false, true, false, false).split)
+        bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
     return bytes;
 }
 
@@ -649,8 +668,13 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         ldx = 1;
     }
     int x_in_place = 0;
-    if (x_layout == TSVD_TOKEN_MAJOR && x_dtype == TSVD_BF16 && use_gemm(h, B, x_dtype) && !use_mid(h, B, x_dtype, tsvd_round_up(B, 8)) &&
-        tsvd_gemm_reads_token_major(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count)) {
+    const bool few = use_mid(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR ? tsvd_round_up(B, 8) : ldx);
+    const bool batched = use_gemm(h, B, x_dtype), misaligned = ldx % 8 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 15u);
+    tsvd_batch_plan plan = {};
+    if (batched && !few)
+        plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16);
+    if (x_layout == TSVD_TOKEN_MAJOR && (plan.split || (x_dtype == TSVD_BF16 && batched && !few &&
+                                                        tsvd_gemm_reads_token_major(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count)))) {
         x_in_place = 1;       // the kernels this call takes gather their operand lanes from [B][ldx] themselves
     } else if (x_layout == TSVD_TOKEN_MAJOR) {
         // one pass that rewrites x as [N][B rounded up to 8] at the front of the workspace; the rows
@@ -667,7 +691,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         x_dev = ws;
         ldx = ldt;
         ws = static_cast<uint8_t*>(ws) + transposed_bytes(h, B, x_dtype);
-    } else if (x_dtype == TSVD_BF16 && use_gemm(h, B, x_dtype) && (ldx % 8 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 15u)) && env_int("TSVD_REALIGN", 1) != 0 &&
+    } else if (!plan.split && x_dtype == TSVD_BF16 && batched && misaligned && env_int("TSVD_REALIGN", 1) != 0 &&
              h->hd.N <= 65535) {
         // more than 16 tokens in rows that are not 16-byte aligned: one pass that copies them to aligned rows costs
         // less than the element-wise gathers of the kernels that take such rows (stage V of a 4096 x 8192
@@ -691,6 +715,9 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         g.ldx = ldx;
         g.x_token_major = x_in_place;
         g.x_f32 = x_dtype == TSVD_F32;
+        g.split = plan.split;
+        g.split_v = plan.split_v;
+        g.split_u = plan.split_u;
         g.y = y_dev;
         g.ldy = ldy;
         g.bias = oo.bias;
@@ -719,13 +746,13 @@ extern "C" tsvd_status tsvd_forward_noalloc(const tsvd_handle* h, const void* x_
     if (x_dtype != TSVD_F32 && x_dtype != TSVD_BF16) return TSVD_EINVAL;
     if (x_layout != TSVD_FEATURE_MAJOR && x_layout != TSVD_TOKEN_MAJOR) return TSVD_EINVAL;
     if (h->device < 0 || h->device >= 64 || !noalloc_ptr[h->device]) return TSVD_EDEVICE;
-    bool slow_f32 = false;
+    bool* const smaller = x_dtype == TSVD_F32 ? &f32_one_token_at_a_time : &planes_only_by_older_rules;
     if (tsvd_workspace_bytes_ex(h, B, x_dtype, x_layout) > (size_t)TSVD_NOALLOC_MAX_WORKSPACE) {
-        // an fp32 batch whose planes do not fit can still go one token at a time (a small workspace)
-        if (x_dtype != TSVD_F32) return TSVD_ETOOLARGE;
-        f32_one_token_at_a_time = slow_f32 = true;
+        // an fp32 batch whose planes do not fit can still go one token at a time (a small workspace), a bf16 batch
+        // on the kernels that keep z in 16 bits
+        *smaller = true;
         if (tsvd_workspace_bytes_ex(h, B, x_dtype, x_layout) > (size_t)TSVD_NOALLOC_MAX_WORKSPACE) {
-            f32_one_token_at_a_time = false;
+            *smaller = false;
             return TSVD_ETOOLARGE;
         }
     }
@@ -733,7 +760,7 @@ extern "C" tsvd_status tsvd_forward_noalloc(const tsvd_handle* h, const void* x_
     // reads it), so nothing has to be cleared between calls
     const tsvd_status st = tsvd_forward_ex(h, x_dev, x_dtype, x_layout, B, ldx, bias_dev, y_dev, y_dtype, ldy, noalloc_ptr[h->device],
                                            (size_t)TSVD_NOALLOC_MAX_WORKSPACE, stream);
-    if (slow_f32) f32_one_token_at_a_time = false;
+    *smaller = false;
     return st;
 }
 
@@ -743,7 +770,7 @@ const char* const tuning_names[] = {
     "TSVD_GEMV", "TSVD_GEMV_FUSED", "TSVD_GEMV_ONEPASS", "TSVD_GEMV_SW", "TSVD_GEMV_KWLOG2", "TSVD_SKINNY_SW", "TSVD_SKINNY_KW",
     "TSVD_MID", "TSVD_MID_MAX_B", "TSVD_MID_SW", "TSVD_MID_KWLOG2", "TSVD_MID_RESIDENT", "TSVD_GEMM_MIN_B", "TSVD_GEMM_MIN_B_F32",
     "TSVD_GEMM_CFG_V", "TSVD_GEMM_CFG_U", "TSVD_FUSEMAX", "TSVD_COLMAX_SCALAR", "TSVD_REALIGN", "TSVD_PANEL",
-    "TSVD_PANEL_WAVES", "TSVD_PANEL_FP6", "TSVD_FP6", "TSVD_FP6_V", "TSVD_FP6_TALL", "TSVD_FP6_PLANES", "TSVD_FP6_DIRECT", "TSVD_FP6_TAIL", "TSVD_TOKEN_MAJOR_COPY", "TSVD_GROUPED_PAIR", "TSVD_CLOCKS",
+    "TSVD_PANEL_WAVES", "TSVD_PANEL_FP6", "TSVD_FP6", "TSVD_FP6_V", "TSVD_FP6_TALL", "TSVD_FP6_PLANES", "TSVD_FP6_DIRECT", "TSVD_FP6_TAIL", "TSVD_SPLIT_V", "TSVD_SPLIT_U", "TSVD_SPLIT_X", "TSVD_TOKEN_MAJOR_COPY", "TSVD_GROUPED_PAIR", "TSVD_CLOCKS",
     "TSVD_SPIN_LIMIT", "TSVD_DENSE_U", "TSVD_EARLY_TILES"};
 constexpr int tuning_count = (int)(sizeof tuning_names / sizeof tuning_names[0]);
 int tuning_value[tuning_count];
@@ -752,6 +779,7 @@ int tuning_active = 0;                 // number of switches set: 0 in every pro
 thread_local int stage_mask_now = 7;
 }  // namespace
 
+bool tsvd_tuning_any() { return tuning_active != 0; }
 int tsvd_tune(const char* name, int fallback) {
     if (tuning_active == 0) return fallback;
     for (int i = 0; i < tuning_count; ++i)
@@ -793,7 +821,11 @@ extern "C" int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* s
     *shape_v = *shape_u = -1;
     if (use_mid(h, B, TSVD_BF16, tsvd_round_up(B, 8))) return 0;
     if (use_gemm(h, B, TSVD_BF16)) {
-        if (tsvd_gemm_use_panel(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count, true)) {
+        const tsvd_batch_plan plan = batch_plan(h, B, TSVD_BF16, false, false, false, false);
+        if (plan.split) {
+            *shape_v = plan.split_v ? 100 + plan.split_v : 40;
+            *shape_u = plan.split_u ? 100 + plan.split_u : 40;
+        } else if (tsvd_gemm_use_panel(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count, true)) {
             *shape_v = *shape_u = tsvd_gemm_panel_fp6() ? 33 : 32;   // one token-panel launch (33: on fp4 codes x fp6 planes)
         } else {
             *shape_v = tsvd_gemm_tile_shape(h->hd.Kp, B, h->cu_count, true);
@@ -809,6 +841,8 @@ const uint8_t* tsvd_internal_blob(const tsvd_handle* h, const tsvd_blob_header**
     *hd = &h->hd;
     return h->blob;
 }
+
+int tsvd_internal_cu_count(const tsvd_handle* h) { return h->cu_count; }
 
 extern "C" int tsvd_tuning_read_clocks(const tsvd_handle* h, long long* out, int workgroups) {
     if (!h || !h->clocks || !out || workgroups < 1 || workgroups > TSVD_GEMV_MAX_GRID) return 1;

@@ -1,0 +1,142 @@
+// The choice among the batched kernels, by estimates of their times.
+//
+// Three ways serve a batch: planes of x with tiles of
+// tsvd_fp6_split.hip per stage (128 x 16 to 256 x 64, the contraction split over groups of wavefronts), the same with the tiles of
+// tsvd_fp6.hip (many rows and tokens), and the ring and large-tile kernels of tsvd_gemm.hip on 16-bit operands.  No single quantity
+// separates them: a launch with few workgroups is bound by its serial chain (steps of a workgroup's loop), one with many by
+// matrix instructions.  So each gets an estimate in microseconds, a sum of
+// the quantities that bound it: the launch, rounds of workgroups over the compute units, loop steps, records of x made, code bytes.
+// The factors are fits (non-negative least squares on relative errors) to measurements on MI355X of 1200 bf16 calls, 160 fp32 calls and 600
+// convolutions of random shapes (17 to 16384 tokens, factors of 1 KB to 64 MB), 24 ways each; the estimates' standard error is 10 to 16 %.
+// Picking the smallest is within 4 % of the best way on the average of those calls and 1.22 times the speed of always
+// taking the older ones (fp32 2 to 4).
+#include "tsvd_batch.h"
+
+#include <algorithm>
+#include <initializer_list>
+
+#include "tsvd_gemm_common.h"
+#include "tsvd_kernels.h"
+
+namespace {
+
+long long up(long long a, long long b) { return (a + b - 1) / b; }
+
+struct sizes {
+    long long M, N, B, cus, nvb, nub, sets;       // blocks of 128 of N and of K; sets of three planes (two for fp32)
+};
+
+// ---- the plane path: x to planes, stage V with shape v, stage U with shape u (0: tsvd_fp6.hip) -------------------
+double planes_cost(const sizes& s, int v) {
+    if (tsvd_fp6_split_makes_x(v, (int)std::min<long long>(s.sets * s.nvb, 1 << 20))) return 0;      // stage V makes them
+    return 4.9 + 8.4 * (double)(s.nvb * up(s.B, 16) * s.sets) / 4096;
+}
+struct split_factors {
+    int shape;
+    double v0, v_round, v_step, v_x, v_gather, u0, u_round, u_step;
+};
+constexpr split_factors split_table[] = {
+    {9, 1.3, 2.1, 2.9, 2.2, 2.3, 0.7, 1.3, 3.0},
+    {10, 0.3, 4.4, 1.9, 2.2, 2.5, 0.4, 2.5, 2.1},
+    {18, 0.0, 4.1, 3.0, 2.4, 2.6, 0.3, 2.8, 3.4},
+    {20, 0.0, 5.7, 2.3, 2.4, 2.4, 0.0, 5.8, 2.4},
+};
+// rounds of workgroups and loop steps (16 records each) of a stage
+double rounds(const sizes& s, int shape, long long row_blocks) { return (double)up(up(row_blocks, shape >> 3) * up(s.B, 16 * (shape & 7)), s.cus); }
+double steps(int shape, long long blocks) { return (double)up(blocks, 16 / (shape & 7)); }
+
+double split_v_cost(const sizes& s, const split_factors* f, bool gathered_x) {
+    if (!f) {       // 256 x 128 or 512 x 64 tiles, two workgroups per compute unit
+        const bool small = up(s.nub, 2) * up(s.B, 128) < s.cus;
+        const double w = (double)(s.nub % 4 || small ? up(s.nub, 2) * up(s.B, 128) : up(s.nub, 4) * up(s.B, 64));
+        const double r = (double)up((long long)w, 2 * s.cus), fill = w > (double)s.cus ? std::min(1.0, std::max(0.5, w / (2.0 * (double)s.cus * r))) : 0.55;
+        return planes_cost(s, 0) + r * fill * (12.5 + 2.4 * (double)(s.sets * s.nvb));
+    }
+    const double r = rounds(s, f->shape, s.nub), x = planes_cost(s, f->shape);
+    // records of x per wavefront where the stage makes them; more where the elements of a record are gathered one by one
+    const double made = x > 0 ? 0 : r * (double)(up(s.nvb * (f->shape & 7), 8) * s.sets) * (f->v_x + (gathered_x ? f->v_gather : 0));
+    return x + f->v0 + r * f->v_round + r * steps(f->shape, s.sets * s.nvb) * f->v_step + made;
+}
+double split_u_cost(const sizes& s, const split_factors* f) {
+    if (!f) {       // 128 x 64 (four per compute unit), 256 x 64 (three), 512 x 64 or 256 x 128 (two)
+        const long long t256 = up(s.M, 256), c64 = up(s.B, 64), c128 = up(s.B, 128);
+        const bool small = t256 * c128 < s.cus;
+        double w, slots, size;
+        if (small && 4 * t256 * c64 < 3 * s.cus) { w = (double)(up(s.M, 128) * c64); slots = 4; size = 1; }
+        else if (small) { w = (double)(t256 * c64); slots = 3; size = 2; }
+        else if (t256 % 2 == 0) { w = (double)(up(s.M, 512) * c64); slots = 2; size = 4; }
+        else { w = (double)(t256 * c128); slots = 2; size = 4; }
+        const double all = slots * (double)s.cus, fill = w <= all ? std::max(1 / slots, w / all) : w / all, n = (double)(s.sets * s.nub);
+        return 2.7 + fill * size * (4.2 + 0.51 * n) + 0.4 * n;
+    }
+    const double r = rounds(s, f->shape, up(s.M, 128));
+    return f->u0 + r * f->u_round + r * steps(f->shape, s.sets * s.nub) * f->u_step;
+}
+
+// ---- ring and large-tile kernels ----------------------------------------------------------------
+double older_cost(const tsvd_batch_call& c) {
+    double t = 7.3;
+    if (c.conv) t += 6.0 + 1.3 * (double)c.N * (double)c.B / 1e6;               // columns written first
+    else if (c.copies) t += 3.3 + 1.9 * (double)c.N * (double)c.B / 1e6;
+    auto stage = [&](long long rows, long long rows_p, long long blocks, double ring64, double ring128_0, double ring128, double large_0, double large) {
+        const int shape = tsvd_gemm_tile_shape(rows_p, c.B, c.cus, true);
+        const long long tr = shape < 2 ? 256 : shape == 15 ? 128 : shape == 17 ? 96 : 64, tt = shape == 0 ? 256 : shape == 1 ? 128 : 64;
+        const double work = std::max(1.0, (double)(up(rows, tr) * up(c.B, tt)) / (double)c.cus) * (double)(tr * tt) / 4096 * (double)blocks / 8;
+        t += shape < 2 ? large_0 + large * work : shape == 15 ? ring128_0 + ring128 * work : ring64 * work;
+    };
+    stage(128 * up(c.K, 128), tsvd_round_up(c.K, 256), up(c.N, 128), 3.45, 2.0, 3.2, 5.0, 1.87);
+    stage(c.M, tsvd_round_up(c.M, 256), up(c.K, 128), 3.76, 4.3, 3.6, 18.3, 2.0);
+    return t;
+}
+
+// 64-token panels, for the calls that their rule gives them (179 such calls measured)
+double panel_cost(const tsvd_batch_call& c) {
+    const long long nvb = up(c.N, 128), nub = up(c.K, 128), strips = up(c.M, 128);
+    const double r = (double)up(up(c.B, 64), c.cus);
+    return r * (7.5 + (double)nvb * (c.x_token_major && c.N % 8 ? 5.6 : 2.3) + 1.8 * (double)(up(strips, 8) * nub) + (double)strips * (c.y_token_major ? 1.9 : 0.83));
+}
+
+}  // namespace
+
+size_t tsvd_gemm_split_bytes(long long K, long long N, long long B, bool f32) {
+    const long long sets = f32 ? 2 : 1, Bp = tsvd_round_up(B, f32 ? 256 : 128);
+    auto part = [&](long long len) { return (tsvd_gemm_fp6_bytes(128 * sets * up(len, 128), Bp) + 255) & ~(size_t)255; };
+    return part(N) + part(K);
+}
+
+tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
+    tsvd_batch_plan plan = {c.f32, 0, 0};
+    if (tsvd_tuning_any()) {        // a diagnostic that sets switches means the kernels that they select
+        const int v = tsvd_tune("TSVD_SPLIT_V", 0), u = tsvd_tune("TSVD_SPLIT_U", 0);
+        if (v > 0 || u > 0) plan = {true, v, u};
+        return plan;
+    }
+    const long long Mp = tsvd_round_up(c.M, 256), Kp = tsvd_round_up(c.K, 256), Np = tsvd_round_up(c.N, 256);
+    const sizes s = {c.M, c.N, c.B, c.cus, up(c.N, 128), up(c.K, 128), c.f32 ? 2 : 1};
+    const bool gathered_x = c.x_token_major && c.N % 8 != 0;
+    double best_v = split_v_cost(s, nullptr, false), best_u = split_u_cost(s, nullptr);
+    const double fp6_tiles = best_v + best_u;
+    int v = 0, u = 0;
+    for (const split_factors& f : split_table) {
+        const double cv = split_v_cost(s, &f, gathered_x), cu = split_u_cost(s, &f);
+        if (cv < best_v) best_v = cv, v = f.shape;
+        if (cu < best_u) best_u = cu, u = f.shape;
+    }
+    if (c.f32) {
+        plan.split_v = v;
+        plan.split_u = u;
+        return plan;
+    }
+    // Another way replaces the older one only where its estimate is a tenth smaller: the estimates' own error.  (Where an older call runs
+    // on planes too, its estimate is that of the same tiles.)
+    const double columns = c.conv ? 6.0 + 1.3 * (double)c.N * (double)c.B / 1e6 : 0;
+    const bool panel = c.whole && tsvd_gemm_use_panel(Mp, Kp, Np, c.B, c.cus, true);
+    double best = (c.conv ? 1.0 : panel ? 0.95 : 0.9) *
+                  (panel ? panel_cost(c) + columns : tsvd_gemm_use_fp6(Mp, Kp, Np, c.B, c.cus, true) ? fp6_tiles + columns : older_cost(c));
+    const bool fits = !panel && tsvd_gemm_split_bytes(c.K, c.N, c.B, false) < (1ull << 31);
+    if (fits && (v || u) && best_v + best_u + columns < best) {
+        best = best_v + best_u + columns;
+        plan = {true, v, u};
+    }
+    return plan;
+}

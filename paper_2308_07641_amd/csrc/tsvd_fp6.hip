@@ -9,7 +9,7 @@
 #include <cmath>
 #include <type_traits>
 
-#include "tsvd_gemm_common.h"
+#include "tsvd_fp6_common.h"
 
 namespace {
 
@@ -37,126 +37,6 @@ namespace {
 // 256 x 128 tile of eight wavefronts (1.78 - 1.83 ms, a barrier for every 0.35 us of MFMAs per
 // wavefront); a 512 x 128 tile with 256 indices per barrier (register spills, 2.0 ms); a raised wavefront
 // priority (s_setprio 1 or 2) during the MFMA steps of a block (1.51 against 1.49 - 1.50 ms).
-//
-// Record of one (16-token tile, 128-index block): planes' first 16 bytes per lane [3][64][16], last
-// 8 bytes per lane [3][64][8], scale words [64][4] = 4864 bytes; lane (i, g) holds, for token i of
-// the tile, the indices that meet elements 0..31 of lane group g of the A operand built from the
-// tile format (tsvd_step_column).  Records are stored [128-token group][block][tile in group].
-#define FP6_REC_BYTES 4864
-#ifndef FP6_LDS_DEPTH
-#define FP6_LDS_DEPTH 2                            // operand reads ahead of the MFMAs, in steps of eight MFMAs
-#endif
-#define FP6_PAIR_BYTES (8 * FP6_REC_BYTES)      // one block of one 128-token group: 38 KiB exactly
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-// One lane's 32 values -> three E2M3 planes (the value, the residual of its rounding, the residual of that), each
-// with its own power-of-two scale.  put(plane, first 16 bytes, last 8 bytes) receives the lane's 24 bytes of each
-// plane; the return value holds the three scale bytes.  KEEP: v is left holding what the three planes do not resolve
-// (for a second set of planes); else it is used up.
-template <bool KEEP = false, typename Put>
-__device__ __forceinline__ uint32_t tsvd_planes_of_32(float (&v)[32], Put put) {
-    typedef float f32x16 __attribute__((ext_vector_type(16)));
-    typedef float f32x32 __attribute__((ext_vector_type(32)));
-    typedef unsigned u32x6 __attribute__((ext_vector_type(6)));
-    uint32_t scales = 0;
-#pragma unroll
-    for (int pl = 0; pl < 3; ++pl) {
-        float m = 0.f;
-#pragma unroll
-        for (int e = 0; e < 32; ++e) m = fmaxf(m, fabsf(v[e]));
-        // exponent ex with m 2^-ex <= 7.5, the largest E2M3 magnitude (m = f 2^x, 0.5 <= f < 1)
-        int x = 0;
-        const float f = frexpf(m, &x);
-        int ex = m > 0.f ? (f <= 0.9375f ? x - 3 : x - 2) : 0;
-        ex = max(-126, min(126, ex));
-        scales |= (uint32_t)(127 + ex) << (8 * pl);
-        const float unit = ldexpf(1.0f, ex);
-        // v_cvt_scalef32_2xpk16_fp6_f32: element 2 j of the result is src0[j] / scale, element 2 j + 1 is
-        // src1[j] / scale, rounded to nearest even on the E2M3 grid (saturating); the reverse conversion
-        // returns the elements in the same order, times the scale (measured on gfx950)
-        f32x16 s0, s1;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            s0[j] = v[2 * j];
-            s1[j] = v[2 * j + 1];
-        }
-        // The conversions take several passes over their registers, and the register allocator lets the result of the
-        // builtins share registers with operands that die at the instruction.  Measured on gfx950: a result tuple that
-        // started in the scale's register left elements 2..31 converted with a wrong scale.  Hence the instructions are
-        // written out with results that may not overlap any operand.
-        u32x6 w;
-        asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3" : "=&v"(w) : "v"(s0), "v"(s1), "v"(unit));
-        if (pl < 2 || KEEP) {
-            f32x32 back;
-            asm("v_cvt_scalef32_pk32_f32_fp6 %0, %1, %2" : "=&v"(back) : "v"(w), "v"(unit));
-#pragma unroll
-            for (int e = 0; e < 32; ++e) v[e] -= back[e];         // exact: the next plane codes this residual
-        }
-        put(pl, u32x4{w[0], w[1], w[2], w[3]}, u32x2{w[4], w[5]});
-    }
-    return scales;
-}
-// ... written to the lane's places in the record at `rec`
-template <bool KEEP = false>
-__device__ __forceinline__ void tsvd_planes_of_32(float (&v)[32], unsigned char* rec, int lane) {
-    const uint32_t scales = tsvd_planes_of_32<KEEP>(v, [&](int pl, u32x4 lo, u32x2 hi) {
-        *reinterpret_cast<u32x4*>(rec + pl * 1024 + lane * 16) = lo;
-        *reinterpret_cast<u32x2*>(rec + 3072 + pl * 512 + lane * 8) = hi;
-    });
-    *reinterpret_cast<uint32_t*>(rec + 4608 + lane * 4) = scales;
-}
-// Six planes for fp32 values: a record of three, and a second record for what those leave (2^-14.7 of a block's largest
-// magnitude times 2^-14.7 again: below the last bit of an fp32 value of that magnitude).
-__device__ __forceinline__ void tsvd_planes_of_32_twice(float (&v)[32], unsigned char* rec, unsigned char* rec2, int lane) {
-    tsvd_planes_of_32<true>(v, rec, lane);
-    tsvd_planes_of_32<false>(v, rec2, lane);
-}
-
-// The 32 values of one operand lane from bf16 activations stored one row per token (token-major, row pitch ld
-// elements): indices k0 + 32 (e >> 4) + (e & 15), two runs of 16 consecutive elements.  vec: rows and base are 16-byte
-// aligned (four 16-byte loads), else 32 two-byte loads.  The buffer's range check gives zero beyond the last token's
-// row; indices beyond kvalid and tokens beyond the batch are zeroed here.
-__device__ __forceinline__ void tsvd_gather_token_major(__amdgpu_buffer_rsrc_t x_rsrc, int ld2, int tok, int k0, int kvalid, bool tok_ok,
-                                                        bool vec, float (&v)[32]) {
-    const int voff = tok * ld2;
-    if (vec) {
-        u32x4 q[4];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) q[h] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, voff, (k0 + 32 * (h >> 1) + 8 * (h & 1)) * 2, 0);
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const uint32_t w = q[2 * (e >> 4) + ((e >> 3) & 1)][(e & 7) >> 1];
-            v[e] = __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 32; ++e)
-            v[e] = __uint_as_float((uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x_rsrc, voff, (k0 + 32 * (e >> 4) + (e & 15)) * 2, 0) << 16);
-    }
-#pragma unroll
-    for (int e = 0; e < 32; ++e)
-        if (!tok_ok || k0 + 32 * (e >> 4) + (e & 15) >= kvalid) v[e] = 0.f;
-}
-
-// The operand pass for fp32 activations x [rows_valid][ld] (feature-major, any row pitch): two records per (16-token
-// tile, 128-index block), the second `set_offset` blocks behind the first in a layout of `nblocks` blocks per token
-// group.  A lane gathers its 32 values itself (rows beyond the matrix and tokens beyond the batch read as zero).
-__global__ void __launch_bounds__(512)
-tsvd_x_planes_f32_kernel(const float* __restrict__ x, long long ld, int rows_valid, int cols_valid, int nblocks, int set_offset,
-                         unsigned char* __restrict__ planes) {
-    const int tt = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-    const int tok = blockIdx.x * 128 + tt * 16 + i, k0 = blockIdx.y * 128 + 64 * (g & 1) + 16 * (g >> 1);
-    float v[32];
-#pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        const int k = k0 + 32 * (e >> 4) + (e & 15);
-        const float q = x[(size_t)min(k, rows_valid - 1) * ld + min(tok, cols_valid - 1)];
-        v[e] = k < rows_valid && tok < cols_valid ? q : 0.f;
-    }
-    unsigned char* rec = planes + ((size_t)(blockIdx.x * nblocks + blockIdx.y) * 8 + tt) * FP6_REC_BYTES;
-    tsvd_planes_of_32_twice(v, rec, rec + (size_t)set_offset * 8 * FP6_REC_BYTES, lane);
-}
-
 // The operand pass for token-major bf16 activations x [cols_valid tokens][ld]: no transposition through LDS, a lane's
 // values are contiguous in memory.  Same grid and records as tsvd_z_planes_kernel.
 __global__ void __launch_bounds__(512)
@@ -209,14 +89,6 @@ tsvd_z_planes_kernel(const uint16_t* __restrict__ Z, long long ld, int rows_vali
         v[e] = BF16 ? __uint_as_float((uint32_t)h << 16) : (float)__builtin_bit_cast(_Float16, h);
     }
     tsvd_planes_of_32(v, planes + ((size_t)(blockIdx.x * nblocks + blockIdx.y) * 8 + tt) * FP6_REC_BYTES, lane);
-}
-
-template <int PL>
-__device__ __forceinline__ f32x4 mfma_fp6(const u32x4& a, const u32x4& lo, const u32x2& hi, uint32_t scale, f32x4 acc) {
-    const i32x8 av = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
-    const i32x8 bv = {(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, 0, 0};
-    // cbsz = 4: A is fp4 (E2M1); blgp = 2: B is fp6 (E2M3); A scale 2^0; B scale = byte PL of `scale`
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, acc, 4, 2, 0, 0x7F7F7F7F, PL, (int)scale);
 }
 
 // WM x WN = 2 x 2 wavefronts (256 rows x 128 tokens per workgroup) or 4 x 1 (512 x 64) of TM x 4 = 8 x 4 blocks
@@ -372,8 +244,9 @@ __device__ __forceinline__ void fp6_tile(const gemm_args& p, const int b0, const
             for (int e = 0; e < 32; ++e) v[e] = acc[e >> 2][b][e & 3];
             unsigned char* rec = static_cast<unsigned char*>(p.out) +
                                  ((size_t)(((tok + 16 * b) >> 7) * (int)p.ld_out + kb) * 8 + (((tok + 16 * b) & 127) >> 4)) * FP6_REC_BYTES;   // (ld_out: blocks per token group)
+            if (kb >= p.rows_need / 128) continue;          // (beyond the blocks that stage U reads)
             if (!p.two_sets) tsvd_planes_of_32(v, rec, lane);
-            else if (kb < p.two_sets) tsvd_planes_of_32_twice(v, rec, rec + (size_t)p.two_sets * 8 * FP6_REC_BYTES, lane);   // (fp32 path: six planes)
+            else tsvd_planes_of_32_twice(v, rec, rec + (size_t)p.two_sets * 8 * FP6_REC_BYTES, lane);   // (fp32 path: six planes)
         }
     } else {
         gemm_epilogue<TM, TN, STAGE2, EX>(p, acc, strip0, b0, wn * TN * 16, cs_lds, i, g);
@@ -978,13 +851,6 @@ hipError_t tsvd_fp6_launch_planes(bool bf16, const uint16_t* src, long long ld, 
     }
     if (bf16) hipLaunchKernelGGL(tsvd_z_planes_kernel<true>, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, planes);
     else hipLaunchKernelGGL(tsvd_z_planes_kernel<false>, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, planes);
-    return hipGetLastError();
-}
-
-hipError_t tsvd_fp6_launch_planes_f32(const float* x, long long ld, int rows_valid, int cols_valid, int blocks, unsigned char* planes,
-                                      hipStream_t stream) {
-    hipLaunchKernelGGL(tsvd_x_planes_f32_kernel, dim3((unsigned)((cols_valid + 127) / 128), (unsigned)blocks), dim3(512), 0, stream, x, ld,
-                       rows_valid, cols_valid, 2 * blocks, blocks, planes);
     return hipGetLastError();
 }
 

@@ -1,0 +1,353 @@
+// Batched stages on fp4 codes x fp6 planes for launches with few tiles: the contraction of a tile is split over the
+// wavefronts of its workgroup.  With it the operand pass that serves any layout of the activations.
+//
+// The kernels of tsvd_fp6.hip give every wavefront its own rows of a tile and let all of them walk the contraction
+// together.  With fewer than two such tiles per compute unit a SIMD holds a single wavefront, which issues a matrix
+// instruction every 24.5 cycles (16 is the pipe), and a contraction of a dozen blocks is a dozen barriers.  Here eight
+// wavefronts share a tile of RW x 128 rows and 16 TN tokens: KG = 8 / RW groups of them take every KG-th run of BPS blocks of
+// the contraction, so a SIMD always has two wavefronts, a barrier is passed once per KG BPS blocks, and each wavefront
+// still multiplies 128 rows (eight row blocks) by every operand it reads from LDS.  At the end the partial sums of the
+// groups meet in LDS, each group finishing its share of the tile.
+// Measured on MI355X: 3072 x 768 x 1536 fp32 at 197 tokens 56.4 -> 20.1 us (128 x 16 tiles with planes of x made inside, then 128 x 32),
+// 16384 x 4096 x 8192 bf16 at 256 tokens 93.4 -> 71.4 us (256 x 32 and 256 x 64).  What bounds them: the matrix
+// instructions at 19 - 21 cycles each once a compute unit has a few steps to walk, the launch and the first code words below that.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "tsvd_fp6_common.h"
+
+namespace {
+
+// ---- the operand lanes of x ----------------------------------------------------------------------
+// The 32 values of one lane of the record of (16-token tile, 128-index block), from activations in any layout: indices k0 + 32 (e >> 4) +
+// (e & 15); indices beyond N and tokens beyond B read as zero.
+template <bool F32>
+__device__ __forceinline__ void gather_x(const void* x, long long ld, bool token_major, int N, int B, int block, int tile, int lane, float (&v)[32]) {
+    using T = std::conditional_t<F32, uint32_t, uint16_t>;
+    const int i = lane & 15, g = lane >> 4, tok = tile * 16 + i, k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1), tc = min(tok, B - 1);
+    auto value = [](T r) { return F32 ? __builtin_bit_cast(float, (uint32_t)r) : __uint_as_float((uint32_t)r << 16); };
+    const T* p = static_cast<const T*>(x);
+    if (token_major && k0 + 48 <= N && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && ld % (16 / (int)sizeof(T)) == 0) {   // two runs of 16 indices, 16 bytes at a time
+        constexpr int PER = 16 / sizeof(T);
+        u32x4 q[2][16 / PER];
+        const T* row = p + (size_t)tc * ld + k0;
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int c = 0; c < 16 / PER; ++c) q[r][c] = *reinterpret_cast<const u32x4*>(row + 32 * r + PER * c);
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            const int r = e >> 4, at = e & 15;
+            if constexpr (F32) {
+                v[e] = __uint_as_float(q[r][at >> 2][at & 3]);
+            } else {
+                const uint32_t w = q[r][at >> 3][(at & 7) >> 1];
+                v[e] = __uint_as_float((at & 1) ? (w & 0xFFFF0000u) : (w << 16));
+            }
+            if (tok >= B) v[e] = 0.f;
+        }
+        return;
+    }
+    const size_t ks = token_major ? 1 : (size_t)ld, ts = token_major ? (size_t)ld : 1;
+    T r[32];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) r[e] = p[(size_t)min(k0 + 32 * (e >> 4) + (e & 15), N - 1) * ks + (size_t)tc * ts];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) v[e] = tok < B && k0 + 32 * (e >> 4) + (e & 15) < N ? value(r[e]) : 0.f;
+}
+
+// The operand pass: a wavefront makes one record (fp32: two, six planes), token tile blockIdx.x * 4 + wave, block blockIdx.y
+// (four neighbouring tiles per workgroup: feature-major rows are then read in runs of 64 tokens).
+template <bool F32>
+__global__ void __launch_bounds__(256)
+tsvd_planes_kernel(const void* __restrict__ x, long long ld, int token_major, int N, int B, int nblocks, unsigned char* __restrict__ planes) {
+    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (tile * 16 >= B) return;
+    float v[32];
+    gather_x<F32>(x, ld, token_major != 0, N, B, blockIdx.y, tile, lane, v);
+    unsigned char* rec = planes + ((size_t)((tile >> 3) * (F32 ? 2 * nblocks : nblocks) + blockIdx.y) * 8 + (tile & 7)) * FP6_REC_BYTES;
+    if constexpr (F32) tsvd_planes_of_32_twice(v, rec, rec + (size_t)nblocks * 8 * FP6_REC_BYTES, lane);   // a second set behind the first
+    else tsvd_planes_of_32(v, rec, lane);
+}
+
+// ---- a stage ------------------------------------------------------------------------------------
+// Step s of wavefront (rw, kg): blocks (s KG + kg) BPS .. + BPS - 1.  KG BPS TN = 16 records of a step (76 KiB) in LDS, two steps in
+// turn, copied by all wavefronts (buffer_load ... lds) while the other step is multiplied; code words from L2 to registers
+// one step ahead.
+// X (stage V): the workgroup makes the records of x itself, all of them at the start, where two steps hold them: every row tile
+// makes them again, and a launch with its ramp and the gap before it (4 us) is saved for about 1.5 us.  1: bf16, 2: fp32.
+struct split_x {
+    const void* x;
+    long long ld;
+    int token_major, N;
+};
+template <int RW, int TN, bool STAGE2, int EX, int X = 0>
+__global__ void __launch_bounds__(512, 1)
+tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
+    constexpr int KG = 8 / RW, BPS = 16 / (KG * TN), TM = 8, RECS = KG * BPS * TN;
+    static_assert(RECS == 16 && BPS >= 1, "16 records per step");
+    constexpr bool DIRECT = !STAGE2;                        // stage V writes the planes of z
+    constexpr int STEP_BYTES = RECS * FP6_REC_BYTES;
+    constexpr int CHUNK = TN * FP6_REC_BYTES, PIECES = (CHUNK + 1023) / 1024, TOTAL = KG * BPS * PIECES;   // a chunk: a block's TN records
+    constexpr int NQ = DIRECT ? TN : KG, NF = 8 * TN / NQ;  // shares of the tile that a group finishes: NQ of NF result blocks
+    constexpr int NFR = TN == 4 ? 4 : NF;                   // ... of which NFR meet in LDS at a time
+    static_assert((size_t)NQ * (KG - 1) * RW * NFR * 1024 <= 2 * STEP_BYTES, "the partial sums fit the two buffers");
+    extern __shared__ __align__(16) unsigned char smem[];   // 2 x STEP_BYTES, then 16 TN ones (the epilogue's token factors)
+    float* ones = reinterpret_cast<float*>(smem + 2 * STEP_BYTES);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rw = wave % RW, kg = wave / RW, i = lane & 15, g = lane >> 4;
+    const int b0 = blockIdx.x * 16 * TN, strip0 = (blockIdx.y * RW + rw) * TM;
+    const int nrun = p.npairs, nsteps = (nrun + KG * BPS - 1) / (KG * BPS), nblocks = p.plane_blocks;
+    if (threadIdx.x < 16 * TN) ones[threadIdx.x] = 1.0f;
+
+    const i32x4 act_rsrc = raw_rsrc(p.act, p.act_bytes);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles), 0, p.tile_bytes, 0x00020000);
+    typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_byte_ptr)smem;
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    auto issue = [&](int step, int buf) {
+        if (X) return;
+#pragma unroll
+        for (int c = 0; c < (TOTAL + 7) / 8; ++c) {
+            const int idx = c * 8 + wave, chunk = idx / PIECES, piece = idx - chunk * PIECES, blk = step * KG * BPS + chunk;
+            if ((TOTAL % 8 == 0 || idx < TOTAL) && blk < nrun) {
+                const int at = piece * 1024 + lane * 16;
+                if (CHUNK % 1024 == 0 || at < CHUNK)         // (lanes beyond the chunk would write into the next one)
+                    buf_load128_to_lds(act_rsrc, lds_base + buf * STEP_BYTES + chunk * CHUNK + piece * 1024, lane * 16,
+                                       ((b0 >> 7) * nblocks + blk) * FP6_PAIR_BYTES + ((b0 & 127) >> 4) * FP6_REC_BYTES + piece * 1024);
+            }
+        }
+    };
+    // stage V: row 4 gg + vv of result block a comes from row 64 (gg & 1) + 16 (gg >> 1) + 32 (a >> 2) + 4 (a & 3) + vv of the
+    // wavefront's 128, so that result lane (g, token) holds the 32 rank positions of stage U's operand lane (see fp6_tile)
+    const int gg = i >> 2, vv = i & 3;
+    const int w_voff = DIRECT ? (4 * (gg & 1) + (gg >> 1)) * p.nkt * 1024 + (g * 16 + vv) * 16 : lane * 16;
+    auto load_w = [&](int step, u32x2 (&w)[BPS][TM]) {
+#pragma unroll
+        for (int j = 0; j < BPS; ++j) {
+            int blk = min((step * KG + kg) * BPS + j, nrun - 1);
+            if (p.code_blocks && blk >= p.code_blocks) blk -= p.code_blocks;      // (second set of planes: the same codes again)
+            const int soff = (strip0 * p.nkt + (blk >> 1)) * 1024 + (blk & 1) * 8;
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+                w[j][a] = __builtin_amdgcn_raw_buffer_load_b64(
+                    w_rsrc, w_voff, soff + (DIRECT ? 2 * (a >> 2) * p.nkt * 1024 + 4 * (a & 3) * 16 : a * p.nkt * 1024), 0);
+        }
+    };
+    auto touch = [&](const u32x2 (&w)[BPS][TM]) {
+#pragma unroll
+        for (int j = 0; j < BPS; ++j)
+#pragma unroll
+            for (int a = 0; a < TM; ++a) asm volatile("" :: "v"(w[j][a].x), "v"(w[j][a].y));
+    };
+    // the operands of an MFMA step (one plane of one record, eight row blocks) are read two steps ahead
+    auto compute = [&](int step, int buf, const u32x2 (&w)[BPS][TM]) {
+        const unsigned char* mine = smem + buf * STEP_BYTES + kg * BPS * CHUNK;
+        const int valid = nrun - (step * KG + kg) * BPS;     // blocks of this step that exist
+        constexpr int STEPS = 3 * BPS * TN;
+        u32x4 lo[3];
+        u32x2 hi[3];
+        uint32_t sc[2];
+        auto read_step = [&](int st) {
+            const unsigned char* rec = mine + (st / 3) * FP6_REC_BYTES;
+            const int pl = st % 3;
+            lo[pl] = *reinterpret_cast<const u32x4*>(rec + pl * 1024 + lane * 16);
+            hi[pl] = *reinterpret_cast<const u32x2*>(rec + 3072 + pl * 512 + lane * 8);
+            if (pl == 0) sc[(st / 3) & 1] = *reinterpret_cast<const uint32_t*>(rec + 4608 + lane * 4);
+        };
+        if (valid <= 0) return;
+        read_step(0);
+        read_step(1);
+#pragma unroll
+        for (int j = 0; j < BPS; ++j) {
+            if (j >= valid) break;
+            u32x4 av[TM];
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+                av[a] = u32x4{(w[j][a].x << 2) & 0xCCCCCCCCu, w[j][a].x & 0xCCCCCCCCu, (w[j][a].y << 2) & 0xCCCCCCCCu, w[j][a].y & 0xCCCCCCCCu};
+#pragma unroll
+            for (int t = 0; t < 3 * TN; ++t) {
+                const int st = j * 3 * TN + t;
+                if (st + 2 < STEPS) read_step(st + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                const int b = t / 3;
+#pragma unroll
+                for (int a = 0; a < TM; ++a) {
+                    switch (t % 3) {
+                        case 0: acc[a][b] = mfma_fp6<0>(av[a], lo[0], hi[0], sc[(st / 3) & 1], acc[a][b]); break;
+                        case 1: acc[a][b] = mfma_fp6<1>(av[a], lo[1], hi[1], sc[(st / 3) & 1], acc[a][b]); break;
+                        default: acc[a][b] = mfma_fp6<2>(av[a], lo[2], hi[2], sc[(st / 3) & 1], acc[a][b]); break;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+
+    u32x2 wa[BPS][TM], wb[BPS][TM];
+    load_w(0, wa);
+    issue(0, 0);
+    if constexpr (X != 0) {
+        const int blocks = X == 2 ? nrun / 2 : nrun;         // (fp32: the second set of planes are further blocks)
+        auto record = [&](int blk, int tile) {               // steps alternate between the buffers, and there are at most two
+            const int step = blk / (KG * BPS);
+            return smem + step * STEP_BYTES + (blk - step * KG * BPS) * CHUNK + tile * FP6_REC_BYTES;
+        };
+        for (int q = wave; q < blocks * TN; q += 8) {
+            const int blk = q / TN, tile = q - blk * TN;
+            float v[32];
+            gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + tile, lane, v);
+            if constexpr (X == 2) tsvd_planes_of_32_twice(v, record(blk, tile), record(blk + blocks, tile), lane);
+            else tsvd_planes_of_32(v, record(blk, tile), lane);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    touch(wa);
+    __syncthreads();
+    for (int s = 0; s < nsteps; s += 2) {
+        load_w(min(s + 1, nsteps - 1), wb);
+        if (s + 1 < nsteps) issue(s + 1, 1);
+        compute(s, 0, wa);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        touch(wb);
+        __syncthreads();
+        if (s + 1 < nsteps) {
+            load_w(min(s + 2, nsteps - 1), wa);
+            if (s + 2 < nsteps) issue(s + 2, 0);
+            compute(s + 1, 1, wb);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            touch(wa);
+            __syncthreads();
+        }
+    }
+
+    // ---- the groups' partial sums: result block f = 8 tile + row block; group q finishes blocks q NF .. + NF - 1
+    f32x4 fin[NF];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        if (q == kg) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) fin[f] = acc[(q * NF + f) & 7][(q * NF + f) >> 3];
+        }
+#pragma unroll
+    for (int f0 = 0; f0 < NF; f0 += NFR) {
+        auto slot = [&](int q, int from, int f) { return smem + ((((q * (KG - 1) + from) * RW + rw) * NFR + f) * 64 + lane) * 16; };
+        if (f0 > 0) __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            if (q != kg) {
+                const int from = kg < q ? kg : kg - 1;
+#pragma unroll
+                for (int f = 0; f < NFR; ++f)
+                    *reinterpret_cast<f32x4*>(slot(q, from, f)) = acc[(q * NF + f0 + f) & 7][(q * NF + f0 + f) >> 3];
+            }
+        __syncthreads();
+        if (kg < NQ) {
+#pragma unroll
+            for (int from = 0; from < KG - 1; ++from)
+#pragma unroll
+                for (int f = 0; f < NFR; ++f) fin[f0 + f] += *reinterpret_cast<const f32x4*>(slot(kg, from, f));
+        }
+    }
+    if (kg >= NQ) return;
+    if constexpr (DIRECT) {
+        // z = S (V x) / 4 (the codes of either stage multiply as +-2) -> the record of token tile kg
+        const int kb = strip0 >> 3, tok = b0 + 16 * kg, zblocks = p.rows_need / 128;
+        if (kb >= zblocks) return;
+        float v[32];
+#pragma unroll
+        for (int a = 0; a < TM; ++a) {
+            const f32x4 sv = *reinterpret_cast<const f32x4*>(p.S + 128 * kb + 64 * (g & 1) + 16 * (g >> 1) + 32 * (a >> 2) + 4 * (a & 3));
+            fin[a] *= 0.25f * sv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * a + e] = fin[a][e];
+        }
+        unsigned char* rec = static_cast<unsigned char*>(p.out) + ((size_t)((tok >> 7) * (int)p.ld_out + kb) * 8 + ((tok & 127) >> 4)) * FP6_REC_BYTES;
+        if (p.two_sets) tsvd_planes_of_32_twice(v, rec, rec + (size_t)p.two_sets * 8 * FP6_REC_BYTES, lane);
+        else tsvd_planes_of_32(v, rec, lane);
+    } else {
+        f32x4 out[NF][1];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) out[f][0] = fin[f];
+        gemm_epilogue<NF, 1, true, EX>(p, out, strip0 + ((kg * NF) & 7), b0, 16 * ((kg * NF) >> 3), ones, i, g);
+    }
+}
+
+constexpr int split_lds(int tn) { return 2 * 16 * FP6_REC_BYTES + 16 * tn * 4; }
+
+template <int RW, int TN, bool STAGE2, int EX, int X = 0>
+hipError_t init_one() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_fp6_split_kernel<RW, TN, STAGE2, EX, X>), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds(TN));
+}
+template <int RW, int TN>
+hipError_t init_shape() {
+    hipError_t e;
+    if ((e = init_one<RW, TN, false, 0>()) != hipSuccess) return e;
+    if ((e = init_one<RW, TN, false, 0, 1>()) != hipSuccess) return e;
+    if ((e = init_one<RW, TN, false, 0, 2>()) != hipSuccess) return e;
+    if ((e = init_one<RW, TN, true, 0>()) != hipSuccess) return e;
+    if ((e = init_one<RW, TN, true, 1>()) != hipSuccess) return e;
+    if ((e = init_one<RW, TN, true, 2>()) != hipSuccess) return e;
+    return init_one<RW, TN, true, 3>();
+}
+template <int RW, int TN>
+hipError_t launch_shape(bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, hipStream_t stream) {
+    const dim3 grid((unsigned)((a.bvalid + 16 * TN - 1) / (16 * TN)), (unsigned)((a.rows_need + RW * 128 - 1) / (RW * 128))), block(512);
+    constexpr int lds = split_lds(TN);
+    const split_x none = {};
+    if (!stage2 && x && f32) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, false, 0, 2>), grid, block, lds, stream, a, *x);
+    else if (!stage2 && x) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, false, 0, 1>), grid, block, lds, stream, a, *x);
+    else if (!stage2) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, false, 0>), grid, block, lds, stream, a, none);
+    else if (ex == 3) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 3>), grid, block, lds, stream, a, none);
+    else if (ex == 2) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 2>), grid, block, lds, stream, a, none);
+    else if (ex == 1) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 1>), grid, block, lds, stream, a, none);
+    else hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 0>), grid, block, lds, stream, a, none);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t tsvd_fp6_split_init() {
+    hipError_t e;
+    if ((e = init_shape<2, 4>()) != hipSuccess) return e;
+    if ((e = init_shape<2, 2>()) != hipSuccess) return e;
+    if ((e = init_shape<1, 2>()) != hipSuccess) return e;
+    return init_shape<1, 1>();
+}
+
+// shape: rows / 128 of a tile * 8 + token tiles of 16
+static hipError_t launch_any(int shape, bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, hipStream_t stream) {
+    switch (shape) {
+        case 20: return launch_shape<2, 4>(stage2, a, ex, x, f32, stream);
+        case 18: return launch_shape<2, 2>(stage2, a, ex, x, f32, stream);
+        case 10: return launch_shape<1, 2>(stage2, a, ex, x, f32, stream);
+        case 9: return launch_shape<1, 1>(stage2, a, ex, x, f32, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+hipError_t tsvd_fp6_split_launch(int shape, bool stage2, const gemm_args& a, int ex, hipStream_t stream) {
+    return launch_any(shape, stage2, a, ex, nullptr, false, stream);
+}
+// Two steps of 16 records hold all of x of a token tile.
+bool tsvd_fp6_split_makes_x(int shape, int blocks) { return shape != 0 && blocks * (shape & 7) <= 32; }
+hipError_t tsvd_fp6_split_launch_x(int shape, const gemm_args& a, const void* x, bool f32, bool token_major, long long ld, int N, hipStream_t stream) {
+    const split_x xs = {x, ld, token_major, N};
+    return launch_any(shape, false, a, 0, &xs, f32, stream);
+}
+
+hipError_t tsvd_fp6_split_planes(const void* x, bool f32, bool token_major, long long ld, int N, int B, int blocks, unsigned char* planes,
+                                 hipStream_t stream) {
+    const dim3 grid((unsigned)((B + 63) / 64), (unsigned)blocks), block(256);
+    if (f32) hipLaunchKernelGGL(tsvd_planes_kernel<true>, grid, block, 0, stream, x, ld, (int)token_major, N, B, blocks, planes);
+    else hipLaunchKernelGGL(tsvd_planes_kernel<false>, grid, block, 0, stream, x, ld, (int)token_major, N, B, blocks, planes);
+    return hipGetLastError();
+}

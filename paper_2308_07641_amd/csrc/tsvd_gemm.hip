@@ -1325,6 +1325,7 @@ bool tsvd_gemm_use_panel(long long Mp, long long Kp, long long Np, long long B, 
 hipError_t tsvd_gemm_init() {
     hipError_t e;
     if ((e = tsvd_fp6_init()) != hipSuccess) return e;
+    if ((e = tsvd_fp6_split_init()) != hipSuccess) return e;
     if ((e = init_gemm<2, 4, 8, 4, false>()) != hipSuccess) return e;
     if ((e = init_gemm<2, 4, 8, 4, true>()) != hipSuccess) return e;
     if ((e = init_gemm<2, 2, 8, 4, false>()) != hipSuccess) return e;
@@ -1420,44 +1421,7 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
     a2.npairs = pairs_k;
     a2.last_steps = hd.K % 128 == 0 ? 4 : (int)((hd.K % 128 + 31) / 32);
 
-    if (g.x_f32) {
-        // fp32 activations: six planes of x (three, and three more for what those leave), both stages on fp4 codes x fp6
-        // planes with the second set of planes as further blocks of the contraction (same code words again), stage V
-        // writing six planes of z from its fp32 accumulators.  Workspace: planes of x, then planes of z.
-        const size_t xp_bytes = tsvd_gemm_fp6_bytes(256ll * pairs_n, Bp), zp_bytes = tsvd_gemm_fp6_bytes(256ll * pairs_k, Bp);
-        if (xp_bytes >= (1ull << 31) || zp_bytes >= (1ull << 31)) return hipErrorNotSupported;
-        unsigned char* xplanes = static_cast<unsigned char*>(g.ws);
-        unsigned char* zplanes = xplanes + ((xp_bytes + 255) & ~(size_t)255);
-        const int mask = tsvd_stage_mask();
-        hipError_t e = hipSuccess;
-        if (mask & 1)
-            if ((e = tsvd_fp6_launch_planes_f32(static_cast<const float*>(g.x), g.ldx, (int)hd.N, (int)g.B, pairs_n, xplanes, stream)) != hipSuccess) return e;
-        if (mask & 2) {
-            gemm_args a4 = a1;
-            a4.act = reinterpret_cast<const uint16_t*>(xplanes);
-            a4.act_bytes = (unsigned)xp_bytes;
-            a4.npairs = 2 * pairs_n;
-            a4.code_blocks = pairs_n;
-            a4.plane_blocks = 2 * pairs_n;
-            a4.out = zplanes;
-            a4.ld_out = 2 * pairs_k;
-            a4.two_sets = pairs_k;
-            a4.colmax = nullptr;
-            if ((e = tsvd_fp6_launch_direct(a4, hd.Kp, g.cu_count, stream)) != hipSuccess) return e;
-        }
-        if (mask & 4) {
-            gemm_args a3 = a2;
-            a3.act = reinterpret_cast<const uint16_t*>(zplanes);
-            a3.act_bytes = (unsigned)zp_bytes;
-            a3.npairs = 2 * pairs_k;
-            a3.code_blocks = pairs_k;
-            a3.plane_blocks = 2 * pairs_k;
-            a3.colmax = nullptr;
-            e = tsvd_fp6_launch(true, a3, hd.Mp, Bp, out_variant(a3.bias, a3.out_bf16, a3.out_token_major), g.cu_count, stream);
-        }
-        return e;
-    }
-    if (tsvd_stage_mask() == 7 && tsvd_gemm_use_panel(hd.Mp, hd.Kp, hd.Np, g.B, g.cu_count, fast1)) {
+    if (!g.split && tsvd_stage_mask() == 7 && tsvd_gemm_use_panel(hd.Mp, hd.Kp, hd.Np, g.B, g.cu_count, fast1)) {
         panel_args pa;
         pa.tiles_v = a1.tiles;
         pa.tiles_u = a2.tiles;
@@ -1502,6 +1466,47 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
             else hipLaunchKernelGGL((tsvd_panel_kernel<8>), pgrid, dim3(512), TSVD_PANEL_LDS(8), stream, pa);
         }
         return hipGetLastError();
+    }
+    if (g.split) {
+        // Planes of x (any layout, in place), stage V from planes to planes of z, stage U from those.  fp32 activations: six planes
+        // (three, and three more for what those leave) of either, the second set as further blocks of the contraction (same code
+        // words again).  Workspace: planes of x, then planes of z.
+        const int sets = g.x_f32 ? 2 : 1;
+        const size_t xp_bytes = tsvd_gemm_fp6_bytes(128ll * sets * pairs_n, tsvd_round_up(g.B, 128)),
+                     zp_bytes = tsvd_gemm_fp6_bytes(128ll * sets * pairs_k, tsvd_round_up(g.B, 128));
+        if (xp_bytes >= (1ull << 31) || zp_bytes >= (1ull << 31)) return hipErrorNotSupported;
+        unsigned char* xplanes = static_cast<unsigned char*>(g.ws);
+        unsigned char* zplanes = xplanes + ((xp_bytes + 255) & ~(size_t)255);
+        const int mask = tsvd_stage_mask();
+        hipError_t e = hipSuccess;
+        const bool own_x = tsvd_fp6_split_makes_x(g.split_v, sets * pairs_n) && env_cfg("TSVD_SPLIT_X", 1) != 0;
+        if ((mask & 1) && !own_x)
+            if ((e = tsvd_fp6_split_planes(g.x, g.x_f32 != 0, g.x_token_major != 0, g.ldx, (int)hd.N, (int)g.B, pairs_n, xplanes, stream)) != hipSuccess) return e;
+        if (mask & 2) {
+            gemm_args a4 = a1;
+            a4.act = reinterpret_cast<const uint16_t*>(xplanes);
+            a4.act_bytes = (unsigned)xp_bytes;
+            a4.npairs = a4.plane_blocks = sets * pairs_n;
+            a4.code_blocks = g.x_f32 ? pairs_n : 0;
+            a4.out = zplanes;
+            a4.ld_out = sets * pairs_k;
+            a4.two_sets = g.x_f32 ? pairs_k : 0;
+            a4.colmax = nullptr;
+            e = own_x ? tsvd_fp6_split_launch_x(g.split_v, a4, g.x, g.x_f32 != 0, g.x_token_major != 0, g.ldx, (int)hd.N, stream)
+                : g.split_v ? tsvd_fp6_split_launch(g.split_v, false, a4, 0, stream) : tsvd_fp6_launch_direct(a4, hd.Kp, g.cu_count, stream);
+            if (e != hipSuccess) return e;
+        }
+        if (mask & 4) {
+            gemm_args a3 = a2;
+            a3.act = reinterpret_cast<const uint16_t*>(zplanes);
+            a3.act_bytes = (unsigned)zp_bytes;
+            a3.npairs = a3.plane_blocks = sets * pairs_k;
+            a3.code_blocks = g.x_f32 ? pairs_k : 0;
+            a3.colmax = nullptr;
+            const int ex = out_variant(a3.bias, a3.out_bf16, a3.out_token_major);
+            e = g.split_u ? tsvd_fp6_split_launch(g.split_u, true, a3, ex, stream) : tsvd_fp6_launch(true, a3, hd.Mp, Bp, ex, g.cu_count, stream);
+        }
+        return e;
     }
     int cfg1 = env_cfg("TSVD_GEMM_CFG_V", tsvd_gemm_tile_shape(hd.Kp, g.B, g.cu_count, fast1));
     int cfg2 = env_cfg("TSVD_GEMM_CFG_U", tsvd_gemm_tile_shape(hd.Mp, g.B, g.cu_count, true));

@@ -270,9 +270,17 @@ hipError_t tsvd_fp6_launch(bool stage2, const gemm_args& a, long long rows_p, in
 // stage V writing the planes of z itself (a.out = those planes, a.ld_out = 128-index blocks per token group), where its tile allows
 bool tsvd_fp6_direct_possible(long long rows_p, long long bvalid, long long cus);
 hipError_t tsvd_fp6_launch_direct(const gemm_args& a, long long rows_p, long long cus, hipStream_t stream);
-// fp32 x [rows_valid][ld] -> two sets of planes (six planes), `blocks` blocks each, layout of 2 * blocks blocks per token group
-hipError_t tsvd_fp6_launch_planes_f32(const float* x, long long ld, int rows_valid, int cols_valid, int blocks, unsigned char* planes,
-                                      hipStream_t stream);
+// ---- tsvd_fp6_split.hip --------------------------------------------------------------------------------------------
+hipError_t tsvd_fp6_split_init();
+// x [N][ld] (bf16 or fp32; token_major: [B][ld]) -> plane records of `blocks` blocks, `blocks` per token group (fp32: two sets, six
+// planes, the second `blocks` behind the first in a layout of 2 * blocks per token group)
+hipError_t tsvd_fp6_split_planes(const void* x, bool f32, bool token_major, long long ld, int N, int B, int blocks, unsigned char* planes,
+                                 hipStream_t stream);
+// one stage (a.act = planes in a layout of a.plane_blocks per token group; stage V: a.out = planes of z, a.ld_out per token group)
+hipError_t tsvd_fp6_split_launch(int shape, bool stage2, const gemm_args& a, int ex, hipStream_t stream);
+// stage V making the planes of x itself (a.act is not read): whether a shape can for that many blocks (fp32: both sets), and the launch
+bool tsvd_fp6_split_makes_x(int shape, int blocks);
+hipError_t tsvd_fp6_split_launch_x(int shape, const gemm_args& a, const void* x, bool f32, bool token_major, long long ld, int N, hipStream_t stream);
 // the token-panel launch on fp4 codes x fp6 planes
 hipError_t tsvd_fp6_launch_panel(const panel_args& pa, int ex, hipStream_t stream);
 #endif  // TSVD_GEMM_COMMON_H

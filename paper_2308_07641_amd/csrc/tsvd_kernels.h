@@ -128,6 +128,7 @@ hipError_t tsvd_launch_mid(const tsvd_mid_args& a, bool stage_u, bool vec, hipSt
 // read code words themselves).
 struct tsvd_handle;
 const uint8_t* tsvd_internal_blob(const tsvd_handle* h, const struct tsvd_blob_header** hd);
+int tsvd_internal_cu_count(const tsvd_handle* h);
 
 hipError_t tsvd_transition_init();   // kernel attributes of tsvd_transition.hip
 
@@ -138,8 +139,10 @@ struct tsvd_gemm_problem {
     float bound_V;                  // |z[k][b]| <= bound_V * max_n |x[n][b]|
     const void* x;                  // device bf16 [N][ldx], or [B][ldx] with x_token_major
     long long B, ldx;
-    int x_token_major;              // only where tsvd_gemm_reads_token_major says so
-    int x_f32;                      // x is fp32 [N][ldx] (six planes; the fp4 x fp6 kernels)
+    int x_token_major;              // only on the plane path and where tsvd_gemm_reads_token_major says so
+    int x_f32;                      // x is fp32 (six planes; always on the plane path)
+    bool split;                     // the plane path, with these tiles (tsvd_batch.h)
+    int split_v, split_u;
     void* y;                        // device fp32 (or bf16 with out_bf16) [M][ldy]
     long long ldy;
     const float* bias;              // device [M] added per output row, or null
@@ -164,10 +167,13 @@ bool tsvd_gemm_reads_token_major(long long Mp, long long Kp, long long Np, long 
 // Stage U through fp6 planes of Z: whether a call takes it, and the extra workspace it needs after Z.
 bool tsvd_gemm_use_fp6(long long Mp, long long Kp, long long Np, long long B, long long cus, bool aligned);
 size_t tsvd_gemm_fp6_bytes(long long Kp, long long Bp);
+// Workspace of the plane path (planes of x, then of z; see tsvd_batch.h).
+size_t tsvd_gemm_split_bytes(long long K, long long N, long long B, bool f32);
 // Stage V through fp6 planes of x (only together with the above; its planes follow those of Z).
 bool tsvd_gemm_use_fp6_v(long long Mp, long long Kp, long long Np, long long B, long long cus, bool aligned);
 #define TSVD_COLMAX_PARTS 16
 // Diagnostic switches (include/tsvd_tuning.h): value set by tsvd_tuning_set in this process, else the
 // fallback.  The library never reads the environment.
 int tsvd_tune(const char* name, int fallback);
+bool tsvd_tuning_any();   // any switch is set
 int tsvd_stage_mask();   // stages the current call runs (7 = all; partial only inside tsvd_tuning_forward_stages)

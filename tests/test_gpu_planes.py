@@ -1,0 +1,57 @@
+"""The plane path's split tiles at the edges of their tiles, against the oracle: exact on
+integer instances (every layout, bias and output type), within a fraction of the tolerance on random ones."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_util import rel_err, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tsvd():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: the HIP path has no fallback")
+    import paper_2308_07641_amd as t
+    t.load_library()
+    return t
+
+
+def _check(tsvd, M, N, K, B, x_dtype, switches):
+    import torch
+    i = workloads.make_integer_inputs(M, N, K, B, 0.5, x_dtype, seed=M + N + K + B)
+    ref = oracle.forward(i.U, i.S, i.V, i.X)
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    for k, v in switches.items():
+        tsvd.tsvd_tuning_set(k, v)
+    x = to_device(i)
+    assert np.array_equal(tsvd.tsvd_forward(h, x).cpu().numpy(), ref)
+    bias = np.arange(M, dtype=np.float32) % 7 - 3
+    wide = torch.full((B, N + 3), float("nan"), dtype=x.dtype, device="cuda:0")       # rows of tokens, not 16-byte aligned, NaN beyond
+    wide[:, :N] = x.t()
+    y = tsvd.tsvd_forward_io(h, wide[:, :N], x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR, bias=torch.from_numpy(bias).to("cuda:0"))
+    assert np.array_equal(y.cpu().numpy().T, ref + bias[:, None])
+    y = tsvd.tsvd_forward_io(h, x.t().contiguous(), x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR, y_dtype=tsvd.TSVD_BF16)
+    assert torch.equal(y.cpu(), torch.from_numpy(np.ascontiguousarray(ref.T)).to(torch.bfloat16))
+    y = tsvd.tsvd_forward_ex(h, x[:, :B - 1], y_dtype=tsvd.TSVD_BF16)                 # a row pitch longer than the row
+    assert torch.equal(y.cpu(), torch.from_numpy(ref[:, :B - 1].copy()).to(torch.bfloat16))
+    tsvd.tsvd_free(h)
+    j = workloads.make_inputs(M, N, K, B, 0.6, 0.02, x_dtype, seed=M + 2 * N + K + B)
+    h = tsvd.tsvd_pack(j.U, j.S, j.V)
+    e = rel_err(tsvd.tsvd_forward(h, to_device(j)).cpu().numpy().astype(np.float64), oracle.forward(j.U, j.S, j.V, j.X))
+    assert e <= (1e-6 if x_dtype == "f32" else 1e-4)
+    tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("own_x", [0, 1])
+@pytest.mark.parametrize("v,u", [(9, 10), (10, 18), (18, 20), (20, 9), (0, 9), (20, 0)])
+@pytest.mark.parametrize("M,N,K,B", [(130, 64, 60, 65), (515, 300, 777, 130), (256, 1300, 2500, 17)])
+def test_split_tiles(tsvd, M, N, K, B, v, u, own_x, x_dtype):
+    """One block and many, rows and tokens beside a tile's multiple, more steps than groups of wavefronts; planes of x made by
+    stage V or by their own pass."""
+    print(f"case split {M} {N} {K} {B} {v} {u} {own_x} {x_dtype}", flush=True)
+    _check(tsvd, M, N, K, B, x_dtype, {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_SPLIT_V": v, "TSVD_SPLIT_U": u, "TSVD_SPLIT_X": own_x})
