@@ -90,6 +90,8 @@ def _stage_u_kernel_name(tsvd, handle, B):
         return "tsvd_panel_kernel", su
     if su == 33:
         return "tsvd_panel_fp6_kernel", su
+    if su == 34:
+        return "tsvd_thin_panel_kernel", su
     if su >= 100:
         return "tsvd_fp6_split_kernel", su
     if su == 40:

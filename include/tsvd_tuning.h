@@ -30,9 +30,9 @@ extern "C" {
  *   stage V always writes fp16 z for a separate pass to turn into planes), TSVD_FP6_TAIL (0: no narrower tiles in the
  *   last round of a launch of 512 x 64 tiles), TSVD_TOKEN_MAJOR_COPY (1: token-major
  *   activations are always copied to feature-major rows first, also for the kernels that can read them in place),
- *   TSVD_SPLIT_V / TSVD_SPLIT_U (tiles of the plane path's stages: 9, 10, 18, 20 =
+ *   TSVD_THIN (1, 2: thin token panels of 16 or 32 tokens), TSVD_SPLIT_V / TSVD_SPLIT_U (tiles of the plane path's stages: 9, 10, 18, 20 =
  *   rows / 128 * 8 + tokens / 16), TSVD_SPLIT_X (0: planes of x always by a pass of their own).  While any switch is set a batch runs on
- *   split tiles only if these ask for them,
+ *   thin panels or split tiles only if these ask for them,
  *   TSVD_GROUPED_PAIR,
  *   TSVD_CLOCKS (1 at tsvd_pack: record phase timestamps per workgroup), TSVD_SPIN_LIMIT (bound of the
  *   single-launch kernels' wait for another workgroup's slice of z, in polls), TSVD_DENSE_U (1 at tsvd_pack: keep a
@@ -53,7 +53,8 @@ tsvd_status tsvd_tuning_forward_stages(const tsvd_handle* h, const void* x_dev, 
                                        int64_t ldy, void* workspace, size_t workspace_bytes, void* stream, int stage_mask);
 
 /* The tile shapes tsvd_forward picks for B tokens of 16-byte-aligned bf16 activations (stage V, stage U):
- * 0..3 / 14..17 as above, 32 / 33 for both when the call is one token-panel launch (16-bit operands / fp4 codes x fp6 planes), 100 + tile (TSVD_SPLIT_V) on the plane path, 40 for the other fp4 x fp6 kernels of the two-launch path,
+ * 0..3 / 14..17 as above, 32 / 33 for both when the call is one token-panel launch (16-bit operands / fp4 codes x fp6 planes), 34 for both when it
+ * is one launch of thin token panels, 100 + tile (TSVD_SPLIT_V) on the plane path, 40 for the other fp4 x fp6 kernels of the two-launch path,
  * -1 where the batched kernels are not used.  Returns 0 on success. */
 int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* shape_v, int* shape_u);
 

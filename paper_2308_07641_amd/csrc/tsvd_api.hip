@@ -14,6 +14,7 @@
 #include "tsvd_batch.h"
 #include "tsvd_kernels.h"
 #include "tsvd_layout.h"
+#include "tsvd_thin.h"
 
 struct tsvd_handle {
     int device;
@@ -98,6 +99,8 @@ hipError_t device_init(int device) {
     e = tsvd_skinny_init();
     if (e != hipSuccess) return e;
     e = tsvd_gemm_init();
+    if (e != hipSuccess) return e;
+    e = tsvd_thin_init();
     if (e != hipSuccess) return e;
     e = tsvd_gemv_init();
     if (e != hipSuccess) return e;
@@ -673,6 +676,24 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
     tsvd_batch_plan plan = {};
     if (batched && !few)
         plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16);
+    if (plan.thin) {
+        // thin token panels: one launch, x in any layout and alignment, no workspace
+        tsvd_thin_problem t = {};
+        t.blob = h->blob;
+        t.hd = &h->hd;
+        t.x = static_cast<const uint16_t*>(x_dev);
+        t.source = x_layout == TSVD_TOKEN_MAJOR ? THIN_TOKEN_MAJOR : THIN_FEATURE_MAJOR;
+        t.B = B;
+        t.ldx = ldx;
+        t.y = y_dev;
+        t.ldy = ldy;
+        t.bias = bias_dev;
+        t.out_bf16 = oo.out_bf16;
+        t.y_token_major = oo.token_major;
+        t.cu_count = h->cu_count;
+        const hipError_t te = tsvd_thin_launch(t, plan.thin, s);
+        if (te != hipErrorNotSupported) return te == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
+    }
     if (x_layout == TSVD_TOKEN_MAJOR && (plan.split || (x_dtype == TSVD_BF16 && batched && !few &&
                                                         tsvd_gemm_reads_token_major(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count)))) {
         x_in_place = 1;       // the kernels this call takes gather their operand lanes from [B][ldx] themselves
@@ -770,7 +791,7 @@ const char* const tuning_names[] = {
     "TSVD_GEMV", "TSVD_GEMV_FUSED", "TSVD_GEMV_ONEPASS", "TSVD_GEMV_SW", "TSVD_GEMV_KWLOG2", "TSVD_SKINNY_SW", "TSVD_SKINNY_KW",
     "TSVD_MID", "TSVD_MID_MAX_B", "TSVD_MID_SW", "TSVD_MID_KWLOG2", "TSVD_MID_RESIDENT", "TSVD_GEMM_MIN_B", "TSVD_GEMM_MIN_B_F32",
     "TSVD_GEMM_CFG_V", "TSVD_GEMM_CFG_U", "TSVD_FUSEMAX", "TSVD_COLMAX_SCALAR", "TSVD_REALIGN", "TSVD_PANEL",
-    "TSVD_PANEL_WAVES", "TSVD_PANEL_FP6", "TSVD_FP6", "TSVD_FP6_V", "TSVD_FP6_TALL", "TSVD_FP6_PLANES", "TSVD_FP6_DIRECT", "TSVD_FP6_TAIL", "TSVD_SPLIT_V", "TSVD_SPLIT_U", "TSVD_SPLIT_X", "TSVD_TOKEN_MAJOR_COPY", "TSVD_GROUPED_PAIR", "TSVD_CLOCKS",
+    "TSVD_PANEL_WAVES", "TSVD_PANEL_FP6", "TSVD_FP6", "TSVD_FP6_V", "TSVD_FP6_TALL", "TSVD_FP6_PLANES", "TSVD_FP6_DIRECT", "TSVD_FP6_TAIL", "TSVD_SPLIT_V", "TSVD_SPLIT_U", "TSVD_SPLIT_X", "TSVD_THIN", "TSVD_TOKEN_MAJOR_COPY", "TSVD_GROUPED_PAIR", "TSVD_CLOCKS",
     "TSVD_SPIN_LIMIT", "TSVD_DENSE_U", "TSVD_EARLY_TILES"};
 constexpr int tuning_count = (int)(sizeof tuning_names / sizeof tuning_names[0]);
 int tuning_value[tuning_count];
@@ -822,7 +843,9 @@ extern "C" int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* s
     if (use_mid(h, B, TSVD_BF16, tsvd_round_up(B, 8))) return 0;
     if (use_gemm(h, B, TSVD_BF16)) {
         const tsvd_batch_plan plan = batch_plan(h, B, TSVD_BF16, false, false, false, false);
-        if (plan.split) {
+        if (plan.thin) {
+            *shape_v = *shape_u = 34;
+        } else if (plan.split) {
             *shape_v = plan.split_v ? 100 + plan.split_v : 40;
             *shape_u = plan.split_u ? 100 + plan.split_u : 40;
         } else if (tsvd_gemm_use_panel(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count, true)) {

@@ -9,6 +9,7 @@ struct tsvd_batch_call {
     bool whole;                     // both stages run (no diagnostic stage mask)
 };
 struct tsvd_batch_plan {
+    int thin;                       // token tiles of a thin panel (tsvd_thin.hip), 0: not on those
     bool split;                     // planes of x, stage V to planes of z, stage U from those (the plane path of tsvd_forward_gemm) ...
     int split_v, split_u;           // ... with these shapes of tsvd_fp6_split_launch, 0: the launches of tsvd_fp6.hip
 };

@@ -1,15 +1,15 @@
 // The choice among the batched kernels, by estimates of their times.
 //
-// Three ways serve a batch: planes of x with tiles of
+// Four ways serve a batch: thin token panels (both stages in one launch, 16 or 32 tokens per workgroup), planes of x with tiles of
 // tsvd_fp6_split.hip per stage (128 x 16 to 256 x 64, the contraction split over groups of wavefronts), the same with the tiles of
 // tsvd_fp6.hip (many rows and tokens), and the ring and large-tile kernels of tsvd_gemm.hip on 16-bit operands.  No single quantity
 // separates them: a launch with few workgroups is bound by its serial chain (steps of a workgroup's loop), one with many by
-// matrix instructions.  So each gets an estimate in microseconds, a sum of
+// matrix instructions, a thin panel by the code words it streams.  So each gets an estimate in microseconds, a sum of
 // the quantities that bound it: the launch, rounds of workgroups over the compute units, loop steps, records of x made, code bytes.
 // The factors are fits (non-negative least squares on relative errors) to measurements on MI355X of 1200 bf16 calls, 160 fp32 calls and 600
-// convolutions of random shapes (17 to 16384 tokens, factors of 1 KB to 64 MB), 24 ways each; the estimates' standard error is 10 to 16 %.
+// convolutions of random shapes (17 to 16384 tokens, factors of 1 KB to 64 MB), 26 ways each; the estimates' standard error is 10 to 16 %.
 // Picking the smallest is within 4 % of the best way on the average of those calls and 1.22 times the speed of always
-// taking the older ones (fp32 2 to 4).
+// taking the older ones (convolutions 1.34, fp32 2 to 4).
 #include "tsvd_batch.h"
 
 #include <algorithm>
@@ -17,6 +17,7 @@
 
 #include "tsvd_gemm_common.h"
 #include "tsvd_kernels.h"
+#include "tsvd_thin.h"
 
 namespace {
 
@@ -73,6 +74,22 @@ double split_u_cost(const sizes& s, const split_factors* f) {
     return f->u0 + r * f->u_round + r * steps(f->shape, s.sets * s.nub) * f->u_step;
 }
 
+// ---- thin panels ----------------------------------------------------------------------------------
+double thin_cost(const tsvd_batch_call& c, int tiles) {
+    const long long nvb = up(c.N, 128), nub = up(c.K, 128), panels = up(c.B, 16 * tiles);
+    const double r = (double)up(panels, c.cus), busy = (double)std::min(panels, c.cus) / (double)c.cus;
+    long long passes = 1ll << 60, units = 0;         // 16-row blocks of stage U per wavefront, and the units they come in
+    for (int utm : {8, 4, 2}) {
+        const long long u = up(up(c.M, 16 * utm), 8);
+        if (u * utm < passes) passes = u * utm, units = u;
+    }
+    const double Kp = (double)tsvd_round_up(c.K, 256), mb_u = Kp * (double)tsvd_round_up(c.M, 256) / 4e6, mb_v = Kp * (double)tsvd_round_up(c.N, 256) / 4e6;
+    const double records = r * (double)up(nvb * tiles, 8), gather = c.conv ? 1 : 0, scalar = c.x_token_major && c.N % 8 ? 1 : 0;
+    const double v = r * (double)(up(nub, 8) * nvb), u = r * (double)(passes * nub) / 8, y = r * (double)passes * (c.out_bf16 ? 0.5 : 1) * (c.y_token_major ? 2.6 : 1);
+    if (tiles == 1) return 1.2 + 3.2 * r + records * (1.5 * scalar + 1.6 * gather) + 0.57 * v + 0.29 * u + 0.35 * r * (double)units + 11.2 * r * mb_u + 8.1 * busy * r * (mb_u + mb_v) + 0.08 * y;
+    return 1.4 + 3.7 * r + records * (2.1 * scalar + 0.92 * gather) + 0.92 * v + 0.45 * u + 0.34 * r * (double)units + 25.1 * r * mb_u + 13.3 * busy * r * (mb_u + mb_v) + 0.10 * y;
+}
+
 // ---- ring and large-tile kernels ----------------------------------------------------------------
 double older_cost(const tsvd_batch_call& c) {
     double t = 7.3;
@@ -105,10 +122,11 @@ size_t tsvd_gemm_split_bytes(long long K, long long N, long long B, bool f32) {
 }
 
 tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
-    tsvd_batch_plan plan = {c.f32, 0, 0};
+    tsvd_batch_plan plan = {0, c.f32, 0, 0};
     if (tsvd_tuning_any()) {        // a diagnostic that sets switches means the kernels that they select
-        const int v = tsvd_tune("TSVD_SPLIT_V", 0), u = tsvd_tune("TSVD_SPLIT_U", 0);
-        if (v > 0 || u > 0) plan = {true, v, u};
+        const int thin = tsvd_tune("TSVD_THIN", 0), v = tsvd_tune("TSVD_SPLIT_V", 0), u = tsvd_tune("TSVD_SPLIT_U", 0);
+        if (thin > 0 && !c.f32 && c.whole) plan.thin = thin;
+        if (v > 0 || u > 0) plan = {plan.thin, true, v, u};
         return plan;
     }
     const long long Mp = tsvd_round_up(c.M, 256), Kp = tsvd_round_up(c.K, 256), Np = tsvd_round_up(c.N, 256);
@@ -136,7 +154,14 @@ tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
     const bool fits = !panel && tsvd_gemm_split_bytes(c.K, c.N, c.B, false) < (1ull << 31);
     if (fits && (v || u) && best_v + best_u + columns < best) {
         best = best_v + best_u + columns;
-        plan = {true, v, u};
+        plan = {0, true, v, u};
     }
+    // (every panel streams both factors: measured for code words that one XCD's L2 holds)
+    if (c.whole && c.K * (c.M + c.N) <= (16ll << 20))
+        for (int tiles : {1, 2})
+            if (tsvd_thin_chunk(c.K, c.N, tiles, c.conv) > 0) {
+                const double t = thin_cost(c, tiles);
+                if (t < best) best = t, plan.thin = tiles;
+            }
     return plan;
 }

@@ -75,3 +75,38 @@ __device__ __forceinline__ void tsvd_store_token_major4(void* y, long long ld, i
     for (int e = 0; e < 4; ++e)
         if (row0 + e < rows_valid) tsvd_store_y(y, at + e, v[e], out_bf16);
 }
+
+// Token-major bf16 output of four 16 x 16 result blocks below each other (rows row0 .. row0 + 63; a lane (i, g) holds token i of
+// rows 16 a + 4 g .. + 3 of block a as two packed words d[a]): the four lane groups transpose their pieces (two swaps of lane
+// rows per word), after which lane group g holds all sixteen rows of block g and stores them as 32 consecutive bytes: 128 bytes per
+// token and store pair where the plain form writes 32.  All 64 lanes must call it; rows and alignment are the caller's concern.
+__device__ __forceinline__ void tsvd_store_token_major_bf16_4x16(void* y, long long ld, int token, bool token_ok, int row0, int g, uint32_t (&d)[4][2]) {
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        auto swap16 = [&](int a, int b) {
+            const auto r = __builtin_amdgcn_permlane16_swap(d[a][w], d[b][w], false, false);
+            d[a][w] = r[0];
+            d[b][w] = r[1];
+        };
+        auto swap32 = [&](int a, int b) {
+            const auto r = __builtin_amdgcn_permlane32_swap(d[a][w], d[b][w], false, false);
+            d[a][w] = r[0];
+            d[b][w] = r[1];
+        };
+        swap16(0, 1);
+        swap16(2, 3);
+        swap32(0, 2);
+        swap32(1, 3);
+    }
+    if (token_ok) {
+        u32x4_t* dst = reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(y) + (size_t)token * ld + row0 + 16 * g);
+        dst[0] = u32x4_t{d[0][0], d[0][1], d[1][0], d[1][1]};
+        dst[1] = u32x4_t{d[2][0], d[2][1], d[3][0], d[3][1]};
+    }
+}
+__device__ __forceinline__ uint32_t tsvd_pack_bf16(float lo, float hi) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
+}

@@ -1,0 +1,454 @@
+// Both stages of a batch in one launch: Y = U (S (V X)) for 16 or 32 tokens per workgroup, on fp4 codes x fp6 planes.
+//
+// The token-panel kernel of tsvd_fp6.hip gives a workgroup 64 tokens and holds x and then z in LDS, which bounds N and K by 1024
+// and needs some 10000 tokens to reach most compute units.  A panel of 16 (32) tokens needs a quarter (half) of both: K + N of
+// thousands fit, and 200 panels are 3200 tokens.  Against separate stages it saves the operand pass, the round trip of z, two launches
+// with their ramps, and the stores of y run while other units multiply (a stage whose tiles all end together pays for
+// them on top: 10 of 54 us on a 16384 x 8192 stage of 256 tokens).  Every workgroup streams all code words, so
+// they have to stay in the L2s.
+//
+// Eight wavefronts.  Planes of x are made block by block (a wavefront per record: gather, convert); wavefront w multiplies the
+// rank blocks w, w + 8, ... of stage V (128 rows x the panel; its result lanes are stage U's operand lanes, see tsvd_panel_fp6_kernel)
+// and writes their planes of z beside those of x; then stage U runs in units of 16 UTM rows, no barrier between them.
+// Where x does not fit beside z its blocks pass through in chunks, two in LDS: four of the wavefronts multiply the one before
+// they make their records of the next, the other four after, so that on every SIMD matrix and vector instructions overlap.
+// Code words go from the L2s to registers, one fetch ahead across rank blocks and units (those of the next unit are in
+// before a unit's stores are issued: loads and stores share one counter); a fetch is 16 bytes per lane and strip, the words of
+// 256 contraction indices.
+// A convolution's columns are gathered straight from the images: a table of offsets per index in LDS, and per token a bit
+// mask of the taps that fall outside its image.
+// Measured on MI355X: 3072 x 768 x 1545 bf16 at 3152 tokens, token-major: 71.5 -> 39.2 us (ring kernels with a copy of x before; 16 tokens per panel); the
+// map of a 3 x 3 convolution, 256 x 2304 x 768 at 6272 positions: 75.5 -> 36.8 us (columns written and read before; 32).
+// What bounds them: the matrix instructions of the panels' last round, and the code words that every workgroup pulls from its L2.
+#include "tsvd_thin.h"
+
+#include <algorithm>
+#include <type_traits>
+
+#include "tsvd_fp6_common.h"
+
+namespace {
+
+struct thin_args {
+    const uint32_t *tiles_v, *tiles_u;
+    unsigned tile_v_bytes, tile_u_bytes;
+    int nkt_v, nkt_u, nvb, nub;              // tiles of 256 per strip; 128-index blocks of N and K that hold anything
+    const uint16_t* x;
+    unsigned x_bytes;                        // below 2^31
+    int N, B, chunk, buffers;        // blocks of x per chunk, chunks in LDS (1: all of x, or 2)
+    long long ldx;
+    int images, H, W, kv1, kv2, Hv, Wv, s1, s2, p1, p2, d1, d2;
+    const float* S;
+    void* y;
+    long long ldy;
+    const float* bias;
+    int M, out_bf16, token_major, utm;       // utm: 16-row blocks per unit of stage U
+};
+
+template <int TN, int RB, int SOURCE, bool CHUNKED>
+__global__ void __launch_bounds__(512, 2)
+tsvd_thin_panel_kernel(thin_args p) {
+    constexpr int NW = 8;
+    using words = u32x4;
+    extern __shared__ __align__(16) unsigned char smem[];    // records [block][tile]: chunk blocks of x, then nub blocks of z
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
+    const int b0 = blockIdx.x * 16 * TN;
+    unsigned char* xrec = smem;
+    unsigned char* zrec = smem + p.buffers * p.chunk * TN * FP6_REC_BYTES;
+    const int* ktab = reinterpret_cast<const int*>(zrec + p.nub * TN * FP6_REC_BYTES);   // THIN_CONV: byte offset of index k in the images
+    const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles_v), 0, p.tile_v_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t u_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles_u), 0, p.tile_u_bytes, 0x00020000);
+
+    // ---- the record of (block, tile) of x, by one wavefront.  What does not exist (indices beyond N, taps outside the image) is
+    // read at an offset beyond the buffer, where loads give zero; tokens beyond the batch repeat the last one (never stored)
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.x), 0, p.x_bytes, 0x00020000);
+    int conv_base = 0;                       // THIN_CONV: byte offset of this lane's token (its tile is the wavefront's), and the taps outside its
+    uint64_t conv_outside = 0;               // image as a bit mask, repeated with the period of the taps
+    if constexpr (SOURCE == THIN_CONV) {
+        const int taps = p.kv1 * p.kv2, channel = p.images * p.H * p.W;
+        for (int k = threadIdx.x; k < 128 * p.nvb; k += 512) {
+            const int t = k / p.kv2, dx = k - t * p.kv2, ci = t / p.kv1, dy = t - ci * p.kv1;
+            const_cast<int*>(ktab)[k] = k < p.N ? 2 * (ci * channel + dy * p.d1 * p.W + dx * p.d2) : (int)0x80000000;
+        }
+        const int tok = min(b0 + 16 * (wave % TN) + i, p.B - 1), plane = p.Hv * p.Wv, img = tok / plane, at = tok - img * plane, py = at / p.Wv,
+                  px = at - py * p.Wv, y0 = py * p.s1 - p.p1, x0 = px * p.s2 - p.p2;
+        conv_base = 2 * (img * p.H * p.W + y0 * p.W + x0);
+        for (int dy = 0; dy < p.kv1; ++dy)
+            for (int dx = 0; dx < p.kv2; ++dx)
+                if ((unsigned)(y0 + dy * p.d1) >= (unsigned)p.H || (unsigned)(x0 + dx * p.d2) >= (unsigned)p.W)
+                    for (int b = dy * p.kv2 + dx; b < 64; b += taps) conv_outside |= 1ull << b;
+        __syncthreads();
+    }
+    auto make_record = [&](int block, int tile, unsigned char* rec) __attribute__((always_inline)) {
+        int tok = min(b0 + 16 * tile + i, p.B - 1);
+        const int k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1);
+        asm volatile("" : "+v"(tok));                                // (what follows from it is formed here, not kept in registers over the MFMAs)
+        constexpr int NONE = (int)0x80000000;
+        float v[32];
+        uint16_t raw[32];
+        auto gather = [&](int e, int off) {
+            raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, off, 0, 0);
+            if (e % 8 == 7) __builtin_amdgcn_sched_barrier(0);      // (the offsets of all 32 at once would not fit the registers)
+        };
+        bool whole = false;                                         // v filled 16 bytes at a time
+        if constexpr (SOURCE == THIN_CONV) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = k0 + 32 * h, first = k % (p.kv1 * p.kv2);
+                const uint32_t out = (uint32_t)(conv_outside >> first);         // bit e: index k + e lies outside the image
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const i32x4 off = *reinterpret_cast<const i32x4*>(ktab + k + 4 * c);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) gather(16 * h + 4 * c + e, (off[e] + conv_base) | (int)((out << (31 - 4 * c - e)) & 0x80000000u));
+                }
+            }
+        } else if constexpr (SOURCE == THIN_TOKEN_MAJOR) {
+            const int row = 2 * tok * (int)p.ldx;
+            if (k0 + 48 <= p.N && !(p.ldx & 7) && !(reinterpret_cast<uintptr_t>(p.x) & 15)) {
+                u32x4 q[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) q[c] = buf_load128(x_rsrc, row + 2 * (k0 + 32 * (c >> 1) + 8 * (c & 1)), 0);
+#pragma unroll
+                for (int e = 0; e < 32; ++e) {
+                    const uint32_t w = q[e >> 3][(e & 7) >> 1];
+                    v[e] = __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
+                }
+                whole = true;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 32; ++e) {
+                    const int k = k0 + 32 * (e >> 4) + (e & 15);
+                    gather(e, (row + 2 * k) | (k < p.N ? 0 : NONE));
+                }
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 32; ++e) {
+                const int k = k0 + 32 * (e >> 4) + (e & 15);
+                gather(e, (2 * (k * (int)p.ldx + tok)) | (k < p.N ? 0 : NONE));
+            }
+        }
+        if (!whole) {
+#pragma unroll
+            for (int e = 0; e < 32; ++e) v[e] = __uint_as_float((uint32_t)raw[e] << 16);
+        }
+        tsvd_planes_of_32(v, rec, lane);
+    };
+
+    // ---- TM row blocks times blocks [0, count) of the records at recs.  w0: the next fetch of the stream of code words that
+    // next(words) continues, on return the one after the last pair's.  The operand of MFMA step t + 2 (a plane of a
+    // record, TM row blocks) is read before the MFMAs of step t.
+    auto run = [&](auto tm_c, const unsigned char* recs, int count, auto& w0, auto next, auto& acc) {
+        constexpr int TM = decltype(tm_c)::value, STEPS = 6 * TN;
+        words w1[TM];
+        u32x4 lo[3];
+        u32x2 hi[3];
+        uint32_t sc[2];
+        const int last = count * TN - 1;
+        auto read_step = [&](int pair, int st) {              // step st of the pair of blocks (3 per record)
+            const unsigned char* rec = recs + min(pair * 2 * TN + st / 3, last) * FP6_REC_BYTES;
+            const int pl = st % 3;
+            lo[pl] = *reinterpret_cast<const u32x4*>(rec + pl * 1024 + lane * 16);
+            hi[pl] = *reinterpret_cast<const u32x2*>(rec + 3072 + pl * 512 + lane * 8);
+            if (pl == 0) sc[(st / 3) & 1] = *reinterpret_cast<const uint32_t*>(rec + 4608 + lane * 4);
+        };
+        auto half = [&](int pair, auto h_c, const words (&w)[TM]) {        // one block of a pair
+            constexpr int h = decltype(h_c)::value, at = 2 * h;
+            u32x4 av[TM];
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+                av[a] = u32x4{(w[a][at] << 2) & 0xCCCCCCCCu, w[a][at] & 0xCCCCCCCCu, (w[a][at + 1] << 2) & 0xCCCCCCCCu, w[a][at + 1] & 0xCCCCCCCCu};
+#pragma unroll
+            for (int t = 0; t < 3 * TN; ++t) {
+                const int st = 3 * TN * h + t, b = t / 3, nx = st + 2;
+                read_step(pair + nx / STEPS, nx % STEPS);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int a = 0; a < TM; ++a) {
+                    switch (t % 3) {
+                        case 0: acc[a][b] = mfma_fp6<0>(av[a], lo[0], hi[0], sc[(st / 3) & 1], acc[a][b]); break;
+                        case 1: acc[a][b] = mfma_fp6<1>(av[a], lo[1], hi[1], sc[(st / 3) & 1], acc[a][b]); break;
+                        default: acc[a][b] = mfma_fp6<2>(av[a], lo[2], hi[2], sc[(st / 3) & 1], acc[a][b]); break;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        const std::integral_constant<int, 0> first{};
+        const std::integral_constant<int, 1> second{};
+        const int fetches = (count + 1) / 2;
+        read_step(0, 0);
+        read_step(0, 1);
+        for (int q = 0; q < fetches; q += 2) {
+            next(w1);
+            half(q, first, w0);
+            if (2 * q + 1 < count) half(q, second, w0);
+            if (q + 1 < fetches) {
+                next(w0);
+                half(q + 1, first, w1);
+                if (2 * q + 3 < count) half(q + 1, second, w1);
+            } else {
+#pragma unroll
+                for (int a = 0; a < TM; ++a) w0[a] = w1[a];
+            }
+        }
+    };
+    // 1-KiB tiles: a lane's 16 bytes are the words of two blocks
+    auto fetch = [&](__amdgpu_buffer_rsrc_t r, int voff, int tile_bytes, int block) -> words {
+        return buf_load128(r, voff, tile_bytes + (block >> 1) * 1024);
+    };
+    constexpr int PER = 2;                                    // blocks per fetch
+
+    // ================= stage V =================
+    {
+        f32x4 acc[RB][8][TN];
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int a = 0; a < 8; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) acc[r][a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int gg = i >> 2, vv = i & 3;
+        const int voff = ((4 * (gg & 1) + (gg >> 1)) * p.nkt_v) * 1024 + (g * 16 + vv) * 16;
+        const int ranks = wave < p.nub ? (p.nub - 1 - wave) / NW + 1 : 0;      // rank blocks of this wavefront
+        int nc = 0, nr = 0, nb = 0;                           // the next fetch: first block of the chunk, rank block, block of the chunk
+        auto next = [&](words (&w)[8]) {
+#pragma unroll
+            for (int a = 0; a < 8; ++a)
+                w[a] = fetch(v_rsrc, voff, (8 * (wave + NW * nr) + 2 * (a >> 2)) * p.nkt_v * 1024 + 4 * (a & 3) * 16, nc + nb);
+            if (nb + PER < min(p.chunk, p.nvb - nc)) nb += PER;
+            else if (nr + 1 < ranks) {                        // (at the end: the last fetch again)
+                ++nr;
+                nb = 0;
+            }
+        };
+        auto make = [&](int c0) __attribute__((always_inline)) {
+            const int blocks = min(p.chunk, p.nvb - c0);
+            unsigned char* rec = xrec + (c0 / p.chunk & (p.buffers - 1)) * p.chunk * TN * FP6_REC_BYTES;
+            for (int q = wave; q < blocks * TN; q += NW) make_record(c0 + q / TN, q % TN, rec + q * FP6_REC_BYTES);
+        };
+        make(0);
+        __syncthreads();
+        auto chunks = [&](auto make_first) __attribute__((always_inline)) {
+            for (int c0 = 0; c0 < p.nvb; c0 += p.chunk) {
+                const int blocks = min(p.chunk, p.nvb - c0);
+                const bool more = c0 + p.chunk < p.nvb;
+                if (decltype(make_first)::value && more) make(c0 + p.chunk);
+                const unsigned char* rec = xrec + (c0 / p.chunk & (p.buffers - 1)) * p.chunk * TN * FP6_REC_BYTES;
+                words w0[8];                                  // (not kept over the making of records: the registers are needed there)
+                nc = c0;
+                nr = nb = 0;
+                if (ranks > 0) next(w0);
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+                    if (r < ranks) run(std::integral_constant<int, 8>{}, rec, blocks, w0, next, acc[r]);
+                if (!decltype(make_first)::value && more) make(c0 + p.chunk);
+                if (more) __syncthreads();
+            }
+        };
+        if (CHUNKED && wave >= NW / 2) chunks(std::true_type{});
+        else chunks(std::false_type{});
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int rank = wave + NW * r;
+            if (rank >= p.nub) break;
+            f32x4 sv[8];
+#pragma unroll
+            for (int a = 0; a < 8; ++a)       // z = S (V x) / 4: the codes of either stage multiply as +-2
+                sv[a] = 0.25f * *reinterpret_cast<const f32x4*>(p.S + 128 * rank + 64 * (g & 1) + 16 * (g >> 1) + 32 * (a >> 2) + 4 * (a & 3));
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                float v[32];
+#pragma unroll
+                for (int e = 0; e < 32; ++e) v[e] = acc[r][e >> 2][b][e & 3] * sv[e >> 2][e & 3];
+                tsvd_planes_of_32(v, zrec + (rank * TN + b) * FP6_REC_BYTES, lane);
+            }
+        }
+    }
+
+    // ================= stage U =================
+    auto stage_u = [&](auto tm_c) {
+        constexpr int TM = decltype(tm_c)::value;
+        const int units = (p.M + 16 * TM - 1) / (16 * TM);
+        int nu = wave, nb = 0;                                // the next fetch: unit, block
+        const int last_unit = wave + (units - 1 - wave) / NW * NW;
+        auto next = [&](words (&w)[TM]) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) w[a] = fetch(u_rsrc, lane * 16, (nu * TM + a) * p.nkt_u * 1024, nb);
+            if (nb + PER < p.nub) nb += PER;
+            else if (nu < last_unit) {                        // (at the end: the last fetch again)
+                nu += NW;
+                nb = 0;
+            }
+        };
+        words w0[TM];
+        if (wave < units) next(w0);
+        __syncthreads();                                      // the planes of z are complete
+        const bool vec4 = !(p.ldy & 3) && !(reinterpret_cast<uintptr_t>(p.y) & 15), aligned4 = !(p.ldy & 1) && !(reinterpret_cast<uintptr_t>(p.y) & 3);
+        const bool vec8 = vec4 && !(p.ldy & 7);
+        for (int unit = wave; unit < units; unit += NW) {
+            const int strip0 = unit * TM;
+            f32x4 acc[TM][TN];
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                f32x4 br = {0.f, 0.f, 0.f, 0.f};
+                if (p.bias) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) br[e] = p.bias[min((strip0 + a) * 16 + 4 * g + e, p.M - 1)];
+                }
+#pragma unroll
+                for (int b = 0; b < TN; ++b) acc[a][b] = br;
+            }
+            run(tm_c, zrec, p.nub, w0, next, acc);
+            // (wait for the next unit's code words here, before the stores)
+#pragma unroll
+            for (int a = 0; a < TM; ++a) asm volatile("" :: "v"(w0[a].x), "v"(w0[a].y));
+            if (p.token_major && p.out_bf16 && vec8 && TM >= 4 && (strip0 + TM) * 16 <= p.M) {
+                if constexpr (TM >= 4) {
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) {
+                        const int col = b0 + 16 * b + i;
+#pragma unroll
+                        for (int a = 0; a < TM; a += 4) {
+                            uint32_t d[4][2];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                d[k][0] = tsvd_pack_bf16(acc[a + k][b][0], acc[a + k][b][1]);
+                                d[k][1] = tsvd_pack_bf16(acc[a + k][b][2], acc[a + k][b][3]);
+                            }
+                            tsvd_store_token_major_bf16_4x16(p.y, p.ldy, col, col < p.B, (strip0 + a) * 16, g, d);
+                        }
+                    }
+                }
+                continue;
+            }
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                const int row0 = (strip0 + a) * 16 + 4 * g;
+#pragma unroll
+                for (int b = 0; b < TN; ++b) {
+                    const int col16 = b0 + 16 * b, col = col16 + i;
+                    const f32x4 v = acc[a][b];
+                    if (p.token_major) {
+                        if (col < p.B) tsvd_store_token_major4(p.y, p.ldy, col, row0, p.M, v[0], v[1], v[2], v[3], p.out_bf16, vec4);
+                    } else if (p.out_bf16) {
+                        tsvd_store_row_pair_bf16(p.y, p.ldy, row0, p.M, col16, i, p.B, v[0], v[1], aligned4);
+                        tsvd_store_row_pair_bf16(p.y, p.ldy, row0 + 2, p.M, col16, i, p.B, v[2], v[3], aligned4);
+                    } else if (col < p.B) {
+                        float* dst = static_cast<float*>(p.y) + (size_t)row0 * p.ldy + col;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (row0 + e < p.M) dst[(size_t)e * p.ldy] = v[e];
+                    }
+                }
+            }
+        }
+    };
+    if (p.utm == 8) stage_u(std::integral_constant<int, 8>{});
+    else if (p.utm == 4) stage_u(std::integral_constant<int, 4>{});
+    else stage_u(std::integral_constant<int, 2>{});
+}
+
+constexpr int LDS_BYTES = 160 * 1024, MAX_TAPS = 48;
+
+template <int TN, int RB, int SOURCE, bool CHUNKED>
+auto kernel() { return tsvd_thin_panel_kernel<TN, RB, SOURCE, CHUNKED>; }
+template <int TN, int RB, int SOURCE>
+hipError_t launch(const thin_args& a, int lds, hipStream_t stream) {
+    const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN))), block(512);
+    if (a.buffers == 2) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true>()), grid, block, lds, stream, a);
+    else hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false>()), grid, block, lds, stream, a);
+    return hipGetLastError();
+}
+template <int TN, int RB>
+hipError_t launch(int source, const thin_args& a, int lds, hipStream_t stream) {
+    if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, lds, stream);
+    if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, lds, stream);
+    return launch<TN, RB, THIN_FEATURE_MAJOR>(a, lds, stream);
+}
+template <int TN, int RB, int SOURCE>
+hipError_t init() {
+    for (const auto k : {kernel<TN, RB, SOURCE, false>(), kernel<TN, RB, SOURCE, true>()}) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <int TN, int RB>
+hipError_t init() {
+    hipError_t e;
+    if ((e = init<TN, RB, THIN_FEATURE_MAJOR>()) != hipSuccess || (e = init<TN, RB, THIN_TOKEN_MAJOR>()) != hipSuccess) return e;
+    return init<TN, RB, THIN_CONV>();
+}
+
+}  // namespace
+
+hipError_t tsvd_thin_init() {
+    hipError_t e;
+    if ((e = init<1, 1>()) != hipSuccess) return e;
+    if ((e = init<1, 2>()) != hipSuccess) return e;
+    return init<2, 1>();
+}
+
+static size_t tsvd_thin_x_bytes(const tsvd_thin_problem& g) {
+    const tsvd_blob_header& hd = *g.hd;
+    if (g.source == THIN_CONV) return (size_t)(hd.N / (g.kv1 * g.kv2)) * g.images * g.H * g.W * 2;
+    const long long rows = g.source == THIN_TOKEN_MAJOR ? g.B : hd.N, cols = g.source == THIN_TOKEN_MAJOR ? hd.N : g.B;
+    return (size_t)((rows - 1) * g.ldx + cols) * 2;
+}
+
+// Blocks of x in LDS at a time: all of them if they fit beside those of z, else two chunks of an even number of blocks (a pair
+// shares its code words), of about equal length; 0: not possible.
+int tsvd_thin_chunk(long long K, long long N, int tiles, bool conv) {
+    const long long nvb = (N + 127) / 128, nub = (K + 127) / 128, table = conv ? nvb * 512 : 0;
+    if (nub > 16 / tiles) return 0;
+    const long long room = ((LDS_BYTES - table) / FP6_REC_BYTES - nub * tiles) / tiles;
+    if (nvb <= room) return (int)nvb;
+    const long long most = room / 2 & ~1ll;
+    if (most < 2) return 0;
+    const long long chunks = (nvb + most - 1) / most;
+    return (int)std::min(most, ((nvb + chunks - 1) / chunks + 1) & ~1ll);
+}
+
+hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t stream) {
+    const tsvd_blob_header& hd = *g.hd;
+    if (tsvd_thin_x_bytes(g) >= (1ull << 30) || (size_t)hd.Mp * hd.Kp / 4 >= (1ull << 31) || (size_t)hd.Kp * hd.Np / 4 >= (1ull << 31))
+        return hipErrorNotSupported;
+    thin_args a;
+    a.tiles_v = reinterpret_cast<const uint32_t*>(g.blob + hd.off_V);
+    a.tiles_u = reinterpret_cast<const uint32_t*>(g.blob + hd.off_U);
+    a.tile_v_bytes = (unsigned)((size_t)hd.Kp * hd.Np / 4);
+    a.tile_u_bytes = (unsigned)((size_t)hd.Mp * hd.Kp / 4);
+    a.nkt_v = (int)(hd.Np / 256);
+    a.nkt_u = (int)(hd.Kp / 256);
+    a.nvb = (int)((hd.N + 127) / 128);
+    a.nub = (int)((hd.K + 127) / 128);
+    a.x = g.x;
+    a.x_bytes = (unsigned)tsvd_thin_x_bytes(g);
+    a.N = (int)hd.N;
+    a.B = (int)g.B;
+    a.ldx = g.ldx;
+    a.images = g.images; a.H = g.H; a.W = g.W; a.kv1 = g.kv1; a.kv2 = g.kv2; a.Hv = g.Hv; a.Wv = g.Wv;
+    a.s1 = g.s1; a.s2 = g.s2; a.p1 = g.p1; a.p2 = g.p2; a.d1 = g.d1; a.d2 = g.d2;
+    a.S = reinterpret_cast<const float*>(g.blob + hd.off_S);
+    a.y = g.y;
+    a.ldy = g.ldy;
+    a.bias = g.bias;
+    a.M = (int)hd.M;
+    a.out_bf16 = g.out_bf16;
+    a.token_major = g.y_token_major;
+    // rows per unit of stage U: the larger units unless they leave wavefronts without one
+    auto passes = [&](int utm) { return ((a.M + 16 * utm - 1) / (16 * utm) + 7) / 8 * utm; };
+    a.utm = passes(8) <= passes(4) && passes(8) <= passes(2) ? 8 : passes(4) <= passes(2) ? 4 : 2;
+    const bool conv = g.source == THIN_CONV;
+    if (conv && g.kv1 * g.kv2 > MAX_TAPS) return hipErrorNotSupported;
+    a.chunk = tsvd_thin_chunk(hd.K, hd.N, tiles, conv);
+    if (a.chunk == 0) return hipErrorNotSupported;
+    a.buffers = a.chunk < a.nvb ? 2 : 1;
+    const int lds = (a.buffers * a.chunk + a.nub) * tiles * FP6_REC_BYTES + (conv ? a.nvb * 512 : 0), rb = (a.nub + 7) / 8;
+    if (tiles == 1 && rb == 1) return launch<1, 1>(g.source, a, lds, stream);
+    if (tiles == 1 && rb == 2) return launch<1, 2>(g.source, a, lds, stream);
+    if (tiles == 2 && rb == 1) return launch<2, 1>(g.source, a, lds, stream);
+    return hipErrorNotSupported;
+}

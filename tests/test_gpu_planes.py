@@ -1,4 +1,4 @@
-"""The plane path's split tiles at the edges of their tiles, against the oracle: exact on
+"""The plane path's split tiles and the thin token panels at the edges of their tiles, against the oracle: exact on
 integer instances (every layout, bias and output type), within a fraction of the tolerance on random ones."""
 import numpy as np
 import pytest
@@ -55,3 +55,12 @@ def test_split_tiles(tsvd, M, N, K, B, v, u, own_x, x_dtype):
     stage V or by their own pass."""
     print(f"case split {M} {N} {K} {B} {v} {u} {own_x} {x_dtype}", flush=True)
     _check(tsvd, M, N, K, B, x_dtype, {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_SPLIT_V": v, "TSVD_SPLIT_U": u, "TSVD_SPLIT_X": own_x})
+
+
+@pytest.mark.parametrize("tiles", [1, 2])
+@pytest.mark.parametrize("M,N,K,B", [(130, 64, 60, 65), (515, 300, 777, 130), (300, 1030, 1024, 47), (200, 2600, 900, 40), (200, 3200, 2048, 19), (64, 100, 2049, 33)])
+def test_thin_panels(tsvd, M, N, K, B, tiles):
+    """x in LDS as a whole and in chunks, one and two rank blocks per wavefront, and sizes that no such panel holds (these take the other
+    kernels)."""
+    print(f"case thin {M} {N} {K} {B} {tiles}", flush=True)
+    _check(tsvd, M, N, K, B, "bf16", {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_THIN": tiles, "TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 9})
