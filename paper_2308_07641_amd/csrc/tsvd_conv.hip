@@ -23,6 +23,8 @@
 #include "tsvd_epilogue.h"
 #include "tsvd_kernels.h"
 #include "tsvd_layout.h"
+#include "tsvd_batch.h"
+#include "tsvd_thin.h"
 
 namespace {
 
@@ -483,7 +485,42 @@ extern "C" tsvd_status tsvd_conv2d_forward(const tsvd_handle* h, const tsvd_conv
     const bool gather = g->form != 1, taps = g->form != 0;
     const void* X = x_dev;
     long long ldx = p.Bv;
-    if (gather) {
+    int64_t M = 0, K = 0, N = 0;
+    (void)tsvd_info(h, &M, &K, &N, nullptr, nullptr);
+    const int cus = tsvd_internal_cu_count(h);
+    int thin = 0;
+    if (gather && p.Bv > 16) {
+        tsvd_batch_call c = {};
+        c.M = M; c.K = K; c.N = N; c.B = p.Bv; c.cus = cus;
+        c.conv = true;
+        c.out_bf16 = !taps && y_dtype == TSVD_BF16;
+        c.whole = tsvd_stage_mask() == 7;
+        thin = tsvd_plan_batch(c).thin;
+    }
+    bool mapped = false;
+    if (thin) {
+        // thin token panels gather the taps of V's kernel from the images themselves
+        tsvd_thin_problem t = {};
+        t.blob = tsvd_internal_blob(h, &t.hd);
+        t.x = static_cast<const uint16_t*>(x_dev);
+        t.source = THIN_CONV;
+        t.B = p.Bv;
+        t.images = (int)images; t.H = (int)H; t.W = (int)W; t.kv1 = p.kv1; t.kv2 = p.kv2; t.Hv = p.Hv; t.Wv = p.Wv;
+        t.s1 = p.v_dim1 ? g->stride1 : 1; t.p1 = p.v_dim1 ? g->pad1 : 0; t.d1 = g->dil1;
+        t.s2 = p.v_dim2 ? g->stride2 : 1; t.p2 = p.v_dim2 ? g->pad2 : 0; t.d2 = g->dil2;
+        t.y = taps ? static_cast<void*>(ws + (g->form == 1 ? 0 : round256((size_t)p.rows_v * p.ldx * 2))) : y_dev;
+        t.ldy = p.Bv;
+        t.bias = taps ? nullptr : bias_dev;
+        t.out_bf16 = !taps && y_dtype == TSVD_BF16;
+        t.cu_count = cus;
+        const hipError_t e = tsvd_thin_launch(t, thin, s);
+        if (e != hipSuccess && e != hipErrorNotSupported) return TSVD_EDEVICE;
+        mapped = e == hipSuccess;
+        if (mapped && !taps) return TSVD_OK;
+    }
+    if (gather && mapped) {
+        ws += round256((size_t)p.rows_v * p.ldx * 2);
+    } else if (gather) {
         uint16_t* cols = reinterpret_cast<uint16_t*>(ws);
         ws += round256((size_t)p.rows_v * p.ldx * 2);
         hipLaunchKernelGGL(tsvd_unfold_kernel, dim3((unsigned)((p.ldx / 8 + 255) / 256), (unsigned)p.rows_v), dim3(256), 0, s,
@@ -500,7 +537,7 @@ extern "C" tsvd_status tsvd_conv2d_forward(const tsvd_handle* h, const tsvd_conv
     }
     const size_t map_ws = tsvd_workspace_bytes_ex(h, p.Bv, TSVD_BF16, TSVD_FEATURE_MAJOR);
     // U is 1 x 1: the map writes the result itself, bias and output type fused
-    tsvd_status st = taps ? tsvd_forward_ex(h, X, TSVD_BF16, TSVD_FEATURE_MAJOR, p.Bv, ldx, nullptr, T, TSVD_F32, p.Bv, ws, map_ws, s)
+    tsvd_status st = mapped ? TSVD_OK : taps ? tsvd_forward_ex(h, X, TSVD_BF16, TSVD_FEATURE_MAJOR, p.Bv, ldx, nullptr, T, TSVD_F32, p.Bv, ws, map_ws, s)
                           : tsvd_forward_ex(h, X, TSVD_BF16, TSVD_FEATURE_MAJOR, p.Bv, ldx, bias_dev, y_dev, y_dtype, p.Bv, ws, map_ws, s);
     if (st != TSVD_OK || !taps) return st;
     hipLaunchKernelGGL(tsvd_fold_kernel, dim3((unsigned)((p.Bo + 255) / 256), (unsigned)g->c_out), dim3(256), 0, s, T, p.Bv, (int)images,

@@ -64,3 +64,32 @@ def test_thin_panels(tsvd, M, N, K, B, tiles):
     kernels)."""
     print(f"case thin {M} {N} {K} {B} {tiles}", flush=True)
     _check(tsvd, M, N, K, B, "bf16", {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_THIN": tiles, "TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 9})
+
+
+@pytest.mark.parametrize("tiles", [1, 2])
+@pytest.mark.parametrize("form,ci,co,k1,k2,geom", [
+    (0, 5, 7, 3, 3, ((1, 1), (1, 1), (1, 1))), (0, 150, 40, 5, 5, ((2, 1), (2, 2), (1, 1))), (2, 20, 33, 3, 2, ((1, 2), (1, 0), (2, 1))),
+    (3, 64, 9, 7, 1, ((2, 2), (3, 0), (1, 1))), (0, 3, 5, 7, 7, ((1, 1), (3, 3), (1, 1)))])
+def test_thin_panels_gather_convolutions(tsvd, form, ci, co, k1, k2, geom, tiles):
+    """Taps outside the image, strides and dilations, x in chunks, and more taps than the bit mask holds (the columns are written
+    then)."""
+    import torch
+    from oracle import conv as oc
+    K, images, H, W = 150, 3, 12, 9
+    rows, cols = {0: (co, ci * k1 * k2), 2: (co * k1, ci * k2), 3: (co * k2, ci * k1)}[form]
+    rng = np.random.default_rng(form + ci + k1)
+    print(f"case thin conv {form} {ci} {co} {k1}x{k2} {tiles}", flush=True)
+    U = rng.choice([-1, 0, 1], size=(rows, K), p=[0.15, 0.7, 0.15]).astype(np.int8)
+    V = rng.choice([-1, 0, 1], size=(K, cols), p=[0.15, 0.7, 0.15]).astype(np.int8)
+    S = rng.integers(-2, 3, size=K).astype(np.float32)
+    x = rng.integers(-2, 3, size=(images, ci, H, W)).astype(np.float32)
+    bias = rng.integers(-4, 5, size=co).astype(np.float32)
+    ref = oc.tsvd_conv2d(x, U, S, V, form, co, ci, k1, k2, *geom, bias=bias)
+    h = tsvd.tsvd_pack(U, S, V)
+    tsvd.tsvd_tuning_set("TSVD_THIN", tiles)
+    xd = torch.from_numpy(np.ascontiguousarray(x.transpose(1, 0, 2, 3))).to("cuda:0").to(torch.bfloat16)
+    for y_dtype in (tsvd.TSVD_F32, tsvd.TSVD_BF16):
+        y = tsvd.tsvd_conv2d_forward(h, form, ci, co, k1, k2, xd, *geom, bias=torch.from_numpy(bias).to("cuda:0"), y_dtype=y_dtype)
+        want = torch.from_numpy(np.ascontiguousarray(ref.transpose(1, 0, 2, 3))).to(y.dtype)
+        assert torch.equal(y.cpu(), want)
+    tsvd.tsvd_free(h)
