@@ -33,7 +33,7 @@ extern "C" {
  *   TSVD_THIN (1, 2: thin token panels of 16 or 32 tokens), TSVD_SPLIT_V / TSVD_SPLIT_U (tiles of the plane path's stages: 9, 10, 18, 20 =
  *   rows / 128 * 8 + tokens / 16), TSVD_SPLIT_X (0: planes of x always by a pass of their own).  While any switch is set a batch runs on
  *   thin panels or split tiles only if these ask for them,
- *   TSVD_GROUPED_PAIR,
+ *   TSVD_GROUPED_PAIR, TSVD_DEPTHWISE (1: depth-wise convolutions on the matrix cores also while other switches are set),
  *   TSVD_CLOCKS (1 at tsvd_pack: record phase timestamps per workgroup), TSVD_SPIN_LIMIT (bound of the
  *   single-launch kernels' wait for another workgroup's slice of z, in polls), TSVD_DENSE_U (1 at tsvd_pack: keep a
  *   second copy of U in the five-elements-per-byte code and run stage U of single-token calls on it),

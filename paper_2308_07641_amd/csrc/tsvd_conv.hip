@@ -12,7 +12,8 @@
 // steps directly: the window of the group's input channels is staged in LDS, V_g is turned into a
 // list of its non-zero taps per rank, and every output position adds / subtracts the listed values
 // (the additions of the method, zeros skipped), multiplies by S and combines the ranks with the
-// signs of U: x is read once and y written once, z stays in registers.
+// signs of U: x is read once and y written once, z stays in registers.  Groups of one input channel with kernels of 3, 5 or 7
+// rows go to tsvd_depthwise.hip instead.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -21,9 +22,10 @@
 
 #include "../../include/tsvd_conv.h"
 #include "tsvd_epilogue.h"
+#include "tsvd_batch.h"
+#include "tsvd_depthwise.h"
 #include "tsvd_kernels.h"
 #include "tsvd_layout.h"
-#include "tsvd_batch.h"
 #include "tsvd_thin.h"
 
 namespace {
@@ -150,13 +152,6 @@ struct grouped_args {
     int rows_in, win;                    // staged window per input channel: rows, columns
 };
 
-// 2-bit code of element (r, c) of a packed matrix with tps tiles per strip.
-__device__ __forceinline__ int code_at(const uint32_t* words, int tps, int r, int c) {
-    int word, bit;
-    tsvd_code_position(r & 15, c & 255, &word, &bit);
-    return (int)(words[((size_t)(r >> 4) * tps + (c >> 8)) * 256 + word] >> bit) & 3;
-}
-
 // grid (bpp * ceil(images / ipb), groups), block 64..256.  Workgroup = group g, output rows
 // [r0, r0 + rb) of ipb images, one after the other.  A thread owns ROWS vertically adjacent
 // positions (ROWS = 4 needs stride1 = 1 and a compile-time row pitch P of the window: the four
@@ -196,11 +191,11 @@ tsvd_grouped_conv_kernel(grouped_args p) {
     // ---- the codes of V_g, all loads in flight at once, then per rank (one wavefront each) the list of its non-zero taps
     for (int idx = threadIdx.x; idx < p.kg * p.ng; idx += blockDim.x) {
         const int k = idx / p.ng, j = idx - k * p.ng;
-        codes[k * stride + j] = (unsigned char)code_at(p.V, p.v_tps, (int)tsvd_rank_position(g * p.kg + k, p.K), j);
+        codes[k * stride + j] = (unsigned char)tsvd_code_at(p.V, p.v_tps, (int)tsvd_rank_position(g * p.kg + k, p.K), j);
     }
     for (int idx = threadIdx.x; idx < MG * p.kg; idx += blockDim.x) {
         const int m = idx / p.kg, k = idx % p.kg;
-        const int code = m < p.mg ? code_at(p.U, p.u_tps, g * p.mg + m, (int)tsvd_rank_position(g * p.kg + k, p.K)) : 0;
+        const int code = m < p.mg ? tsvd_code_at(p.U, p.u_tps, g * p.mg + m, (int)tsvd_rank_position(g * p.kg + k, p.K)) : 0;
         ucode[idx] = code == 1 ? 1.f : code == 3 ? -1.f : 0.f;
     }
     for (int k = threadIdx.x; k < p.kg; k += blockDim.x) sval[k] = p.S[tsvd_rank_position(g * p.kg + k, p.K)];
@@ -471,6 +466,12 @@ extern "C" tsvd_status tsvd_conv2d_forward(const tsvd_handle* h, const tsvd_conv
         a.K = (int)hd->K;
         a.x = static_cast<const uint16_t*>(x_dev); a.y = y_dev; a.bias = bias_dev; a.out_bf16 = y_dtype == TSVD_BF16;
         hipStream_t gs = static_cast<hipStream_t>(stream);
+        if (a.cg == 1 && (!tsvd_tuning_any() || tsvd_tune("TSVD_DEPTHWISE", 0) != 0)) {      // on the matrix cores
+            tsvd_depthwise_problem d = {a.U, a.V, a.u_tps, a.v_tps, a.S, a.K, (int)g->groups, a.mg, a.kg, a.x, a.y, a.bias, a.out_bf16,
+                                        a.images, a.H, a.W, a.Ho, a.Wo, a.k1, a.k2, a.s1, a.s2, a.p1, a.p2, a.d1, a.d2, tsvd_internal_cu_count(h)};
+            const hipError_t e = tsvd_depthwise_launch(d, gs);
+            if (e != hipErrorNotSupported) return e == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
+        }
         if (MG == 1) launch_grouped<1>(a, ROWS, P, PAIR, g->groups, threads, gs);
         else if (MG == 2) launch_grouped<2>(a, ROWS, P, PAIR, g->groups, threads, gs);
         else if (MG == 4) launch_grouped<4>(a, ROWS, P, PAIR, g->groups, threads, gs);

@@ -90,3 +90,10 @@ __host__ __device__ static inline void tsvd_code_position(int r_in_tile, int c_i
     *word = lane * 4 + 2 * h + (v >> 1);
     *bit = 2 * (2 * n + (v & 1));
 }
+
+// 2-bit code of element (r, c) of a packed matrix with tps tiles per strip.
+__device__ inline int tsvd_code_at(const uint32_t* words, int tps, int r, int c) {
+    int word, bit;
+    tsvd_code_position(r & 15, c & 255, &word, &bit);
+    return (int)(words[((size_t)(r >> 4) * tps + (c >> 8)) * 256 + word] >> bit) & 3;
+}
