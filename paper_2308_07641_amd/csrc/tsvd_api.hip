@@ -131,8 +131,12 @@ void shape_skinny(tsvd_skinny_args& a) {
     a.kw = std::max(1, std::min(std::min(16 / a.sw, a.nkt), env_int("TSVD_SKINNY_KW", kw)));
 }
 
-size_t skinny_workspace(const tsvd_handle* h) {
-    return 256 + (size_t)16 * (size_t)h->hd.Kp;      // exponents, then 16 digit planes of Kp bytes
+// Tokens that the single-token kernels take in one launch (planes of z: 2 MiB at most, K being at most 16384 there).
+int gemv_tokens(const tsvd_handle* h, int64_t B) {
+    return tsvd_gemv_fits(h->hd.Np, h->hd.Kp) ? (int)std::min<int64_t>(B, TSVD_GEMV_MAX_TOKENS) : 1;
+}
+size_t skinny_workspace(const tsvd_handle* h, int64_t B) {
+    return 256 + (size_t)std::max(16, 8 * gemv_tokens(h, B)) * (size_t)h->hd.Kp;      // exponents, then digit planes of Kp bytes: 8 per token
 }
 
 int pow2_ceil(int64_t v) {
@@ -147,11 +151,14 @@ int pow2_floor(int64_t v) {
 }
 
 // One token through the tsvd_gemv kernels; returns false if the shape does not fit them.
-bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t ldx, void* y, int64_t ldy,
-              const out_opts& oo, int* meta, unsigned char* planes, hipStream_t stream, tsvd_status* st) {
+// tokens: each on workgroups of its own, x_token and y_token elements from one to the next
+bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t ldx, int tokens, int64_t x_token, void* y, int64_t ldy,
+              int64_t y_token, const out_opts& oo, int* meta, unsigned char* planes, hipStream_t stream, tsvd_status* st) {
     const tsvd_blob_header& hd = h->hd;
     if (env_int("TSVD_GEMV", 1) == 0 || !tsvd_gemv_fits(hd.Np, hd.Kp)) return false;
     const int mask = tsvd_stage_mask();
+    // (16 bytes of fp32, 8 of bf16 at a time)
+    const bool vec = ldx == 1 && hd.N % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (tokens == 1 || x_token % 4 == 0);
     if (mask == 7 && !h->dense_u && env_int("TSVD_GEMV_FUSED", 1) != 0 && tsvd_gemv_fused_fits(hd.Mp, hd.Kp, hd.Np)) {
         // a small matrix: both stages in one launch of one workgroup
         tsvd_gemv_fused_args f;
@@ -160,14 +167,15 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
         f.tiles_u = h->blob + hd.off_U; f.strips_u = (int)((hd.M + 15) / 16); f.nkt_u = (int)(hd.Kp / 256);
         f.N = (int)hd.N; f.Np = (int)hd.Np; f.Kp = (int)hd.Kp; f.M = (int)hd.M;
         f.x = x; f.x_is_bf16 = x_dtype == TSVD_BF16; f.ldx = ldx;
-        f.x_vec = ldx == 1 && hd.N % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+        f.x_vec = vec;
+        f.tokens = tokens; f.x_token = x_token; f.y_token = y_token;
         f.S = reinterpret_cast<const float*>(h->blob + hd.off_S);
         f.bound_V = h->bound_V;
         f.y = y; f.ldy = ldy; f.bias = oo.bias; f.out_bf16 = oo.out_bf16;
         *st = tsvd_launch_gemv_fused(f, stream) == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
         return true;
     }
-    if (mask == 7 && h->sync && !h->dense_u && env_int("TSVD_GEMV_ONEPASS", 0) != 0) {
+    if (mask == 7 && tokens == 1 && h->sync && !h->dense_u && env_int("TSVD_GEMV_ONEPASS", 0) != 0) {
         // both stages in one launch (z handed over between workgroups through the handle's tagged buffer)
         tsvd_handle* hm = const_cast<tsvd_handle*>(h);
         int expected = 0;
@@ -179,7 +187,7 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
             f.tiles_u = h->blob + hd.off_U;
             f.N = (int)hd.N; f.Np = (int)hd.Np; f.Kp = (int)hd.Kp; f.M = (int)hd.M;
             f.x = x; f.x_is_bf16 = x_dtype == TSVD_BF16; f.ldx = ldx;
-            f.x_vec = ldx == 1 && hd.N % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+            f.x_vec = vec;
             f.S = reinterpret_cast<const float*>(h->blob + hd.off_S);
             f.bound_V = h->bound_V;
             f.counter = reinterpret_cast<unsigned*>(h->sync);
@@ -191,20 +199,28 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
             return true;
         }
     }
-    // sw strips x kw splits = 16 wavefronts; about one workgroup per compute unit for large matrices
+    // sw strips x kw splits = 16 wavefronts, strips so that no compute unit gets a second workgroup: every workgroup stages its token's
+    // planes first, and the second would start with that when the first is done (measured: 12175 x 149 x 7168 15.8 us with two strips,
+    // 12.2 with four; 15 tokens of 5290 x 285 x 3200 54 us with one, 17 with sixteen).  Where few splits are possible four strips at least:
+    // with 256 columns a workgroup of one strip has one wavefront with work (7978 x 128 x 109: 9.0 -> 7.8 us).
     auto shape = [&](tsvd_gemv_args& a) {
+        auto splits = [&](int sw) {
+            int kl = 0;
+            while ((sw << (kl + 1)) <= 16 && (2 << kl) <= a.nkt) ++kl;
+            return kl;
+        };
         int sw = 1;
-        while (sw < 16 && a.strips / (sw * 2) >= 256) sw *= 2;
-        int kl = 0;
-        while ((sw << (kl + 1)) <= 16 && (2 << kl) <= a.nkt) ++kl;
+        while (sw < 16 && (long long)((a.strips + sw - 1) / sw) * tokens > h->cu_count) sw *= 2;
+        while ((sw << splits(sw)) < 4) sw *= 2;
         a.sw = std::max(1, std::min(16, env_int("TSVD_GEMV_SW", sw)));
-        a.kw_log2 = std::max(0, env_int("TSVD_GEMV_KWLOG2", kl));
+        a.kw_log2 = std::max(0, env_int("TSVD_GEMV_KWLOG2", splits(a.sw)));
         while ((a.sw << a.kw_log2) > 16) --a.kw_log2;
     };
     tsvd_gemv_args a;
     std::memset(&a, 0, sizeof a);
     a.N = (int)hd.N; a.Np = (int)hd.Np; a.Kp = (int)hd.Kp;
     a.meta = meta;
+    a.tokens = tokens; a.x_token = x_token; a.y_token = y_token;
     a.clocks = h->clocks;
     a.early_tiles = env_int("TSVD_EARLY_TILES", 1);
     if (mask & 2) {
@@ -215,7 +231,7 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
         a.x = x;
         a.x_is_bf16 = x_dtype == TSVD_BF16;
         a.ldx = ldx;
-        a.x_vec = ldx == 1 && hd.N % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+        a.x_vec = vec;
         a.S = reinterpret_cast<const float*>(h->blob + hd.off_S);
         a.bound_V = h->bound_V;
         a.planes_out = planes;
@@ -257,7 +273,17 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
     return true;
 }
 
-tsvd_status forward_skinny(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t B, int64_t ldx,
+// x_token_major: only for calls that gemv_serves
+bool gemv_serves(const tsvd_handle* h) { return tsvd_gemv_fits(h->hd.Np, h->hd.Kp) && env_int("TSVD_GEMV", 1) != 0; }
+// 2 - 16 bf16 tokens on the single-token kernels side by side instead of the few-token kernels: those take 13 - 20 us at any size (two
+// launches that pass the activations through LDS in slabs, and a copy of token-major x), these 6 - 12 us and 0.08 us more per MB
+// of code words and token.  Measured on 316 random calls: they meet at 60 MB x tokens; rows of x at odd element offsets, which the few-token kernels
+// gather one by one (75 - 105 us), are copied to aligned rows before.
+bool side_by_side(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
+    return x_dtype == TSVD_BF16 && B >= 2 && B <= 16 && !tsvd_tuning_any() && !h->dense_u && gemv_serves(h) &&
+           (double)B * (double)h->hd.Kp * (double)(h->hd.Mp + h->hd.Np) / 4.0 <= 60.0e6;
+}
+tsvd_status forward_skinny(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t B, int64_t ldx, bool x_token_major,
                            void* y, int64_t ldy, const out_opts& oo, void* ws, hipStream_t stream) {
     const size_t yelt = oo.out_bf16 ? 2 : 4;
     const tsvd_blob_header& hd = h->hd;
@@ -265,14 +291,16 @@ tsvd_status forward_skinny(const tsvd_handle* h, const void* x, tsvd_dtype x_dty
     unsigned char* planes = static_cast<unsigned char*>(ws) + 256;
     const size_t xelt = x_dtype == TSVD_BF16 ? 2 : 4;
     const int mask = tsvd_stage_mask();
-    if (tsvd_gemv_fits(hd.Np, hd.Kp) && env_int("TSVD_GEMV", 1) != 0) {
-        // one token at a time through the fast kernels (each pass re-reads the weights)
-        for (int64_t b0 = 0; b0 < B; ++b0) {
+    if (gemv_serves(h)) {
+        // tokens side by side through the single-token kernels (each reads the weights; stage U on the denser code: one at a time)
+        const int step = h->dense_u ? 1 : gemv_tokens(h, B);
+        const int64_t x_token = x_token_major ? ldx : 1, y_token = oo.token_major ? ldy : 1;
+        for (int64_t b0 = 0; b0 < B; b0 += step) {
             tsvd_status gst = TSVD_OK;
-            // one token's output: column b0 of y [M][ldy], or row b0 of y [B][ldy] (then consecutive in memory)
-            uint8_t* yb = static_cast<uint8_t*>(y) + (oo.token_major ? (size_t)b0 * (size_t)ldy : (size_t)b0) * yelt;
-            if (!try_gemv(h, static_cast<const uint8_t*>(x) + (size_t)b0 * xelt, x_dtype, ldx,
-                          yb, oo.token_major ? 1 : ldy, oo, meta, planes, stream, &gst))
+            // one token's output: column b of y [M][ldy], or row b of y [B][ldy] (then consecutive in memory)
+            if (!try_gemv(h, static_cast<const uint8_t*>(x) + (size_t)(b0 * x_token) * xelt, x_dtype, x_token_major ? 1 : ldx,
+                          (int)std::min<int64_t>(step, B - b0), x_token, static_cast<uint8_t*>(y) + (size_t)(b0 * y_token) * yelt,
+                          oo.token_major ? 1 : ldy, y_token, oo, meta, planes, stream, &gst))
                 return TSVD_EUNSUPPORTED;
             if (gst != TSVD_OK) return gst;
         }
@@ -591,10 +619,12 @@ extern "C" tsvd_status tsvd_info(const tsvd_handle* h, int64_t* M, int64_t* K, i
 namespace {
 size_t base_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     // (the few-token path is chosen per call, by the row stride too: cover every candidate)
-    const size_t few = round256(std::max(skinny_workspace(h), mid_workspace(h)));
+    const size_t few = round256(std::max(skinny_workspace(h, B), mid_workspace(h)));
     if (use_gemm(h, B, x_dtype)) return std::max(gemm_workspace(h, B, x_dtype), B <= 64 ? few : (size_t)0);
     return few;
 }
+// (whether a call of few tokens may copy rows that start at odd elements: for the sizes whose workspace stays small)
+bool realigns_few(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) { return x_dtype == TSVD_BF16 && B > 1 && B <= 16 && h->hd.N <= 65535 && h->hd.Kp <= 65536; }
 // feature-major copy of token-major activations: [N][B rounded up to 8] elements
 size_t transposed_bytes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     return round256((size_t)h->hd.N * (size_t)tsvd_round_up(B, 8) * (x_dtype == TSVD_BF16 ? 2 : 4));
@@ -606,7 +636,7 @@ extern "C" size_t tsvd_workspace_bytes_ex(const tsvd_handle* h, int64_t B, tsvd_
     if (x_layout != TSVD_FEATURE_MAJOR && x_layout != TSVD_TOKEN_MAJOR) return 0;
     // (feature-major rows that are not 16-byte aligned are copied too, when the call goes to the batched kernels:
     // the alignment is not known here, so the room is always there)
-    const bool copy = x_layout == TSVD_TOKEN_MAJOR || use_gemm(h, B, x_dtype);
+    const bool copy = x_layout == TSVD_TOKEN_MAJOR || use_gemm(h, B, x_dtype) || realigns_few(h, B, x_dtype);
     return base_workspace(h, B, x_dtype) + (copy ? transposed_bytes(h, B, x_dtype) : 0);
 }
 
@@ -671,8 +701,13 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         ldx = 1;
     }
     int x_in_place = 0;
-    const bool few = use_mid(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR ? tsvd_round_up(B, 8) : ldx);
     const bool batched = use_gemm(h, B, x_dtype), misaligned = ldx % 8 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 15u);
+    // rows that are not 16-byte aligned get a copy that is: for more than 16 tokens one pass costs less than the element-wise gathers of the
+    // kernels that take such rows (stage V of a 4096 x 8192 factor at 300 tokens: 251 us gathered, 3 + 35 us copied), for
+    // fewer where rows start at odd elements; TSVD_REALIGN=0 keeps the gathers
+    const bool realign = x_layout == TSVD_FEATURE_MAJOR && x_dtype == TSVD_BF16 && B > 1 && env_int("TSVD_REALIGN", 1) != 0 && h->hd.N <= 65535 &&
+                         (batched ? misaligned : realigns_few(h, B, x_dtype) && (ldx % 2 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 3u)));
+    const bool few = !side_by_side(h, B, x_dtype) && use_mid(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR || realign ? tsvd_round_up(B, 8) : ldx);
     tsvd_batch_plan plan = {};
     if (batched && !few)
         plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16);
@@ -694,7 +729,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         const hipError_t te = tsvd_thin_launch(t, plan.thin, s);
         if (te != hipErrorNotSupported) return te == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
     }
-    if (x_layout == TSVD_TOKEN_MAJOR && (plan.split || (x_dtype == TSVD_BF16 && batched && !few &&
+    if (x_layout == TSVD_TOKEN_MAJOR && (plan.split || (!batched && !few && gemv_serves(h)) || (x_dtype == TSVD_BF16 && batched && !few &&
                                                         tsvd_gemm_reads_token_major(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count)))) {
         x_in_place = 1;       // the kernels this call takes gather their operand lanes from [B][ldx] themselves
     } else if (x_layout == TSVD_TOKEN_MAJOR) {
@@ -712,11 +747,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         x_dev = ws;
         ldx = ldt;
         ws = static_cast<uint8_t*>(ws) + transposed_bytes(h, B, x_dtype);
-    } else if (!plan.split && x_dtype == TSVD_BF16 && batched && misaligned && env_int("TSVD_REALIGN", 1) != 0 &&
-             h->hd.N <= 65535) {
-        // more than 16 tokens in rows that are not 16-byte aligned: one pass that copies them to aligned rows costs
-        // less than the element-wise gathers of the kernels that take such rows (stage V of a 4096 x 8192
-        // factor at 300 tokens: 251 us gathered, 3 + 35 us copied); TSVD_REALIGN=0 keeps the gathers
+    } else if (realign && (few || (batched && !plan.split))) {
         const int64_t ldt = tsvd_round_up(B, 8);
         hipLaunchKernelGGL(tsvd_realign_kernel, dim3((unsigned)((ldt + 255) / 256), (unsigned)h->hd.N), dim3(256), 0, s,
                            static_cast<const uint16_t*>(x_dev), (long long)ldx, (int)B, static_cast<uint16_t*>(ws), (long long)ldt);
@@ -725,7 +756,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         ldx = ldt;
         ws = static_cast<uint8_t*>(ws) + transposed_bytes(h, B, x_dtype);
     }
-    if (!x_in_place && use_mid(h, B, x_dtype, ldx)) return forward_mid(h, x_dev, B, ldx, y_dev, ldy, oo, ws, s);
+    if (few) return forward_mid(h, x_dev, B, ldx, y_dev, ldy, oo, ws, s);
     if (use_gemm(h, B, x_dtype)) {
         tsvd_gemm_problem g;
         g.blob = h->blob;
@@ -750,7 +781,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         const hipError_t ge = tsvd_forward_gemm(g, s);
         return ge == hipSuccess ? TSVD_OK : ge == hipErrorNotSupported ? TSVD_EUNSUPPORTED : TSVD_EDEVICE;
     }
-    return forward_skinny(h, x_dev, x_dtype, B, ldx, y_dev, ldy, oo, ws, s);
+    return forward_skinny(h, x_dev, x_dtype, B, ldx, x_in_place, y_dev, ldy, oo, ws, s);
 }
 
 extern "C" tsvd_status tsvd_forward(const tsvd_handle* h, const void* x_dev, tsvd_dtype x_dtype, int64_t B,
@@ -840,7 +871,7 @@ extern "C" tsvd_status tsvd_tuning_forward_stages(const tsvd_handle* h, const vo
 extern "C" int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* shape_v, int* shape_u) {
     if (!h || !shape_v || !shape_u || B < 1) return 1;
     *shape_v = *shape_u = -1;
-    if (use_mid(h, B, TSVD_BF16, tsvd_round_up(B, 8))) return 0;
+    if (B <= 16 || use_mid(h, B, TSVD_BF16, tsvd_round_up(B, 8))) return 0;
     if (use_gemm(h, B, TSVD_BF16)) {
         const tsvd_batch_plan plan = batch_plan(h, B, TSVD_BF16, false, false, false, false);
         if (plan.thin) {

@@ -180,10 +180,23 @@ __device__ __forceinline__ double combine_planes(const float* sums) {
 // (stage V: 4096 elements of x per round; stage U: 2048 columns of the planes per round).
 // All loads are unconditional (out-of-range indices are clamped to valid memory and the values
 // discarded): a load under a branch would make the compiler wait for every outstanding load.
-template <bool STAGE_U, int ROUNDS>
+// MANY: several tokens in the launch (its index arithmetic in front of the loads would cost a single token 0.5 us of 14.1).
+template <bool STAGE_U, int ROUNDS, bool MANY>
 __global__ void __launch_bounds__(1024)
 tsvd_gemv_kernel(tsvd_gemv_args p) {
     extern __shared__ __align__(16) unsigned char smem[];
+    // With several tokens the workgroups of one part of the matrix follow each other on one XCD (consecutive workgroups go to the
+    // eight of them in turn), so that all but the first find its tiles in that L2.
+    int blk = blockIdx.x, tok = 0;
+    if constexpr (MANY) {
+        const int rest = (int)blockIdx.x >> 3;
+        tok = rest % p.tokens;
+        blk = rest / p.tokens * 8 + ((int)blockIdx.x & 7);
+        if (blk * p.sw >= p.strips) return;
+    }
+    const unsigned char* const px = static_cast<const unsigned char*>(p.x) + (size_t)tok * p.x_token * (p.x_is_bf16 ? 2 : 4);
+    unsigned char* const py = static_cast<unsigned char*>(p.y) + (size_t)tok * p.y_token * (p.out_bf16 ? 2 : 4);
+    const size_t pz = (size_t)tok * 8 * p.Kp;              // the token's planes of z
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, g = lane >> 4;
     const int kdim = STAGE_U ? p.Kp : p.Np;               // contraction length (padded)
@@ -195,7 +208,7 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
     const unsigned char* xlane = planes + (size_t)(i & 7) * pstride + 32 * g;   // MFMA columns 8..15 repeat 0..7
     const int kw = 1 << p.kw_log2;
     const int sidx = wave >> p.kw_log2, q = wave & (kw - 1);
-    const int strip = blockIdx.x * p.sw + sidx;
+    const int strip = blk * p.sw + sidx;
     const bool active = sidx < p.sw && strip < p.strips;
     const u32x4* wp = reinterpret_cast<const u32x4*>(p.tiles) + ((size_t)(active ? strip : 0) * p.nkt) * 64 + lane;
     TICK(0);
@@ -206,15 +219,15 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
     int ex_in = 0, ex_z = 0;
     // the scale (stage V) or bias (stage U) of the row this thread finishes, requested first: a load issued in the
     // epilogue would cost a full round trip to memory at the very end of the launch
-    const int row_own = min((int)blockIdx.x * p.sw * 16 + (int)(threadIdx.x & 255), p.rows_out - 1);
+    const int row_own = min(blk * p.sw * 16 + (int)(threadIdx.x & 255), p.rows_out - 1);
     float tail_own = 0.f;
     if constexpr (STAGE_U) { if (p.bias) tail_own = p.bias[row_own]; }
     else tail_own = p.S[row_own];
     if constexpr (STAGE_U) {
-        ex_in = p.meta[0];
+        ex_in = p.meta[tok];
         // plane c is copied by threads c * 128 .. c * 128 + 127, 16 bytes each per round
         const int c = threadIdx.x >> 7, t = threadIdx.x & 127;
-        const u32x4* src = reinterpret_cast<const u32x4*>(p.planes_in + (size_t)c * p.Kp);
+        const u32x4* src = reinterpret_cast<const u32x4*>(p.planes_in + pz + (size_t)c * p.Kp);
         const int last = p.Kp / 16 - 1;
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) zv[r] = src[min(t + 128 * r, last)];
@@ -225,19 +238,19 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
             if (p.x_vec) {                                     // contiguous, aligned, N % 4 == 0
                 const int kc = min(k, p.N - 4);
                 if (p.x_is_bf16) {
-                    const u32x2 v = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(p.x) + kc);
+                    const u32x2 v = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(px) + kc);
                     xv[r][0] = __uint_as_float(v.x << 16); xv[r][1] = __uint_as_float(v.x & 0xFFFF0000u);
                     xv[r][2] = __uint_as_float(v.y << 16); xv[r][3] = __uint_as_float(v.y & 0xFFFF0000u);
                 } else {
-                    const f32x4 v = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.x) + kc);
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(px) + kc);
                     xv[r][0] = v.x; xv[r][1] = v.y; xv[r][2] = v.z; xv[r][3] = v.w;
                 }
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const size_t off = (size_t)min(k + e, p.N - 1) * p.ldx;
-                    xv[r][e] = p.x_is_bf16 ? __uint_as_float(((uint32_t) static_cast<const uint16_t*>(p.x)[off]) << 16)
-                                           : static_cast<const float*>(p.x)[off];
+                    xv[r][e] = p.x_is_bf16 ? __uint_as_float(((uint32_t) reinterpret_cast<const uint16_t*>(px)[off]) << 16)
+                                           : reinterpret_cast<const float*>(px)[off];
                 }
             }
         }
@@ -285,7 +298,7 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
         m = wave_max(m);
         ex_in = bound_exponent(m);
         ex_z = bound_exponent(p.bound_V * m) + 1;   // one more bit for the rounding of the bound itself
-        if (blockIdx.x == 0 && threadIdx.x == 0) p.meta[0] = ex_z;
+        if (blk == 0 && threadIdx.x == 0) p.meta[tok] = ex_z;
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
             const int k = 4 * (threadIdx.x + 1024 * r);
@@ -336,17 +349,17 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
     }
     __syncthreads();
     for (int rl = threadIdx.x; rl < p.sw * 16; rl += blockDim.x) {
-        const int row = blockIdx.x * p.sw * 16 + rl;
+        const int row = blk * p.sw * 16 + rl;
         if (row >= p.rows_out) continue;
         // acc = 2 * sum_k A[row][k] * fixed(in[k]): undo the factor 2 and the fixed-point scale
         const double val = combine_planes(sums + rl * 8) * pow2(ex_in - 31);
         if constexpr (STAGE_U) {
-            tsvd_store_y(p.y, (size_t)row * p.ldy, (float)(p.bias ? val + (double)tail_own : val), p.out_bf16);
+            tsvd_store_y(py, (size_t)row * p.ldy, (float)(p.bias ? val + (double)tail_own : val), p.out_bf16);
         } else {
             const float z = (float)((double)tail_own * val);
             uint32_t ev, od;
             digit_codes(z, ex_z, ev, od);
-            unsigned char* dst = p.planes_out + row;
+            unsigned char* dst = p.planes_out + pz + row;
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 dst[(size_t)(2 * d) * p.Kp] = (unsigned char)(ev >> (8 * d));
@@ -368,6 +381,8 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
 __global__ void __launch_bounds__(1024)
 tsvd_gemv_fused_kernel(tsvd_gemv_fused_args p) {
     extern __shared__ __align__(16) unsigned char smem[];
+    const unsigned char* const px = static_cast<const unsigned char*>(p.x) + (size_t)blockIdx.x * p.x_token * (p.x_is_bf16 ? 2 : 4);
+    unsigned char* const py = static_cast<unsigned char*>(p.y) + (size_t)blockIdx.x * p.y_token * (p.out_bf16 ? 2 : 4);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, g = lane >> 4;
     const int xstride = p.Np + 16, zstride = p.Kp + 16;
@@ -383,19 +398,19 @@ tsvd_gemv_fused_kernel(tsvd_gemv_fused_args p) {
         if (p.x_vec) {
             const int kc = min(k, p.N - 4);
             if (p.x_is_bf16) {
-                const u32x2 v = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(p.x) + kc);
+                const u32x2 v = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(px) + kc);
                 xv[0] = __uint_as_float(v.x << 16); xv[1] = __uint_as_float(v.x & 0xFFFF0000u);
                 xv[2] = __uint_as_float(v.y << 16); xv[3] = __uint_as_float(v.y & 0xFFFF0000u);
             } else {
-                const f32x4 v = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.x) + kc);
+                const f32x4 v = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(px) + kc);
                 xv[0] = v.x; xv[1] = v.y; xv[2] = v.z; xv[3] = v.w;
             }
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const size_t off = (size_t)min(k + e, p.N - 1) * p.ldx;
-                xv[e] = p.x_is_bf16 ? __uint_as_float(((uint32_t) static_cast<const uint16_t*>(p.x)[off]) << 16)
-                                    : static_cast<const float*>(p.x)[off];
+                xv[e] = p.x_is_bf16 ? __uint_as_float(((uint32_t) reinterpret_cast<const uint16_t*>(px)[off]) << 16)
+                                    : reinterpret_cast<const float*>(px)[off];
             }
         }
     }
@@ -489,7 +504,7 @@ tsvd_gemv_fused_kernel(tsvd_gemv_fused_args p) {
             const int row = 256 * r + threadIdx.x;
             if (row < p.M) {
                 const double val = combine_planes(wred + threadIdx.x * 8) * pow2(ex_z - 31);
-                tsvd_store_y(p.y, (size_t)row * p.ldy, (float)(p.bias ? val + (double)p.bias[row] : val), p.out_bf16);
+                tsvd_store_y(py, (size_t)row * p.ldy, (float)(p.bias ? val + (double)p.bias[row] : val), p.out_bf16);
             }
         }
         __syncthreads();
@@ -855,8 +870,16 @@ size_t gemv_fused_lds_bytes(long long Np, long long Kp) {
 namespace {
 template <bool STAGE_U, int ROUNDS>
 hipError_t init_one() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_gemv_kernel<STAGE_U, ROUNDS>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_gemv_kernel<STAGE_U, ROUNDS, false>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, TSVD_SKINNY_MAX_LDS);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_gemv_kernel<STAGE_U, ROUNDS, true>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, TSVD_SKINNY_MAX_LDS);
+}
+template <bool STAGE_U, int ROUNDS>
+void launch_one(const tsvd_gemv_args& a, dim3 grid, size_t lds, hipStream_t stream) {
+    if (a.tokens > 1) hipLaunchKernelGGL((tsvd_gemv_kernel<STAGE_U, ROUNDS, true>), grid, dim3(1024), lds, stream, a);
+    else hipLaunchKernelGGL((tsvd_gemv_kernel<STAGE_U, ROUNDS, false>), grid, dim3(1024), lds, stream, a);
 }
 size_t gemv_lds_bytes(long long kdim) {
     return ((8 * (size_t)(kdim + 16) + 255) & ~(size_t)255) + (16 * 256 + 256 * 8 + 64) * sizeof(float);
@@ -871,10 +894,10 @@ bool tsvd_gemv_fused_fits(long long Mp, long long Kp, long long Np) {
 }
 
 hipError_t tsvd_launch_gemv_fused(const tsvd_gemv_fused_args& a, hipStream_t stream) {
-    if (a.strips_v < 1 || a.strips_u < 1 || a.nkt_v < 1 || a.nkt_u < 1 || a.Np > 4096 ||
+    if (a.tokens < 1 || a.strips_v < 1 || a.strips_u < 1 || a.nkt_v < 1 || a.nkt_u < 1 || a.Np > 4096 ||
         ((a.strips_v + 15) / 16) * a.nkt_v > FUSED_MAX_ITEMS || ((a.strips_u + 15) / 16) * a.nkt_u > FUSED_MAX_ITEMS)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(tsvd_gemv_fused_kernel, dim3(1), dim3(1024), gemv_fused_lds_bytes(a.Np, a.Kp), stream, a);
+    hipLaunchKernelGGL(tsvd_gemv_fused_kernel, dim3(a.tokens), dim3(1024), gemv_fused_lds_bytes(a.Np, a.Kp), stream, a);
     return hipGetLastError();
 }
 
@@ -902,20 +925,21 @@ bool tsvd_gemv_fits(long long Np, long long Kp) {
 }
 
 hipError_t tsvd_launch_gemv(const tsvd_gemv_args& a, bool stage_u, hipStream_t stream) {
-    if (!tsvd_gemv_fits(a.Np, a.Kp) || a.sw < 1 || a.kw_log2 < 0 || (a.sw << a.kw_log2) > 16 || a.strips < 1)
+    if (!tsvd_gemv_fits(a.Np, a.Kp) || a.sw < 1 || a.kw_log2 < 0 || (a.sw << a.kw_log2) > 16 || a.strips < 1 || a.tokens < 1 || a.tokens > TSVD_GEMV_MAX_TOKENS)
         return hipErrorInvalidValue;
-    const dim3 grid((a.strips + a.sw - 1) / a.sw), block(1024);
+    const unsigned blocks = (unsigned)((a.strips + a.sw - 1) / a.sw);
+    const dim3 grid(a.tokens > 1 ? (blocks + 7) / 8 * 8 * a.tokens : blocks);
     if (stage_u) {
         const size_t lds = gemv_lds_bytes(a.Kp);
-        if (a.Kp <= 2048) hipLaunchKernelGGL((tsvd_gemv_kernel<true, 1>), grid, block, lds, stream, a);
-        else if (a.Kp <= 4096) hipLaunchKernelGGL((tsvd_gemv_kernel<true, 2>), grid, block, lds, stream, a);
-        else if (a.Kp <= 8192) hipLaunchKernelGGL((tsvd_gemv_kernel<true, 4>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((tsvd_gemv_kernel<true, 8>), grid, block, lds, stream, a);
+        if (a.Kp <= 2048) launch_one<true, 1>(a, grid, lds, stream);
+        else if (a.Kp <= 4096) launch_one<true, 2>(a, grid, lds, stream);
+        else if (a.Kp <= 8192) launch_one<true, 4>(a, grid, lds, stream);
+        else launch_one<true, 8>(a, grid, lds, stream);
     } else {
         const size_t lds = gemv_lds_bytes(a.Np);
-        if (a.Np <= 4096) hipLaunchKernelGGL((tsvd_gemv_kernel<false, 1>), grid, block, lds, stream, a);
-        else if (a.Np <= 8192) hipLaunchKernelGGL((tsvd_gemv_kernel<false, 2>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((tsvd_gemv_kernel<false, 4>), grid, block, lds, stream, a);
+        if (a.Np <= 4096) launch_one<false, 1>(a, grid, lds, stream);
+        else if (a.Np <= 8192) launch_one<false, 2>(a, grid, lds, stream);
+        else launch_one<false, 4>(a, grid, lds, stream);
     }
     return hipGetLastError();
 }

@@ -48,14 +48,15 @@ struct tsvd_gemv_args {
     // stage V
     const void* x; int x_is_bf16; int x_vec; long long ldx;   // x_vec: contiguous and 16-byte aligned
     const float* S; float bound_V;
-    unsigned char* planes_out;            // fp8 digit planes of z, [8][Kp]
+    unsigned char* planes_out;            // fp8 digit planes of z, [tokens][8][Kp]
     // stage U
     const unsigned char* planes_in;
     void* y; long long ldy;               // fp32 (or bf16 with out_bf16) [M][ldy]
     const float* bias; int out_bf16;      // bias per output row or null; output type
-    int* meta;                            // fixed-point exponent of z (written by V, read by U)
+    int* meta;                            // [tokens] fixed-point exponents of z (written by V, read by U)
     int early_tiles;                      // 1: the first tile request goes out with the activation loads (default), 0: after them
     long long* clocks;                    // optional tuning aid: [grid][16] phase timestamps, or null
+    int tokens; long long x_token, y_token;   // tokens of the launch (each on workgroups of its own), elements from one to the next
 };
 // Both stages of a single token in ONE launch of ONE workgroup, for matrices of at most 64 tiles
 // per stage (tsvd_gemv.hip): z never leaves LDS.
@@ -64,6 +65,7 @@ struct tsvd_gemv_fused_args {
     const void* tiles_u; int strips_u, nkt_u;     // U: ceil(M/16) strips, Kp/256 tiles
     int N, Np, Kp, M;
     const void* x; int x_is_bf16; int x_vec; long long ldx;
+    int tokens; long long x_token, y_token;       // a workgroup per token
     const float* S; float bound_V;
     void* y; long long ldy; const float* bias; int out_bf16;
 };
@@ -102,6 +104,7 @@ hipError_t tsvd_gemv_init();
 bool tsvd_gemv_fits(long long Np, long long Kp);
 hipError_t tsvd_launch_gemv(const tsvd_gemv_args& a, bool stage_u, hipStream_t stream);
 #define TSVD_GEMV_MAX_GRID 1024
+#define TSVD_GEMV_MAX_TOKENS 16
 
 // One stage of the few-token path (tsvd_mid.hip): 2 <= B <= 16 tokens of bf16 activations.
 struct tsvd_mid_args {

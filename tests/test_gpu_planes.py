@@ -20,7 +20,7 @@ def tsvd():
     return t
 
 
-def _check(tsvd, M, N, K, B, x_dtype, switches):
+def _check(tsvd, M, N, K, B, x_dtype, switches, bf16_tol=1e-4):
     import torch
     i = workloads.make_integer_inputs(M, N, K, B, 0.5, x_dtype, seed=M + N + K + B)
     ref = oracle.forward(i.U, i.S, i.V, i.X)
@@ -42,7 +42,7 @@ def _check(tsvd, M, N, K, B, x_dtype, switches):
     j = workloads.make_inputs(M, N, K, B, 0.6, 0.02, x_dtype, seed=M + 2 * N + K + B)
     h = tsvd.tsvd_pack(j.U, j.S, j.V)
     e = rel_err(tsvd.tsvd_forward(h, to_device(j)).cpu().numpy().astype(np.float64), oracle.forward(j.U, j.S, j.V, j.X))
-    assert e <= (1e-6 if x_dtype == "f32" else 1e-4)
+    assert e <= (1e-6 if x_dtype == "f32" else bf16_tol)
     tsvd.tsvd_free(h)
 
 
