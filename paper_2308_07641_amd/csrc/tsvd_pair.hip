@@ -7,10 +7,12 @@
 // [512, 256] matrix.  Rounding: every squaring perturbs its matrix by a few units in the last place of its norm, so the
 // vector is off by rounding over the gap, as with any backward-stable method.
 //
-// The result is X s for the fixed start vector s of the Lanczos process, the projection of the start vector: so the
-// sign is the one with a positive product with the start vector, which is also the sign that process gives (its
-// tridiagonal matrix has positive off-diagonal entries, its leading eigenvector entries of one sign), and in a
-// degenerate leading space both return the same vector.
+// The result is X x_j, with x_j the column of X that has the largest diagonal entry: that entry is at least trace / n, so
+// its unit vector e_j has a cosine of at least 1 / sqrt(n) with the leading space whatever the matrix (a fixed vector, as the start
+// vector of the Lanczos process, may be orthogonal to it), and the product with X takes the rounding of x_j back to that
+// of X itself.  In a degenerate leading space that is one of its vectors.
+// The sign is the one with a positive product with the start vector of the Lanczos process, which is also the sign that
+// process gives (its tridiagonal matrix has positive off-diagonal entries, its leading eigenvector entries of one sign).
 #include "tsvd_pair.h"
 
 #include <algorithm>
@@ -45,8 +47,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 // as zero, c = 1.  Extra workgroups compute s = R v0 where the shorter side is the rows.
 // Otherwise P = X[step & 1], symmetric, zero beyond n, c = 1 / trace^2: the trace of every X from the second on is
 // sum lambda^2 / (sum lambda)^2 of the one before, 1 - 2 (lambda_2 / lambda_1)^(2^p) near the end.  Once that is within 1e-6 of
-// 1, X itself has the ratio squared, below 2.5e-13, and is the result (the residual |R^T u - sigma v| is that times the gap,
-// against the 1e-12 sigma of the Lanczos process): every workgroup of this and the later launches returns.
+// 1, X itself has the ratio squared, below 2.5e-13, and is the result (X x_j has it squared again, times at most sqrt(n)):
+// every workgroup of this and the later launches returns.
 template <int T, bool GRAM, bool TR>
 __global__ void __launch_bounds__(256)
 tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step) {
@@ -182,18 +184,41 @@ tsvd_pair_start_kernel(double* __restrict__ v0, int N, tsvd_pair_state* state) {
     }
 }
 
-// The vector of the shorter side, a wavefront per row: X s.
+// The vector of the shorter side, a wavefront per row: X x_j, x_j the row (or column) of X with the largest diagonal entry, the first of
+// equal ones; its sign that of s x_j.  Every workgroup finds j and the sign for itself, in the same order.
 __global__ void __launch_bounds__(256)
 tsvd_pair_short_kernel(tsvd_pair_plan p, int count) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    __shared__ double most[4], red[4];
+    __shared__ int where[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * 4 + wave;
     const int last = p.state->last;
     if (blockIdx.x == 0 && threadIdx.x == 0 && last < 0) ++p.state->missed;
-    if (row >= p.n) return;
-    const double* X = p.X[(last >= 0 ? last : count) & 1] + (size_t)row * p.np;
+    const double* X = p.X[(last >= 0 ? last : count) & 1];
+    double best = -1.0;
+    int j = 0;
+    for (int d = threadIdx.x; d < p.n; d += 256) {
+        const double v = X[(size_t)d * (p.np + 1)];
+        if (v > best) best = v, j = d;
+    }
+    auto take = [&](double v, int d) {
+        if (v > best || (v == best && d < j)) best = v, j = d;
+    };
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) take(__shfl_xor(best, o, 64), __shfl_xor(j, o, 64));
+    if (lane == 0) most[wave] = best, where[wave] = j;
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) take(most[w], where[w]);
+    const double* x = X + (size_t)j * p.np;
+    double sx = 0.0;
+    for (int k = threadIdx.x; k < p.n; k += 256) sx += x[k] * p.s[k];
+    sx = wave_sum(sx);
+    if (lane == 0) red[wave] = sx;
     double a = 0.0;
-    for (int k = lane; k < p.n; k += 64) a += X[k] * p.s[k];
+    const double* mine = X + (size_t)min(row, p.n - 1) * p.np;
+    for (int k = lane; k < p.n; k += 64) a += mine[k] * x[k];
     a = wave_sum(a);
-    if (lane == 0) (p.N <= p.M ? p.v : p.u)[row] = a;
+    __syncthreads();
+    if (lane == 0 && row < p.n) (p.N <= p.M ? p.v : p.u)[row] = (red[0] + red[1]) + (red[2] + red[3]) < 0.0 ? -a : a;
 }
 
 // The vector of the longer side.  N <= M: u = R v, a wavefront per row.  M < N: v = R^T u, 64 columns per workgroup, the

@@ -128,6 +128,28 @@ def test_leading_singular_pair_by_squarings_at_tile_edges(tsvd, M, N):
         assert v @ start > 0                                                        # the sign is that of the start vector
 
 
+@pytest.mark.parametrize("M,N", [(128, 64), (64, 128), (500, 420)])
+@pytest.mark.parametrize("cos", [0.0, 1e-12, 1e-6])
+def test_leading_singular_pair_whatever_its_angle_to_the_start_vector(tsvd, M, N, cos):
+    """The leading direction is orthogonal to the fixed start vector, or nearly: the pair must be as exact as any other."""
+    rng = np.random.default_rng(M + N)
+    n = min(M, N)
+    start = 1.0 + 0.5 * np.sin(1.0 + 0.7 * np.arange(N))
+    start /= np.linalg.norm(start)
+    v0 = rng.standard_normal(N)
+    v0 -= start * (start @ v0)
+    v0 = np.sqrt(1.0 - cos * cos) * v0 / np.linalg.norm(v0) + cos * start
+    A = np.linalg.qr(rng.standard_normal((M, n)))[0]
+    B = np.linalg.qr(np.column_stack([v0, rng.standard_normal((N, n - 1))]))[0]
+    R = (A * 0.9 ** np.arange(n)) @ B.T
+    print(f"case pair off the start vector M={M} N={N} cos={cos}", flush=True)
+    u, sigma, v, _ = tsvd.tsvd_leading_singular_pair(_dev(R))
+    u, sigma, v = u.cpu().numpy(), float(sigma.cpu()[0]), v.cpu().numpy()
+    assert abs(sigma - 1.0) <= 1e-12
+    assert np.linalg.norm(R @ v - sigma * u) <= 1e-12 and np.linalg.norm(R.T @ u - sigma * v) <= 1e-12
+    assert abs(abs(v @ v0) - 1.0) <= 1e-12
+
+
 def test_transition_follows_the_oracle_on_separated_spectra(tsvd):
     """Algorithm 2 end to end.  W is built with well separated singular values, so every residual
     has a clear leading pair and both sides must pick the same ternary vectors: U S V, S and the
