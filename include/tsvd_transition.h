@@ -55,6 +55,7 @@ tsvd_status tsvd_residual(const double* W_dev, const int8_t* U_dev, int64_t ldu,
  * Golub-Kahan-Lanczos bidiagonalisation with full reorthogonalisation (restarted every 128 steps).  Either way the residual
  * |R^T u - sigma v| of the pair ends below 1e-12 sigma, unless max_steps squarings or Lanczos steps were not enough.  The host
  * looks at the progress in between, so the call SYNCHRONISES with the stream.
+ * The sum of the squares of R has to stay within the range of fp64 (entries of about 1e-150 to 1e150).
  *   u_dev [M], v_dev [N] : unit vectors; sigma_dev [1]; steps_dev optional int32[1]: squarings or Lanczos steps taken.
  *   workspace : device, at least tsvd_leading_singular_pair_workspace(M, N) bytes, 256-byte aligned.
  * The sign of the pair (u, v) is arbitrary, as it is for any SVD routine.  M, N <= 8192. */

@@ -45,7 +45,10 @@ __device__ __forceinline__ double wave_sum(double v) {
 //
 // GRAM (first launch): P is R by its rows (TR = false) or columns (TR), any pitch; rows beyond n and indices beyond L read
 // as zero, c = 1.  Extra workgroups compute s = R v0 where the shorter side is the rows.
-// Otherwise P = X[step & 1], symmetric, zero beyond n, c = 1 / trace^2: the trace of every X from the second on is
+// Otherwise P = X[step & 1], symmetric, zero beyond n, c = 1 / trace^2.  The Gram matrix has the squares of R's magnitudes, and
+// their squares would leave the range of fp64 for entries of R beyond 1e77 or below 1e-81: step 0 scales its operands by the power of
+// two next to its trace (exact; a reduction and a barrier before the products, in this step only).  So R counts as long as its sum of
+// squares does, 1e-150 to 1e150.  The trace of every X from the second on is
 // sum lambda^2 / (sum lambda)^2 of the one before, 1 - 2 (lambda_2 / lambda_1)^(2^p) near the end.  Once that is within 1e-6 of
 // 1, X itself has the ratio squared, below 2.5e-13, and is the result (X x_j has it squared again, times at most sqrt(n)):
 // every workgroup of this and the later launches returns.
@@ -95,11 +98,26 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
         return TR ? f64x2{row[(size_t)k0 * p.N], row[(size_t)k1 * p.N]} : f64x2{row[k0], row[k1]};
     };
     // everything a wavefront needs is requested before anything is waited for
-    double tr = 0.0;
+    double tr = 0.0, trace = 0.0, scale = 1.0;
     int done = -1;
     if constexpr (!GRAM) {
         done = p.state->last;
         tr = P[(size_t)min((int)threadIdx.x, p.np - 1) * (p.np + 1)];
+    }
+    auto sum_trace = [&] {                                   // the wavefronts' shares of the trace into red
+        if ((int)threadIdx.x >= p.np) tr = 0.0;
+        for (int d = threadIdx.x + 256; d < p.np; d += 256) tr += P[(size_t)d * (p.np + 1)];
+        tr = wave_sum(tr);
+        if (lane == 0) red[wave] = tr;
+    };
+    if (!GRAM && step == 0) {
+        sum_trace();
+        __syncthreads();
+        trace = (red[0] + red[1]) + (red[2] + red[3]);
+        int e = 0;
+        (void)frexp(trace, &e);
+        scale = ldexp(1.0, -max(e, -1000));
+        trace *= scale;
     }
     for (int k0 = wave * 64; k0 < L; k0 += 256) {
         f64x2 a[T][8], b[T][8];
@@ -124,6 +142,14 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
                     }
         } else if (done >= 0) {
             break;
+        } else if (step == 0) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int q = 0; q < T; ++q) {
+                    a[q][t] *= scale;
+                    b[q][t] *= scale;
+                }
         }
 #pragma unroll
         for (int t = 0; t < 8; ++t)
@@ -138,10 +164,7 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
     double c = 1.0;
     if constexpr (!GRAM) {
         if (done >= 0) return;
-        if ((int)threadIdx.x >= p.np) tr = 0.0;
-        for (int d = threadIdx.x + 256; d < p.np; d += 256) tr += P[(size_t)d * (p.np + 1)];
-        tr = wave_sum(tr);
-        if (lane == 0) red[wave] = tr;
+        if (step > 0) sum_trace();
     }
     // result lane (i, g): column i, rows g + 4 v
 #pragma unroll
@@ -152,10 +175,12 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
             for (int v = 0; v < 4; ++v) part[wave][(qa * T + qb) * 256 + (g + 4 * v) * 16 + i] = acc[qa][qb][v];
     __syncthreads();
     if constexpr (!GRAM) {
-        const double trace = (red[0] + red[1]) + (red[2] + red[3]);
-        if (step > 0 && fabs(1.0 - trace) < 1e-6) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = step;
-            return;
+        if (step > 0) {
+            trace = (red[0] + red[1]) + (red[2] + red[3]);
+            if (fabs(1.0 - trace) < 1e-6) {
+                if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = step;
+                return;
+            }
         }
         c = trace > 0.0 ? 1.0 / (trace * trace) : 0.0;
     }

@@ -150,6 +150,23 @@ def test_leading_singular_pair_whatever_its_angle_to_the_start_vector(tsvd, M, N
     assert abs(abs(v @ v0) - 1.0) <= 1e-12
 
 
+@pytest.mark.parametrize("M,N", [(128, 64), (64, 128), (500, 420)])
+@pytest.mark.parametrize("power", [330, -330, 490, -490])
+def test_leading_singular_pair_of_very_large_and_small_entries(tsvd, M, N, power):
+    """Entries of 1e99 to 1e147 and their inverses: scaling a matrix by a power of two scales sigma by it and leaves the vectors."""
+    R = np.random.default_rng(M + N).laplace(size=(M, N))
+    print(f"case pair range M={M} N={N} power={power}", flush=True)
+    u, sigma, v, _ = tsvd.tsvd_leading_singular_pair(_dev(R))
+    us, sigmas, vs, _ = tsvd.tsvd_leading_singular_pair(_dev(np.ldexp(R, power)))
+    assert abs(np.ldexp(float(sigmas.cpu()[0]), -power) - float(sigma.cpu()[0])) <= 1e-13 * float(sigma.cpu()[0])
+    assert (us - u).abs().max() <= 1e-11 and (vs - v).abs().max() <= 1e-11
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(R), THETA, 0.0, 3)
+    Us, Ss, Vs, errss, status_s = tsvd.tsvd_transition(_dev(np.ldexp(R, power)), THETA, 0.0, 3)
+    assert status == status_s == 0
+    assert (U == Us).all() and (V == Vs).all()
+    assert np.max(np.abs(np.ldexp(Ss.cpu().numpy(), -power) - S.cpu().numpy())) <= 1e-12 * float(S.abs().max())
+
+
 def test_transition_follows_the_oracle_on_separated_spectra(tsvd):
     """Algorithm 2 end to end.  W is built with well separated singular values, so every residual
     has a clear leading pair and both sides must pick the same ternary vectors: U S V, S and the
