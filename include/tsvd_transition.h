@@ -66,7 +66,7 @@ tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M, int64_t N
 
 /* Algorithm 2 with q = 1, chaining the calls above: until |W - U diag(S) V|_F / |W|_F <= tol or
  * the rank reaches max_rank.  SYNCHRONISES with the stream once per iteration (the exit test
- * reads one number back; the following iteration is enqueued by then and dropped where the loop ends).
+ * reads one number back; up to min(M, N) = 2048 the following iteration is enqueued by then and dropped where the loop ends).
  *   W_dev : [M][N] fp64.   U_dev : [M][max_rank] int8, V_dev : [max_rank][N] int8, S_dev :
  *   [max_rank] fp64: the first *rank_out columns / rows / entries are the result (U has row stride
  *   max_rank).   errors_host : optional host array [max_rank]: relative error after each iteration.

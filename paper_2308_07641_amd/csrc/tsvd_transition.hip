@@ -1188,8 +1188,9 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         launch_solve(G, (long long)max_rank, dvec, (int)K, scales[i % 3], scales[(i + 2) % 3], nullptr, part, (int)take, (int)M, factor, s);
         residual(i, K);
     };
-    // One iteration is always enqueued beyond the one the host waits for: it costs nothing where the loop goes on, and
-    // where the loop ends nothing of it is used (its components lie beyond the rank, its scales in a buffer of their own).
+    // With squarings one iteration is always enqueued beyond the one the host waits for: it costs nothing where the loop goes on, and
+    // where the loop ends nothing of it is used (its components lie beyond the rank, its scales in a buffer of their own).  The
+    // Lanczos process waits for the device itself: there the next iteration is enqueued once the loop is known to go on.
     int64_t K = 0, i = 1, ahead = 0;                                         // ahead: components enqueued
     int64_t take = std::min<int64_t>(q, max_rank);
     if (st == TSVD_OK && wnorm2 > 0.0) {
@@ -1197,7 +1198,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         ahead = take;
         while (st == TSVD_OK) {
             const int64_t next = std::min<int64_t>(q, max_rank - ahead);
-            if (next > 0) enqueue(i + 1, ahead, next);
+            if (squares && next > 0) enqueue(i + 1, ahead, next);
             if (st != TSVD_OK || !wait_for(i)) break;
             if (seen.pair.missed != 0 && squarings < TSVD_PAIR_MAX_SQUARINGS) {
                 // some pair needed more squarings: back to the residual before this iteration, with more of them
@@ -1218,6 +1219,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
             K += take;
             *rank_out = K;
             if (err <= tol || next <= 0) break;
+            if (!squares) enqueue(i + 1, ahead, next);
             take = next;
             ahead += next;
             ++i;

@@ -231,6 +231,37 @@ def test_transition_wide_matrix_and_rank_limit(tsvd):
     assert np.max(np.abs(np.array(errs) - np.array(eo))) <= 1e-9
 
 
+@pytest.mark.parametrize("M,N", [(2049, 2049), (2100, 2500)])
+def test_transition_beyond_the_sizes_of_the_squarings(tsvd, M, N):
+    """min(M, N) above 2048: leading pairs by Lanczos steps.  W has rank five, so the residual of K components has rank 5 + K and its
+    leading pair follows from thin factors.  Exit by the rank limit, by the tolerance and by a vector without a ternary neighbour."""
+    rng = np.random.default_rng(M + N)
+    A = np.linalg.qr(rng.standard_normal((M, 5)))[0] * 2.0 ** -np.arange(5)
+    B = np.linalg.qr(rng.standard_normal((N, 5)))[0].T
+    W = A @ B
+    Uo, Vo, scales, errors = np.zeros((M, 0)), np.zeros((0, N)), [np.zeros(0)], []
+    for _ in range(3):
+        ql, rl = np.linalg.qr(np.hstack([A, -Uo * scales[-1]]))
+        qr, rr = np.linalg.qr(np.vstack([B, Vo]).T)
+        a, _, b = np.linalg.svd(rl @ rr.T)
+        Uo = np.column_stack([Uo, tr.ternarize(ql @ a[:, 0], THETA)])
+        Vo = np.vstack([Vo, tr.ternarize(qr @ b[0, :], THETA)])
+        scales.append(np.linalg.solve((Uo.T @ Uo) * (Vo @ Vo.T), np.einsum("mk,mk->k", Uo, A @ (B @ Vo.T))))
+        errors.append(np.linalg.norm(W - (Uo * scales[-1]) @ Vo) / np.linalg.norm(W))
+    for K, tol in ((3, 0.0), (2, 0.5 * (errors[0] + errors[1]))):
+        print(f"case transition {M} {N} tol={tol}", flush=True)
+        U, S, V, errs, status = tsvd.tsvd_transition(_dev(W), THETA, tol, 3)
+        assert status == 0 and U.shape == (M, K) and V.shape == (K, N)
+        U, S, V = U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy()
+        for k in range(K):
+            sign = 1 if np.array_equal(U[:, k], Uo[:, k]) else -1
+            assert np.array_equal(sign * U[:, k], Uo[:, k]) and np.array_equal(sign * V[k, :], Vo[k, :]), k
+        assert np.max(np.abs(S - scales[K])) <= 1e-8 * np.max(np.abs(S))
+        assert np.max(np.abs(np.array(errs) - np.array(errors[:K]))) <= 1e-9
+    with pytest.raises(tsvd.TsvdError):
+        tsvd.tsvd_transition(_dev(W), 0.05, 0.0, 3)
+
+
 def test_transition_reports_a_vector_without_ternary_neighbour(tsvd):
     """At a tiny theta no ternary vector is close enough: the oracle raises, the GPU call returns
     the value error with rank 0."""
