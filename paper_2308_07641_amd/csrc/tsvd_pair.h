@@ -8,7 +8,8 @@
 // What the device reports about the squarings of one pair.
 struct tsvd_pair_state {
     int last;            // index of the squared matrix that is numerically of rank one, -1 while there is none
-    int missed;          // pairs since the caller cleared it whose squarings ended before that
+    int missed;          // pairs since it was last cleared whose squarings ended before that
+    int needed;          // most squarings that a pair needed since it was last cleared (all that were enqueued, where they were not enough)
 };
 
 struct tsvd_pair_plan {

@@ -206,6 +206,7 @@ tsvd_pair_start_kernel(double* __restrict__ v0, int N, tsvd_pair_state* state) {
     if (k == 0) {
         state->last = -1;
         state->missed = 0;
+        state->needed = 0;
     }
 }
 
@@ -217,7 +218,10 @@ tsvd_pair_short_kernel(tsvd_pair_plan p, int count) {
     __shared__ int where[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * 4 + wave;
     const int last = p.state->last;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && last < 0) ++p.state->missed;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (last < 0) ++p.state->missed;
+        p.state->needed = max(p.state->needed, last < 0 ? count : last + 1);
+    }
     const double* X = p.X[(last >= 0 ? last : count) & 1];
     double best = -1.0;
     int j = 0;

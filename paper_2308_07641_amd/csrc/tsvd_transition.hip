@@ -525,15 +525,18 @@ tsvd_residual_kernel(const double* __restrict__ W, const int8_t* __restrict__ U,
 struct transition_report {
     tsvd_pair_state pair;
     int failed;              // ternarizations without a result
-    int unused;
 };
+static_assert(sizeof(transition_report) % 8 == 0, "doubles follow it");
 __global__ void __launch_bounds__(256)
 tsvd_residual_rows_kernel(const double* __restrict__ W, const int8_t* __restrict__ Ut, int mp, const double* __restrict__ S,
                           const int8_t* __restrict__ V, int np, int M, int N, int K, double* __restrict__ R, double* __restrict__ part,
-                          const transition_report* __restrict__ seen, transition_report* __restrict__ told) {
+                          transition_report* __restrict__ seen, transition_report* __restrict__ told) {
     extern __shared__ __align__(16) unsigned char smem[];
     double* us = reinterpret_cast<double*>(smem);               // [4][K]
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) told[0] = seen[0];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        told[0] = seen[0];
+        seen[0].pair.missed = seen[0].pair.needed = 0;          // (of one iteration each)
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.y * 4, m = m0 + wave, n = blockIdx.x * 256 + 4 * lane;
     for (int k = threadIdx.x; k < K; k += 256) {
         const int w = *reinterpret_cast<const int*>(Ut + (size_t)k * mp + m0);
@@ -950,7 +953,7 @@ extern "C" tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M
         tsvd_pair_prepare(M, N, workspace, &plan, s);
         const int limit = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(1, (int)max_steps));
         int count = 0;
-        for (tsvd_pair_state state = {-1, 0}; count < limit && state.last < 0;) {
+        for (tsvd_pair_state state = {-1, 0, 0}; count < limit && state.last < 0;) {
             const int to = std::min(limit, count == 0 ? 16 : count + 8);
             tsvd_pair_square(plan, R_dev, count, to, s);
             count = to;
@@ -1151,7 +1154,10 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     residual(0, 0);                                                          // R = W, |W|^2
     double wnorm2 = 0.0;
     if (wait_for(0)) wnorm2 = rnorm2;
-    int squarings = 16;                                                      // enqueued per pair; grows if a pair needs more
+    // Squarings enqueued per pair: those beyond the ones a pair needs return at once, too few cost the iteration again.  Sixteen, and
+    // two more than the last iteration needed where that is more: one nearly degenerate residual leaves nothing behind.
+    constexpr int SQUARINGS = 16;
+    int squarings = SQUARINGS;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
     auto enqueue = [&](int64_t i, int64_t first, int64_t take) {
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
@@ -1200,9 +1206,9 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
             const int64_t next = std::min<int64_t>(q, max_rank - ahead);
             if (squares && next > 0) enqueue(i + 1, ahead, next);
             if (st != TSVD_OK || !wait_for(i)) break;
-            if (seen.pair.missed != 0 && squarings < TSVD_PAIR_MAX_SQUARINGS) {
+            if (seen.pair.missed != 0 && seen.pair.needed < TSVD_PAIR_MAX_SQUARINGS) {
                 // some pair needed more squarings: back to the residual before this iteration, with more of them
-                squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, squarings + 8);
+                squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, seen.pair.needed + 8);
                 if (!ok(hipStreamSynchronize(s)) || !ok(hipMemsetAsync(rep, 0, sizeof(transition_report), s))) break;
                 residual(i - 1, K);
                 enqueue(i, K, take);
@@ -1213,6 +1219,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
                 st = TSVD_EVALUE;           // no ternary vector within theta: the components of an unfinished iteration are dropped
                 break;
             }
+            squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(SQUARINGS, seen.pair.needed + 2));
             const double err = std::sqrt(rnorm2 / wnorm2);
             if (errors_host)
                 for (int64_t r = K; r < K + take; ++r) errors_host[r] = err;      // (one error per iteration, repeated for its components)

@@ -218,6 +218,31 @@ def test_transition_with_several_components_per_iteration(tsvd, q):
         assert all(np.array_equal(U7[:, k], Uo6[:, k]) or np.array_equal(-U7[:, k], Uo6[:, k]) for k in range(6))
 
 
+@pytest.mark.parametrize("q", [1, 2])
+@pytest.mark.parametrize("M,N", [(96, 80), (80, 96)])
+def test_transition_with_a_nearly_degenerate_residual(tsvd, M, N, q):
+    """The leading singular values of W are 1e-7 of themselves apart, which takes 27 squarings: the iteration that meets them is taken
+    again with more of them, those after it are not, and all follow the oracle."""
+    rng = np.random.default_rng(10)          # (as above: with ternary neighbours, and gaps of 2e-2 from the second iteration on)
+    r = 12
+    A, _ = np.linalg.qr(rng.standard_normal((M, r)))
+    B, _ = np.linalg.qr(rng.standard_normal((N, r)))
+    sv = 1.7 ** -np.arange(r)
+    sv[1] = 1.0 - 1e-7
+    W = (A * sv[None, :]) @ B.T
+    rank = 8
+    Uo, So, Vo, eo = tr.transition(W, THETA, q=q, max_rank=rank)
+    print(f"case nearly degenerate {M} {N} {q}", flush=True)
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(W), THETA, 0.0, rank, q=q)
+    assert status == 0
+    U, S, V = U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy()
+    for k in range(rank):
+        sign = 1 if np.array_equal(U[:, k], Uo[:, k]) else -1
+        assert np.array_equal(sign * U[:, k], Uo[:, k]) and np.array_equal(sign * V[k, :], Vo[k, :]), k
+    assert np.max(np.abs(S - So)) <= 1e-8 * np.max(np.abs(So))
+    assert np.max(np.abs(np.array(errs)[q - 1::q] - np.array(eo))) <= 1e-9
+
+
 def test_transition_wide_matrix_and_rank_limit(tsvd):
     """M < N, exit by the rank limit, status and shapes; the first components equal the oracle's."""
     W = np.random.default_rng(12).laplace(size=(48, 160))
