@@ -17,6 +17,8 @@
 
 #include <algorithm>
 
+#include "tsvd_wave.h"
+
 namespace {
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
@@ -27,12 +29,6 @@ size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 // Shorter side from which the squarings cost more than the Lanczos steps: a squaring is n^3 multiplications, a Lanczos
 // step two passes over R.
 constexpr int PAIR_MAX_N = 2048;
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // Workgroup (bi, bj), bi <= bj, of Y = c P P^T for P [rows][L]: T x T blocks of 16 x 16, the contraction split over four
 // wavefronts (v_mfma_f64_16x16x4), each 64 indices at a time; the block and its mirror image are stored.
@@ -210,44 +206,54 @@ tsvd_pair_start_kernel(double* __restrict__ v0, int N, tsvd_pair_state* state) {
     }
 }
 
-// The vector of the shorter side, a wavefront per row: X x_j, x_j the row (or column) of X with the largest diagonal entry, the first of
-// equal ones; its sign that of s x_j.  Every workgroup finds j and the sign for itself, in the same order.
+// The vector of the shorter side, a wavefront per row: X x_j, x_j the row (or column) of X with the largest diagonal entry (to
+// nine bits: the upper words of the entries, their last bits replaced by the index); its sign that of s x_j.  Every
+// workgroup finds j and the sign for itself.  A chain of loads (state, diagonal, x_j): what does not depend on j is requested first.
+static_assert(PAIR_MAX_N <= 2048, "eleven bits of an index");
 __global__ void __launch_bounds__(256)
 tsvd_pair_short_kernel(tsvd_pair_plan p, int count) {
-    __shared__ double most[4], red[4];
-    __shared__ int where[4];
+    __shared__ uint32_t most[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * 4 + wave;
     const int last = p.state->last;
+    const double* X = p.X[(last >= 0 ? last : count) & 1];
+    const double* mine = X + (size_t)min(row, p.n - 1) * p.np;
+    uint32_t best = 0;
+    for (int d = threadIdx.x; d < p.n; d += 256)
+        best = max(best, ((uint32_t)(__builtin_bit_cast(uint64_t, X[(size_t)d * (p.np + 1)]) >> 32) & ~2047u) | (uint32_t)(2047 - d));
+    double xr[4], sr[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        xr[t] = mine[min(lane + 64 * t, p.n - 1)];
+        sr[t] = p.s[min(lane + 64 * t, p.n - 1)];
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (last < 0) ++p.state->missed;
         p.state->needed = max(p.state->needed, last < 0 ? count : last + 1);
     }
-    const double* X = p.X[(last >= 0 ? last : count) & 1];
-    double best = -1.0;
-    int j = 0;
-    for (int d = threadIdx.x; d < p.n; d += 256) {
-        const double v = X[(size_t)d * (p.np + 1)];
-        if (v > best) best = v, j = d;
-    }
-    auto take = [&](double v, int d) {
-        if (v > best || (v == best && d < j)) best = v, j = d;
-    };
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) take(__shfl_xor(best, o, 64), __shfl_xor(j, o, 64));
-    if (lane == 0) most[wave] = best, where[wave] = j;
+    best = max(best, lane_xor32<32>(best));
+    best = max(best, lane_xor32<16>(best));
+    best = max(best, lane_xor32<8>(best));
+    best = max(best, lane_xor32<4>(best));
+    best = max(best, lane_xor32<2>(best));
+    best = max(best, lane_xor32<1>(best));
+    if (lane == 0) most[wave] = best;
     __syncthreads();
-    for (int w = 0; w < 4; ++w) take(most[w], where[w]);
+    const int j = 2047 - (int)(max(max(most[0], most[1]), max(most[2], most[3])) & 2047u);
     const double* x = X + (size_t)j * p.np;
-    double sx = 0.0;
-    for (int k = threadIdx.x; k < p.n; k += 256) sx += x[k] * p.s[k];
-    sx = wave_sum(sx);
-    if (lane == 0) red[wave] = sx;
-    double a = 0.0;
-    const double* mine = X + (size_t)min(row, p.n - 1) * p.np;
-    for (int k = lane; k < p.n; k += 64) a += mine[k] * x[k];
+    double a = 0.0, sx = 0.0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const double v = lane + 64 * t < p.n ? x[min(lane + 64 * t, p.n - 1)] : 0.0;
+        a += xr[t] * v;
+        sx += sr[t] * v;
+    }
+    for (int k = lane + 256; k < p.n; k += 64) {
+        a += mine[k] * x[k];
+        sx += p.s[k] * x[k];
+    }
     a = wave_sum(a);
-    __syncthreads();
-    if (lane == 0 && row < p.n) (p.N <= p.M ? p.v : p.u)[row] = (red[0] + red[1]) + (red[2] + red[3]) < 0.0 ? -a : a;
+    sx = wave_sum(sx);                                       // (of every wavefront: cheaper than a second barrier)
+    if (lane == 0 && row < p.n) (p.N <= p.M ? p.v : p.u)[row] = sx < 0.0 ? -a : a;
 }
 
 // The vector of the longer side.  N <= M: u = R v, a wavefront per row.  M < N: v = R^T u, 64 columns per workgroup, the
