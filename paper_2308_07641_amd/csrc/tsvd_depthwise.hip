@@ -42,7 +42,8 @@ __device__ __forceinline__ bool each(std::integer_sequence<int, u...>, F f) {
 
 // ROW: elements per load of a row of x (8, or 2 / 1 where rows are not 16-byte aligned).  STEP: both strides.  With stride 2 the window of
 // 16 outputs would not fit 32 columns: a tile is 8 columns of two output rows there, and an input row is multiplied by the taps of both.
-// VEC: rows of y are a multiple of four elements (then a lane's four columns are inside or outside together and are stored at once).
+// VEC: rows of y are a multiple of four elements and y is aligned to four (then a lane's four columns are inside or outside together
+// and are stored at once).
 template <int K1, int STEP, int ROW, bool VEC>
 __global__ void __launch_bounds__(256, K1 == 7 && STEP == 1 ? 3 : 2)
 tsvd_depthwise_kernel(depthwise_args p) {
@@ -194,7 +195,8 @@ template <int K1, int STEP>
 void launch(const depthwise_args& a, int row, dim3 grid, hipStream_t stream) {
     auto go = [&](auto row_c) {
         constexpr int ROW = decltype(row_c)::value;
-        if (a.g.Wo % 4 == 0) hipLaunchKernelGGL((tsvd_depthwise_kernel<K1, STEP, ROW, true>), grid, dim3(256), 0, stream, a);
+        const bool vec = a.g.Wo % 4 == 0 && reinterpret_cast<uintptr_t>(a.g.y) % (a.g.out_bf16 ? 8 : 16) == 0;
+        if (vec) hipLaunchKernelGGL((tsvd_depthwise_kernel<K1, STEP, ROW, true>), grid, dim3(256), 0, stream, a);
         else hipLaunchKernelGGL((tsvd_depthwise_kernel<K1, STEP, ROW, false>), grid, dim3(256), 0, stream, a);
     };
     if (row == 8) go(std::integral_constant<int, 8>{});

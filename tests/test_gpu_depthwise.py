@@ -45,3 +45,38 @@ def test_depthwise_exact_and_random(tsvd, case):  # noqa: F811
     ref = oc.tsvd_conv2d(workloads.bf16_bits_to_f32(xb), U, S, V, 0, co, G, k1, k2, *geom, bias=bias, groups=G)
     got = _run(tsvd, U, S, V, 0, co, G, k1, k2, xb, geom, bias, tsvd.TSVD_F32, G)
     assert np.abs(got - ref).max() <= 1e-6 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3, 4])
+def test_depthwise_result_at_any_element(tsvd, offset, y_dtype):  # noqa: F811
+    """The C ABI takes any y aligned to its elements: rows of a multiple of four elements that start `offset` elements
+    beyond a 16-byte boundary, exact, and nothing written beside them."""
+    import ctypes
+
+    import torch
+    G, kg, k, images, H, W = 3, 2, 5, 2, 12, 16
+    rng = np.random.default_rng(offset)
+    U = np.kron(np.eye(G, dtype=np.int8), rng.choice([-1, 1], size=(1, kg)).astype(np.int8))
+    V = rng.integers(-1, 2, size=(G * kg, k * k)).astype(np.int8)
+    S = rng.integers(-2, 3, size=G * kg).astype(np.float32)
+    x = rng.integers(-2, 3, size=(images, G, H, W)).astype(np.float32)
+    ref = oc.tsvd_conv2d(x, U, S, V, 0, G, G, k, k, (1, 1), (2, 2), (1, 1), groups=G).transpose(1, 0, 2, 3).reshape(-1)
+    dtype = torch.float32 if y_dtype == "f32" else torch.bfloat16
+    xd = torch.from_numpy(np.ascontiguousarray(x.transpose(1, 0, 2, 3))).to("cuda:0").to(torch.bfloat16)
+    buf = torch.full((ref.size + 16,), -77.0, dtype=dtype, device="cuda:0")
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda:0")
+    h = tsvd.tsvd_pack(U, S, V)
+    geometry = (ctypes.c_int32 * 12)(0, G, G, k, k, 1, 1, 2, 2, 1, 1, G)
+    p, i64 = ctypes.c_void_p, ctypes.c_int64
+    print(f"case depthwise y at element {offset} {y_dtype}", flush=True)
+    forward = ctypes.CDLL(tsvd.lib_path()).tsvd_conv2d_forward
+    st = forward(p(h.ptr), geometry, p(xd.data_ptr()), i64(images), i64(H), i64(W), p(None), p(buf[offset:].data_ptr()),
+                 ctypes.c_int(tsvd.TSVD_F32 if y_dtype == "f32" else tsvd.TSVD_BF16), p(ws.data_ptr()), ctypes.c_size_t(256),
+                 p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    got = buf.float().cpu().numpy()
+    tsvd.tsvd_free(h)
+    assert st == 0
+    assert np.array_equal(got[offset:offset + ref.size], ref)
+    assert (got[:offset] == -77.0).all() and (got[offset + ref.size:] == -77.0).all()
