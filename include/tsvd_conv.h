@@ -26,6 +26,10 @@
  * Activations are feature-major like everywhere in this library: x_dev is bf16
  * [C_in][images][H][W], y_dev is [C_out][images][Ho][Wo] fp32 or bf16, both contiguous, with
  * Ho = (H + 2 pad1 - dil1 (K1 - 1) - 1) / stride1 + 1 and Wo likewise.  Zero padding.
+ * Inputs must be finite, as for tsvd_forward, but for one case: in a grouped convolution a value that is
+ * not finite stays near its taps.  With one input channel per group and kernels of 3, 5 or 7 rows of at most
+ * 7 taps, stride 1 or 2 and no dilation it reaches the outputs whose own non-zero taps hold it (a scale: the
+ * outputs of its channel), else at most those whose window, or the window of a horizontal neighbour, holds it.
  */
 #ifndef TSVD_CONV_H
 #define TSVD_CONV_H

@@ -12,6 +12,10 @@
 // The banded matrices are the same for every strip and column tile of a channel: the four wavefronts of a workgroup make them
 // together, then each keeps all of them in registers.
 //
+// The zeros of a band meet every column of the window, so an infinite or NaN pixel makes all outputs of its strip's rows NaN, and a
+// scale that is not finite all outputs of the channel.  Every such output is itself not finite: a lane that has stored one computes its
+// outputs again on the factors, tap by tap, zeros skipped, where only the outputs are touched whose taps hold the value.
+//
 // Measured on MI355X: 96 channels of 56 x 56, 7 x 7 at rank 5, 32 images, bf16: 68.4 -> 15.0 us (6.7 of them matrix instructions, about 3 the latency of the
 // first loads and the bands, 2 the launch); 60 random geometries of 64 to 768 channels: 1.3 to 33 times the speed of the kernel on the factors.
 #include "tsvd_depthwise.h"
@@ -40,6 +44,44 @@ __device__ __forceinline__ bool each(std::integer_sequence<int, u...>, F f) {
     return (f(std::integral_constant<int, u>{}) && ...);
 }
 
+// The outputs of this lane on the factors, one at a time.  (Everything is derived again from the lane's number: kept in registers over
+// the kernel's loop it would cost occupancy.)
+template <int STEP>
+__device__ __forceinline__ void outputs_on_factors(const depthwise_args& p, int wave) {
+    const tsvd_depthwise_problem& g = p.g;
+    int all = -1;
+    asm volatile("" : "+s"(all));
+    const int lane = __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+    const int i = lane & 15, q = lane >> 4, m = blockIdx.y, group = m / g.mg, task = blockIdx.x * 4 + wave;
+    const int ct = task % p.col_tiles, strip = task / p.col_tiles * 16 + i, img = strip / p.segments, row0 = (strip - img * p.segments) * p.R;
+    if (strip >= p.strips) return;
+    const int ox = ct * (16 / STEP) + 4 * (STEP == 1 ? q : q & 1), oend = min(ox + 4, g.Wo), yend = min(row0 + p.R, g.Ho);
+    const uint16_t* plane = g.x + ((size_t)group * g.images + img) * g.H * g.W;
+    const float b = g.bias ? g.bias[m] : 0.f;
+    for (int oy = row0 + (STEP == 1 ? 0 : q >> 1); oy < yend; oy += STEP) {
+#pragma unroll 1
+        for (int c = ox; c < oend; ++c) {
+            float y = 0.f;
+#pragma unroll 1
+            for (int k = 0; k < g.kg; ++k) {
+                const int pos = (int)tsvd_rank_position(group * g.kg + k, g.K), u = tsvd_code_at(g.U, g.u_tps, m, pos);
+                if (!(u & 1)) continue;
+                float z = 0.f;
+#pragma unroll 1
+                for (int tap = 0; tap < g.k1 * g.k2; ++tap) {
+                    const int v = tsvd_code_at(g.V, g.v_tps, pos, tap), dy = tap / g.k2, iy = oy * STEP - g.p1 + dy, ix = c * STEP - g.p2 + tap - dy * g.k2;
+                    if (!(v & 1) || (unsigned)iy >= (unsigned)g.H || (unsigned)ix >= (unsigned)g.W) continue;
+                    const float xv = __uint_as_float((uint32_t)plane[(size_t)iy * g.W + ix] << 16);
+                    z += v & 2 ? -xv : xv;
+                }
+                z *= g.S[pos];
+                y += u & 2 ? -z : z;
+            }
+            tsvd_store_y(g.y, (((size_t)m * g.images + img) * g.Ho + oy) * g.Wo + c, y + b, g.out_bf16);
+        }
+    }
+}
+
 // ROW: elements per load of a row of x (8, or 2 / 1 where rows are not 16-byte aligned).  STEP: both strides.  With stride 2 the window of
 // 16 outputs would not fit 32 columns: a tile is 8 columns of two output rows there, and an input row is multiplied by the taps of both.
 // VEC: rows of y are a multiple of four elements and y is aligned to four (then a lane's four columns are inside or outside together
@@ -56,6 +98,7 @@ tsvd_depthwise_kernel(depthwise_args p) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, q = lane >> 4;
     const int m = blockIdx.y, group = m / g.mg, task = blockIdx.x * 4 + wave;
     const bool active = task < p.tasks;
+    const int scalar_wave = __builtin_amdgcn_readfirstlane(wave);    // (for the outputs that are computed again)
 
     // ---- this lane's strip and columns; the rows of the first output
     const int ct = task % p.col_tiles, strip = task / p.col_tiles * 16 + i, img = strip / p.segments, row0 = (strip - img * p.segments) * p.R;
@@ -155,6 +198,7 @@ tsvd_depthwise_kernel(depthwise_args p) {
     unsigned at = (unsigned)((img * g.Ho + row0 + orow) * g.Wo + ox) * esize;
     if (VEC && ox >= g.Wo) at = NONE;
     const int tiles = (p.R + STEP - 1) / STEP;
+    bool odd = false;                                 // an output was not finite
     auto tile = [&](auto u_c, int t) __attribute__((always_inline)) {          // t % PERIOD = u
         constexpr int u = decltype(u_c)::value;
 #pragma unroll
@@ -181,6 +225,7 @@ tsvd_depthwise_kernel(depthwise_args p) {
                 else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[e]), yr, (int)te, 0, 0);
             }
         }
+        odd |= !(fabsf(y[0]) < INFINITY);         // (a value that spreads reaches all four)
         at += yp;
     };
     int t = 0;
@@ -189,6 +234,9 @@ tsvd_depthwise_kernel(depthwise_args p) {
         return ++t < tiles;
     })) {
     }
+    if (!odd) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the stores of the same elements are done)
+    outputs_on_factors<STEP>(p, scalar_wave);
 }
 
 template <int K1, int STEP>

@@ -80,3 +80,37 @@ def test_depthwise_result_at_any_element(tsvd, offset, y_dtype):  # noqa: F811
     assert st == 0
     assert np.array_equal(got[offset:offset + ref.size], ref)
     assert (got[:offset] == -77.0).all() and (got[offset + ref.size:] == -77.0).all()
+
+
+@pytest.mark.parametrize("k1,k2,st,pad,H,W", [(7, 7, 1, 3, 20, 40), (3, 5, 1, 1, 17, 19), (5, 5, 2, 2, 22, 36)])
+def test_depthwise_values_that_are_not_finite_stay_with_their_taps(tsvd, k1, k2, st, pad, H, W):  # noqa: F811
+    """Infinite and NaN pixels, and an infinite scale, reach the outputs whose own taps hold them and no others."""
+    G, kg, images = 3, 3, 2
+    rng = np.random.default_rng(k1 + 10 * k2 + st)
+    U = np.zeros((G, G * kg), dtype=np.int8)
+    for g in range(G):
+        U[g, g * kg:(g + 1) * kg] = [1, -1, 0]
+    V = rng.choice([-1, 0, 1], size=(G * kg, k1 * k2), p=[0.2, 0.6, 0.2]).astype(np.int8)
+    S = (rng.standard_normal(G * kg) * 0.3).astype(np.float32)
+    S[2 * kg] = np.inf                                            # the last channel
+    S[2] = np.nan                                                 # of a rank that no output uses
+    x = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(rng.standard_normal((images, G, H, W)).astype(np.float32)))
+    x[0, 0, 3, 5], x[0, 0, 9, W - 1], x[1, 0, 0, 0], x[1, 1, H - 1, 17] = np.inf, np.nan, -np.inf, np.inf
+    Ho, Wo = (H + 2 * pad - k1) // st + 1, (W + 2 * pad - k2) // st + 1
+    ref = np.zeros((images, G, Ho, Wo))
+    with np.errstate(invalid="ignore"):
+        for i, g, oy, ox in np.ndindex(*ref.shape):
+            for k in range(g * kg, g * kg + 2):
+                z = 0.0
+                for t in np.nonzero(V[k])[0]:
+                    iy, ix = oy * st - pad + t // k2, ox * st - pad + t % k2
+                    if 0 <= iy < H and 0 <= ix < W:
+                        z += float(V[k, t]) * float(x[i, g, iy, ix])
+                ref[i, g, oy, ox] += float(U[g, k]) * (float(S[k]) * z)
+    print(f"case depthwise not finite {k1} {k2} {st}", flush=True)
+    got = _run(tsvd, U, S, V, 0, G, G, k1, k2, workloads.f32_to_bf16_bits(x), ((st, st), (pad, pad), (1, 1)), None, tsvd.TSVD_F32, G)
+    finite = np.isfinite(ref)
+    assert finite[:, :2].mean() > 0.5 and not finite.all()
+    assert np.array_equal(np.isfinite(got), finite)
+    assert np.array_equal(got[~finite], ref[~finite], equal_nan=True)
+    assert np.abs(got[finite] - ref[finite]).max() <= 1e-6 * np.abs(ref[finite]).max()
