@@ -243,6 +243,39 @@ def test_transition_with_a_nearly_degenerate_residual(tsvd, M, N, q):
     assert np.max(np.abs(np.array(errs)[q - 1::q] - np.array(eo))) <= 1e-9
 
 
+@pytest.mark.parametrize("q,rank", [(1, 14), (2, 12), (3, 14)])
+def test_transition_with_coinciding_components(tsvd, q, rank):
+    """The residual's leading pair has its largest entries where the component before it was taken, so the same component is
+    appended again: the Gram matrix of Eq. (3) is singular and the loop leaves its Cholesky factor for conjugate gradients, for this
+    and all later iterations.  Residual, errors and factors must still be the oracle's."""
+    rng = np.random.default_rng(8)          # (gaps of 1e-2 at least in every iteration)
+    M, N, half, theta = 60, 50, 24, 1.0
+    c, r = np.zeros(M), np.zeros(N)
+    c[1:half], r[1:half] = rng.uniform(0.8, 1.2, half - 1), rng.uniform(0.8, 1.2, half - 1)
+    c, r = c / np.linalg.norm(c), r / np.linalg.norm(r)
+    W = 0.5 * np.outer(c, r)
+    W[0] += r
+    W[:, 0] += c
+    W[0, 0] = 3.0            # then the pair of [[0, 1], [1, 0.5]] in the bases (e_0, c), (e_0, r) leads: (0.62, 0.79)
+    A = np.linalg.qr(rng.standard_normal((M - half, 6)))[0]
+    B = np.linalg.qr(rng.standard_normal((N - half, 6)))[0]
+    W[half:, half:] = (A * np.array([2.0, 1.1, 0.9, 0.7, 0.4, 0.2])) @ B.T
+    Uo, So, Vo, eo = tr.transition(W, theta, q=q, max_rank=rank - rank % q)
+    G = (Uo.T @ Uo).astype(float) * (Vo @ Vo.T)
+    first = next(k for k in range(1, Uo.shape[1] + 1) if np.linalg.matrix_rank(G[:k, :k]) < k)      # components up to the first repeated one
+    print(f"case coinciding components q={q}: repeated at {first} of {Uo.shape[1]}", flush=True)
+    assert first < Uo.shape[1]
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(W), theta, 0.0, rank, q=q)
+    assert status == 0 and U.shape == (M, rank)
+    U, S, V = U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy()
+    for k in range(Uo.shape[1]):
+        sign = 1 if np.array_equal(U[:, k], Uo[:, k]) else -1
+        assert np.array_equal(sign * U[:, k], Uo[:, k]) and np.array_equal(sign * V[k, :], Vo[k, :]), k
+    assert np.max(np.abs(np.array(errs)[q - 1:len(eo) * q:q] - np.array(eo))) <= 1e-9
+    best = W - tr.reconstruction(U, tr.fit_scales(U, V, W), V)
+    assert np.max(np.abs(W - tr.reconstruction(U, S, V) - best)) <= 1e-9
+
+
 def test_transition_wide_matrix_and_rank_limit(tsvd):
     """M < N, exit by the rank limit, status and shapes; the first components equal the oracle's."""
     W = np.random.default_rng(12).laplace(size=(48, 160))
