@@ -109,7 +109,7 @@ tsvd_status tsvd_dense_unpack_host(const void* blob, size_t blob_bytes, int8_t* 
  *   x_dev : device, [N][B] row-major with row stride ldx >= B elements of x_dtype.  Any stride and
  *           alignment is accepted; bf16 rows that start on 16-byte boundaries (ldx a multiple of 8, base
  *           16-byte aligned) are read in place, others are first copied to such rows inside the
- *           workspace when B > 16 (one extra pass over x).
+ *           workspace where the chosen kernels need it (one extra pass over x).
  *   y_dev : device, [M][B] row-major with row stride ldy >= B elements of y_dtype (TSVD_F32, or
  *           TSVD_BF16: the fp32 result rounded to nearest even).
  *   workspace : device scratch for the intermediate z, at least
@@ -122,18 +122,25 @@ tsvd_status tsvd_dense_unpack_host(const void* blob, size_t blob_bytes, int8_t* 
  * x, y and workspace are owned by the caller and must not alias.  Inputs must be finite.
  *
  * Arithmetic (accumulation is fp32 or exact everywhere; the oracle-relative bounds are those the tests check):
- *   B = 1 (and TSVD_F32 activations with 2 <= B <= 16, which are handled one token at a time, each pass streaming
- *     the weights again): x is converted to sign-magnitude fixed point with 30 bits below the largest |x| (entries below
+ *   B = 1, TSVD_F32 with 2 <= B <= 16, and TSVD_BF16 with 2 <= B <= 16 on factors whose packed bytes times B are at most 60e6
+ *     (several tokens per launch where the factors fit the single-token kernels, else two at a time, each reading the weights):
+ *     x is converted per token to sign-magnitude fixed point with 30 bits below the largest |x| (entries below
  *     2^-31 of it become 0), every sum of V(.) and U(.) is then an exact integer; z = S * (V x) is rounded to fp32
  *     and converted the same way relative to the bound max_k |S_k| nnz(V[k,:]) * max|x|.  Error: 1e-5 of max|y| at
  *     most (measured 1e-7 .. 8e-7).
- *   2 <= B (TSVD_BF16): x enters exactly, stage V accumulates exact products in fp32, z is multiplied by a
- *     per-token power of two that keeps it in range and rounded to fp16 (11 significant bits), stage U accumulates
- *     exact products in fp32.  Long contractions with many tiles, and calls with many tokens on a small
- *     factorisation (one launch for both stages), multiply fp4 codes by three fp6 (E2M3) planes of the
- *     activations with block scales, which resolve 2^-14.7 of the largest magnitude among 32 neighbours; where
- *     stage V makes the planes of z itself, z is never rounded to 16 bits.  Error: 2e-3 of max|y| at most
- *     (measured 2.0e-4 .. 2.4e-4 with fp16 z, 2e-5 .. 4e-5 without).
+ *   2 <= B (TSVD_BF16) otherwise: one of two, whichever the library estimates to be faster (the choice depends on sizes, layouts and
+ *     the GPU, never on values).
+ *     - 16-bit operands (what B <= 16 takes): x enters exactly, stage V accumulates exact products in fp32, z is multiplied by a
+ *       per-token power of two that keeps it in range and rounded to fp16 (11 significant bits), stage U accumulates
+ *       exact products in fp32.  Error: 2e-3 of max|y| at most (measured 2.0e-4 .. 2.4e-4).
+ *     - planes: fp4 codes times three fp6 (E2M3) planes with block scales, of x and z or of z alone.  They hold a value to 2^-14
+ *       of the largest magnitude among 32 neighbours of the contraction (bf16 values of at least 2^-7 of that magnitude exactly,
+ *       smaller ones to 2^-15 of it); z goes from fp32 sums into its planes where x is on planes too, else through fp16 as above.
+ *       Error: 2e-3 of max|y| at most (measured 2e-5 .. 5e-5; 2.0e-4 .. 2.4e-4 through fp16).  This is relative to
+ *       the whole of y.  A row of V whose non-zero entries avoid a feature far larger than its neighbours still carries
+ *       2^-15 of that feature per neighbour: rows of y made of such ranks alone are off by 3e-5 to 9e-5 of their own norm for features 20
+ *       to 60 times the rest, 1e-4 to 5e-4 at 200 times, 1e-3 to 5e-3 at 2000 times (16-bit operands: 2.1e-4 in all of them).
+ *       Callers whose rows need more pass x as TSVD_F32.
  *   17 <= B (TSVD_F32): fp4 codes times SIX fp6 planes of the activations of either stage (three, and three more for
  *     what those leave: below the last bit of an fp32 value of a block's largest magnitude), fp32 accumulation; z goes
  *     from the accumulators straight into its planes.  Error: 1e-5 of max|y| at most (measured 2e-7 .. 1.4e-6).
@@ -154,9 +161,8 @@ tsvd_status tsvd_forward(const tsvd_handle* h, const void* x_dev, tsvd_dtype x_d
  * bias=True) added to every token, fused into the last kernel of the call.
  *
  *   x_layout : TSVD_FEATURE_MAJOR: x_dev is [N][B], ldx >= B (as tsvd_forward);
- *              TSVD_TOKEN_MAJOR:   x_dev is [B][N], ldx >= N.  Batched bf16 calls that run on fp4 codes x fp6
- *              planes (many tokens on a small factorisation; long contractions with many tiles) read it in place;
- *              other calls first rewrite it feature-major into the workspace (one extra pass over x).
+ *              TSVD_TOKEN_MAJOR:   x_dev is [B][N], ldx >= N.  Calls on planes of x and on the single-token kernels
+ *              read it in place; other calls first rewrite it feature-major into the workspace (one extra pass over x).
  *   bias_dev : device fp32 [M], or NULL for none.
  *   y_dev    : [M][B] with row stride ldy >= B, TSVD_F32 or TSVD_BF16 (rounded to nearest even
  *              from the fp32 value after the bias).

@@ -95,7 +95,7 @@ tsvd_z_planes_kernel(const uint16_t* __restrict__ Z, long long ld, int rows_vali
 // each, two workgroups per compute unit, or 4 x 1 of 4 x 4 blocks (256 x 64), three, or of 2 x 4 blocks (128 x 64), four; two LDS buffers of one 128-index block each; code words straight from global memory to
 // registers, one block ahead.
 // NPL: planes multiplied, 3 or (switch TSVD_FP6_PLANES=2, never by default) the first two: two thirds of the MFMAs
-// for activations exact to 2^-9.8 instead of 2^-14.7 of a block's largest magnitude.
+// for activations exact to 2^-9 instead of 2^-14 of a block's largest magnitude.
 // The work of one workgroup: the tile of WM TM 16 rows from strip tile_strip0 on, tokens b0 .. b0 + 16 TN WN
 // (TN = 4 token blocks per wavefront everywhere but in the last, partly filled round of tsvd_gemm_fp6_tail_kernel).
 template <bool STAGE2, int EX, int WM, int WN, int TM, int NPL, bool DIRECT, int TN = 4>

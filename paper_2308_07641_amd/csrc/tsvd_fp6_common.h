@@ -73,8 +73,8 @@ __device__ __forceinline__ void tsvd_planes_of_32(float (&v)[32], unsigned char*
     });
     *reinterpret_cast<uint32_t*>(rec + 4608 + lane * 4) = scales;
 }
-// Six planes for fp32 values: a record of three, and a second record for what those leave (2^-14.7 of a block's largest
-// magnitude times 2^-14.7 again: below the last bit of an fp32 value of that magnitude).
+// Six planes for fp32 values: a record of three, and a second record for what those leave (2^-14 of a block's largest
+// magnitude times 2^-14 again: below the last bit of an fp32 value of that magnitude).
 __device__ __forceinline__ void tsvd_planes_of_32_twice(float (&v)[32], unsigned char* rec, unsigned char* rec2, int lane) {
     tsvd_planes_of_32<true>(v, rec, lane);
     tsvd_planes_of_32<false>(v, rec2, lane);

@@ -93,3 +93,65 @@ def test_thin_panels_gather_convolutions(tsvd, form, ci, co, k1, k2, geom, tiles
         want = torch.from_numpy(np.ascontiguousarray(ref.transpose(1, 0, 2, 3))).to(y.dtype)
         assert torch.equal(y.cpu(), want)
     tsvd.tsvd_free(h)
+
+
+PLANE_PATHS = [{"TSVD_THIN": 1}, {"TSVD_THIN": 2}, {"TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 10}, {"TSVD_SPLIT_V": 18, "TSVD_SPLIT_U": 20, "TSVD_SPLIT_X": 1}]
+
+
+def _on_planes(tsvd, h, x, switches):
+    for k, v in {"TSVD_MID": 0, "TSVD_PANEL": 0, **switches}.items():
+        tsvd.tsvd_tuning_set(k, v)
+    return tsvd.tsvd_forward_io(h, x, x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR).cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("switches", PLANE_PATHS, ids=str)
+def test_values_within_two_to_the_seven_of_their_neighbours_are_exact(tsvd, switches):
+    """What tsvd.h states for bf16 activations on planes: each value that is at least 2^-7 of the largest of its 32 neighbours enters
+    exactly.  V and U pick one entry per row, so y is x itself, permuted."""
+    import torch
+    rng = np.random.default_rng(7)
+    N, B = 333, 70
+    pick, place, sign = rng.permutation(N), rng.permutation(N), rng.choice([-1, 1], N)
+    V, U = np.zeros((N, N), np.int8), np.zeros((N, N), np.int8)
+    V[np.arange(N), pick] = sign
+    U[place, np.arange(N)] = 1
+    x = rng.choice([-1, 1], (B, N)) * np.ldexp(rng.integers(128, 256, (B, N)) / 128.0, rng.integers(-6, 1, (B, N)))      # 2^-6 .. 2 - 2^-7
+    h = tsvd.tsvd_pack(U, np.ones(N, np.float32), V)
+    print(f"case exact values {switches}", flush=True)
+    y = _on_planes(tsvd, h, torch.from_numpy(x).to("cuda:0").to(torch.bfloat16), switches)
+    want = np.empty_like(x)
+    want[:, place] = x[:, pick] * sign
+    assert np.array_equal(y, want)
+    tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("outlier", [200.0, 2000.0])
+@pytest.mark.parametrize("switches", PLANE_PATHS, ids=str)
+def test_rows_free_of_massive_outliers(tsvd, switches, outlier):
+    """Three features far above the rest, seen by a third of the ranks; rows of y that use none of those keep the precision that
+    tsvd.h states.  An x smaller than 2^-7 of the largest m of its neighbours is off by 2^-15 m at most, so y = U (S (V x)) by a sum of such
+    errors with the signs of V and U (bounded here by its root mean square over those, neighbours taken as 64); z of such ranks shares its
+    neighbours with others of them only: 2^-14 of a block's largest value, which is four times its rms at most, 2.5e-4 of y."""
+    import torch
+    rng = np.random.default_rng(int(outlier))
+    M, N, K, B, free_ranks, free_rows = 256, 640, 384, 70, 256, 128
+    U, V = (rng.choice([-1, 0, 1], size=s, p=[0.25, 0.5, 0.25]).astype(np.int8) for s in ((M, K), (K, N)))
+    S = np.abs(rng.standard_normal(K)).astype(np.float32)
+    massive = [3, 200, 333]
+    V[:free_ranks, massive] = 0
+    U[:free_rows, free_ranks:] = 0
+    x = rng.standard_normal((B, N))
+    x[:, massive] *= outlier
+    xd = torch.from_numpy(x).to("cuda:0").to(torch.bfloat16)
+    x = xd.double().cpu().numpy()
+    h = tsvd.tsvd_pack(U, S, V)
+    print(f"case massive outliers {outlier} {switches}", flush=True)
+    y = _on_planes(tsvd, h, xd, switches)
+    z = (x @ V.T.astype(np.float64)) * S
+    want = z @ U.T.astype(np.float64)
+    e2 = (2.0 ** -15 * np.repeat(np.abs(x).reshape(B, N // 64, 64).max(axis=2), 64, axis=1)) ** 2
+    bound = np.sqrt(((e2 @ (V != 0).T) * S ** 2) @ (U != 0).T)[:, :free_rows]
+    err = (y - want)[:, :free_rows]
+    assert np.linalg.norm(err) <= np.linalg.norm(bound) + 2.5e-4 * np.linalg.norm(want[:, :free_rows])
+    assert rel_err(y, want) <= 1e-4                                                # the whole of y
+    tsvd.tsvd_free(h)
