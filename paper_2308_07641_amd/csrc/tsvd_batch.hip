@@ -6,10 +6,11 @@
 // separates them: a launch with few workgroups is bound by its serial chain (steps of a workgroup's loop), one with many by
 // matrix instructions, a thin panel by the code words it streams.  So each gets an estimate in microseconds, a sum of
 // the quantities that bound it: the launch, rounds of workgroups over the compute units, loop steps, records of x made, code bytes.
-// The factors are fits (non-negative least squares on relative errors) to measurements on MI355X of 1200 bf16 calls, 160 fp32 calls and 600
-// convolutions of random shapes (17 to 16384 tokens, factors of 1 KB to 64 MB), 26 ways each; the estimates' standard error is 10 to 16 %.
-// Picking the smallest is within 4 % of the best way on the average of those calls and 1.22 times the speed of always
-// taking the older ones (convolutions 1.34, fp32 2 to 4).
+// The factors are fits (non-negative least squares on relative errors) to measurements on MI355X of calls of random shapes (17 to
+// 16384 tokens, factors of 1 KB to 64 MB).  Checked on 220 other calls (profiles/batch_choice.csv: each of the ways timed, and what
+// the rule took): the estimates' root mean square error is 10 to 15 % for bf16, 8 to 20 % for fp32 and 10 to 13 % for
+// convolutions; the time of the way taken is 4.9 % above the best way's on the average for bf16 (one call in ten more than 18 %), 2.6 % for fp32, 1.4 %
+// for convolutions, and 1.20, 1.84 and 1.23 times the speed of always taking the older ones.
 #include "tsvd_batch.h"
 
 #include <algorithm>

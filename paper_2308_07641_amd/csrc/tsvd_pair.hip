@@ -3,11 +3,11 @@
 // With A the Gram matrix on the shorter side (R^T R or R R^T, n = min(M, N)), A^(2^p) tends to the projector onto the
 // leading singular direction: p squarings are 2^p power steps.  On the close singular values of a random matrix (gaps of
 // 1e-2 .. 1e-4) that takes 10 .. 18 launches that fill the chip, where Lanczos bidiagonalisation takes 60 .. 100 steps
-// of four launches each, two of them a single workgroup: 76 steps at 44 us against 12 squarings at about 4 us on a
-// [512, 256] matrix.  Rounding: every squaring perturbs its matrix by a few units in the last place of its norm, so the
+// of four launches each, two of them a single workgroup: 2.5 ms against 0.16 ms for the pair of a [512, 256] Laplace
+// matrix (64 steps at 39 us; 11 squarings at 5.6 us in a kernel trace, and 0.1 ms of launches and waits).  Rounding: every squaring perturbs its matrix by a few units in the last place of its norm, so the
 // vector is off by rounding over the gap, as with any backward-stable method.
 //
-// The result is X x_j, with x_j the column of X that has the largest diagonal entry: that entry is at least trace / n, so
+// The result is X x_j, with x_j the column of X that has the largest diagonal entry (to nine bits): that entry is at least trace / n, so
 // its unit vector e_j has a cosine of at least 1 / sqrt(n) with the leading space whatever the matrix (a fixed vector, as the start
 // vector of the Lanczos process, may be orthogonal to it), and the product with X takes the rounding of x_j back to that
 // of X itself.  In a degenerate leading space that is one of its vectors.
@@ -26,8 +26,11 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Shorter side from which the squarings cost more than the Lanczos steps: a squaring is n^3 multiplications, a Lanczos
-// step two passes over R.
+// Shorter side up to which the squarings are taken.  A squaring is n^3 multiplications, a Lanczos step two passes over R; how many
+// of either are needed depends on the gap.  Measured, squarings against Lanczos: a pair well apart from the rest (6 squarings, 32 steps)
+// 0.68 / 1.49 ms at 1024, 2.9 / 2.6 at 2048, 5.1 / 3.0 at 2560, 8.6 / 3.5 at 3072; a Laplace matrix (13 - 15, 96 - 128) 1.0 / 7.1, 4.6 / 17.0,
+// 8.9 / 20.4, 17.0 / 30.0 ms.  So the line is where the better case of the Lanczos process begins to win; a Laplace
+// matrix would gain from squarings up to 3500 and more, at 2 n^2 doubles of scratch.
 constexpr int PAIR_MAX_N = 2048;
 
 // Workgroup (bi, bj), bi <= bj, of Y = c P P^T for P [rows][L]: T x T blocks of 16 x 16, the contraction split over four
