@@ -5,8 +5,8 @@
 
 A step is one pass of the whole hot path (all kernels of tsvd_forward) over one batch of the
 seeded synthetic workload; inputs are resident in HBM before the timed region.  The headline
-line is for the largest configuration of the benchmark spec that fits one GPU, the OPT-66B fc1 prefill
-shape (opt66b_fc1_prefill); the other workloads are reported in "per_config" of the same JSON line.
+line is for the largest configuration that fits one GPU, the OPT-66B fc1 prefill shape (opt66b_fc1_prefill:
+36864 x 9216 at rank 18432, 2048 tokens); the other workloads are reported in "per_config" of the same JSON line.
 The roofline of a batched workload prices the algorithmic flops of its dominant kernel (stage U:
 2 M K B) against the dense MFMA peak of the operand types that kernel multiplies (fp4 x fp6:
 10.1 PFLOP/s; bf16 / fp16: 2.5 PFLOP/s, given beside it); B = 1 prices algorithmic bytes
@@ -200,27 +200,26 @@ def bench_workload(name, steps, warmup, with_cpu=True, cpu_budget_s=4.0):
                            "frac": res["executed_tflops"] / PEAK_MFMA_TFLOPS,
                            "traffic": traffic,
                            "whole_path_frac": res["executed_tflops"] / PEAK_MFMA_TFLOPS}
-    elif batched and kernel_name == "tsvd_panel_fp6_kernel":
+    elif batched and kernel_name in ("tsvd_panel_fp6_kernel", "tsvd_thin_panel_kernel"):
         # one launch does both stages on fp4 codes x three fp6 planes (x and z as planes in LDS): the call IS the
         # dominant kernel.  Achieved = ALGORITHMIC flops 2 K (M + N) B per second against the 10.1 PFLOP/s fp4 / fp6
-        # peak; three times as many are executed; the fraction of the 2.5 PFLOP/s bf16 / fp16 peak is given beside it
-        # because that is what the benchmark spec prices the batched path against.
+        # peak; three times as many are executed; the fraction of the 2.5 PFLOP/s bf16 / fp16 peak is given beside it.
         res["two_launch_stage_ms"] = res.pop("stage_ms")
         ach = res["executed_tflops"]
-        res["roofline"] = {"bound": "mfma", "kernel": "tsvd_panel_fp6_kernel (both stages, fp4 x fp6 MFMA, 3 planes)",
+        res["roofline"] = {"bound": "mfma", "kernel": kernel_name + " (both stages, fp4 x fp6 MFMA, 3 planes)",
                            "achieved": ach, "peak": PEAK_MFMA_FP6_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_MFMA_FP6_TFLOPS,
                            "executed_tflops": 3.0 * ach, "executed_frac": 3.0 * ach / PEAK_MFMA_FP6_TFLOPS,
                            "frac_of_bf16_peak": ach / PEAK_MFMA_TFLOPS,
                            "traffic": traffic,
                            "whole_path_frac_of_bf16_peak": ach / PEAK_MFMA_TFLOPS}
-    elif batched and kernel_name == "tsvd_gemm_fp6_kernel":
+    elif batched and kernel_name in ("tsvd_gemm_fp6_kernel", "tsvd_fp6_split_kernel"):
         # stage U = fp4 x fp6 kernel (+ the planes pass where stage V leaves fp16 z).  Achieved = ALGORITHMIC flops (2 M K B) per second; the
         # kernel executes three times as many (three planes) on the fp4 / fp6 MFMA path, whose dense
         # peak is 10.1 PFLOP/s; the fraction of the 2.5 PFLOP/s fp16 peak is given beside it because that
         # is what every other batched kernel here is priced against.
         fl_u = 2.0 * w.K * w.M * w.B
         ach = fl_u / (u_ms * 1e-3) / 1e12
-        res["roofline"] = {"bound": "mfma", "kernel": "tsvd_gemm_fp6_kernel (stage U, fp4 x fp6 MFMA, 3 planes; where stage V does not write the planes of z "
+        res["roofline"] = {"bound": "mfma", "kernel": kernel_name + " (stage U, fp4 x fp6 MFMA, 3 planes; where stage V does not write the planes of z "
                                                      "itself, timed together with the operand pass tsvd_z_planes_kernel, about 2 % of it)",
                            "achieved": ach, "peak": PEAK_MFMA_FP6_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_MFMA_FP6_TFLOPS,
                            "algorithmic_flops": fl_u, "launch_ms": u_ms,
@@ -456,10 +455,9 @@ def main():
         names.insert(0, PRIMARY)
     per = {}
     for n in names:
-        steps = args.steps if workloads.WORKLOADS[n].B * workloads.WORKLOADS[n].K < 1 << 24 else max(5, args.steps // 10)
-        per[n] = bench_workload(n, steps, args.warmup, with_cpu=not args.no_cpu,
+        per[n] = bench_workload(n, args.steps, args.warmup, with_cpu=not args.no_cpu,
                                 cpu_budget_s=12.0 if n == PRIMARY else 3.0)
-        per[n]["steps"] = steps
+        per[n]["steps"] = args.steps
         print(f"[bench] {n}: {json.dumps(per[n])}", file=sys.stderr, flush=True)
 
     if not args.no_transition and not args.no_cpu:
