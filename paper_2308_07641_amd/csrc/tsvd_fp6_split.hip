@@ -9,8 +9,10 @@
 // still multiplies 128 rows (eight row blocks) by every operand it reads from LDS.  At the end the partial sums of the
 // groups meet in LDS, each group finishing its share of the tile.
 // Measured on MI355X: 3072 x 768 x 1536 fp32 at 197 tokens 56.4 -> 20.1 us (128 x 16 tiles with planes of x made inside, then 128 x 32),
-// 16384 x 4096 x 8192 bf16 at 256 tokens 93.4 -> 71.4 us (256 x 32 and 256 x 64).  What bounds them: the matrix
-// instructions at 19 - 21 cycles each once a compute unit has a few steps to walk, the launch and the first code words below that.
+// 16384 x 4096 x 8192 bf16 at 256 tokens 93.4 -> 71.4 us (256 x 32 and 256 x 64).  What bounds them, by counters: stage U of the
+// second (a workgroup per compute unit, 3072 MFMAs per SIMD in 53 us) has the matrix pipes busy half of the cycles at 0.38 of
+// a wavefront's time waiting; its stage V (23 us) 0.28, the stages of the first (11 us each) 0.07 and 0.20: there the launch, the first code
+// words and the sum of the groups weigh more than the products.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
