@@ -83,7 +83,7 @@ def test_fit_scales_minimum_norm_for_duplicated_components(tsvd):
 @pytest.mark.parametrize("M,N", [(40, 30), (512, 256), (100, 700)])
 def test_leading_singular_pair(tsvd, M, N):
     """Against the library SVD on a matrix with a clear leading component and on a plain Laplace
-    matrix, whose leading singular values are close (the Lanczos process must still separate them)."""
+    matrix, whose leading singular values are close (the squarings must still separate them)."""
     rng = np.random.default_rng(M + N)
     u0 = rng.standard_normal(M); u0 /= np.linalg.norm(u0)
     v0 = rng.standard_normal(N); v0 /= np.linalg.norm(v0)
