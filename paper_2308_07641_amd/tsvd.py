@@ -363,7 +363,7 @@ def tsvd_residual(W, U, S, V, stream=None):
 
 
 def tsvd_leading_singular_pair(R, max_iters: int = 512, stream=None):
-    """(u [M], sigma [1], v [N], steps [1]) of R float64 [M, N] by Lanczos bidiagonalisation."""
+    """(u [M], sigma [1], v [N], steps [1]) of R float64 [M, N] by squarings of its Gram matrix (Lanczos steps beyond min(M, N) = 2048)."""
     import torch
     M, N = R.shape
     _need(R, torch.float64, (M, N), "R")

@@ -150,6 +150,22 @@ def test_leading_singular_pair_whatever_its_angle_to_the_start_vector(tsvd, M, N
     assert abs(abs(v @ v0) - 1.0) <= 1e-12
 
 
+@pytest.mark.parametrize("M,N", [(2060, 2048), (2048, 2060), (2049, 2060)])
+def test_leading_singular_pair_where_the_method_changes(tsvd, M, N):
+    """The largest size of the squarings, both orientations, and the first of the Lanczos steps; the leading vectors are
+    the last unit vectors, so the column that the squarings pick is the last one."""
+    rng = np.random.default_rng(M)
+    n = min(M, N)
+    A, B = (np.linalg.qr(np.column_stack([np.eye(L)[:, -1], rng.standard_normal((L, n - 1))]))[0] for L in (M, N))
+    R = (A * np.concatenate([[1.0], np.linspace(0.97, 0.0, n - 1)])) @ B.T
+    print(f"case pair at the change M={M} N={N}", flush=True)
+    u, sigma, v, steps = tsvd.tsvd_leading_singular_pair(_dev(R))
+    u, sigma, v = u.cpu().numpy(), float(sigma.cpu()[0]), v.cpu().numpy()
+    assert (int(steps.cpu()[0]) > 16) == (n > 2048)
+    assert abs(sigma - 1.0) <= 1e-12 and abs(abs(u[-1]) - 1.0) <= 1e-12 and abs(abs(v[-1]) - 1.0) <= 1e-12
+    assert np.linalg.norm(R @ v - sigma * u) <= 1e-12 and np.linalg.norm(R.T @ u - sigma * v) <= 1e-12
+
+
 @pytest.mark.parametrize("M,N", [(128, 64), (64, 128), (500, 420)])
 @pytest.mark.parametrize("power", [330, -330, 490, -490])
 def test_leading_singular_pair_of_very_large_and_small_entries(tsvd, M, N, power):
