@@ -85,7 +85,7 @@ def _stage_u_kernel_name(tsvd, handle, B):
     except ValueError:
         return "batched stage-U kernel", -1
     if su < 0:
-        return "batched stage-U kernel", su
+        return "tsvd_few_u_kernel", su
     if su == 32:
         return "tsvd_panel_kernel", su
     if su == 33:
@@ -188,7 +188,7 @@ def bench_workload(name, steps, warmup, with_cpu=True, cpu_budget_s=4.0):
                               "frac_of_bf16_peak": flops_exec / (lb_ms * 1e-3) / 1e12 / PEAK_MFMA_TFLOPS}
         del yb
     kernel_name, shape_u = _stage_u_kernel_name(tsvd, handles[0], w.B) if batched else (None, -1)
-    kernel_key = f"{kernel_name}:{shape_u}" if batched else ("tsvd_mid_kernel" if w.B > 1 else "tsvd_gemv_kernel")
+    kernel_key = f"{kernel_name}:{shape_u}" if batched else ("tsvd_few_u_kernel" if w.B > 1 else "tsvd_gemv_kernel")
     traffic = _traffic_from_profile(name, kernel_key)
     res["dominant_kernel_key"] = kernel_key
     if batched and kernel_name == "tsvd_panel_kernel":
@@ -244,7 +244,7 @@ def bench_workload(name, steps, warmup, with_cpu=True, cpu_budget_s=4.0):
         _, warm_ev = _timed(step_one, steps, warmup)
         res["cache_warm_event_ms"] = warm_ev
         gbs = bytes_u / (u_ms * 1e-3) / 1e9
-        res["roofline"] = {"bound": "hbm", "kernel": "tsvd_mid_kernel (stage U)" if few else "tsvd_gemv_kernel (stage U)",
+        res["roofline"] = {"bound": "hbm", "kernel": "tsvd_few_u_kernel (stage U)" if few else "tsvd_gemv_kernel (stage U)",
                            "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS,
                            "traffic": traffic, "algorithmic_bytes": bytes_u,
                            "whole_path_gbs": bytes_alg / (ev_ms * 1e-3) / 1e9,

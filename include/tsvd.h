@@ -108,7 +108,7 @@ tsvd_status tsvd_dense_unpack_host(const void* blob, size_t blob_bytes, int8_t* 
  *
  *   x_dev : device, [N][B] row-major with row stride ldx >= B elements of x_dtype.  Any stride and
  *           alignment is accepted; bf16 rows that start on 16-byte boundaries (ldx a multiple of 8, base
- *           16-byte aligned) are read in place, others are first copied to such rows inside the
+ *           16-byte aligned) are read in place, others too by the kernels for few tokens; else they are first copied to such rows inside the
  *           workspace where the chosen kernels need it (one extra pass over x).
  *   y_dev : device, [M][B] row-major with row stride ldy >= B elements of y_dtype (TSVD_F32, or
  *           TSVD_BF16: the fp32 result rounded to nearest even).
@@ -127,12 +127,16 @@ tsvd_status tsvd_dense_unpack_host(const void* blob, size_t blob_bytes, int8_t* 
  *     x is converted per token to sign-magnitude fixed point with 30 bits below the largest |x| (entries below
  *     2^-31 of it become 0), every sum of V(.) and U(.) is then an exact integer; z = S * (V x) is rounded to fp32
  *     and converted the same way relative to the bound max_k |S_k| nnz(V[k,:]) * max|x|.  Error: 1e-5 of max|y| at
- *     most (measured 1e-7 .. 8e-7).
- *   2 <= B (TSVD_BF16) otherwise: one of two, whichever the library estimates to be faster (the choice depends on sizes, layouts and
+ *     most (measured 1e-7 .. 8e-7).  TSVD_BF16 on factors of up to 512 ranks and 1 MB of packed bytes: x as it is (exact products
+ *     summed in fp32), and z from those sums into FIVE fp6 (E2M3) planes with block scales, which hold a value to 2^-24 of the largest
+ *     magnitude among 32 neighbours; the same error, and as there the result of a token does not depend on the others.
+ *   2 <= B (TSVD_BF16) otherwise: one of three, whichever the library estimates to be faster (the choice depends on sizes, layouts and
  *     the GPU, never on values).
- *     - 16-bit operands (what B <= 16 takes): x enters exactly, stage V accumulates exact products in fp32, z is multiplied by a
+ *     - 16-bit operands: x enters exactly, stage V accumulates exact products in fp32, z is multiplied by a
  *       per-token power of two that keeps it in range and rounded to fp16 (11 significant bits), stage U accumulates
  *       exact products in fp32.  Error: 2e-3 of max|y| at most (measured 2.0e-4 .. 2.4e-4).
+ *     - x as it is, z in THREE planes (what B <= 16 takes): z goes from fp32 sums into planes that hold it to 2^-14 of the largest magnitude among
+ *       32 neighbours.  Error: 2e-3 of max|y| at most (measured 2e-5 .. 3e-5).
  *     - planes: fp4 codes times three fp6 (E2M3) planes with block scales, of x and z or of z alone.  They hold a value to 2^-14
  *       of the largest magnitude among 32 neighbours of the contraction (bf16 values of at least 2^-7 of that magnitude exactly,
  *       smaller ones to 2^-15 of it); z goes from fp32 sums into its planes where x is on planes too, else through fp16 as above.

@@ -12,6 +12,7 @@
 #include "../../include/tsvd.h"
 #include "../../include/tsvd_tuning.h"
 #include "tsvd_batch.h"
+#include "tsvd_few.h"
 #include "tsvd_kernels.h"
 #include "tsvd_layout.h"
 #include "tsvd_thin.h"
@@ -105,6 +106,8 @@ hipError_t device_init(int device) {
     e = tsvd_gemv_init();
     if (e != hipSuccess) return e;
     e = tsvd_mid_init();
+    if (e != hipSuccess) return e;
+    e = tsvd_few_init();
     if (e != hipSuccess) return e;
     e = tsvd_gemv_dense_init();
     if (e != hipSuccess) return e;
@@ -275,13 +278,28 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
 
 // x_token_major: only for calls that gemv_serves
 bool gemv_serves(const tsvd_handle* h) { return tsvd_gemv_fits(h->hd.Np, h->hd.Kp) && env_int("TSVD_GEMV", 1) != 0; }
-// 2 - 16 bf16 tokens on the single-token kernels side by side instead of the few-token kernels: those take 13 - 20 us at any size (two
-// launches that pass the activations through LDS in slabs, and a copy of token-major x), these 6 - 12 us and 0.08 us more per MB
-// of code words and token.  Measured on 316 random calls: they meet at 60 MB x tokens; rows of x at odd element offsets, which the few-token kernels
-// gather one by one (75 - 105 us), are copied to aligned rows before.
-bool side_by_side(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
-    return x_dtype == TSVD_BF16 && B >= 2 && B <= 16 && !tsvd_tuning_any() && !h->dense_u && gemv_serves(h) &&
-           (double)B * (double)h->hd.Kp * (double)(h->hd.Mp + h->hd.Np) / 4.0 <= 60.0e6;
+double code_bytes(const tsvd_handle* h) { return (double)h->hd.Kp * (double)(h->hd.Mp + h->hd.Np) / 4.0; }
+// 2 - 16 bf16 tokens whose z is kept as in fp32 (side by side on the single-token kernels, or on five planes of the few-token kernels): up to
+// 60 MB of code words times tokens.  Beyond, side by side takes longer than z in three planes (0.15 us for every MB and token).
+bool z_as_fp32(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
+    return x_dtype == TSVD_BF16 && B >= 2 && B <= 16 && !tsvd_tuning_any() && !h->dense_u && gemv_serves(h) && (double)B * code_bytes(h) <= 60.0e6;
+}
+// Small factors on five planes, 1 to 16 tokens alike (a token's result does not depend on how many stand beside it): up to 512 ranks and 1 MB of code
+// words, and not where one workgroup does a token fastest.  Measured against side by side on 30 such factors: 1 token 0.98 of the
+// time on the average (0.90 .. 1.06), 2 to 8 tokens 0.87, 16 tokens 0.80; at 640 to 2500 ranks one token would take 1.04 .. 1.2 times as long.  The error
+// against 64 bits is 4e-8 to 1.3e-7 of the norm of y, side by side 1e-7 to 4e-6.
+bool five_planes(const tsvd_handle* h) {
+    const tsvd_blob_header& hd = h->hd;
+    return !h->dense_u && hd.Kp <= 512 && code_bytes(h) <= 1.0e6 && (!tsvd_gemv_fused_fits(hd.Mp, hd.Kp, hd.Np) || hd.Mp > 768);
+}
+// The planes of z of a call of up to 16 tokens on the few-token kernels (0: on others).
+int few_planes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, int64_t ldx, bool x_token_major) {
+    const tsvd_blob_header& hd = h->hd;
+    // (Kp: the records have to fit the fixed workspace of tsvd_forward_noalloc, as z in 16 bits does)
+    if (x_dtype != TSVD_BF16 || B > 16 || hd.Kp > (1 << 18) || !tsvd_few_fits(hd, B, ldx, x_token_major)) return 0;
+    if (tsvd_tuning_any()) return B <= env_int("TSVD_FEW", 0) ? (env_int("TSVD_FEW_PLANES", 3) == 5 ? 5 : 3) : 0;
+    if (five_planes(h)) return 5;
+    return B == 1 || z_as_fp32(h, B, x_dtype) ? 0 : 3;
 }
 tsvd_status forward_skinny(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t B, int64_t ldx, bool x_token_major,
                            void* y, int64_t ldy, const out_opts& oo, void* ws, hipStream_t stream) {
@@ -350,29 +368,14 @@ tsvd_status forward_skinny(const tsvd_handle* h, const void* x, tsvd_dtype x_dty
     return TSVD_OK;
 }
 
-// ---- few-token path: groups of up to 16 tokens of bf16 activations, two launches per group ------
-// Up to 16 tokens always; up to 64 tokens (2..4 groups, each streaming the weights again, mostly
-// from the last-level cache) when the packed weights are large: there the batched kernels, with
-// few and narrow token tiles, spend their time re-reading z through L2 (measured on MI355X,
-// 16384 x 4096 x 8192: 38 us against 111 us at B = 32; 3072 x 768 x 1536: 24 us against 15 us).
+// ---- slab path for few tokens: groups of up to 16 tokens of bf16 activations, two launches per group ------
+// What the few-token kernels (few_planes) do not take: rows of fewer than eight values, and more than 2^18 ranks.
 bool use_mid(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, int64_t ldx) {
     if (x_dtype != TSVD_BF16 || B < 2 || B > 64 || env_int("TSVD_MID", 1) == 0) return false;
     // (32-bit byte offsets into x in the kernel, which also addresses up to four slabs of 2048 rows
     // beyond the last one: the range check returns zeros there)
     if (((uint64_t)h->hd.Np + 8192) * (uint64_t)ldx * 2 >= (1ull << 31)) return false;
-    if (B <= 16) return true;
-    const int forced = env_int("TSVD_MID_MAX_B", 0);       // tuning switch: largest B served here
-    if (forced > 0) return B <= forced;
-    // Measured break-even against the batched kernels, which launch only the 64-token tiles that hold tokens.
-    // Aligned rows: two groups of 16 pay off between about 4 and 60 MB of packed weights (10.5 MB: 21.5 against
-    // 27 us; 42 MB: 39 against 49 us; 94 MB: 95 against 82 us; 255 MB: 194 against 142 us), three and four
-    // groups never (24 MB at 48 tokens: 65 against 38 us; 42 MB: 61 against 50 us; 255 MB: 299 against 140 us).
-    // Unaligned rows take a slower batched kernel: 2, 3, 4 groups pay off from about 1.7, 4.5 and 8 MB.
-    const double code_bytes = (double)h->hd.Kp * (double)(h->hd.Mp + h->hd.Np) / 4.0;
-    const int groups = (int)((B + 15) / 16);
-    if (ldx % 8 == 0) return groups == 2 && code_bytes >= 4.2e6 && code_bytes < 60.0e6;
-    static const double min_bytes[5] = {0.0, 0.0, 4.2e6, 11.2e6, 20.0e6};
-    return code_bytes >= min_bytes[groups] * 0.4;
+    return B <= std::max(16, env_int("TSVD_MID_MAX_B", 16));       // (tuning switch: largest B served here, in groups of 16)
 }
 
 size_t mid_workspace(const tsvd_handle* h) {
@@ -461,12 +464,15 @@ thread_local bool planes_only_by_older_rules = false;
 
 // How a batched call runs that the few-token kernels leave.  copies: x would have to be copied for the kernels that read aligned
 // feature-major rows.
-tsvd_batch_plan batch_plan(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, bool x_token_major, bool copies, bool y_token_major, bool out_bf16) {
+tsvd_batch_plan batch_plan(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, bool x_token_major, bool copies, bool y_token_major, bool out_bf16,
+                           bool x_aligned, bool few) {
     tsvd_batch_call c = {};
     c.M = h->hd.M; c.K = h->hd.K; c.N = h->hd.N; c.B = B; c.cus = h->cu_count;
     c.f32 = x_dtype == TSVD_F32;
     c.x_token_major = x_token_major; c.y_token_major = y_token_major; c.out_bf16 = out_bf16; c.copies = copies;
     c.whole = tsvd_stage_mask() == 7;
+    c.x_aligned = x_aligned;
+    c.few = few && !c.f32 && !planes_only_by_older_rules;
     tsvd_batch_plan plan = tsvd_plan_batch(c);
     if (planes_only_by_older_rules && !c.f32) plan.split = false;
     return plan;
@@ -481,8 +487,11 @@ size_t gemm_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     if (tsvd_gemm_use_fp6(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count, true))      // planes of Z, and of X for stage V
         bytes += round256(tsvd_gemm_fp6_bytes(h->hd.Kp, Bp)) + round256(tsvd_gemm_fp6_bytes(h->hd.Np, Bp));
     // (asked as for the call that favours planes most)
-    if (use_gemm(h, B, x_dtype) && batch_plan(h, B, x_dtype, false, true, false, false).split)
-        bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
+    if (use_gemm(h, B, x_dtype)) {
+        if (batch_plan(h, B, x_dtype, false, true, false, false, true, false).split) bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
+        // (likewise: token-major y costs the panels more)
+        if (batch_plan(h, B, x_dtype, true, true, true, true, true, true).few) bytes = std::max(bytes, tsvd_few_bytes(h->hd.Kp, B, 3));
+    }
     return bytes;
 }
 
@@ -619,7 +628,8 @@ extern "C" tsvd_status tsvd_info(const tsvd_handle* h, int64_t* M, int64_t* K, i
 namespace {
 size_t base_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     // (the few-token path is chosen per call, by the row stride too: cover every candidate)
-    const size_t few = round256(std::max(skinny_workspace(h, B), mid_workspace(h)));
+    size_t few = round256(std::max(skinny_workspace(h, B), mid_workspace(h)));
+    if (x_dtype == TSVD_BF16 && B <= 16 && h->hd.Kp <= (1 << 18)) few = std::max(few, tsvd_few_bytes(h->hd.Kp, B, five_planes(h) || tsvd_tuning_any() ? 5 : 3));
     if (use_gemm(h, B, x_dtype)) return std::max(gemm_workspace(h, B, x_dtype), B <= 64 ? few : (size_t)0);
     return few;
 }
@@ -707,10 +717,19 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
     // fewer where rows start at odd elements; TSVD_REALIGN=0 keeps the gathers
     const bool realign = x_layout == TSVD_FEATURE_MAJOR && x_dtype == TSVD_BF16 && B > 1 && env_int("TSVD_REALIGN", 1) != 0 && h->hd.N <= 65535 &&
                          (batched ? misaligned : realigns_few(h, B, x_dtype) && (ldx % 2 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 3u)));
-    const bool few = !side_by_side(h, B, x_dtype) && use_mid(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR || realign ? tsvd_round_up(B, 8) : ldx);
+    const int z_planes = few_planes(h, B, x_dtype, ldx, x_layout == TSVD_TOKEN_MAJOR);
+    const bool few = !z_planes && !z_as_fp32(h, B, x_dtype) && use_mid(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR || realign ? tsvd_round_up(B, 8) : ldx);
     tsvd_batch_plan plan = {};
     if (batched && !few)
-        plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16);
+        plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16, !misaligned,
+                          tsvd_few_fits(h->hd, B, ldx, x_layout == TSVD_TOKEN_MAJOR) && tsvd_few_bytes(h->hd.Kp, B, 3) <= need);
+    if (z_planes || plan.few) {
+        // few tokens: x in any layout and alignment, planes of z in the workspace
+        const tsvd_few_problem f = {h->blob, &h->hd, static_cast<const uint16_t*>(x_dev), B, B == 1 && ldx == 1 ? h->hd.N : ldx, x_layout == TSVD_TOKEN_MAJOR || (B == 1 && ldx == 1), y_dev, ldy,
+                                    oo.token_major, oo.out_bf16, bias_dev, static_cast<unsigned char*>(ws), z_planes ? z_planes : 3, h->cu_count,
+                                    tsvd_stage_mask()};
+        return tsvd_few_launch(f, s) == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
+    }
     if (plan.thin) {
         // thin token panels: one launch, x in any layout and alignment, no workspace
         tsvd_thin_problem t = {};
@@ -819,7 +838,7 @@ extern "C" tsvd_status tsvd_forward_noalloc(const tsvd_handle* h, const void* x_
 namespace {
 const char* const tuning_names[] = {
     "TSVD_GEMV", "TSVD_GEMV_FUSED", "TSVD_GEMV_ONEPASS", "TSVD_GEMV_SW", "TSVD_GEMV_KWLOG2", "TSVD_SKINNY_SW", "TSVD_SKINNY_KW",
-    "TSVD_MID", "TSVD_MID_MAX_B", "TSVD_MID_SW", "TSVD_MID_KWLOG2", "TSVD_MID_RESIDENT", "TSVD_GEMM_MIN_B", "TSVD_GEMM_MIN_B_F32",
+    "TSVD_FEW", "TSVD_FEW_PLANES", "TSVD_FEW_KWLOG2", "TSVD_FEW_SW_V", "TSVD_FEW_SW_U", "TSVD_FEW_RW_U", "TSVD_MID", "TSVD_MID_MAX_B", "TSVD_MID_SW", "TSVD_MID_KWLOG2", "TSVD_MID_RESIDENT", "TSVD_GEMM_MIN_B", "TSVD_GEMM_MIN_B_F32",
     "TSVD_GEMM_CFG_V", "TSVD_GEMM_CFG_U", "TSVD_FUSEMAX", "TSVD_COLMAX_SCALAR", "TSVD_REALIGN", "TSVD_PANEL",
     "TSVD_PANEL_WAVES", "TSVD_PANEL_FP6", "TSVD_FP6", "TSVD_FP6_V", "TSVD_FP6_TALL", "TSVD_FP6_PLANES", "TSVD_FP6_DIRECT", "TSVD_FP6_TAIL", "TSVD_SPLIT_V", "TSVD_SPLIT_U", "TSVD_SPLIT_X", "TSVD_THIN", "TSVD_TOKEN_MAJOR_COPY", "TSVD_GROUPED_PAIR", "TSVD_DEPTHWISE", "TSVD_CLOCKS",
     "TSVD_SPIN_LIMIT", "TSVD_DENSE_U", "TSVD_EARLY_TILES"};
@@ -872,7 +891,8 @@ extern "C" int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* s
     *shape_v = *shape_u = -1;
     if (B <= 16 || use_mid(h, B, TSVD_BF16, tsvd_round_up(B, 8))) return 0;
     if (use_gemm(h, B, TSVD_BF16)) {
-        const tsvd_batch_plan plan = batch_plan(h, B, TSVD_BF16, false, false, false, false);
+        const tsvd_batch_plan plan = batch_plan(h, B, TSVD_BF16, false, false, false, false, true, true);
+        if (plan.few) return 0;
         if (plan.thin) {
             *shape_v = *shape_u = 34;
         } else if (plan.split) {

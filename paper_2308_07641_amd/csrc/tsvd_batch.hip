@@ -1,7 +1,7 @@
 // The choice among the batched kernels, by estimates of their times.
 //
-// Four ways serve a batch: thin token panels (both stages in one launch, 16 or 32 tokens per workgroup), planes of x with tiles of
-// tsvd_fp6_split.hip per stage (128 x 16 to 256 x 64, the contraction split over groups of wavefronts), the same with the tiles of
+// Five ways serve a batch: the few-token kernels (tsvd_few.hip, groups of 16 tokens side by side), thin token panels (both stages in one
+// launch, 16 or 32 tokens per workgroup), planes of x with tiles of tsvd_fp6_split.hip per stage (128 x 16 to 256 x 64, the contraction split over groups of wavefronts), the same with the tiles of
 // tsvd_fp6.hip (many rows and tokens), and the ring and large-tile kernels of tsvd_gemm.hip on 16-bit operands.  No single quantity
 // separates them: a launch with few workgroups is bound by its serial chain (steps of a workgroup's loop), one with many by
 // matrix instructions, a thin panel by the code words it streams.  So each gets an estimate in microseconds, a sum of
@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <initializer_list>
 
+#include "tsvd_few.h"
 #include "tsvd_gemm_common.h"
 #include "tsvd_kernels.h"
 #include "tsvd_thin.h"
@@ -123,11 +124,12 @@ size_t tsvd_gemm_split_bytes(long long K, long long N, long long B, bool f32) {
 }
 
 tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
-    tsvd_batch_plan plan = {0, c.f32, 0, 0};
+    tsvd_batch_plan plan = {false, 0, c.f32, 0, 0};
     if (tsvd_tuning_any()) {        // a diagnostic that sets switches means the kernels that they select
         const int thin = tsvd_tune("TSVD_THIN", 0), v = tsvd_tune("TSVD_SPLIT_V", 0), u = tsvd_tune("TSVD_SPLIT_U", 0);
         if (thin > 0 && !c.f32 && c.whole) plan.thin = thin;
-        if (v > 0 || u > 0) plan = {plan.thin, true, v, u};
+        plan.few = c.few && c.B <= tsvd_tune("TSVD_FEW", 0);
+        if (v > 0 || u > 0) plan = {false, plan.thin, true, v, u};
         return plan;
     }
     const long long Mp = tsvd_round_up(c.M, 256), Kp = tsvd_round_up(c.K, 256), Np = tsvd_round_up(c.N, 256);
@@ -155,7 +157,7 @@ tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
     const bool fits = !panel && tsvd_gemm_split_bytes(c.K, c.N, c.B, false) < (1ull << 31);
     if (fits && (v || u) && best_v + best_u + columns < best) {
         best = best_v + best_u + columns;
-        plan = {0, true, v, u};
+        plan = {false, 0, true, v, u};
     }
     // (every panel streams both factors: measured for code words that one XCD's L2 holds)
     if (c.whole && c.K * (c.M + c.N) <= (16ll << 20))
@@ -164,5 +166,12 @@ tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
                 const double t = thin_cost(c, tiles);
                 if (t < best) best = t, plan.thin = tiles;
             }
+    // Few tokens: each group of 16 reads both factors again, measured up to 600 tokens.  A twentieth and 0.7 us less than the best of the others (what
+    // either estimate is off by where a call is hardly more than its launches).  On 200 calls of 17 to 512 tokens 0.68 of the time without
+    // them on the average, 0.3 to 0.5 for thousands of rows at 17 to 64 tokens; the worst 1.1.
+    if (c.few && c.whole && c.B <= 1024) {
+        const double t = tsvd_few_cost({c.M, c.N, c.K, c.B, c.cus, c.x_token_major, c.x_aligned, c.out_bf16});
+        plan.few = t < 0.95 * best && t < best - 0.7;
+    }
     return plan;
 }

@@ -1,0 +1,78 @@
+"""The few-token kernels on planes of z (tsvd_few.hip): exact on integer instances and within the bounds of include/tsvd.h on random ones, over
+launch shapes, layouts, alignments and the ends of rows and of the array."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_util import rel_err, to_device
+from test_gpu_planes import _check, tsvd  # noqa: F401  (the module's fixture)
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [{}, {"TSVD_FEW_SW_V": 4, "TSVD_FEW_SW_U": 1, "TSVD_FEW_RW_U": 1}, {"TSVD_FEW_SW_U": 4, "TSVD_FEW_RW_U": 4}, {"TSVD_FEW_KWLOG2": 1}]
+
+
+CALLS = [
+    (70, 60, 40, 2),                # one column of tiles for either stage
+    (300, 9, 40, 2),                # hardly more than one chunk of a row
+    (300, 513, 270, 8), (515, 300, 777, 9),                 # eight tokens and one more
+    (256, 255, 300, 9), (256, 257, 300, 5), (256, 263, 300, 18), (100, 511, 700, 31),      # ends of rows beside a chunk and a tile
+    (40, 4500, 2100, 7), (2100, 9000, 520, 20),             # several columns for a wavefront
+    (130, 64, 60, 33), (300, 1030, 1024, 47), (640, 200, 300, 96)]      # groups of tokens, the last one of one token and full
+
+
+@pytest.mark.parametrize("planes,M,N,K,B", [(3, *c) for c in CALLS] + [(5, *c) for c in CALLS if c[3] <= 16])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_few_tokens_on_planes(tsvd, planes, M, N, K, B, shape):  # noqa: F811
+    """(1e-6 for five planes: fp32 sums of a few hundred to a few thousand terms over 2^-24 of z.)"""
+    print(f"case few on planes {M} {N} {K} {B} {shape} {planes}", flush=True)
+    _check(tsvd, M, N, K, B, "bf16", {"TSVD_FEW": 128, "TSVD_FEW_PLANES": planes, **shape}, 1e-4 if planes == 3 else 1e-6)
+
+
+@pytest.mark.parametrize("B,ld,col0", [(3, 10, 0), (5, 10, 2), (4, 9, 1), (9, 24, 8), (16, 40, 5), (19, 33, 7)])
+def test_neighbours_that_are_not_finite(tsvd, B, ld, col0):  # noqa: F811
+    """Columns of a wider matrix, NaN beside them; and rows of tokens that begin at odd elements, NaN between."""
+    import torch
+    i = workloads.make_integer_inputs(90, 700, 300, B, 0.5, "bf16", seed=77 + B + ld)
+    ref = oracle.forward(i.U, i.S, i.V, i.X)
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    tsvd.tsvd_tuning_set("TSVD_FEW", 64)
+    print(f"case few neighbours {B} {ld} {col0}", flush=True)
+    wide = torch.full((700, ld), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    wide[:, col0:col0 + B] = to_device(i)
+    assert np.array_equal(tsvd.tsvd_forward(h, wide[:, col0:col0 + B]).cpu().numpy(), ref)
+    rows = torch.full((B, 700 + ld), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    rows[:, col0:col0 + 700] = to_device(i).t()
+    y = tsvd.tsvd_forward_io(h, rows[:, col0:col0 + 700], x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR)
+    assert np.array_equal(y.cpu().numpy().T, ref)
+    tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("M,N,K,B", [(1100, 700, 500, 1), (1100, 700, 500, 6), (4096, 4096, 5900, 7), (2500, 640, 1300, 40), (500, 2400, 130, 300)])
+def test_calls_that_take_them_by_default(tsvd, M, N, K, B):  # noqa: F811
+    """Five planes on small factors (error of fp32 sums), three beyond; the same bits for either layout of x and y, and replayed from a
+    captured graph."""
+    import torch
+    i = workloads.make_inputs(M, N, K, B, 0.6, 0.02, "bf16", seed=M + B)
+    ref = oracle.forward(i.U, i.S, i.V, i.X)
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    x = to_device(i)
+    print(f"case few by default {M} {N} {K} {B}", flush=True)
+    y = tsvd.tsvd_forward(h, x)
+    assert rel_err(y.cpu().numpy().astype(np.float64), ref) <= (1e-6 if B <= 6 else 1e-4)
+    yt = tsvd.tsvd_forward_io(h, x.t().contiguous(), x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR)
+    assert torch.equal(yt.t(), y)
+    ws = torch.empty(tsvd.tsvd_workspace_bytes(h, B, tsvd.TSVD_BF16), dtype=torch.uint8, device="cuda:0")
+    out = torch.zeros_like(y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tsvd.tsvd_forward(h, x, out, workspace=ws)
+    for _ in range(3):
+        out.zero_()
+        ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, y)
+    tsvd.tsvd_free(h)
