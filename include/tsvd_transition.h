@@ -64,7 +64,8 @@ tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M, int64_t N
                                        double* v_dev, double* sigma_dev, int32_t* steps_dev, void* workspace,
                                        size_t workspace_bytes, void* stream);
 
-/* Algorithm 2 with q = 1, chaining the calls above: until |W - U diag(S) V|_F / |W|_F <= tol or
+/* Algorithm 2 with q = 1, chaining the calls above (up to min(M, N) = 768 the squarings end where a few directions are left, and a
+ * factorisation of what is left gives the pair to the same precision): until |W - U diag(S) V|_F / |W|_F <= tol or
  * the rank reaches max_rank.  SYNCHRONISES with the stream once per iteration (the exit test
  * reads one number back; up to min(M, N) = 2048 the following iteration is enqueued by then and dropped where the loop ends).
  *   W_dev : [M][N] fp64.   U_dev : [M][max_rank] int8, V_dev : [max_rank][N] int8, S_dev :

@@ -8,14 +8,15 @@
 // What the device reports about the squarings of one pair.
 struct tsvd_pair_state {
     int last;            // index of the squared matrix that is numerically of rank one, -1 while there is none
-    int missed;          // pairs since it was last cleared whose squarings ended before that
-    int needed;          // most squarings that a pair needed since it was last cleared (all that were enqueued, where they were not enough)
+    int missed;          // pairs since it was last cleared whose squarings were not enough
+    int needed;          // most squarings that a pair since it was last cleared should have had
 };
 
 struct tsvd_pair_plan {
     int M, N;            // of R
     int n, np;           // the shorter side, and rounded up to 64
     double* X[2];        // [np][np] the squared matrices in turn
+    double* diag[2];     // [np] their diagonals
     double* v0;          // [N] start vector
     double* s;           // [n] start vector on the shorter side (v0 itself where that is the columns)
     tsvd_pair_state* state;
@@ -31,8 +32,14 @@ size_t tsvd_pair_bytes(int64_t M, int64_t N);
 void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* plan, hipStream_t stream);
 // Gram matrix of R [M][N] and its squarings `from` .. `to` - 1 (from = 0 computes the Gram matrix first).
 void tsvd_pair_square(const tsvd_pair_plan& plan, const double* R, int from, int to, hipStream_t stream);
-// plan.u and plan.v from the last squared matrix; `count` squarings were enqueued in total.
-void tsvd_pair_vectors(const tsvd_pair_plan& plan, const double* R, int count, hipStream_t stream);
+// plan.u and plan.v from the last squared matrix; `count` squarings were enqueued in total.  any_rank: it need not be of rank one (where
+// tsvd_pair_any_rank).
+void tsvd_pair_vectors(const tsvd_pair_plan& plan, const double* R, int count, bool any_rank, hipStream_t stream);
+bool tsvd_pair_any_rank(const tsvd_pair_plan& plan);
+// Squarings after which that is likely to do for a matrix of which nothing is known (sixteen where they have to lead to rank one); the
+// device then says what it wants (tsvd_pair_state).
+int tsvd_pair_first_squarings(const tsvd_pair_plan& plan);
+hipError_t tsvd_pair_init();
 // Unit vectors, singular value and number of squarings (steps may be null) of the pair in the plan.
 void tsvd_pair_normalise(const tsvd_pair_plan& plan, int count, double* u, double* v, double* sigma, int32_t* steps, hipStream_t stream);
 // R -= sigma u v^T for the pair in the plan.

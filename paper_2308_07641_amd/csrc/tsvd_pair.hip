@@ -34,13 +34,14 @@ size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 constexpr int PAIR_MAX_N = 2048;
 
 // Workgroup (bi, bj), bi <= bj, of Y = c P P^T for P [rows][L]: T x T blocks of 16 x 16, the contraction split over four
-// wavefronts (v_mfma_f64_16x16x4), each 64 indices at a time; the block and its mirror image are stored.
+// wavefronts (v_mfma_f64_16x16x4), each 64 indices at a time (the Gram matrix of a small n, whose contraction is longer: eight, 32 at a time);
+// the block and its mirror image are stored, and the diagonal once more by itself, so that its readers find 256 entries in 16 lines.
 //
 // The order of the contraction index is free as long as both operands share it: lane group g of a wavefront takes the
-// indices 8 t + 2 g, 8 t + 2 g + 1 of its 64 with load t, so a load is 16 bytes per lane and touches 16 row segments of
+// indices 8 t + 2 g, 8 t + 2 g + 1 of its share with load t, so a load is 16 bytes per lane and touches 16 row segments of
 // 64 bytes.  Bound by the latency of the loads and of the chain of MFMAs (64 cycles each): small tiles on many
-// workgroups while n is small (n = 256: 136 workgroups of 16 MFMAs per wavefront), 32 x 32 tiles, which read half as much
-// per product, beyond.
+// workgroups while n is small (n = 256: 136 workgroups of 16 MFMAs per wavefront, 5.6 us; on eight wavefronts of 8 MFMAs 5.9 us; the Gram matrix of
+// 512 rows 6.2 us on four, 5.7 us on eight), 32 x 32 tiles, which read half as much per product, beyond.
 //
 // GRAM (first launch): P is R by its rows (TR = false) or columns (TR), any pitch; rows beyond n and indices beyond L read
 // as zero, c = 1.  Extra workgroups compute s = R v0 where the shorter side is the rows.
@@ -52,16 +53,17 @@ constexpr int PAIR_MAX_N = 2048;
 // 1, X itself has the ratio squared, below 2.5e-13, and is the result (X x_j has it squared again, times at most sqrt(n)):
 // every workgroup of this and the later launches returns.
 template <int T, bool GRAM, bool TR>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(T == 1 && GRAM ? 512 : 256)
 tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step) {
-    __shared__ __align__(16) double part[4][T * T * 256];
-    __shared__ double red[4];
+    constexpr int W = T == 1 && GRAM ? 8 : 4, SHARE = 256 / W, LOADS = SHARE / 8;      // wavefronts; indices of one at a time
+    __shared__ __align__(16) double part[W][T * T * 256];
+    __shared__ double red[W];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
     const int nb = p.np / (16 * T), tiles = nb * (nb + 1) / 2;
     if constexpr (GRAM) {
         if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = -1;
         if ((int)blockIdx.x >= tiles) {                     // s = R v0, a wavefront per row
-            const int m = ((int)blockIdx.x - tiles) * 4 + wave;
+            const int m = ((int)blockIdx.x - tiles) * W + wave;
             if (m < p.M) {
                 double a = 0.0;
                 for (int k = lane; k < p.N; k += 64) a += R[(size_t)m * p.N + k] * p.v0[k];
@@ -77,6 +79,7 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
     const int bi = (int)blockIdx.x - bj * (bj + 1) / 2;
 
     const double* P = GRAM ? R : p.X[step & 1];
+    const double* D = p.diag[step & 1];
     const int L = GRAM ? (TR ? p.M : p.N) : p.np;
     f64x4 acc[T][T];
 #pragma unroll
@@ -101,27 +104,33 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
     int done = -1;
     if constexpr (!GRAM) {
         done = p.state->last;
-        tr = P[(size_t)min((int)threadIdx.x, p.np - 1) * (p.np + 1)];
+        tr = D[min((int)threadIdx.x, p.np - 1)];
     }
     auto sum_trace = [&] {                                   // the wavefronts' shares of the trace into red
         if ((int)threadIdx.x >= p.np) tr = 0.0;
-        for (int d = threadIdx.x + 256; d < p.np; d += 256) tr += P[(size_t)d * (p.np + 1)];
+        for (int d = threadIdx.x + 64 * W; d < p.np; d += 64 * W) tr += D[d];
         tr = wave_sum(tr);
         if (lane == 0) red[wave] = tr;
+    };
+    auto all = [&] {
+        double a = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) a += red[w];
+        return a;
     };
     if (!GRAM && step == 0) {
         sum_trace();
         __syncthreads();
-        trace = (red[0] + red[1]) + (red[2] + red[3]);
+        trace = all();
         int e = 0;
         (void)frexp(trace, &e);
         scale = ldexp(1.0, -max(e, -1000));
         trace *= scale;
     }
-    for (int k0 = wave * 64; k0 < L; k0 += 256) {
-        f64x2 a[T][8], b[T][8];
+    for (int k0 = wave * SHARE; k0 < L; k0 += 256) {
+        f64x2 a[T][LOADS], b[T][LOADS];
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
+        for (int t = 0; t < LOADS; ++t)
 #pragma unroll
             for (int q = 0; q < T; ++q) {
                 a[q][t] = load(arow[q], k0 + 8 * t + 2 * g);
@@ -130,7 +139,7 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (GRAM) {                                // rows beyond n and indices beyond L count as zero
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
+            for (int t = 0; t < LOADS; ++t)
 #pragma unroll
                 for (int q = 0; q < T; ++q)
 #pragma unroll
@@ -143,7 +152,7 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
             break;
         } else if (step == 0) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
+            for (int t = 0; t < LOADS; ++t)
 #pragma unroll
                 for (int q = 0; q < T; ++q) {
                     a[q][t] *= scale;
@@ -151,7 +160,7 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
                 }
         }
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
+        for (int t = 0; t < LOADS; ++t)
 #pragma unroll
             for (int e = 0; e < 2; ++e)
 #pragma unroll
@@ -175,7 +184,7 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
     __syncthreads();
     if constexpr (!GRAM) {
         if (step > 0) {
-            trace = (red[0] + red[1]) + (red[2] + red[3]);
+            trace = all();
             if (fabs(1.0 - trace) < 1e-6) {
                 if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = step;
                 return;
@@ -184,16 +193,28 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
         c = trace > 0.0 ? 1.0 / (trace * trace) : 0.0;
     }
     double* Y = p.X[GRAM ? 0 : (step + 1) & 1];
-    const int r = threadIdx.x >> 4, cc = threadIdx.x & 15;
+    double* YD = p.diag[GRAM ? 0 : (step + 1) & 1];
+    // (eight wavefronts: the second half of them writes the mirror image)
+    const int r = (threadIdx.x & 255) >> 4, cc = threadIdx.x & 15;
+    const bool first = threadIdx.x < 256, second = W == 4 || !first;
 #pragma unroll
     for (int qa = 0; qa < T; ++qa)
 #pragma unroll
         for (int qb = 0; qb < T; ++qb) {
             const int at = (qa * T + qb) * 256;
             const int row = (bi * T + qa) * 16, col = (bj * T + qb) * 16;
-            auto sum = [&](int e) { return ((part[0][at + e] + part[1][at + e]) + (part[2][at + e] + part[3][at + e])) * c; };
-            Y[(size_t)(row + r) * p.np + col + cc] = sum(r * 16 + cc);
-            if (bi != bj) Y[(size_t)(col + r) * p.np + row + cc] = sum(cc * 16 + r);
+            auto sum = [&](int e) {
+                double a = 0.0;
+#pragma unroll
+                for (int w = 0; w < W; ++w) a += part[w][at + e];
+                return a * c;
+            };
+            if (first) {
+                const double y = sum(r * 16 + cc);
+                Y[(size_t)(row + r) * p.np + col + cc] = y;
+                if (row + r == col + cc) YD[row + r] = y;
+            }
+            if (second && bi != bj) Y[(size_t)(col + r) * p.np + row + cc] = sum(cc * 16 + r);
         }
 }
 
@@ -257,6 +278,133 @@ tsvd_pair_short_kernel(tsvd_pair_plan p, int count) {
     a = wave_sum(a);
     sx = wave_sum(sx);                                       // (of every wavefront: cheaper than a second barrier)
     if (lane == 0 && row < p.n) (p.N <= p.M ? p.v : p.u)[row] = sx < 0.0 ? -a : a;
+}
+
+// The same from a squared matrix that is not of rank one yet, n <= 768 (what fits LDS).  After p squarings all but a few eigenvalues are below rounding, and what
+// is left of the squarings is work on a matrix of that rank: X = L L^T by a Cholesky factorisation with the largest remaining diagonal entry as the
+// pivot (until it is below 2^-50 of the first: X is positive semidefinite, so nothing larger is left anywhere, and the factorisation is as
+// accurate as a squaring), S = L^T L [16][16] with the eigenvalues of X, squared until it is of rank one, and the vector L y with y the column
+// of S^2 that has the largest diagonal entry.  One workgroup, a row a thread.
+//
+// Bound by its chain of latencies: a pivot is two barriers and a column of X from L2 (0.5 us), a squaring of S four MFMAs and a trace in one
+// wavefront (0.25 us: S is symmetric, so the result registers of the MFMA are its operands of the next).  Loops are kept short rather than
+// unrolled: every instruction runs a few times at most, and straight-line code waits for its own fetches (unrolled over the pivots with L in
+// registers the kernel took 22 us).  On a [512, 256] Laplace matrix 8 squarings leave 8 .. 14 pivots, in the place of 3 to 6 squarings of
+// 6.3 us and of two or three launches that had nothing to do.  More than 16 pivots: the pair counts as missed and is taken again with more squarings.
+constexpr int TAIL_RANK = 16, TAIL_PITCH = TAIL_RANK + 1, TAIL_MAX_N = 768;
+static_assert(TAIL_MAX_N * TAIL_PITCH * 8 + TAIL_MAX_N / 64 * 2048 + 1024 <= 160 * 1024, "LDS");
+__global__ void __launch_bounds__(TAIL_MAX_N)
+tsvd_pair_tail_kernel(tsvd_pair_plan p, int count) {
+    extern __shared__ __align__(16) unsigned char tail_lds[];
+    double* L = reinterpret_cast<double*>(tail_lds);         // [threads][TAIL_PITCH]
+    __shared__ double row_j[TAIL_RANK + 1], y[TAIL_RANK], tot[TAIL_MAX_N / 64], part[TAIL_MAX_N / 64][256];
+    __shared__ uint32_t keys[TAIL_MAX_N / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6, i = lane & 15, g = lane >> 4;
+    const int last = p.state->last;
+    const double* X = p.X[(last >= 0 ? last : count) & 1];
+    double d = tid < p.n ? p.diag[(last >= 0 ? last : count) & 1][tid] : -1.0;
+    const double s = p.s[min(tid, p.n - 1)];
+    double* mine = L + tid * TAIL_PITCH;
+#pragma unroll
+    for (int k = 0; k < TAIL_RANK; ++k) mine[k] = 0.0;
+    double tol = 0.0;
+    int r = 0;
+    bool over = false;
+#pragma unroll 1
+    for (int k = 0;; ++k) {
+        uint32_t best = d > 0.0 ? ((uint32_t)(__builtin_bit_cast(uint64_t, d) >> 32) & ~1023u) | (uint32_t)(1023 - tid) : 0u;
+        best = max(best, lane_xor32<32>(best));
+        best = max(best, lane_xor32<16>(best));
+        best = max(best, lane_xor32<8>(best));
+        best = max(best, lane_xor32<4>(best));
+        best = max(best, lane_xor32<2>(best));
+        best = max(best, lane_xor32<1>(best));
+        if (lane == 0) keys[wave] = best;
+        __syncthreads();
+        for (int w = 0; w < waves; ++w) best = max(best, keys[w]);
+        const int j = min(1023 - (int)(best & 1023u), p.n - 1);
+        const double x = X[(size_t)j * p.np + tid];
+        if (tid == j) {
+            row_j[TAIL_RANK] = best ? d : 0.0;
+#pragma unroll 4
+            for (int q = 0; q < k; ++q) row_j[q] = mine[q];
+        }
+        __syncthreads();
+        const double dj = row_j[TAIL_RANK];
+        if (k == 0) tol = dj * 0x1p-50;
+        over = dj > tol && k == TAIL_RANK;
+        if (!(dj > tol) || over) break;
+        double a = 0.0, b = 0.0;
+        for (int q = 0; q < k; q += 2) {                     // (an odd k meets a zero)
+            a += mine[q] * row_j[q];
+            b += mine[q + 1] * (q + 1 < k ? row_j[q + 1] : 0.0);
+        }
+        const double root = sqrt(dj), v = tid == j ? root : (x - (a + b)) / root;
+        mine[k] = v;
+        d = tid == j ? -1.0 : d - v * v;
+        r = k + 1;
+    }
+    if (tid == 0) {
+        // squarings that the next such pair (after `over`: this one) should get: halving the exponent nearly doubles the pivots
+        const int want = over ? count + 3 : r > 12 ? count + 1 : last >= 0 ? last + 1 : r <= 5 ? max(count - 1, 1) : count;
+        if (over) ++p.state->missed;
+        p.state->needed = max(p.state->needed, want);
+    }
+    // ---- S = L^T L: a wavefront's share from its own 64 rows, then one wavefront
+    f64x4 S = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int t = 0; t < 16; ++t) {
+        const double a = L[(wave * 64 + 4 * t + g) * TAIL_PITCH + i];
+        S = __builtin_amdgcn_mfma_f64_16x16x4f64(a, a, S, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[wave][lane * 4 + v] = S[v];
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll 1
+        for (int w = 1; w < waves; ++w)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[v] += part[w][lane * 4 + v];
+        // lane (i, g) holds column i, rows g + 4 v; its diagonal entry, if it has one, v = i / 4
+        auto diagonal = [&] {
+            const double e = i < 8 ? i < 4 ? S[0] : S[1] : i < 12 ? S[2] : S[3];
+            return (i & 3) == g ? e : 0.0;
+        };
+        auto square = [&](double c) {
+            f64x4 sq = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) sq = __builtin_amdgcn_mfma_f64_16x16x4f64(S[t], S[t], sq, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[v] = sq[v] * c;
+        };
+#pragma unroll 1
+        for (int step = count; step < TSVD_PAIR_MAX_SQUARINGS; ++step) {
+            const double trace = wave_sum(diagonal());
+            if (step > count && fabs(1.0 - trace) < 1e-6) break;
+            square(trace > 0.0 ? 1.0 / (trace * trace) : 0.0);
+        }
+        uint32_t best = ((uint32_t)(__builtin_bit_cast(uint64_t, fmax(diagonal(), 0.0)) >> 32) & ~15u) | (uint32_t)(15 - i);
+        best = max(best, lane_xor32<32>(best));
+        best = max(best, lane_xor32<16>(best));
+        best = max(best, lane_xor32<8>(best));
+        best = max(best, lane_xor32<4>(best));
+        best = max(best, lane_xor32<2>(best));
+        best = max(best, lane_xor32<1>(best));
+        square(1.0);
+        if (i == 15 - (int)(best & 15u))
+#pragma unroll
+            for (int v = 0; v < 4; ++v) y[g + 4 * v] = S[v];
+    }
+    __syncthreads();
+    double v = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < TAIL_RANK; ++k) v += mine[k] * y[k];
+    double sx = wave_sum(tid < p.n ? s * v : 0.0);
+    if (lane == 0) tot[wave] = sx;
+    __syncthreads();
+    sx = 0.0;
+    for (int w = 0; w < waves; ++w) sx += tot[w];
+    if (tid < p.n) (p.N <= p.M ? p.v : p.u)[tid] = sx < 0.0 ? -v : v;
 }
 
 // The vector of the longer side.  N <= M: u = R v, a wavefront per row.  M < N: v = R^T u, 64 columns per workgroup, the
@@ -327,11 +475,18 @@ tsvd_pair_deflate_kernel(tsvd_pair_plan p, double* __restrict__ R) {
 
 }  // namespace
 
+hipError_t tsvd_pair_init() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_pair_tail_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, TAIL_MAX_N * TAIL_PITCH * 8);
+}
+
+bool tsvd_pair_any_rank(const tsvd_pair_plan& p) { return p.np <= TAIL_MAX_N; }
+int tsvd_pair_first_squarings(const tsvd_pair_plan& p) { return !tsvd_pair_any_rank(p) ? 16 : p.np <= 128 ? 8 : p.np <= 512 ? 9 : 10; }
+
 bool tsvd_pair_squares(int64_t M, int64_t N) { return std::min(M, N) <= PAIR_MAX_N; }
 
 size_t tsvd_pair_bytes(int64_t M, int64_t N) {
     const size_t np = (size_t)(std::min(M, N) + 63) / 64 * 64;
-    return 2 * round256(np * np * 8) + 3 * round256((size_t)N * 8) + 2 * round256((size_t)M * 8) + 256;
+    return 2 * round256(np * np * 8) + 2 * round256(np * 8) + 3 * round256((size_t)N * 8) + 2 * round256((size_t)M * 8) + 256;
 }
 
 void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* p, hipStream_t stream) {
@@ -344,6 +499,8 @@ void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* p, hipSt
     p->M = (int)M; p->N = (int)N; p->n = (int)std::min(M, N); p->np = (p->n + 63) / 64 * 64;
     p->X[0] = take((size_t)p->np * p->np);
     p->X[1] = take((size_t)p->np * p->np);
+    p->diag[0] = take((size_t)p->np);
+    p->diag[1] = take((size_t)p->np);
     p->v0 = take((size_t)N);
     p->s = N <= M ? p->v0 : take((size_t)M);
     p->u = take((size_t)M);
@@ -358,11 +515,11 @@ void tsvd_pair_square(const tsvd_pair_plan& p, const double* R, int from, int to
     const unsigned tiles = (unsigned)(nb * (nb + 1) / 2);
     if (from == 0) {
         const bool cols = p.N <= p.M;
-        const unsigned grid = tiles + (cols ? 0u : (unsigned)((p.M + 3) / 4));
+        const unsigned grid = tiles + (cols ? 0u : (unsigned)(big ? (p.M + 3) / 4 : (p.M + 7) / 8));
         if (big && cols) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, true, true>), dim3(grid), dim3(256), 0, stream, p, R, 0);
         else if (big) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, true, false>), dim3(grid), dim3(256), 0, stream, p, R, 0);
-        else if (cols) hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, true>), dim3(grid), dim3(256), 0, stream, p, R, 0);
-        else hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, false>), dim3(grid), dim3(256), 0, stream, p, R, 0);
+        else if (cols) hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, true>), dim3(grid), dim3(512), 0, stream, p, R, 0);
+        else hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, false>), dim3(grid), dim3(512), 0, stream, p, R, 0);
     }
     for (int step = from; step < to; ++step) {
         if (big) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, false, false>), dim3(tiles), dim3(256), 0, stream, p, R, step);
@@ -370,8 +527,9 @@ void tsvd_pair_square(const tsvd_pair_plan& p, const double* R, int from, int to
     }
 }
 
-void tsvd_pair_vectors(const tsvd_pair_plan& p, const double* R, int count, hipStream_t stream) {
-    hipLaunchKernelGGL(tsvd_pair_short_kernel, dim3((unsigned)((p.n + 3) / 4)), dim3(256), 0, stream, p, count);
+void tsvd_pair_vectors(const tsvd_pair_plan& p, const double* R, int count, bool any_rank, hipStream_t stream) {
+    if (any_rank) hipLaunchKernelGGL(tsvd_pair_tail_kernel, dim3(1), dim3((unsigned)p.np), (unsigned)(p.np * TAIL_PITCH * 8), stream, p, count);
+    else hipLaunchKernelGGL(tsvd_pair_short_kernel, dim3((unsigned)((p.n + 3) / 4)), dim3(256), 0, stream, p, count);
     const unsigned grid = p.N <= p.M ? (unsigned)((p.M + 3) / 4) : (unsigned)((p.N + 63) / 64);
     hipLaunchKernelGGL(tsvd_pair_long_kernel, dim3(grid), dim3(256), 0, stream, p, R);
 }

@@ -928,7 +928,7 @@ extern "C" tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M
             if (hipMemcpyAsync(&state, plan.state, sizeof state, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
                 return TSVD_EDEVICE;
         }
-        tsvd_pair_vectors(plan, R_dev, count, s);
+        tsvd_pair_vectors(plan, R_dev, count, false, s);
         tsvd_pair_normalise(plan, count, u_dev, v_dev, sigma_dev, steps_dev, s);
         return hipGetLastError() == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
     }
@@ -1008,6 +1008,7 @@ extern "C" tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M
 
 hipError_t tsvd_transition_init() {
     hipError_t e;
+    if ((e = tsvd_pair_init()) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_pcg_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  std::max(5 * FIT_MAX_K * 8, 5 * PCG_LDS_K * 8 + PCG_LDS_K * PCG_LDS_K * 8) + 1024 * 8)) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_residual_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1122,10 +1123,11 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     residual(0, 0);                                                          // R = W, |W|^2
     double wnorm2 = 0.0;
     if (wait_for(0)) wnorm2 = rnorm2;
-    // Squarings enqueued per pair: those beyond the ones a pair needs return at once, too few cost the iteration again.  Sixteen, and
-    // two more than the last iteration needed where that is more: one nearly degenerate residual leaves nothing behind.
-    constexpr int SQUARINGS = 16;
-    int squarings = SQUARINGS;
+    // Squarings enqueued per pair: what the iteration before found right (tsvd_pair_tail_kernel).  Where they have to lead to rank one: sixteen
+    // (those beyond the ones a pair needs return at once), and two more than the last iteration needed where that is more.  Too few
+    // cost the iteration again.
+    const bool any_rank = squares && tsvd_pair_any_rank(plan);
+    int squarings = squares ? tsvd_pair_first_squarings(plan) : 0;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
     auto enqueue = [&](int64_t i, int64_t first, int64_t take) {
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
@@ -1138,7 +1140,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         for (int64_t j = 0; j < take; ++j) {
             if (squares) {
                 tsvd_pair_square(plan, src, 0, squarings, s);
-                tsvd_pair_vectors(plan, src, squarings, s);
+                tsvd_pair_vectors(plan, src, squarings, any_rank, s);
                 if (j + 1 < take) tsvd_pair_deflate(plan, Rwork, s);
             } else {
                 const tsvd_status ps = tsvd_leading_singular_pair(src, M, N, 4 * GKL_MAX_STEPS, u, v, sigma, nullptr, base + at_svd, bytes_svd, s);
@@ -1176,7 +1178,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
             if (st != TSVD_OK || !wait_for(i)) break;
             if (seen.pair.missed != 0 && seen.pair.needed < TSVD_PAIR_MAX_SQUARINGS) {
                 // some pair needed more squarings: back to the residual before this iteration, with more of them
-                squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, seen.pair.needed + 8);
+                squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, seen.pair.needed + (any_rank ? 0 : 8));
                 if (!ok(hipStreamSynchronize(s)) || !ok(hipMemsetAsync(rep, 0, sizeof(transition_report), s))) break;
                 residual(i - 1, K);
                 enqueue(i, K, take);
@@ -1187,7 +1189,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
                 st = TSVD_EVALUE;           // no ternary vector within theta: the components of an unfinished iteration are dropped
                 break;
             }
-            squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(SQUARINGS, seen.pair.needed + 2));
+            squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(1, seen.pair.needed) : std::max(16, seen.pair.needed + 2));
             const double err = std::sqrt(rnorm2 / wnorm2);
             if (errors_host)
                 for (int64_t r = K; r < K + take; ++r) errors_host[r] = err;      // (one error per iteration, repeated for its components)

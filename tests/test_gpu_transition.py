@@ -376,3 +376,36 @@ def test_transition_on_a_laplace_matrix(tsvd):
     assert abs(K - Uo.shape[1]) <= 0.05 * Uo.shape[1] + 2
     r = (np.count_nonzero(U) + np.count_nonzero(V)) / (U.size + V.size)
     assert 0.25 < r < 0.33
+
+
+def test_transition_of_equal_singular_values(tsvd):
+    """A Hadamard matrix: all singular values equal, so no number of squarings leaves a matrix of low rank and any vector will do; the
+    pair taken is a unit vector and a column (or row), which is ternary, and every component removes one of 32."""
+    H = np.ones((1, 1))
+    for _ in range(5):
+        H = np.block([[H, H], [H, -H]])
+    print("case equal singular values", flush=True)
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(3.0 * H), THETA, 0.0, 4)
+    assert status == 0 and U.shape == (32, 4)
+    assert np.max(np.abs(np.array(errs) - np.sqrt(1.0 - np.arange(1, 5) / 32.0))) <= 1e-12
+
+
+@pytest.mark.parametrize("M,N", [(64, 65), (70, 60), (300, 250), (768, 790), (769, 800)])
+def test_transition_with_many_close_singular_values(tsvd, M, N):
+    """Twenty leading singular values within a tenth of each other: the squarings end with a dozen directions, at the sizes on both sides of a
+    workgroup's and of the largest whose end is factorised; each residual's pair is separated by 5e-3, and all must follow the oracle."""
+    rng = np.random.default_rng(12)
+    r = 24
+    A = np.linalg.qr(rng.standard_normal((M, r)))[0]
+    B = np.linalg.qr(rng.standard_normal((N, r)))[0]
+    W = (A * np.concatenate([1.0 - 0.005 * np.arange(20), [0.5, 0.4, 0.3, 0.2]])) @ B.T
+    rank = 3
+    Uo, So, Vo, eo = tr.transition(W, THETA, max_rank=rank)
+    print(f"case many close {M} {N}", flush=True)
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(W), THETA, 0.0, rank)
+    assert status == 0
+    U, S, V = U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy()
+    for k in range(rank):
+        sign = 1 if np.array_equal(U[:, k], Uo[:, k]) else -1
+        assert np.array_equal(sign * U[:, k], Uo[:, k]) and np.array_equal(sign * V[k, :], Vo[k, :]), k
+    assert np.max(np.abs(np.array(errs) - np.array(eo))) <= 1e-9
