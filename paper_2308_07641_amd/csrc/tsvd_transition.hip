@@ -42,7 +42,9 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
 // bitonic network: partners less than a wavefront apart meet through cross-lane moves, those in other wavefronts through
 // LDS (6 of the 45 stages at 512 entries), those of one thread in its registers.  Then prefix sums in sorted order (wave
 // scans and the totals of the wavefronts before), and the smallest q whose cosine reaches cos(theta).  Padding
-// (-1) sorts last.  (With the whole list in LDS and 256 threads, every stage behind a barrier, 512 entries took 23 us.)
+// (-1) sorts last.  (With the whole list in LDS and 256 threads, every stage behind a barrier, 512 entries took 23 us.)  512 entries take 5.7 us: 1.9
+// thousand cycles for the first loads, 7.3 for the network (two wavefronts share a SIMD, and issue some ten operations a stage), 2.3 for
+// the sums and the search: 7 before the scan went by moves between lanes and one lane of a wavefront reported (7.8 us).
 struct ternarize_job {
     const double* x; long long ldx; int n;
     int8_t* t; long long ldt;
@@ -58,12 +60,12 @@ struct ternarize_args {
 template <int E>
 __global__ void __launch_bounds__(TERN_THREADS)
 tsvd_ternarize_kernel(ternarize_args p) {
-    __shared__ double keys[E > 1 ? TERN_THREADS * 2 : TERN_THREADS];
+    __shared__ double keys[2 * TERN_THREADS];
     __shared__ double tot[2][TERN_THREADS / 64];
     __shared__ int qmin;
     __shared__ double threshold;
     const ternarize_job& job = p.job[blockIdx.y];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, T = blockDim.x, nw = T >> 6, n = job.n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), T = blockDim.x, nw = T >> 6, n = job.n;
     const double* xr = job.x + (size_t)blockIdx.x * job.ldx;
     int8_t* tr = job.t + (size_t)blockIdx.x * job.ldt;
     if (tid == 0) qmin = 0x7FFFFFFF;
@@ -82,9 +84,15 @@ tsvd_ternarize_kernel(ternarize_args p) {
     for (int w = 0; w < nw; ++w) length += tot[0][w];
     length = sqrt(length);
     int flip = 0;
-    auto exchange = [&](int e, int k, int j, double b) {                            // position e T + tid meets the one j away
-        const int s = e * T + tid;
-        a[e] = (((s & k) == 0) == ((s & j) == 0)) ? fmax(a[e], b) : fmin(a[e], b);
+    // Position e T + tid meets the one j away: the larger of the two stays where (position & k) and (position & j) agree.  In a wavefront either
+    // condition is a mask of lanes, so a stage is the move, a maximum, a minimum and the choice between them, with nothing that waits for a
+    // scalar register (and no quieting of NaNs before the maximum: 165 cycles a stage).
+    constexpr uint64_t BIT[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0F0F0F0F0F0F0F0Full, 0x00FF00FF00FF00FFull, 0x0000FFFF0000FFFFull, 0x00000000FFFFFFFFull};
+    auto meet = [&](int e, uint64_t larger, double b) {
+        double hi, lo;
+        asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(a[e]), "v"(b));
+        asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(a[e]), "v"(b));
+        a[e] = __builtin_amdgcn_inverse_ballot_w64(larger) ? hi : lo;
     };
     for (int k = 2; k <= p.npow2; k <<= 1) {
         for (int j = k >> 1; j >= 64; j >>= 1) {
@@ -104,44 +112,44 @@ tsvd_ternarize_kernel(ternarize_args p) {
             } else {
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    double* buf = keys + (E > 1 ? flip * TERN_THREADS : 0);
-                    if (E == 1) __syncthreads();                                    // (the reads of the stage before)
+                    double* buf = keys + flip * TERN_THREADS;                       // (the other one's readers may be behind)
                     buf[tid] = a[e];
                     __syncthreads();
-                    exchange(e, k, j, buf[tid ^ j]);
+                    const int s = e * T + wave * 64;
+                    meet(e, ((s & k) == 0) == ((s & j) == 0) ? ~0ull : 0ull, buf[tid ^ j]);
                     flip ^= 1;
                 }
             }
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if (k >= 64) exchange(e, k, 32, lane_xor<32>(a[e]));
-            if (k >= 32) exchange(e, k, 16, lane_xor<16>(a[e]));
-            if (k >= 16) exchange(e, k, 8, lane_xor<8>(a[e]));
-            if (k >= 8) exchange(e, k, 4, lane_xor<4>(a[e]));
-            if (k >= 4) exchange(e, k, 2, lane_xor<2>(a[e]));
-            exchange(e, k, 1, lane_xor<1>(a[e]));
+            const uint64_t mk = __ballot(((e * T + tid) & k) == 0);
+            if (k >= 64) meet(e, ~(mk ^ BIT[5]), lane_xor<32>(a[e]));
+            if (k >= 32) meet(e, ~(mk ^ BIT[4]), lane_xor<16>(a[e]));
+            if (k >= 16) meet(e, ~(mk ^ BIT[3]), lane_xor<8>(a[e]));
+            if (k >= 8) meet(e, ~(mk ^ BIT[2]), lane_xor<4>(a[e]));
+            if (k >= 4) meet(e, ~(mk ^ BIT[1]), lane_xor<2>(a[e]));
+            meet(e, ~(mk ^ BIT[0]), lane_xor<1>(a[e]));
         }
     }
     double carry = 0.0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        double run = fmax(a[e], 0.0);
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double up = __shfl_up(run, o, 64);
-            if (lane >= o) run += up;
-        }
+        double run = wave_scan(fmax(a[e], 0.0));
         if (lane == 63) tot[(e + 1) & 1][wave] = run;
         __syncthreads();
         double before = carry;
+#pragma unroll 8
         for (int w = 0; w < nw; ++w) {
-            if (w < wave) before += tot[(e + 1) & 1][w];
-            carry += tot[(e + 1) & 1][w];
+            const double t = tot[(e + 1) & 1][w];
+            if (w < wave) before += t;
+            carry += t;
         }
         run += before;
         const int q = e * T + tid + 1;
-        if (a[e] >= 0.0 && length > 0.0 && run / (sqrt((double)q) * length) >= p.cos_theta) atomicMin(&qmin, q);
+        // (one lane of a wavefront reports)
+        const uint64_t reached = __ballot(a[e] >= 0.0 && length > 0.0 && run / (sqrt((double)q) * length) >= p.cos_theta);
+        if (lane == 0 && reached != 0) atomicMin(&qmin, e * T + wave * 64 + __builtin_ctzll(reached) + 1);
     }
     __syncthreads();
     const int q = qmin;
@@ -378,29 +386,32 @@ tsvd_pcg_kernel(const double* __restrict__ G, long long ldg, double* __restrict_
     solve_pcg(smem, G, ldg, d, K, s, s0, iters, part, fresh, M);
 }
 
-// ---- Eq. (3), the solve while Algorithm 2 has at most 64 components: one row of the Cholesky factor more per component ----
-// G = L L^T grows by a row and a column per component, and so do L (a forward substitution) and y = L^-1 d (one entry);
-// only the back substitution L^T s = y runs over everything.  One wavefront, a row per lane: a step of either
-// substitution is a lane broadcast, a multiplication and a multiply-add on an entry of L that was read ahead, so 32
-// components take 64 steps of about 40 cycles where conjugate gradients took some twenty iterations of 2000 (19 us).
-// L [CHOL_K][CHOL_K] and y live in `factor` between the calls.  A pivot below 1e-10 of its diagonal entry (two components
+// ---- Eq. (3), the solve while Algorithm 2 has at most 64 components: one row of the triangular factor more per component ----
+// G = L D L^T (L unit lower triangular) grows by a row and a column per component, and so do L (a forward substitution), D and w = L^-1 d (one
+// entry each); only the back substitution L^T s = D^-1 w runs over everything.  One wavefront, a row per lane: a step of either
+// substitution is a lane broadcast and a multiply-add on an entry of L that was read ahead; L is held with zeros on and above its diagonal, so
+// that lanes already done are left alone without a choice.  32 components take 64 steps, where conjugate gradients took some twenty
+// iterations of 2000 cycles (19 us) and a Cholesky factor with a multiplication by 1 / l_jj in every step 170 cycles each: 5.3 us a launch, now 4.3.
+// L [CHOL_K][CHOL_K], 1 / D and w live in `factor` between the calls.  A pivot below 1e-10 of its diagonal entry (two components
 // that nearly coincide) sets factor's last word, and this and all later calls go through conjugate gradients.
 #define CHOL_K 64
-#define CHOL_DOUBLES (CHOL_K * CHOL_K + CHOL_K + 1)
+#define CHOL_DOUBLES (CHOL_K * CHOL_K + 2 * CHOL_K + 1)
 #define CHOL_PITCH (CHOL_K + 1)
 __global__ void __launch_bounds__(256)
 tsvd_scales_kernel(const double* __restrict__ G, long long ldg, double* __restrict__ d, int K, double* __restrict__ s,
                    const double* __restrict__ s0, const double* __restrict__ part, int fresh, int M, double* __restrict__ factor) {
     extern __shared__ __align__(16) unsigned char smem[];
-    double* Ll = reinterpret_cast<double*>(smem);           // [K][CHOL_PITCH]
+    double* Ll = reinterpret_cast<double*>(smem);           // [K rounded up to 8][CHOL_PITCH], zero on and above the diagonal
     __shared__ double tot[CHOL_K][4];
     __shared__ int singular;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double* y = factor + CHOL_K * CHOL_K;
-    double* marked = y + CHOL_K;
+    double* w = factor + CHOL_K * CHOL_K;
+    double* dinv = w + CHOL_K;
+    double* marked = dinv + CHOL_K;
     if (tid == 0) singular = marked[0] != 0.0;
 #pragma unroll 4
     for (int e = tid; e < fresh * CHOL_K; e += 256) Ll[(e >> 6) * CHOL_PITCH + (e & 63)] = factor[e];
+    for (int e = fresh * CHOL_K + tid; e < ((K + 7) & ~7) * CHOL_K; e += 256) Ll[(e >> 6) * CHOL_PITCH + (e & 63)] = 0.0;
     for (int k = fresh; k < K; ++k) {
         double a = 0.0;
         for (int m = tid; m < M; m += 256) a += part[(size_t)(k - fresh) * M + m];
@@ -414,31 +425,29 @@ tsvd_scales_kernel(const double* __restrict__ G, long long ldg, double* __restri
             return __builtin_bit_cast(double, (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)b, from) |
                                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(b >> 32), from) << 32));
         };
-        double inv = lane < fresh ? 1.0 / Ll[lane * CHOL_PITCH + lane] : 0.0, yl = lane < fresh ? y[lane] : 0.0;
+        double inv = lane < fresh ? dinv[lane] : 0.0, wl = lane < fresh ? w[lane] : 0.0;
         bool bad = false;
         for (int r = fresh; r < K && !bad; ++r) {
-            const double* row = Ll + min(lane, r) * CHOL_PITCH;
+            const double* row = Ll + min(lane, r) * CHOL_PITCH;                // (row r itself is zero still)
             double x = lane <= r ? G[(size_t)r * ldg + lane] : 0.0;
             const double dr = (tot[r][0] + tot[r][1]) + (tot[r][2] + tot[r][3]), grr = broadcast(x, r);
-            for (int j0 = 0; j0 < r; j0 += 8)               // (steps at and beyond r change nothing)
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int j = j0 + t;
-                    const double lj = broadcast(x, j) * broadcast(inv, j), e = row[j];
-                    x = lane < r && lane >= j ? lane == j ? lj : x - e * lj : x;
-                }
             if (lane >= r) x = 0.0;
-            const double pivot = grr - wave_sum(x * x), dot = wave_sum(x * yl);
+            for (int j0 = 0; j0 < r; j0 += 8) {             // (steps at and beyond r meet zeros)
+                double e[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) e[t] = row[j0 + t];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) x -= broadcast(x, j0 + t) * e[t];
+            }
+            const double l = x * inv, pivot = grr - wave_sum(x * l), dot = wave_sum(l * wl);
             bad = !(pivot > 1e-10 * grr);
-            const double diag = sqrt(pivot);
             if (lane == r) {
-                x = diag;
-                inv = 1.0 / diag;
-                yl = (dr - dot) / diag;
+                inv = 1.0 / pivot;
+                wl = dr - dot;
                 d[r] = dr;
             }
-            Ll[r * CHOL_PITCH + lane] = x;
-            factor[r * CHOL_K + lane] = x;
+            Ll[r * CHOL_PITCH + lane] = l;
+            factor[r * CHOL_K + lane] = l;
         }
         if (bad) {
             if (lane == 0) {
@@ -446,15 +455,18 @@ tsvd_scales_kernel(const double* __restrict__ G, long long ldg, double* __restri
                 marked[0] = 1.0;
             }
         } else {
-            if (lane >= fresh && lane < K) y[lane] = yl;
-            double x = yl;
-            for (int j0 = (K - 1) & ~7; j0 >= 0; j0 -= 8)
+            if (lane >= fresh && lane < K) {
+                w[lane] = wl;
+                dinv[lane] = inv;
+            }
+            double x = wl * inv;
+            for (int j0 = (K - 1) & ~7; j0 >= 0; j0 -= 8) {                     // (rows from K on are zero)
+                double e[8];
 #pragma unroll
-                for (int t = 7; t >= 0; --t) {
-                    const int j = j0 + t;
-                    const double sj = broadcast(x, j) * broadcast(inv, j), e = Ll[min(j, K - 1) * CHOL_PITCH + lane];
-                    x = j < K && lane <= j ? lane == j ? sj : x - e * sj : x;
-                }
+                for (int t = 0; t < 8; ++t) e[t] = Ll[(j0 + t) * CHOL_PITCH + lane];
+#pragma unroll
+                for (int t = 7; t >= 0; --t) x -= broadcast(x, j0 + t) * e[t];
+            }
             if (lane < K) s[lane] = x;
         }
     }
@@ -839,7 +851,8 @@ void launch_solve(const double* G, long long ldg, double* d, int K, double* s, c
     const bool lds = K <= PCG_LDS_K;
     const size_t bytes = (size_t)5 * K * 8 + 1024 * 8 + (lds ? (size_t)K * K * 8 : 0);
     if (factor && K <= CHOL_K) {
-        hipLaunchKernelGGL(tsvd_scales_kernel, dim3(1), dim3(256), bytes, stream, G, ldg, d, K, s, s0, part, K - fresh_count, M, factor);
+        const size_t rows = (size_t)((K + 7) & ~7) * CHOL_PITCH * 8;           // the factor, or what conjugate gradients need
+        hipLaunchKernelGGL(tsvd_scales_kernel, dim3(1), dim3(256), std::max(bytes, rows), stream, G, ldg, d, K, s, s0, part, K - fresh_count, M, factor);
         return;
     }
     hipLaunchKernelGGL(tsvd_pcg_kernel, dim3(1), dim3(lds ? (unsigned)((K + 63) & ~63) : 1024u), bytes, stream, G, ldg, d, K, s, s0, iters, part,

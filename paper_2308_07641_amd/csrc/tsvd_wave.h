@@ -38,4 +38,21 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Sum over the lanes up to and including one's own: rows of 16 lanes, then the totals of the rows before.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_shifted(double v) {      // zero where the move has no source
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)b, CTRL, ROWS, 0xF, false), hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(b >> 32), CTRL, ROWS, 0xF, false);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+__device__ __forceinline__ double wave_scan(double v) {
+    v += lane_shifted<0x111, 0xF>(v);            // row_shr 1, 2, 4, 8
+    v += lane_shifted<0x112, 0xF>(v);
+    v += lane_shifted<0x114, 0xF>(v);
+    v += lane_shifted<0x118, 0xF>(v);
+    v += lane_shifted<0x142, 0xA>(v);            // row_bcast 15 into rows 1 and 3
+    v += lane_shifted<0x143, 0xC>(v);            // row_bcast 31 into rows 2 and 3
+    return v;
+}
+
 }  // namespace
