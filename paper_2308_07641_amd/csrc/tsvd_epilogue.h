@@ -23,11 +23,10 @@ __device__ __forceinline__ void tsvd_store_y(void* y, size_t idx, float v, int o
 // Neighbouring lanes swap one value (DPP quad_perm [1,0,3,2]), so that an even lane holds tokens
 // (i, i + 1) of row r and the odd lane next to it tokens (i - 1, i) of row r + 1; one packed
 // conversion (nearest even) and one 4-byte store per lane then cover both rows with all 64 lanes
-// active: half the store instructions of the fp32 form for half the bytes.  aligned4 (uniform):
-// the row stride is even and y 4-byte aligned; otherwise the pair is written as two 2-byte stores.
+// active: half the store instructions of the fp32 form for half the bytes, at any address.
 // Must be called by all 16 lanes of a lane group together.
 __device__ __forceinline__ void tsvd_store_row_pair_bf16(void* y, long long ld, int r, int rows_valid, int col16, int i,
-                                                         int bvalid, float v0, float v1, bool aligned4) {
+                                                         int bvalid, float v0, float v1) {
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
     const int odd = i & 1, c = col16 + i - odd;
@@ -39,12 +38,8 @@ __device__ __forceinline__ void tsvd_store_row_pair_bf16(void* y, long long ld, 
     if (row < rows_valid) {
         uint16_t* dst = static_cast<uint16_t*>(y) + (size_t)row * ld + c;
         if (c + 1 < bvalid) {
-            if (aligned4) {
-                *reinterpret_cast<uint32_t*>(dst) = pk;
-            } else {
-                dst[0] = (uint16_t)pk;
-                dst[1] = (uint16_t)(pk >> 16);
-            }
+            typedef uint32_t u32_at __attribute__((aligned(2)));
+            *reinterpret_cast<u32_at*>(dst) = pk;
         } else if (c < bvalid) {
             *dst = (uint16_t)pk;
         }
@@ -53,20 +48,23 @@ __device__ __forceinline__ void tsvd_store_row_pair_bf16(void* y, long long ld, 
 
 // Token-major output y[token][row]: the lane of a 16 x 16 result block that holds token `token` of rows
 // row0 .. row0 + 3 (row0 a multiple of 4) writes them side by side: one 16-byte (fp32) or 8-byte (bf16)
-// store when the four rows exist and vec_ok says that ld is a multiple of 4 elements and y is 16-byte
-// aligned; element by element otherwise.
+// store when the four rows exist, at whatever address the rows' pitch gives (vector memory takes any); element by element otherwise.
+// (By element where the pitch is no multiple of 16 bytes, as before, the address unit is what bounds the call: 9070 x 960 x 200 at
+// 940 tokens, fp32, 41.8 -> 23.8 us; 813 x 184 x 86 at 9460, bf16 in and out, 33.3 -> 23.2 us with the loads of tsvd_gather_row.)
 __device__ __forceinline__ void tsvd_store_token_major4(void* y, long long ld, int token, int row0, int rows_valid,
-                                                        float v0, float v1, float v2, float v3, int out_bf16, bool vec_ok) {
+                                                        float v0, float v1, float v2, float v3, int out_bf16) {
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    typedef f32x4_t f32x4_at __attribute__((aligned(4)));
+    typedef u32x2_t u32x2_at __attribute__((aligned(2)));
     const size_t at = (size_t)token * ld + row0;
-    if (vec_ok && row0 + 3 < rows_valid) {
+    if (row0 + 3 < rows_valid) {
         if (out_bf16) {
             const u32x2_t pk = {(uint32_t)tsvd_bf16_rne(v0) | ((uint32_t)tsvd_bf16_rne(v1) << 16),
                                 (uint32_t)tsvd_bf16_rne(v2) | ((uint32_t)tsvd_bf16_rne(v3) << 16)};
-            *reinterpret_cast<u32x2_t*>(static_cast<uint16_t*>(y) + at) = pk;
+            *reinterpret_cast<u32x2_at*>(static_cast<uint16_t*>(y) + at) = pk;
         } else {
-            *reinterpret_cast<f32x4_t*>(static_cast<float*>(y) + at) = f32x4_t{v0, v1, v2, v3};
+            *reinterpret_cast<f32x4_at*>(static_cast<float*>(y) + at) = f32x4_t{v0, v1, v2, v3};
         }
         return;
     }
@@ -79,7 +77,7 @@ __device__ __forceinline__ void tsvd_store_token_major4(void* y, long long ld, i
 // Token-major bf16 output of four 16 x 16 result blocks below each other (rows row0 .. row0 + 63; a lane (i, g) holds token i of
 // rows 16 a + 4 g .. + 3 of block a as two packed words d[a]): the four lane groups transpose their pieces (two swaps of lane
 // rows per word), after which lane group g holds all sixteen rows of block g and stores them as 32 consecutive bytes: 128 bytes per
-// token and store pair where the plain form writes 32.  All 64 lanes must call it; rows and alignment are the caller's concern.
+// token and store pair where the plain form writes 32, at any address.  All 64 lanes must call it; the rows must exist.
 __device__ __forceinline__ void tsvd_store_token_major_bf16_4x16(void* y, long long ld, int token, bool token_ok, int row0, int g, uint32_t (&d)[4][2]) {
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -100,7 +98,8 @@ __device__ __forceinline__ void tsvd_store_token_major_bf16_4x16(void* y, long l
         swap32(1, 3);
     }
     if (token_ok) {
-        u32x4_t* dst = reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(y) + (size_t)token * ld + row0 + 16 * g);
+        typedef u32x4_t u32x4_at __attribute__((aligned(2)));
+        u32x4_at* dst = reinterpret_cast<u32x4_at*>(static_cast<uint16_t*>(y) + (size_t)token * ld + row0 + 16 * g);
         dst[0] = u32x4_t{d[0][0], d[0][1], d[1][0], d[1][1]};
         dst[1] = u32x4_t{d[2][0], d[2][1], d[3][0], d[3][1]};
     }

@@ -40,13 +40,16 @@ namespace {
 // The operand pass for token-major bf16 activations x [cols_valid tokens][ld]: no transposition through LDS, a lane's
 // values are contiguous in memory.  Same grid and records as tsvd_z_planes_kernel.
 __global__ void __launch_bounds__(512)
-tsvd_x_planes_token_major_kernel(const uint16_t* __restrict__ x, long long ld, unsigned x_bytes, int rows_valid, int cols_valid, int nblocks,
-                                 int vec, unsigned char* __restrict__ planes) {
+tsvd_x_planes_token_major_kernel(const uint16_t* __restrict__ x, long long ld, int rows_valid, int cols_valid, int nblocks,
+                                 unsigned char* __restrict__ planes) {
     const int tt = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x), 0, x_bytes, 0x00020000);
     const int tok = blockIdx.x * 128 + tt * 16 + i;
     float v[32];
-    tsvd_gather_token_major(x_rsrc, (int)ld * 2, tok, blockIdx.y * 128 + 64 * (g & 1) + 16 * (g >> 1), rows_valid, tok < cols_valid, vec != 0, v);
+    tsvd_gather_row(x + (size_t)min(tok, cols_valid - 1) * ld, blockIdx.y * 128 + 64 * (g & 1) + 16 * (g >> 1), rows_valid,
+                    (int)blockIdx.y * 128 + 128 <= rows_valid, v);
+#pragma unroll
+    for (int e = 0; e < 32; ++e)
+        if (tok >= cols_valid) v[e] = 0.f;
     tsvd_planes_of_32(v, planes + ((size_t)(blockIdx.x * nblocks + blockIdx.y) * 8 + tt) * FP6_REC_BYTES, lane);
 }
 
@@ -312,7 +315,7 @@ tsvd_gemm_fp6_tail_kernel(gemm_args p) {
 #define TSVD_PANEL6_LDS (TSVD_PANEL6_MAX_BLOCKS * 4 * FP6_REC_BYTES)          // 155648
 #define TSVD_PANEL6_LDS_EX (TSVD_PANEL6_LDS + TSVD_PANEL_BIAS_ROWS * 4)        // 163840: all of it
 
-template <int EX = 0>
+template <int EX, bool ROWS>            // ROWS: x is [tokens][ldx]
 __global__ void __launch_bounds__(512, 1)
 tsvd_panel_fp6_kernel(panel_args p) {
     constexpr int TM = 8, TN = 4, NW = 8, BT = 64;
@@ -390,13 +393,15 @@ tsvd_panel_fp6_kernel(panel_args p) {
             for (int e = 0; e < 32; ++e)
                 raw[e] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x_rsrc, voff, (nb * 128 + 32 * (e >> 4) + (e & 15)) * ld2, 0);
         };
-        if (p.x_token_major) {
-            // x is [tokens][ldx]: a lane's two runs of 16 indices are contiguous, nothing to transpose
-            const bool vec = !(p.ldx & 7) && !(reinterpret_cast<uintptr_t>(p.x) & 15);
+        if constexpr (ROWS) {
+            // a lane's two runs of 16 indices are contiguous, nothing to transpose
             for (int q = wave; q < njobs; q += NW) {
                 const int tok = b0 + 16 * (q & 3) + i;
                 float v[32];
-                tsvd_gather_token_major(x_rsrc, ld2, tok, (q >> 2) * 128 + 64 * (g & 1) + 16 * (g >> 1), p.N, tok < p.B, vec, v);
+                tsvd_gather_row(p.x + (size_t)min(tok, p.B - 1) * p.ldx, (q >> 2) * 128 + 64 * (g & 1) + 16 * (g >> 1), p.N, (q >> 2) * 128 + 128 <= p.N, v);
+#pragma unroll
+                for (int e = 0; e < 32; ++e)
+                    if (tok >= p.B) v[e] = 0.f;
                 tsvd_planes_of_32(v, smem + q * FP6_REC_BYTES, lane);
             }
         } else {
@@ -600,7 +605,7 @@ tsvd_panel_fp6_kernel(panel_args p) {
                             if (col < p.B)
                                 tsvd_store_token_major4(p.y, p.ldy, col, (strip0 + a) * 16 + 4 * g, p.M, acc[a][b][0] + br[a][0],
                                                         acc[a][b][1] + br[a][1], acc[a][b][2] + br[a][2], acc[a][b][3] + br[a][3],
-                                                        p.out_bf16, vec_ok);
+                                                        p.out_bf16);
                         }
                     }
                 } else if constexpr (EX == 2) {
@@ -636,7 +641,7 @@ tsvd_panel_fp6_kernel(panel_args p) {
 #pragma unroll
                                 for (int b = 0; b < UTN; ++b)
                                     tsvd_store_row_pair_bf16(p.y, p.ldy, (strip0 + a) * 16 + 4 * g + vp, p.M, c0 + b * 16, i, p.B,
-                                                             acc[a][b][vp] + br[a][vp], acc[a][b][vp + 1] + br[a][vp + 1], aligned4);
+                                                             acc[a][b][vp] + br[a][vp], acc[a][b][vp + 1] + br[a][vp + 1]);
                             }
                         }
                     }
@@ -844,9 +849,7 @@ hipError_t tsvd_fp6_launch_planes(bool bf16, const uint16_t* src, long long ld, 
                                   int blocks, long long B, unsigned char* planes, hipStream_t stream, bool token_major) {
     const dim3 grid((unsigned)((B + 127) / 128), (unsigned)blocks), block(512);
     if (token_major) {       // (bf16 x, one row per token)
-        const int vec = !(ld & 7) && !(reinterpret_cast<uintptr_t>(src) & 15);
-        hipLaunchKernelGGL(tsvd_x_planes_token_major_kernel, grid, block, 0, stream, src, ld, (unsigned)((size_t)cols_valid * ld * 2), rows_valid,
-                           cols_valid, nblocks_per_group, vec, planes);
+        hipLaunchKernelGGL(tsvd_x_planes_token_major_kernel, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, planes);
         return hipGetLastError();
     }
     if (bf16) hipLaunchKernelGGL(tsvd_z_planes_kernel<true>, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, planes);
@@ -856,10 +859,9 @@ hipError_t tsvd_fp6_launch_planes(bool bf16, const uint16_t* src, long long ld, 
 
 hipError_t tsvd_fp6_launch_panel(const panel_args& pa, int ex, hipStream_t stream) {
     const dim3 grid((unsigned)((pa.B + 63) / 64)), block(512);
-    if (ex == 3) hipLaunchKernelGGL((tsvd_panel_fp6_kernel<3>), grid, block, TSVD_PANEL6_LDS_EX, stream, pa);
-    else if (ex == 2) hipLaunchKernelGGL((tsvd_panel_fp6_kernel<2>), grid, block, TSVD_PANEL6_LDS_EX, stream, pa);
-    else if (ex == 1) hipLaunchKernelGGL((tsvd_panel_fp6_kernel<1>), grid, block, TSVD_PANEL6_LDS_EX, stream, pa);
-    else hipLaunchKernelGGL((tsvd_panel_fp6_kernel<0>), grid, block, TSVD_PANEL6_LDS, stream, pa);
+    auto run = [&](auto k) { hipLaunchKernelGGL(k, grid, block, ex ? TSVD_PANEL6_LDS_EX : TSVD_PANEL6_LDS, stream, pa); };
+    if (pa.x_token_major) run(ex == 3 ? tsvd_panel_fp6_kernel<3, true> : ex == 2 ? tsvd_panel_fp6_kernel<2, true> : ex == 1 ? tsvd_panel_fp6_kernel<1, true> : tsvd_panel_fp6_kernel<0, true>);
+    else run(ex == 3 ? tsvd_panel_fp6_kernel<3, false> : ex == 2 ? tsvd_panel_fp6_kernel<2, false> : ex == 1 ? tsvd_panel_fp6_kernel<1, false> : tsvd_panel_fp6_kernel<0, false>);
     return hipGetLastError();
 }
 
@@ -878,12 +880,8 @@ hipError_t tsvd_fp6_init() {
     if ((e = init_fp6_tail<false, 0, true>()) != hipSuccess) return e;
     if ((e = init_fp6_direct<2, 2>()) != hipSuccess) return e;
     if ((e = init_fp6_direct<4, 1>()) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_panel_fp6_kernel<0>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TSVD_PANEL6_LDS)) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_panel_fp6_kernel<1>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TSVD_PANEL6_LDS_EX)) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_panel_fp6_kernel<2>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TSVD_PANEL6_LDS_EX)) != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_panel_fp6_kernel<3>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               TSVD_PANEL6_LDS_EX);
+    for (const auto k : {tsvd_panel_fp6_kernel<0, false>, tsvd_panel_fp6_kernel<0, true>, tsvd_panel_fp6_kernel<1, false>, tsvd_panel_fp6_kernel<1, true>,
+                         tsvd_panel_fp6_kernel<2, false>, tsvd_panel_fp6_kernel<2, true>, tsvd_panel_fp6_kernel<3, false>, tsvd_panel_fp6_kernel<3, true>})
+        if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, TSVD_PANEL6_LDS_EX)) != hipSuccess) return e;
+    return hipSuccess;
 }

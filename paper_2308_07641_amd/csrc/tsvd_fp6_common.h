@@ -80,30 +80,48 @@ __device__ __forceinline__ void tsvd_planes_of_32_twice(float (&v)[32], unsigned
     tsvd_planes_of_32<false>(v, rec2, lane);
 }
 
-// The 32 values of one operand lane from bf16 activations stored one row per token (token-major, row pitch ld
-// elements): indices k0 + 32 (e >> 4) + (e & 15), two runs of 16 consecutive elements.  vec: rows and base are 16-byte
-// aligned (four 16-byte loads), else 32 two-byte loads.  The buffer's range check gives zero beyond the last token's
-// row; indices beyond kvalid and tokens beyond the batch are zeroed here.
-__device__ __forceinline__ void tsvd_gather_token_major(__amdgpu_buffer_rsrc_t x_rsrc, int ld2, int tok, int k0, int kvalid, bool tok_ok,
-                                                        bool vec, float (&v)[32]) {
-    const int voff = tok * ld2;
-    if (vec) {
-        u32x4 q[4];
+// The 32 values of one operand lane from a token's row of N activations (T: uint16_t, the bits of bf16, or uint32_t, those of fp32): indices
+// k0 + 32 (e >> 4) + (e & 15), two runs of 16 consecutive elements, 16 bytes at a time at whatever address the row has (vector
+// memory takes any; a load per element costs 32 instructions that the address unit takes a lane group at a time).  A chunk that
+// would pass the row's end is read to end there and shifted; indices beyond N are zero.  (313 x 1049 x 384 at 5299 tokens 26.1 -> 18.2 us.)  inside (uniform): all of this lane's
+// block lies below N.
+template <typename T>
+__device__ __forceinline__ void tsvd_gather_row(const T* row, int k0, int N, bool inside, float (&v)[32]) {
+    typedef u32x4 chunk_at __attribute__((aligned(2)));
+    constexpr int PER = 16 / sizeof(T), CHUNKS = 32 / PER;
+    u32x4 q[CHUNKS];
+    auto first = [&](int c) { return k0 + (c < CHUNKS / 2 ? 0 : 32 - 16) + PER * c; };
+    if (inside) {
 #pragma unroll
-        for (int h = 0; h < 4; ++h) q[h] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, voff, (k0 + 32 * (h >> 1) + 8 * (h & 1)) * 2, 0);
+        for (int c = 0; c < CHUNKS; ++c) q[c] = *reinterpret_cast<const chunk_at*>(row + first(c));
+    } else if (N >= PER) {
 #pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const uint32_t w = q[2 * (e >> 4) + ((e >> 3) & 1)][(e & 7) >> 1];
-            v[e] = __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
+        for (int c = 0; c < CHUNKS; ++c) q[c] = *reinterpret_cast<const chunk_at*>(row + min(first(c), N - PER));
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {
+            const int bits = 8 * (int)sizeof(T) * max(0, first(c) - (N - PER));
+            const unsigned __int128 w = __builtin_bit_cast(unsigned __int128, q[c]);
+            q[c] = __builtin_bit_cast(u32x4, bits < 128 ? w >> (bits & 127) : (unsigned __int128)0);
         }
     } else {
 #pragma unroll
-        for (int e = 0; e < 32; ++e)
-            v[e] = __uint_as_float((uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x_rsrc, voff, (k0 + 32 * (e >> 4) + (e & 15)) * 2, 0) << 16);
+        for (int c = 0; c < CHUNKS; ++c) {
+            unsigned __int128 w = 0;
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+                if (first(c) + e < N) w |= (unsigned __int128)row[first(c) + e] << (8 * (int)sizeof(T) * e);
+            q[c] = __builtin_bit_cast(u32x4, w);
+        }
     }
 #pragma unroll
-    for (int e = 0; e < 32; ++e)
-        if (!tok_ok || k0 + 32 * (e >> 4) + (e & 15) >= kvalid) v[e] = 0.f;
+    for (int e = 0; e < 32; ++e) {
+        if constexpr (sizeof(T) == 4) {
+            v[e] = __uint_as_float(q[e >> 2][e & 3]);
+        } else {
+            const uint32_t w = q[e >> 3][(e & 7) >> 1];
+            v[e] = __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
+        }
+    }
 }
 
 template <int PL>

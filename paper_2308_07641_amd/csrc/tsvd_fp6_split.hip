@@ -30,33 +30,18 @@ template <bool F32>
 __device__ __forceinline__ void gather_x(const void* x, long long ld, bool token_major, int N, int B, int block, int tile, int lane, float (&v)[32]) {
     using T = std::conditional_t<F32, uint32_t, uint16_t>;
     const int i = lane & 15, g = lane >> 4, tok = tile * 16 + i, k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1), tc = min(tok, B - 1);
-    auto value = [](T r) { return F32 ? __builtin_bit_cast(float, (uint32_t)r) : __uint_as_float((uint32_t)r << 16); };
     const T* p = static_cast<const T*>(x);
-    if (token_major && k0 + 48 <= N && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && ld % (16 / (int)sizeof(T)) == 0) {   // two runs of 16 indices, 16 bytes at a time
-        constexpr int PER = 16 / sizeof(T);
-        u32x4 q[2][16 / PER];
-        const T* row = p + (size_t)tc * ld + k0;
+    if (token_major) {
+        tsvd_gather_row(p + (size_t)tc * ld, k0, N, block * 128 + 128 <= N, v);
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int c = 0; c < 16 / PER; ++c) q[r][c] = *reinterpret_cast<const u32x4*>(row + 32 * r + PER * c);
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const int r = e >> 4, at = e & 15;
-            if constexpr (F32) {
-                v[e] = __uint_as_float(q[r][at >> 2][at & 3]);
-            } else {
-                const uint32_t w = q[r][at >> 3][(at & 7) >> 1];
-                v[e] = __uint_as_float((at & 1) ? (w & 0xFFFF0000u) : (w << 16));
-            }
+        for (int e = 0; e < 32; ++e)
             if (tok >= B) v[e] = 0.f;
-        }
         return;
     }
-    const size_t ks = token_major ? 1 : (size_t)ld, ts = token_major ? (size_t)ld : 1;
+    auto value = [](T r) { return F32 ? __builtin_bit_cast(float, (uint32_t)r) : __uint_as_float((uint32_t)r << 16); };
     T r[32];
 #pragma unroll
-    for (int e = 0; e < 32; ++e) r[e] = p[(size_t)min(k0 + 32 * (e >> 4) + (e & 15), N - 1) * ks + (size_t)tc * ts];
+    for (int e = 0; e < 32; ++e) r[e] = p[(size_t)min(k0 + 32 * (e >> 4) + (e & 15), N - 1) * ld + tc];
 #pragma unroll
     for (int e = 0; e < 32; ++e) v[e] = tok < B && k0 + 32 * (e >> 4) + (e & 15) < N ? value(r[e]) : 0.f;
 }

@@ -1083,7 +1083,6 @@ tsvd_panel_kernel(panel_args p) {
                 else fill([](int) { return 0.f; });
             }
             if constexpr (EX == 3) {
-                const bool vec_ok = !(p.ldy & 3) && !(reinterpret_cast<uintptr_t>(p.y) & 15);
 #pragma unroll
                 for (int a = 0; a < TM; ++a) {
 #pragma unroll
@@ -1092,11 +1091,10 @@ tsvd_panel_kernel(panel_args p) {
                         if (col < p.B)
                             tsvd_store_token_major4(p.y, p.ldy, col, (strip0 + a) * 16 + 4 * g, p.M, acc[a][b][0] * c2[b] + br[a][0],
                                                     acc[a][b][1] * c2[b] + br[a][1], acc[a][b][2] * c2[b] + br[a][2],
-                                                    acc[a][b][3] * c2[b] + br[a][3], p.out_bf16, vec_ok);
+                                                    acc[a][b][3] * c2[b] + br[a][3], p.out_bf16);
                     }
                 }
             } else if constexpr (EX == 2) {
-                const bool aligned4 = !(p.ldy & 1) && !(reinterpret_cast<uintptr_t>(p.y) & 3);
 #pragma unroll
                 for (int a = 0; a < TM; ++a) {
 #pragma unroll
@@ -1104,7 +1102,7 @@ tsvd_panel_kernel(panel_args p) {
 #pragma unroll
                         for (int b = 0; b < TN; ++b)
                             tsvd_store_row_pair_bf16(p.y, p.ldy, (strip0 + a) * 16 + 4 * g + vp, p.M, b0 + b * 16, i, p.B,
-                                                     acc[a][b][vp] * c2[b] + br[a][vp], acc[a][b][vp + 1] * c2[b] + br[a][vp + 1], aligned4);
+                                                     acc[a][b][vp] * c2[b] + br[a][vp], acc[a][b][vp + 1] * c2[b] + br[a][vp + 1]);
                     }
                 }
             } else if constexpr (EX == 1) {

@@ -140,7 +140,6 @@ __device__ __forceinline__ void gemm_epilogue(const gemm_args& p, f32x4 (&acc)[T
         }
     }
     if constexpr (STAGE2 && EX == 3) {        // token-major output (fp32 or bf16, with or without bias): four rows per store
-        const bool vec_ok = !(p.ld_out & 3) && !(reinterpret_cast<uintptr_t>(p.out) & 15);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
 #pragma unroll
@@ -149,13 +148,12 @@ __device__ __forceinline__ void gemm_epilogue(const gemm_args& p, f32x4 (&acc)[T
                 if (col < p.bvalid)
                     tsvd_store_token_major4(p.out, p.ld_out, col, (strip0 + a) * 16 + 4 * g, p.rows_valid, acc[a][b][0] * cs[b] + sr[a][0],
                                             acc[a][b][1] * cs[b] + sr[a][1], acc[a][b][2] * cs[b] + sr[a][2], acc[a][b][3] * cs[b] + sr[a][3],
-                                            p.out_bf16, vec_ok);
+                                            p.out_bf16);
             }
         }
         return;
     }
     if constexpr (STAGE2 && EX == 2) {        // bf16 in pairs: rows two by two, tokens left to right
-        const bool aligned4 = !(p.ld_out & 1) && !(reinterpret_cast<uintptr_t>(p.out) & 3);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
 #pragma unroll
@@ -163,7 +161,7 @@ __device__ __forceinline__ void gemm_epilogue(const gemm_args& p, f32x4 (&acc)[T
 #pragma unroll
                 for (int b = 0; b < TN; ++b)
                     tsvd_store_row_pair_bf16(p.out, p.ld_out, (strip0 + a) * 16 + 4 * g + vp, p.rows_valid, col0 + b * 16, i, p.bvalid,
-                                             acc[a][b][vp] * cs[b] + sr[a][vp], acc[a][b][vp + 1] * cs[b] + sr[a][vp + 1], aligned4);
+                                             acc[a][b][vp] * cs[b] + sr[a][vp], acc[a][b][vp + 1] * cs[b] + sr[a][vp + 1]);
             }
         }
         return;

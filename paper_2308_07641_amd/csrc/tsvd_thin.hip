@@ -92,7 +92,6 @@ tsvd_thin_panel_kernel(thin_args p) {
             raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, off, 0, 0);
             if (e % 8 == 7) __builtin_amdgcn_sched_barrier(0);      // (the offsets of all 32 at once would not fit the registers)
         };
-        bool whole = false;                                         // v filled 16 bytes at a time
         if constexpr (SOURCE == THIN_CONV) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -106,24 +105,7 @@ tsvd_thin_panel_kernel(thin_args p) {
                 }
             }
         } else if constexpr (SOURCE == THIN_TOKEN_MAJOR) {
-            const int row = 2 * tok * (int)p.ldx;
-            if (k0 + 48 <= p.N && !(p.ldx & 7) && !(reinterpret_cast<uintptr_t>(p.x) & 15)) {
-                u32x4 q[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) q[c] = buf_load128(x_rsrc, row + 2 * (k0 + 32 * (c >> 1) + 8 * (c & 1)), 0);
-#pragma unroll
-                for (int e = 0; e < 32; ++e) {
-                    const uint32_t w = q[e >> 3][(e & 7) >> 1];
-                    v[e] = __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
-                }
-                whole = true;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 32; ++e) {
-                    const int k = k0 + 32 * (e >> 4) + (e & 15);
-                    gather(e, (row + 2 * k) | (k < p.N ? 0 : NONE));
-                }
-            }
+            tsvd_gather_row(p.x + (size_t)tok * p.ldx, k0, p.N, block * 128 + 128 <= p.N, v);
         } else {
 #pragma unroll
             for (int e = 0; e < 32; ++e) {
@@ -131,7 +113,7 @@ tsvd_thin_panel_kernel(thin_args p) {
                 gather(e, (2 * (k * (int)p.ldx + tok)) | (k < p.N ? 0 : NONE));
             }
         }
-        if (!whole) {
+        if constexpr (SOURCE != THIN_TOKEN_MAJOR) {
 #pragma unroll
             for (int e = 0; e < 32; ++e) v[e] = __uint_as_float((uint32_t)raw[e] << 16);
         }
@@ -287,8 +269,6 @@ tsvd_thin_panel_kernel(thin_args p) {
         words w0[TM];
         if (wave < units) next(w0);
         __syncthreads();                                      // the planes of z are complete
-        const bool vec4 = !(p.ldy & 3) && !(reinterpret_cast<uintptr_t>(p.y) & 15), aligned4 = !(p.ldy & 1) && !(reinterpret_cast<uintptr_t>(p.y) & 3);
-        const bool vec8 = vec4 && !(p.ldy & 7);
         for (int unit = wave; unit < units; unit += NW) {
             const int strip0 = unit * TM;
             f32x4 acc[TM][TN];
@@ -306,7 +286,7 @@ tsvd_thin_panel_kernel(thin_args p) {
             // (wait for the next unit's code words here, before the stores)
 #pragma unroll
             for (int a = 0; a < TM; ++a) asm volatile("" :: "v"(w0[a].x), "v"(w0[a].y));
-            if (p.token_major && p.out_bf16 && vec8 && TM >= 4 && (strip0 + TM) * 16 <= p.M) {
+            if (p.token_major && p.out_bf16 && TM >= 4 && (strip0 + TM) * 16 <= p.M) {
                 if constexpr (TM >= 4) {
 #pragma unroll
                     for (int b = 0; b < TN; ++b) {
@@ -333,10 +313,10 @@ tsvd_thin_panel_kernel(thin_args p) {
                     const int col16 = b0 + 16 * b, col = col16 + i;
                     const f32x4 v = acc[a][b];
                     if (p.token_major) {
-                        if (col < p.B) tsvd_store_token_major4(p.y, p.ldy, col, row0, p.M, v[0], v[1], v[2], v[3], p.out_bf16, vec4);
+                        if (col < p.B) tsvd_store_token_major4(p.y, p.ldy, col, row0, p.M, v[0], v[1], v[2], v[3], p.out_bf16);
                     } else if (p.out_bf16) {
-                        tsvd_store_row_pair_bf16(p.y, p.ldy, row0, p.M, col16, i, p.B, v[0], v[1], aligned4);
-                        tsvd_store_row_pair_bf16(p.y, p.ldy, row0 + 2, p.M, col16, i, p.B, v[2], v[3], aligned4);
+                        tsvd_store_row_pair_bf16(p.y, p.ldy, row0, p.M, col16, i, p.B, v[0], v[1]);
+                        tsvd_store_row_pair_bf16(p.y, p.ldy, row0 + 2, p.M, col16, i, p.B, v[2], v[3]);
                     } else if (col < p.B) {
                         float* dst = static_cast<float*>(p.y) + (size_t)row0 * p.ldy + col;
 #pragma unroll

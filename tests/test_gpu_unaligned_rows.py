@@ -1,0 +1,44 @@
+"""Rows of tokens at any element: activations are read and results written 16 bytes at a time at addresses that are no multiple of it.  Integer instances
+are exact; beside x lies NaN and beside y a mark that has to stay."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_util import to_device
+from test_gpu_planes import tsvd  # noqa: F401  (the module's fixture)
+
+pytestmark = pytest.mark.gpu
+
+# fp16 z, token panels of 64, thin panels of 16 and of 32, split tiles on their own x and on planes of it, plane path on large tiles
+ROUTES = [{"TSVD_FP6": 0, "TSVD_PANEL": 0}, {"TSVD_PANEL": 1}, {"TSVD_THIN": 1}, {"TSVD_THIN": 2}, {"TSVD_PANEL": 0, "TSVD_SPLIT_V": 10, "TSVD_SPLIT_U": 10, "TSVD_SPLIT_X": 1},
+          {"TSVD_PANEL": 0, "TSVD_SPLIT_V": 10, "TSVD_SPLIT_U": 10, "TSVD_SPLIT_X": 0}, {"TSVD_PANEL": 0, "TSVD_FP6": 1}]
+
+
+@pytest.mark.parametrize("M,N,K,B", [(64, 5, 40, 17), (66, 8, 70, 40), (131, 127, 60, 33), (129, 129, 130, 65), (257, 251, 200, 130), (67, 263, 300, 49)])
+@pytest.mark.parametrize("route", ROUTES, ids=str)
+@pytest.mark.parametrize("x_dtype,y_dtype", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "bf16"), ("f32", "f32")])
+def test_rows_at_any_element(tsvd, M, N, K, B, route, x_dtype, y_dtype):  # noqa: F811
+    import torch
+    i = workloads.make_integer_inputs(M, N, K, B, 0.5, x_dtype, seed=M + N + K + B)
+    ref = torch.from_numpy(np.ascontiguousarray(oracle.forward(i.U, i.S, i.V, i.X).T))
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    for k, v in route.items():
+        tsvd.tsvd_tuning_set(k, v)
+    x, out = to_device(i), torch.bfloat16 if y_dtype == "bf16" else torch.float32
+    for before, after in ((0, 0), (1, 0), (3, 2), (8, 8)):
+        print(f"case rows at any element {M} {N} {K} {B} {route} {x_dtype} {y_dtype} {before} {after}", flush=True)
+        wide = torch.full((B, before + N + after), float("nan"), dtype=x.dtype, device="cuda:0")
+        wide[:, before:before + N] = x.t()
+        y = torch.full((B, before + M + after), -77.0, dtype=out, device="cuda:0")
+        tsvd.tsvd_forward_io(h, wide[:, before:before + N], x_layout=tsvd.TSVD_TOKEN_MAJOR, y=y[:, before:before + M], y_dtype=tsvd.TSVD_BF16 if y_dtype == "bf16" else tsvd.TSVD_F32,
+                             y_layout=tsvd.TSVD_TOKEN_MAJOR)
+        got = y.cpu()
+        assert torch.equal(got[:, before:before + M], ref.to(out))
+        assert (got[:, :before] == -77).all() and (got[:, before + M:] == -77).all()
+        f = torch.full((M, before + B + after), -77.0, dtype=out, device="cuda:0")      # feature-major y: pairs of tokens per store
+        tsvd.tsvd_forward_ex(h, x, y=f[:, before:before + B], y_dtype=tsvd.TSVD_BF16 if y_dtype == "bf16" else tsvd.TSVD_F32)
+        got = f.cpu()
+        assert torch.equal(got[:, before:before + B], ref.to(out).t())
+        assert (got[:, :before] == -77).all() and (got[:, before + B:] == -77).all()
+    tsvd.tsvd_free(h)
