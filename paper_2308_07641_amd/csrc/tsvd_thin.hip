@@ -54,7 +54,12 @@ tsvd_thin_panel_kernel(thin_args p) {
     using words = u32x4;
     extern __shared__ __align__(16) unsigned char smem[];    // records [block][tile]: chunk blocks of x, then nub blocks of z
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
-    const int b0 = blockIdx.x * 16 * TN;
+    // workgroups go to the eight XCDs in turn; each takes a run of neighbouring panels there, so that the lines that panels share (32 or 64
+    // bytes of a feature-major row each) are fetched into one L2: 5019 x 4308 x 768 at 11841 tokens 253 -> 199 us, 256 x 954 x 1461 at
+    // 6905 38.6 -> 30.9 us.  (Rows of tokens share nothing; convolutions gain 0 to 3 % in one launch, and lose 1 to 5 % where another launch
+    // folds the result.)
+    const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, more = gridDim.x & 7;
+    const int b0 = (SOURCE == THIN_FEATURE_MAJOR ? xcd * per + min(xcd, more) + (blockIdx.x >> 3) : blockIdx.x) * 16 * TN;
     unsigned char* xrec = smem;
     unsigned char* zrec = smem + p.buffers * p.chunk * TN * FP6_REC_BYTES;
     const int* ktab = reinterpret_cast<const int*>(zrec + p.nub * TN * FP6_REC_BYTES);   // THIN_CONV: byte offset of index k in the images
