@@ -45,6 +45,7 @@ struct thin_args {
     long long ldy;
     const float* bias;
     int M, out_bf16, token_major, utm;       // utm: 16-row blocks per unit of stage U
+    int runs;                                // neighbouring panels on one XCD
 };
 
 template <int TN, int RB, int SOURCE, bool CHUNKED>
@@ -54,12 +55,10 @@ tsvd_thin_panel_kernel(thin_args p) {
     using words = u32x4;
     extern __shared__ __align__(16) unsigned char smem[];    // records [block][tile]: chunk blocks of x, then nub blocks of z
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
-    // workgroups go to the eight XCDs in turn; each takes a run of neighbouring panels there, so that the lines that panels share (32 or 64
-    // bytes of a feature-major row each) are fetched into one L2: 5019 x 4308 x 768 at 11841 tokens 253 -> 199 us, 256 x 954 x 1461 at
-    // 6905 38.6 -> 30.9 us.  (Rows of tokens share nothing; convolutions gain 0 to 3 % in one launch, and lose 1 to 5 % where another launch
-    // folds the result.)
+    // workgroups go to the eight XCDs in turn; with p.runs each XCD takes a run of neighbouring panels, so that the lines that
+    // panels share (32 or 64 bytes of a feature-major row each) are fetched into one L2
     const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, more = gridDim.x & 7;
-    const int b0 = (SOURCE == THIN_FEATURE_MAJOR ? xcd * per + min(xcd, more) + (blockIdx.x >> 3) : blockIdx.x) * 16 * TN;
+    const int b0 = (p.runs ? xcd * per + min(xcd, more) + (blockIdx.x >> 3) : blockIdx.x) * 16 * TN;
     unsigned char* xrec = smem;
     unsigned char* zrec = smem + p.buffers * p.chunk * TN * FP6_REC_BYTES;
     const int* ktab = reinterpret_cast<const int*>(zrec + p.nub * TN * FP6_REC_BYTES);   // THIN_CONV: byte offset of index k in the images
@@ -425,6 +424,11 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
     a.M = (int)hd.M;
     a.out_bf16 = g.out_bf16;
     a.token_major = g.y_token_major;
+// Feature-major rows of enough panels, unless y outweighs x: 5019 x 4308 x 768 at 11841 tokens 253 -> 199 us, 244 x 2015 x 1536 at 3621
+    // 33.9 -> 26.7, 975 x 320 x 125 at 3773 13.3 -> 10.9, 5926 x 1340 x 768 at 3019 51.4 -> 46.2 us.  With 50 panels 9.3 -> 10.0 (575 x 177 x 122), for
+    // 2304 rows on 98 27.3 -> 29.4 and 2358 on 415 38.6 -> 40.8 us (a convolution's columns, whose fold reads y next), 7635 rows on 128 26.5 -> 27.4.  Rows
+    // of tokens share nothing; gathered convolutions: 0.95 to 1.1.
+    a.runs = g.source == THIN_FEATURE_MAJOR && g.B > 64 * 16 * tiles && a.M <= 5 * a.N;
     // rows per unit of stage U: the larger units unless they leave wavefronts without one
     auto passes = [&](int utm) { return ((a.M + 16 * utm - 1) / (16 * utm) + 7) / 8 * utm; };
     a.utm = passes(8) <= passes(4) && passes(8) <= passes(2) ? 8 : passes(4) <= passes(2) ? 4 : 2;
