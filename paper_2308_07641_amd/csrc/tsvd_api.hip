@@ -79,12 +79,23 @@ tsvd_transpose_kernel(const T* __restrict__ x, long long ldx, int B, int N, T* _
 }
 
 // Feature-major activations with unaligned rows [N][ldx] -> [N][ldt] (ldt a multiple of 8 elements, the padding
-// columns zero): one thread per element, consecutive threads along a row.
+// columns zero): eight elements per thread, consecutive threads along a row; the last ones of a row are read to end at its end and shifted.
+// (An element per thread: 2 TB/s, 69 us for 4759 rows of 7406 tokens.)
 __global__ void __launch_bounds__(256)
 tsvd_realign_kernel(const uint16_t* __restrict__ x, long long ldx, int B, uint16_t* __restrict__ xt, long long ldt) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    const size_t n = blockIdx.y;
-    if (b < ldt) xt[n * ldt + b] = b < B ? x[n * ldx + b] : (uint16_t)0;
+    typedef unsigned __int128 u128;
+    typedef u128 u128_at __attribute__((aligned(2)));
+    const int b = (blockIdx.x * 256 + threadIdx.x) * 8;
+    const uint16_t* row = x + (size_t)blockIdx.y * ldx;
+    if (b >= ldt) return;
+    u128 v = 0;
+    if (B >= 8) {
+        const int first = min(b, B - 8);
+        v = *reinterpret_cast<const u128_at*>(row + first) >> (16 * (b - first));
+    } else {
+        for (int e = 0; e < B; ++e) v |= (u128)row[e] << (16 * e);
+    }
+    *reinterpret_cast<u128*>(xt + (size_t)blockIdx.y * ldt + b) = v;
 }
 
 // One-time, per-device setup (the device is current): kernel attributes, address of the static workspace.
@@ -748,7 +759,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         if (te != hipErrorNotSupported) return te == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
     }
     if (x_layout == TSVD_TOKEN_MAJOR && (plan.split || (!batched && !few && gemv_serves(h)) || (x_dtype == TSVD_BF16 && batched && !few &&
-                                                        tsvd_gemm_reads_token_major(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count)))) {
+                                                        tsvd_gemm_reads_in_place(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count)))) {
         x_in_place = 1;       // the kernels this call takes gather their operand lanes from [B][ldx] themselves
     } else if (x_layout == TSVD_TOKEN_MAJOR) {
         // one pass that rewrites x as [N][B rounded up to 8] at the front of the workspace; the rows
@@ -765,9 +776,9 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         x_dev = ws;
         ldx = ldt;
         ws = static_cast<uint8_t*>(ws) + transposed_bytes(h, B, x_dtype);
-    } else if (realign && (few || (batched && !plan.split))) {
+    } else if (realign && (few || (batched && !plan.split && !tsvd_gemm_reads_in_place(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count)))) {
         const int64_t ldt = tsvd_round_up(B, 8);
-        hipLaunchKernelGGL(tsvd_realign_kernel, dim3((unsigned)((ldt + 255) / 256), (unsigned)h->hd.N), dim3(256), 0, s,
+        hipLaunchKernelGGL(tsvd_realign_kernel, dim3((unsigned)((ldt + 2047) / 2048), (unsigned)h->hd.N), dim3(256), 0, s,
                            static_cast<const uint16_t*>(x_dev), (long long)ldx, (int)B, static_cast<uint16_t*>(ws), (long long)ldt);
         if (hipGetLastError() != hipSuccess) return TSVD_EDEVICE;
         x_dev = ws;

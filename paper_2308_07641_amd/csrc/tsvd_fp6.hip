@@ -64,15 +64,16 @@ tsvd_z_planes_kernel(const uint16_t* __restrict__ Z, long long ld, int rows_vali
     __shared__ uint32_t zt[128 * 65];                 // [index][token pair], pitch 65 words
     const int tt = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     {
-        // (ld is even and the matrix 4-byte aligned; rows and columns beyond the matrix read as zero:
-        // clamped addresses, masked afterwards)
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(Z);
+        // (pairs of columns at any address: the last odd one is read with its neighbour and shifted; rows
+        // and columns beyond the matrix are zero)
+        typedef uint32_t pair_at __attribute__((aligned(2)));
         uint32_t r[16];
 #pragma unroll
         for (int n = 0; n < 16; ++n) {                // 128 rows x 64 words = 8192 words, 16 per thread
             const int idx = n * 512 + threadIdx.x, row = blockIdx.y * 128 + (idx >> 6), col = blockIdx.x * 128 + 2 * (idx & 63);
-            uint32_t v = src[((size_t)min(row, rows_valid - 1) * ld + min(col, cols_valid - 1)) / 2];
-            if (col + 1 >= cols_valid) v &= 0xFFFFu;
+            const uint16_t* src = Z + (size_t)min(row, rows_valid - 1) * ld;
+            uint32_t v = cols_valid > 1 ? *reinterpret_cast<const pair_at*>(src + min(col, cols_valid - 2)) : (uint32_t)*src << 16;
+            if (col + 1 >= cols_valid) v >>= 16;
             r[n] = row < rows_valid && col < cols_valid ? v : 0u;
         }
 #pragma unroll
@@ -719,7 +720,7 @@ bool tsvd_gemm_use_fp6(long long Mp, long long Kp, long long Np, long long B, lo
 
 // The same for stage V (planes of x), only together with the fp6 stage U (the workspace holds both
 // sets of planes then): TSVD_FP6_V = 0 never, 1 whenever possible, default by the rule of stage U
-// applied to stage V's own sizes.  Needs x with an even row pitch at a 4-byte aligned address.
+// applied to stage V's own sizes.
 bool tsvd_gemm_use_fp6_v(long long Mp, long long Kp, long long Np, long long B, long long cus, bool aligned) {
     if (!aligned || !tsvd_gemm_use_fp6(Mp, Kp, Np, B, cus, aligned)) return false;
     const int mode = tsvd_tune("TSVD_FP6_V", -1);
@@ -731,7 +732,11 @@ bool tsvd_gemm_use_fp6_v(long long Mp, long long Kp, long long Np, long long B, 
     // has its column maxima fused in; planes, a separate column-maximum launch and 128 x 64 or 256 x 64 tiles beat
     // it for contractions of 4096 (whole call 97 -> 92 us on 16384 x 4096 x 8192 at 256 tokens, 73 -> 68 us on
     // 8192 x 4096 x 4096 at 512) but not of 3072 (64 -> 70 us on 12288 x 3072 x 6144 at 256) or 2048 (58 -> 58 us)
-    return (Np >= 2048 && (Kp / 256) * ((B + 127) / 128) >= cus) || (Np >= 4096 && (Kp / 128) * ((B + 63) / 64) >= cus);
+    // With those tiles and planes of z straight from stage V (no fp16 z, no column maxima, no pass over z) short contractions gain
+    // too: 27 calls of N 96 to 1962 0.80 to 0.99 of the time (6259 ranks x 384 at 8007 tokens 454 -> 405 us, 3403 x 96 at 6592 317 -> 294)
+    const bool tiles = (Kp / 256) * ((B + 127) / 128) >= cus;
+    if (tiles && tsvd_fp6_direct_possible(Kp, B, cus)) return true;
+    return (Np >= 2048 && tiles) || (Np >= 4096 && (Kp / 128) * ((B + 63) / 64) >= cus);
 }
 
 template <int WM, int WN>

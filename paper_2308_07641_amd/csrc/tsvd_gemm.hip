@@ -1301,9 +1301,9 @@ int tsvd_gemm_tile_shape(long long rows, long long B, long long cus, bool aligne
     return 16;
 }
 
-// Token-major x in place: the token-panel launch on fp4 x fp6, and the fp4 x fp6 stage V that needs no column maxima
-// (TSVD_TOKEN_MAJOR_COPY = 1: always copy first).
-bool tsvd_gemm_reads_token_major(long long Mp, long long Kp, long long Np, long long B, long long cus) {
+// x in place, in either layout and at any alignment: the token-panel launch on fp4 x fp6, and the fp4 x fp6 stage V that needs no
+// column maxima (TSVD_TOKEN_MAJOR_COPY = 1: always copy first).
+bool tsvd_gemm_reads_in_place(long long Mp, long long Kp, long long Np, long long B, long long cus) {
     if (tsvd_tune("TSVD_TOKEN_MAJOR_COPY", 0) != 0) return false;
     if (tsvd_stage_mask() == 7 && tsvd_gemm_use_panel(Mp, Kp, Np, B, cus, true)) return tsvd_gemm_panel_fp6();
     return tsvd_gemm_use_fp6_v(Mp, Kp, Np, B, cus, true) && tsvd_fp6_direct_possible(Kp, B, cus);
@@ -1373,8 +1373,8 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
     a1.ld = g.ldx;
     a1.kvalid = (int)hd.N;
     a1.bvalid = (int)g.B;
-    // (token-major x is read in place by the fp4 x fp6 kernels only, which need no alignment: the rules see it as aligned)
-    const bool fast1 = g.x_token_major || ((g.ldx % 8 == 0) && ((reinterpret_cast<uintptr_t>(g.x) & 15u) == 0));
+    // (token-major x is read in place by the fp4 x fp6 kernels only, which need no alignment: the rules see what those read as aligned)
+    const bool fast1 = g.x_token_major || (!g.x_f32 && tsvd_gemm_reads_in_place(hd.Mp, hd.Kp, hd.Np, g.B, g.cu_count)) || ((g.ldx % 8 == 0) && ((reinterpret_cast<uintptr_t>(g.x) & 15u) == 0));
     a1.act_bytes = (unsigned)((size_t)(g.x_token_major ? g.B : hd.N) * g.ldx * 2);
     a1.tile_bytes = (unsigned)((size_t)hd.Kp * hd.Np / 4);
     a1.S = reinterpret_cast<const float*>(g.blob + hd.off_S);
@@ -1449,9 +1449,10 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
         const dim3 pgrid((unsigned)((g.B + 63) / 64));
         const int ex = out_variant(g.bias, g.out_bf16, g.y_token_major);
         if (tsvd_gemm_panel_fp6()) {                   // fp4 codes x fp6 planes (TSVD_PANEL_FP6 = 0: the 16-bit panel kernel)
+            pa.x_bytes = (unsigned)(((hd.N - 1) * g.ldx + g.B) * 2);     // (feature-major rows, read by element)
             return tsvd_fp6_launch_panel(pa, ex, stream);
         } else if (g.x_token_major) {
-            return hipErrorInvalidValue;               // (tsvd_gemm_reads_token_major said no)
+            return hipErrorInvalidValue;               // (tsvd_gemm_reads_in_place said no)
         } else if (env_cfg("TSVD_PANEL_WAVES", 16) == 16) {   // tuning switch: 16 is about 5 % faster on MI355X
             if (ex == 3) hipLaunchKernelGGL((tsvd_panel_kernel<16, 3>), pgrid, dim3(1024), TSVD_PANEL_LDS_EX(16), stream, pa);
             else if (ex == 2) hipLaunchKernelGGL((tsvd_panel_kernel<16, 2>), pgrid, dim3(1024), TSVD_PANEL_LDS_EX(16), stream, pa);
@@ -1513,7 +1514,7 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
     // ... writing the planes of z itself where its tile allows: no fp16 z, no column maxima, no separate pass over z
     const bool direct = fp6_v && tsvd_fp6_direct_possible(hd.Kp, g.B, g.cu_count);
     const bool fuse = is_ring(cfg1) && env_cfg("TSVD_FUSEMAX", 1) != 0 && !fp6_v;
-    if (g.x_token_major && !direct) return hipErrorInvalidValue;   // (tsvd_gemm_reads_token_major said no)
+    if (g.x_token_major && !direct) return hipErrorInvalidValue;   // (tsvd_gemm_reads_in_place said no)
 
     // Profiling switch: TSVD_STAGE_MASK selects the kernels to launch (1 column maxima,
     // 2 stage V, 4 stage U; default all).  Skipped kernels leave the workspace as it is.

@@ -142,7 +142,7 @@ struct tsvd_gemm_problem {
     float bound_V;                  // |z[k][b]| <= bound_V * max_n |x[n][b]|
     const void* x;                  // device bf16 [N][ldx], or [B][ldx] with x_token_major
     long long B, ldx;
-    int x_token_major;              // only on the plane path and where tsvd_gemm_reads_token_major says so
+    int x_token_major;              // only on the plane path and where tsvd_gemm_reads_in_place says so
     int x_f32;                      // x is fp32 (six planes; always on the plane path)
     bool split;                     // the plane path, with these tiles (tsvd_batch.h)
     int split_v, split_u;
@@ -166,7 +166,7 @@ bool tsvd_gemm_use_panel(long long Mp, long long Kp, long long Np, long long B, 
 bool tsvd_gemm_panel_fp6();
 // True when a batched call reads token-major bf16 activations in place (the kernels on fp4 codes x fp6 planes gather
 // their operand lanes themselves); other calls get a feature-major copy first.
-bool tsvd_gemm_reads_token_major(long long Mp, long long Kp, long long Np, long long B, long long cus);
+bool tsvd_gemm_reads_in_place(long long Mp, long long Kp, long long Np, long long B, long long cus);
 // Stage U through fp6 planes of Z: whether a call takes it, and the extra workspace it needs after Z.
 bool tsvd_gemm_use_fp6(long long Mp, long long Kp, long long Np, long long B, long long cus, bool aligned);
 size_t tsvd_gemm_fp6_bytes(long long Kp, long long Bp);

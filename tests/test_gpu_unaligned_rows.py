@@ -1,4 +1,4 @@
-"""Rows of tokens at any element: activations are read and results written 16 bytes at a time at addresses that are no multiple of it.  Integer instances
+"""Rows of tokens, and of features, at any element: activations are read and results written 16 bytes at a time at addresses that are no multiple of it.  Integer instances
 are exact; beside x lies NaN and beside y a mark that has to stay."""
 import numpy as np
 import pytest
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 # fp16 z, token panels of 64, thin panels of 16 and of 32, split tiles on their own x and on planes of it, plane path on large tiles
 ROUTES = [{"TSVD_FP6": 0, "TSVD_PANEL": 0}, {"TSVD_PANEL": 1}, {"TSVD_THIN": 1}, {"TSVD_THIN": 2}, {"TSVD_PANEL": 0, "TSVD_SPLIT_V": 10, "TSVD_SPLIT_U": 10, "TSVD_SPLIT_X": 1},
-          {"TSVD_PANEL": 0, "TSVD_SPLIT_V": 10, "TSVD_SPLIT_U": 10, "TSVD_SPLIT_X": 0}, {"TSVD_PANEL": 0, "TSVD_FP6": 1}]
+          {"TSVD_PANEL": 0, "TSVD_SPLIT_V": 10, "TSVD_SPLIT_U": 10, "TSVD_SPLIT_X": 0}, {"TSVD_PANEL": 0, "TSVD_FP6": 1},
+          {"TSVD_PANEL": 0, "TSVD_FP6": 1, "TSVD_FP6_V": 1, "TSVD_GEMM_CFG_V": 3, "TSVD_FP6_TALL": 0}]      # (the last: planes of z from stage V)
 
 
 @pytest.mark.parametrize("M,N,K,B", [(64, 5, 40, 17), (66, 8, 70, 40), (131, 127, 60, 33), (129, 129, 130, 65), (257, 251, 200, 130), (67, 263, 300, 49)])
@@ -36,8 +37,10 @@ def test_rows_at_any_element(tsvd, M, N, K, B, route, x_dtype, y_dtype):  # noqa
         got = y.cpu()
         assert torch.equal(got[:, before:before + M], ref.to(out))
         assert (got[:, :before] == -77).all() and (got[:, before + M:] == -77).all()
+        xf = torch.full((N, before + B + after), float("nan"), dtype=x.dtype, device="cuda:0")
+        xf[:, before:before + B] = x
         f = torch.full((M, before + B + after), -77.0, dtype=out, device="cuda:0")      # feature-major y: pairs of tokens per store
-        tsvd.tsvd_forward_ex(h, x, y=f[:, before:before + B], y_dtype=tsvd.TSVD_BF16 if y_dtype == "bf16" else tsvd.TSVD_F32)
+        tsvd.tsvd_forward_ex(h, xf[:, before:before + B], y=f[:, before:before + B], y_dtype=tsvd.TSVD_BF16 if y_dtype == "bf16" else tsvd.TSVD_F32)
         got = f.cpu()
         assert torch.equal(got[:, before:before + B], ref.to(out).t())
         assert (got[:, :before] == -77).all() and (got[:, before + B:] == -77).all()
