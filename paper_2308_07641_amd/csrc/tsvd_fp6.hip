@@ -572,30 +572,38 @@ tsvd_panel_fp6_kernel(panel_args p) {
                 int c0 = b0 + tile0 * 16;                     // first token of the unit
                 asm volatile("" : "+s"(c0));                  // (addresses are formed here, not kept in registers over the MFMAs)
                 if constexpr (EX == 3) {
+                    if (p.out_bf16 && strip0 * 16 + 128 <= p.M) {       // sixteen rows of a token per lane
+#pragma unroll
+                        for (int a = 0; a < TM; a += 4)
+#pragma unroll
+                            for (int b = 0; b < UTN; ++b) {
+                                uint32_t d[4][2];
+#pragma unroll
+                                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                                    for (int h = 0; h < 2; ++h)
+                                        d[k][h] = tsvd_pack_bf16(acc[a + k][b][2 * h] + br[a + k][2 * h], acc[a + k][b][2 * h + 1] + br[a + k][2 * h + 1]);
+                                const int col = c0 + b * 16 + i;
+                                tsvd_store_token_major_bf16_4x16(p.y, p.ldy, col, col < p.B, (strip0 + a) * 16, g, d);
+                            }
+                        continue;
+                    }
                     const bool vec_ok = !(p.ldy & 3) && !(reinterpret_cast<uintptr_t>(p.y) & 15);
-                    if (vec_ok && c0 + UTN * 16 <= p.B && strip0 * 16 + 128 <= p.M && p.ldy < (1ll << 22)) {
-                        // every token and row of the unit exists: the lane's four rows of a token as one 16-byte (fp32) or
-                        // 8-byte (bf16) store at a per-lane constant offset plus a scalar
-                        const int esz = p.out_bf16 ? 2 : 4;
-                        const size_t left = ((size_t)(p.B - c0) * p.ldy - strip0 * 16) * esz;
+                    if (vec_ok && !p.out_bf16 && c0 + UTN * 16 <= p.B && strip0 * 16 + 128 <= p.M && p.ldy < (1ll << 22)) {
+                        // every token and row of the unit exists: the lane's four rows of a token as one 16-byte store at a
+                        // per-lane constant offset plus a scalar
+                        const size_t left = ((size_t)(p.B - c0) * p.ldy - strip0 * 16) * 4;
                         const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                            static_cast<unsigned char*>(p.y) + ((size_t)c0 * p.ldy + strip0 * 16) * esz, 0,
-                            (int)(left < 0xFFFFFFFFull ? left : 0xFFFFFFFFull), 0x00020000);
-                        const int y_voff = (i * (int)p.ldy + 4 * g) * esz;
+                            static_cast<float*>(p.y) + (size_t)c0 * p.ldy + strip0 * 16, 0, (int)(left < 0xFFFFFFFFull ? left : 0xFFFFFFFFull), 0x00020000);
+                        const int y_voff = (i * (int)p.ldy + 4 * g) * 4;
 #pragma unroll
                         for (int a = 0; a < TM; ++a)
 #pragma unroll
-                            for (int b = 0; b < UTN; ++b) {
-                                const float v0 = acc[a][b][0] + br[a][0], v1 = acc[a][b][1] + br[a][1], v2 = acc[a][b][2] + br[a][2],
-                                            v3 = acc[a][b][3] + br[a][3];
-                                if (p.out_bf16)
-                                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{(uint32_t)tsvd_bf16_rne(v0) | ((uint32_t)tsvd_bf16_rne(v1) << 16),
-                                                                                (uint32_t)tsvd_bf16_rne(v2) | ((uint32_t)tsvd_bf16_rne(v3) << 16)},
-                                                                          y_rsrc, y_voff + a * 16 * 2, b * 16 * (int)p.ldy * 2, 0);
-                                else
-                                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v0), __float_as_uint(v1), __float_as_uint(v2), __float_as_uint(v3)},
-                                                                           y_rsrc, y_voff + a * 16 * 4, b * 16 * (int)p.ldy * 4, 0);
-                            }
+                            for (int b = 0; b < UTN; ++b)
+                                __builtin_amdgcn_raw_buffer_store_b128(
+                                    u32x4{__float_as_uint(acc[a][b][0] + br[a][0]), __float_as_uint(acc[a][b][1] + br[a][1]),
+                                          __float_as_uint(acc[a][b][2] + br[a][2]), __float_as_uint(acc[a][b][3] + br[a][3])},
+                                    y_rsrc, y_voff + a * 16 * 4, b * 16 * (int)p.ldy * 4, 0);
                         continue;
                     }
 #pragma unroll

@@ -139,7 +139,26 @@ __device__ __forceinline__ void gemm_epilogue(const gemm_args& p, f32x4 (&acc)[T
                 for (int v = 0; v < 4; ++v) sr[a][v] = 0.f;
         }
     }
-    if constexpr (STAGE2 && EX == 3) {        // token-major output (fp32 or bf16, with or without bias): four rows per store
+    if constexpr (STAGE2 && EX == 3) {        // token-major output (fp32 or bf16, with or without bias): four rows per store, or sixteen
+        if constexpr (TM % 4 == 0) {
+            if (p.out_bf16 && (strip0 + TM) * 16 <= p.rows_valid) {
+#pragma unroll
+                for (int a = 0; a < TM; a += 4) {
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) {
+                        const int col = col0 + b * 16 + i;
+                        uint32_t d[4][2];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h)
+                                d[k][h] = tsvd_pack_bf16(acc[a + k][b][2 * h] * cs[b] + sr[a + k][2 * h], acc[a + k][b][2 * h + 1] * cs[b] + sr[a + k][2 * h + 1]);
+                        tsvd_store_token_major_bf16_4x16(p.out, p.ld_out, col, col < p.bvalid, (strip0 + a) * 16, g, d);
+                    }
+                }
+                return;
+            }
+        }
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
 #pragma unroll
