@@ -36,19 +36,19 @@ double planes_cost(const sizes& s, int v) {
 }
 struct split_factors {
     int shape;
-    double v0, v_round, v_step, v_x, v_gather, u0, u_round, u_step;
+    double v0, v_round, v_step, v_x, u0, u_round, u_step;
 };
 constexpr split_factors split_table[] = {
-    {9, 1.3, 2.1, 2.9, 2.2, 2.3, 0.7, 1.3, 3.0},
-    {10, 0.3, 4.4, 1.9, 2.2, 2.5, 0.4, 2.5, 2.1},
-    {18, 0.0, 4.1, 3.0, 2.4, 2.6, 0.3, 2.8, 3.4},
-    {20, 0.0, 5.7, 2.3, 2.4, 2.4, 0.0, 5.8, 2.4},
+    {9, 1.3, 2.1, 2.9, 2.2, 0.7, 1.3, 3.0},
+    {10, 0.3, 4.4, 1.9, 2.2, 0.4, 2.5, 2.1},
+    {18, 0.0, 4.1, 3.0, 2.4, 0.3, 2.8, 3.4},
+    {20, 0.0, 5.7, 2.3, 2.4, 0.0, 5.8, 2.4},
 };
 // rounds of workgroups and loop steps (16 records each) of a stage
 double rounds(const sizes& s, int shape, long long row_blocks) { return (double)up(up(row_blocks, shape >> 3) * up(s.B, 16 * (shape & 7)), s.cus); }
 double steps(int shape, long long blocks) { return (double)up(blocks, 16 / (shape & 7)); }
 
-double split_v_cost(const sizes& s, const split_factors* f, bool gathered_x) {
+double split_v_cost(const sizes& s, const split_factors* f) {
     if (!f) {       // 256 x 128 or 512 x 64 tiles, two workgroups per compute unit
         const bool small = up(s.nub, 2) * up(s.B, 128) < s.cus;
         const double w = (double)(s.nub % 4 || small ? up(s.nub, 2) * up(s.B, 128) : up(s.nub, 4) * up(s.B, 64));
@@ -56,8 +56,8 @@ double split_v_cost(const sizes& s, const split_factors* f, bool gathered_x) {
         return planes_cost(s, 0) + r * fill * (12.5 + 2.4 * (double)(s.sets * s.nvb));
     }
     const double r = rounds(s, f->shape, s.nub), x = planes_cost(s, f->shape);
-    // records of x per wavefront where the stage makes them; more where the elements of a record are gathered one by one
-    const double made = x > 0 ? 0 : r * (double)(up(s.nvb * (f->shape & 7), 8) * s.sets) * (f->v_x + (gathered_x ? f->v_gather : 0));
+    // records of x per wavefront where the stage makes them
+    const double made = x > 0 ? 0 : r * (double)(up(s.nvb * (f->shape & 7), 8) * s.sets) * f->v_x;
     return x + f->v0 + r * f->v_round + r * steps(f->shape, s.sets * s.nvb) * f->v_step + made;
 }
 double split_u_cost(const sizes& s, const split_factors* f) {
@@ -86,17 +86,30 @@ double thin_cost(const tsvd_batch_call& c, int tiles) {
         if (u * utm < passes) passes = u * utm, units = u;
     }
     const double Kp = (double)tsvd_round_up(c.K, 256), mb_u = Kp * (double)tsvd_round_up(c.M, 256) / 4e6, mb_v = Kp * (double)tsvd_round_up(c.N, 256) / 4e6;
-    const double records = r * (double)up(nvb * tiles, 8), gather = c.conv ? 1 : 0, scalar = c.x_token_major && c.N % 8 ? 1 : 0;
-    const double v = r * (double)(up(nub, 8) * nvb), u = r * (double)(passes * nub) / 8, y = r * (double)passes * (c.out_bf16 ? 0.5 : 1) * (c.y_token_major ? 2.6 : 1);
-    if (tiles == 1) return 1.2 + 3.2 * r + records * (1.5 * scalar + 1.6 * gather) + 0.57 * v + 0.29 * u + 0.35 * r * (double)units + 11.2 * r * mb_u + 8.1 * busy * r * (mb_u + mb_v) + 0.08 * y;
-    return 1.4 + 3.7 * r + records * (2.1 * scalar + 0.92 * gather) + 0.92 * v + 0.45 * u + 0.34 * r * (double)units + 25.1 * r * mb_u + 13.3 * busy * r * (mb_u + mb_v) + 0.10 * y;
+    if (c.x_token_major) {      // (a pass of stage U takes its blocks of K, or its part of y: the stores of all panels share the memory)
+        auto total = [&](double t, double round, double record, double v1, double block, double store, double pass, double unit, double code) {
+            return t + r * (round + (double)up(nvb * tiles, 8) * record + v1 * (double)(up(nub, 8) * nvb) + unit * (double)units + code * busy * (mb_u + mb_v) +
+                            (double)passes * std::max(block * (double)nub, store * busy * (c.out_bf16 ? 0.5 : 1) + pass));
+        };
+        return tiles == 1 ? total(2.2, 2.07, 0.60, 0.473, 0.085, 0.096, 0.195, 0.483, 4.28) : total(3.0, 1.54, 0.66, 0.84, 0.165, 0.196, 0.386, 0.45, 11.6);
+    }
+    const double gather = c.conv ? r * (double)up(nvb * tiles, 8) : 0, v = r * (double)(up(nub, 8) * nvb), u = r * (double)(passes * nub) / 8,
+                 y = r * (double)passes * (c.out_bf16 ? 0.5 : 1) * (c.y_token_major ? 2.6 : 1);
+    if (tiles == 1) return 1.2 + 3.2 * r + 1.6 * gather + 0.57 * v + 0.29 * u + 0.35 * r * (double)units + 11.2 * r * mb_u + 8.1 * busy * r * (mb_u + mb_v) + 0.08 * y;
+    return 1.4 + 3.7 * r + 0.92 * gather + 0.92 * v + 0.45 * u + 0.34 * r * (double)units + 25.1 * r * mb_u + 13.3 * busy * r * (mb_u + mb_v) + 0.10 * y;
+}
+
+// A copy of x for the kernels that read aligned feature-major rows: a transposition, or rows moved to aligned ones.
+double copy_cost(const tsvd_batch_call& c) {
+    const double m = (double)c.N * (double)c.B / 1e6;
+    return c.copies ? 3.3 + 1.9 * m : 0;
 }
 
 // ---- ring and large-tile kernels ----------------------------------------------------------------
 double older_cost(const tsvd_batch_call& c) {
     double t = 7.3;
     if (c.conv) t += 6.0 + 1.3 * (double)c.N * (double)c.B / 1e6;               // columns written first
-    else if (c.copies) t += 3.3 + 1.9 * (double)c.N * (double)c.B / 1e6;
+    else t += copy_cost(c);
     auto stage = [&](long long rows, long long rows_p, long long blocks, double ring64, double ring128_0, double ring128, double large_0, double large) {
         const int shape = tsvd_gemm_tile_shape(rows_p, c.B, c.cus, true);
         const long long tr = shape < 2 ? 256 : shape == 15 ? 128 : shape == 17 ? 96 : 64, tt = shape == 0 ? 256 : shape == 1 ? 128 : 64;
@@ -108,11 +121,12 @@ double older_cost(const tsvd_batch_call& c) {
     return t;
 }
 
-// 64-token panels, for the calls that their rule gives them (179 such calls measured)
+// 64-token panels, for the calls that their rule gives them (288 such calls measured)
 double panel_cost(const tsvd_batch_call& c) {
     const long long nvb = up(c.N, 128), nub = up(c.K, 128), strips = up(c.M, 128);
     const double r = (double)up(up(c.B, 64), c.cus);
-    return r * (7.5 + (double)nvb * (c.x_token_major && c.N % 8 ? 5.6 : 2.3) + 1.8 * (double)(up(strips, 8) * nub) + (double)strips * (c.y_token_major ? 1.9 : 0.83));
+    if (c.x_token_major) return r * (6.3 + 2.2 * (double)nvb + 1.3 * (double)(up(strips, 8) * nub) + (double)strips * (c.y_token_major ? 0.95 : 0.61));
+    return 0.95 * r * (7.5 + 2.3 * (double)nvb + 1.8 * (double)(up(strips, 8) * nub) + (double)strips * (c.y_token_major ? 1.9 : 0.83));
 }
 
 }  // namespace
@@ -134,12 +148,11 @@ tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
     }
     const long long Mp = tsvd_round_up(c.M, 256), Kp = tsvd_round_up(c.K, 256), Np = tsvd_round_up(c.N, 256);
     const sizes s = {c.M, c.N, c.B, c.cus, up(c.N, 128), up(c.K, 128), c.f32 ? 2 : 1};
-    const bool gathered_x = c.x_token_major && c.N % 8 != 0;
-    double best_v = split_v_cost(s, nullptr, false), best_u = split_u_cost(s, nullptr);
+    double best_v = split_v_cost(s, nullptr), best_u = split_u_cost(s, nullptr);
     const double fp6_tiles = best_v + best_u;
     int v = 0, u = 0;
     for (const split_factors& f : split_table) {
-        const double cv = split_v_cost(s, &f, gathered_x), cu = split_u_cost(s, &f);
+        const double cv = split_v_cost(s, &f), cu = split_u_cost(s, &f);
         if (cv < best_v) best_v = cv, v = f.shape;
         if (cu < best_u) best_u = cu, u = f.shape;
     }
@@ -148,12 +161,16 @@ tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
         plan.split_u = u;
         return plan;
     }
-    // Another way replaces the older one only where its estimate is a tenth smaller: the estimates' own error.  (Where an older call runs
-    // on planes too, its estimate is that of the same tiles.)
+    // Another way replaces the older one only where its estimate is a tenth smaller, the estimates' own error (a twentieth for rows of tokens: on 150
+    // such calls of 513 to 16384 tokens that the factors are not fitted to, 0.97 of the time of the choices made by the factors from before
+    // rows were read and written at any alignment; feature-major calls gain nothing by a new fit).  Where an older call runs on planes of x
+    // too, its estimate is that of the same tiles; where stage V is on 16-bit operands it has a pass over z, and x copied.
     const double columns = c.conv ? 6.0 + 1.3 * (double)c.N * (double)c.B / 1e6 : 0;
     const bool panel = c.whole && tsvd_gemm_use_panel(Mp, Kp, Np, c.B, c.cus, true);
-    double best = (c.conv ? 1.0 : panel ? 0.95 : 0.9) *
-                  (panel ? panel_cost(c) + columns : tsvd_gemm_use_fp6(Mp, Kp, Np, c.B, c.cus, true) ? fp6_tiles + columns : older_cost(c));
+    double best = (c.conv || panel ? 1.0 : c.x_token_major ? 0.95 : 0.9) *
+                  (panel ? panel_cost(c) + columns
+                   : !tsvd_gemm_use_fp6(Mp, Kp, Np, c.B, c.cus, true) ? older_cost(c)
+                   : c.x_token_major && !tsvd_gemm_reads_in_place(Mp, Kp, Np, c.B, c.cus) ? 1.15 * fp6_tiles + copy_cost(c) : fp6_tiles + columns);
     const bool fits = !panel && tsvd_gemm_split_bytes(c.K, c.N, c.B, false) < (1ull << 31);
     if (fits && (v || u) && best_v + best_u + columns < best) {
         best = best_v + best_u + columns;
