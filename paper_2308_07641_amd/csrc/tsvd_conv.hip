@@ -41,6 +41,7 @@ struct conv_plan {
     long long rows_v, rows_u;      // N and M of the packed matrix
     long long Bv, Bo;              // columns of the linear map, output positions (all images)
     long long ldx;                 // row stride of the gathered columns (multiple of 8)
+    long long ldt;                 // row stride of the map's result where U has taps: whole lines of 128 bytes
     bool fits;                     // within the index limits of the gather / map / tap-sum path
 };
 
@@ -67,6 +68,7 @@ bool make_plan(const tsvd_conv_geometry& g, int64_t images, int64_t H, int64_t W
     p->Bv = images * (long long)p->Hv * p->Wv;
     p->Bo = images * ho * wo;
     p->ldx = (p->Bv + 7) / 8 * 8;
+    p->ldt = (p->Bv + 31) / 32 * 32;
     // (grid.y carries the rows of the gather and the output channels of the tap sum)
     p->fits = p->Bv < (1LL << 24) && p->Bo < (1LL << 31) && images * H * W < (1LL << 31) && p->rows_v <= 65535 && g.c_out <= 65535;
     return true;
@@ -110,24 +112,38 @@ tsvd_unfold_kernel(const uint16_t* __restrict__ x, int images, int H, int W, int
 
 // Taps of U: y[co][img][oy][ox] = bias[co] + sum_{du1, du2} T[(co, du1, du2)][img][ty][tx] with
 // ty = oy stride1 + du1 dil1 - pad1 where U handles dimension 1, else ty = oy; tx likewise; taps
-// outside the positions V produced contribute nothing (zero padding).
+// outside the positions V produced contribute nothing (zero padding).  A thread per output; the loads of G taps (a divisor of
+// their number where 3, 5 or 9 is one) go out together; a tap outside reads the row's first element, which is not added.
+// (One after the other, behind a branch each: 384 -> 384 channels 5 x 5 rank 77, an image of 7 x 7, whole call 23.8 -> 15.1 us; 288 -> 390 3 x 3 rank 128, 3 of
+// 56 x 56, 77 -> 64.)
+template <int G>
 __global__ void __launch_bounds__(256)
 tsvd_fold_kernel(const float* __restrict__ T, long long ldt, int images, int Hv, int Wv, int ku1, int ku2, int Ho, int Wo, int s1,
                  int s2, int p1, int p2, int d1, int d2, int u_dim1, int u_dim2, const float* __restrict__ bias, void* __restrict__ y,
                  long long Bo, int out_bf16) {
-    const long long col = (long long)blockIdx.x * 256 + threadIdx.x;
+    const unsigned col = blockIdx.x * 256 + threadIdx.x;          // (below 2^31)
     if (col >= Bo) return;
-    const int co = blockIdx.y;
-    const int ox = (int)(col % Wo), oy = (int)((col / Wo) % Ho), img = (int)(col / ((long long)Wo * Ho));
+    const int co = blockIdx.y, taps = ku1 * ku2;
+    const unsigned line = col / (unsigned)Wo, image = line / (unsigned)Ho;
+    const int ox = (int)(col - line * Wo), oy = (int)(line - image * Ho);
+    const int ty0 = u_dim1 ? oy * s1 - p1 : oy, tx0 = u_dim2 ? ox * s2 - p2 : ox;
+    const int at = ((int)image * Hv + ty0) * Wv + tx0;            // (positions of V: below 2^24)
     float acc = bias ? bias[co] : 0.f;
-    for (int a = 0; a < ku1; ++a) {
-        const int ty = u_dim1 ? oy * s1 + a * d1 - p1 : oy;
-        if (ty < 0 || ty >= Hv) continue;
-        for (int b = 0; b < ku2; ++b) {
-            const int tx = u_dim2 ? ox * s2 + b * d2 - p2 : ox;
-            if (tx < 0 || tx >= Wv) continue;
-            acc += T[(size_t)((co * ku1 + a) * ku2 + b) * ldt + ((size_t)img * Hv + ty) * Wv + tx];
+    const float* row = T + (size_t)co * taps * ldt;
+    int a = 0, b = 0;
+    for (int t0 = 0; t0 < taps; t0 += G) {
+        float v[G];
+        bool in[G];
+#pragma unroll
+        for (int e = 0; e < G; ++e) {
+            const int dy = a * d1, dx = b * d2;
+            in[e] = t0 + e < taps && (unsigned)(ty0 + dy) < (unsigned)Hv && (unsigned)(tx0 + dx) < (unsigned)Wv;
+            v[e] = row[in[e] ? at + dy * Wv + dx : 0];
+            if (t0 + e + 1 < taps) row += ldt;
+            if (++b == ku2) b = 0, ++a;
         }
+#pragma unroll
+        for (int e = 0; e < G; ++e) acc = in[e] ? acc + v[e] : acc;
     }
     tsvd_store_y(y, (size_t)co * Bo + col, acc, out_bf16);
 }
@@ -438,7 +454,7 @@ extern "C" size_t tsvd_conv2d_workspace_bytes(const tsvd_handle* h, const tsvd_c
     }
     if (!p.fits || !shapes_match(h, p)) return 0;
     const size_t cols = g->form == 1 ? 0 : round256((size_t)p.rows_v * p.ldx * 2);
-    const size_t taps = g->form == 0 ? 0 : round256((size_t)p.rows_u * p.Bv * 4);
+    const size_t taps = g->form == 0 ? 0 : round256((size_t)p.rows_u * p.ldt * 4);
     return cols + taps + tsvd_workspace_bytes_ex(h, p.Bv, TSVD_BF16, TSVD_FEATURE_MAJOR);
 }
 
@@ -510,7 +526,7 @@ extern "C" tsvd_status tsvd_conv2d_forward(const tsvd_handle* h, const tsvd_conv
         t.s1 = p.v_dim1 ? g->stride1 : 1; t.p1 = p.v_dim1 ? g->pad1 : 0; t.d1 = g->dil1;
         t.s2 = p.v_dim2 ? g->stride2 : 1; t.p2 = p.v_dim2 ? g->pad2 : 0; t.d2 = g->dil2;
         t.y = taps ? static_cast<void*>(ws + (g->form == 1 ? 0 : round256((size_t)p.rows_v * p.ldx * 2))) : y_dev;
-        t.ldy = p.Bv;
+        t.ldy = taps ? p.ldt : p.Bv;
         t.bias = taps ? nullptr : bias_dev;
         t.out_bf16 = !taps && y_dtype == TSVD_BF16;
         const hipError_t e = tsvd_thin_launch(t, thin, s);
@@ -533,15 +549,19 @@ extern "C" tsvd_status tsvd_conv2d_forward(const tsvd_handle* h, const tsvd_conv
     float* T = nullptr;
     if (taps) {
         T = reinterpret_cast<float*>(ws);
-        ws += round256((size_t)p.rows_u * p.Bv * 4);
+        ws += round256((size_t)p.rows_u * p.ldt * 4);
     }
     const size_t map_ws = tsvd_workspace_bytes_ex(h, p.Bv, TSVD_BF16, TSVD_FEATURE_MAJOR);
     // U is 1 x 1: the map writes the result itself, bias and output type fused
-    tsvd_status st = mapped ? TSVD_OK : taps ? tsvd_forward_ex(h, X, TSVD_BF16, TSVD_FEATURE_MAJOR, p.Bv, ldx, nullptr, T, TSVD_F32, p.Bv, ws, map_ws, s)
+    tsvd_status st = mapped ? TSVD_OK : taps ? tsvd_forward_ex(h, X, TSVD_BF16, TSVD_FEATURE_MAJOR, p.Bv, ldx, nullptr, T, TSVD_F32, p.ldt, ws, map_ws, s)
                           : tsvd_forward_ex(h, X, TSVD_BF16, TSVD_FEATURE_MAJOR, p.Bv, ldx, bias_dev, y_dev, y_dtype, p.Bv, ws, map_ws, s);
     if (st != TSVD_OK || !taps) return st;
-    hipLaunchKernelGGL(tsvd_fold_kernel, dim3((unsigned)((p.Bo + 255) / 256), (unsigned)g->c_out), dim3(256), 0, s, T, p.Bv, (int)images,
-                       p.Hv, p.Wv, p.ku1, p.ku2, p.Ho, p.Wo, g->stride1, g->stride2, g->pad1, g->pad2, g->dil1, g->dil2,
-                       (int)!p.v_dim1, (int)!p.v_dim2, bias_dev, y_dev, p.Bo, (int)(y_dtype == TSVD_BF16));
+    const int ku = p.ku1 * p.ku2;
+    auto fold = [&](auto k) {
+        hipLaunchKernelGGL(k, dim3((unsigned)((p.Bo + 255) / 256), (unsigned)g->c_out), dim3(256), 0, s, T, p.ldt, (int)images,
+                           p.Hv, p.Wv, p.ku1, p.ku2, p.Ho, p.Wo, g->stride1, g->stride2, g->pad1, g->pad2, g->dil1, g->dil2,
+                           (int)!p.v_dim1, (int)!p.v_dim2, bias_dev, y_dev, p.Bo, (int)(y_dtype == TSVD_BF16));
+    };
+    ku % 9 == 0 ? fold(tsvd_fold_kernel<9>) : ku % 5 == 0 ? fold(tsvd_fold_kernel<5>) : ku % 3 == 0 ? fold(tsvd_fold_kernel<3>) : fold(tsvd_fold_kernel<4>);
     return hipGetLastError() == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
 }
