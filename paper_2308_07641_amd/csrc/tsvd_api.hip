@@ -499,7 +499,8 @@ size_t gemm_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
         bytes += round256(tsvd_gemm_fp6_bytes(h->hd.Kp, Bp)) + round256(tsvd_gemm_fp6_bytes(h->hd.Np, Bp));
     // (asked as for the call that favours planes most)
     if (use_gemm(h, B, x_dtype)) {
-        if (batch_plan(h, B, x_dtype, false, true, false, false, true, false).split) bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
+        for (const bool tokens : {false, true})      // (either layout of x: their margins differ)
+            if (batch_plan(h, B, x_dtype, tokens, true, false, false, true, false).split) bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
         // (likewise: token-major y costs the panels more)
         if (batch_plan(h, B, x_dtype, true, true, true, true, true, true).few) bytes = std::max(bytes, tsvd_few_bytes(h->hd.Kp, B, 3));
     }
@@ -734,6 +735,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
     if (batched && !few)
         plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16, !misaligned,
                           tsvd_few_fits(h->hd, B, ldx, x_layout == TSVD_TOKEN_MAJOR) && tsvd_few_bytes(h->hd.Kp, B, 3) <= need);
+    if (plan.split && x_dtype == TSVD_BF16 && tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false) > need) plan.split = false;   // (never more than was asked for)
     if (z_planes || plan.few) {
         // few tokens: x in any layout and alignment, planes of z in the workspace
         const tsvd_few_problem f = {h->blob, &h->hd, static_cast<const uint16_t*>(x_dev), B, B == 1 && ldx == 1 ? h->hd.N : ldx, x_layout == TSVD_TOKEN_MAJOR || (B == 1 && ldx == 1), y_dev, ldy,

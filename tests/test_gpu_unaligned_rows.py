@@ -45,3 +45,20 @@ def test_rows_at_any_element(tsvd, M, N, K, B, route, x_dtype, y_dtype):  # noqa
         assert torch.equal(got[:, before:before + B], ref.to(out).t())
         assert (got[:, :before] == -77).all() and (got[:, before + B:] == -77).all()
     tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("M,N,K,B", [(805, 144, 1604, 866), (1572, 113, 2093, 900), (2216, 122, 832, 697), (1466, 250, 2301, 216), (1241, 315, 733, 419)])
+def test_workspace_of_rows_of_tokens_is_enough(tsvd, M, N, K, B):  # noqa: F811
+    """Calls that take the split tiles for rows of tokens only: nothing is written beyond the workspace that was asked for."""
+    import torch
+    i = workloads.make_integer_inputs(M, N, K, B, 0.5, "bf16", seed=M + B)
+    ref = torch.from_numpy(np.ascontiguousarray(oracle.forward(i.U, i.S, i.V, i.X).T))
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    x = to_device(i).t().contiguous()
+    need = tsvd.tsvd_workspace_bytes_ex(h, B, tsvd.TSVD_BF16, tsvd.TSVD_TOKEN_MAJOR)
+    ws = torch.full((need + (32 << 20),), 93, dtype=torch.uint8, device="cuda:0")
+    print(f"case workspace {M} {N} {K} {B} {need}", flush=True)
+    y = tsvd.tsvd_forward_io(h, x, x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR, workspace=ws[:need])
+    assert (ws[need:] == 93).all()
+    assert torch.equal(y.cpu(), ref)
+    tsvd.tsvd_free(h)
