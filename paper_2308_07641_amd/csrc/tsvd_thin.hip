@@ -31,25 +31,24 @@
 
 namespace {
 
-struct thin_args {       // (arguments are fetched by lines of 64 bytes, each a trip to memory: what every panel needs lies in the first two)
+struct thin_args {
     const uint32_t *tiles_v, *tiles_u;
     unsigned tile_v_bytes, tile_u_bytes;
-    int runs;                                // panels, where neighbouring ones go to one XCD; else 0
-    int nvb, nub, chunk, buffers;            // 128-index blocks of N and K that hold anything; blocks of x per chunk, chunks in LDS (1: all of x, or 2)
-    unsigned x_bytes;                        // below 2^31
+    int nkt_v, nkt_u, nvb, nub;              // tiles of 256 per strip; 128-index blocks of N and K that hold anything
     const uint16_t* x;
-    int N, B;
+    unsigned x_bytes;                        // below 2^31
+    int N, B, chunk, buffers;        // blocks of x per chunk, chunks in LDS (1: all of x, or 2)
     long long ldx;
+    int images, H, W, kv1, kv2, Hv, Wv, s1, s2, p1, p2, d1, d2;
     const float* S;
     void* y;
     long long ldy;
     const float* bias;
-    int nkt_v, nkt_u;                        // tiles of 256 per strip
-    int M, out_bf16, utm;                    // utm: 16-row blocks per unit of stage U
-    int images, H, W, kv1, kv2, Hv, Wv, s1, s2, p1, p2, d1, d2;
+    int M, out_bf16, token_major, utm;       // utm: 16-row blocks per unit of stage U
+    int runs;                                // neighbouring panels on one XCD
 };
 
-template <int TN, int RB, int SOURCE, bool CHUNKED, bool ROWS>      // ROWS: y is [tokens][ldy]
+template <int TN, int RB, int SOURCE, bool CHUNKED>
 __global__ void __launch_bounds__(512, 2)
 tsvd_thin_panel_kernel(thin_args p) {
     constexpr int NW = 8;
@@ -58,8 +57,8 @@ tsvd_thin_panel_kernel(thin_args p) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
     // workgroups go to the eight XCDs in turn; with p.runs each XCD takes a run of neighbouring panels, so that the lines that
     // panels share (32 or 64 bytes of a feature-major row each) are fetched into one L2
-    const int xcd = blockIdx.x & 7, per = p.runs >> 3, more = p.runs & 7;
-    const int b0 = (SOURCE == THIN_FEATURE_MAJOR && p.runs ? xcd * per + min(xcd, more) + (blockIdx.x >> 3) : blockIdx.x) * 16 * TN;
+    const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, more = gridDim.x & 7;
+    const int b0 = (p.runs ? xcd * per + min(xcd, more) + (blockIdx.x >> 3) : blockIdx.x) * 16 * TN;
     unsigned char* xrec = smem;
     unsigned char* zrec = smem + p.buffers * p.chunk * TN * FP6_REC_BYTES;
     const int* ktab = reinterpret_cast<const int*>(zrec + p.nub * TN * FP6_REC_BYTES);   // THIN_CONV: byte offset of index k in the images
@@ -291,8 +290,8 @@ tsvd_thin_panel_kernel(thin_args p) {
             // (wait for the next unit's code words here, before the stores)
 #pragma unroll
             for (int a = 0; a < TM; ++a) asm volatile("" :: "v"(w0[a].x), "v"(w0[a].y));
-            if (ROWS && p.out_bf16 && TM >= 4 && (strip0 + TM) * 16 <= p.M) {
-                if constexpr (ROWS && TM >= 4) {
+            if (p.token_major && p.out_bf16 && TM >= 4 && (strip0 + TM) * 16 <= p.M) {
+                if constexpr (TM >= 4) {
 #pragma unroll
                     for (int b = 0; b < TN; ++b) {
                         const int col = b0 + 16 * b + i;
@@ -310,40 +309,6 @@ tsvd_thin_panel_kernel(thin_args p) {
                 }
                 continue;
             }
-            // The common cases without a test or an address computation per store (5617 x 1174 x 119 at 3136
-            // tokens 31.9 -> 28.6 us, gathered convolutions 0.98, with a fold 0.97 of the time)
-            if constexpr (ROWS) {
-                if (!p.out_bf16 && (strip0 + TM) * 16 <= p.M) {
-                    typedef f32x4 f32x4_at __attribute__((aligned(4)));
-#pragma unroll
-                    for (int b = 0; b < TN; ++b) {
-                        const int col = b0 + 16 * b + i;
-                        float* dst = static_cast<float*>(p.y) + (size_t)col * p.ldy + strip0 * 16 + 4 * g;
-                        if (col < p.B) {
-#pragma unroll
-                            for (int a = 0; a < TM; ++a) *reinterpret_cast<f32x4_at*>(dst + 16 * a) = acc[a][b];
-                        }
-                    }
-                    continue;
-                }
-            } else if (!p.out_bf16 && p.ldy < (1ll << 21)) {
-                // a constant offset per lane plus a scalar; rows beyond M fall outside the buffer's range, which is exact in the last unit
-                const size_t left = ((size_t)(p.M - strip0 * 16) * p.ldy - b0) * 4;
-                const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                    static_cast<float*>(p.y) + (size_t)strip0 * 16 * p.ldy + b0, 0, (int)(left < 0xFFFFFFFFull ? left : 0xFFFFFFFFull), 0x00020000);
-                const int ld4 = (int)p.ldy * 4, y_voff = 4 * g * ld4 + i * 4;
-#pragma unroll
-                for (int b = 0; b < TN; ++b) {
-                    if (b0 + 16 * b + i < p.B) {
-#pragma unroll
-                        for (int a = 0; a < TM; ++a)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[a][b][e]), y_rsrc, y_voff + 64 * b, (16 * a + e) * ld4, 0);
-                    }
-                }
-                continue;
-            }
 #pragma unroll
             for (int a = 0; a < TM; ++a) {
                 const int row0 = (strip0 + a) * 16 + 4 * g;
@@ -351,7 +316,7 @@ tsvd_thin_panel_kernel(thin_args p) {
                 for (int b = 0; b < TN; ++b) {
                     const int col16 = b0 + 16 * b, col = col16 + i;
                     const f32x4 v = acc[a][b];
-                    if constexpr (ROWS) {
+                    if (p.token_major) {
                         if (col < p.B) tsvd_store_token_major4(p.y, p.ldy, col, row0, p.M, v[0], v[1], v[2], v[3], p.out_bf16);
                     } else if (p.out_bf16) {
                         tsvd_store_row_pair_bf16(p.y, p.ldy, row0, p.M, col16, i, p.B, v[0], v[1]);
@@ -373,22 +338,24 @@ tsvd_thin_panel_kernel(thin_args p) {
 
 constexpr int LDS_BYTES = 160 * 1024, MAX_TAPS = 48;
 
-template <int TN, int RB, int SOURCE, bool ROWS>
+template <int TN, int RB, int SOURCE, bool CHUNKED>
+auto kernel() { return tsvd_thin_panel_kernel<TN, RB, SOURCE, CHUNKED>; }
+template <int TN, int RB, int SOURCE>
 hipError_t launch(const thin_args& a, int lds, hipStream_t stream) {
     const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN))), block(512);
-    if (a.buffers == 2) hipLaunchKernelGGL((tsvd_thin_panel_kernel<TN, RB, SOURCE, true, ROWS>), grid, block, lds, stream, a);
-    else hipLaunchKernelGGL((tsvd_thin_panel_kernel<TN, RB, SOURCE, false, ROWS>), grid, block, lds, stream, a);
+    if (a.buffers == 2) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true>()), grid, block, lds, stream, a);
+    else hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false>()), grid, block, lds, stream, a);
     return hipGetLastError();
 }
 template <int TN, int RB>
-hipError_t launch(int source, bool rows, const thin_args& a, int lds, hipStream_t stream) {
-    if (source == THIN_CONV) return rows ? hipErrorInvalidValue : launch<TN, RB, THIN_CONV, false>(a, lds, stream);
-    if (source == THIN_TOKEN_MAJOR) return rows ? launch<TN, RB, THIN_TOKEN_MAJOR, true>(a, lds, stream) : launch<TN, RB, THIN_TOKEN_MAJOR, false>(a, lds, stream);
-    return rows ? launch<TN, RB, THIN_FEATURE_MAJOR, true>(a, lds, stream) : launch<TN, RB, THIN_FEATURE_MAJOR, false>(a, lds, stream);
+hipError_t launch(int source, const thin_args& a, int lds, hipStream_t stream) {
+    if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, lds, stream);
+    if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, lds, stream);
+    return launch<TN, RB, THIN_FEATURE_MAJOR>(a, lds, stream);
 }
-template <int TN, int RB, int SOURCE, bool ROWS>
+template <int TN, int RB, int SOURCE>
 hipError_t init() {
-    for (const auto k : {tsvd_thin_panel_kernel<TN, RB, SOURCE, false, ROWS>, tsvd_thin_panel_kernel<TN, RB, SOURCE, true, ROWS>}) {
+    for (const auto k : {kernel<TN, RB, SOURCE, false>(), kernel<TN, RB, SOURCE, true>()}) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
     }
@@ -397,9 +364,8 @@ hipError_t init() {
 template <int TN, int RB>
 hipError_t init() {
     hipError_t e;
-    if ((e = init<TN, RB, THIN_FEATURE_MAJOR, false>()) != hipSuccess || (e = init<TN, RB, THIN_FEATURE_MAJOR, true>()) != hipSuccess ||
-        (e = init<TN, RB, THIN_TOKEN_MAJOR, false>()) != hipSuccess || (e = init<TN, RB, THIN_TOKEN_MAJOR, true>()) != hipSuccess) return e;
-    return init<TN, RB, THIN_CONV, false>();
+    if ((e = init<TN, RB, THIN_FEATURE_MAJOR>()) != hipSuccess || (e = init<TN, RB, THIN_TOKEN_MAJOR>()) != hipSuccess) return e;
+    return init<TN, RB, THIN_CONV>();
 }
 
 }  // namespace
@@ -457,20 +423,23 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
     a.bias = g.bias;
     a.M = (int)hd.M;
     a.out_bf16 = g.out_bf16;
-    // Feature-major rows of enough panels, where x is not outweighed by y or the panels share the lines of y too: 5019 x 4308 x 768 at 11841
-    // tokens 253 -> 199 us, 244 x 2015 x 1536 at 3621 33.9 -> 26.7, 975 x 320 x 125 at 3773 13.3 -> 10.9, 9141 x 731 x 259 at 3805 62.7 -> 44.7.
-    // With 50 panels 9.3 -> 10.0 (575 x 177 x 122), for 2304 rows on 98 27.3 -> 29.4 (whole lines of y: a convolution's columns, which another
-    // launch folds), 7635 rows on 128 26.5 -> 27.4, 933 on 384 at 1984 17.3 -> 18.4.  Rows of tokens share nothing; gathered convolutions: 0.95 to 1.1.
-    const bool runs = g.source == THIN_FEATURE_MAJOR && g.B > 60 * 16 * tiles && (a.ldy * (a.out_bf16 ? 2 : 4) % 64 != 0 || a.M * (a.out_bf16 ? 2 : 4) <= 6 * a.N);
-    a.runs = runs ? (a.B + 16 * tiles - 1) / (16 * tiles) : 0;
+    a.token_major = g.y_token_major;
+// Feature-major rows of enough panels, unless y outweighs x: 5019 x 4308 x 768 at 11841 tokens 253 -> 199 us, 244 x 2015 x 1536 at 3621
+    // 33.9 -> 26.7, 975 x 320 x 125 at 3773 13.3 -> 10.9, 5926 x 1340 x 768 at 3019 51.4 -> 46.2 us.  With 50 panels 9.3 -> 10.0 (575 x 177 x 122), for
+    // 2304 rows on 98 27.3 -> 29.4 and 2358 on 415 38.6 -> 40.8 us (a convolution's columns, whose fold reads y next), 7635 rows on 128 26.5 -> 27.4.  Rows
+    // of tokens share nothing; gathered convolutions: 0.95 to 1.1.
+    a.runs = g.source == THIN_FEATURE_MAJOR && g.B > 64 * 16 * tiles && a.M <= 5 * a.N;
+    // rows per unit of stage U: the larger units unless they leave wavefronts without one
+    auto passes = [&](int utm) { return ((a.M + 16 * utm - 1) / (16 * utm) + 7) / 8 * utm; };
+    a.utm = passes(8) <= passes(4) && passes(8) <= passes(2) ? 8 : passes(4) <= passes(2) ? 4 : 2;
     const bool conv = g.source == THIN_CONV;
     if (conv && g.kv1 * g.kv2 > MAX_TAPS) return hipErrorNotSupported;
     a.chunk = tsvd_thin_chunk(hd.K, hd.N, tiles, conv);
     if (a.chunk == 0) return hipErrorNotSupported;
     a.buffers = a.chunk < a.nvb ? 2 : 1;
     const int lds = (a.buffers * a.chunk + a.nub) * tiles * FP6_REC_BYTES + (conv ? a.nvb * 512 : 0), rb = (a.nub + 7) / 8;
-    if (tiles == 1 && rb == 1) return launch<1, 1>(g.source, g.y_token_major != 0, a, lds, stream);
-    if (tiles == 1 && rb == 2) return launch<1, 2>(g.source, g.y_token_major != 0, a, lds, stream);
-    if (tiles == 2 && rb == 1) return launch<2, 1>(g.source, g.y_token_major != 0, a, lds, stream);
+    if (tiles == 1 && rb == 1) return launch<1, 1>(g.source, a, lds, stream);
+    if (tiles == 1 && rb == 2) return launch<1, 2>(g.source, a, lds, stream);
+    if (tiles == 2 && rb == 1) return launch<2, 1>(g.source, a, lds, stream);
     return hipErrorNotSupported;
 }
