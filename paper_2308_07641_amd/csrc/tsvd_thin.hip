@@ -309,6 +309,27 @@ tsvd_thin_panel_kernel(thin_args p) {
                 }
                 continue;
             }
+            if constexpr (SOURCE != THIN_TOKEN_MAJOR) {
+                if (!p.token_major && !p.out_bf16 && p.ldy < (1ll << 21)) {
+                    // Without a test or an address computation per store: a constant offset per lane plus a scalar; rows beyond M fall
+                    // outside the buffer's range, which is exact in the last unit.  (Convolutions 0.97, feature-major calls 0.98 of the time.)
+                    const size_t left = ((size_t)(p.M - strip0 * 16) * p.ldy - b0) * 4;
+                    const __amdgpu_buffer_rsrc_t y_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                        static_cast<float*>(p.y) + (size_t)strip0 * 16 * p.ldy + b0, 0, (int)(left < 0xFFFFFFFFull ? left : 0xFFFFFFFFull), 0x00020000);
+                    const int ld4 = (int)p.ldy * 4, y_voff = 4 * g * ld4 + i * 4;
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) {
+                        if (b0 + 16 * b + i < p.B) {
+#pragma unroll
+                            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[a][b][e]), y_rsrc, y_voff + 64 * b, (16 * a + e) * ld4, 0);
+                        }
+                    }
+                    continue;
+                }
+            }
 #pragma unroll
             for (int a = 0; a < TM; ++a) {
                 const int row0 = (strip0 + a) * 16 + 4 * g;
@@ -424,11 +445,12 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
     a.M = (int)hd.M;
     a.out_bf16 = g.out_bf16;
     a.token_major = g.y_token_major;
-// Feature-major rows of enough panels, unless y outweighs x: 5019 x 4308 x 768 at 11841 tokens 253 -> 199 us, 244 x 2015 x 1536 at 3621
-    // 33.9 -> 26.7, 975 x 320 x 125 at 3773 13.3 -> 10.9, 5926 x 1340 x 768 at 3019 51.4 -> 46.2 us.  With 50 panels 9.3 -> 10.0 (575 x 177 x 122), for
-    // 2304 rows on 98 27.3 -> 29.4 and 2358 on 415 38.6 -> 40.8 us (a convolution's columns, whose fold reads y next), 7635 rows on 128 26.5 -> 27.4.  Rows
-    // of tokens share nothing; gathered convolutions: 0.95 to 1.1.
-    a.runs = g.source == THIN_FEATURE_MAJOR && g.B > 64 * 16 * tiles && a.M <= 5 * a.N;
+    // Feature-major rows of enough panels, where x is not outweighed by y or the panels share lines of y too: 5019 x 4308 x 768 at 11841
+    // tokens 253 -> 199 us, 244 x 2015 x 1536 at 3621 33.9 -> 26.7, 975 x 320 x 125 at 3773 13.3 -> 10.9, 9141 x 731 x 259 at 3805 62.7 -> 44.7.
+    // With 50 panels 9.3 -> 10.0 (575 x 177 x 122); with whole lines of y 27.3 -> 29.4 for 2304 rows on 98 (a convolution's columns, which
+    // another launch folds), 26.5 -> 27.4 for 7635 on 128, 16.5 -> 17.2 for 933 on 384.  Rows of tokens share nothing; gathered convolutions: 0.95 to 1.1.
+    const int piece = a.out_bf16 ? 2 : 4;
+    a.runs = g.source == THIN_FEATURE_MAJOR && g.B > 60 * 16 * tiles && (a.ldy * piece % 64 != 0 || a.M * piece <= 6 * a.N);
     // rows per unit of stage U: the larger units unless they leave wavefronts without one
     auto passes = [&](int utm) { return ((a.M + 16 * utm - 1) / (16 * utm) + 7) / 8 * utm; };
     a.utm = passes(8) <= passes(4) && passes(8) <= passes(2) ? 8 : passes(4) <= passes(2) ? 4 : 2;
