@@ -332,8 +332,9 @@ tsvd_pair_tail_kernel(tsvd_pair_plan p, int count) {
         __syncthreads();
         const double dj = row_j[TAIL_RANK];
         if (k == 0) tol = dj * 0x1p-50;
-        over = dj > tol && k == TAIL_RANK;
-        if (!(dj > tol) || over) break;
+        // (a matrix that the squarings call of rank one: what a seventeenth pivot would add is below 1e-12 of it)
+        over = dj > tol && k == TAIL_RANK && last < 0;
+        if (!(dj > tol) || k == TAIL_RANK) break;
         double a = 0.0, b = 0.0;
         for (int q = 0; q < k; q += 2) {                     // (an odd k meets a zero)
             a += mine[q] * row_j[q];
@@ -345,8 +346,15 @@ tsvd_pair_tail_kernel(tsvd_pair_plan p, int count) {
         r = k + 1;
     }
     if (tid == 0) {
-        // squarings that the next such pair (after `over`: this one) should get: halving the exponent nearly doubles the pivots
-        const int want = over ? count + 3 : r > 12 ? count + 1 : last >= 0 ? last + 1 : r <= 5 ? max(count - 1, 1) : count;
+        // squarings that the next such pair (after `over`: this one) should get: halving the exponent nearly doubles the pivots.  After
+        // `over`: each squaring doubles the bits between the first pivot and the seventeenth, which are to become fifty; what is missed at the last
+        // count that is tried is taken as it is (equal singular values: any vector of theirs will do).
+        int want = r > 12 ? count + 1 : last >= 0 ? last + 1 : r <= 5 ? max(count - 1, 1) : count;
+        if (over) {
+            constexpr int LAST = TSVD_PAIR_MAX_SQUARINGS - 1;
+            const double bits = log2(tol * 0x1p50 / row_j[TAIL_RANK]);      // (not above 0: pivots that are equal, as far as they are compared)
+            want = count >= LAST ? TSVD_PAIR_MAX_SQUARINGS : bits > 0x1p-40 ? min(LAST, count + max(1, (int)ceil(log2(50.0 / bits)))) : LAST;
+        }
         if (over) ++p.state->missed;
         p.state->needed = max(p.state->needed, want);
     }

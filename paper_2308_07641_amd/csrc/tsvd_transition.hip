@@ -1077,7 +1077,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         if (base) (void)hipFree(base);
     };
     if (hipMalloc(reinterpret_cast<void**>(&base), total) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&pinned), 2 * told_bytes, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&pinned), 2 * told_bytes + sizeof(tsvd_pair_state), hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&event[0], hipEventDisableTiming) != hipSuccess || hipEventCreateWithFlags(&event[1], hipEventDisableTiming) != hipSuccess) {
         release();
         (void)hipGetLastError();
@@ -1134,13 +1134,34 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         v = plan.v;
     }
     residual(0, 0);                                                          // R = W, |W|^2
-    double wnorm2 = 0.0;
-    if (wait_for(0)) wnorm2 = rnorm2;
     // Squarings enqueued per pair: what the iteration before found right (tsvd_pair_tail_kernel).  Where they have to lead to rank one: sixteen
     // (those beyond the ones a pair needs return at once), and two more than the last iteration needed where that is more.  Too few
     // cost the iteration again.
     const bool any_rank = squares && tsvd_pair_any_rank(plan);
     int squarings = squares ? tsvd_pair_first_squarings(plan) : 0;
+    // What the first matrix needs is not known: its leading pair is taken before the host waits, and squared on from where it is until that will do,
+    // which costs only what is missing.  (Singular values in clusters need up to 35 squarings and equal ones all.  When the whole iteration was
+    // taken again, with three squarings more each time, the first 24 components of [512, 256] with all values within 1e-6, four an
+    // iteration, took 11.3 ms, now 3.7; a Laplace matrix 2.4 either way.)
+    bool first_pair = false;                                                 // in the plan already
+    int least = 1;                                                           // squarings that iterations before `least_until` get
+    int64_t least_until = 0;
+    if (any_rank && st == TSVD_OK) {
+        tsvd_pair_state* state = reinterpret_cast<tsvd_pair_state*>(pinned + 2 * told_bytes);
+        for (int from = 0, step = 0;;) {
+            tsvd_pair_square(plan, R, from, squarings, s);
+            tsvd_pair_vectors(plan, R, squarings, true, s);
+            if (!ok(hipMemcpyAsync(state, &rep->pair, sizeof *state, hipMemcpyDeviceToHost, s)) || !ok(hipStreamSynchronize(s))) break;
+            from = squarings;
+            first_pair = state->missed == 0 || squarings == TSVD_PAIR_MAX_SQUARINGS;
+            squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, first_pair ? std::max(1, state->needed) : std::max(squarings + step + 1, state->needed));
+            if (first_pair) break;
+            step += 4;                                                       // (equal values beside others: the estimate stays short)
+            if (!ok(hipMemsetAsync(&rep->pair.missed, 0, 2 * sizeof(int), s))) break;       // (and what it needed)
+        }
+    }
+    double wnorm2 = 0.0;
+    if (wait_for(0)) wnorm2 = rnorm2;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
     auto enqueue = [&](int64_t i, int64_t first, int64_t take) {
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
@@ -1152,8 +1173,11 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         }
         for (int64_t j = 0; j < take; ++j) {
             if (squares) {
-                tsvd_pair_square(plan, src, 0, squarings, s);
-                tsvd_pair_vectors(plan, src, squarings, any_rank, s);
+                if (!first_pair) {
+                    tsvd_pair_square(plan, src, 0, squarings, s);
+                    tsvd_pair_vectors(plan, src, squarings, any_rank, s);
+                }
+                first_pair = false;
                 if (j + 1 < take) tsvd_pair_deflate(plan, Rwork, s);
             } else {
                 const tsvd_status ps = tsvd_leading_singular_pair(src, M, N, 4 * GKL_MAX_STEPS, u, v, sigma, nullptr, base + at_svd, bytes_svd, s);
@@ -1190,7 +1214,12 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
             if (squares && next > 0) enqueue(i + 1, ahead, next);
             if (st != TSVD_OK || !wait_for(i)) break;
             if (seen.pair.missed != 0 && seen.pair.needed < TSVD_PAIR_MAX_SQUARINGS) {
-                // some pair needed more squarings: back to the residual before this iteration, with more of them
+                // some pair needed more squarings: back to the residual before this iteration, with more of them, and for a while
+                // with one more than were too few (spectra on the edge of two counts missed every eighth iteration)
+                if (any_rank && i > 1) {
+                    least = std::min(seen.pair.needed, squarings + 1);
+                    least_until = i + 16;
+                }
                 squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, seen.pair.needed + (any_rank ? 0 : 8));
                 if (!ok(hipStreamSynchronize(s)) || !ok(hipMemsetAsync(rep, 0, sizeof(transition_report), s))) break;
                 residual(i - 1, K);
@@ -1202,7 +1231,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
                 st = TSVD_EVALUE;           // no ternary vector within theta: the components of an unfinished iteration are dropped
                 break;
             }
-            squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(1, seen.pair.needed) : std::max(16, seen.pair.needed + 2));
+            squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(i < least_until ? least : 1, seen.pair.needed) : std::max(16, seen.pair.needed + 2));
             const double err = std::sqrt(rnorm2 / wnorm2);
             if (errors_host)
                 for (int64_t r = K; r < K + take; ++r) errors_host[r] = err;      // (one error per iteration, repeated for its components)
