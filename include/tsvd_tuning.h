@@ -20,7 +20,7 @@ extern "C" {
  *   TSVD_GEMV (0: single-token calls take the general slab kernel), TSVD_GEMV_FUSED (0: small single-token
  *   problems take two launches), TSVD_GEMV_ONEPASS (0: single-token calls take one launch per stage),
  *   TSVD_GEMV_SW / TSVD_GEMV_KWLOG2, TSVD_SKINNY_SW / TSVD_SKINNY_KW (workgroup shapes),
- *   TSVD_FEW (largest number of bf16 tokens that the few-token kernels serve while any switch is set, default 0), TSVD_FEW_PLANES (3, 5:
+ *   TSVD_FEW (largest number of bf16 tokens that the few-token kernels serve while any switch is set, default 0), TSVD_FEW_PLANES (4, 5:
  *   planes of z there), TSVD_FEW_KWLOG2, TSVD_FEW_SW_V, TSVD_FEW_SW_U, TSVD_FEW_RW_U (their launch shapes),
  *   TSVD_MID (0: slab kernel for few tokens off), TSVD_MID_MAX_B, TSVD_MID_SW, TSVD_MID_KWLOG2, TSVD_MID_RESIDENT,
  *   TSVD_GEMM_MIN_B, TSVD_GEMM_CFG_V / TSVD_GEMM_CFG_U (tile shape of a batched stage: 0..3 large tiles,

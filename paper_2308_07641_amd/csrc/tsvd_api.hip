@@ -291,7 +291,7 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
 bool gemv_serves(const tsvd_handle* h) { return tsvd_gemv_fits(h->hd.Np, h->hd.Kp) && env_int("TSVD_GEMV", 1) != 0; }
 double code_bytes(const tsvd_handle* h) { return (double)h->hd.Kp * (double)(h->hd.Mp + h->hd.Np) / 4.0; }
 // 2 - 16 bf16 tokens whose z is kept as in fp32 (side by side on the single-token kernels, or on five planes of the few-token kernels): up to
-// 60 MB of code words times tokens.  Beyond, side by side takes longer than z in three planes (0.15 us for every MB and token).
+// 60 MB of code words times tokens.  Beyond, side by side takes longer than z in four planes (0.15 us for every MB and token).
 bool z_as_fp32(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     return x_dtype == TSVD_BF16 && B >= 2 && B <= 16 && !tsvd_tuning_any() && !h->dense_u && gemv_serves(h) && (double)B * code_bytes(h) <= 60.0e6;
 }
@@ -308,9 +308,9 @@ int few_planes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, int64_t ldx,
     const tsvd_blob_header& hd = h->hd;
     // (Kp: the records have to fit the fixed workspace of tsvd_forward_noalloc, as z in 16 bits does)
     if (x_dtype != TSVD_BF16 || B > 16 || hd.Kp > (1 << 18) || !tsvd_few_fits(hd, B, ldx, x_token_major)) return 0;
-    if (tsvd_tuning_any()) return B <= env_int("TSVD_FEW", 0) ? (env_int("TSVD_FEW_PLANES", 3) == 5 ? 5 : 3) : 0;
+    if (tsvd_tuning_any()) return B <= env_int("TSVD_FEW", 0) ? (env_int("TSVD_FEW_PLANES", 4) == 5 ? 5 : 4) : 0;
     if (five_planes(h)) return 5;
-    return B == 1 || z_as_fp32(h, B, x_dtype) ? 0 : 3;
+    return B == 1 || z_as_fp32(h, B, x_dtype) ? 0 : 4;
 }
 tsvd_status forward_skinny(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t B, int64_t ldx, bool x_token_major,
                            void* y, int64_t ldy, const out_opts& oo, void* ws, hipStream_t stream) {
@@ -502,7 +502,7 @@ size_t gemm_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
         for (const bool tokens : {false, true})      // (either layout of x: their margins differ)
             if (batch_plan(h, B, x_dtype, tokens, true, false, false, true, false).split) bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
         // (likewise: token-major y costs the panels more)
-        if (batch_plan(h, B, x_dtype, true, true, true, true, true, true).few) bytes = std::max(bytes, tsvd_few_bytes(h->hd.Kp, B, 3));
+        if (batch_plan(h, B, x_dtype, true, true, true, true, true, true).few) bytes = std::max(bytes, tsvd_few_bytes(h->hd.Kp, B, 4));
     }
     return bytes;
 }
@@ -641,7 +641,7 @@ namespace {
 size_t base_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     // (the few-token path is chosen per call, by the row stride too: cover every candidate)
     size_t few = round256(std::max(skinny_workspace(h, B), mid_workspace(h)));
-    if (x_dtype == TSVD_BF16 && B <= 16 && h->hd.Kp <= (1 << 18)) few = std::max(few, tsvd_few_bytes(h->hd.Kp, B, five_planes(h) || tsvd_tuning_any() ? 5 : 3));
+    if (x_dtype == TSVD_BF16 && B <= 16 && h->hd.Kp <= (1 << 18)) few = std::max(few, tsvd_few_bytes(h->hd.Kp, B, five_planes(h) || tsvd_tuning_any() ? 5 : 4));
     if (use_gemm(h, B, x_dtype)) return std::max(gemm_workspace(h, B, x_dtype), B <= 64 ? few : (size_t)0);
     return few;
 }
@@ -734,12 +734,12 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
     tsvd_batch_plan plan = {};
     if (batched && !few)
         plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16, !misaligned,
-                          tsvd_few_fits(h->hd, B, ldx, x_layout == TSVD_TOKEN_MAJOR) && tsvd_few_bytes(h->hd.Kp, B, 3) <= need);
+                          tsvd_few_fits(h->hd, B, ldx, x_layout == TSVD_TOKEN_MAJOR) && tsvd_few_bytes(h->hd.Kp, B, 4) <= need);
     if (plan.split && x_dtype == TSVD_BF16 && tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false) > need) plan.split = false;   // (never more than was asked for)
     if (z_planes || plan.few) {
         // few tokens: x in any layout and alignment, planes of z in the workspace
         const tsvd_few_problem f = {h->blob, &h->hd, static_cast<const uint16_t*>(x_dev), B, B == 1 && ldx == 1 ? h->hd.N : ldx, x_layout == TSVD_TOKEN_MAJOR || (B == 1 && ldx == 1), y_dev, ldy,
-                                    oo.token_major, oo.out_bf16, bias_dev, static_cast<unsigned char*>(ws), z_planes ? z_planes : 3, h->cu_count,
+                                    oo.token_major, oo.out_bf16, bias_dev, static_cast<unsigned char*>(ws), z_planes ? z_planes : 4, h->cu_count,
                                     tsvd_stage_mask()};
         return tsvd_few_launch(f, s) == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
     }

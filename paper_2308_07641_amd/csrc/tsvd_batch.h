@@ -11,7 +11,7 @@ struct tsvd_batch_call {
     bool whole;                     // both stages run (no diagnostic stage mask)
 };
 struct tsvd_batch_plan {
-    bool few;                       // on the few-token kernels, z in three planes; what follows then says what the call would take else
+    bool few;                       // on the few-token kernels, z in four planes; what follows then says what the call would take else
     int thin;                       // token tiles of a thin panel (tsvd_thin.hip), 0: not on those
     bool split;                     // planes of x, stage V to planes of z, stage U from those (the plane path of tsvd_forward_gemm) ...
     int split_v, split_u;           // ... with these shapes of tsvd_fp6_split_launch, 0: the launches of tsvd_fp6.hip

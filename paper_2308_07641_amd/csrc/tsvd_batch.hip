@@ -184,8 +184,9 @@ tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
                 if (t < best) best = t, plan.thin = tiles;
             }
     // Few tokens: each group of 16 reads both factors again, measured up to 600 tokens.  A twentieth and 0.7 us less than the best of the others (what
-    // either estimate is off by where a call is hardly more than its launches).  On 200 calls of 17 to 512 tokens 0.68 of the time without
-    // them on the average, 0.3 to 0.5 for thousands of rows at 17 to 64 tokens; the worst 1.1.
+    // either estimate is off by where a call is hardly more than its launches).  On 200 calls of 17 to 128 tokens 0.67
+    // of the time without them on the average (the worst 1.04), 0.3 to 0.4 for thousands of rows at 17 to 30 tokens; on 160 of 129 to 1024 tokens 0.83.
+    // (The best of both ways would have been 0.6 and 0.9 % faster.)
     if (c.few && c.whole && c.B <= 1024) {
         const double t = tsvd_few_cost({c.M, c.N, c.K, c.B, c.cus, c.x_token_major, c.x_aligned, c.out_bf16});
         plan.few = t < 0.95 * best && t < best - 0.7;

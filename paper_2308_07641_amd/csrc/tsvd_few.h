@@ -17,7 +17,7 @@ struct tsvd_few_args {
     int N;
     const float* S;
     unsigned char* planes;                // records of z [groups of 16 tokens][blocks], Kp / 128 blocks
-    int blocks, z_planes;                 // 3 or 5 planes
+    int blocks, z_planes;                 // 4 or 5 planes
     void* y;                              // stage U: fp32 or bf16 [M][ld] or [B][ld]
     const float* bias;
     int out_bf16, M;
@@ -34,7 +34,7 @@ struct tsvd_few_problem {
     int y_token_major, out_bf16;
     const float* bias;
     unsigned char* planes;                // tsvd_few_bytes
-    int z_planes;                         // 3 (z off by 2^-14 of the largest of 32 neighbours), or 5 (2^-24)
+    int z_planes;                         // 4 (z off by 2^-19 of the largest of 32 neighbours), or 5 (2^-24)
     int cu_count, stages;                 // (2: stage V, 4: stage U)
 };
 hipError_t tsvd_few_init();
@@ -43,7 +43,7 @@ size_t tsvd_few_bytes(long long Kp, long long B, int z_planes);
 bool tsvd_few_fits(const tsvd_blob_header& hd, long long B, long long ldx, bool x_token_major);
 hipError_t tsvd_few_launch(const tsvd_few_problem& f, hipStream_t stream);
 
-// Estimate of a call on three planes in microseconds.
+// Estimate of a call on four planes in microseconds.
 struct tsvd_few_call {
     long long M, N, K, B, cus;
     bool x_token_major, x_aligned, out_bf16;      // x_aligned: rows of x start on 16 bytes

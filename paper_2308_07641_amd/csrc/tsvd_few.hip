@@ -8,11 +8,13 @@
 // by them, each tile requested one column ahead; the partial sums of the kw wavefronts meet in LDS once, at the end.
 //
 // Stage V multiplies bf16 x as it is (codes expanded to 0 / +2 / -2 in 16 bits: 64 operations and 8 MFMAs a tile) and leaves z as
-// three or five E2M3 planes (tsvd_fp6_common.h), which stage U multiplies by the codes as fp4 numbers: 8 operations and 6 (10) MFMAs a tile.
+// four or five E2M3 planes (tsvd_fp6_common.h), which stage U multiplies by the codes as fp4 numbers: 8 operations and 8 (10) MFMAs a tile.
 //
 // Measured on MI355X against the kernels that take x and fp16 z through LDS in slabs (tsvd_mid.hip): 16384 x 4096 x 8192, 16 tokens, token-major
-// (a transposition pass before) 20.9 -> 15.5 us: stage V 7.9 -> 6.0, stage U 12.0 -> 9.0 .. 10.2 (33.5 MB of codes and 84 MB of z
-// from L2).  Loading operand lanes of x straight from rows of tokens cost stage V 1.5 us more (16-byte pieces of 32 lines per request), and requests
+// (a transposition pass before) 21.4 -> 17.9 us a call, in a kernel trace stage V 7.9 -> 6.7, stage U 12.0 -> 10.9 (16.8 MB of codes and 105 MB of z
+// from L2).  Four planes rather than three: three cost 1.2 us less there and 0.7 us on small calls, but leave 2^-14 of the largest of 32
+// neighbours, so rows of y made of ranks beside such that see a feature 2000 times the rest were off by 1.1e-3 (fp16 z 2.1e-4, four planes 3e-5).  A
+// record of seven whole pieces cost 1.5 us more than six and the scales apart.  Loading operand lanes of x straight from rows of tokens cost stage V 1.5 us more (16-byte pieces of 32 lines per request), and requests
 // of 8 and 4 bytes for the ends of the planes cost stage U 1 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -37,12 +39,11 @@ __device__ __forceinline__ u32x2 lds_tr(const unsigned char* lds_byte_ptr) {
     return __builtin_bit_cast(u32x2, r);
 }
 
-// Record of z of (16 tokens, 128 rank positions): a lane's planes, 24 bytes each, and a scale byte for each, in pieces of 16 bytes [pieces][64][16].
-// Three planes: five pieces, the scales in word 2 of the last; five planes: eight pieces, the scales in its words 2 and 3.
-constexpr int pieces_of(int planes) { return planes == 3 ? 5 : 8; }
-constexpr int record_bytes(int planes) { return 1024 * pieces_of(planes); }
+// Record of z of (16 tokens, 128 rank positions): a lane's planes, 24 bytes each, in pieces of 16 bytes [pieces][64][16], and a scale byte for each.
+// Four planes: six pieces, then the scales [64][4]; five planes: eight pieces, the scales in words 2 and 3 of the last.
+constexpr int record_bytes(int planes) { return planes == 4 ? 6 * 1024 + 256 : 8 * 1024; }
 
-// Operand of stage U: the pieces of a lane (five planes: all eight).  (Variables of their own: from a structure or an array the compiler reads
+// Operand of stage U: the pieces of a lane (four planes: six of them, word 0 of the seventh the scales).  (Variables of their own: from a structure or an array the compiler reads
 // a plane's first words as part of a longer vector, and then keeps everything in scratch memory.)
 #define FEW_OPERAND(n) u32x4 n##0, n##1, n##2, n##3, n##4, n##5, n##6, n##7
 #define FEW_OPERAND_OF(n) n##0, n##1, n##2, n##3, n##4, n##5, n##6, n##7
@@ -213,38 +214,35 @@ tsvd_few_v_kernel(tsvd_few_args p) {
             v[e] = zl[(16 * l0 + e) * RED_PITCH + t];
             v[16 + e] = zl[(16 * l1 + e) * RED_PITCH + t];
         }
-        // v is left holding what three planes do not resolve; two planes more take that
-        u32x4 lo[6];
-        u32x2 hi[6];
-        auto planes = [&](auto first) {
-            return tsvd_planes_of_32<first == 0>(v, [&](int pl, u32x4 l, u32x2 h) {
-                lo[first + pl] = l;
-                hi[first + pl] = h;
-            });
-        };
-        uint32_t scales = planes(std::integral_constant<int, 0>{}), more = 0u;
-        if (p.z_planes == 5) {
-            const uint32_t rest = planes(std::integral_constant<int, 3>{});
-            scales |= rest << 24;
-            more = rest >> 8 & 0xFFu;
-        }
-        u32x4* rec = reinterpret_cast<u32x4*>(p.planes + ((size_t)blockIdx.y * p.blocks + (sg >> 3)) * record_bytes(p.z_planes)) + 16 * gr + t;
+        u32x4 lo[5];
+        u32x2 hi[5];
+        const uint32_t scales = tsvd_planes_of_32<true, 4>(v, [&](int pl, u32x4 l, u32x2 h) {
+            lo[pl] = l;
+            hi[pl] = h;
+        });
+        unsigned char* rec_bytes = p.planes + ((size_t)blockIdx.y * p.blocks + (sg >> 3)) * record_bytes(p.z_planes);
+        u32x4* rec = reinterpret_cast<u32x4*>(rec_bytes) + 16 * gr + t;
         rec[0] = lo[0];
         rec[64] = u32x4{hi[0].x, hi[0].y, lo[1].x, lo[1].y};
         rec[128] = u32x4{lo[1].z, lo[1].w, hi[1].x, hi[1].y};
         rec[192] = lo[2];
-        if (p.z_planes == 3) {
-            rec[256] = u32x4{hi[2].x, hi[2].y, scales, 0u};
+        rec[256] = u32x4{hi[2].x, hi[2].y, lo[3].x, lo[3].y};
+        rec[320] = u32x4{lo[3].z, lo[3].w, hi[3].x, hi[3].y};
+        if (p.z_planes == 4) {
+            reinterpret_cast<uint32_t*>(rec_bytes + 6 * 1024)[16 * gr + t] = scales;
         } else {
-            rec[256] = u32x4{hi[2].x, hi[2].y, lo[3].x, lo[3].y};
-            rec[320] = u32x4{lo[3].z, lo[3].w, hi[3].x, hi[3].y};
+            // v holds what four planes do not resolve
+            const uint32_t fifth = tsvd_planes_of_32<false, 1>(v, [&](int, u32x4 l, u32x2 h) {
+                lo[4] = l;
+                hi[4] = h;
+            });
             rec[384] = lo[4];
-            rec[448] = u32x4{hi[4].x, hi[4].y, scales, more};
+            rec[448] = u32x4{hi[4].x, hi[4].y, scales, fifth};
         }
     }
 }
 
-// Stage U.  The records of two blocks (256 rank positions) in registers, 20 or 32 each; a block's next record is requested when its products are issued.
+// Stage U.  The records of two blocks (256 rank positions) in registers, 25 or 32 each; a block's next record is requested when its products are issued.
 template <int PLANES, int KWL, int SW>
 __global__ void __launch_bounds__(1024)
 tsvd_few_u_kernel(tsvd_few_args p) {
@@ -255,6 +253,7 @@ tsvd_few_u_kernel(tsvd_few_args p) {
     const int tok0 = blockIdx.y * 16, threads = blockDim.x, rows = p.strips_wg * 16, row0 = blockIdx.x * rows;
     const int strip0 = blockIdx.x * p.strips_wg + rw * SW, strip_bytes = p.nkt * 1024;
     const unsigned char* z = p.planes + (size_t)blockIdx.y * p.blocks * record_bytes(PLANES) + (16 * g + min(i, p.B - 1 - tok0)) * 16;
+    const unsigned char* z_scales = z + 6 * 1024 - (16 * g + min(i, p.B - 1 - tok0)) * 12;       // (four planes)
     // (tokens that do not exist: the last one's operands again: with one token a sixteenth of the bytes, and no uninitialised columns)
     // thread t finishes outputs t, t + threads, ...: the index that runs along a row of y first
     auto output = [&](int n, int& row, int& tok) {
@@ -277,8 +276,9 @@ tsvd_few_u_kernel(tsvd_few_args p) {
     auto load_w = [&](int s, int T) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(tiles[s] + T * 1024) + lane); };
     auto load_z = [&](int block, u32x4& p0, u32x4& p1, u32x4& p2, u32x4& p3, u32x4& p4, u32x4& p5, u32x4& p6, u32x4& p7) {
         auto piece = [&](int c) { return *reinterpret_cast<const u32x4*>(z + (size_t)block * record_bytes(PLANES) + c * 1024); };
-        p0 = piece(0), p1 = piece(1), p2 = piece(2), p3 = piece(3), p4 = piece(4);
-        if constexpr (PLANES == 5) p5 = piece(5), p6 = piece(6), p7 = piece(7);
+        p0 = piece(0), p1 = piece(1), p2 = piece(2), p3 = piece(3), p4 = piece(4), p5 = piece(5);
+        if constexpr (PLANES == 5) p6 = piece(6), p7 = piece(7);
+        else p6.x = *reinterpret_cast<const uint32_t*>(z_scales + (size_t)block * record_bytes(PLANES));
     };
     f32x4 acc[SW];
 #pragma unroll
@@ -288,11 +288,9 @@ tsvd_few_u_kernel(tsvd_few_args p) {
     auto multiply = [&](uint32_t w0, uint32_t w1, f32x4& a, const u32x4& p0, const u32x4& p1, const u32x4& p2, const u32x4& p3, const u32x4& p4,
                         const u32x4& p5, const u32x4& p6, const u32x4& p7) {
         const u32x4 av = {(w0 << 2) & 0xCCCCCCCCu, w0 & 0xCCCCCCCCu, (w1 << 2) & 0xCCCCCCCCu, w1 & 0xCCCCCCCCu};
-        const uint32_t scales = PLANES == 5 ? p7.z : p4.z;
-        if constexpr (PLANES == 5) {
-            a = mfma_fp6<0>(av, p6, u32x2{p7.x, p7.y}, p7.w, a);
-            a = mfma_fp6<3>(av, u32x4{p4.z, p4.w, p5.x, p5.y}, u32x2{p5.z, p5.w}, scales, a);
-        }
+        const uint32_t scales = PLANES == 5 ? p7.z : p6.x;
+        if constexpr (PLANES == 5) a = mfma_fp6<0>(av, p6, u32x2{p7.x, p7.y}, p7.w, a);
+        a = mfma_fp6<3>(av, u32x4{p4.z, p4.w, p5.x, p5.y}, u32x2{p5.z, p5.w}, scales, a);
         a = mfma_fp6<2>(av, p3, u32x2{p4.x, p4.y}, scales, a);
         a = mfma_fp6<1>(av, u32x4{p1.z, p1.w, p2.x, p2.y}, u32x2{p2.z, p2.w}, scales, a);
         a = mfma_fp6<0>(av, p0, u32x2{p1.x, p1.y}, scales, a);
@@ -346,7 +344,7 @@ hipError_t init_one() {
     constexpr int most = 16 * WAVE_X;
     constexpr int S2 = SW < 2 ? 2 : SW;
     hipError_t e;
-    for (const void* k : {(const void*)tsvd_few_u_kernel<3, KWL, SW>, (const void*)tsvd_few_u_kernel<5, KWL, SW>})
+    for (const void* k : {(const void*)tsvd_few_u_kernel<4, KWL, SW>, (const void*)tsvd_few_u_kernel<5, KWL, SW>})
         if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most)) != hipSuccess) return e;
     for (const void* k : {(const void*)tsvd_few_v_kernel<true, true, KWL, S2>, (const void*)tsvd_few_v_kernel<true, false, KWL, S2>,
                           (const void*)tsvd_few_v_kernel<false, true, KWL, S2>, (const void*)tsvd_few_v_kernel<false, false, KWL, S2>})
@@ -365,7 +363,7 @@ hipError_t launch(const tsvd_few_args& a, stage st, dim3 grid, int waves, hipStr
     constexpr int S2 = SW < 2 ? 2 : SW;
     const dim3 block((unsigned)waves * 64);
     const unsigned lds = (unsigned)(st == STAGE_U ? lds_parts(waves, SW) : lds_v(waves, SW, a.strips_wg));
-    if (st == STAGE_U) (a.z_planes == 3 ? tsvd_few_u_kernel<3, KWL, SW> : tsvd_few_u_kernel<5, KWL, SW>)<<<grid, block, lds, stream>>>(a);
+    if (st == STAGE_U) (a.z_planes == 4 ? tsvd_few_u_kernel<4, KWL, SW> : tsvd_few_u_kernel<5, KWL, SW>)<<<grid, block, lds, stream>>>(a);
     else if (SW == 1) return hipErrorInvalidValue;          // (planes are made of pairs of strips)
     else (a.token_major ? a.B <= 8 ? tsvd_few_v_kernel<true, true, KWL, S2> : tsvd_few_v_kernel<true, false, KWL, S2>
                         : a.B <= 8 ? tsvd_few_v_kernel<false, true, KWL, S2> : tsvd_few_v_kernel<false, false, KWL, S2>)<<<grid, block, lds, stream>>>(a);
@@ -438,7 +436,7 @@ hipError_t tsvd_few_init() {
 size_t tsvd_few_bytes(long long Kp, long long B, int planes) { return (size_t)((B + 15) / 16) * (size_t)(Kp / 128) * record_bytes(planes); }
 
 // A call in microseconds: launches, columns of a wavefront in turn, columns that the wavefronts of a compute unit share (activations, then
-// strips), rounds of workgroups, results.  Non-negative least squares on relative errors over 500 calls of random sizes (2 to 600 tokens): 12 % rms.
+// strips), rounds of workgroups, results.  Non-negative least squares on relative errors over 500 calls of random sizes (2 to 600 tokens): 11 % rms.
 double tsvd_few_cost(const tsvd_few_call& c) {
     const long long groups = (c.B + 15) / 16, nkt_v = (c.N + 255) / 256, nkt_u = (c.K + 255) / 256;
     struct stage_terms { double turn, share, rounds; int sw; };
@@ -451,8 +449,8 @@ double tsvd_few_cost(const tsvd_few_call& c) {
     };
     const stage_terms v = terms(STAGE_V, nkt_u * 16, nkt_v), u = terms(STAGE_U, (c.M + 15) / 16, nkt_u);
     const double results = (double)c.M * (double)c.B * (c.out_bf16 ? 0.5 : 1.0) / (1e3 * (double)c.cus);
-    return 5.3 + 0.54 * u.turn + (0.017 + 0.041 * u.sw) * u.share + 0.79 * u.rounds + 0.54 * results + 0.70 * v.turn +
-           ((c.x_token_major ? 0.032 : c.x_aligned ? 0.086 : 0.118) + 0.071 * v.sw) * v.share + 1.34 * v.rounds;
+    return 6.24 + 0.38 * u.turn + 0.056 * u.sw * u.share + 0.13 * u.rounds + 0.45 * results + 0.56 * v.turn +
+           ((c.x_token_major ? 0 : c.x_aligned ? 0.069 : 0.182) + 0.077 * v.sw) * v.share + 0.96 * v.rounds;
 }
 
 bool tsvd_few_fits(const tsvd_blob_header& hd, long long B, long long ldx, bool x_token_major) {

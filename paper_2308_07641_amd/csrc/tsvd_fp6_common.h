@@ -17,18 +17,18 @@ namespace {
 #define FP6_PAIR_BYTES (8 * FP6_REC_BYTES)      // one block of one 128-token group: 38 KiB exactly
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-// One lane's 32 values -> three E2M3 planes (the value, the residual of its rounding, the residual of that), each
+// One lane's 32 values -> COUNT (three) E2M3 planes (the value, the residual of its rounding, the residual of that, ...), each
 // with its own power-of-two scale.  put(plane, first 16 bytes, last 8 bytes) receives the lane's 24 bytes of each
-// plane; the return value holds the three scale bytes.  KEEP: v is left holding what the three planes do not resolve
+// plane; the return value holds the scale bytes (COUNT <= 4).  KEEP: v is left holding what the planes do not resolve
 // (for a second set of planes); else it is used up.
-template <bool KEEP = false, typename Put>
+template <bool KEEP = false, int COUNT = 3, typename Put>
 __device__ __forceinline__ uint32_t tsvd_planes_of_32(float (&v)[32], Put put) {
     typedef float f32x16 __attribute__((ext_vector_type(16)));
     typedef float f32x32 __attribute__((ext_vector_type(32)));
     typedef unsigned u32x6 __attribute__((ext_vector_type(6)));
     uint32_t scales = 0;
 #pragma unroll
-    for (int pl = 0; pl < 3; ++pl) {
+    for (int pl = 0; pl < COUNT; ++pl) {
         float m = 0.f;
 #pragma unroll
         for (int e = 0; e < 32; ++e) m = fmaxf(m, fabsf(v[e]));
@@ -54,7 +54,7 @@ __device__ __forceinline__ uint32_t tsvd_planes_of_32(float (&v)[32], Put put) {
         // written out with results that may not overlap any operand.
         u32x6 w;
         asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3" : "=&v"(w) : "v"(s0), "v"(s1), "v"(unit));
-        if (pl < 2 || KEEP) {
+        if (pl < COUNT - 1 || KEEP) {
             f32x32 back;
             asm("v_cvt_scalef32_pk32_f32_fp6 %0, %1, %2" : "=&v"(back) : "v"(w), "v"(unit));
 #pragma unroll

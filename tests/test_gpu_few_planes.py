@@ -22,12 +22,13 @@ CALLS = [
     (130, 64, 60, 33), (300, 1030, 1024, 47), (640, 200, 300, 96)]      # groups of tokens, the last one of one token and full
 
 
-@pytest.mark.parametrize("planes,M,N,K,B", [(3, *c) for c in CALLS] + [(5, *c) for c in CALLS if c[3] <= 16])
+@pytest.mark.parametrize("planes,M,N,K,B", [(4, *c) for c in CALLS] + [(5, *c) for c in CALLS if c[3] <= 16])
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_few_tokens_on_planes(tsvd, planes, M, N, K, B, shape):  # noqa: F811
-    """(1e-6 for five planes: fp32 sums of a few hundred to a few thousand terms over 2^-24 of z.)"""
+    """(1e-6 for five planes: fp32 sums of a few hundred to a few thousand terms over 2^-24 of z; four planes: 2^-19, a 32nd of the 1e-4
+    that three planes are allowed, and some.)"""
     print(f"case few on planes {M} {N} {K} {B} {shape} {planes}", flush=True)
-    _check(tsvd, M, N, K, B, "bf16", {"TSVD_FEW": 128, "TSVD_FEW_PLANES": planes, **shape}, 1e-4 if planes == 3 else 1e-6)
+    _check(tsvd, M, N, K, B, "bf16", {"TSVD_FEW": 128, "TSVD_FEW_PLANES": planes, **shape}, 1e-5 if planes == 4 else 1e-6)
 
 
 @pytest.mark.parametrize("B,ld,col0", [(3, 10, 0), (5, 10, 2), (4, 9, 1), (9, 24, 8), (16, 40, 5), (19, 33, 7)])
@@ -51,7 +52,7 @@ def test_neighbours_that_are_not_finite(tsvd, B, ld, col0):  # noqa: F811
 
 @pytest.mark.parametrize("M,N,K,B", [(1100, 700, 500, 1), (1100, 700, 500, 6), (4096, 4096, 5900, 7), (2500, 640, 1300, 40), (500, 2400, 130, 300)])
 def test_calls_that_take_them_by_default(tsvd, M, N, K, B):  # noqa: F811
-    """Five planes on small factors (error of fp32 sums), three beyond; the same bits for either layout of x and y, and replayed from a
+    """Five planes on small factors (error of fp32 sums), four beyond; the same bits for either layout of x and y, and replayed from a
     captured graph."""
     import torch
     i = workloads.make_inputs(M, N, K, B, 0.6, 0.02, "bf16", seed=M + B)
@@ -60,7 +61,7 @@ def test_calls_that_take_them_by_default(tsvd, M, N, K, B):  # noqa: F811
     x = to_device(i)
     print(f"case few by default {M} {N} {K} {B}", flush=True)
     y = tsvd.tsvd_forward(h, x)
-    assert rel_err(y.cpu().numpy().astype(np.float64), ref) <= (1e-6 if B <= 6 else 1e-4)
+    assert rel_err(y.cpu().numpy().astype(np.float64), ref) <= (1e-6 if B <= 6 else 1e-5)
     yt = tsvd.tsvd_forward_io(h, x.t().contiguous(), x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR)
     assert torch.equal(yt.t(), y)
     ws = torch.empty(tsvd.tsvd_workspace_bytes(h, B, tsvd.TSVD_BF16), dtype=torch.uint8, device="cuda:0")
@@ -75,4 +76,35 @@ def test_calls_that_take_them_by_default(tsvd, M, N, K, B):  # noqa: F811
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, y)
+    tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("M,N,K,B,switch", [(256, 640, 500, 16, 64), (200, 700, 1300, 40, 64), (512, 4096, 7000, 16, None)])
+def test_ranks_beside_those_of_massive_outliers(tsvd, M, N, K, B, switch):  # noqa: F811
+    """Three features 2000 times the rest, seen by half of the ranks, these among the others; rows of y that use only the others.  z of four planes is off by
+    2^-20 of the largest of 32 neighbours at most (here: of 128), and has to keep what 11 bits of each value would."""
+    import torch
+    rng = np.random.default_rng(M + K)
+    U, V = (rng.choice([-1, 0, 1], size=s, p=[0.25, 0.5, 0.25]).astype(np.int8) for s in ((M, K), (K, N)))
+    S = np.abs(rng.standard_normal(K)).astype(np.float32)
+    massive, free, rows = [3, N // 3, N // 2 + 1], rng.permutation(K)[:K // 2], M // 2
+    V[np.ix_(free, massive)] = 0
+    U[:rows, np.setdiff1d(np.arange(K), free)] = 0
+    x = rng.standard_normal((B, N))
+    x[:, massive] *= 2000.0
+    xd = torch.from_numpy(x).to("cuda:0").to(torch.bfloat16)
+    x = xd.double().cpu().numpy()
+    h = tsvd.tsvd_pack(U, S, V)
+    if switch:
+        tsvd.tsvd_tuning_set("TSVD_FEW", switch)
+    print(f"case few beside outliers {M} {N} {K} {B}", flush=True)
+    y = tsvd.tsvd_forward_io(h, xd, x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR).cpu().numpy().astype(np.float64)
+    z = (x @ V.T.astype(np.float64)) * S
+    want = z @ U.T.astype(np.float64)
+    pad = np.pad(np.abs(z), ((0, 0), (0, -K % 128)))
+    e2 = (2.0 ** -20 * np.repeat(pad.reshape(B, -1, 128).max(axis=2), 128, axis=1)[:, :K]) ** 2
+    bound, size = np.sqrt(e2 @ (U != 0).T)[:, :rows], np.linalg.norm(want[:, :rows])
+    err = np.linalg.norm((y - want)[:, :rows])
+    assert err <= np.linalg.norm(bound) + 1e-6 * size
+    assert err <= 2.0 ** -12 * size
     tsvd.tsvd_free(h)

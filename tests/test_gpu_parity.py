@@ -836,7 +836,7 @@ def test_fp6_tail_tiles(tsvd, M, K):
     y1, h = run_forward(j)
     tsvd.tsvd_free(h)
     assert not np.isnan(y1).any()
-    assert rel_err(y1[:, cols], ref) <= 1e-4            # (three planes, z never rounded to 16 bits)
+    assert rel_err(y1[:, cols], ref) <= 1e-4            # (planes, z never rounded to 16 bits)
     tsvd.tsvd_tuning_set("TSVD_FP6_TAIL", 0)
     y0, h = run_forward(j)
     tsvd.tsvd_free(h)
