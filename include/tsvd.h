@@ -138,7 +138,8 @@ tsvd_status tsvd_dense_unpack_host(const void* blob, size_t blob_bytes, int8_t* 
  *     - x as it is, z in FOUR planes (what B <= 16 takes): z goes from fp32 sums into planes that hold it to 2^-19 of the largest magnitude among
  *       32 neighbours.  Error: 2e-3 of max|y| at most (measured 7e-7).  Rows of y that use only ranks without a feature far larger than the rest,
  *       where such ranks stand beside others: 3e-6 to 6e-6 of their own norm at 200 times the rest, 3e-5 to 6e-5 at 2000 times.
- *     - planes: fp4 codes times three fp6 (E2M3) planes with block scales, of x and z or of z alone.  They hold a value to 2^-14
+ *     - planes: fp4 codes times three fp6 (E2M3) planes with block scales, of x and z or of z alone (large batches with N <= 1280 that would
+ *       otherwise have x as it is: six planes of x, which hold a bf16 value down to 2^-29 of that magnitude).  They hold a value to 2^-14
  *       of the largest magnitude among 32 neighbours of the contraction (bf16 values of at least 2^-7 of that magnitude exactly,
  *       smaller ones to 2^-15 of it); z goes from fp32 sums into its planes where x is on planes too, else through fp16 as above.
  *       Error: 2e-3 of max|y| at most (measured 2e-5 .. 5e-5; 2.0e-4 .. 2.4e-4 through fp16).  This is relative to

@@ -27,7 +27,7 @@ extern "C" {
  *   14..17 ring kernel), TSVD_FUSEMAX, TSVD_COLMAX_SCALAR, TSVD_REALIGN, TSVD_PANEL, TSVD_PANEL_WAVES,
  *   TSVD_GEMM_MIN_B_F32 (fewest tokens of fp32 activations that take the batched kernels, default 17),
  *   TSVD_PANEL_FP6 (0: the token-panel launch on 16-bit operands instead of fp4 codes x fp6 planes),
- *   TSVD_FP6, TSVD_FP6_V, TSVD_FP6_TALL, TSVD_FP6_PLANES (2: two instead of three fp6 planes -- about five
+ *   TSVD_FP6, TSVD_FP6_V (2: six planes of x), TSVD_FP6_TALL, TSVD_FP6_PLANES (2: two instead of three fp6 planes -- about five
  *   times the error, inside the tolerance without margin; never a default), TSVD_FP6_DIRECT (0: the fp4 x fp6
  *   stage V always writes fp16 z for a separate pass to turn into planes), TSVD_FP6_TAIL (0: no narrower tiles in the
  *   last round of a launch of 512 x 64 tiles), TSVD_TOKEN_MAJOR_COPY (1: token-major

@@ -496,7 +496,8 @@ size_t gemm_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     size_t bytes = round256((size_t)(TSVD_COLMAX_PARTS + 1) * Bp * 4) + round256((size_t)h->hd.Kp * (size_t)Bp * 2);
     // (the rule is asked as for aligned rows: a caller with unaligned rows then reserves a little too much)
     if (tsvd_gemm_use_fp6(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count, true))      // planes of Z, and of X for stage V
-        bytes += round256(tsvd_gemm_fp6_bytes(h->hd.Kp, Bp)) + round256(tsvd_gemm_fp6_bytes(h->hd.Np, Bp));
+        bytes += round256(tsvd_gemm_fp6_bytes(h->hd.Kp, Bp)) +
+                 round256(tsvd_gemm_fp6_bytes((tsvd_gemm_x_twice(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count) ? 2 : 1) * h->hd.Np, Bp));
     // (asked as for the call that favours planes most)
     if (use_gemm(h, B, x_dtype)) {
         for (const bool tokens : {false, true})      // (either layout of x: their margins differ)

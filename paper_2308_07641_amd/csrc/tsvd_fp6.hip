@@ -38,9 +38,10 @@ namespace {
 // wavefront); a 512 x 128 tile with 256 indices per barrier (register spills, 2.0 ms); a raised wavefront
 // priority (s_setprio 1 or 2) during the MFMA steps of a block (1.51 against 1.49 - 1.50 ms).
 // The operand pass for token-major bf16 activations x [cols_valid tokens][ld]: no transposition through LDS, a lane's
-// values are contiguous in memory.  Same grid and records as tsvd_z_planes_kernel.
+// values are contiguous in memory.  Same grid and records as tsvd_z_planes_kernel; second: blocks from a record to that of a second set of
+// planes, for what the first leaves (0: none).
 __global__ void __launch_bounds__(512)
-tsvd_x_planes_token_major_kernel(const uint16_t* __restrict__ x, long long ld, int rows_valid, int cols_valid, int nblocks,
+tsvd_x_planes_token_major_kernel(const uint16_t* __restrict__ x, long long ld, int rows_valid, int cols_valid, int nblocks, int second,
                                  unsigned char* __restrict__ planes) {
     const int tt = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     const int tok = blockIdx.x * 128 + tt * 16 + i;
@@ -50,7 +51,9 @@ tsvd_x_planes_token_major_kernel(const uint16_t* __restrict__ x, long long ld, i
 #pragma unroll
     for (int e = 0; e < 32; ++e)
         if (tok >= cols_valid) v[e] = 0.f;
-    tsvd_planes_of_32(v, planes + ((size_t)(blockIdx.x * nblocks + blockIdx.y) * 8 + tt) * FP6_REC_BYTES, lane);
+    unsigned char* rec = planes + ((size_t)(blockIdx.x * nblocks + blockIdx.y) * 8 + tt) * FP6_REC_BYTES;
+    if (!second) tsvd_planes_of_32(v, rec, lane);
+    else tsvd_planes_of_32_twice(v, rec, rec + (size_t)second * 8 * FP6_REC_BYTES, lane);
 }
 
 // grid (Bp / 128, Kp / 128), block 512 = 8 tiles x 64 lanes.  The [128 indices][128 tokens] block of Z
@@ -59,7 +62,7 @@ tsvd_x_planes_token_major_kernel(const uint16_t* __restrict__ x, long long ld, i
 // different rows, fall on different banks).
 template <bool BF16>
 __global__ void __launch_bounds__(512)
-tsvd_z_planes_kernel(const uint16_t* __restrict__ Z, long long ld, int rows_valid, int cols_valid, int nblocks,
+tsvd_z_planes_kernel(const uint16_t* __restrict__ Z, long long ld, int rows_valid, int cols_valid, int nblocks, int second,
                      unsigned char* __restrict__ planes) {
     __shared__ uint32_t zt[128 * 65];                 // [index][token pair], pitch 65 words
     const int tt = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
@@ -92,7 +95,9 @@ tsvd_z_planes_kernel(const uint16_t* __restrict__ Z, long long ld, int rows_vali
         const uint16_t h = (tok & 1) ? (uint16_t)(w >> 16) : (uint16_t)(w & 0xFFFFu);
         v[e] = BF16 ? __uint_as_float((uint32_t)h << 16) : (float)__builtin_bit_cast(_Float16, h);
     }
-    tsvd_planes_of_32(v, planes + ((size_t)(blockIdx.x * nblocks + blockIdx.y) * 8 + tt) * FP6_REC_BYTES, lane);
+    unsigned char* rec = planes + ((size_t)(blockIdx.x * nblocks + blockIdx.y) * 8 + tt) * FP6_REC_BYTES;
+    if (!BF16 || !second) tsvd_planes_of_32(v, rec, lane);
+    else tsvd_planes_of_32_twice(v, rec, rec + (size_t)second * 8 * FP6_REC_BYTES, lane);
 }
 
 // WM x WN = 2 x 2 wavefronts (256 rows x 128 tokens per workgroup) or 4 x 1 (512 x 64) of TM x 4 = 8 x 4 blocks
@@ -727,24 +732,33 @@ bool tsvd_gemm_use_fp6(long long Mp, long long Kp, long long Np, long long B, lo
 }
 
 // The same for stage V (planes of x), only together with the fp6 stage U (the workspace holds both
-// sets of planes then): TSVD_FP6_V = 0 never, 1 whenever possible, default by the rule of stage U
+// sets of planes then): TSVD_FP6_V = 0 never, 1 or 2 whenever possible, default by the rule of stage U
 // applied to stage V's own sizes.
 bool tsvd_gemm_use_fp6_v(long long Mp, long long Kp, long long Np, long long B, long long cus, bool aligned) {
     if (!aligned || !tsvd_gemm_use_fp6(Mp, Kp, Np, B, cus, aligned)) return false;
     const int mode = tsvd_tune("TSVD_FP6_V", -1);
     const long long Bp = tsvd_round_up(B, 256);
-    if (mode == 0 || tsvd_gemm_fp6_bytes(Np, Bp) >= (1ull << 31)) return false;
-    if (mode == 1) return true;
+    if (mode == 0 || tsvd_gemm_fp6_bytes(Np < 2048 || mode == 2 ? 2 * Np : Np, Bp) >= (1ull << 31)) return false;
+    if (mode >= 1) return true;
     // With a 256 x 128 tile for every compute unit (where stage V would run on the large-tile kernel): measured
     // 18432 x 9216 at 2048 tokens 480 -> 17 + 406 us.  With fewer tiles stage V would run on the ring kernel, which
     // has its column maxima fused in; planes, a separate column-maximum launch and 128 x 64 or 256 x 64 tiles beat
     // it for contractions of 4096 (whole call 97 -> 92 us on 16384 x 4096 x 8192 at 256 tokens, 73 -> 68 us on
     // 8192 x 4096 x 4096 at 512) but not of 3072 (64 -> 70 us on 12288 x 3072 x 6144 at 256) or 2048 (58 -> 58 us)
-    // With those tiles and planes of z straight from stage V (no fp16 z, no column maxima, no pass over z) short contractions gain
-    // too: 27 calls of N 96 to 1962 0.80 to 0.99 of the time (6259 ranks x 384 at 8007 tokens 454 -> 405 us, 3403 x 96 at 6592 317 -> 294)
+    // Short contractions, with those tiles and planes of z straight from stage V (no fp16 z, no column maxima, no pass over z): on six planes of x, as
+    // three leave 2^-15 of a feature that stands out in every one of its 31 neighbours, where 16-bit operands have x exactly (rows of y
+    // that avoid a feature 2000 times the rest: 4e-3 off on three planes, 2e-5 on six, 2.1e-4 on 16-bit operands).  Against those, rows of features / rows of
+    // tokens: 0.91 / 0.91 of the time at N = 96, 0.96 / 0.95 at 384, 0.95 / 0.93 at 768, 0.98 / 0.91 at 1024, 1.02 / 0.93 at 1300, 1.04 / 0.99 at 1500, 1.18 / 0.92
+    // at 1700 (600 .. 5000 rows, 2048 .. 8000 ranks, 6592 .. 16384 tokens; three planes 0.76 to 0.92).
     const bool tiles = (Kp / 256) * ((B + 127) / 128) >= cus;
-    if (tiles && tsvd_fp6_direct_possible(Kp, B, cus)) return true;
+    if (tiles && Np <= 1280 && tsvd_fp6_direct_possible(Kp, B, cus)) return true;      // (tsvd_gemm_x_twice)
     return (Np >= 2048 && tiles) || (Np >= 4096 && (Kp / 128) * ((B + 63) / 64) >= cus);
+}
+
+// Whether stage V on planes takes six planes of x (three, and three for what those leave).  TSVD_FP6_V = 2: wherever possible.
+bool tsvd_gemm_x_twice(long long Mp, long long Kp, long long Np, long long B, long long cus) {
+    const int mode = tsvd_tune("TSVD_FP6_V", -1);
+    return (mode == 2 || (mode < 0 && Np < 2048)) && tsvd_gemm_use_fp6_v(Mp, Kp, Np, B, cus, true) && tsvd_fp6_direct_possible(Kp, B, cus);
 }
 
 template <int WM, int WN>
@@ -859,14 +873,14 @@ hipError_t tsvd_fp6_launch_direct(const gemm_args& a, long long rows_p, long lon
 }
 
 hipError_t tsvd_fp6_launch_planes(bool bf16, const uint16_t* src, long long ld, int rows_valid, int cols_valid, int nblocks_per_group,
-                                  int blocks, long long B, unsigned char* planes, hipStream_t stream, bool token_major) {
+                                  int blocks, long long B, unsigned char* planes, hipStream_t stream, bool token_major, int second) {
     const dim3 grid((unsigned)((B + 127) / 128), (unsigned)blocks), block(512);
     if (token_major) {       // (bf16 x, one row per token)
-        hipLaunchKernelGGL(tsvd_x_planes_token_major_kernel, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, planes);
+        hipLaunchKernelGGL(tsvd_x_planes_token_major_kernel, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, second, planes);
         return hipGetLastError();
     }
-    if (bf16) hipLaunchKernelGGL(tsvd_z_planes_kernel<true>, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, planes);
-    else hipLaunchKernelGGL(tsvd_z_planes_kernel<false>, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, planes);
+    if (bf16) hipLaunchKernelGGL(tsvd_z_planes_kernel<true>, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, second, planes);
+    else hipLaunchKernelGGL(tsvd_z_planes_kernel<false>, grid, block, 0, stream, src, ld, rows_valid, cols_valid, nblocks_per_group, 0, planes);
     return hipGetLastError();
 }
 

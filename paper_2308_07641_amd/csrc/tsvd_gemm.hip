@@ -1534,11 +1534,16 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
     if ((mask & 2) && fp6_v) {
         unsigned char* xplanes = reinterpret_cast<unsigned char*>(Z) + (((size_t)hd.Kp * Bp * 2 + 255) & ~(size_t)255) +
                                  ((tsvd_gemm_fp6_bytes(hd.Kp, Bp) + 255) & ~(size_t)255);
-        if ((e = tsvd_fp6_launch_planes(true, static_cast<const uint16_t*>(g.x), (long long)g.ldx, (int)hd.N, (int)g.B, (int)(hd.Np / 128),
-                                        a1.npairs, g.B, xplanes, stream, g.x_token_major != 0)) != hipSuccess) return e;
+        const bool twice = tsvd_gemm_x_twice(hd.Mp, hd.Kp, hd.Np, g.B, g.cu_count);
         gemm_args a4 = a1;
         a4.act = reinterpret_cast<const uint16_t*>(xplanes);
-        a4.act_bytes = (unsigned)tsvd_gemm_fp6_bytes(hd.Np, Bp);
+        a4.act_bytes = (unsigned)tsvd_gemm_fp6_bytes((twice ? 2 : 1) * hd.Np, Bp);
+        if (twice) {                                   // (the second set behind the first: the same code words again)
+            a4.npairs = a4.plane_blocks = 2 * pairs_n;
+            a4.code_blocks = pairs_n;
+        }
+        if ((e = tsvd_fp6_launch_planes(true, static_cast<const uint16_t*>(g.x), (long long)g.ldx, (int)hd.N, (int)g.B, twice ? 2 * pairs_n : (int)(hd.Np / 128),
+                                        pairs_n, g.B, xplanes, stream, g.x_token_major != 0, twice ? pairs_n : 0)) != hipSuccess) return e;
         if (direct) {
             a4.out = reinterpret_cast<unsigned char*>(Z) + (((size_t)hd.Kp * Bp * 2 + 255) & ~(size_t)255);   // the planes of z
             a4.ld_out = hd.Kp / 128;                                                                       // blocks per token group

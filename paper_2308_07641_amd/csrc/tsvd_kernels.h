@@ -174,6 +174,8 @@ size_t tsvd_gemm_fp6_bytes(long long Kp, long long Bp);
 size_t tsvd_gemm_split_bytes(long long K, long long N, long long B, bool f32);
 // Stage V through fp6 planes of x (only together with the above; its planes follow those of Z).
 bool tsvd_gemm_use_fp6_v(long long Mp, long long Kp, long long Np, long long B, long long cus, bool aligned);
+// ... with a second set of planes of x, for what the first leaves, as further blocks of the contraction.
+bool tsvd_gemm_x_twice(long long Mp, long long Kp, long long Np, long long B, long long cus);
 #define TSVD_COLMAX_PARTS 16
 // Diagnostic switches (include/tsvd_tuning.h): value set by tsvd_tuning_set in this process, else the
 // fallback.  The library never reads the environment.

@@ -155,3 +155,44 @@ def test_rows_free_of_massive_outliers(tsvd, switches, outlier):
     assert np.linalg.norm(err) <= np.linalg.norm(bound) + 2.5e-4 * np.linalg.norm(want[:, :free_rows])
     assert rel_err(y, want) <= 1e-4                                                # the whole of y
     tsvd.tsvd_free(h)
+
+
+TWO_SETS = [{"TSVD_PANEL": 0, "TSVD_FP6": 1, "TSVD_FP6_V": 2, "TSVD_GEMM_CFG_V": 3, "TSVD_FP6_TALL": tall} for tall in (0, 1)]
+
+
+@pytest.mark.parametrize("switches", TWO_SETS, ids=str)
+@pytest.mark.parametrize("M,N,K,B", [(130, 64, 60, 65), (515, 300, 777, 130), (300, 129, 512, 47), (200, 1280, 1025, 129)])
+def test_stage_v_on_two_sets_of_planes(tsvd, M, N, K, B, switches):
+    """An odd and an even number of blocks, one and several, tokens beside a tile's multiple."""
+    print(f"case two sets {M} {N} {K} {B} {switches}", flush=True)
+    _check(tsvd, M, N, K, B, "bf16", switches)
+
+
+@pytest.mark.parametrize("outlier", [200.0, 2000.0, 30000.0])
+@pytest.mark.parametrize("M,N,K,B,switches", [(256, 640, 768, 130, TWO_SETS[0]), (256, 640, 768, 130, TWO_SETS[1]), (2048, 512, 2304, 8192, {})], ids=str)
+def test_large_batches_with_massive_outliers(tsvd, M, N, K, B, switches, outlier):
+    """Rows of y that use only ranks which avoid three features far above the rest, in blocks of their own: what is off there is z on
+    three planes, 2^-14 of a block's largest value, four times its rms at most; x counts as it is.  (The last call takes these kernels by itself.)"""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(int(outlier) + K)
+    U, V = (torch.randint(0, 4, s, generator=g, device="cuda:0").sub_(1).clamp_(max=1).double() for s in ((M, K), (K, N)))
+    U, V = U * torch.randint(0, 2, U.shape, generator=g, device="cuda:0"), V * torch.randint(0, 2, V.shape, generator=g, device="cuda:0")
+    S = torch.randn(K, generator=g, device="cuda:0", dtype=torch.float64).abs().float()
+    massive, free_ranks, free_rows = [3, 200, 333], K // 2, M // 2
+    V[:free_ranks, massive] = 0
+    U[:free_rows, free_ranks:] = 0
+    x = torch.randn((B, N), generator=g, device="cuda:0")
+    x[:, massive] *= outlier
+    x = x.to(torch.bfloat16)
+    h = tsvd.tsvd_pack(U.to(torch.int8).cpu().numpy(), S.cpu().numpy(), V.to(torch.int8).cpu().numpy())
+    for k, v in switches.items():
+        tsvd.tsvd_tuning_set(k, v)
+    print(f"case large batch, massive outliers {outlier} {switches}", flush=True)
+    want = ((x.double() @ V.t().contiguous()) * S.double()) @ U.t().contiguous()
+    y = tsvd.tsvd_forward_io(h, x, x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR).double()
+    assert (y - want)[:, :free_rows].norm() <= 2.5e-4 * want[:, :free_rows].norm()
+    y2 = tsvd.tsvd_forward(h, x.t().contiguous()).double().t()
+    assert (y2 - want)[:, :free_rows].norm() <= 2.5e-4 * want[:, :free_rows].norm()
+    assert (y - want).norm() <= 2.5e-4 * want.norm()
+    tsvd.tsvd_free(h)
