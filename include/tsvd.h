@@ -204,10 +204,11 @@ tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, tsvd_dtype 
  * fixed array of TSVD_NOALLOC_MAX_WORKSPACE bytes that the loaded library holds on every GPU it has
  * been used on, until the process ends.  The call allocates and frees nothing, on the host or on the
  * device, and takes no workspace argument; x, bias and y are the caller's as before.
- *   - TSVD_NOALLOC_MAX_WORKSPACE (16 MiB) holds any single-token or few-token call, and batched calls whose fp16
- *     z [K][B rounded up to 256] plus a copy of x fit, e.g. 512 tokens at K = 1536, N = 768 need 2.4 MB.  Where
- *     tsvd_workspace_bytes_ex(h, B, x_dtype, x_layout) is larger only for the planes of x and z, the call takes other kernels
- *     than tsvd_forward_ex: a bf16 batch those that keep z in 16 bits, an fp32 batch goes one token at a time as batches below 17
+ *   - TSVD_NOALLOC_MAX_WORKSPACE (16 MiB) holds any single-token call, calls of 2 to 16 tokens on up to 2^18 ranks (x token-major: where 32 bytes
+ *     for each rank and feature fit), and batched calls whose fp16 z [K][B rounded up to 256] plus a copy of x fit, e.g. 512 tokens at
+ *     K = 1536, N = 768 need 2.4 MB.  Where tsvd_workspace_bytes_ex(h, B, x_dtype, x_layout) is larger only for planes of x and z that the library
+ *     would estimate to be faster, a bf16 batch takes the kernels that it takes without those (large batches of long contractions
+ *     are on planes there too, other calls keep z in 16 bits), and an fp32 batch goes one token at a time as batches below 17
  *     tokens do.  The results then differ within the bounds stated above, and the speed too.
  *   - Returns TSVD_ETOOLARGE (nothing enqueued, y untouched) when that does not fit either.
  *   - All calls on one GPU share that GPU's array, whatever the handle or stream: calls that

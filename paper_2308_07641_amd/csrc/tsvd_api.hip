@@ -306,7 +306,7 @@ bool five_planes(const tsvd_handle* h) {
 // The planes of z of a call of up to 16 tokens on the few-token kernels (0: on others).
 int few_planes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, int64_t ldx, bool x_token_major) {
     const tsvd_blob_header& hd = h->hd;
-    // (Kp: the records have to fit the fixed workspace of tsvd_forward_noalloc, as z in 16 bits does)
+    // (Kp: the records, 50 or 64 bytes a rank, have to fit the fixed workspace of tsvd_forward_noalloc by themselves)
     if (x_dtype != TSVD_BF16 || B > 16 || hd.Kp > (1 << 18) || !tsvd_few_fits(hd, B, ldx, x_token_major)) return 0;
     if (tsvd_tuning_any()) return B <= env_int("TSVD_FEW", 0) ? (env_int("TSVD_FEW_PLANES", 4) == 5 ? 5 : 4) : 0;
     if (five_planes(h)) return 5;
@@ -502,8 +502,6 @@ size_t gemm_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     if (use_gemm(h, B, x_dtype)) {
         for (const bool tokens : {false, true})      // (either layout of x: their margins differ)
             if (batch_plan(h, B, x_dtype, tokens, true, false, false, true, false).split) bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
-        // (likewise: token-major y costs the panels more)
-        if (batch_plan(h, B, x_dtype, true, true, true, true, true, true).few) bytes = std::max(bytes, tsvd_few_bytes(h->hd.Kp, B, 4));
     }
     return bytes;
 }
@@ -639,10 +637,16 @@ extern "C" tsvd_status tsvd_info(const tsvd_handle* h, int64_t* M, int64_t* K, i
 }
 
 namespace {
+// What the few-token kernels on planes take, where a call may go to them: they read x in place, so this is not beside a copy of x.
+size_t few_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
+    if (x_dtype != TSVD_BF16) return 0;
+    if (B <= 16) return h->hd.Kp <= (1 << 18) ? round256(tsvd_few_bytes(h->hd.Kp, B, five_planes(h) || tsvd_tuning_any() ? 5 : 4)) : 0;
+    // (asked as for the call that favours them most: token-major y costs the panels more)
+    return use_gemm(h, B, x_dtype) && batch_plan(h, B, x_dtype, true, true, true, true, true, true).few ? round256(tsvd_few_bytes(h->hd.Kp, B, 4)) : 0;
+}
+// ... and all other kernels (which of them a call takes depends on the row stride too: cover every candidate).
 size_t base_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
-    // (the few-token path is chosen per call, by the row stride too: cover every candidate)
-    size_t few = round256(std::max(skinny_workspace(h, B), mid_workspace(h)));
-    if (x_dtype == TSVD_BF16 && B <= 16 && h->hd.Kp <= (1 << 18)) few = std::max(few, tsvd_few_bytes(h->hd.Kp, B, five_planes(h) || tsvd_tuning_any() ? 5 : 4));
+    const size_t few = round256(std::max(skinny_workspace(h, B), mid_workspace(h)));
     if (use_gemm(h, B, x_dtype)) return std::max(gemm_workspace(h, B, x_dtype), B <= 64 ? few : (size_t)0);
     return few;
 }
@@ -660,7 +664,7 @@ extern "C" size_t tsvd_workspace_bytes_ex(const tsvd_handle* h, int64_t B, tsvd_
     // (feature-major rows that are not 16-byte aligned are copied too, when the call goes to the batched kernels:
     // the alignment is not known here, so the room is always there)
     const bool copy = x_layout == TSVD_TOKEN_MAJOR || use_gemm(h, B, x_dtype) || realigns_few(h, B, x_dtype);
-    return base_workspace(h, B, x_dtype) + (copy ? transposed_bytes(h, B, x_dtype) : 0);
+    return std::max(base_workspace(h, B, x_dtype) + (copy ? transposed_bytes(h, B, x_dtype) : 0), few_workspace(h, B, x_dtype));
 }
 
 extern "C" size_t tsvd_workspace_bytes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {

@@ -97,3 +97,23 @@ def test_noalloc_fp32_batches():
     torch.cuda.synchronize()
     assert rel_err(y.cpu().numpy().astype(np.float64), oracle.forward(i.U, i.S, i.V, i.X)) <= 1e-5
     tsvd.tsvd_free(h)
+
+
+def test_noalloc_takes_few_tokens_of_very_many_features():
+    """x token-major: the kernels that take it read it in place, so their planes of z need no room beside a copy of x.  (Both together are beyond the
+    16 MiB here; z in 16 bits beside a copy is not.)"""
+    import torch
+    import paper_2308_07641_amd as tsvd
+    M, N, K, B = 64, 524000, 250, 16
+    rng = np.random.default_rng(940)
+    U, V = rng.integers(-1, 2, (M, K), dtype=np.int8), rng.integers(-1, 2, (K, N), dtype=np.int8)
+    S = rng.random(K, dtype=np.float32)
+    h = tsvd.tsvd_pack(U, S, V)
+    print(f"case noalloc {M} {N} {K} {B}", flush=True)
+    assert tsvd.tsvd_workspace_bytes_ex(h, B, tsvd.TSVD_BF16, tsvd.TSVD_TOKEN_MAJOR) <= tsvd.TSVD_NOALLOC_MAX_WORKSPACE
+    x = torch.randn((B, N), generator=torch.Generator().manual_seed(941)).to(torch.bfloat16).to("cuda:0")
+    y = tsvd.tsvd_forward_noalloc(h, x, torch.full((M, B), float("nan"), device="cuda:0"), x_layout=tsvd.TSVD_TOKEN_MAJOR)
+    z = torch.from_numpy(V).to("cuda:0").double() @ x.double().t().contiguous() * torch.from_numpy(S).to("cuda:0").double()[:, None]
+    ref = (torch.from_numpy(U).to("cuda:0").double() @ z).cpu().numpy()
+    assert rel_err(y.cpu().numpy().astype(np.float64), ref) <= 1e-5
+    tsvd.tsvd_free(h)
