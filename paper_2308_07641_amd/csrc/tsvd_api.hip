@@ -475,7 +475,7 @@ thread_local bool planes_only_by_older_rules = false;
 
 // How a batched call runs that the few-token kernels leave.  copies: x would have to be copied for the kernels that read aligned
 // feature-major rows.
-tsvd_batch_plan batch_plan(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, bool x_token_major, bool copies, bool y_token_major, bool out_bf16,
+tsvd_batch_call batch_call(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, bool x_token_major, bool copies, bool y_token_major, bool out_bf16,
                            bool x_aligned, bool few) {
     tsvd_batch_call c = {};
     c.M = h->hd.M; c.K = h->hd.K; c.N = h->hd.N; c.B = B; c.cus = h->cu_count;
@@ -484,6 +484,9 @@ tsvd_batch_plan batch_plan(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, 
     c.whole = tsvd_stage_mask() == 7;
     c.x_aligned = x_aligned;
     c.few = few && !c.f32 && !planes_only_by_older_rules;
+    return c;
+}
+tsvd_batch_plan batch_plan(const tsvd_batch_call& c) {
     tsvd_batch_plan plan = tsvd_plan_batch(c);
     if (planes_only_by_older_rules && !c.f32) plan.split = false;
     return plan;
@@ -499,9 +502,9 @@ size_t gemm_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
         bytes += round256(tsvd_gemm_fp6_bytes(h->hd.Kp, Bp)) +
                  round256(tsvd_gemm_fp6_bytes((tsvd_gemm_x_twice(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count) ? 2 : 1) * h->hd.Np, Bp));
     // (asked as for the call that favours planes most)
-    if (use_gemm(h, B, x_dtype)) {
-        for (const bool tokens : {false, true})      // (either layout of x: their margins differ)
-            if (batch_plan(h, B, x_dtype, tokens, true, false, false, true, false).split) bytes = std::max(bytes, tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false));
+    if (use_gemm(h, B, x_dtype) && !planes_only_by_older_rules) {
+        const size_t split = tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false);
+        if (split > bytes && tsvd_batch_may_split(batch_call(h, B, x_dtype, false, true, false, false, true, false))) bytes = split;
     }
     return bytes;
 }
@@ -637,12 +640,13 @@ extern "C" tsvd_status tsvd_info(const tsvd_handle* h, int64_t* M, int64_t* K, i
 }
 
 namespace {
-// What the few-token kernels on planes take, where a call may go to them: they read x in place, so this is not beside a copy of x.
-size_t few_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
+// What the few-token kernels on planes take, where a call may go to them and it is more than `others`: they read x in place, so this is not beside a copy of x.
+size_t few_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, size_t others) {
     if (x_dtype != TSVD_BF16) return 0;
     if (B <= 16) return h->hd.Kp <= (1 << 18) ? round256(tsvd_few_bytes(h->hd.Kp, B, five_planes(h) || tsvd_tuning_any() ? 5 : 4)) : 0;
+    const size_t bytes = round256(tsvd_few_bytes(h->hd.Kp, B, 4));
     // (asked as for the call that favours them most: token-major y costs the panels more)
-    return use_gemm(h, B, x_dtype) && batch_plan(h, B, x_dtype, true, true, true, true, true, true).few ? round256(tsvd_few_bytes(h->hd.Kp, B, 4)) : 0;
+    return use_gemm(h, B, x_dtype) && bytes > others && batch_plan(batch_call(h, B, x_dtype, true, true, true, true, true, true)).few ? bytes : 0;
 }
 // ... and all other kernels (which of them a call takes depends on the row stride too: cover every candidate).
 size_t base_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
@@ -664,7 +668,8 @@ extern "C" size_t tsvd_workspace_bytes_ex(const tsvd_handle* h, int64_t B, tsvd_
     // (feature-major rows that are not 16-byte aligned are copied too, when the call goes to the batched kernels:
     // the alignment is not known here, so the room is always there)
     const bool copy = x_layout == TSVD_TOKEN_MAJOR || use_gemm(h, B, x_dtype) || realigns_few(h, B, x_dtype);
-    return std::max(base_workspace(h, B, x_dtype) + (copy ? transposed_bytes(h, B, x_dtype) : 0), few_workspace(h, B, x_dtype));
+    const size_t others = base_workspace(h, B, x_dtype) + (copy ? transposed_bytes(h, B, x_dtype) : 0);
+    return std::max(others, few_workspace(h, B, x_dtype, others));
 }
 
 extern "C" size_t tsvd_workspace_bytes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
@@ -738,8 +743,8 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
     const bool few = !z_planes && !z_as_fp32(h, B, x_dtype) && use_mid(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR || realign ? tsvd_round_up(B, 8) : ldx);
     tsvd_batch_plan plan = {};
     if (batched && !few)
-        plan = batch_plan(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16, !misaligned,
-                          tsvd_few_fits(h->hd, B, ldx, x_layout == TSVD_TOKEN_MAJOR) && tsvd_few_bytes(h->hd.Kp, B, 4) <= need);
+        plan = batch_plan(batch_call(h, B, x_dtype, x_layout == TSVD_TOKEN_MAJOR, x_layout == TSVD_TOKEN_MAJOR || misaligned, oo.token_major, oo.out_bf16, !misaligned,
+                                     tsvd_few_fits(h->hd, B, ldx, x_layout == TSVD_TOKEN_MAJOR) && tsvd_few_bytes(h->hd.Kp, B, 4) <= need));
     if (plan.split && x_dtype == TSVD_BF16 && tsvd_gemm_split_bytes(h->hd.K, h->hd.N, B, false) > need) plan.split = false;   // (never more than was asked for)
     if (z_planes || plan.few) {
         // few tokens: x in any layout and alignment, planes of z in the workspace
@@ -909,7 +914,7 @@ extern "C" int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* s
     *shape_v = *shape_u = -1;
     if (B <= 16 || use_mid(h, B, TSVD_BF16, tsvd_round_up(B, 8))) return 0;
     if (use_gemm(h, B, TSVD_BF16)) {
-        const tsvd_batch_plan plan = batch_plan(h, B, TSVD_BF16, false, false, false, false, true, true);
+        const tsvd_batch_plan plan = batch_plan(batch_call(h, B, TSVD_BF16, false, false, false, false, true, true));
         if (plan.few) return 0;
         if (plan.thin) {
             *shape_v = *shape_u = 34;

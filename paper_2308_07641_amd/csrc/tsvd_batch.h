@@ -17,3 +17,5 @@ struct tsvd_batch_plan {
     int split_v, split_u;           // ... with these shapes of tsvd_fp6_split_launch, 0: the launches of tsvd_fp6.hip
 };
 tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c);
+// Whether such a call is on the plane path in either layout of x (their margins differ).
+bool tsvd_batch_may_split(tsvd_batch_call c);

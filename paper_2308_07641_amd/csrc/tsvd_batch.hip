@@ -129,12 +129,59 @@ double panel_cost(const tsvd_batch_call& c) {
     return 0.95 * r * (7.5 + 2.3 * (double)nvb + 1.8 * (double)(up(strips, 8) * nub) + (double)strips * (c.y_token_major ? 1.9 : 0.83));
 }
 
+// The shapes of the plane path's stages, 0 each for the tiles of tsvd_fp6.hip.
+struct tiles_choice {
+    int v, u;
+    double time, fp6_tiles;         // with these shapes; with 0 and 0
+};
+tiles_choice choose_tiles(const tsvd_batch_call& c) {
+    const sizes s = {c.M, c.N, c.B, c.cus, up(c.N, 128), up(c.K, 128), c.f32 ? 2 : 1};
+    double best_v = split_v_cost(s, nullptr), best_u = split_u_cost(s, nullptr);
+    tiles_choice t = {0, 0, 0, best_v + best_u};
+    for (const split_factors& f : split_table) {
+        const double cv = split_v_cost(s, &f), cu = split_u_cost(s, &f);
+        if (cv < best_v) best_v = cv, t.v = f.shape;
+        if (cu < best_u) best_u = cu, t.u = f.shape;
+    }
+    t.time = best_v + best_u;
+    return t;
+}
+// The columns of a convolution, written first.
+double columns_cost(const tsvd_batch_call& c) { return c.conv ? 6.0 + 1.3 * (double)c.N * (double)c.B / 1e6 : 0; }
+bool takes_panel(const tsvd_batch_call& c) {
+    return c.whole && tsvd_gemm_use_panel(tsvd_round_up(c.M, 256), tsvd_round_up(c.K, 256), tsvd_round_up(c.N, 256), c.B, c.cus, true);
+}
+// Another way replaces the older one only where its estimate is below this: a tenth less, the estimates' own error (a twentieth for rows of tokens: on 150
+// such calls of 513 to 16384 tokens that the factors are not fitted to, 0.97 of the time of the choices made by the factors from before
+// rows were read and written at any alignment; feature-major calls gain nothing by a new fit).  Where an older call runs on planes of x
+// too, its estimate is that of the same tiles; where stage V is on 16-bit operands it has a pass over z, and x copied.
+double to_beat(const tsvd_batch_call& c, double fp6_tiles, bool panel) {
+    const long long Mp = tsvd_round_up(c.M, 256), Kp = tsvd_round_up(c.K, 256), Np = tsvd_round_up(c.N, 256);
+    return (c.conv || panel ? 1.0 : c.x_token_major ? 0.95 : 0.9) *
+           (panel ? panel_cost(c) + columns_cost(c)
+            : !tsvd_gemm_use_fp6(Mp, Kp, Np, c.B, c.cus, true) ? older_cost(c)
+            : c.x_token_major && !tsvd_gemm_reads_in_place(Mp, Kp, Np, c.B, c.cus) ? 1.15 * fp6_tiles + copy_cost(c) : fp6_tiles + columns_cost(c));
+}
+bool splits(const tsvd_batch_call& c, const tiles_choice& t, bool panel, double beat) {
+    return !panel && (t.v || t.u) && t.time + columns_cost(c) < beat && tsvd_gemm_split_bytes(c.K, c.N, c.B, false) < (1ull << 31);
+}
+
 }  // namespace
 
 size_t tsvd_gemm_split_bytes(long long K, long long N, long long B, bool f32) {
     const long long sets = f32 ? 2 : 1, Bp = tsvd_round_up(B, f32 ? 256 : 128);
     auto part = [&](long long len) { return (tsvd_gemm_fp6_bytes(128 * sets * up(len, 128), Bp) + 255) & ~(size_t)255; };
     return part(N) + part(K);
+}
+
+bool tsvd_batch_may_split(tsvd_batch_call c) {
+    const bool panel = takes_panel(c);
+    const tiles_choice t = choose_tiles(c);
+    for (const bool tokens : {false, true}) {
+        c.x_token_major = tokens;
+        if (tsvd_tuning_any() ? tsvd_plan_batch(c).split : splits(c, t, panel, to_beat(c, t.fp6_tiles, panel))) return true;
+    }
+    return false;
 }
 
 tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
@@ -146,35 +193,17 @@ tsvd_batch_plan tsvd_plan_batch(const tsvd_batch_call& c) {
         if (v > 0 || u > 0) plan = {false, plan.thin, true, v, u};
         return plan;
     }
-    const long long Mp = tsvd_round_up(c.M, 256), Kp = tsvd_round_up(c.K, 256), Np = tsvd_round_up(c.N, 256);
-    const sizes s = {c.M, c.N, c.B, c.cus, up(c.N, 128), up(c.K, 128), c.f32 ? 2 : 1};
-    double best_v = split_v_cost(s, nullptr), best_u = split_u_cost(s, nullptr);
-    const double fp6_tiles = best_v + best_u;
-    int v = 0, u = 0;
-    for (const split_factors& f : split_table) {
-        const double cv = split_v_cost(s, &f), cu = split_u_cost(s, &f);
-        if (cv < best_v) best_v = cv, v = f.shape;
-        if (cu < best_u) best_u = cu, u = f.shape;
-    }
+    const tiles_choice t = choose_tiles(c);
     if (c.f32) {
-        plan.split_v = v;
-        plan.split_u = u;
+        plan.split_v = t.v;
+        plan.split_u = t.u;
         return plan;
     }
-    // Another way replaces the older one only where its estimate is a tenth smaller, the estimates' own error (a twentieth for rows of tokens: on 150
-    // such calls of 513 to 16384 tokens that the factors are not fitted to, 0.97 of the time of the choices made by the factors from before
-    // rows were read and written at any alignment; feature-major calls gain nothing by a new fit).  Where an older call runs on planes of x
-    // too, its estimate is that of the same tiles; where stage V is on 16-bit operands it has a pass over z, and x copied.
-    const double columns = c.conv ? 6.0 + 1.3 * (double)c.N * (double)c.B / 1e6 : 0;
-    const bool panel = c.whole && tsvd_gemm_use_panel(Mp, Kp, Np, c.B, c.cus, true);
-    double best = (c.conv || panel ? 1.0 : c.x_token_major ? 0.95 : 0.9) *
-                  (panel ? panel_cost(c) + columns
-                   : !tsvd_gemm_use_fp6(Mp, Kp, Np, c.B, c.cus, true) ? older_cost(c)
-                   : c.x_token_major && !tsvd_gemm_reads_in_place(Mp, Kp, Np, c.B, c.cus) ? 1.15 * fp6_tiles + copy_cost(c) : fp6_tiles + columns);
-    const bool fits = !panel && tsvd_gemm_split_bytes(c.K, c.N, c.B, false) < (1ull << 31);
-    if (fits && (v || u) && best_v + best_u + columns < best) {
-        best = best_v + best_u + columns;
-        plan = {false, 0, true, v, u};
+    const bool panel = takes_panel(c);
+    double best = to_beat(c, t.fp6_tiles, panel);
+    if (splits(c, t, panel, best)) {
+        best = t.time + columns_cost(c);
+        plan = {false, 0, true, t.v, t.u};
     }
     // (every panel streams both factors: measured for code words that one XCD's L2 holds)
     if (c.whole && c.K * (c.M + c.N) <= (16ll << 20))
