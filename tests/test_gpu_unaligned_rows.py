@@ -62,3 +62,72 @@ def test_workspace_of_rows_of_tokens_is_enough(tsvd, M, N, K, B):  # noqa: F811
     assert (ws[need:] == 93).all()
     assert torch.equal(y.cpu(), ref)
     tsvd.tsvd_free(h)
+
+
+# (beside those: the single-token kernels, slabs, few tokens, ring and large tiles, narrow tiles on planes, six planes of x, the 16-bit token panel)
+MORE_ROUTES = [{}, {"TSVD_GEMV": 0, "TSVD_MID": 1}, {"TSVD_FEW": 64}, {"TSVD_PANEL": 0, "TSVD_GEMM_CFG_U": 14, "TSVD_GEMM_CFG_V": 15}, {"TSVD_PANEL": 0, "TSVD_GEMM_CFG_U": 16, "TSVD_GEMM_CFG_V": 16},
+               {"TSVD_PANEL": 0, "TSVD_GEMM_CFG_U": 0, "TSVD_GEMM_CFG_V": 1}, {"TSVD_PANEL": 0, "TSVD_GEMM_CFG_U": 2, "TSVD_GEMM_CFG_V": 3},
+               {"TSVD_PANEL": 0, "TSVD_FP6": 1, "TSVD_FP6_V": 1, "TSVD_GEMM_CFG_V": 3, "TSVD_FP6_TALL": 3}, {"TSVD_PANEL": 0, "TSVD_FP6": 1, "TSVD_FP6_V": 2, "TSVD_GEMM_CFG_V": 3, "TSVD_FP6_TALL": 1},
+               {"TSVD_PANEL": 1, "TSVD_PANEL_FP6": 0}]
+
+
+@pytest.mark.parametrize("M,N,K,B", [(66, 8, 70, 40), (131, 127, 60, 33), (257, 251, 200, 136), (520, 64, 300, 16), (300, 100, 80, 1)])
+@pytest.mark.parametrize("route", ROUTES + MORE_ROUTES, ids=str)
+def test_what_lies_behind_y_stays(tsvd, M, N, K, B, route):  # noqa: F811
+    """Rows of tiles beyond y's last row, and tokens beyond the last token, are not stored: what lies there in memory keeps its mark.  (Tests beside the columns of y
+    do not show this: stores without a test of the row rest on the range of a buffer that ends with y.)"""
+    import torch
+    i = workloads.make_integer_inputs(M, N, K, B, 0.5, "bf16", seed=M + N + K + B)
+    ref = torch.from_numpy(np.ascontiguousarray(oracle.forward(i.U, i.S, i.V, i.X)))
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    for k, v in route.items():
+        tsvd.tsvd_tuning_set(k, v)
+    x = to_device(i)
+    for out, code in ((torch.float32, tsvd.TSVD_F32), (torch.bfloat16, tsvd.TSVD_BF16)):
+        for tokens in (False, True):
+            for beside in (0, 3):
+                print(f"case behind y {M} {N} {K} {B} {route} {out} {tokens} {beside}", flush=True)
+                rows, cols = (B, M) if tokens else (M, B)
+                y = torch.full((rows + 520, cols + beside), -77.0, dtype=out, device="cuda:0")
+                if tokens:
+                    tsvd.tsvd_forward_io(h, x.t().contiguous(), x_layout=tsvd.TSVD_TOKEN_MAJOR, y=y[:rows, :cols], y_dtype=code, y_layout=tsvd.TSVD_TOKEN_MAJOR)
+                else:
+                    tsvd.tsvd_forward_ex(h, x, y=y[:rows, :cols], y_dtype=code)
+                got = y.cpu()
+                assert torch.equal(got[:rows, :cols], (ref.t() if tokens else ref).to(out))
+                assert (got[rows:] == -77).all() and (got[:rows, cols:] == -77).all()
+    tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("form,co,k,groups", [(0, 33, 3, 1), (1, 21, 3, 1), (2, 40, 3, 1), (3, 9, 5, 1), (0, 12, 5, 12)])
+@pytest.mark.parametrize("tiles", [0, 1, 2])
+def test_what_lies_behind_a_convolution_stays(tsvd, form, co, k, groups, tiles):  # noqa: F811
+    import ctypes
+    import torch
+    from oracle import conv as oc
+    ci, rank, images, H, W = (co if groups > 1 else 24), 20, 3, 11, 9
+    mu, nv = {0: (1, k * k), 1: (k * k, 1), 2: (k, k), 3: (k, k)}[form]
+    rng = np.random.default_rng(form + co)
+    K = rank * groups
+    U = rng.choice([-1, 0, 1], size=(co * mu, K), p=[0.2, 0.6, 0.2]).astype(np.int8)
+    if groups > 1:
+        U *= (np.arange(co)[:, None] // (co // groups) == np.arange(K)[None, :] // rank).astype(np.int8)
+    V = rng.choice([-1, 0, 1], size=(K, ci // groups * nv), p=[0.2, 0.6, 0.2]).astype(np.int8)
+    S = rng.integers(-2, 3, size=K).astype(np.float32)
+    h = tsvd.tsvd_pack(U, S, V)
+    if tiles:
+        tsvd.tsvd_tuning_set("TSVD_THIN", tiles)
+    x = torch.from_numpy(rng.integers(-2, 3, size=(ci, images, H, W)).astype(np.float32)).to("cuda:0").to(torch.bfloat16)
+    print(f"case behind a convolution {form} {co} {k} {groups} {tiles}", flush=True)
+    want = tsvd.tsvd_conv2d_forward(h, form, ci, co, k, k, x, (1, 1), (k // 2, k // 2), groups=groups)
+    lib, geometry = tsvd.load_library(), (ctypes.c_int32 * 12)(form, ci, co, k, k, 1, 1, k // 2, k // 2, 1, 1, groups)
+    need = lib.tsvd_conv2d_workspace_bytes(h.ptr, ctypes.addressof(geometry), images, H, W)
+    ws = torch.empty(need + (1 << 16), dtype=torch.uint8, device="cuda:0").fill_(93)
+    y = torch.full((co + 64, images, H, W), -77.0, device="cuda:0")
+    assert lib.tsvd_conv2d_forward(h.ptr, ctypes.addressof(geometry), x.data_ptr(), images, H, W, None, y.data_ptr(), 0, ws.data_ptr(), need, None) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(y[:co], want) and (y[co:] == -77).all() and (ws[need:] == 93).all()
+    if groups == 1:
+        ref = oc.tsvd_conv2d(x.float().cpu().numpy().transpose(1, 0, 2, 3), U, S, V, form, co, ci, k, k, (1, 1), (k // 2, k // 2), (1, 1))
+        assert np.array_equal(want.cpu().numpy(), ref.transpose(1, 0, 2, 3))
+    tsvd.tsvd_free(h)
