@@ -296,9 +296,12 @@ bool z_as_fp32(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     return x_dtype == TSVD_BF16 && B >= 2 && B <= 16 && !tsvd_tuning_any() && !h->dense_u && gemv_serves(h) && (double)B * code_bytes(h) <= 60.0e6;
 }
 // Small factors on five planes, 1 to 16 tokens alike (a token's result does not depend on how many stand beside it): up to 512 ranks and 1 MB of code
-// words, and not where one workgroup does a token fastest.  Measured against side by side on 30 such factors: 1 token 0.98 of the
-// time on the average (0.90 .. 1.06), 2 to 8 tokens 0.87, 16 tokens 0.80; at 640 to 2500 ranks one token would take 1.04 .. 1.2 times as long.  The error
-// against 64 bits is 4e-8 to 1.3e-7 of the norm of y, side by side 1e-7 to 4e-6.
+// words, and not where one workgroup does a token fastest.  Measured against side by side on 30 such factors: 2 to 8 tokens 0.87 of the time,
+// 16 tokens 0.80; at 640 to 2500 ranks one token would take 1.04 .. 1.2 times as long.  One token, 36 factors of 250 .. 2000 rows, 200 .. 1000 columns, 200 and
+// 500 ranks: against the one workgroup of up to 768 padded rows 1.00 .. 1.40 (0.94 once) of its time, beyond, against two launches, 0.92 .. 1.11 (1.04 on the
+// average: what two tokens and more gain is paid for here).  The error against 64 bits is 5e-8 to 1.3e-7 of the norm of y, side by side 1e-7 to 4e-6;
+// and on rows that avoid features 20 to 30000 times the rest, or where such features cancel, a tenth to a thousandth of that of the integers side by
+// side, whose grid is 2^-31 of the largest sum that could be.
 bool five_planes(const tsvd_handle* h) {
     const tsvd_blob_header& hd = h->hd;
     return !h->dense_u && hd.Kp <= 512 && code_bytes(h) <= 1.0e6 && (!tsvd_gemv_fused_fits(hd.Mp, hd.Kp, hd.Np) || hd.Mp > 768);
@@ -734,9 +737,10 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
     }
     int x_in_place = 0;
     const bool batched = use_gemm(h, B, x_dtype), misaligned = ldx % 8 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 15u);
-    // rows that are not 16-byte aligned get a copy that is: for more than 16 tokens one pass costs less than the element-wise gathers of the
-    // kernels that take such rows (stage V of a 4096 x 8192 factor at 300 tokens: 251 us gathered, 3 + 35 us copied), for
-    // fewer where rows start at odd elements; TSVD_REALIGN=0 keeps the gathers
+    // rows that are not 16-byte aligned get a copy that is, where the kernels of the call do not read them in place anyway (few tokens, panels, planes
+    // of x): for more than 16 tokens one pass costs less than the element-wise gathers of the ring and large-tile
+    // kernels (stage V of a 4096 x 8192 factor at 300 tokens: 251 us gathered, 3 + 35 us copied), for
+    // fewer, on the slab kernel, where rows start at odd elements; TSVD_REALIGN=0 keeps the gathers
     const bool realign = x_layout == TSVD_FEATURE_MAJOR && x_dtype == TSVD_BF16 && B > 1 && env_int("TSVD_REALIGN", 1) != 0 && h->hd.N <= 65535 &&
                          (batched ? misaligned : realigns_few(h, B, x_dtype) && (ldx % 2 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 3u)));
     const int z_planes = few_planes(h, B, x_dtype, ldx, x_layout == TSVD_TOKEN_MAJOR);
