@@ -128,15 +128,16 @@ tsvd_status tsvd_dense_unpack_host(const void* blob, size_t blob_bytes, int8_t* 
  *     2^-31 of it become 0), every sum of V(.) and U(.) is then an exact integer; z = S * (V x) is rounded to fp32
  *     and converted the same way relative to the bound max_k |S_k| nnz(V[k,:]) * max|x|.  Error: 1e-5 of max|y| at
  *     most (measured 1e-7 .. 8e-7).  TSVD_BF16 on factors of up to 512 ranks and 1 MB of packed bytes: x as it is (exact products
- *     summed in fp32), and z from those sums into FIVE fp6 (E2M3) planes with block scales, which hold a value to 2^-24 of the largest
- *     magnitude among 32 neighbours; the same error, and as there the result of a token does not depend on the others.
+ *     summed in fp32), and z from those sums (beyond fp32: fp64 sums) into FIVE fp6 (E2M3) planes with block scales, which hold a value to 2^-24 of the largest
+ *     magnitude among 32 neighbours; the same error (of max|y| where terms do not cancel: an fp32 sum is off by 2^-24 of its largest partial sum, the
+ *     integers by 2^-31 of the largest sum that could be), and as there the result of a token does not depend on the others.
  *   2 <= B (TSVD_BF16) otherwise: one of three, whichever the library estimates to be faster (the choice depends on sizes, layouts and
  *     the GPU, never on values).
  *     - 16-bit operands: x enters exactly, stage V accumulates exact products in fp32, z is multiplied by a
  *       per-token power of two that keeps it in range and rounded to fp16 (11 significant bits), stage U accumulates
  *       exact products in fp32.  Error: 2e-3 of max|y| at most (measured 2.0e-4 .. 2.4e-4).
  *     - x as it is, z in FOUR planes (what B <= 16 takes): z goes from fp32 sums into planes that hold it to 2^-19 of the largest magnitude among
- *       32 neighbours.  Error: 2e-3 of max|y| at most (measured 7e-7).  Rows of y that use only ranks without a feature far larger than the rest,
+ *       32 neighbours.  Sums beyond fp32 are taken again in fp64, so that a z within fp32 counts as it is.  Error: 2e-3 of max|y| at most (measured 7e-7).  Rows of y that use only ranks without a feature far larger than the rest,
  *       where such ranks stand beside others: 3e-6 to 6e-6 of their own norm at 200 times the rest, 3e-5 to 6e-5 at 2000 times.
  *     - planes: fp4 codes times three fp6 (E2M3) planes with block scales, of x and z or of z alone (large batches with N <= 1280 that would
  *       otherwise have x as it is: six planes of x, which hold a bf16 value down to 2^-29 of that magnitude).  They hold a value to 2^-14

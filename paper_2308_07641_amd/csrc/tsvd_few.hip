@@ -77,6 +77,25 @@ __device__ __forceinline__ void leave_parts(float* red, const f32x4 (&acc)[SW], 
         for (int v = 0; v < 4; ++v) red[(size_t)(wave * SW + s) * RED_BLOCK + (4 * g + v) * RED_PITCH + i] = acc[s][v];
 }
 
+// x[values] times row `row` of a strip's tiles, by a wavefront, in 64 bits: for the sums of doubled values that leave fp32 (|x| of 1e37 and more).
+__device__ __forceinline__ double row_sum(const unsigned char* strip, int row, int nkt, const uint16_t* x, int step, int N, int lane) {
+    double sum = 0.0;
+    for (int n = lane; n < 16 * nkt; n += 64) {              // word d of lane (row, g) of tile T
+        const int T = n >> 4, g = n >> 2 & 3, d = n & 3, at = 256 * T + 128 * (d >> 1) + 32 * (d & 1) + 64 * (g & 1) + 16 * (g >> 1);
+        const uint32_t w = *reinterpret_cast<const uint32_t*>(strip + T * 1024 + (16 * g + row) * 16 + 4 * d);
+        for (int e = 0; e < 16; ++e) {                       // value e: half e >> 3, of it register m = e & 3 in 16 bits e >> 2 & 1
+            const uint32_t code = w >> (16 * (e >> 2 & 1) + 4 * (e & 3) + 2 * (e >> 3));
+            if ((code & 1) && at + e < N) {
+                const double v = (double)__uint_as_float((uint32_t)x[(size_t)(at + e) * step] << 16);
+                sum += code & 2 ? -v : v;
+            }
+        }
+    }
+    for (int m = 1; m < 64; m *= 2) sum += __shfl_xor(sum, m);
+    return sum;
+}
+__device__ __forceinline__ bool in_fp32(float z) { return fabsf(z) <= 3.402823466e38f; }        // (false for NaN)
+
 }  // namespace
 
 // Stage V.  Workgroup (b, t) of kw wavefronts: SW strips, tokens 16 t ...; wavefront q: tile columns q, q + kw, ...
@@ -200,26 +219,51 @@ tsvd_few_v_kernel(tsvd_few_args p) {
 #pragma unroll
     for (int n = 0; n < outputs_of<KWL, SW>; ++n) {
         const int e = tid + n * threads;
-        if (e < outputs) zl[(e >> 4) * RED_PITCH + (e & 15)] = sum_parts<KWL, SW>(red, e >> 4, e & 15) * (0.25f * S[n]);
+        if (e < outputs) {
+            const float z = sum_parts<KWL, SW>(red, e >> 4, e & 15) * (0.25f * S[n]);
+            zl[(e >> 4) * RED_PITCH + (e & 15)] = in_fp32(z) ? z : INFINITY;     // (no NaN: maxima do not show it)
+        }
     }
     __syncthreads();
+    if (wave) return;
     // ---- planes: thread (pair of strips m, token): the 32 values of one operand lane of stage U
-    if (tid < SW * 8 && tok0 + (tid & 15) < p.B) {
-        const int m = tid >> 4, t = tid & 15;
-        const int l0 = SW == 2 ? 0 : 4 * (m >> 1) + (m & 1), l1 = SW == 2 ? 1 : l0 + 2;
-        const int sg = strip_of(blockIdx.x, SW, l0), gr = ((sg >> 2) & 1) | ((sg & 1) << 1);
-        float v[32];
+    const bool busy = lane < SW * 8 && tok0 + (lane & 15) < p.B;
+    const int m = (lane >> 4) & (SW / 2 - 1), t = lane & 15;
+    const int l0 = SW == 2 ? 0 : m, l1 = SW == 2 ? 1 : l0 + 2;
+    const int sg = strip_of(blockIdx.x, SW, l0), gr = ((sg >> 2) & 1) | ((sg & 1) << 1);
+    float v[32], top;
+    auto values = [&] {
+        top = 0.f;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             v[e] = zl[(16 * l0 + e) * RED_PITCH + t];
             v[16 + e] = zl[(16 * l1 + e) * RED_PITCH + t];
         }
+#pragma unroll
+        for (int e = 0; e < 32; ++e) top = fmaxf(top, fabsf(v[e]));
+    };
+    // Sums of doubled values leave fp32 from |x| of 1e37 on, though z may not: those are taken again by this wavefront alone.  (It costs others nothing but a
+    // look at a maximum that is needed anyway: 0.05 us of 8 to 18.  A flag in LDS that all wavefronts look at: 0.3.)
+    values();
+    if (__builtin_expect(__any(busy && !in_fp32(top)), 0)) {
+        for (int e = 0; e < outputs; ++e) {
+            const int row = e >> 4, strip = strip_of(blockIdx.x, SW, row >> 4), token = tok0 + (e & 15);
+            float& z = zl[row * RED_PITCH + (e & 15)];
+            if (token >= p.B || in_fp32(z)) continue;
+            const double sum = row_sum(p.tiles + (size_t)strip * p.nkt * 1024, row & 15, p.nkt, p.x + (TOKENS ? (size_t)token * ld : token), TOKENS ? 1 : ld, p.N, lane);
+            const float exact = (float)(sum * (0.5 * (double)p.S[strip * 16 + (row & 15)]));
+            z = in_fp32(exact) ? exact : INFINITY;
+        }
+        values();
+    }
+    if (busy) {
+        const uint32_t lost = in_fp32(top) ? 0u : ~0u;       // scales of z that is beyond fp32 itself: no numbers in y
         u32x4 lo[5];
         u32x2 hi[5];
-        const uint32_t scales = tsvd_planes_of_32<true, 4>(v, [&](int pl, u32x4 l, u32x2 h) {
+        const uint32_t scales = lost | tsvd_planes_of_32<true, 4, true, true>(v, [&](int pl, u32x4 l, u32x2 h) {
             lo[pl] = l;
             hi[pl] = h;
-        });
+        }, top);
         unsigned char* rec_bytes = p.planes + ((size_t)blockIdx.y * p.blocks + (sg >> 3)) * record_bytes(p.z_planes);
         u32x4* rec = reinterpret_cast<u32x4*>(rec_bytes) + 16 * gr + t;
         rec[0] = lo[0];
@@ -232,7 +276,7 @@ tsvd_few_v_kernel(tsvd_few_args p) {
             reinterpret_cast<uint32_t*>(rec_bytes + 6 * 1024)[16 * gr + t] = scales;
         } else {
             // v holds what four planes do not resolve
-            const uint32_t fifth = tsvd_planes_of_32<false, 1>(v, [&](int, u32x4 l, u32x2 h) {
+            const uint32_t fifth = lost | tsvd_planes_of_32<false, 1>(v, [&](int, u32x4 l, u32x2 h) {
                 lo[4] = l;
                 hi[4] = h;
             });
@@ -289,11 +333,11 @@ tsvd_few_u_kernel(tsvd_few_args p) {
                         const u32x4& p5, const u32x4& p6, const u32x4& p7) {
         const u32x4 av = {(w0 << 2) & 0xCCCCCCCCu, w0 & 0xCCCCCCCCu, (w1 << 2) & 0xCCCCCCCCu, w1 & 0xCCCCCCCCu};
         const uint32_t scales = PLANES == 5 ? p7.z : p6.x;
-        if constexpr (PLANES == 5) a = mfma_fp6<0>(av, p6, u32x2{p7.x, p7.y}, p7.w, a);
-        a = mfma_fp6<3>(av, u32x4{p4.z, p4.w, p5.x, p5.y}, u32x2{p5.z, p5.w}, scales, a);
-        a = mfma_fp6<2>(av, p3, u32x2{p4.x, p4.y}, scales, a);
-        a = mfma_fp6<1>(av, u32x4{p1.z, p1.w, p2.x, p2.y}, u32x2{p2.z, p2.w}, scales, a);
-        a = mfma_fp6<0>(av, p0, u32x2{p1.x, p1.y}, scales, a);
+        if constexpr (PLANES == 5) a = mfma_fp6<0, 4>(av, p6, u32x2{p7.x, p7.y}, p7.w, a);
+        a = mfma_fp6<3, 3>(av, u32x4{p4.z, p4.w, p5.x, p5.y}, u32x2{p5.z, p5.w}, scales, a);
+        a = mfma_fp6<2, 2>(av, p3, u32x2{p4.x, p4.y}, scales, a);
+        a = mfma_fp6<1, 1>(av, u32x4{p1.z, p1.w, p2.x, p2.y}, u32x2{p2.z, p2.w}, scales, a);
+        a = mfma_fp6<0, 0>(av, p0, u32x2{p1.x, p1.y}, scales, a);
     };
     FEW_OPERAND(z0);
     FEW_OPERAND(z1);

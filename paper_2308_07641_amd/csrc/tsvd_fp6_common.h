@@ -20,18 +20,23 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 // One lane's 32 values -> COUNT (three) E2M3 planes (the value, the residual of its rounding, the residual of that, ...), each
 // with its own power-of-two scale.  put(plane, first 16 bytes, last 8 bytes) receives the lane's 24 bytes of each
 // plane; the return value holds the scale bytes (COUNT <= 4).  KEEP: v is left holding what the planes do not resolve
-// (for a second set of planes); else it is used up.
-template <bool KEEP = false, int COUNT = 3, typename Put>
-__device__ __forceinline__ uint32_t tsvd_planes_of_32(float (&v)[32], Put put) {
+// (for a second set of planes); else it is used up.  RISE: what is left from the second plane on is multiplied by 2^4 at each, so that the scales of
+// the last planes reach below 2^-126 (mfma_fp6 takes that back: the third plane is 2^4 times what it stands for, the fourth 2^8, the fifth 2^12).
+// TOP: the caller knows the largest magnitude.
+template <bool KEEP = false, int COUNT = 3, bool RISE = false, bool TOP = false, typename Put>
+__device__ __forceinline__ uint32_t tsvd_planes_of_32(float (&v)[32], Put put, float top = 0.f) {
     typedef float f32x16 __attribute__((ext_vector_type(16)));
     typedef float f32x32 __attribute__((ext_vector_type(32)));
     typedef unsigned u32x6 __attribute__((ext_vector_type(6)));
     uint32_t scales = 0;
 #pragma unroll
     for (int pl = 0; pl < COUNT; ++pl) {
-        float m = 0.f;
+        float m = top;
+        if (!TOP || pl > 0) {
+            m = 0.f;
 #pragma unroll
-        for (int e = 0; e < 32; ++e) m = fmaxf(m, fabsf(v[e]));
+            for (int e = 0; e < 32; ++e) m = fmaxf(m, fabsf(v[e]));
+        }
         // exponent ex with m 2^-ex <= 7.5, the largest E2M3 magnitude (m = f 2^x, 0.5 <= f < 1)
         int x = 0;
         const float f = frexpf(m, &x);
@@ -56,9 +61,12 @@ __device__ __forceinline__ uint32_t tsvd_planes_of_32(float (&v)[32], Put put) {
         asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3" : "=&v"(w) : "v"(s0), "v"(s1), "v"(unit));
         if (pl < COUNT - 1 || KEEP) {
             f32x32 back;
-            asm("v_cvt_scalef32_pk32_f32_fp6 %0, %1, %2" : "=&v"(back) : "v"(w), "v"(unit));
+            constexpr float STEP = 16.f;
+            const bool rise = RISE && pl > 0;
+            asm("v_cvt_scalef32_pk32_f32_fp6 %0, %1, %2" : "=&v"(back) : "v"(w), "v"(rise ? STEP * unit : unit));
+            // exact: the next plane codes this residual (v is at most 2^-4 of the first plane's here, so that 2^4 times it is in range)
 #pragma unroll
-            for (int e = 0; e < 32; ++e) v[e] -= back[e];         // exact: the next plane codes this residual
+            for (int e = 0; e < 32; ++e) v[e] = rise ? fmaf(STEP, v[e], -back[e]) : v[e] - back[e];
         }
         put(pl, u32x4{w[0], w[1], w[2], w[3]}, u32x2{w[4], w[5]});
     }
@@ -124,12 +132,14 @@ __device__ __forceinline__ void tsvd_gather_row(const T* row, int k0, int N, boo
     }
 }
 
-template <int PL>
+// RISEN: the plane's number among those that tsvd_planes_of_32 left with RISE
+template <int PL, int RISEN = -1>
 __device__ __forceinline__ f32x4 mfma_fp6(const u32x4& a, const u32x4& lo, const u32x2& hi, uint32_t scale, f32x4 acc) {
     const i32x8 av = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
     const i32x8 bv = {(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, 0, 0};
-    // cbsz = 4: A is fp4 (E2M1); blgp = 2: B is fp6 (E2M3); A scale 2^0; B scale = byte PL of `scale`
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, acc, 4, 2, 0, 0x7F7F7F7F, PL, (int)scale);
+    // cbsz = 4: A is fp4 (E2M1); blgp = 2: B is fp6 (E2M3); A scale 2^0 (2^-4, 2^-8, 2^-12: bytes 1 to 3); B scale = byte PL of `scale`
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, acc, 4, 2, RISEN < 2 ? 0 : RISEN - 1, RISEN < 0 ? 0x7F7F7F7F : 0x73777B7F,
+                                                            PL, (int)scale);
 }
 
 }  // namespace

@@ -108,3 +108,46 @@ def test_ranks_beside_those_of_massive_outliers(tsvd, M, N, K, B, switch):  # no
     assert err <= np.linalg.norm(bound) + 1e-6 * size
     assert err <= 2.0 ** -12 * size
     tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("M,N,K,B,switch", [(1100, 700, 500, 1, None), (1100, 700, 500, 6, None), (900, 1030, 270, 16, None), (4096, 4096, 5900, 7, None), (2500, 640, 1300, 40, None),
+                                            (70, 600, 300, 9, {"TSVD_FEW_SW_V": 4}), (300, 2100, 300, 16, {"TSVD_FEW_KWLOG2": 1})])
+@pytest.mark.parametrize("size,scale", [(1e37, 1e-10), (2.0 ** 127, 2.0 ** -126), (1e-30, 1.0), (1e-36, 1.0)])
+def test_activations_near_the_ends_of_fp32(tsvd, M, N, K, B, switch, size, scale):  # noqa: F811
+    """Sums of doubled activations beyond fp32 where z and y are numbers again, and z whose last planes are below 2^-126: the bounds of ordinary sizes."""
+    import torch
+    rng = np.random.default_rng(M + N + K + B)
+    U, V = (rng.choice([-1, 0, 1], size=s, p=[0.25, 0.5, 0.25]).astype(np.int8) for s in ((M, K), (K, N)))
+    S = (rng.uniform(0.5, 1.0, K) * scale).astype(np.float32)
+    x = torch.from_numpy(rng.uniform(-1, 1, (B, N)) * size).to(torch.bfloat16)
+    want = ((x.double().numpy() @ V.T.astype(np.float64)) * S.astype(np.float64)) @ U.T.astype(np.float64)
+    h = tsvd.tsvd_pack(U, S, V)
+    for k, v in ({"TSVD_FEW": 64, **switch} if switch else {}).items():
+        tsvd.tsvd_tuning_set(k, v)
+    print(f"case few near the ends {M} {N} {K} {B} {size} {scale}", flush=True)
+    y = tsvd.tsvd_forward_io(h, x.to("cuda:0"), x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR).double().cpu().numpy()
+    y2 = tsvd.tsvd_forward(h, x.t().clone(memory_format=torch.contiguous_format).to("cuda:0")).t().double().cpu().numpy()
+    for got in (y, y2):
+        assert np.linalg.norm(got - want) <= (1e-6 if K <= 512 and not switch else 1e-5) * np.linalg.norm(want)
+    tsvd.tsvd_free(h)
+
+
+def test_z_beyond_fp32_is_no_number_in_y(tsvd):  # noqa: F811
+    """z of one token beyond fp32: not a number (rather than an ordinary one) in the rows of that token, all others as they are."""
+    import torch
+    M, N, K, B = 300, 640, 300, 9
+    rng = np.random.default_rng(5)
+    U, V = (rng.choice([-1, 1], size=s).astype(np.int8) for s in ((M, K), (K, N)))
+    h = tsvd.tsvd_pack(U, np.full(K, 3.0, np.float32), V)
+    x = torch.from_numpy(rng.integers(-2, 3, (B, N)).astype(np.float32)).to(torch.bfloat16)
+    big = x.clone()
+    big[4] = torch.from_numpy(np.where(V[7] > 0, 1e38, -1e38)).to(torch.bfloat16)
+    for switches in ({"TSVD_FEW": 16, "TSVD_FEW_PLANES": 4}, {"TSVD_FEW": 16, "TSVD_FEW_PLANES": 5}):
+        for k, v in switches.items():
+            tsvd.tsvd_tuning_set(k, v)
+        print(f"case few z beyond fp32 {switches}", flush=True)
+        y, plain = (tsvd.tsvd_forward_io(h, v.to("cuda:0"), x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR).cpu() for v in (big, x))
+        others = [t for t in range(B) if t != 4]
+        assert not torch.isfinite(y[4]).any() and torch.equal(y[others], plain[others])
+        assert torch.equal(plain[others].double(), (x[others].double() @ torch.from_numpy(V).double().t() * 3.0) @ torch.from_numpy(U).double().t())
+    tsvd.tsvd_free(h)
