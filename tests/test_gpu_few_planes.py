@@ -52,8 +52,8 @@ def test_neighbours_that_are_not_finite(tsvd, B, ld, col0):  # noqa: F811
 
 @pytest.mark.parametrize("M,N,K,B", [(1100, 700, 500, 1), (1100, 700, 500, 6), (4096, 4096, 5900, 7), (2500, 640, 1300, 40), (500, 2400, 130, 300)])
 def test_calls_that_take_them_by_default(tsvd, M, N, K, B):  # noqa: F811
-    """Five planes on small factors (error of fp32 sums), four beyond; the same bits for either layout of x and y, and replayed from a
-    captured graph."""
+    """Five planes on small factors (error of fp32 sums), four beyond; the bits of the same kernels asked for by name (no other kernel has them), for
+    either layout of x and y, and replayed from a captured graph; nothing behind the workspace that was asked for."""
     import torch
     i = workloads.make_inputs(M, N, K, B, 0.6, 0.02, "bf16", seed=M + B)
     ref = oracle.forward(i.U, i.S, i.V, i.X)
@@ -64,8 +64,15 @@ def test_calls_that_take_them_by_default(tsvd, M, N, K, B):  # noqa: F811
     assert rel_err(y.cpu().numpy().astype(np.float64), ref) <= (1e-6 if B <= 6 else 1e-5)
     yt = tsvd.tsvd_forward_io(h, x.t().contiguous(), x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR)
     assert torch.equal(yt.t(), y)
-    ws = torch.empty(tsvd.tsvd_workspace_bytes(h, B, tsvd.TSVD_BF16), dtype=torch.uint8, device="cuda:0")
-    out = torch.zeros_like(y)
+    for k, v in {"TSVD_FEW": 1024, "TSVD_FEW_PLANES": 5 if K <= 512 and B <= 16 else 4}.items():
+        tsvd.tsvd_tuning_set(k, v)
+    assert torch.equal(tsvd.tsvd_forward(h, x), y)
+    tsvd.tsvd_tuning_set("TSVD_FEW", 0)
+    assert not torch.equal(tsvd.tsvd_forward(h, x), y)
+    tsvd.tsvd_tuning_reset()
+    need = tsvd.tsvd_workspace_bytes(h, B, tsvd.TSVD_BF16)
+    marked = torch.full((need + (1 << 16),), 93, dtype=torch.uint8, device="cuda:0")
+    ws, out = marked[:need], torch.zeros_like(y)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
@@ -75,7 +82,7 @@ def test_calls_that_take_them_by_default(tsvd, M, N, K, B):  # noqa: F811
         ws.fill_(255)
         graph.replay()
         torch.cuda.synchronize()
-        assert torch.equal(out, y)
+        assert torch.equal(out, y) and (marked[need:] == 93).all()
     tsvd.tsvd_free(h)
 
 
@@ -150,4 +157,65 @@ def test_z_beyond_fp32_is_no_number_in_y(tsvd):  # noqa: F811
         others = [t for t in range(B) if t != 4]
         assert not torch.isfinite(y[4]).any() and torch.equal(y[others], plain[others])
         assert torch.equal(plain[others].double(), (x[others].double() @ torch.from_numpy(V).double().t() * 3.0) @ torch.from_numpy(U).double().t())
+    tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("M,N,K", [(1100, 700, 500), (900, 4099, 250), (3000, 2000, 300)])
+def test_a_token_has_the_same_bits_among_others(tsvd, M, N, K):  # noqa: F811
+    """1 to 16 tokens on small factors."""
+    import torch
+    i = workloads.make_inputs(M, N, K, 16, 0.6, 0.02, "bf16", seed=M + N)
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    x = to_device(i)
+    print(f"case few tokens' bits {M} {N} {K}", flush=True)
+    alone = torch.cat([tsvd.tsvd_forward(h, x[:, t:t + 1].clone()) for t in range(16)], dim=1)
+    for B in (2, 8, 9, 16):
+        for first in {0, 16 - B}:
+            xb = x[:, first:first + B]
+            assert torch.equal(tsvd.tsvd_forward(h, xb), alone[:, first:first + B])
+            assert torch.equal(tsvd.tsvd_forward_io(h, xb.t().contiguous(), x_layout=tsvd.TSVD_TOKEN_MAJOR), alone[:, first:first + B])
+    tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("M,N,K", [(900, 4000, 256), (800, 14000, 200), (3000, 2000, 300)])
+@pytest.mark.parametrize("kind", ["offset", "outliers", "opposite"])
+def test_sums_that_cancel_on_five_planes(tsvd, M, N, K, kind):  # noqa: F811
+    """Activations with a common offset, or a few far above the rest, and rows of V in which these cancel.  An fp32 sum is off by 2^-24 of its partial sums, at
+    most of the sum of magnitudes, at each of its additions: one for each 8 values of a wavefront's columns and each wavefront.  The
+    integers of the single-token kernels, on a grid of 2^-31 of the largest sum that could be, do not come closer."""
+    import torch
+    rng = np.random.default_rng(N + K)
+    half = N // 4
+    V = np.zeros((K, N), np.int8)
+    for k in range(K):
+        at = rng.permutation(N)
+        V[k, at[:half]], V[k, at[half:2 * half]] = 1, -1
+    x = rng.standard_normal(N)
+    if kind == "offset":
+        x += 100.0
+    elif kind == "outliers":
+        x[rng.permutation(N)[:N // 100]] *= 200.0
+    else:
+        x[[3, N - 2]] = 3000.0, -3000.0
+        V[:, 3] = V[:, N - 2] = 1
+    U = rng.choice([-1, 0, 1], size=(M, K), p=[0.25, 0.5, 0.25]).astype(np.int8)
+    S = np.abs(rng.standard_normal(K)).astype(np.float32)
+    xb = torch.from_numpy(x).to(torch.bfloat16)
+    x = xb.double().numpy()
+    z = (V.astype(np.float64) @ x) * S
+    want = U.astype(np.float64) @ z
+    nkt = -(-N // 256)
+    kw = min(16, 1 << (nkt.bit_length() - 1))
+    adds = 32 * -(-nkt // kw) + kw
+    dz = adds * 2.0 ** -24 * S * (np.abs(V).astype(np.float64) @ np.abs(x)) + 2.0 ** -23 * np.abs(z).max()
+    h = tsvd.tsvd_pack(U, S, V)
+    print(f"case few sums that cancel {M} {N} {K} {kind}", flush=True)
+    xd = xb.to("cuda:0")[:, None].contiguous()
+    y = tsvd.tsvd_forward(h, xd).double().cpu().numpy()[:, 0]
+    tsvd.tsvd_tuning_set("TSVD_FEW", 0)
+    integers = tsvd.tsvd_forward(h, xd).double().cpu().numpy()[:, 0]
+    assert not np.array_equal(y, integers)
+    assert (np.abs(y - want) <= np.abs(U) @ dz + 2.0 ** -20 * (np.abs(U) @ np.abs(z))).all()
+    print(f"{np.linalg.norm(y - want) / np.linalg.norm(want):.1e}, integers {np.linalg.norm(integers - want) / np.linalg.norm(want):.1e}", flush=True)
+    assert np.linalg.norm(y - want) <= np.linalg.norm(integers - want)
     tsvd.tsvd_free(h)
