@@ -147,7 +147,7 @@ tsvd_status tsvd_dense_unpack_host(const void* blob, size_t blob_bytes, int8_t* 
  *       the whole of y.  A row of V whose non-zero entries avoid a feature far larger than its neighbours still carries
  *       2^-15 of that feature per neighbour: rows of y made of such ranks alone are off by 3e-5 to 9e-5 of their own norm for features 20
  *       to 60 times the rest, 1e-4 to 5e-4 at 200 times, 1e-3 to 5e-3 at 2000 times (16-bit operands: 2.1e-4 in all of them).
- *       Callers whose rows need more pass x as TSVD_F32.
+ *       Callers whose rows need more pass x as TSVD_F32.  Scales of planes end at 2^-126: values below about 1e-34 keep fewer bits there, and sums beyond fp32 no number.
  *   17 <= B (TSVD_F32): fp4 codes times SIX fp6 planes of the activations of either stage (three, and three more for
  *     what those leave: below the last bit of an fp32 value of a block's largest magnitude), fp32 accumulation; z goes
  *     from the accumulators straight into its planes.  Error: 1e-5 of max|y| at most (measured 2e-7 .. 1.4e-6).

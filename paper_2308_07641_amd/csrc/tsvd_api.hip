@@ -383,7 +383,7 @@ tsvd_status forward_skinny(const tsvd_handle* h, const void* x, tsvd_dtype x_dty
 }
 
 // ---- slab path for few tokens: groups of up to 16 tokens of bf16 activations, two launches per group ------
-// What the few-token kernels (few_planes) do not take: rows of fewer than eight values, and more than 2^18 ranks.
+// What the few-token kernels (few_planes) do not take: fewer than eight values, odd rows too far apart for them (tsvd_few_fits), and more than 2^18 ranks.
 bool use_mid(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, int64_t ldx) {
     if (x_dtype != TSVD_BF16 || B < 2 || B > 64 || env_int("TSVD_MID", 1) == 0) return false;
     // (32-bit byte offsets into x in the kernel, which also addresses up to four slabs of 2048 rows
@@ -657,7 +657,8 @@ size_t base_workspace(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     if (use_gemm(h, B, x_dtype)) return std::max(gemm_workspace(h, B, x_dtype), B <= 64 ? few : (size_t)0);
     return few;
 }
-// (whether a call of few tokens may copy rows that start at odd elements: for the sizes whose workspace stays small)
+// (whether a call of few tokens may copy rows that start at odd elements: for the sizes whose workspace stays small.  The slab kernel gains by it, which
+// without switches serves what tsvd_few_fits leaves: rows too far apart for 32-bit places, and fewer than eight values)
 bool realigns_few(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) { return x_dtype == TSVD_BF16 && B > 1 && B <= 16 && h->hd.N <= 65535 && h->hd.Kp <= 65536; }
 // feature-major copy of token-major activations: [N][B rounded up to 8] elements
 size_t transposed_bytes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
@@ -740,7 +741,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
     // rows that are not 16-byte aligned get a copy that is, where the kernels of the call do not read them in place anyway (few tokens, panels, planes
     // of x): for more than 16 tokens one pass costs less than the element-wise gathers of the ring and large-tile
     // kernels (stage V of a 4096 x 8192 factor at 300 tokens: 251 us gathered, 3 + 35 us copied), for
-    // fewer, on the slab kernel, where rows start at odd elements; TSVD_REALIGN=0 keeps the gathers
+    // fewer, on the slab kernel (use_mid), where rows start at odd elements; TSVD_REALIGN=0 keeps the gathers
     const bool realign = x_layout == TSVD_FEATURE_MAJOR && x_dtype == TSVD_BF16 && B > 1 && env_int("TSVD_REALIGN", 1) != 0 && h->hd.N <= 65535 &&
                          (batched ? misaligned : realigns_few(h, B, x_dtype) && (ldx % 2 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 3u)));
     const int z_planes = few_planes(h, B, x_dtype, ldx, x_layout == TSVD_TOKEN_MAJOR);

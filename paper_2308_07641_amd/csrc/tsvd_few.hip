@@ -2,16 +2,17 @@
 // Network Compression"; supplement Table S1), one launch each, a group of 16 tokens filling the columns of the matrix instruction.
 //
 // Such a call is bound by the chain of latencies of its two launches and, on large factors, by what a compute unit can take in: the codes
-// once (HBM), and all activations for every workgroup (L2: 20 to 25 bytes a cycle and compute unit, whatever asks for them).  So no
+// once (HBM), and all activations for every workgroup (L2: 20 to 25 bytes a cycle and compute unit, as the 0.54 MB for each in the 10 us of stage U below).  So no
 // barrier stands between the launch and the products, and activations are read in whole lines: a wavefront owns columns of tiles (256 indices of the
 // contraction, kw wavefronts side by side), holds their activations in registers in operand order, and multiplies the tiles of SW strips
 // by them, each tile requested one column ahead; the partial sums of the kw wavefronts meet in LDS once, at the end.
 //
 // Stage V multiplies bf16 x as it is (codes expanded to 0 / +2 / -2 in 16 bits: 64 operations and 8 MFMAs a tile) and leaves z as
-// four or five E2M3 planes (tsvd_fp6_common.h), which stage U multiplies by the codes as fp4 numbers: 8 operations and 8 (10) MFMAs a tile.
+// four or five E2M3 planes (tsvd_fp6_common.h), which stage U multiplies by the codes as fp4 numbers: 12 operations and 8 (10) MFMAs a tile
+// (a tile is two blocks of 128 rank positions, 6 operations each).
 //
 // Measured on MI355X against the kernels that take x and fp16 z through LDS in slabs (tsvd_mid.hip): 16384 x 4096 x 8192, 16 tokens, token-major
-// (a transposition pass before) 21.4 -> 17.9 us a call, in a kernel trace stage V 7.9 -> 6.7, stage U 12.0 -> 10.9 (16.8 MB of codes and 105 MB of z
+// (a transposition pass before) 21.4 -> 17.9 us a call, in a kernel trace stage V 7.9 -> 6.7, stage U 12.0 -> 10.9 (33.5 MB of codes and 105 MB of z
 // from L2).  Four planes rather than three: three cost 1.2 us less there and 0.7 us on small calls, but leave 2^-14 of the largest of 32
 // neighbours, so rows of y made of ranks beside such that see a feature 2000 times the rest were off by 1.1e-3 (fp16 z 2.1e-4, four planes 3e-5).  A
 // record of seven whole pieces cost 1.5 us more than six and the scales apart.  Loading operand lanes of x straight from rows of tokens cost stage V 1.5 us more (16-byte pieces of 32 lines per request), and requests
@@ -29,7 +30,7 @@
 
 namespace {
 
-// LDS of a wavefront for its column of x: 16 rows of 256 tokens' values, padded by 16 bytes against bank conflicts (256 rows of 32 bytes otherwise)
+// LDS of a wavefront for its column of x: the rows of 16 tokens, 256 values each, padded by 16 bytes against bank conflicts (256 rows of 32 bytes otherwise)
 constexpr int ROW_PITCH = 528, WAVE_X = 16 * ROW_PITCH;
 constexpr int RED_PITCH = 17, RED_BLOCK = 16 * RED_PITCH;      // floats: a 16 x 16 result block, rows padded against bank conflicts
 
