@@ -84,12 +84,14 @@ __device__ __forceinline__ double row_sum(const unsigned char* strip, int row, i
     for (int n = lane; n < 16 * nkt; n += 64) {              // word d of lane (row, g) of tile T
         const int T = n >> 4, g = n >> 2 & 3, d = n & 3, at = 256 * T + 128 * (d >> 1) + 32 * (d & 1) + 64 * (g & 1) + 16 * (g >> 1);
         const uint32_t w = *reinterpret_cast<const uint32_t*>(strip + T * 1024 + (16 * g + row) * 16 + 4 * d);
+        uint16_t v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = x[(size_t)min(at + e, N - 1) * step];
+#pragma unroll
         for (int e = 0; e < 16; ++e) {                       // value e: half e >> 3, of it register m = e & 3 in 16 bits e >> 2 & 1
-            const uint32_t code = w >> (16 * (e >> 2 & 1) + 4 * (e & 3) + 2 * (e >> 3));
-            if ((code & 1) && at + e < N) {
-                const double v = (double)__uint_as_float((uint32_t)x[(size_t)(at + e) * step] << 16);
-                sum += code & 2 ? -v : v;
-            }
+            const uint32_t code = w >> (16 * (e >> 2 & 1) + 4 * (e & 3) + 2 * (e >> 3));      // (0 beyond N)
+            const double value = (double)__uint_as_float((uint32_t)v[e] << 16);
+            sum += code & 1 ? code & 2 ? -value : value : 0.0;
         }
     }
     for (int m = 1; m < 64; m *= 2) sum += __shfl_xor(sum, m);
