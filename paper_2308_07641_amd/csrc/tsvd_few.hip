@@ -12,7 +12,7 @@
 // (a tile is two blocks of 128 rank positions, 6 operations each).
 //
 // Measured on MI355X against the kernels that take x and fp16 z through LDS in slabs (tsvd_mid.hip): 16384 x 4096 x 8192, 16 tokens, token-major
-// (a transposition pass before) 21.4 -> 17.9 us a call, in a kernel trace stage V 7.9 -> 6.7, stage U 12.0 -> 10.9 (33.5 MB of codes and 105 MB of z
+// (a transposition pass before) 21.4 -> 18.0 us a call, in a kernel trace stage V 7.9 -> 6.5, stage U 12.0 -> 11.0 (33.5 MB of codes and 105 MB of z
 // from L2).  Four planes rather than three: three cost 1.2 us less there and 0.7 us on small calls, but leave 2^-14 of the largest of 32
 // neighbours, so rows of y made of ranks beside such that see a feature 2000 times the rest were off by 1.1e-3 (fp16 z 2.1e-4, four planes 3e-5).  A
 // record of seven whole pieces cost 1.5 us more than six and the scales apart.  Loading operand lanes of x straight from rows of tokens cost stage V 1.5 us more (16-byte pieces of 32 lines per request), and requests
