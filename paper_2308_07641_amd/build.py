@@ -12,6 +12,7 @@ BINDING = os.path.join(HERE, "_tsvd_torch.so")
 SOURCES = ["tsvd_pack.cpp", "tsvd_api.hip", "tsvd_skinny.hip", "tsvd_gemv.hip", "tsvd_mid.hip", "tsvd_few.hip", "tsvd_dense.hip", "tsvd_gemm.hip", "tsvd_fp6.hip", "tsvd_fp6_split.hip", "tsvd_thin.hip", "tsvd_batch.hip", "tsvd_transition.hip", "tsvd_pair.hip", "tsvd_conv.hip", "tsvd_depthwise.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-pthread",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",      # leading scalar arguments of kernels come in registers
          "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument"]
 
 

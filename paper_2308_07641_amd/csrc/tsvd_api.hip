@@ -173,11 +173,11 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
     const int mask = tsvd_stage_mask();
     // (16 bytes of fp32, 8 of bf16 at a time)
     const bool vec = ldx == 1 && hd.N % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (tokens == 1 || x_token % 4 == 0);
-    if (mask == 7 && !h->dense_u && env_int("TSVD_GEMV_FUSED", 1) != 0 && tsvd_gemv_fused_fits(hd.Mp, hd.Kp, hd.Np)) {
-        // a small matrix: both stages in one launch of one workgroup
+    if (mask == 7 && !h->dense_u && env_int("TSVD_GEMV_FUSED", 1) != 0) {
+        // a small V: both stages in one launch
         tsvd_gemv_fused_args f;
         std::memset(&f, 0, sizeof f);
-        f.tiles_v = h->blob + hd.off_V; f.strips_v = (int)(hd.Kp / 16); f.nkt_v = (int)(hd.Np / 256);
+        f.tiles_v = h->blob + hd.off_V; f.strips_v = (int)((hd.K + 127) / 128 * 8); f.nkt_v = (int)(hd.Np / 256);
         f.tiles_u = h->blob + hd.off_U; f.strips_u = (int)((hd.M + 15) / 16); f.nkt_u = (int)(hd.Kp / 256);
         f.N = (int)hd.N; f.Np = (int)hd.Np; f.Kp = (int)hd.Kp; f.M = (int)hd.M;
         f.x = x; f.x_is_bf16 = x_dtype == TSVD_BF16; f.ldx = ldx;
@@ -186,8 +186,10 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
         f.S = reinterpret_cast<const float*>(h->blob + hd.off_S);
         f.bound_V = h->bound_V;
         f.y = y; f.ldy = ldy; f.bias = oo.bias; f.out_bf16 = oo.out_bf16;
-        *st = tsvd_launch_gemv_fused(f, stream) == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
-        return true;
+        if (tsvd_gemv_fused_fits(f, h->cu_count)) {
+            *st = tsvd_launch_gemv_fused(f, h->cu_count, stream) == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
+            return true;
+        }
     }
     if (mask == 7 && tokens == 1 && h->sync && !h->dense_u && env_int("TSVD_GEMV_ONEPASS", 0) != 0) {
         // both stages in one launch (z handed over between workgroups through the handle's tagged buffer)
@@ -304,7 +306,7 @@ bool z_as_fp32(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
 // side, whose grid is 2^-31 of the largest sum that could be.
 bool five_planes(const tsvd_handle* h) {
     const tsvd_blob_header& hd = h->hd;
-    return !h->dense_u && hd.Kp <= 512 && code_bytes(h) <= 1.0e6 && (!tsvd_gemv_fused_fits(hd.Mp, hd.Kp, hd.Np) || hd.Mp > 768);
+    return !h->dense_u && hd.Kp <= 512 && code_bytes(h) <= 1.0e6 && (!tsvd_gemv_one_workgroup(hd.Mp, hd.Kp, hd.Np) || hd.Mp > 768);
 }
 // The planes of z of a call of up to 16 tokens on the few-token kernels (0: on others).
 int few_planes(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype, int64_t ldx, bool x_token_major) {

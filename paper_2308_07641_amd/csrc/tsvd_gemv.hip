@@ -61,10 +61,12 @@ __device__ __forceinline__ f32x4 mfma_step(uint32_t w0, uint32_t w1, const u32x4
     return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, acc, 4, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
 }
 
+// A tile times the planes at xrow: of each half (128 indices) the lane's 32 bytes of its column's plane, 16 at 0 and at SUB, those of the second half HALF behind.
+template <int SUB = 16, int HALF = 128>
 __device__ __forceinline__ void tile_steps(const u32x4& w, const unsigned char* xrow, f32x4& acc0, f32x4& acc1) {
-    const u32x4* xb = reinterpret_cast<const u32x4*>(xrow);
-    acc0 = mfma_step(w.x, w.y, xb[0], xb[1], acc0);      // columns   0..127 of the tile
-    acc1 = mfma_step(w.z, w.w, xb[8], xb[9], acc1);      // columns 128..255
+    auto part = [&](int at) { return *reinterpret_cast<const u32x4*>(xrow + at); };
+    acc0 = mfma_step(w.x, w.y, part(0), part(SUB), acc0);                    // columns   0..127 of the tile
+    acc1 = mfma_step(w.z, w.w, part(HALF), part(HALF + SUB), acc1);          // columns 128..255
 }
 
 // fp8 (E4M3) codes of four integers 0..15 held one per byte.
@@ -87,19 +89,6 @@ __device__ __forceinline__ void codes_of_fixed(uint32_t mag, bool negative, uint
 __device__ __forceinline__ void digit_codes(float v, int ex, uint32_t& even, uint32_t& odd) {
     codes_of_fixed(fixed_magnitude(v, ex), v < 0.f, even, odd);
 }
-// Four consecutive activations' codes (even[e], odd[e]) -> one 32-bit word per digit plane in LDS.
-__device__ __forceinline__ void store_plane_words(unsigned char* planes, int pstride, int k, const uint32_t (&ev)[4], const uint32_t (&od)[4]) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t we = ((ev[0] >> (8 * d)) & 0xFFu) | (((ev[1] >> (8 * d)) & 0xFFu) << 8) |
-                            (((ev[2] >> (8 * d)) & 0xFFu) << 16) | (((ev[3] >> (8 * d)) & 0xFFu) << 24);
-        const uint32_t wo = ((od[0] >> (8 * d)) & 0xFFu) | (((od[1] >> (8 * d)) & 0xFFu) << 8) |
-                            (((od[2] >> (8 * d)) & 0xFFu) << 16) | (((od[3] >> (8 * d)) & 0xFFu) << 24);
-        *reinterpret_cast<uint32_t*>(planes + (size_t)(2 * d) * pstride + k) = we;
-        *reinterpret_cast<uint32_t*>(planes + (size_t)(2 * d + 1) * pstride + k) = wo;
-    }
-}
-
 // 4 x 4 byte transposition: out[d] byte e = in[e] byte d (eight byte permutes).
 __device__ __forceinline__ void transpose_bytes(const uint32_t (&in)[4], uint32_t (&out)[4]) {
     const uint32_t t0 = __builtin_amdgcn_perm(in[1], in[0], 0x05010400u);    // in0.b0 in1.b0 in0.b1 in1.b1
@@ -113,10 +102,10 @@ __device__ __forceinline__ void transpose_bytes(const uint32_t (&in)[4], uint32_
 }
 
 // Digit planes of four consecutive activations given as sign-magnitude fixed point (bit 31 sign, magnitude
-// <= 2^30): eight 32-bit words, one per plane, written at column k of the planes in LDS.  The digits are
+// <= 2^30): eight 32-bit words, one per plane, written at `at` of the first plane in LDS and pitch bytes on for each other.  The digits are
 // transposed first (nibbles of the four magnitudes -> one word of four digits per plane), so that the
 // fp8 conversion and the sign run once per plane word.  Same codes as digit_codes element by element.
-__device__ __forceinline__ void store_planes_of_fixed(unsigned char* planes, int pstride, int k, const uint32_t (&w)[4]) {
+__device__ __forceinline__ void store_planes_of_fixed(unsigned char* at, int pitch, const uint32_t (&w)[4]) {
     uint32_t even[4], odd[4], te[4], to[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -129,8 +118,8 @@ __device__ __forceinline__ void store_planes_of_fixed(unsigned char* planes, int
     const uint32_t sign = ((w[0] >> 24) & 0x80u) | ((w[1] >> 16) & 0x8000u) | ((w[2] >> 8) & 0x800000u) | (w[3] & 0x80000000u);
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        *reinterpret_cast<uint32_t*>(planes + (size_t)(2 * d) * pstride + k) = fp8_of_nibbles(te[d]) | sign;
-        *reinterpret_cast<uint32_t*>(planes + (size_t)(2 * d + 1) * pstride + k) = fp8_of_nibbles(to[d]) | sign;
+        *reinterpret_cast<uint32_t*>(at + 2 * d * pitch) = fp8_of_nibbles(te[d]) | sign;
+        *reinterpret_cast<uint32_t*>(at + (2 * d + 1) * pitch) = fp8_of_nibbles(to[d]) | sign;
     }
 }
 __device__ __forceinline__ uint32_t fixed_word(float v, int ex) { return fixed_magnitude(v, ex) | (v < 0.f ? 0x80000000u : 0u); }
@@ -307,7 +296,7 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
                 uint32_t w[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[e] = fixed_word(xv[r][e], ex_in);
-                store_planes_of_fixed(planes, pstride, k, w);
+                store_planes_of_fixed(planes + k, pstride, w);
             }
         }
     }
@@ -370,34 +359,63 @@ tsvd_gemv_kernel(tsvd_gemv_args p) {
     TICK(4);
 }
 
-// ---- both stages in one launch of one workgroup (small matrices) ---------------------------------
-// For a matrix of a few dozen tiles a call is nothing but latency: two launches, each with its own
-// round trips for x / z and the weights.  Here one workgroup issues ALL its loads at entry (x, then
-// the tiles of V and of U: at most four per wavefront and stage, held in registers), runs stage V
-// with wavefront w on strips w, w + 16, ..., digitises z straight into LDS, and runs stage U
-// from there: one launch, z never leaves the compute unit, and the U tiles arrive while stage V
-// computes.  Same arithmetic as tsvd_gemv_kernel (exact integer sums, fp64 recombination).
-#define FUSED_MAX_ITEMS 4      // tiles per wavefront and stage
+// ---- both stages in one launch (small V) -----------------------------------------------------------
+// For a matrix of a few hundred tiles a call is nothing but latency and launches: two of those, each with its own round
+// trips for x / z and the weights, and 3.4 us of the host's time each.  Here every workgroup computes the whole z (V comes
+// from the L2s, x is a few KB), digitises it into LDS and multiplies its own slice of the rows of U by it: z never leaves
+// the compute unit, and no workgroup waits for another.  All loads are issued at entry in the order of need (the
+// tiles of V and of U stay in registers, at most NV and NU per wavefront), so that the tiles of U arrive while stage V
+// computes.  Every round of stage V leaves its sums in LDS before the one barrier behind them, so there are five
+// barriers whatever the number of ranks.  Same arithmetic as tsvd_gemv_kernel (exact integer sums, fp64
+// recombination), so the same bits.
+// The first arguments are scalars so that they come preloaded in registers (the struct behind them is needed later): the first load
+// is issued 0.15 us earlier.
+// Measured on MI355X, us a call, against one workgroup with barriers in every round of strips (256 x 256 x 512 fp32: 5.75 -> 3.93) or two launches (1000 x 300 x 700
+// bf16 6.8 -> 5.75, 831 x 1173 x 211 fp32 7.25 -> 5.9, 1000 x 300 x 300 fp32 at 4 tokens 7.85 -> 5.4, 2000 x 1000 x 300 fp32 at 16 9.2 -> 6.9).  It takes V
+// of up to six tiles a wavefront: every workgroup takes in all of it, 27 ns a tile where its L2 has not seen them before, so that with
+// eight (1024 x 512) a call is as fast as two launches and with twelve (1024 x 576) 2 us slower.
+struct gemv_fused_rest {
+    void* y;
+    const float* bias;
+    long long x_token, y_token, ldx, ldy;
+    float bound_V;
+    int M, strips_u;
+};
+// Its digit planes in LDS, in the order in which a wavefront reads them: value k = 256 T + 128 h + 32 g + 16 u + e of plane p at
+// 2176 T + 1088 h + 544 u + 128 g + 16 p + e, so that one 16-byte read of all lane groups is 512 consecutive bytes (lanes of columns 8..15 repeat
+// 0..7).  The 32 bytes between such runs spread what a wavefront writes over the banks.  (Planes one behind the other, as in tsvd_gemv_kernel, where
+// lane groups meet in the same banks: 0.1 us more for each round of tiles.  There the copies of 16 bytes a lane are what this order would make slower, by 1 to 3 % of a call.)
+constexpr int FUSED_TILE = 2176;
+__device__ __forceinline__ int fused_at(int p, int k) { return (k >> 8) * FUSED_TILE + (k >> 7 & 1) * 1088 + (k >> 4 & 1) * 544 + (k >> 5 & 3) * 128 + p * 16 + (k & 15); }
+__host__ __device__ constexpr size_t fused_plane_bytes(long long kdim) { return (size_t)((kdim / 256 * FUSED_TILE + 255) & ~255ll); }
+enum : unsigned { FUSED_BF16_IN = 1, FUSED_VEC = 2, FUSED_BF16_OUT = 4 };
+template <int NV, int NU>
 __global__ void __launch_bounds__(1024)
-tsvd_gemv_fused_kernel(tsvd_gemv_fused_args p) {
+tsvd_gemv_fused_kernel(const void* x, const u32x4* tiles_v, const u32x4* tiles_u, const float* S, int N, int nkt_v, int strips_v, int nkt_u, unsigned flags,
+                       gemv_fused_rest p) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const unsigned char* const px = static_cast<const unsigned char*>(p.x) + (size_t)blockIdx.x * p.x_token * (p.x_is_bf16 ? 2 : 4);
-    unsigned char* const py = static_cast<unsigned char*>(p.y) + (size_t)blockIdx.x * p.y_token * (p.out_bf16 ? 2 : 4);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool x_is_bf16 = flags & FUSED_BF16_IN;
+    const unsigned char* px = static_cast<const unsigned char*>(x);
+    if (blockIdx.y > 0) px += (size_t)blockIdx.y * p.x_token * (x_is_bf16 ? 2 : 4);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = lane & 15, g = lane >> 4;
-    const int xstride = p.Np + 16, zstride = p.Kp + 16;
-    unsigned char* xplanes = smem;                                              // [8][Np + 16]
-    unsigned char* zplanes = smem + (((size_t)8 * xstride + 255) & ~(size_t)255);   // [8][Kp + 16]
-    float* wred = reinterpret_cast<float*>(zplanes + (((size_t)8 * zstride + 255) & ~(size_t)255));   // [16][16][8]
-    float* scratch = wred + 16 * 128;
+    const int Np = 256 * nkt_v, Kp = 256 * nkt_u;           // (strips_v: those that hold ranks, to the next 128)
+    // stage V: 16 >> kwl_v strips side by side, each by 1 << kwl_v wavefronts (tile columns q, q + kw, ...), in rounds; stage U the same in one round
+    const int kwl_v = flags >> 8 & 15, kwl_u = flags >> 12;
+    const int par_v = 16 >> kwl_v, q_v = wave & ((1 << kwl_v) - 1), cols_v = (nkt_v + (1 << kwl_v) - 1) >> kwl_v;
+    const int sw_u = 16 >> kwl_u, q_u = wave & ((1 << kwl_u) - 1), strip_u = blockIdx.x * sw_u + (wave >> kwl_u);
+    unsigned char* xplanes = smem;
+    unsigned char* zplanes = smem + fused_plane_bytes(Np);
+    float* red = reinterpret_cast<float*>(zplanes + fused_plane_bytes(Kp));           // [strip][kw][16][8]
+    __shared__ float scratch[16];
 
     // ---- every load, in the order of need
     float xv[4];
     {
         const int k = 4 * threadIdx.x;
-        if (p.x_vec) {
-            const int kc = min(k, p.N - 4);
-            if (p.x_is_bf16) {
+        if (flags & FUSED_VEC) {
+            const int kc = min(k, N - 4);
+            if (x_is_bf16) {
                 const u32x2 v = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(px) + kc);
                 xv[0] = __uint_as_float(v.x << 16); xv[1] = __uint_as_float(v.x & 0xFFFF0000u);
                 xv[2] = __uint_as_float(v.y << 16); xv[3] = __uint_as_float(v.y & 0xFFFF0000u);
@@ -408,25 +426,31 @@ tsvd_gemv_fused_kernel(tsvd_gemv_fused_args p) {
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const size_t off = (size_t)min(k + e, p.N - 1) * p.ldx;
-                xv[e] = p.x_is_bf16 ? __uint_as_float(((uint32_t) reinterpret_cast<const uint16_t*>(px)[off]) << 16)
-                                    : reinterpret_cast<const float*>(px)[off];
+                const size_t off = (size_t)min(k + e, N - 1) * p.ldx;
+                xv[e] = x_is_bf16 ? __uint_as_float(((uint32_t) reinterpret_cast<const uint16_t*>(px)[off]) << 16)
+                                  : reinterpret_cast<const float*>(px)[off];
             }
         }
     }
-    // item j of a stage: strip wave + 16 (j / nkt), tile j % nkt (clamped loads; unused items are never consumed)
-    const int rounds_v = (p.strips_v + 15) / 16, rounds_u = (p.strips_u + 15) / 16;
-    u32x4 pv[FUSED_MAX_ITEMS], pu[FUSED_MAX_ITEMS];
+    // item j of stage V: column j % cols_v of its round j / cols_v (clamped loads; items beyond the last are never consumed)
+    u32x4 pv[NV], pu[NU];
+    {
+        int strip = wave >> kwl_v, col = q_v;
 #pragma unroll
-    for (int j = 0; j < FUSED_MAX_ITEMS; ++j) {
-        const int strip = min(wave + 16 * (j / p.nkt_v), p.strips_v - 1), T = j % p.nkt_v;
-        pv[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p.tiles_v) + ((size_t)strip * p.nkt_v + T) * 64 + lane);
+        for (int j = 0; j < NV; ++j) {
+            pv[j] = tiles_v[((size_t)min(strip, strips_v - 1) * nkt_v + min(col, nkt_v - 1)) * 64 + lane];
+            col += 1 << kwl_v;
+            if (col >= cols_v << kwl_v) col = q_v, strip += par_v;
+        }
     }
+    float s_own[2];                          // scales of the ranks that this thread finishes
 #pragma unroll
-    for (int j = 0; j < FUSED_MAX_ITEMS; ++j) {
-        const int strip = min(wave + 16 * (j / p.nkt_u), p.strips_u - 1), T = j % p.nkt_u;
-        pu[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p.tiles_u) + ((size_t)strip * p.nkt_u + T) * 64 + lane);
-    }
+    for (int r = 0; r < 2; ++r) s_own[r] = S[min((int)threadIdx.x + 1024 * r, Kp - 1)];
+#pragma unroll
+    for (int j = 0; j < NU; ++j)
+        pu[j] = __builtin_nontemporal_load(tiles_u + ((size_t)min(strip_u, p.strips_u - 1) * nkt_u + min(q_u + (j << kwl_u), nkt_u - 1)) * 64 + lane);
+    const int row_own = blockIdx.x * sw_u * 16 + (int)threadIdx.x;
+    const float bias_own = p.bias ? p.bias[min(row_own, p.M - 1)] : 0.f;
 
     // ---- x -> digit planes in LDS
     float m = 0.f;
@@ -434,7 +458,7 @@ tsvd_gemv_fused_kernel(tsvd_gemv_fused_args p) {
         const int k = 4 * threadIdx.x;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            xv[e] = k + e < p.N ? xv[e] : 0.f;
+            xv[e] = k + e < N ? xv[e] : 0.f;
             m = fmaxf(m, fabsf(xv[e]));
         }
     }
@@ -443,71 +467,87 @@ tsvd_gemv_fused_kernel(tsvd_gemv_fused_args p) {
     __syncthreads();
     m = wave_max(scratch[lane & 15]);
     const int ex_x = bound_exponent(m);
-    const int ex_z = bound_exponent(p.bound_V * m) + 1;
+    const int ex_z = bound_exponent(p.bound_V * m) + 1;   // one more bit for the rounding of the bound itself
     {
         const int k = 4 * threadIdx.x;
-        if (k < p.Np) {
-            uint32_t ev[4], od[4];
+        if (k < Np) {
+            uint32_t w[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) digit_codes(xv[e], ex_x, ev[e], od[e]);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const uint32_t we = ((ev[0] >> (8 * d)) & 0xFFu) | (((ev[1] >> (8 * d)) & 0xFFu) << 8) |
-                                    (((ev[2] >> (8 * d)) & 0xFFu) << 16) | (((ev[3] >> (8 * d)) & 0xFFu) << 24);
-                const uint32_t wo = ((od[0] >> (8 * d)) & 0xFFu) | (((od[1] >> (8 * d)) & 0xFFu) << 8) |
-                                    (((od[2] >> (8 * d)) & 0xFFu) << 16) | (((od[3] >> (8 * d)) & 0xFFu) << 24);
-                *reinterpret_cast<uint32_t*>(xplanes + (size_t)(2 * d) * xstride + k) = we;
-                *reinterpret_cast<uint32_t*>(xplanes + (size_t)(2 * d + 1) * xstride + k) = wo;
-            }
+            for (int e = 0; e < 4; ++e) w[e] = fixed_word(xv[e], ex_x);
+            store_planes_of_fixed(xplanes + fused_at(0, k), 16, w);
         }
     }
     __syncthreads();
 
-    // One round of a stage: wavefront w multiplies strip w + 16 r with the planes, the 256 rows of
-    // the round are finished by threads 0..255 (row t of the round) from the plane sums in LDS.
-    auto round_sums = [&](const u32x4 (&tiles)[FUSED_MAX_ITEMS], int r, int nkt, const unsigned char* planes, int pstride) {
-        const unsigned char* xlane = planes + (size_t)(i & 7) * pstride + 32 * g;
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < FUSED_MAX_ITEMS; ++j)
-            if (j / nkt == r) tile_steps(tiles[j], xlane + (j % nkt) * 256, acc0, acc1);
+    // the sums of a strip's part, rows 4 g + v (D layout of the 16x16 MFMA: lane (i, g) holds column i; only columns 0..7 matter)
+    auto leave = [&](int slot, const f32x4& acc) {
         if (i < 8) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) wred[wave * 128 + (4 * g + v) * 8 + i] = acc0[v] + acc1[v];
+            for (int v = 0; v < 4; ++v) red[slot * 128 + (4 * g + v) * 8 + i] = acc[v];
         }
     };
-    // ---- stage V: z = S * (V x), digitised into LDS
-    for (int r = 0; r < rounds_v; ++r) {
-        round_sums(pv, r, p.nkt_v, xplanes, xstride);
-        __syncthreads();
-        if (threadIdx.x < 256) {
-            const int row = 256 * r + threadIdx.x;
-            if (row < p.Kp) {
-                const double val = combine_planes(wred + threadIdx.x * 8) * pow2(ex_x - 31);
-                const float z = (float)((double)p.S[row] * val);
-                uint32_t ev, od;
-                digit_codes(z, ex_z, ev, od);
+    // row `row` of the strips' sums over the 1 << kwl parts (integers < 2^24: exact)
+    auto total = [&](int row, int kwl) {
+        const float* src = red + (size_t)((row >> 4) << kwl) * 128 + (row & 15) * 8;
+        float sums[8];
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    zplanes[(size_t)(2 * d) * zstride + row] = (unsigned char)(ev >> (8 * d));
-                    zplanes[(size_t)(2 * d + 1) * zstride + row] = (unsigned char)(od >> (8 * d));
-                }
+        for (int d = 0; d < 8; ++d) sums[d] = src[d];
+        for (int c = 1; c < 1 << kwl; ++c)
+#pragma unroll
+            for (int d = 0; d < 8; ++d) sums[d] += src[c * 128 + d];
+        double a = (double)sums[7];
+#pragma unroll
+        for (int d = 6; d >= 0; --d) a = a * 16.0 + (double)sums[d];
+        return a;
+    };
+    // ---- stage V: z = S * (V x), digitised into LDS
+    {
+        const unsigned char* xlane = xplanes + (i & 7) * 16 + 128 * g;
+        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+        int strip = wave >> kwl_v, col = q_v;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            if (strip < strips_v && col < nkt_v) tile_steps<544, 1088>(pv[j], xlane + col * FUSED_TILE, acc0, acc1);
+            col += 1 << kwl_v;
+            if (col >= cols_v << kwl_v) {
+                if (strip < strips_v) leave((strip << kwl_v) + q_v, acc0 + acc1);
+                acc0 = acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+                col = q_v, strip += par_v;
             }
         }
-        __syncthreads();
     }
-    // ---- stage U: y = U z
-    for (int r = 0; r < rounds_u; ++r) {
-        round_sums(pu, r, p.nkt_u, zplanes, zstride);
-        __syncthreads();
-        if (threadIdx.x < 256) {
-            const int row = 256 * r + threadIdx.x;
-            if (row < p.M) {
-                const double val = combine_planes(wred + threadIdx.x * 8) * pow2(ex_z - 31);
-                tsvd_store_y(py, (size_t)row * p.ldy, (float)(p.bias ? val + (double)p.bias[row] : val), p.out_bf16);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int row = (int)threadIdx.x + 1024 * r;
+        if (row < Kp) {
+            const float z = row < 16 * strips_v ? (float)((double)s_own[r] * (total(row, kwl_v) * pow2(ex_x - 31))) : 0.f;
+            uint32_t ev, od;
+            digit_codes(z, ex_z, ev, od);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                zplanes[fused_at(2 * d, row)] = (unsigned char)(ev >> (8 * d));
+                zplanes[fused_at(2 * d + 1, row)] = (unsigned char)(od >> (8 * d));
             }
         }
-        __syncthreads();
+    }
+    __syncthreads();
+    // ---- stage U: y = U z, rows of this workgroup
+    {
+        const unsigned char* zlane = zplanes + (i & 7) * 16 + 128 * g;
+        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NU; ++j) {
+            const int T = q_u + (j << kwl_u);
+            if (T < nkt_u) tile_steps<544, 1088>(pu[j], zlane + T * FUSED_TILE, acc0, acc1);
+        }
+        leave(wave, acc0 + acc1);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < 16 * sw_u && row_own < p.M) {
+        const double val = total(threadIdx.x, kwl_u) * pow2(ex_z - 31);
+        unsigned char* py = static_cast<unsigned char*>(p.y) + (size_t)blockIdx.y * p.y_token * (flags & FUSED_BF16_OUT ? 2 : 4);
+        tsvd_store_y(py, (size_t)row_own * p.ldy, (float)(p.bias ? val + (double)bias_own : val), (flags & FUSED_BF16_OUT) != 0);
     }
 }
 
@@ -641,7 +681,7 @@ tsvd_gemv_onepass_kernel(tsvd_gemv_onepass_args p) {
             uint32_t w[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) w[e] = fixed_word(xv[r][e], ex_x);
-            store_planes_of_fixed(xplanes, xstride, k, w);
+            store_planes_of_fixed(xplanes + k, xstride, w);
         }
     }
     TICK(10);
@@ -747,7 +787,7 @@ tsvd_gemv_onepass_kernel(tsvd_gemv_onepass_args p) {
                 all = all && (unsigned)(zw[r][e] >> 32) == tag;
             }
             if (all) {
-                store_planes_of_fixed(zplanes, zstride, k, w);
+                store_planes_of_fixed(zplanes + k, zstride, w);
             } else {
                 // (a slice holds a multiple of 16 rows, so the four elements lie in one slice)
                 const int j = k / slice_rows;
@@ -863,10 +903,6 @@ hipError_t tsvd_launch_gemv_onepass(const tsvd_gemv_onepass_args& a, hipStream_t
     return hipGetLastError();
 }
 
-size_t gemv_fused_lds_bytes(long long Np, long long Kp) {
-    return ((8 * (size_t)(Np + 16) + 255) & ~(size_t)255) + ((8 * (size_t)(Kp + 16) + 255) & ~(size_t)255) + (16 * 128 + 64) * sizeof(float);
-}
-
 namespace {
 template <bool STAGE_U, int ROUNDS>
 hipError_t init_one() {
@@ -886,25 +922,69 @@ size_t gemv_lds_bytes(long long kdim) {
 }
 }  // namespace
 
-bool tsvd_gemv_fused_fits(long long Mp, long long Kp, long long Np) {
-    // at most FUSED_MAX_ITEMS tiles per wavefront and stage; x in one load round
+namespace {
+constexpr int FUSED_NV = 6, FUSED_NU = 4;      // tiles per wavefront in registers at most
+// How a call runs in one launch: splits of a strip's columns over wavefronts, items per wavefront, grid, LDS.
+struct fused_shape {
+    int kwl_v, kwl_u, items_v, items_u;
+    unsigned slices;
+    size_t lds;
+};
+bool shape_fused(const tsvd_gemv_fused_args& a, int cus, fused_shape* f) {
+    if (a.Np > 4096 || a.Kp > 2048 || a.N < 1 || a.tokens < 1 || a.strips_v < 1 || a.strips_v * 16 > a.Kp || a.nkt_v * 256 != a.Np || a.Kp % 256 || a.strips_u < 1) return false;
+    const size_t planes = fused_plane_bytes(a.Np) + fused_plane_bytes(a.Kp);
+    f->items_v = FUSED_NV + 1;
+    for (int kl = 0; kl <= 4 && (1 << kl) < 2 * a.nkt_v; ++kl) {
+        const int par = 16 >> kl, items = (a.strips_v + par - 1) / par * ((a.nkt_v + (1 << kl) - 1) >> kl);
+        const size_t lds = planes + (size_t)std::max(a.strips_v << kl, 16) * 512;
+        if (items < f->items_v && lds + 64 <= TSVD_SKINNY_MAX_LDS) f->items_v = items, f->kwl_v = kl, f->lds = lds;
+    }
+    if (f->items_v > FUSED_NV) return false;
+    // as few strips per workgroup as leave every compute unit one at most
+    const int nkt_u = a.Kp / 256;
+    for (int kl = 4; kl >= 0; --kl) {
+        if ((1 << kl) >= 2 * nkt_u && kl > 2) continue;      // (idle wavefronts; 4 strips per workgroup at least)
+        f->kwl_u = kl;
+        f->items_u = (nkt_u + (1 << kl) - 1) >> kl;
+        f->slices = (unsigned)((a.strips_u + (16 >> kl) - 1) / (16 >> kl));
+        if ((long long)f->slices * a.tokens <= cus) break;
+    }
+    return f->items_u <= FUSED_NU && (long long)f->slices * a.tokens <= cus;
+}
+}  // namespace
+
+bool tsvd_gemv_one_workgroup(long long Mp, long long Kp, long long Np) {
     const long long rounds_v = (Kp / 16 + 15) / 16, rounds_u = (Mp / 16 + 15) / 16;
-    return Np <= 4096 && rounds_v * (Np / 256) <= FUSED_MAX_ITEMS && rounds_u * (Kp / 256) <= FUSED_MAX_ITEMS &&
-           gemv_fused_lds_bytes(Np, Kp) <= TSVD_SKINNY_MAX_LDS;
+    return Np <= 4096 && rounds_v * (Np / 256) <= 4 && rounds_u * (Kp / 256) <= 4;
 }
 
-hipError_t tsvd_launch_gemv_fused(const tsvd_gemv_fused_args& a, hipStream_t stream) {
-    if (a.tokens < 1 || a.strips_v < 1 || a.strips_u < 1 || a.nkt_v < 1 || a.nkt_u < 1 || a.Np > 4096 ||
-        ((a.strips_v + 15) / 16) * a.nkt_v > FUSED_MAX_ITEMS || ((a.strips_u + 15) / 16) * a.nkt_u > FUSED_MAX_ITEMS)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(tsvd_gemv_fused_kernel, dim3(a.tokens), dim3(1024), gemv_fused_lds_bytes(a.Np, a.Kp), stream, a);
+bool tsvd_gemv_fused_fits(const tsvd_gemv_fused_args& a, int cus) {
+    fused_shape f;
+    return shape_fused(a, cus, &f);
+}
+
+hipError_t tsvd_launch_gemv_fused(const tsvd_gemv_fused_args& a, int cus, hipStream_t stream) {
+    fused_shape f;
+    if (!shape_fused(a, cus, &f)) return hipErrorInvalidValue;
+    const gemv_fused_rest r = {a.y, a.bias, a.x_token, a.y_token, a.ldx, a.ldy, a.bound_V, a.M, a.strips_u};
+    const unsigned flags = (a.x_is_bf16 ? FUSED_BF16_IN : 0u) | (a.x_vec ? FUSED_VEC : 0u) | (a.out_bf16 ? FUSED_BF16_OUT : 0u) |
+                           (unsigned)(f.kwl_v << 8 | f.kwl_u << 12);
+    const dim3 grid(f.slices, (unsigned)a.tokens), block(1024);
+#define FUSED_LAUNCH(NV_, NU_) hipLaunchKernelGGL((tsvd_gemv_fused_kernel<NV_, NU_>), grid, block, f.lds, stream, a.x, static_cast<const u32x4*>(a.tiles_v), \
+        static_cast<const u32x4*>(a.tiles_u), a.S, a.N, a.nkt_v, a.strips_v, a.Kp / 256, flags, r)
+    if (f.items_v <= 2 && f.items_u <= 1) FUSED_LAUNCH(2, 1);
+    else if (f.items_v <= 2) FUSED_LAUNCH(2, 4);
+    else if (f.items_v <= 4) FUSED_LAUNCH(4, 4);
+    else FUSED_LAUNCH(6, 4);
+#undef FUSED_LAUNCH
     return hipGetLastError();
 }
 
 hipError_t tsvd_gemv_init() {
     hipError_t e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_gemv_fused_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 TSVD_SKINNY_MAX_LDS)) != hipSuccess) return e;
+    for (const void* k : {(const void*)tsvd_gemv_fused_kernel<2, 1>, (const void*)tsvd_gemv_fused_kernel<2, 4>, (const void*)tsvd_gemv_fused_kernel<4, 4>,
+                          (const void*)tsvd_gemv_fused_kernel<6, 4>})
+        if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, TSVD_SKINNY_MAX_LDS)) != hipSuccess) return e;
 #define ONEPASS_ATTR(NV_, NU_) \
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_gemv_onepass_kernel<NV_, NU_>), \
                                  hipFuncAttributeMaxDynamicSharedMemorySize, TSVD_SKINNY_MAX_LDS)) != hipSuccess) return e;

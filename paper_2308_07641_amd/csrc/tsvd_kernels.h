@@ -58,14 +58,13 @@ struct tsvd_gemv_args {
     long long* clocks;                    // optional tuning aid: [grid][16] phase timestamps, or null
     int tokens; long long x_token, y_token;   // tokens of the launch (each on workgroups of its own), elements from one to the next
 };
-// Both stages of a single token in ONE launch of ONE workgroup, for matrices of at most 64 tiles
-// per stage (tsvd_gemv.hip): z never leaves LDS.
+// Both stages in ONE launch, every workgroup computing the whole z for its own slice of y's rows (tsvd_gemv.hip): small V.
 struct tsvd_gemv_fused_args {
-    const void* tiles_v; int strips_v, nkt_v;     // V: Kp/16 strips, Np/256 tiles
+    const void* tiles_v; int strips_v, nkt_v;     // V: the strips that hold ranks (to the next 128: the order of the last ranks is the format's), Np/256 tiles
     const void* tiles_u; int strips_u, nkt_u;     // U: ceil(M/16) strips, Kp/256 tiles
     int N, Np, Kp, M;
     const void* x; int x_is_bf16; int x_vec; long long ldx;
-    int tokens; long long x_token, y_token;       // a workgroup per token
+    int tokens; long long x_token, y_token;       // tokens of the launch (each on workgroups of its own)
     const float* S; float bound_V;
     void* y; long long ldy; const float* bias; int out_bf16;
 };
@@ -98,8 +97,9 @@ size_t tsvd_gemv_dense_lds(long long Kp);
 hipError_t tsvd_gemv_dense_init();
 hipError_t tsvd_launch_gemv_dense(const tsvd_gemv_dense_args& a, hipStream_t stream);
 void tsvd_internal_dense_from_blob(const void* blob, void* out);   // tsvd_pack.cpp: recodes U's tiles of a host blob
-bool tsvd_gemv_fused_fits(long long Mp, long long Kp, long long Np);
-hipError_t tsvd_launch_gemv_fused(const tsvd_gemv_fused_args& a, hipStream_t stream);
+bool tsvd_gemv_one_workgroup(long long Mp, long long Kp, long long Np);   // at most 64 tiles per stage, four a wavefront
+bool tsvd_gemv_fused_fits(const tsvd_gemv_fused_args& a, int cus);
+hipError_t tsvd_launch_gemv_fused(const tsvd_gemv_fused_args& a, int cus, hipStream_t stream);
 hipError_t tsvd_gemv_init();
 bool tsvd_gemv_fits(long long Np, long long Kp);
 hipError_t tsvd_launch_gemv(const tsvd_gemv_args& a, bool stage_u, hipStream_t stream);
