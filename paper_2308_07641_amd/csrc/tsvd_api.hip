@@ -774,6 +774,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
         t.bias = bias_dev;
         t.out_bf16 = oo.out_bf16;
         t.y_token_major = oo.token_major;
+        t.cus = h->cu_count;
         const hipError_t te = tsvd_thin_launch(t, plan.thin, s);
         if (te != hipErrorNotSupported) return te == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
     }

@@ -529,6 +529,7 @@ extern "C" tsvd_status tsvd_conv2d_forward(const tsvd_handle* h, const tsvd_conv
         t.ldy = taps ? p.ldt : p.Bv;
         t.bias = taps ? nullptr : bias_dev;
         t.out_bf16 = !taps && y_dtype == TSVD_BF16;
+        t.cus = cus;
         const hipError_t e = tsvd_thin_launch(t, thin, s);
         if (e != hipSuccess && e != hipErrorNotSupported) return TSVD_EDEVICE;
         mapped = e == hipSuccess;

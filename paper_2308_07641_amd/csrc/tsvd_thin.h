@@ -20,6 +20,7 @@ struct tsvd_thin_problem {
     long long ldy;
     const float* bias;
     int out_bf16, y_token_major;
+    int cus;                        // compute units of the device
 };
 // Blocks of 128 indices of x that a panel of `tiles` token tiles holds in LDS at a time, 0 where such panels are not possible.
 int tsvd_thin_chunk(long long K, long long N, int tiles, bool conv);

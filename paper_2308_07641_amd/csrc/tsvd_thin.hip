@@ -46,6 +46,7 @@ struct thin_args {
     const float* bias;
     int M, out_bf16, token_major, utm;       // utm: 16-row blocks per unit of stage U
     int runs;                                // neighbouring panels on one XCD
+    int slices;                              // workgroups of a panel, each with the whole z and its part of y's rows
 };
 
 template <int TN, int RB, int SOURCE, bool CHUNKED>
@@ -259,21 +260,23 @@ tsvd_thin_panel_kernel(thin_args p) {
     auto stage_u = [&](auto tm_c) {
         constexpr int TM = decltype(tm_c)::value;
         const int units = (p.M + 16 * TM - 1) / (16 * TM);
-        int nu = wave, nb = 0;                                // the next fetch: unit, block
-        const int last_unit = wave + (units - 1 - wave) / NW * NW;
+        // units are dealt to the wavefronts of all slices of the panel
+        const int first = wave + NW * blockIdx.y, stride = NW * gridDim.y;
+        int nu = first, nb = 0;                               // the next fetch: unit, block
+        const int last_unit = first + (units - 1 - first) / stride * stride;
         auto next = [&](words (&w)[TM]) {
 #pragma unroll
             for (int a = 0; a < TM; ++a) w[a] = fetch(u_rsrc, lane * 16, (nu * TM + a) * p.nkt_u * 1024, nb);
             if (nb + PER < p.nub) nb += PER;
             else if (nu < last_unit) {                        // (at the end: the last fetch again)
-                nu += NW;
+                nu += stride;
                 nb = 0;
             }
         };
         words w0[TM];
-        if (wave < units) next(w0);
+        if (first < units) next(w0);
         __syncthreads();                                      // the planes of z are complete
-        for (int unit = wave; unit < units; unit += NW) {
+        for (int unit = first; unit < units; unit += stride) {
             const int strip0 = unit * TM;
             f32x4 acc[TM][TN];
 #pragma unroll
@@ -363,7 +366,7 @@ template <int TN, int RB, int SOURCE, bool CHUNKED>
 auto kernel() { return tsvd_thin_panel_kernel<TN, RB, SOURCE, CHUNKED>; }
 template <int TN, int RB, int SOURCE>
 hipError_t launch(const thin_args& a, int lds, hipStream_t stream) {
-    const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN))), block(512);
+    const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN)), (unsigned)a.slices), block(512);
     if (a.buffers == 2) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true>()), grid, block, lds, stream, a);
     else hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false>()), grid, block, lds, stream, a);
     return hipGetLastError();
@@ -453,9 +456,18 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
     // every call 0.947 and 0.976; where it says yes 0.70 .. 1.02.
     const int piece = a.out_bf16 ? 2 : 4;
     a.runs = g.source == THIN_FEATURE_MAJOR && g.B > 60 * 16 * tiles && (a.ldy * piece % 64 != 0 || a.M * piece <= 6 * a.N);
-    // rows per unit of stage U: the larger units unless they leave wavefronts without one
-    auto passes = [&](int utm) { return ((a.M + 16 * utm - 1) / (16 * utm) + 7) / 8 * utm; };
-    a.utm = passes(8) <= passes(4) && passes(8) <= passes(2) ? 8 : passes(4) <= passes(2) ? 4 : 2;
+    // Rows per unit of stage U: the larger units unless they leave wavefronts without one.  Fewer panels than half of the compute units: several workgroups
+    // for each, which all make the whole z of their tokens and deal the units among them, as many as shorten stage U (888 x 384 x 69 at 881
+    // tokens, 56 panels: 7.8 us with one, 7.0 with two, 6.6 with four; 918 x 348 x 192 at 320 8.0 -> 6.65; convolutions of few positions 0.79 to 0.98 of the time, no call slower).
+    auto passes = [&](int utm, int slices) { return ((a.M + 16 * utm - 1) / (16 * utm) + 8 * slices - 1) / (8 * slices) * utm; };
+    const long long panels = (g.B + 16 * tiles - 1) / (16 * tiles);
+    int best = 1 << 30;
+    a.slices = 1;
+    for (int slices = 1; slices == 1 || slices * panels <= g.cus; ++slices) {
+        for (int utm : {8, 4, 2})
+            if (passes(utm, slices) < best) best = passes(utm, slices), a.slices = slices, a.utm = utm;
+        if (best == 2) break;
+    }
     const bool conv = g.source == THIN_CONV;
     if (conv && g.kv1 * g.kv2 > MAX_TAPS) return hipErrorNotSupported;
     a.chunk = tsvd_thin_chunk(hd.K, hd.N, tiles, conv);

@@ -196,3 +196,13 @@ def test_large_batches_with_massive_outliers(tsvd, M, N, K, B, switches, outlier
     assert (y2 - want)[:, :free_rows].norm() <= 2.5e-4 * want[:, :free_rows].norm()
     assert (y - want).norm() <= 2.5e-4 * want.norm()
     tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("M,N,K,B", [(1, 40, 70, 20), (31, 300, 130, 33), (33, 129, 260, 17), (129, 300, 900, 40), (2050, 200, 130, 50), (4100, 130, 1020, 18), (9000, 257, 100, 65),
+                                     (520, 140, 257, 2040), (300, 260, 90, 2049)])
+@pytest.mark.parametrize("tiles", [1, 2])
+def test_thin_panels_of_several_workgroups(tsvd, M, N, K, B, tiles):
+    """Few panels: the rows of y dealt among several workgroups of a panel, down to units of 32 rows, the last ones without any; and the numbers of
+    panels where two workgroups a panel begin.  (The bits of one workgroup a panel: the bound is that of test_thin_panels.)"""
+    print(f"case thin of several workgroups {M} {N} {K} {B} {tiles}", flush=True)
+    _check(tsvd, M, N, K, B, "bf16", {"TSVD_THIN": tiles})
