@@ -4,7 +4,7 @@
 // leading singular direction: p squarings are 2^p power steps.  On the close singular values of a random matrix (gaps of
 // 1e-2 .. 1e-4) that takes 10 .. 18 launches that fill the chip, where Lanczos bidiagonalisation takes 60 .. 100 steps
 // of four launches each, two of them a single workgroup: 2.5 ms against 0.16 ms for the pair of a [512, 256] Laplace
-// matrix (64 steps at 39 us; 11 squarings at 5.6 us in a kernel trace, and 0.1 ms of launches and waits).  Rounding: every squaring perturbs its matrix by a few units in the last place of its norm, so the
+// matrix (64 steps at 39 us; 11 squarings at 5.2 us in a kernel trace, and 0.1 ms of launches and waits).  Rounding: every squaring perturbs its matrix by a few units in the last place of its norm, so the
 // vector is off by rounding over the gap, as with any backward-stable method.
 //
 // The result is X x_j, with x_j the column of X that has the largest diagonal entry (to nine bits): that entry is at least trace / n, so
@@ -40,7 +40,7 @@ constexpr int PAIR_MAX_N = 2048;
 // The order of the contraction index is free as long as both operands share it: lane group g of a wavefront takes the
 // indices 8 t + 2 g, 8 t + 2 g + 1 of its share with load t, so a load is 16 bytes per lane and touches 16 row segments of
 // 64 bytes.  Bound by the latency of the loads and of the chain of MFMAs (64 cycles each): small tiles on many
-// workgroups while n is small (n = 256: 136 workgroups of 16 MFMAs per wavefront, 5.6 us; on eight wavefronts of 8 MFMAs 5.9 us; the Gram matrix of
+// workgroups while n is small (n = 256: 136 workgroups of 16 MFMAs per wavefront, 5.2 us; on eight wavefronts of 8 MFMAs 5.9 against 5.6 us; the Gram matrix of
 // 512 rows 6.2 us on four, 5.7 us on eight), 32 x 32 tiles, which read half as much per product, beyond.
 //
 // GRAM (first launch): P is R by its rows (TR = false) or columns (TR), any pitch; rows beyond n and indices beyond L read
@@ -52,35 +52,61 @@ constexpr int PAIR_MAX_N = 2048;
 // sum lambda^2 / (sum lambda)^2 of the one before, 1 - 2 (lambda_2 / lambda_1)^(2^p) near the end.  Once that is within 1e-6 of
 // 1, X itself has the ratio squared, below 2.5e-13, and is the result (X x_j has it squared again, times at most sqrt(n)):
 // every workgroup of this and the later launches returns.
+// (GRAM only; the scalars in front of it come preloaded in registers)
+struct pair_square_rest {
+    int n, M, N;
+    const double* v0;
+    double* s;
+};
+// The tiles of the upper triangle by XCD (workgroups go to the eight of them in turn), where no XCD gets more than one for each of its 32 compute units: the blocks
+// of 16 T rows in four groups of k; six XCDs take a pair of groups each, two take two groups' own triangles, so that every L2 fetches half
+// of the matrix instead of all of it (with arguments preloaded and results written through: a squaring of n = 256 5.7 -> 5.2 us, a component of [512, 256] 104 -> 96).  With more tiles in turn (768 x 700, where XCDs would get 36 to 42: 2.2 -> 2.9 ms).
+// Returns false for workgroups without a tile.
+__host__ __device__ constexpr int pair_group(int nb) { return (nb + 3) / 4; }
+__host__ __device__ constexpr int pair_grid(int nb) { return pair_group(nb) <= 5 ? 8 * pair_group(nb) * (pair_group(nb) + 1) : nb * (nb + 1) / 2; }
+__device__ __forceinline__ bool pair_tile(int nb, int block, int& bi, int& bj) {
+    const int k = pair_group(nb), xcd = block & 7, t = block >> 3, half = k * (k + 1) / 2;
+    int u = block, from = 0;                 // place in a triangle, its first block
+    if (k <= 5) {
+        if (xcd < 6) {
+            const int gi = xcd < 3 ? 0 : xcd < 5 ? 1 : 2, gj = xcd < 3 ? xcd + 1 : xcd < 5 ? xcd - 1 : 3;
+            bi = gi * k + t / k, bj = gj * k + t % k;
+            return t < k * k && bj < nb;
+        }
+        u = t < half ? t : t - half;
+        from = (2 * (xcd - 6) + (t >= half)) * k;
+    }
+    int j = (int)((sqrtf(8.0f * (float)u + 1.0f) - 1.0f) * 0.5f);
+    while (j * (j + 1) / 2 > u) --j;
+    while ((j + 1) * (j + 2) / 2 <= u) ++j;
+    bi = from + u - j * (j + 1) / 2, bj = from + j;
+    return bj < nb;
+}
 template <int T, bool GRAM, bool TR>
 __global__ void __launch_bounds__(T == 1 && GRAM ? 512 : 256)
-tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step) {
+tsvd_pair_square_kernel(const double* __restrict__ P, double* __restrict__ Y, const double* __restrict__ D, double* __restrict__ YD, tsvd_pair_state* state,
+                        int np, int step, pair_square_rest p) {
     constexpr int W = T == 1 && GRAM ? 8 : 4, SHARE = 256 / W, LOADS = SHARE / 8;      // wavefronts; indices of one at a time
     __shared__ __align__(16) double part[W][T * T * 256];
     __shared__ double red[W];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
-    const int nb = p.np / (16 * T), tiles = nb * (nb + 1) / 2;
+    const int nb = np / (16 * T);
     if constexpr (GRAM) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = -1;
-        if ((int)blockIdx.x >= tiles) {                     // s = R v0, a wavefront per row
-            const int m = ((int)blockIdx.x - tiles) * W + wave;
+        if (blockIdx.x == 0 && threadIdx.x == 0) state->last = -1;
+        if ((int)blockIdx.x >= pair_grid(nb)) {             // s = R v0, a wavefront per row
+            const int m = ((int)blockIdx.x - pair_grid(nb)) * W + wave;
             if (m < p.M) {
                 double a = 0.0;
-                for (int k = lane; k < p.N; k += 64) a += R[(size_t)m * p.N + k] * p.v0[k];
+                for (int k = lane; k < p.N; k += 64) a += P[(size_t)m * p.N + k] * p.v0[k];
                 a = wave_sum(a);
                 if (lane == 0) p.s[m] = a;
             }
             return;
         }
     }
-    int bj = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
-    while (bj * (bj + 1) / 2 > (int)blockIdx.x) --bj;
-    while ((bj + 1) * (bj + 2) / 2 <= (int)blockIdx.x) ++bj;
-    const int bi = (int)blockIdx.x - bj * (bj + 1) / 2;
-
-    const double* P = GRAM ? R : p.X[step & 1];
-    const double* D = p.diag[step & 1];
-    const int L = GRAM ? (TR ? p.M : p.N) : p.np;
+    int bi, bj;
+    if (!pair_tile(nb, blockIdx.x, bi, bj)) return;
+    const int L = GRAM ? (TR ? p.M : p.N) : np;
     f64x4 acc[T][T];
 #pragma unroll
     for (int a = 0; a < T; ++a)
@@ -91,8 +117,8 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
 #pragma unroll
     for (int q = 0; q < T; ++q) {
         const int ra = (bi * T + q) * 16 + i, rb = (bj * T + q) * 16 + i;
-        arow[q] = GRAM ? P + (TR ? (size_t)min(ra, p.n - 1) : (size_t)min(ra, p.n - 1) * p.N) : P + (size_t)ra * p.np;
-        brow[q] = GRAM ? P + (TR ? (size_t)min(rb, p.n - 1) : (size_t)min(rb, p.n - 1) * p.N) : P + (size_t)rb * p.np;
+        arow[q] = GRAM ? P + (TR ? (size_t)min(ra, p.n - 1) : (size_t)min(ra, p.n - 1) * p.N) : P + (size_t)ra * np;
+        brow[q] = GRAM ? P + (TR ? (size_t)min(rb, p.n - 1) : (size_t)min(rb, p.n - 1) * p.N) : P + (size_t)rb * np;
     }
     auto load = [&](const double* row, int k) -> f64x2 {     // P[row][k], P[row][k + 1]; GRAM: indices clamped
         if constexpr (!GRAM) return *reinterpret_cast<const f64x2*>(row + k);
@@ -103,12 +129,12 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
     double tr = 0.0, trace = 0.0, scale = 1.0;
     int done = -1;
     if constexpr (!GRAM) {
-        done = p.state->last;
-        tr = D[min((int)threadIdx.x, p.np - 1)];
+        done = state->last;
+        tr = D[min((int)threadIdx.x, np - 1)];
     }
     auto sum_trace = [&] {                                   // the wavefronts' shares of the trace into red
-        if ((int)threadIdx.x >= p.np) tr = 0.0;
-        for (int d = threadIdx.x + 64 * W; d < p.np; d += 64 * W) tr += D[d];
+        if ((int)threadIdx.x >= np) tr = 0.0;
+        for (int d = threadIdx.x + 64 * W; d < np; d += 64 * W) tr += D[d];
         tr = wave_sum(tr);
         if (lane == 0) red[wave] = tr;
     };
@@ -186,14 +212,15 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
         if (step > 0) {
             trace = all();
             if (fabs(1.0 - trace) < 1e-6) {
-                if (blockIdx.x == 0 && threadIdx.x == 0) p.state->last = step;
+                if (blockIdx.x == 0 && threadIdx.x == 0) state->last = step;
                 return;
             }
         }
         c = trace > 0.0 ? 1.0 / (trace * trace) : 0.0;
     }
-    double* Y = p.X[GRAM ? 0 : (step + 1) & 1];
-    double* YD = p.diag[GRAM ? 0 : (step + 1) & 1];
+    // Written through to memory at once: what a launch leaves in the L2s of the XCDs that computed it is written back before the next one starts (0.3 us of
+    // 5.7).  (Not for R, the vectors or the system, whose launches write less or in lines of their own: 0.0 to 0.7 us longer.)
+    auto store_through = [](double* at, double v) { __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     // (eight wavefronts: the second half of them writes the mirror image)
     const int r = (threadIdx.x & 255) >> 4, cc = threadIdx.x & 15;
     const bool first = threadIdx.x < 256, second = W == 4 || !first;
@@ -211,10 +238,10 @@ tsvd_pair_square_kernel(tsvd_pair_plan p, const double* __restrict__ R, int step
             };
             if (first) {
                 const double y = sum(r * 16 + cc);
-                Y[(size_t)(row + r) * p.np + col + cc] = y;
-                if (row + r == col + cc) YD[row + r] = y;
+                store_through(&Y[(size_t)(row + r) * np + col + cc], y);
+                if (row + r == col + cc) store_through(&YD[row + r], y);
             }
-            if (second && bi != bj) Y[(size_t)(col + r) * p.np + row + cc] = sum(cc * 16 + r);
+            if (second && bi != bj) store_through(&Y[(size_t)(col + r) * np + row + cc], sum(cc * 16 + r));
         }
 }
 
@@ -520,19 +547,24 @@ void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* p, hipSt
 void tsvd_pair_square(const tsvd_pair_plan& p, const double* R, int from, int to, hipStream_t stream) {
     const bool big = p.np > 384;
     const int nb = p.np / (big ? 32 : 16);
-    const unsigned tiles = (unsigned)(nb * (nb + 1) / 2);
+    const unsigned tiles = (unsigned)pair_grid(nb);
+    const pair_square_rest rest = {p.n, p.M, p.N, p.v0, p.s};
+#define PAIR_SQUARE(T, GRAM, TR, grid, threads, in, at, step) \
+    hipLaunchKernelGGL((tsvd_pair_square_kernel<T, GRAM, TR>), dim3(grid), dim3(threads), 0, stream, in, p.X[at], p.diag[1 - (at)], p.diag[at], p.state, p.np, step, rest)
     if (from == 0) {
         const bool cols = p.N <= p.M;
         const unsigned grid = tiles + (cols ? 0u : (unsigned)(big ? (p.M + 3) / 4 : (p.M + 7) / 8));
-        if (big && cols) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, true, true>), dim3(grid), dim3(256), 0, stream, p, R, 0);
-        else if (big) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, true, false>), dim3(grid), dim3(256), 0, stream, p, R, 0);
-        else if (cols) hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, true>), dim3(grid), dim3(512), 0, stream, p, R, 0);
-        else hipLaunchKernelGGL((tsvd_pair_square_kernel<1, true, false>), dim3(grid), dim3(512), 0, stream, p, R, 0);
+        if (big && cols) PAIR_SQUARE(2, true, true, grid, 256, R, 0, 0);
+        else if (big) PAIR_SQUARE(2, true, false, grid, 256, R, 0, 0);
+        else if (cols) PAIR_SQUARE(1, true, true, grid, 512, R, 0, 0);
+        else PAIR_SQUARE(1, true, false, grid, 512, R, 0, 0);
     }
     for (int step = from; step < to; ++step) {
-        if (big) hipLaunchKernelGGL((tsvd_pair_square_kernel<2, false, false>), dim3(tiles), dim3(256), 0, stream, p, R, step);
-        else hipLaunchKernelGGL((tsvd_pair_square_kernel<1, false, false>), dim3(tiles), dim3(256), 0, stream, p, R, step);
+        const int at = (step + 1) & 1;
+        if (big) PAIR_SQUARE(2, false, false, tiles, 256, p.X[1 - at], at, step);
+        else PAIR_SQUARE(1, false, false, tiles, 256, p.X[1 - at], at, step);
     }
+#undef PAIR_SQUARE
 }
 
 void tsvd_pair_vectors(const tsvd_pair_plan& p, const double* R, int count, bool any_rank, hipStream_t stream) {
