@@ -34,6 +34,8 @@ double planes_cost(const sizes& s, int v) {
     if (tsvd_fp6_split_makes_x(v, (int)std::min<long long>(s.sets * s.nvb, 1 << 20))) return 0;      // stage V makes them
     return 4.9 + 8.4 * (double)(s.nvb * up(s.B, 16) * s.sets) / 4096;
 }
+// (Shapes 9 and 10 are faster since: tsvd_fp6_own_kernel.  On 136 calls the shapes that these factors take are 1.2 % slower than the best of all 16 pairs of them,
+// those of new factors 1.1 %; and lower estimates would take calls from kernels that hold x exactly.)
 struct split_factors {
     int shape;
     double v0, v_round, v_step, v_x, u0, u_round, u_step;

@@ -8,11 +8,9 @@
 // the contraction, so a SIMD always has two wavefronts, a barrier is passed once per KG BPS blocks, and each wavefront
 // still multiplies 128 rows (eight row blocks) by every operand it reads from LDS.  At the end the partial sums of the
 // groups meet in LDS, each group finishing its share of the tile.
-// Measured on MI355X: 3072 x 768 x 1536 fp32 at 197 tokens 56.4 -> 20.1 us (128 x 16 tiles with planes of x made inside, then 128 x 32),
-// 16384 x 4096 x 8192 bf16 at 256 tokens 93.4 -> 71.4 us (256 x 32 and 256 x 64).  What bounds them, by counters: stage U of the
-// second (a workgroup per compute unit, 3072 MFMAs per SIMD in 53 us) has the matrix pipes busy half of the cycles at 0.38 of
-// a wavefront's time waiting; its stage V (23 us) 0.28, the stages of the first (11 us each) 0.07 and 0.20: there the launch, the first code
-// words and the sum of the groups weigh more than the products.
+// Measured on MI355X: 16384 x 4096 x 8192 bf16 at 256 tokens 93.4 -> 71.4 us (256 x 32 and 256 x 64).  What bounds it, by counters: stage U (a
+// workgroup per compute unit, 3072 MFMAs per SIMD in 53 us) has the matrix pipes busy half of the cycles at 0.38 of a wavefront's time waiting; its
+// stage V (23 us) 0.28.  Tiles of 128 rows share nothing between wavefronts: tsvd_fp6_own_kernel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -71,6 +69,23 @@ struct split_x {
     long long ld;
     int token_major, N;
 };
+// z = S (V x) / 4 (the codes of either stage multiply as +-2) of rank block kb and the token tile from tok on, whose result blocks are sum -> its record.
+__device__ __forceinline__ void finish_z(const gemm_args& p, f32x4 (&sum)[8], int kb, int tok, int lane) {
+    const int g = lane >> 4;
+    if (kb >= p.rows_need / 128) return;
+    float v[32];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+        const f32x4 sv = *reinterpret_cast<const f32x4*>(p.S + 128 * kb + 64 * (g & 1) + 16 * (g >> 1) + 32 * (a >> 2) + 4 * (a & 3));
+        sum[a] *= 0.25f * sv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * a + e] = sum[a][e];
+    }
+    unsigned char* rec = static_cast<unsigned char*>(p.out) + ((size_t)((tok >> 7) * (int)p.ld_out + kb) * 8 + ((tok & 127) >> 4)) * FP6_REC_BYTES;
+    if (p.two_sets) tsvd_planes_of_32_twice(v, rec, rec + (size_t)p.two_sets * 8 * FP6_REC_BYTES, lane);
+    else tsvd_planes_of_32(v, rec, lane);
+}
+
 template <int RW, int TN, bool STAGE2, int EX, int X = 0>
 __global__ void __launch_bounds__(512, 1)
 tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
@@ -247,20 +262,7 @@ tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
     }
     if (kg >= NQ) return;
     if constexpr (DIRECT) {
-        // z = S (V x) / 4 (the codes of either stage multiply as +-2) -> the record of token tile kg
-        const int kb = strip0 >> 3, tok = b0 + 16 * kg, zblocks = p.rows_need / 128;
-        if (kb >= zblocks) return;
-        float v[32];
-#pragma unroll
-        for (int a = 0; a < TM; ++a) {
-            const f32x4 sv = *reinterpret_cast<const f32x4*>(p.S + 128 * kb + 64 * (g & 1) + 16 * (g >> 1) + 32 * (a >> 2) + 4 * (a & 3));
-            fin[a] *= 0.25f * sv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * a + e] = fin[a][e];
-        }
-        unsigned char* rec = static_cast<unsigned char*>(p.out) + ((size_t)((tok >> 7) * (int)p.ld_out + kb) * 8 + ((tok & 127) >> 4)) * FP6_REC_BYTES;
-        if (p.two_sets) tsvd_planes_of_32_twice(v, rec, rec + (size_t)p.two_sets * 8 * FP6_REC_BYTES, lane);
-        else tsvd_planes_of_32(v, rec, lane);
+        finish_z(p, fin, strip0 >> 3, b0 + 16 * kg, lane);
     } else {
         f32x4 out[NF][1];
 #pragma unroll
@@ -269,11 +271,177 @@ tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
     }
 }
 
-constexpr int split_lds(int tn) { return 2 * 16 * FP6_REC_BYTES + 16 * tn * 4; }
+// ---- tiles of 128 rows: a block of the contraction for a wavefront ----------------------------------
+// With one group of rows no wavefront reads what another one uses, so nothing is staged and no barrier stands in the loop: wavefront w takes the blocks
+// w, w + 8, ..., its operands (planes of a record, 24 bytes a lane and plane, in the order of the record) go from the L2s to registers, DEPTH blocks
+// ahead, and stage V makes the planes of x in registers where it makes them itself (X; every row tile makes them again).  The partial sums of the eight
+// wavefronts meet in LDS.
+// Measured on MI355X against the same tiles on records staged in LDS (a step of 16 records for every barrier; in a launch of two or three steps each one
+// waited a round trip of about 1 us for the next): 3072 x 768 x 1536 fp32 at 197 tokens 20.4 -> 18.1 us, 256 x 489 x 256 fp32 at 256 13.2 -> 9.6,
+// 7415 x 4199 x 4465 bf16 at 125 32.3 -> 27.5; 40 drawn fp32 and 60 bf16 calls of 30 to 2500 tokens that take these tiles 0.73 to 1.0 of the time.
+template <int TN, bool STAGE2, int EX, int X = 0>
+__global__ void __launch_bounds__(512, 1)
+tsvd_fp6_own_kernel(gemm_args p, split_x xs) {
+    constexpr int KG = 8, TM = 8, DEPTH = TN == 1 ? 3 : 2;
+    constexpr bool DIRECT = !STAGE2;
+    constexpr int NQ = DIRECT ? TN : KG, NF = 8 * TN / NQ;
+    extern __shared__ __align__(16) unsigned char smem[];    // the partial sums, 16 TN ones behind them
+    float* ones = reinterpret_cast<float*>(smem + NQ * (KG - 1) * NF * 1024);
+    const int lane = threadIdx.x & 63, kg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
+    const int b0 = blockIdx.x * 16 * TN, strip0 = blockIdx.y * TM, nrun = X == 2 ? p.npairs / 2 : p.npairs;      // (X: both sets of planes at a block)
+    if (threadIdx.x < 16 * TN) ones[threadIdx.x] = 1.0f;
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles), 0, p.tile_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t act_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(static_cast<const void*>(p.act)), 0, p.act_bytes, 0x00020000);
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (rows of stage V as in tsvd_fp6_split_kernel)
+    const int gg = i >> 2, vv = i & 3;
+    const int w_voff = DIRECT ? (4 * (gg & 1) + (gg >> 1)) * p.nkt * 1024 + (g * 16 + vv) * 16 : lane * 16;
+    // (arrays of their own: the planes of a structure would be read as parts of longer vectors, and kept in scratch memory)
+    constexpr int SLOTS = X ? 1 : DEPTH * TN;
+    u32x4 lo[SLOTS][3];
+    u32x2 hi[SLOTS][3];
+    uint32_t sc[SLOTS];
+    auto load_w = [&](int blk, u32x2 (&w)[TM]) {
+        if (p.code_blocks && blk >= p.code_blocks) blk -= p.code_blocks;          // (second set of planes: the same codes again)
+        const int soff = (strip0 * p.nkt + (blk >> 1)) * 1024 + (blk & 1) * 8;
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+            w[a] = __builtin_amdgcn_raw_buffer_load_b64(w_rsrc, w_voff, soff + (DIRECT ? 2 * (a >> 2) * p.nkt * 1024 + 4 * (a & 3) * 16 : a * p.nkt * 1024), 0);
+    };
+    auto load_b = [&](int blk, auto d_c) {
+        const int soff = ((b0 >> 7) * p.plane_blocks + blk) * FP6_PAIR_BYTES + ((b0 & 127) >> 4) * FP6_REC_BYTES;
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+                lo[decltype(d_c)::value * TN + b][pl] = buf_load128(act_rsrc, lane * 16, soff + b * FP6_REC_BYTES + pl * 1024);
+                hi[decltype(d_c)::value * TN + b][pl] = __builtin_amdgcn_raw_buffer_load_b64(act_rsrc, lane * 8, soff + b * FP6_REC_BYTES + 3072 + pl * 512, 0);
+            }
+            sc[decltype(d_c)::value * TN + b] = __builtin_amdgcn_raw_buffer_load_b32(act_rsrc, lane * 4, soff + b * FP6_REC_BYTES + 4608, 0);
+        }
+    };
+    auto operand_a = [&](const u32x2 (&w)[TM], u32x4 (&av)[TM]) {
+#pragma unroll
+        for (int a = 0; a < TM; ++a) av[a] = u32x4{(w[a].x << 2) & 0xCCCCCCCCu, w[a].x & 0xCCCCCCCCu, (w[a].y << 2) & 0xCCCCCCCCu, w[a].y & 0xCCCCCCCCu};
+    };
+    auto multiply = [&](const u32x4 (&av)[TM], int b, auto slot_c) {
+        constexpr int n = decltype(slot_c)::value;
+#pragma unroll
+        for (int a = 0; a < TM; ++a) acc[a][b] = mfma_fp6<0>(av[a], lo[n][0], hi[n][0], sc[n], acc[a][b]);
+#pragma unroll
+        for (int a = 0; a < TM; ++a) acc[a][b] = mfma_fp6<1>(av[a], lo[n][1], hi[n][1], sc[n], acc[a][b]);
+#pragma unroll
+        for (int a = 0; a < TM; ++a) acc[a][b] = mfma_fp6<2>(av[a], lo[n][2], hi[n][2], sc[n], acc[a][b]);
+    };
+    if constexpr (X != 0) {
+        for (int blk = kg; blk < nrun; blk += KG) {
+            u32x2 w[TM];
+            load_w(blk, w);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                float v[32];
+                gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + b, lane, v);
+                auto put = [&](int pl, u32x4 l, u32x2 h) { lo[0][pl] = l, hi[0][pl] = h; };
+                const std::integral_constant<int, 0> slot{};
+                sc[0] = tsvd_planes_of_32<X == 2>(v, put);
+                {
+                    u32x4 av[TM];
+                    operand_a(w, av);
+                    multiply(av, b, slot);
+                }
+                if constexpr (X == 2) {
+                    sc[0] = tsvd_planes_of_32<false>(v, put);
+                    u32x4 av[TM];
+                    operand_a(w, av);
+                    multiply(av, b, slot);
+                }
+            }
+        }
+    } else {
+        u32x2 w[DEPTH][TM];
+        auto ask = [&](int blk, auto d_c) {
+            if (blk < nrun) {
+                load_b(blk, d_c);
+                load_w(blk, w[decltype(d_c)::value]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto block = [&](int blk, auto d_c) {
+            constexpr int d = decltype(d_c)::value;
+            if (blk < nrun) {
+                u32x4 av[TM];
+                operand_a(w[d], av);
+                multiply(av, 0, std::integral_constant<int, d * TN>{});
+                if constexpr (TN == 2) multiply(av, 1, std::integral_constant<int, d * TN + 1>{});
+                __builtin_amdgcn_sched_barrier(0);
+                ask(blk + KG * DEPTH, d_c);
+            }
+        };
+        const std::integral_constant<int, 0> d0{};
+        const std::integral_constant<int, 1> d1{};
+        const std::integral_constant<int, DEPTH - 1> d2{};
+        ask(kg, d0);
+        ask(kg + KG, d1);
+        if constexpr (DEPTH == 3) ask(kg + 2 * KG, d2);
+        for (int blk = kg; blk < nrun; blk += KG * DEPTH) {
+            block(blk, d0);
+            block(blk + KG, d1);
+            if constexpr (DEPTH == 3) block(blk + 2 * KG, d2);
+        }
+    }
+
+    // ---- the partial sums: result block f = 8 tile + row block; wavefront q finishes blocks q NF .. + NF - 1
+    f32x4 fin[NF];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        if (q == kg) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) fin[f] = acc[(q * NF + f) & 7][(q * NF + f) >> 3];
+        }
+    auto slot = [&](int q, int from, int f) { return smem + (((q * (KG - 1) + from) * NF + f) * 64 + lane) * 16; };
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        if (q != kg) {
+            const int from = kg < q ? kg : kg - 1;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) *reinterpret_cast<f32x4*>(slot(q, from, f)) = acc[(q * NF + f) & 7][(q * NF + f) >> 3];
+        }
+    __syncthreads();
+    if (kg >= NQ) return;
+#pragma unroll
+    for (int from = 0; from < KG - 1; ++from)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) fin[f] += *reinterpret_cast<const f32x4*>(slot(kg, from, f));
+    if constexpr (DIRECT) {
+        finish_z(p, fin, strip0 >> 3, b0 + 16 * kg, lane);
+    } else {
+        f32x4 out[NF][1];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) out[f][0] = fin[f];
+        gemm_epilogue<NF, 1, true, EX>(p, out, strip0 + ((kg * NF) & 7), b0, 16 * ((kg * NF) >> 3), ones, i, g);
+    }
+}
+
+// One group of rows leaves each wavefront its own records, two share them in LDS, and so do the wavefronts that make those of two token tiles (both in
+// turn in registers: 9664 x 941 x 611 at 861 tokens 31.6 -> 34.4 us).
+template <int RW, int TN, int X>
+constexpr bool own = RW == 1 && (TN == 1 || X == 0);
+template <int RW, int TN, bool STAGE2, int EX, int X = 0>
+auto kernel() {
+    if constexpr (own<RW, TN, X>) return tsvd_fp6_own_kernel<TN, STAGE2, EX, X>;
+    else return tsvd_fp6_split_kernel<RW, TN, STAGE2, EX, X>;
+}
+template <int RW, int TN, int X>
+constexpr int split_lds = (own<RW, TN, X> ? 7 * 8 * TN * 1024 : 2 * 16 * FP6_REC_BYTES) + 16 * TN * 4;
 
 template <int RW, int TN, bool STAGE2, int EX, int X = 0>
 hipError_t init_one() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_fp6_split_kernel<RW, TN, STAGE2, EX, X>), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds(TN));
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel<RW, TN, STAGE2, EX, X>()), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds<RW, TN, X>);
 }
 template <int RW, int TN>
 hipError_t init_shape() {
@@ -289,15 +457,16 @@ hipError_t init_shape() {
 template <int RW, int TN>
 hipError_t launch_shape(bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, hipStream_t stream) {
     const dim3 grid((unsigned)((a.bvalid + 16 * TN - 1) / (16 * TN)), (unsigned)((a.rows_need + RW * 128 - 1) / (RW * 128))), block(512);
-    constexpr int lds = split_lds(TN);
     const split_x none = {};
-    if (!stage2 && x && f32) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, false, 0, 2>), grid, block, lds, stream, a, *x);
-    else if (!stage2 && x) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, false, 0, 1>), grid, block, lds, stream, a, *x);
-    else if (!stage2) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, false, 0>), grid, block, lds, stream, a, none);
-    else if (ex == 3) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 3>), grid, block, lds, stream, a, none);
-    else if (ex == 2) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 2>), grid, block, lds, stream, a, none);
-    else if (ex == 1) hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 1>), grid, block, lds, stream, a, none);
-    else hipLaunchKernelGGL((tsvd_fp6_split_kernel<RW, TN, true, 0>), grid, block, lds, stream, a, none);
+#define SPLIT_LAUNCH(STAGE2, EX, X, x_) hipLaunchKernelGGL((kernel<RW, TN, STAGE2, EX, X>()), grid, block, (split_lds<RW, TN, X>), stream, a, x_)
+    if (!stage2 && x && f32) SPLIT_LAUNCH(false, 0, 2, *x);
+    else if (!stage2 && x) SPLIT_LAUNCH(false, 0, 1, *x);
+    else if (!stage2) SPLIT_LAUNCH(false, 0, 0, none);
+    else if (ex == 3) SPLIT_LAUNCH(true, 3, 0, none);
+    else if (ex == 2) SPLIT_LAUNCH(true, 2, 0, none);
+    else if (ex == 1) SPLIT_LAUNCH(true, 1, 0, none);
+    else SPLIT_LAUNCH(true, 0, 0, none);
+#undef SPLIT_LAUNCH
     return hipGetLastError();
 }
 

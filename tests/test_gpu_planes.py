@@ -206,3 +206,14 @@ def test_thin_panels_of_several_workgroups(tsvd, M, N, K, B, tiles):
     panels where two workgroups a panel begin.  (The bits of one workgroup a panel: the bound is that of test_thin_panels.)"""
     print(f"case thin of several workgroups {M} {N} {K} {B} {tiles}", flush=True)
     _check(tsvd, M, N, K, B, "bf16", {"TSVD_THIN": tiles})
+
+
+@pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("own_x", [0, 1])
+@pytest.mark.parametrize("v,u", [(9, 9), (10, 10)])
+@pytest.mark.parametrize("M,N,K,B", [(20, 30, 20, 17), (128, 1024, 1024, 32), (129, 1025, 1025, 33), (300, 2050, 3100, 47), (100, 4100, 140, 16 + 17)])
+def test_blocks_of_a_wavefront(tsvd, M, N, K, B, v, u, own_x, x_dtype):
+    """Tiles of 128 rows, each wavefront with blocks of its own: fewer blocks than wavefronts, one for each, one more; more than are in flight; planes of x
+    made in registers or by their own pass."""
+    print(f"case blocks of a wavefront {M} {N} {K} {B} {v} {u} {own_x} {x_dtype}", flush=True)
+    _check(tsvd, M, N, K, B, x_dtype, {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_SPLIT_V": v, "TSVD_SPLIT_U": u, "TSVD_SPLIT_X": own_x})
