@@ -69,6 +69,26 @@ struct split_x {
     long long ld;
     int token_major, N;
 };
+// Which tiles an XCD works on (workgroups go to the eight of them in turn: a grid of 8 x tiles x rows): 1 << row_log2 groups of gridDim.z row tiles, times
+// 8 >> row_log2 groups of gridDim.y token tiles, one pair of groups for each, so that its L2 fetches a part of the codes and a part of the
+// planes.  (Launches without such groups, a grid of token tiles x row tiles, are kernels of their own: the choice by an argument cost each of them 0.15 us.)
+struct split_place {
+    int row_log2, row_tiles, token_tiles;
+};
+struct split_tile {
+    int token, row;
+    bool exists;
+};
+template <bool PLACED, typename Extra>
+__device__ __forceinline__ split_tile tile_of(const Extra& p) {
+    if constexpr (PLACED) {
+        const int row = (blockIdx.x & ((1 << p.row_log2) - 1)) * gridDim.z + blockIdx.z, token = (blockIdx.x >> p.row_log2) * gridDim.y + blockIdx.y;
+        return {token, row, row < p.row_tiles && token < p.token_tiles};
+    } else {
+        return {(int)blockIdx.x, (int)blockIdx.y, true};
+    }
+}
+
 // z = S (V x) / 4 (the codes of either stage multiply as +-2) of rank block kb and the token tile from tok on, whose result blocks are sum -> its record.
 __device__ __forceinline__ void finish_z(const gemm_args& p, f32x4 (&sum)[8], int kb, int tok, int lane) {
     const int g = lane >> 4;
@@ -86,9 +106,12 @@ __device__ __forceinline__ void finish_z(const gemm_args& p, f32x4 (&sum)[8], in
     else tsvd_planes_of_32(v, rec, lane);
 }
 
-template <int RW, int TN, bool STAGE2, int EX, int X = 0>
+template <int RW, int TN, bool STAGE2, int EX, int X, bool PLACED>
 __global__ void __launch_bounds__(512, 1)
-tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
+tsvd_fp6_split_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x> extra) {
+    split_x xs = {};
+    if constexpr (!PLACED) xs = extra;
+    const split_tile tile = tile_of<PLACED>(extra);
     constexpr int KG = 8 / RW, BPS = 16 / (KG * TN), TM = 8, RECS = KG * BPS * TN;
     static_assert(RECS == 16 && BPS >= 1, "16 records per step");
     constexpr bool DIRECT = !STAGE2;                        // stage V writes the planes of z
@@ -101,7 +124,7 @@ tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
     float* ones = reinterpret_cast<float*>(smem + 2 * STEP_BYTES);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rw = wave % RW, kg = wave / RW, i = lane & 15, g = lane >> 4;
-    const int b0 = blockIdx.x * 16 * TN, strip0 = (blockIdx.y * RW + rw) * TM;
+    const int b0 = tile.token * 16 * TN, strip0 = (tile.row * RW + rw) * TM;
     const int nrun = p.npairs, nsteps = (nrun + KG * BPS - 1) / (KG * BPS), nblocks = p.plane_blocks;
     if (threadIdx.x < 16 * TN) ones[threadIdx.x] = 1.0f;
 
@@ -197,6 +220,7 @@ tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
 
     u32x2 wa[BPS][TM], wb[BPS][TM];
     load_w(0, wa);
+    if (PLACED && !tile.exists) return;
     issue(0, 0);
     if constexpr (X != 0) {
         const int blocks = X == 2 ? nrun / 2 : nrun;         // (fp32: the second set of planes are further blocks)
@@ -279,16 +303,19 @@ tsvd_fp6_split_kernel(gemm_args p, split_x xs) {
 // Measured on MI355X against the same tiles on records staged in LDS (a step of 16 records for every barrier; in a launch of two or three steps each one
 // waited a round trip of about 1 us for the next): 3072 x 768 x 1536 fp32 at 197 tokens 20.4 -> 18.1 us, 256 x 489 x 256 fp32 at 256 13.2 -> 9.6,
 // 7415 x 4199 x 4465 bf16 at 125 32.3 -> 27.5; 40 drawn fp32 and 60 bf16 calls of 30 to 2500 tokens that take these tiles 0.73 to 1.0 of the time.
-template <int TN, bool STAGE2, int EX, int X = 0>
+template <int TN, bool STAGE2, int EX, int X, bool PLACED>
 __global__ void __launch_bounds__(512, 1)
-tsvd_fp6_own_kernel(gemm_args p, split_x xs) {
+tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x> extra) {
+    split_x xs = {};
+    if constexpr (!PLACED) xs = extra;
+    const split_tile tile = tile_of<PLACED>(extra);
     constexpr int KG = 8, TM = 8, DEPTH = TN == 1 ? 3 : 2;
     constexpr bool DIRECT = !STAGE2;
     constexpr int NQ = DIRECT ? TN : KG, NF = 8 * TN / NQ;
     extern __shared__ __align__(16) unsigned char smem[];    // the partial sums, 16 TN ones behind them
     float* ones = reinterpret_cast<float*>(smem + NQ * (KG - 1) * NF * 1024);
     const int lane = threadIdx.x & 63, kg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
-    const int b0 = blockIdx.x * 16 * TN, strip0 = blockIdx.y * TM, nrun = X == 2 ? p.npairs / 2 : p.npairs;      // (X: both sets of planes at a block)
+    const int b0 = tile.token * 16 * TN, strip0 = tile.row * TM, nrun = X == 2 ? p.npairs / 2 : p.npairs;      // (X: both sets of planes at a block)
     if (threadIdx.x < 16 * TN) ones[threadIdx.x] = 1.0f;
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles), 0, p.tile_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t act_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(static_cast<const void*>(p.act)), 0, p.act_bytes, 0x00020000);
@@ -388,6 +415,7 @@ tsvd_fp6_own_kernel(gemm_args p, split_x xs) {
         ask(kg, d0);
         ask(kg + KG, d1);
         if constexpr (DEPTH == 3) ask(kg + 2 * KG, d2);
+        if (PLACED && !tile.exists) return;
         for (int blk = kg; blk < nrun; blk += KG * DEPTH) {
             block(blk, d0);
             block(blk + KG, d1);
@@ -431,17 +459,19 @@ tsvd_fp6_own_kernel(gemm_args p, split_x xs) {
 // turn in registers: 9664 x 941 x 611 at 861 tokens 31.6 -> 34.4 us).
 template <int RW, int TN, int X>
 constexpr bool own = RW == 1 && (TN == 1 || X == 0);
-template <int RW, int TN, bool STAGE2, int EX, int X = 0>
+template <int RW, int TN, bool STAGE2, int EX, int X = 0, bool PLACED = false>
 auto kernel() {
-    if constexpr (own<RW, TN, X>) return tsvd_fp6_own_kernel<TN, STAGE2, EX, X>;
-    else return tsvd_fp6_split_kernel<RW, TN, STAGE2, EX, X>;
+    if constexpr (own<RW, TN, X>) return tsvd_fp6_own_kernel<TN, STAGE2, EX, X, PLACED>;
+    else return tsvd_fp6_split_kernel<RW, TN, STAGE2, EX, X, PLACED>;
 }
 template <int RW, int TN, int X>
 constexpr int split_lds = (own<RW, TN, X> ? 7 * 8 * TN * 1024 : 2 * 16 * FP6_REC_BYTES) + 16 * TN * 4;
 
 template <int RW, int TN, bool STAGE2, int EX, int X = 0>
 hipError_t init_one() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel<RW, TN, STAGE2, EX, X>()), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds<RW, TN, X>);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel<RW, TN, STAGE2, EX, X>()), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds<RW, TN, X>);
+    if (e != hipSuccess || X != 0) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel<RW, TN, STAGE2, EX, 0, true>()), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds<RW, TN, 0>);
 }
 template <int RW, int TN>
 hipError_t init_shape() {
@@ -454,18 +484,52 @@ hipError_t init_shape() {
     if ((e = init_one<RW, TN, true, 2>()) != hipSuccess) return e;
     return init_one<RW, TN, true, 3>();
 }
+// The groups that leave an XCD the fewest bytes, for launches of one round of workgroups.  Tiles in turn where they are about as good: an XCD then sees one in
+// gcd(token tiles, 8) of the token tiles, and (token tiles) / 8 of the row tiles.  16384 x 4096 x 8192 at 256 tokens (an XCD's codes of stage U 16.8 -> 4.2 MB, planes
+// 1.3 -> 5; of stage V 8.4 -> 2.1 MB, planes 0.3 -> 1.2) 73.5 -> 68.7 us, 3072 x 768 x 1536 fp32 at 197 18.1 -> 17.1, 275 x 1257 x 597 fp32 at 418 19.7 -> 17.3;
+// on 66 drawn calls 0.88 to 1.0 of the time (one 1.03).  Launches of several rounds: 0.97 to 1.04, 1.01 on the average.  A saving below half a megabyte: nothing.
+bool place_of(long long row_tiles, long long token_tiles, double code_bytes, double act_bytes, split_place* p, dim3* grid) {
+    *grid = dim3((unsigned)token_tiles, (unsigned)row_tiles);
+    if (row_tiles * token_tiles > 256) return false;
+    int d = 8;
+    while (token_tiles % d) d /= 2;
+    const double plain = code_bytes * std::min(1.0, (double)token_tiles / 8) + act_bytes / d;
+    double best = std::min(0.9 * plain, plain - 512e3);
+    bool found = false;
+    for (int log2 = 0; log2 <= 3; ++log2) {
+        const long long rows = (row_tiles + (1 << log2) - 1) >> log2, groups = 8 >> log2, tiles = (token_tiles + groups - 1) / groups;
+        const double bytes = code_bytes / (1 << log2) + act_bytes / (double)groups;
+        if (rows * tiles > 32 || bytes >= best) continue;
+        best = bytes;
+        found = true;
+        *p = {log2, (int)row_tiles, (int)token_tiles};
+        *grid = dim3(8, (unsigned)tiles, (unsigned)rows);
+    }
+    return found;
+}
 template <int RW, int TN>
 hipError_t launch_shape(bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, hipStream_t stream) {
-    const dim3 grid((unsigned)((a.bvalid + 16 * TN - 1) / (16 * TN)), (unsigned)((a.rows_need + RW * 128 - 1) / (RW * 128))), block(512);
-    const split_x none = {};
-#define SPLIT_LAUNCH(STAGE2, EX, X, x_) hipLaunchKernelGGL((kernel<RW, TN, STAGE2, EX, X>()), grid, block, (split_lds<RW, TN, X>), stream, a, x_)
-    if (!stage2 && x && f32) SPLIT_LAUNCH(false, 0, 2, *x);
-    else if (!stage2 && x) SPLIT_LAUNCH(false, 0, 1, *x);
-    else if (!stage2) SPLIT_LAUNCH(false, 0, 0, none);
-    else if (ex == 3) SPLIT_LAUNCH(true, 3, 0, none);
-    else if (ex == 2) SPLIT_LAUNCH(true, 2, 0, none);
-    else if (ex == 1) SPLIT_LAUNCH(true, 1, 0, none);
-    else SPLIT_LAUNCH(true, 0, 0, none);
+    const unsigned token_tiles = (unsigned)((a.bvalid + 16 * TN - 1) / (16 * TN)), row_tiles = (unsigned)((a.rows_need + RW * 128 - 1) / (RW * 128));
+    dim3 grid(token_tiles, row_tiles);
+    const dim3 block(512);
+#define SPLIT_LAUNCH(STAGE2, EX, X, PLACED, extra) hipLaunchKernelGGL((kernel<RW, TN, STAGE2, EX, X, PLACED>()), grid, block, (split_lds<RW, TN, X>), stream, a, extra)
+#define SPLIT_STAGE(PLACED, extra)                                  \
+    do {                                                            \
+        if (!stage2) SPLIT_LAUNCH(false, 0, 0, PLACED, extra);      \
+        else if (ex == 3) SPLIT_LAUNCH(true, 3, 0, PLACED, extra);  \
+        else if (ex == 2) SPLIT_LAUNCH(true, 2, 0, PLACED, extra);  \
+        else if (ex == 1) SPLIT_LAUNCH(true, 1, 0, PLACED, extra);  \
+        else SPLIT_LAUNCH(true, 0, 0, PLACED, extra);               \
+    } while (0)
+    split_place place;
+    // (bytes of what the launch reads: 2 bits a code, a record of 4864 bytes for 16 tokens and 128 indices)
+    if (!stage2 && x && f32) SPLIT_LAUNCH(false, 0, 2, false, *x);
+    else if (!stage2 && x) SPLIT_LAUNCH(false, 0, 1, false, *x);
+    else if (place_of(row_tiles, token_tiles, (double)a.rows_need * 32.0 * (a.code_blocks ? a.code_blocks : a.npairs),
+                      (double)a.npairs * ((a.bvalid + 15) / 16) * FP6_REC_BYTES, &place, &grid))
+        SPLIT_STAGE(true, place);
+    else SPLIT_STAGE(false, split_x{});
+#undef SPLIT_STAGE
 #undef SPLIT_LAUNCH
     return hipGetLastError();
 }
