@@ -93,7 +93,7 @@ def _stage_u_kernel_name(tsvd, handle, B):
     if su == 34:
         return "tsvd_thin_panel_kernel", su
     if su >= 100:
-        return "tsvd_fp6_split_kernel", su
+        return ("tsvd_fp6_pair_kernel" if su - 100 >= 16 else "tsvd_fp6_own_kernel"), su      # tiles of 256 rows, of 128
     if su == 40:
         return "tsvd_gemm_fp6_kernel", su
     return ("tsvd_gemm_ring_kernel" if su >= 14 else "tsvd_gemm_pipe_kernel"), su
@@ -212,7 +212,7 @@ def bench_workload(name, steps, warmup, with_cpu=True, cpu_budget_s=4.0):
                            "frac_of_bf16_peak": ach / PEAK_MFMA_TFLOPS,
                            "traffic": traffic,
                            "whole_path_frac_of_bf16_peak": ach / PEAK_MFMA_TFLOPS}
-    elif batched and kernel_name in ("tsvd_gemm_fp6_kernel", "tsvd_fp6_split_kernel"):
+    elif batched and kernel_name in ("tsvd_gemm_fp6_kernel", "tsvd_fp6_pair_kernel", "tsvd_fp6_own_kernel"):
         # stage U = fp4 x fp6 kernel (+ the planes pass where stage V leaves fp16 z).  Achieved = ALGORITHMIC flops (2 M K B) per second; the
         # kernel executes three times as many (three planes) on the fp4 / fp6 MFMA path, whose dense
         # peak is 10.1 PFLOP/s; the fraction of the 2.5 PFLOP/s fp16 peak is given beside it because that

@@ -4,13 +4,11 @@
 // The kernels of tsvd_fp6.hip give every wavefront its own rows of a tile and let all of them walk the contraction
 // together.  With fewer than two such tiles per compute unit a SIMD holds a single wavefront, which issues a matrix
 // instruction every 24.5 cycles (16 is the pipe), and a contraction of a dozen blocks is a dozen barriers.  Here eight
-// wavefronts share a tile of RW x 128 rows and 16 TN tokens: KG = 8 / RW groups of them take every KG-th run of BPS blocks of
-// the contraction, so a SIMD always has two wavefronts, a barrier is passed once per KG BPS blocks, and each wavefront
-// still multiplies 128 rows (eight row blocks) by every operand it reads from LDS.  At the end the partial sums of the
-// groups meet in LDS, each group finishing its share of the tile.
-// Measured on MI355X: 16384 x 4096 x 8192 bf16 at 256 tokens 93.4 -> 71.4 us (256 x 32 and 256 x 64).  What bounds it, by counters: stage U (a
-// workgroup per compute unit, 3072 MFMAs per SIMD in 53 us) has the matrix pipes busy half of the cycles at 0.38 of a wavefront's time waiting; its
-// stage V (23 us) 0.28.  Tiles of 128 rows share nothing between wavefronts: tsvd_fp6_own_kernel.
+// wavefronts share a tile of RW x 128 rows and 16 TN tokens: KG = 8 / RW groups of them take blocks of the contraction of their own, so a SIMD always has
+// two wavefronts, and each wavefront still multiplies 128 rows (eight row blocks) by every operand that it reads.  At the end the partial sums of
+// the groups meet in LDS, each group finishing its share of the tile.  Nobody waits for wavefronts that it shares nothing with: tiles of 256 rows
+// (tsvd_fp6_pair_kernel) tie two of them to each other, those of 128 rows (tsvd_fp6_own_kernel) none; where stage V makes the records of x itself, all
+// wavefronts do that first and meet once (tsvd_fp6_panel_kernel).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -59,9 +57,6 @@ tsvd_planes_kernel(const void* __restrict__ x, long long ld, int token_major, in
 }
 
 // ---- a stage ------------------------------------------------------------------------------------
-// Step s of wavefront (rw, kg): blocks (s KG + kg) BPS .. + BPS - 1.  KG BPS TN = 16 records of a step (76 KiB) in LDS, two steps in
-// turn, copied by all wavefronts (buffer_load ... lds) while the other step is multiplied; code words from L2 to registers
-// one step ahead.
 // X (stage V): the workgroup makes the records of x itself, all of them at the start, where two steps hold them: every row tile
 // makes them again, and a launch with its ramp and the gap before it (4 us) is saved for about 1.5 us.  1: bf16, 2: fp32.
 struct split_x {
@@ -106,32 +101,174 @@ __device__ __forceinline__ void finish_z(const gemm_args& p, f32x4 (&sum)[8], in
     else tsvd_planes_of_32(v, rec, lane);
 }
 
-template <int RW, int TN, bool STAGE2, int EX, int X, bool PLACED>
+// ---- stage V that makes the records of x itself, in tiles that several wavefronts read them in -------
+// Step s of wavefront (rw, kg): blocks (s KG + kg) BPS .. + BPS - 1, so 16 records (76 KiB) a step, and two steps hold all of x of a token tile: made at the
+// start, by all wavefronts, and multiplied behind a single barrier.
+// Measured on MI355X without the barrier and the turn of buffers that each step had: 2099 x 500 x 5441 fp32 at 657 tokens 56.7 -> 50.6 us, 5854 x 256 x 1383 fp32 at
+// 328 23.3 -> 21.6, 13446 x 128 x 8569 fp32 at 781 296 -> 272 (each with a stage U of pairs where that has 256 rows).
+template <int RW, int TN, int X>
 __global__ void __launch_bounds__(512, 1)
-tsvd_fp6_split_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x> extra) {
-    split_x xs = {};
-    if constexpr (!PLACED) xs = extra;
-    const split_tile tile = tile_of<PLACED>(extra);
+tsvd_fp6_panel_kernel(gemm_args p, split_x xs) {
     constexpr int KG = 8 / RW, BPS = 16 / (KG * TN), TM = 8, RECS = KG * BPS * TN;
     static_assert(RECS == 16 && BPS >= 1, "16 records per step");
-    constexpr bool DIRECT = !STAGE2;                        // stage V writes the planes of z
-    constexpr int STEP_BYTES = RECS * FP6_REC_BYTES;
-    constexpr int CHUNK = TN * FP6_REC_BYTES, PIECES = (CHUNK + 1023) / 1024, TOTAL = KG * BPS * PIECES;   // a chunk: a block's TN records
-    constexpr int NQ = DIRECT ? TN : KG, NF = 8 * TN / NQ;  // shares of the tile that a group finishes: NQ of NF result blocks
-    constexpr int NFR = TN == 4 ? 4 : NF;                   // ... of which NFR meet in LDS at a time
-    static_assert((size_t)NQ * (KG - 1) * RW * NFR * 1024 <= 2 * STEP_BYTES, "the partial sums fit the two buffers");
-    extern __shared__ __align__(16) unsigned char smem[];   // 2 x STEP_BYTES, then 16 TN ones (the epilogue's token factors)
-    float* ones = reinterpret_cast<float*>(smem + 2 * STEP_BYTES);
+    constexpr int CHUNK = TN * FP6_REC_BYTES, STEP_BYTES = RECS * FP6_REC_BYTES;   // a chunk: a block's TN records
+    constexpr int NFR = TN == 4 ? 4 : 8;                    // result blocks that meet in LDS at a time
+    static_assert((size_t)TN * (KG - 1) * RW * NFR * 1024 <= 2 * STEP_BYTES, "the partial sums fit the records");
+    extern __shared__ __align__(16) unsigned char smem[];   // 2 x STEP_BYTES
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rw = wave % RW, kg = wave / RW, i = lane & 15, g = lane >> 4;
+    const int b0 = blockIdx.x * 16 * TN, strip0 = (blockIdx.y * RW + rw) * TM;
+    const int nrun = p.npairs;
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles), 0, p.tile_bytes, 0x00020000);
+
+    // row 4 gg + vv of result block a comes from row 64 (gg & 1) + 16 (gg >> 1) + 32 (a >> 2) + 4 (a & 3) + vv of the
+    // wavefront's 128, so that result lane (g, token) holds the 32 rank positions of stage U's operand lane (see fp6_tile)
+    const int gg = i >> 2, vv = i & 3;
+    const int w_voff = (4 * (gg & 1) + (gg >> 1)) * p.nkt * 1024 + (g * 16 + vv) * 16;
+    u32x2 w[2][BPS][TM];
+#pragma unroll
+    for (int step = 0; step < 2; ++step)
+#pragma unroll
+        for (int j = 0; j < BPS; ++j) {
+            int blk = min((step * KG + kg) * BPS + j, nrun - 1);
+            if (p.code_blocks && blk >= p.code_blocks) blk -= p.code_blocks;      // (second set of planes: the same codes again)
+            const int soff = (strip0 * p.nkt + (blk >> 1)) * 1024 + (blk & 1) * 8;
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+                w[step][j][a] = __builtin_amdgcn_raw_buffer_load_b64(w_rsrc, w_voff, soff + 2 * (a >> 2) * p.nkt * 1024 + 4 * (a & 3) * 16, 0);
+        }
+    const int blocks = X == 2 ? nrun / 2 : nrun;             // (fp32: the second set of planes are further blocks)
+    auto record = [&](int blk, int tile) {
+        const int step = blk / (KG * BPS);
+        return smem + step * STEP_BYTES + (blk - step * KG * BPS) * CHUNK + tile * FP6_REC_BYTES;
+    };
+    for (int q = wave; q < blocks * TN; q += 8) {
+        const int blk = q / TN, tile = q - blk * TN;
+        float v[32];
+        gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + tile, lane, v);
+        if constexpr (X == 2) tsvd_planes_of_32_twice(v, record(blk, tile), record(blk + blocks, tile), lane);
+        else tsvd_planes_of_32(v, record(blk, tile), lane);
+    }
+    __syncthreads();
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the operands of an MFMA step (one plane of one record, eight row blocks) are read two steps ahead
+#pragma unroll
+    for (int step = 0; step < 2; ++step) {
+        const unsigned char* mine = smem + step * STEP_BYTES + kg * BPS * CHUNK;
+        const int valid = nrun - (step * KG + kg) * BPS;     // blocks of this step that exist
+        if (valid <= 0) break;
+        constexpr int STEPS = 3 * BPS * TN;
+        u32x4 lo[3];
+        u32x2 hi[3];
+        uint32_t sc[2];
+        auto read_step = [&](int st) {
+            const unsigned char* rec = mine + (st / 3) * FP6_REC_BYTES;
+            const int pl = st % 3;
+            lo[pl] = *reinterpret_cast<const u32x4*>(rec + pl * 1024 + lane * 16);
+            hi[pl] = *reinterpret_cast<const u32x2*>(rec + 3072 + pl * 512 + lane * 8);
+            if (pl == 0) sc[(st / 3) & 1] = *reinterpret_cast<const uint32_t*>(rec + 4608 + lane * 4);
+        };
+        read_step(0);
+        read_step(1);
+#pragma unroll
+        for (int j = 0; j < BPS; ++j) {
+            if (j >= valid) break;
+            u32x4 av[TM];
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                const u32x2 c = w[step][j][a];
+                av[a] = u32x4{(c.x << 2) & 0xCCCCCCCCu, c.x & 0xCCCCCCCCu, (c.y << 2) & 0xCCCCCCCCu, c.y & 0xCCCCCCCCu};
+            }
+#pragma unroll
+            for (int t = 0; t < 3 * TN; ++t) {
+                const int st = j * 3 * TN + t;
+                if (st + 2 < STEPS) read_step(st + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                const int b = t / 3;
+#pragma unroll
+                for (int a = 0; a < TM; ++a) {
+                    switch (t % 3) {
+                        case 0: acc[a][b] = mfma_fp6<0>(av[a], lo[0], hi[0], sc[(st / 3) & 1], acc[a][b]); break;
+                        case 1: acc[a][b] = mfma_fp6<1>(av[a], lo[1], hi[1], sc[(st / 3) & 1], acc[a][b]); break;
+                        default: acc[a][b] = mfma_fp6<2>(av[a], lo[2], hi[2], sc[(st / 3) & 1], acc[a][b]); break;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- the groups' partial sums: result block f = 8 tile + row block; group q finishes token tile q
+    f32x4 fin[8];
+#pragma unroll
+    for (int q = 0; q < TN; ++q)
+        if (q == kg) {
+#pragma unroll
+            for (int f = 0; f < 8; ++f) fin[f] = acc[f][q];
+        }
+#pragma unroll
+    for (int f0 = 0; f0 < 8; f0 += NFR) {
+        auto slot = [&](int q, int other, int f) { return smem + ((((q * (KG - 1) + other) * RW + rw) * NFR + f) * 64 + lane) * 16; };
+        if (f0 > 0) __syncthreads();
+#pragma unroll
+        for (int q = 0; q < TN; ++q)
+            if (q != kg) {
+                const int other = kg < q ? kg : kg - 1;
+#pragma unroll
+                for (int f = 0; f < NFR; ++f) *reinterpret_cast<f32x4*>(slot(q, other, f)) = acc[f0 + f][q];
+            }
+        __syncthreads();
+        if (kg < TN) {
+#pragma unroll
+            for (int other = 0; other < KG - 1; ++other)
+#pragma unroll
+                for (int f = 0; f < NFR; ++f) fin[f0 + f] += *reinterpret_cast<const f32x4*>(slot(kg, other, f));
+        }
+    }
+    if (kg < TN) finish_z(p, fin, strip0 >> 3, b0 + 16 * kg, lane);
+}
+
+// ---- tiles of 256 rows: a pair of wavefronts goes its own way -----------------------------------------
+// Two wavefronts (rw = 0, 1), on two SIMDs, share the records of their blocks; the other three pairs of the workgroup have blocks of their own.  So only the two
+// wait for each other, through words in LDS: a SIMD's older wavefront, which issues first, is then a step or two ahead of its younger
+// one instead of idle in front of a barrier.  A step is four records, two steps in LDS for each pair, copied by its two wavefronts
+// (buffer_load ... lds) while the other one is multiplied.
+// Measured on MI355X against one barrier for all eight wavefronts before each step of 16 records: 16384 x 4096 x 8192 bf16 at 256 tokens 68.3 -> 65.2 us,
+// 773 x 7298 x 1424 at 981 41.9 -> 37.2, 12534 x 640 x 8950 at 92 41.5 -> 35.5, 13876 x 640 x 6211 at 256 49.0 -> 46.5; on 45 drawn calls that take these tiles 0.85 to
+// 1.0 of the time.  What bounds it is the issue of a SIMD's two wavefronts: 24 to 27 cycles a matrix instruction where the pipe takes 16 to 18, the codes'
+// decoding and the operand reads between them.
+template <int TN, bool STAGE2, int EX, bool PLACED>
+__global__ void __launch_bounds__(512, 1)
+tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x> extra) {
+    constexpr int RW = 2, KG = 4, TM = 8, BPS = 4 / TN;
+    constexpr bool DIRECT = !STAGE2;
+    constexpr int CHUNK = TN * FP6_REC_BYTES, PIECES = (CHUNK + 1023) / 1024, STEP_BYTES = BPS * CHUNK;
+    constexpr int NQ = DIRECT ? TN : KG, NF = 8 * TN / NQ, NFR = TN == 4 ? 4 : NF;
+    static_assert((size_t)NQ * (KG - 1) * RW * NFR * 1024 <= 8 * STEP_BYTES, "the partial sums fit the buffers");
+    extern __shared__ __align__(16) unsigned char smem[];    // [pair][2] steps, then 16 TN ones, then a word for each wavefront
+    float* ones = reinterpret_cast<float*>(smem + 8 * STEP_BYTES);
+    int* ready = reinterpret_cast<int*>(ones + 16 * TN);
+    const split_tile tile = tile_of<PLACED>(extra);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rw = wave % RW, kg = wave / RW, i = lane & 15, g = lane >> 4;
     const int b0 = tile.token * 16 * TN, strip0 = (tile.row * RW + rw) * TM;
-    const int nrun = p.npairs, nsteps = (nrun + KG * BPS - 1) / (KG * BPS), nblocks = p.plane_blocks;
+    const int nrun = p.npairs, nsteps = (nrun + BPS - 1) / BPS, nblocks = p.plane_blocks;
+    // steps of this pair
+    const int from = nsteps * kg / KG, count = nsteps * (kg + 1) / KG - from;
     if (threadIdx.x < 16 * TN) ones[threadIdx.x] = 1.0f;
+    if (threadIdx.x < 8) ready[threadIdx.x] = 0;
 
     const i32x4 act_rsrc = raw_rsrc(p.act, p.act_bytes);
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles), 0, p.tile_bytes, 0x00020000);
     typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_byte_ptr)smem;
+    unsigned char* const mine = smem + kg * 2 * STEP_BYTES;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_byte_ptr)mine;
 
     f32x4 acc[TM][TN];
 #pragma unroll
@@ -139,12 +276,11 @@ tsvd_fp6_split_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split
 #pragma unroll
         for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    auto issue = [&](int step, int buf) {
-        if (X) return;
+    auto issue = [&](int step, int buf) {                    // step of the launch; this wavefront's half of its pieces
 #pragma unroll
-        for (int c = 0; c < (TOTAL + 7) / 8; ++c) {
-            const int idx = c * 8 + wave, chunk = idx / PIECES, piece = idx - chunk * PIECES, blk = step * KG * BPS + chunk;
-            if ((TOTAL % 8 == 0 || idx < TOTAL) && blk < nrun) {
+        for (int c = 0; c < (BPS * PIECES + 1) / 2; ++c) {
+            const int idx = 2 * c + rw, chunk = idx / PIECES, piece = idx - chunk * PIECES, blk = step * BPS + chunk;
+            if (idx < BPS * PIECES && blk < nrun) {
                 const int at = piece * 1024 + lane * 16;
                 if (CHUNK % 1024 == 0 || at < CHUNK)         // (lanes beyond the chunk would write into the next one)
                     buf_load128_to_lds(act_rsrc, lds_base + buf * STEP_BYTES + chunk * CHUNK + piece * 1024, lane * 16,
@@ -152,14 +288,13 @@ tsvd_fp6_split_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split
             }
         }
     };
-    // stage V: row 4 gg + vv of result block a comes from row 64 (gg & 1) + 16 (gg >> 1) + 32 (a >> 2) + 4 (a & 3) + vv of the
-    // wavefront's 128, so that result lane (g, token) holds the 32 rank positions of stage U's operand lane (see fp6_tile)
+    // (rows of stage V as in tsvd_fp6_panel_kernel)
     const int gg = i >> 2, vv = i & 3;
     const int w_voff = DIRECT ? (4 * (gg & 1) + (gg >> 1)) * p.nkt * 1024 + (g * 16 + vv) * 16 : lane * 16;
     auto load_w = [&](int step, u32x2 (&w)[BPS][TM]) {
 #pragma unroll
         for (int j = 0; j < BPS; ++j) {
-            int blk = min((step * KG + kg) * BPS + j, nrun - 1);
+            int blk = min(step * BPS + j, nrun - 1);
             if (p.code_blocks && blk >= p.code_blocks) blk -= p.code_blocks;      // (second set of planes: the same codes again)
             const int soff = (strip0 * p.nkt + (blk >> 1)) * 1024 + (blk & 1) * 8;
 #pragma unroll
@@ -174,22 +309,25 @@ tsvd_fp6_split_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split
 #pragma unroll
             for (int a = 0; a < TM; ++a) asm volatile("" :: "v"(w[j][a].x), "v"(w[j][a].y));
     };
-    // the operands of an MFMA step (one plane of one record, eight row blocks) are read two steps ahead
+    // What both wavefronts of the pair requested for their step `s` has arrived, and both are done with the step before it.
+    auto meet = [&](int s) {
+        __hip_atomic_store(ready + wave, s + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        while (__hip_atomic_load(ready + (wave ^ 1), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= s) {}
+    };
     auto compute = [&](int step, int buf, const u32x2 (&w)[BPS][TM]) {
-        const unsigned char* mine = smem + buf * STEP_BYTES + kg * BPS * CHUNK;
-        const int valid = nrun - (step * KG + kg) * BPS;     // blocks of this step that exist
+        const unsigned char* recs = mine + buf * STEP_BYTES;
+        const int valid = nrun - step * BPS;                 // blocks of this step that exist
         constexpr int STEPS = 3 * BPS * TN;
         u32x4 lo[3];
         u32x2 hi[3];
         uint32_t sc[2];
         auto read_step = [&](int st) {
-            const unsigned char* rec = mine + (st / 3) * FP6_REC_BYTES;
+            const unsigned char* rec = recs + (st / 3) * FP6_REC_BYTES;
             const int pl = st % 3;
             lo[pl] = *reinterpret_cast<const u32x4*>(rec + pl * 1024 + lane * 16);
             hi[pl] = *reinterpret_cast<const u32x2*>(rec + 3072 + pl * 512 + lane * 8);
             if (pl == 0) sc[(st / 3) & 1] = *reinterpret_cast<const uint32_t*>(rec + 4608 + lane * 4);
         };
-        if (valid <= 0) return;
         read_step(0);
         read_step(1);
 #pragma unroll
@@ -219,44 +357,33 @@ tsvd_fp6_split_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split
     };
 
     u32x2 wa[BPS][TM], wb[BPS][TM];
-    load_w(0, wa);
+    load_w(min(from, nsteps - 1), wa);
     if (PLACED && !tile.exists) return;
-    issue(0, 0);
-    if constexpr (X != 0) {
-        const int blocks = X == 2 ? nrun / 2 : nrun;         // (fp32: the second set of planes are further blocks)
-        auto record = [&](int blk, int tile) {               // steps alternate between the buffers, and there are at most two
-            const int step = blk / (KG * BPS);
-            return smem + step * STEP_BYTES + (blk - step * KG * BPS) * CHUNK + tile * FP6_REC_BYTES;
-        };
-        for (int q = wave; q < blocks * TN; q += 8) {
-            const int blk = q / TN, tile = q - blk * TN;
-            float v[32];
-            gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + tile, lane, v);
-            if constexpr (X == 2) tsvd_planes_of_32_twice(v, record(blk, tile), record(blk + blocks, tile), lane);
-            else tsvd_planes_of_32(v, record(blk, tile), lane);
-        }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    touch(wa);
-    __syncthreads();
-    for (int s = 0; s < nsteps; s += 2) {
-        load_w(min(s + 1, nsteps - 1), wb);
-        if (s + 1 < nsteps) issue(s + 1, 1);
-        compute(s, 0, wa);
+    if (count > 0) issue(from, 0);
+    __syncthreads();                                         // (the words are zero)
+    for (int s = 0; s < count; s += 2) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        touch(wb);
-        __syncthreads();
-        if (s + 1 < nsteps) {
-            load_w(min(s + 2, nsteps - 1), wa);
-            if (s + 2 < nsteps) issue(s + 2, 0);
-            compute(s + 1, 1, wb);
+        touch(wa);
+        meet(s);
+        if (s + 1 < count) {
+            load_w(from + s + 1, wb);
+            issue(from + s + 1, 1);
+        }
+        compute(from + s, 0, wa);
+        if (s + 1 < count) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            touch(wa);
-            __syncthreads();
+            touch(wb);
+            meet(s + 1);
+            if (s + 2 < count) {
+                load_w(from + s + 2, wa);
+                issue(from + s + 2, 0);
+            }
+            compute(from + s + 1, 1, wb);
         }
     }
+    __syncthreads();
 
-    // ---- the groups' partial sums: result block f = 8 tile + row block; group q finishes blocks q NF .. + NF - 1
+    // ---- the pairs' partial sums: result block f = 8 tile + row block; pair q finishes blocks q NF .. + NF - 1
     f32x4 fin[NF];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
@@ -266,22 +393,22 @@ tsvd_fp6_split_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split
         }
 #pragma unroll
     for (int f0 = 0; f0 < NF; f0 += NFR) {
-        auto slot = [&](int q, int from, int f) { return smem + ((((q * (KG - 1) + from) * RW + rw) * NFR + f) * 64 + lane) * 16; };
+        auto slot = [&](int q, int other, int f) { return smem + ((((q * (KG - 1) + other) * RW + rw) * NFR + f) * 64 + lane) * 16; };
         if (f0 > 0) __syncthreads();
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
             if (q != kg) {
-                const int from = kg < q ? kg : kg - 1;
+                const int other = kg < q ? kg : kg - 1;
 #pragma unroll
                 for (int f = 0; f < NFR; ++f)
-                    *reinterpret_cast<f32x4*>(slot(q, from, f)) = acc[(q * NF + f0 + f) & 7][(q * NF + f0 + f) >> 3];
+                    *reinterpret_cast<f32x4*>(slot(q, other, f)) = acc[(q * NF + f0 + f) & 7][(q * NF + f0 + f) >> 3];
             }
         __syncthreads();
         if (kg < NQ) {
 #pragma unroll
-            for (int from = 0; from < KG - 1; ++from)
+            for (int other = 0; other < KG - 1; ++other)
 #pragma unroll
-                for (int f = 0; f < NFR; ++f) fin[f0 + f] += *reinterpret_cast<const f32x4*>(slot(kg, from, f));
+                for (int f = 0; f < NFR; ++f) fin[f0 + f] += *reinterpret_cast<const f32x4*>(slot(kg, other, f));
         }
     }
     if (kg >= NQ) return;
@@ -325,7 +452,7 @@ tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // (rows of stage V as in tsvd_fp6_split_kernel)
+    // (rows of stage V as in tsvd_fp6_panel_kernel)
     const int gg = i >> 2, vv = i & 3;
     const int w_voff = DIRECT ? (4 * (gg & 1) + (gg >> 1)) * p.nkt * 1024 + (g * 16 + vv) * 16 : lane * 16;
     // (arrays of their own: the planes of a structure would be read as parts of longer vectors, and kept in scratch memory)
@@ -462,10 +589,11 @@ constexpr bool own = RW == 1 && (TN == 1 || X == 0);
 template <int RW, int TN, bool STAGE2, int EX, int X = 0, bool PLACED = false>
 auto kernel() {
     if constexpr (own<RW, TN, X>) return tsvd_fp6_own_kernel<TN, STAGE2, EX, X, PLACED>;
-    else return tsvd_fp6_split_kernel<RW, TN, STAGE2, EX, X, PLACED>;
+    else if constexpr (X == 0) return tsvd_fp6_pair_kernel<TN, STAGE2, EX, PLACED>;
+    else return tsvd_fp6_panel_kernel<RW, TN, X>;
 }
 template <int RW, int TN, int X>
-constexpr int split_lds = (own<RW, TN, X> ? 7 * 8 * TN * 1024 : 2 * 16 * FP6_REC_BYTES) + 16 * TN * 4;
+constexpr int split_lds = (own<RW, TN, X> ? 7 * 8 * TN * 1024 : 2 * 16 * FP6_REC_BYTES + (X == 0 ? 32 : 0)) + 16 * TN * 4;
 
 template <int RW, int TN, bool STAGE2, int EX, int X = 0>
 hipError_t init_one() {

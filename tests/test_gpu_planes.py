@@ -220,6 +220,17 @@ def test_blocks_of_a_wavefront(tsvd, M, N, K, B, v, u, own_x, x_dtype):
 
 
 @pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("own_x", [0, 1])
+@pytest.mark.parametrize("v,u", [(18, 18), (20, 20)])
+@pytest.mark.parametrize("M,N,K,B", [(20, 30, 20, 17), (257, 500, 510, 64), (300, 1025, 1150, 65), (512, 1030, 2050, 31), (130, 3330, 3900, 97), (90, 640, 900, 1025)])
+def test_blocks_of_a_pair(tsvd, M, N, K, B, v, u, own_x, x_dtype):
+    """Tiles of 256 rows, each pair of wavefronts with blocks of its own: pairs without any, with one, an odd and an even number of steps, a last step
+    that is not full; planes of x made by all wavefronts first or by their own pass."""
+    print(f"case blocks of a pair {M} {N} {K} {B} {v} {u} {own_x} {x_dtype}", flush=True)
+    _check(tsvd, M, N, K, B, x_dtype, {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_SPLIT_V": v, "TSVD_SPLIT_U": u, "TSVD_SPLIT_X": own_x})
+
+
+@pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("M,N,K,B,v,u", [(700, 5000, 2600, 300, 9, 9), (1900, 4500, 2100, 130, 10, 10), (2600, 4300, 2300, 200, 18, 18), (2050, 8300, 1100, 513, 20, 20),
                                          (4100, 4200, 1030, 40, 18, 9)])
 def test_tiles_by_xcd(tsvd, M, N, K, B, v, u, x_dtype):
