@@ -16,8 +16,9 @@
 // scale that is not finite all outputs of the channel.  Every such output is itself not finite: a lane that has stored one computes its
 // outputs again on the factors, tap by tap, zeros skipped, where only the outputs are touched whose taps hold the value.
 //
-// Measured on MI355X: 96 channels of 56 x 56, 7 x 7 at rank 5, 32 images, bf16: 68.4 -> 15.0 us (6.7 of them matrix instructions, about 3 the latency of the
-// first loads and the bands, 2 the launch); 60 random geometries of 64 to 768 channels: 1.04 to 41 times the speed of the kernel on the factors, 5.2 on the geometric average.
+// Measured on MI355X: 96 channels of 56 x 56, 7 x 7 at rank 5, 32 images, bf16: 14.4 us (68 on the factors): 6.7 of them matrix instructions, about 3.5 the latency of the
+// first loads and the bands, 2 the launch; 640 of 28 x 28, 5 x 5, stride 2, 8 images 7.8, 217 of 28 x 28, 7 x 7, 32 images 11.3 (16.6 and 14.5 with rows in loads of
+// two elements and more of them ahead).  60 random geometries of 64 to 768 channels: 1.04 to 41 times the speed of the kernel on the factors.
 #include "tsvd_depthwise.h"
 
 #include <algorithm>
@@ -82,15 +83,20 @@ __device__ __forceinline__ void outputs_on_factors(const depthwise_args& p, int 
     }
 }
 
-// ROW: elements per load of a row of x (8, or 2 / 1 where rows are not 16-byte aligned).  STEP: both strides.  With stride 2 the window of
-// 16 outputs would not fit 32 columns: a tile is 8 columns of two output rows there, and an input row is multiplied by the taps of both.
+// ROW: elements per load of a row of x: 8 where rows are aligned to 16 bytes, else 4 at any alignment, or 1 in rows of fewer than four.  (Rows of an even number
+// of elements were loaded by 2, odd ones by 1: four and eight requests a row, which keep the address unit busy longer than the row's matrix instructions the
+// matrix pipe.)  STEP: both strides.  With stride 2 the window of 16 outputs would not fit 32 columns: a tile is 8 columns of two output rows there, and an input
+// row is multiplied by the taps of both.
 // VEC: rows of y are a multiple of four elements and y is aligned to four (then a lane's four columns are inside or outside together
 // and are stored at once).
 template <int K1, int STEP, int ROW, bool VEC>
 __global__ void __launch_bounds__(256, K1 == 7 && STEP == 1 ? 3 : 2)
 tsvd_depthwise_kernel(depthwise_args p) {
     constexpr int COLS = 16 / STEP, NR = K1 + (STEP - 1) * STEP, ADV = STEP * STEP;      // of a tile: columns, input rows, input rows to the next
-    constexpr int RING = STEP == 1 ? NR + 3 : NR > 9 ? 20 : NR > 5 ? 16 : 12, PERIOD = STEP == 1 ? RING : RING / ADV;   // rows in registers; tiles until slots repeat
+    // Rows in registers, and tiles until the slots repeat.  As few as keep a row's latency behind a tile or two: every further row is requested by all wavefronts
+    // before the first product, and the loop is unrolled over the slots.  (Three rows ahead with stride 1, 16 or 20 slots with stride 2: 2 % slower
+    // with rows by 8, 663 channels of 7 x 7, 3 x 3, stride 2, 2 images 6.3 -> 9.9 us.)
+    constexpr int RING = STEP == 1 ? NR + (ROW == 1 ? 0 : 2) : NR > 8 ? 12 : 8, PERIOD = STEP == 1 ? RING : RING / ADV;
     const tsvd_depthwise_problem& g = p.g;
     __shared__ u32x2 weight[64];                      // of a tap its three parts (bf16: the first two, the last); the last entry is zero
     __shared__ __align__(16) unsigned char bands[NR * 3 * 1024];
@@ -107,46 +113,70 @@ tsvd_depthwise_kernel(depthwise_args p) {
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.x) + (size_t)group * (p.plane_bytes / 2), 0, (int)p.plane_bytes, 0x00020000);
     const int iy_first = row0 * STEP - g.p1, base = 2 * img * g.H * g.W, pitch = 2 * g.W;
     constexpr unsigned NONE = 0x40000000u;                  // beyond the buffer (below 2^30 bytes): loads give zero
-    unsigned col_off[8 / ROW];
+    constexpr int LOADS = 8 / ROW;
+    unsigned col_off[LOADS], beyond[LOADS];
 #pragma unroll
-    for (int e = 0; e < 8 / ROW; ++e) {
-        const int col = c0 + 8 * q + ROW * e;         // (ROW divides the width: all of its elements are inside or none)
-        col_off[e] = col >= 0 && col < g.W && strip_ok ? (unsigned)(base + 2 * col) : NONE;
+    for (int e = 0; e < LOADS; ++e) {
+        // (columns are multiples of ROW: the four elements of a load lie inside the row, or outside, or their last one to three beyond it)
+        const int col = c0 + 8 * q + ROW * e, more = ROW == 4 ? max(0, col + 4 - g.W) : 0;
+        col_off[e] = col >= 0 && col < g.W && strip_ok ? (unsigned)(base + 2 * (col - more)) : NONE;
+        beyond[e] = 16 * (more & 3);
     }
     auto load_row = [&](int j) __attribute__((always_inline)) {                // row j of the strip's window
         const int iy = iy_first + j;
         const unsigned off = (unsigned)iy < (unsigned)g.H ? (unsigned)(iy * pitch) : NONE;
         if constexpr (ROW == 8) {
             return buf_load128(xr, (int)(off + col_off[0]), 0);
+        } else if constexpr (ROW == 4) {
+            const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(xr, (int)(off + col_off[0]), 0, 0);
+            const u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(xr, (int)(off + col_off[1]), 0, 0);
+            return u32x4{lo.x, lo.y, hi.x, hi.y};
         } else {
             u32x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if constexpr (ROW == 2) {
-                    v[e] = buf_load32(xr, (int)(off + col_off[e]), 0);
-                } else {
-                    const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(xr, (int)(off + col_off[2 * e]), 0, 0);
-                    const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(xr, (int)(off + col_off[2 * e + 1]), 0, 0);
-                    v[e] = lo | hi << 16;
-                }
+                const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(xr, (int)(off + col_off[2 * e]), 0, 0);
+                const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(xr, (int)(off + col_off[2 * e + 1]), 0, 0);
+                v[e] = lo | hi << 16;
             }
             return v;
         }
     };
+    // Four elements that end with the row where the lane's four do not: those before are shifted out, where the row is first needed (here its loads would
+    // be awaited).
+    auto in_place = [&](u32x4& v) __attribute__((always_inline)) {
+        if constexpr (ROW == 4) {
+            const uint64_t lo = ((uint64_t)v.y << 32 | v.x) >> beyond[0], hi = ((uint64_t)v.w << 32 | v.z) >> beyond[1];
+            v = u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+        }
+    };
     u32x4 ring[RING];                                 // row j in slot j % RING
+    // ---- what the first term of this thread is made of, requested ahead of the rows (results come in the order of the requests)
+    const int taps = g.k1 * g.k2, ranks = min(g.kg, NR * 3 * 256 / 49);         // (ranks whose terms fit at a time)
+    const int idx0 = min((int)threadIdx.x, ranks * taps - 1), pos0 = (int)tsvd_rank_position(group * g.kg + idx0 / taps, g.K), tap0 = idx0 % taps;
+    int u_word, u_bit, v_word, v_bit;
+    tsvd_code_position(m & 15, pos0 & 255, &u_word, &u_bit);
+    tsvd_code_position(pos0 & 15, tap0, &v_word, &v_bit);
+    const uint32_t u_codes = g.U[((size_t)(m >> 4) * g.u_tps + (pos0 >> 8)) * 256 + u_word], v_codes = g.V[(size_t)(pos0 >> 4) * g.v_tps * 256 + v_word];
+    const float s_first = g.S[pos0];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < RING - ADV; ++j) ring[j] = load_row(j);
+    __builtin_amdgcn_sched_barrier(0);
 
     // ---- the kernel of the channel, then its banded matrices
-    const int taps = g.k1 * g.k2, ranks = min(g.kg, NR * 3 * 256 / 49);         // (ranks whose terms fit at a time)
     float w = 0.f;                                    // of tap threadIdx.x
     for (int k0 = 0; k0 < g.kg; k0 += ranks) {
         const int n = min(ranks, g.kg - k0);
         if (k0) __syncthreads();
         for (int idx = threadIdx.x; idx < n * taps; idx += 256) {
-            const int k = idx / taps, pos = (int)tsvd_rank_position(group * g.kg + k0 + k, g.K);
-            const int u = tsvd_code_at(g.U, g.u_tps, m, pos), v = tsvd_code_at(g.V, g.v_tps, pos, idx - k * taps);
-            const float s = g.S[pos];
+            int u = (int)(u_codes >> u_bit), v = (int)(v_codes >> v_bit);
+            float s = s_first;
+            if (k0 > 0 || idx >= 256) {
+                const int k = idx / taps, pos = (int)tsvd_rank_position(group * g.kg + k0 + k, g.K);
+                u = tsvd_code_at(g.U, g.u_tps, m, pos), v = tsvd_code_at(g.V, g.v_tps, pos, idx - k * taps);
+                s = g.S[pos];
+            }
             terms[idx] = (u & v & 1) ? ((u ^ v) & 2 ? -s : s) : 0.f;
         }
         __syncthreads();
@@ -164,10 +194,10 @@ tsvd_depthwise_kernel(depthwise_args p) {
         weight[threadIdx.x] = u32x2{part[0] | part[1] << 16, part[2]};
     }
     __syncthreads();
-    const int shift = first - c0;                     // (the same for every tile: a tile starts at a multiple of 16 columns)
+    const int from_c0 = first - c0;                   // (the same for every tile: a tile starts at a multiple of 16 columns)
     for (int f = wave; f < NR; f += 4) {
         const int dy = f - i / COLS * STEP;
-        const int at = (unsigned)dy < (unsigned)K1 ? dy * g.k2 : 63, first_dx = 8 * q - shift - i % COLS * STEP;   // window column of element 0, from the output's first
+        const int at = (unsigned)dy < (unsigned)K1 ? dy * g.k2 : 63, first_dx = 8 * q - from_c0 - i % COLS * STEP;   // window column of element 0, from the output's first
         u32x4 part[3];
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
@@ -204,6 +234,8 @@ tsvd_depthwise_kernel(depthwise_args p) {
 #pragma unroll
         for (int j = RING - ADV; j < RING; ++j) ring[(u * ADV + j) % RING] = load_row(t * ADV + j);
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = NR - ADV; f < NR; ++f) in_place(ring[(u * ADV + f) % RING]);
         f32x4 acc[3];
         acc[0] = f32x4{b, b, b, b};
         acc[1] = acc[2] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -228,6 +260,8 @@ tsvd_depthwise_kernel(depthwise_args p) {
         odd |= !(fabsf(y[0]) < INFINITY);         // (a value that spreads reaches all four)
         at += yp;
     };
+#pragma unroll
+    for (int f = 0; f < NR - ADV; ++f) in_place(ring[f]);
     int t = 0;
     while (each(std::make_integer_sequence<int, PERIOD>{}, [&](auto u) __attribute__((always_inline)) {
         tile(u, t);
@@ -248,7 +282,7 @@ void launch(const depthwise_args& a, int row, dim3 grid, hipStream_t stream) {
         else hipLaunchKernelGGL((tsvd_depthwise_kernel<K1, STEP, ROW, false>), grid, dim3(256), 0, stream, a);
     };
     if (row == 8) go(std::integral_constant<int, 8>{});
-    else if (row == 2) go(std::integral_constant<int, 2>{});
+    else if (row == 4) go(std::integral_constant<int, 4>{});
     else go(std::integral_constant<int, 1>{});
 }
 
@@ -265,13 +299,13 @@ hipError_t tsvd_depthwise_launch(const tsvd_depthwise_problem& g, hipStream_t st
     const int cols = 16 / g.s1;
     a.col_tiles = (g.Wo + cols - 1) / cols;
     // Output rows per strip: short strips reload k1 - 1 rows each, long ones leave compute units idle.  In units of a matrix instruction, per
-    // round of workgroups: the rows of a strip, and about 250 for the bands and the first rows.
+    // round of workgroups: the rows of a strip, and for the bands and the first rows what was best on 27 geometries (100 in place of 60: 1.5 % slower, 30: one of them 18 %).
     long long best = -1;
     for (int n = 1; n <= std::min(g.Ho, 64); ++n) {
         const int R = (g.Ho + n - 1) / n, segments = (g.Ho + R - 1) / R;
         const long long strips = (long long)g.images * segments, tasks = (strips + 15) / 16 * a.col_tiles, blocks = (tasks + 3) / 4 * channels;
         const long long work = (long long)((R + g.s1 - 1) / g.s1) * 3 * (g.k1 + (g.s1 - 1) * g.s1);
-        const long long cost = (blocks + g.cu_count - 1) / g.cu_count * (work + 4 * g.k1 + 100) + work;
+        const long long cost = (blocks + g.cu_count - 1) / g.cu_count * (work + 4 * g.k1 + 60) + work;
         if (best < 0 || cost < best) {
             best = cost;
             a.R = R; a.segments = segments; a.strips = (int)strips; a.tasks = (int)tasks;
@@ -279,7 +313,7 @@ hipError_t tsvd_depthwise_launch(const tsvd_depthwise_problem& g, hipStream_t st
     }
     const dim3 grid((unsigned)((a.tasks + 3) / 4), (unsigned)channels);
     const uintptr_t at = reinterpret_cast<uintptr_t>(g.x);
-    const int row = g.W % 8 == 0 && at % 16 == 0 ? 8 : g.W % 2 == 0 && at % 4 == 0 ? 2 : 1;
+    const int row = g.W % 8 == 0 && at % 16 == 0 ? 8 : g.W >= 4 ? 4 : 1;
     if (g.s1 == 1) {
         if (g.k1 == 3) launch<3, 1>(a, row, grid, stream);
         else if (g.k1 == 5) launch<5, 1>(a, row, grid, stream);

@@ -47,6 +47,39 @@ def test_depthwise_exact_and_random(tsvd, case):  # noqa: F811
     assert np.abs(got - ref).max() <= 1e-6 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 6, 7, 8, 11, 16, 18, 29])
+@pytest.mark.parametrize("k,st", [(3, 1), (5, 1), (7, 1), (3, 2), (5, 2), (7, 2)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_depthwise_rows_of_any_width_at_any_element(tsvd, offset, k, st, W):  # noqa: F811
+    """Rows of every remainder, x at 16 bytes and one element beyond: the loads that end with a row, at the ends of x too, with infinities on both sides
+    of x (nothing from there may reach a result).  Exact."""
+    import ctypes
+
+    import torch
+    G, kg, images, H = 3, 6, 18, 9
+    rng = np.random.default_rng(100 * W + k)
+    U = np.kron(np.eye(G, dtype=np.int8), rng.choice([-1, 1], size=(1, kg)).astype(np.int8))
+    V = rng.integers(-1, 2, size=(G * kg, k * k)).astype(np.int8)
+    S = rng.integers(-2, 3, size=G * kg).astype(np.float32)
+    x = rng.integers(-2, 3, size=(images, G, H, W)).astype(np.float32)
+    ref = oc.tsvd_conv2d(x, U, S, V, 0, G, G, k, k, (st, st), (k // 2, k // 2), (1, 1), groups=G).transpose(1, 0, 2, 3).reshape(-1)
+    xd = torch.full((x.size + 48,), float("inf"), dtype=torch.bfloat16, device="cuda:0")
+    xd[16 + offset:16 + offset + x.size] = torch.from_numpy(np.ascontiguousarray(x.transpose(1, 0, 2, 3))).to("cuda:0").to(torch.bfloat16).flatten()
+    y = torch.empty(ref.size, dtype=torch.float32, device="cuda:0")
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda:0")
+    h = tsvd.tsvd_pack(U, S, V)
+    geometry = (ctypes.c_int32 * 12)(0, G, G, k, k, st, st, k // 2, k // 2, 1, 1, G)
+    p, i64 = ctypes.c_void_p, ctypes.c_int64
+    print(f"case depthwise rows of {W} at element {offset}, {k} x {k}, stride {st}", flush=True)
+    forward = ctypes.CDLL(tsvd.lib_path()).tsvd_conv2d_forward
+    status = forward(p(h.ptr), geometry, p(xd[16 + offset:].data_ptr()), i64(images), i64(H), i64(W), p(None), p(y.data_ptr()), ctypes.c_int(tsvd.TSVD_F32),
+                     p(ws.data_ptr()), ctypes.c_size_t(256), p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    tsvd.tsvd_free(h)
+    assert status == 0
+    assert np.array_equal(y.cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("offset", [0, 1, 2, 3, 4])
 def test_depthwise_result_at_any_element(tsvd, offset, y_dtype):  # noqa: F811
