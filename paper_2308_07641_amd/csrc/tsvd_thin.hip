@@ -16,7 +16,9 @@
 // before a unit's stores are issued: loads and stores share one counter); a fetch is 16 bytes per lane and strip, the words of
 // 256 contraction indices.
 // A convolution's columns are gathered straight from the images: a table of offsets per index in LDS, and per token a bit
-// mask of the taps that fall outside its image.
+// mask of the taps that fall outside its image.  Rows of three taps come as one load of four elements each, six for sixteen indices, with a table and a mask of rows: the
+// address unit's requests bound the gather (3 x 3: 256 x 2304 x 116 at 14896 positions 52.4 -> 42.6 us, 89 x 1683 x 78 at 3920 19.1 -> 14.8, 128 x 621 x 412 at 27440
+// 56.8 -> 46.7; 60 drawn convolutions, 25 of them with such rows, 0.946 of the time).
 // Measured on MI355X: 3072 x 768 x 1545 bf16 at 3152 tokens, token-major: 71.5 -> 39.2 us (ring kernels with a copy of x before; 16 tokens per panel); the
 // map of a 3 x 3 convolution, 256 x 2304 x 768 at 6272 positions: 75.5 -> 36.8 us (columns written and read before; 32).
 // What bounds them: the matrix instructions of the panels' last round, and the code words that every workgroup pulls from its L2.  By
@@ -49,6 +51,9 @@ struct thin_args {
     int slices;                              // workgroups of a panel, each with the whole z and its part of y's rows
 };
 
+// THIN_CONV whose V takes rows of three taps side by side, of images of four columns and more: a row is one load of four elements.
+constexpr int THIN_CONV_ROWS = 3;
+
 template <int TN, int RB, int SOURCE, bool CHUNKED>
 __global__ void __launch_bounds__(512, 2)
 tsvd_thin_panel_kernel(thin_args p) {
@@ -69,8 +74,9 @@ tsvd_thin_panel_kernel(thin_args p) {
     // ---- the record of (block, tile) of x, by one wavefront.  What does not exist (indices beyond N, taps outside the image) is
     // read at an offset beyond the buffer, where loads give zero; tokens beyond the batch repeat the last one (never stored)
     const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.x), 0, p.x_bytes, 0x00020000);
-    int conv_base = 0;                       // THIN_CONV: byte offset of this lane's token (its tile is the wavefront's), and the taps outside its
-    uint64_t conv_outside = 0;               // image as a bit mask, repeated with the period of the taps
+    int conv_base = 0;                       // THIN_CONV: byte offset of this lane's token (its tile is the wavefront's), and the taps (rows of taps) outside
+    uint64_t conv_outside = 0;               // its image as a bit mask, repeated with the period of the taps (of the rows)
+    int conv_right = 0, conv_left = 0;       // THIN_CONV_ROWS: bits by which what a load of a row begins with lies before the first tap, and behind it
     if constexpr (SOURCE == THIN_CONV) {
         const int taps = p.kv1 * p.kv2, channel = p.images * p.H * p.W;
         for (int k = threadIdx.x; k < 128 * p.nvb; k += 512) {
@@ -86,6 +92,22 @@ tsvd_thin_panel_kernel(thin_args p) {
                     for (int b = dy * p.kv2 + dx; b < 64; b += taps) conv_outside |= 1ull << b;
         __syncthreads();
     }
+    if constexpr (SOURCE == THIN_CONV_ROWS) {
+        const int channel = p.images * p.H * p.W;
+        for (int r = threadIdx.x; r < 128 * p.nvb / 3 + 2; r += 512) {
+            const int ci = r / p.kv1, dy = r - ci * p.kv1;
+            const_cast<int*>(ktab)[r] = 3 * r < p.N ? 2 * (ci * channel + dy * p.d1 * p.W) : (int)0x80000000;
+        }
+        const int tok = min(b0 + 16 * (wave % TN) + i, p.B - 1), plane = p.Hv * p.Wv, img = tok / plane, at = tok - img * plane, py = at / p.Wv,
+                  px = at - py * p.Wv, y0 = py * p.s1 - p.p1, x0 = px * p.s2 - p.p2, from = max(0, min(x0, p.W - 4)), by = x0 - from;
+        conv_base = 2 * (img * p.H * p.W + y0 * p.W + from);
+        conv_right = 16 * max(0, min(by, 3));
+        conv_left = 16 * max(0, min(-by, 3));
+        for (int dy = 0; dy < p.kv1; ++dy)
+            if ((unsigned)(y0 + dy * p.d1) >= (unsigned)p.H || by > 3 || by < -3)
+                for (int b = dy; b < 64; b += p.kv1) conv_outside |= 1ull << b;
+        __syncthreads();
+    }
     auto make_record = [&](int block, int tile, unsigned char* rec) __attribute__((always_inline)) {
         int tok = min(b0 + 16 * tile + i, p.B - 1);
         const int k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1);
@@ -97,7 +119,41 @@ tsvd_thin_panel_kernel(thin_args p) {
             raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, off, 0, 0);
             if (e % 8 == 7) __builtin_amdgcn_sched_barrier(0);      // (the offsets of all 32 at once would not fit the registers)
         };
-        if constexpr (SOURCE == THIN_CONV) {
+        if constexpr (SOURCE == THIN_CONV_ROWS) {
+            // the rows of three that sixteen indices from k on lie in, six of them
+            u32x2 rows[2][6];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = (k0 + 32 * h) / 3;
+                const uint32_t out = (uint32_t)(conv_outside >> (r % p.kv1));
+#pragma unroll
+                for (int j = 0; j < 6; ++j)
+                    rows[h][j] = __builtin_amdgcn_raw_buffer_load_b64(x_rsrc, (ktab[r + j] + conv_base) | (int)((out << (31 - j)) & 0x80000000u), 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t s[9];                                       // eighteen values, two in a word
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {                        // (shifts bring zeros in where taps lie beside the image)
+                    rows[h][j] = __builtin_bit_cast(u32x2, __builtin_bit_cast(uint64_t, rows[h][j]) >> conv_right << conv_left);
+                    if (j % 2) {
+                        const u32x2 a = rows[h][j - 1], b = rows[h][j];
+                        s[3 * (j / 2)] = a.x;
+                        s[3 * (j / 2) + 1] = __builtin_amdgcn_perm(b.x, a.y, 0x05040100u);
+                        s[3 * (j / 2) + 2] = __builtin_amdgcn_alignbit(b.y, b.x, 16);
+                    }
+                }
+                const int first = (k0 + 32 * h) % 3;
+                const uint32_t half = first == 1 ? 16 : 0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t two = __builtin_amdgcn_alignbit(s[e + 1], first == 2 ? s[e + 1] : s[e], half);
+                    v[16 * h + 2 * e] = __uint_as_float(two << 16);
+                    v[16 * h + 2 * e + 1] = __uint_as_float(two & 0xFFFF0000u);
+                }
+            }
+        } else if constexpr (SOURCE == THIN_CONV) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int k = k0 + 32 * h, first = k % (p.kv1 * p.kv2);
@@ -118,7 +174,7 @@ tsvd_thin_panel_kernel(thin_args p) {
                 gather(e, (2 * (k * (int)p.ldx + tok)) | (k < p.N ? 0 : NONE));
             }
         }
-        if constexpr (SOURCE != THIN_TOKEN_MAJOR) {
+        if constexpr (SOURCE == THIN_CONV || SOURCE == THIN_FEATURE_MAJOR) {
 #pragma unroll
             for (int e = 0; e < 32; ++e) v[e] = __uint_as_float((uint32_t)raw[e] << 16);
         }
@@ -215,7 +271,16 @@ tsvd_thin_panel_kernel(thin_args p) {
         auto make = [&](int c0) __attribute__((always_inline)) {
             const int blocks = min(p.chunk, p.nvb - c0);
             unsigned char* rec = xrec + (c0 / p.chunk & (p.buffers - 1)) * p.chunk * TN * FP6_REC_BYTES;
-            for (int q = wave; q < blocks * TN; q += NW) make_record(c0 + q / TN, q % TN, rec + q * FP6_REC_BYTES);
+            // Beside the multiplication of a chunk: wavefronts of fewer rank blocks first make as many records as take its time, a fifth of them, then all
+            // in turn.  (Records of a convolution's single elements are bound by the address unit, whoever makes them: 315 -> 320 us with this on 228 x 12800 x 388.)
+            int each = 0;
+            const int side = wave / TN, tile = wave % TN, busy = (p.nub % NW + TN - 1 - tile) / TN, idle = NW / TN - busy;
+            if (CHUNKED && SOURCE != THIN_CONV && c0 > 0 && busy > 0 && idle > 0) {
+                each = min(blocks * TN / 5, blocks / idle);
+                if (side >= busy)
+                    for (int q = side - busy; q < idle * each; q += idle) make_record(c0 + q, tile, rec + (q * TN + tile) * FP6_REC_BYTES);
+            }
+            for (int q = idle * each + (each ? NW / TN - 1 - side : side); q < blocks; q += NW / TN) make_record(c0 + q, tile, rec + (q * TN + tile) * FP6_REC_BYTES);
         };
         make(0);
         __syncthreads();
@@ -373,6 +438,7 @@ hipError_t launch(const thin_args& a, int lds, hipStream_t stream) {
 }
 template <int TN, int RB>
 hipError_t launch(int source, const thin_args& a, int lds, hipStream_t stream) {
+    if (source == THIN_CONV && a.kv2 == 3 && a.d2 == 1 && a.W >= 4) return launch<TN, RB, THIN_CONV_ROWS>(a, lds, stream);
     if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, lds, stream);
     if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, lds, stream);
     return launch<TN, RB, THIN_FEATURE_MAJOR>(a, lds, stream);
@@ -389,7 +455,8 @@ template <int TN, int RB>
 hipError_t init() {
     hipError_t e;
     if ((e = init<TN, RB, THIN_FEATURE_MAJOR>()) != hipSuccess || (e = init<TN, RB, THIN_TOKEN_MAJOR>()) != hipSuccess) return e;
-    return init<TN, RB, THIN_CONV>();
+    if ((e = init<TN, RB, THIN_CONV>()) != hipSuccess) return e;
+    return init<TN, RB, THIN_CONV_ROWS>();
 }
 
 }  // namespace

@@ -249,3 +249,32 @@ def test_tiles_by_xcd(tsvd, M, N, K, B, v, u, x_dtype):
     assert np.array_equal(y.cpu().numpy(), oracle.forward(i.U, i.S, i.V, i.X))
     assert bool((guarded[need:] == 0x5A).all())
     tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("tiles", [1, 2])
+@pytest.mark.parametrize("form,ci,co,k1,K,H,W,geom", [
+    (0, 5, 7, 3, 60, 6, 4, ((1, 1), (1, 1), (1, 1))), (0, 5, 7, 3, 60, 6, 3, ((1, 1), (1, 1), (1, 1))), (0, 43, 9, 3, 150, 5, 9, ((2, 3), (4, 5), (2, 1))),
+    (0, 20, 9, 5, 150, 7, 11, ((1, 2), (0, 3), (1, 1))), (2, 90, 3, 2, 300, 6, 5, ((1, 1), (1, 2), (1, 1))), (0, 20, 9, 3, 150, 7, 11, ((1, 1), (2, 2), (1, 2))),
+    (0, 300, 5, 3, 150, 5, 7, ((1, 1), (1, 1), (1, 1))), (0, 460, 5, 3, 777, 5, 5, ((1, 1), (1, 1), (1, 1))), (0, 460, 5, 3, 1100, 5, 5, ((1, 1), (0, 1), (1, 1)))])
+def test_thin_panels_gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom, tiles):
+    """Rows of three taps in loads of four elements: images as wide as a load and narrower (which take element loads, as dilated rows do), taps that
+    begin more than a load before or behind a row, kernels of more and fewer rows, x at an odd element; and x in chunks that wavefronts of
+    fewer rank blocks make more records of.  Exact."""
+    import torch
+    from oracle import conv as oc
+    k2, images = 3, 5
+    rows, cols = {0: (co, ci * k1 * k2), 2: (co * k1, ci * k2)}[form]
+    rng = np.random.default_rng(form + ci + k1 + K + W)
+    print(f"case thin rows of three {form} {ci} {co} {k1} {K} {H} {W} {geom} {tiles}", flush=True)
+    U = rng.choice([-1, 0, 1], size=(rows, K), p=[0.05, 0.9, 0.05]).astype(np.int8)
+    V = rng.choice([-1, 0, 1], size=(K, cols), p=[0.05, 0.9, 0.05]).astype(np.int8)
+    S = rng.integers(-1, 2, size=K).astype(np.float32)
+    x = rng.integers(-1, 2, size=(images, ci, H, W)).astype(np.float32)
+    ref = oc.tsvd_conv2d(x, U, S, V, form, co, ci, k1, k2, *geom)
+    h = tsvd.tsvd_pack(U, S, V)
+    tsvd.tsvd_tuning_set("TSVD_THIN", tiles)
+    xd = torch.full((x.size + 9,), float("nan"), dtype=torch.bfloat16, device="cuda:0")        # (nothing from beside x may reach y)
+    xd = xd[1:1 + x.size].view(ci, images, H, W).copy_(torch.from_numpy(x.transpose(1, 0, 2, 3)))
+    y = tsvd.tsvd_conv2d_forward(h, form, ci, co, k1, k2, xd, *geom)
+    assert torch.equal(y.cpu(), torch.from_numpy(np.ascontiguousarray(ref.transpose(1, 0, 2, 3))).to(y.dtype))
+    tsvd.tsvd_free(h)
