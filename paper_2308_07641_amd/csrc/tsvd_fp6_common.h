@@ -132,6 +132,66 @@ __device__ __forceinline__ void tsvd_gather_row(const T* row, int k0, int N, boo
     }
 }
 
+// The 32 values of one operand lane from feature-major bf16 x (N rows of B tokens, ld apart; eight values at least): features 128 block .., tokens tok0 .. + 15 of
+// a wavefront.  Its 128 rows of 32 bytes come as four chunks of eight tokens a lane, at any alignment, and are transposed in 4 KiB of LDS of its own (a load per value
+// costs 32 requests, which keep the address unit busy, and an address each).  Row r of the 64 of two runs lies at position r ^ 2 ((r >> 4 ^ r >> 5) & 1), so that the lane groups
+// served in a cycle hit different banks.  A chunk that would pass the end of x is read to end there and shifted; features beyond N
+// are zero; tokens beyond B hold what stands there, and nobody stores what becomes of them.
+// block, tok0: uniform.
+__device__ __forceinline__ bool tsvd_columns_end(long long ld, int N, int block) {       // (a chunk ends at most 63 tokens beyond B: four more rows of 17 are more)
+    return 128 * block + 132 > N || ld < 17 || ld >= 1 << 23;
+}
+__device__ __forceinline__ int tsvd_column_row(int j, int lane) {                        // row of the block that a lane's chunk j comes from
+    const int pos = (lane >> 1) + 32 * (j & 1), r = pos ^ ((((pos >> 4) ^ (pos >> 5)) & 1) << 1);
+    return 32 * (j >> 1) + 64 * (r >> 5) + (r & 31);
+}
+__device__ __forceinline__ void tsvd_request_columns(const uint16_t* x, long long ld, int N, int B, int block, int tok0, int lane, u32x4 (&raw)[4]) {
+    typedef u32x4 chunk_at __attribute__((aligned(2)));
+    if (tsvd_columns_end(ld, N, block)) {
+        const long long last = (long long)(N - 1) * ld + B - 8;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            raw[j] = *reinterpret_cast<const chunk_at*>(x + min(min(128 * block + tsvd_column_row(j, lane), N) * ld + (tok0 + 8 * (lane & 1)), last));
+    } else {
+        const uint16_t* base = x + 128 * block * ld + tok0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            raw[j] = *reinterpret_cast<const chunk_at*>(base + 32 * (j >> 1) * ld + (unsigned)(tsvd_column_row(j & 1, lane) * (int)ld + 8 * (lane & 1)));
+    }
+}
+__device__ __forceinline__ void tsvd_columns_of(u32x4 (&raw)[4], long long ld, int N, int B, int block, int tok0, int lane, unsigned char* slot, float (&v)[32]) {
+    if (tsvd_columns_end(ld, N, block)) {
+        const long long last = (long long)(N - 1) * ld + B - 8;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int by = (int)min(max(min(128 * block + tsvd_column_row(j, lane), N) * ld + (tok0 + 8 * (lane & 1)) - last, 0ll), 8ll);       // values read too early
+            if (__any((by & 7) != 0)) {
+                const unsigned __int128 w = __builtin_bit_cast(unsigned __int128, raw[j]);
+                raw[j] = __builtin_bit_cast(u32x4, w >> (16 * by & 127));
+            }
+            if (by == 8) raw[j] = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4*>(slot + j * 1024 + lane * 16) = raw[j];
+    __builtin_amdgcn_wave_barrier();
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr_t;
+    auto transposed = [](const unsigned char* at) { return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)at)); };
+    const int i = lane & 15, g = lane >> 4, row = 32 * (g & 1) + 16 * (g >> 1) + (i >> 3) + 4 * ((i >> 2) & 1), turned = (g & 1) ^ (g >> 1);
+    const int at_lo = (row + 2 * turned) * 32 + (i & 3) * 8, at_hi = (row + 2 * (1 - turned)) * 32 + (i & 3) * 8;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {                            // values 8 j .. + 7: word m holds m and m + 4 of them
+        const u32x2 lo = transposed(slot + (j >> 1) * 2048 + at_lo + (j & 1) * 256), hi = transposed(slot + (j >> 1) * 2048 + at_hi + (j & 1) * 256);
+        const uint32_t w[4] = {lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            v[8 * j + m] = __uint_as_float(w[m] << 16);
+            v[8 * j + m + 4] = __uint_as_float(w[m] & 0xFFFF0000u);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 // RISEN: the plane's number among those that tsvd_planes_of_32 left with RISE
 template <int PL, int RISEN = -1>
 __device__ __forceinline__ f32x4 mfma_fp6(const u32x4& a, const u32x4& lo, const u32x2& hi, uint32_t scale, f32x4 acc) {

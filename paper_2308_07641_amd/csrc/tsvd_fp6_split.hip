@@ -21,9 +21,10 @@ namespace {
 
 // ---- the operand lanes of x ----------------------------------------------------------------------
 // The 32 values of one lane of the record of (16-token tile, 128-index block), from activations in any layout: indices k0 + 32 (e >> 4) +
-// (e & 15); indices beyond N and tokens beyond B read as zero.
+// (e & 15); indices beyond N read as zero, tokens beyond B as anything.  slot: 4 KiB of LDS of this wavefront, for bf16.  (Feature-major bf16 with a load per
+// value before: 5541 x 729 x 4962 at 50 tokens 17.2 -> 15.5 us, 704 x 5696 x 767 at 378 21.4 -> 19.4, 256 x 8183 x 2961 at 92 24.0 -> 22.6.)
 template <bool F32>
-__device__ __forceinline__ void gather_x(const void* x, long long ld, bool token_major, int N, int B, int block, int tile, int lane, float (&v)[32]) {
+__device__ __forceinline__ void gather_x(const void* x, long long ld, bool token_major, int N, int B, int block, int tile, int lane, float (&v)[32], unsigned char* slot) {
     using T = std::conditional_t<F32, uint32_t, uint16_t>;
     const int i = lane & 15, g = lane >> 4, tok = tile * 16 + i, k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1), tc = min(tok, B - 1);
     const T* p = static_cast<const T*>(x);
@@ -34,12 +35,17 @@ __device__ __forceinline__ void gather_x(const void* x, long long ld, bool token
             if (tok >= B) v[e] = 0.f;
         return;
     }
-    auto value = [](T r) { return F32 ? __builtin_bit_cast(float, (uint32_t)r) : __uint_as_float((uint32_t)r << 16); };
-    T r[32];
+    if constexpr (!F32) {
+        u32x4 chunks[4];
+        tsvd_request_columns(p, ld, N, B, block, 16 * tile, lane, chunks);
+        tsvd_columns_of(chunks, ld, N, B, block, 16 * tile, lane, slot, v);
+    } else {
+        T r[32];
 #pragma unroll
-    for (int e = 0; e < 32; ++e) r[e] = p[(size_t)min(k0 + 32 * (e >> 4) + (e & 15), N - 1) * ld + tc];
+        for (int e = 0; e < 32; ++e) r[e] = p[(size_t)min(k0 + 32 * (e >> 4) + (e & 15), N - 1) * ld + tc];
 #pragma unroll
-    for (int e = 0; e < 32; ++e) v[e] = tok < B && k0 + 32 * (e >> 4) + (e & 15) < N ? value(r[e]) : 0.f;
+        for (int e = 0; e < 32; ++e) v[e] = tok < B && k0 + 32 * (e >> 4) + (e & 15) < N ? __uint_as_float(r[e]) : 0.f;
+    }
 }
 
 // The operand pass: a wavefront makes one record (fp32: two, six planes), token tile blockIdx.x * 4 + wave, block blockIdx.y
@@ -47,10 +53,11 @@ __device__ __forceinline__ void gather_x(const void* x, long long ld, bool token
 template <bool F32>
 __global__ void __launch_bounds__(256)
 tsvd_planes_kernel(const void* __restrict__ x, long long ld, int token_major, int N, int B, int nblocks, unsigned char* __restrict__ planes) {
-    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int tile = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    __shared__ __align__(16) unsigned char slots[F32 ? 16 : 4 * 4096];
     if (tile * 16 >= B) return;
     float v[32];
-    gather_x<F32>(x, ld, token_major != 0, N, B, blockIdx.y, tile, lane, v);
+    gather_x<F32>(x, ld, token_major != 0, N, B, blockIdx.y, tile, lane, v, slots + (F32 ? 0 : (tile & 3) * 4096));
     unsigned char* rec = planes + ((size_t)((tile >> 3) * (F32 ? 2 * nblocks : nblocks) + blockIdx.y) * 8 + (tile & 7)) * FP6_REC_BYTES;
     if constexpr (F32) tsvd_planes_of_32_twice(v, rec, rec + (size_t)nblocks * 8 * FP6_REC_BYTES, lane);   // a second set behind the first
     else tsvd_planes_of_32(v, rec, lane);
@@ -145,7 +152,7 @@ tsvd_fp6_panel_kernel(gemm_args p, split_x xs) {
     for (int q = wave; q < blocks * TN; q += 8) {
         const int blk = q / TN, tile = q - blk * TN;
         float v[32];
-        gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + tile, lane, v);
+        gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + tile, lane, v, record(blk, tile));
         if constexpr (X == 2) tsvd_planes_of_32_twice(v, record(blk, tile), record(blk + blocks, tile), lane);
         else tsvd_planes_of_32(v, record(blk, tile), lane);
     }
@@ -499,7 +506,7 @@ tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x
 #pragma unroll
             for (int b = 0; b < TN; ++b) {
                 float v[32];
-                gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + b, lane, v);
+                gather_x<X == 2>(xs.x, xs.ld, xs.token_major != 0, xs.N, p.bvalid, blk, (b0 >> 4) + b, lane, v, smem + kg * 4096);
                 auto put = [&](int pl, u32x4 l, u32x2 h) { lo[0][pl] = l, hi[0][pl] = h; };
                 const std::integral_constant<int, 0> slot{};
                 sc[0] = tsvd_planes_of_32<X == 2>(v, put);
@@ -549,6 +556,8 @@ tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x
             if constexpr (DEPTH == 3) block(blk + 2 * KG, d2);
         }
     }
+
+    if (X == 1 && !xs.token_major) __syncthreads();           // (x passed through where the sums meet)
 
     // ---- the partial sums: result block f = 8 tile + row block; wavefront q finishes blocks q NF .. + NF - 1
     f32x4 fin[NF];
@@ -688,12 +697,14 @@ hipError_t tsvd_fp6_split_launch(int shape, bool stage2, const gemm_args& a, int
 // Two steps of 16 records hold all of x of a token tile.
 bool tsvd_fp6_split_makes_x(int shape, int blocks) { return shape != 0 && blocks * (shape & 7) <= 32; }
 hipError_t tsvd_fp6_split_launch_x(int shape, const gemm_args& a, const void* x, bool f32, bool token_major, long long ld, int N, hipStream_t stream) {
+    if (!f32 && !token_major && (N - 1) * ld + a.bvalid < 8) return hipErrorInvalidValue;
     const split_x xs = {x, ld, token_major, N};
     return launch_any(shape, false, a, 0, &xs, f32, stream);
 }
 
 hipError_t tsvd_fp6_split_planes(const void* x, bool f32, bool token_major, long long ld, int N, int B, int blocks, unsigned char* planes,
                                  hipStream_t stream) {
+    if (!f32 && !token_major && (N - 1) * ld + B < 8) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((B + 63) / 64), (unsigned)blocks), block(256);
     if (f32) hipLaunchKernelGGL(tsvd_planes_kernel<true>, grid, block, 0, stream, x, ld, (int)token_major, N, B, blocks, planes);
     else hipLaunchKernelGGL(tsvd_planes_kernel<false>, grid, block, 0, stream, x, ld, (int)token_major, N, B, blocks, planes);

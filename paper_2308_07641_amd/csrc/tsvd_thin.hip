@@ -53,6 +53,10 @@ struct thin_args {
 
 // THIN_CONV whose V takes rows of three taps side by side, of images of four columns and more: a row is one load of four elements.
 constexpr int THIN_CONV_ROWS = 3;
+// THIN_FEATURE_MAJOR in chunks of eight tokens, transposed in LDS (tsvd_request_columns), where a wavefront makes more than one record: 3712 x 1804 x 807 at 185 tokens
+// 18.3 -> 14.5 us, 2303 x 1152 x 577 at 439 15.7 -> 13.7, 1071 x 4096 x 177 at 1984 32.2 -> 28.2.  A single record is there sooner by element loads: 320 x 340 x 114 at
+// 123 tokens 6.3 against 6.5 us, 312 x 512 x 356 at 3367 9.0 against 9.2.
+constexpr int THIN_COLUMNS = 4;
 
 template <int TN, int RB, int SOURCE, bool CHUNKED>
 __global__ void __launch_bounds__(512, 2)
@@ -108,7 +112,8 @@ tsvd_thin_panel_kernel(thin_args p) {
                 for (int b = dy; b < 64; b += p.kv1) conv_outside |= 1ull << b;
         __syncthreads();
     }
-    auto make_record = [&](int block, int tile, unsigned char* rec) __attribute__((always_inline)) {
+    u32x4 chunks[4];                         // THIN_COLUMNS: what the next record is made of
+    auto make_record = [&](int block, int tile, unsigned char* rec, auto read) __attribute__((always_inline)) {
         int tok = min(b0 + 16 * tile + i, p.B - 1);
         const int k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1);
         asm volatile("" : "+v"(tok));                                // (what follows from it is formed here, not kept in registers over the MFMAs)
@@ -167,6 +172,8 @@ tsvd_thin_panel_kernel(thin_args p) {
             }
         } else if constexpr (SOURCE == THIN_TOKEN_MAJOR) {
             tsvd_gather_row(p.x + (size_t)tok * p.ldx, k0, p.N, block * 128 + 128 <= p.N, v);
+        } else if constexpr (SOURCE == THIN_COLUMNS) {
+            tsvd_columns_of(chunks, p.ldx, p.N, p.B, block, b0 + 16 * tile, lane, rec, v);     // (through the record's own place)
         } else {
 #pragma unroll
             for (int e = 0; e < 32; ++e) {
@@ -178,6 +185,7 @@ tsvd_thin_panel_kernel(thin_args p) {
 #pragma unroll
             for (int e = 0; e < 32; ++e) v[e] = __uint_as_float((uint32_t)raw[e] << 16);
         }
+        read();                                              // (what the record is made of is in registers)
         tsvd_planes_of_32(v, rec, lane);
     };
 
@@ -268,6 +276,15 @@ tsvd_thin_panel_kernel(thin_args p) {
                 nb = 0;
             }
         };
+        // Blocks first, first + step, ... below end of the chunk at c0.  (THIN_COLUMNS: a record's chunks are requested before the one ahead of it is made: its
+        // conversion takes about as long as the trip.)
+        auto records = [&](int c0, int first, int step, int end, int tile, unsigned char* rec) __attribute__((always_inline)) {
+            auto request = [&](int q) { tsvd_request_columns(p.x, p.ldx, p.N, p.B, c0 + q, b0 + 16 * tile, lane, chunks); };
+            if (SOURCE == THIN_COLUMNS && first < end) request(first);
+            for (int q = first; q < end; q += step) make_record(c0 + q, tile, rec + (q * TN + tile) * FP6_REC_BYTES, [&] {
+                if (SOURCE == THIN_COLUMNS && q + step < end) request(q + step);
+            });
+        };
         auto make = [&](int c0) __attribute__((always_inline)) {
             const int blocks = min(p.chunk, p.nvb - c0);
             unsigned char* rec = xrec + (c0 / p.chunk & (p.buffers - 1)) * p.chunk * TN * FP6_REC_BYTES;
@@ -277,17 +294,16 @@ tsvd_thin_panel_kernel(thin_args p) {
             const int side = wave / TN, tile = wave % TN, busy = (p.nub % NW + TN - 1 - tile) / TN, idle = NW / TN - busy;
             if (CHUNKED && SOURCE != THIN_CONV && c0 > 0 && busy > 0 && idle > 0) {
                 each = min(blocks * TN / 5, blocks / idle);
-                if (side >= busy)
-                    for (int q = side - busy; q < idle * each; q += idle) make_record(c0 + q, tile, rec + (q * TN + tile) * FP6_REC_BYTES);
+                if (side >= busy) records(c0, side - busy, idle, idle * each, tile, rec);
             }
-            for (int q = idle * each + (each ? NW / TN - 1 - side : side); q < blocks; q += NW / TN) make_record(c0 + q, tile, rec + (q * TN + tile) * FP6_REC_BYTES);
+            records(c0, idle * each + (each ? NW / TN - 1 - side : side), NW / TN, blocks, tile, rec);
         };
         make(0);
         __syncthreads();
         auto chunks = [&](auto make_first) __attribute__((always_inline)) {
             for (int c0 = 0; c0 < p.nvb; c0 += p.chunk) {
                 const int blocks = min(p.chunk, p.nvb - c0);
-                const bool more = c0 + p.chunk < p.nvb;
+                const bool more = (CHUNKED || SOURCE == THIN_TOKEN_MAJOR) && c0 + p.chunk < p.nvb;       // (x as a whole: no code for more, but rows of tokens were 1.5 % slower without)
                 if (decltype(make_first)::value && more) make(c0 + p.chunk);
                 const unsigned char* rec = xrec + (c0 / p.chunk & (p.buffers - 1)) * p.chunk * TN * FP6_REC_BYTES;
                 words w0[8];                                  // (not kept over the making of records: the registers are needed there)
@@ -441,6 +457,7 @@ hipError_t launch(int source, const thin_args& a, int lds, hipStream_t stream) {
     if (source == THIN_CONV && a.kv2 == 3 && a.d2 == 1 && a.W >= 4) return launch<TN, RB, THIN_CONV_ROWS>(a, lds, stream);
     if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, lds, stream);
     if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, lds, stream);
+    if (a.nvb * TN > 8) return launch<TN, RB, THIN_COLUMNS>(a, lds, stream);
     return launch<TN, RB, THIN_FEATURE_MAJOR>(a, lds, stream);
 }
 template <int TN, int RB, int SOURCE>
@@ -455,6 +472,7 @@ template <int TN, int RB>
 hipError_t init() {
     hipError_t e;
     if ((e = init<TN, RB, THIN_FEATURE_MAJOR>()) != hipSuccess || (e = init<TN, RB, THIN_TOKEN_MAJOR>()) != hipSuccess) return e;
+    if ((e = init<TN, RB, THIN_COLUMNS>()) != hipSuccess) return e;
     if ((e = init<TN, RB, THIN_CONV>()) != hipSuccess) return e;
     return init<TN, RB, THIN_CONV_ROWS>();
 }
@@ -490,7 +508,7 @@ int tsvd_thin_chunk(long long K, long long N, int tiles, bool conv) {
 
 hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t stream) {
     const tsvd_blob_header& hd = *g.hd;
-    if (tsvd_thin_x_bytes(g) >= (1ull << 30) || (size_t)hd.Mp * hd.Kp / 4 >= (1ull << 31) || (size_t)hd.Kp * hd.Np / 4 >= (1ull << 31))
+    if ((g.source == THIN_FEATURE_MAJOR && tsvd_thin_x_bytes(g) < 16) || tsvd_thin_x_bytes(g) >= (1ull << 30) || (size_t)hd.Mp * hd.Kp / 4 >= (1ull << 31) || (size_t)hd.Kp * hd.Np / 4 >= (1ull << 31))
         return hipErrorNotSupported;
     thin_args a;
     a.tiles_v = reinterpret_cast<const uint32_t*>(g.blob + hd.off_V);

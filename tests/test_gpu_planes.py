@@ -278,3 +278,27 @@ def test_thin_panels_gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom,
     y = tsvd.tsvd_conv2d_forward(h, form, ci, co, k1, k2, xd, *geom)
     assert torch.equal(y.cpu(), torch.from_numpy(np.ascontiguousarray(ref.transpose(1, 0, 2, 3))).to(y.dtype))
     tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("switches", [{"TSVD_THIN": 1}, {"TSVD_THIN": 2}, {"TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 10}, {"TSVD_SPLIT_V": 10, "TSVD_SPLIT_U": 10, "TSVD_SPLIT_X": 1},
+                                      {"TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 9, "TSVD_SPLIT_X": 1}, {"TSVD_SPLIT_V": 20, "TSVD_SPLIT_U": 18, "TSVD_SPLIT_X": 1}], ids=str)
+@pytest.mark.parametrize("N,B,pad", [(1153, 17, 0), (1157, 23, 3), (1279, 33, 0), (1280, 40, 1), (129, 50, 0), (8, 17, 0), (1, 19, 5), (4097, 30, 2)])
+def test_columns_of_feature_major_x(tsvd, N, B, pad, switches):
+    """Feature-major bf16 x read in chunks of eight tokens: rows at odd elements, a last chunk that ends with x, features one beyond a block, the last rows of
+    a block, one row.  What stands beside the tokens is no number and reaches no result.  Exact."""
+    import torch
+    M, K = 70, 150
+    print(f"case columns {N} {B} {pad} {switches}", flush=True)
+    rng = np.random.default_rng(N + B)
+    U = rng.choice([-1, 0, 1], size=(M, K), p=[0.1, 0.8, 0.1]).astype(np.int8)
+    V = rng.choice([-1, 0, 1], size=(K, N), p=[0.05, 0.9, 0.05]).astype(np.int8)
+    S = rng.integers(-1, 2, size=K).astype(np.float32)
+    X = rng.integers(-1, 2, size=(N, B)).astype(np.float32)
+    h = tsvd.tsvd_pack(U, S, V)
+    for k, v in {"TSVD_MID": 0, "TSVD_PANEL": 0, **switches}.items():
+        tsvd.tsvd_tuning_set(k, v)
+    x = torch.full(((N - 1) * (B + pad) + B + 1,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    view = torch.as_strided(x, (N, B), (B + pad, 1), 1).copy_(torch.from_numpy(X))
+    y = tsvd.tsvd_forward(h, view)
+    assert np.array_equal(y.cpu().numpy(), oracle.forward(U, S, V, X).astype(np.float32))
+    tsvd.tsvd_free(h)
