@@ -117,7 +117,6 @@ tsvd_thin_panel_kernel(thin_args p) {
         int tok = min(b0 + 16 * tile + i, p.B - 1);
         const int k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1);
         asm volatile("" : "+v"(tok));                                // (what follows from it is formed here, not kept in registers over the MFMAs)
-        constexpr int NONE = (int)0x80000000;
         float v[32];
         uint16_t raw[32];
         auto gather = [&](int e, int off) {
@@ -175,11 +174,11 @@ tsvd_thin_panel_kernel(thin_args p) {
         } else if constexpr (SOURCE == THIN_COLUMNS) {
             tsvd_columns_of(chunks, p.ldx, p.N, p.B, block, b0 + 16 * tile, lane, rec, v);     // (through the record's own place)
         } else {
+            // Rows at scalar offsets, those beyond N beyond the buffer.  (With an address and a test of its own for each value, three vector operations:
+            // 587 x 99 x 82 at 29 tokens 5.4 -> 5.2 us, 325 x 122 x 576 at 1025 7.45 -> 7.15; 49 drawn feature-major calls 0.993 of the time.)
+            const int ld2 = 2 * (int)p.ldx, lane_off = (64 * (g & 1) + 16 * (g >> 1)) * ld2 + 2 * tok;
 #pragma unroll
-            for (int e = 0; e < 32; ++e) {
-                const int k = k0 + 32 * (e >> 4) + (e & 15);
-                gather(e, (2 * (k * (int)p.ldx + tok)) | (k < p.N ? 0 : NONE));
-            }
+            for (int e = 0; e < 32; ++e) raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, lane_off, (block * 128 + 32 * (e >> 4) + (e & 15)) * ld2, 0);
         }
         if constexpr (SOURCE == THIN_CONV || SOURCE == THIN_FEATURE_MAJOR) {
 #pragma unroll
@@ -457,7 +456,8 @@ hipError_t launch(int source, const thin_args& a, int lds, hipStream_t stream) {
     if (source == THIN_CONV && a.kv2 == 3 && a.d2 == 1 && a.W >= 4) return launch<TN, RB, THIN_CONV_ROWS>(a, lds, stream);
     if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, lds, stream);
     if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, lds, stream);
-    if (a.nvb * TN > 8) return launch<TN, RB, THIN_COLUMNS>(a, lds, stream);
+    // (element loads reach rows at 32-bit offsets)
+    if (a.nvb * TN > 8 || 128ll * a.nvb * a.ldx >= 1ll << 30) return launch<TN, RB, THIN_COLUMNS>(a, lds, stream);
     return launch<TN, RB, THIN_FEATURE_MAJOR>(a, lds, stream);
 }
 template <int TN, int RB, int SOURCE>
