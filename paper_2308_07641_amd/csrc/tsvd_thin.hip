@@ -20,7 +20,7 @@
 // address unit's requests bound the gather (3 x 3: 256 x 2304 x 116 at 14896 positions 52.4 -> 42.6 us, 89 x 1683 x 78 at 3920 19.1 -> 14.8, 128 x 621 x 412 at 27440
 // 56.8 -> 46.7; 60 drawn convolutions, 25 of them with such rows, 0.946 of the time).
 // Measured on MI355X: 3072 x 768 x 1545 bf16 at 3152 tokens, token-major: 71.5 -> 39.2 us (ring kernels with a copy of x before; 16 tokens per panel); the
-// map of a 3 x 3 convolution, 256 x 2304 x 768 at 6272 positions: 75.5 -> 36.8 us (columns written and read before; 32).
+// map of a 3 x 3 convolution, 256 x 2304 x 768 at 6272 positions: 75.5 -> 34.3 us (columns written and read before; 32).
 // What bounds them: the matrix instructions of the panels' last round, and the code words that every workgroup pulls from its L2.  By
 // counters the matrix pipes are busy 0.43 of the compute units' cycles in the first and 0.28 in the second (which has 196 panels, and six rank blocks
 // in stage V for eight wavefronts).
