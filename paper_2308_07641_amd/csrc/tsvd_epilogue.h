@@ -5,6 +5,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// The scalar offset of an access to a buffer of `bytes` bytes.  The range check compares the vector offset with what the scalar offset leaves of the buffer, so
+// it holds for scalar offsets up to the end: rows behind that (of x beyond N, of y beyond M) are put at the end, where every vector offset is outside.
+__device__ __forceinline__ int tsvd_buffer_offset(int offset, uint32_t bytes) { return (int)min((uint32_t)offset, bytes); }
+
 // fp32 -> bf16 bit pattern, round to nearest even (NaN stays NaN).
 __device__ __forceinline__ uint16_t tsvd_bf16_rne(float v) {
     const uint32_t u = __float_as_uint(v);

@@ -397,7 +397,7 @@ tsvd_panel_fp6_kernel(panel_args p) {
             const int voff = (64 * (g & 1) + 16 * (g >> 1)) * ld2 + (b0 + 16 * b + i) * 2;
 #pragma unroll
             for (int e = 0; e < 32; ++e)
-                raw[e] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x_rsrc, voff, (nb * 128 + 32 * (e >> 4) + (e & 15)) * ld2, 0);
+                raw[e] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x_rsrc, voff, tsvd_buffer_offset((nb * 128 + 32 * (e >> 4) + (e & 15)) * ld2, p.x_bytes), 0);
         };
         if constexpr (ROWS) {
             // a lane's two runs of 16 indices are contiguous, nothing to transpose

@@ -227,7 +227,7 @@ tsvd_gemm_kernel(gemm_args p) {
     auto load_x = [&](int stage) {
         const int k0 = stage_k0(stage);
         if constexpr (FAST) {
-            const int soff = k0 * (int)p.ld * 2;
+            const int soff = tsvd_buffer_offset(k0 * (int)p.ld * 2, p.act_bytes);
 #pragma unroll
             for (int c = 0; c < CPT; ++c) xreg[c] = buf_load128(act_rsrc, x_voff[c], soff);
         } else {
@@ -376,7 +376,7 @@ tsvd_gemm_pipe_kernel(gemm_args p) {
         for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     auto issue_x = [&](int stage, int buf) {
-        const int soff = (256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2;
+        const int soff = tsvd_buffer_offset((256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2, p.act_bytes);
 #pragma unroll
         for (int c = 0; c < SPW; ++c)
             buf_load128_to_lds(act_rsrc, lds0 + buf * STAGE_BYTES + c * NW * 1024, x_voff[c], soff);
@@ -613,7 +613,7 @@ tsvd_gemm_ring_kernel(gemm_args p) {
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
                 const int stage = 2 * pair + st;
-                const int soff = (256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2;
+                const int soff = tsvd_buffer_offset((256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2, p.act_bytes);
 #pragma unroll
                 for (int c = 0; c < SPW; ++c)
                     if (part < 0 || (((s * 2 + st) * SPW + c) & 3) == part)
@@ -933,7 +933,7 @@ tsvd_panel_kernel(panel_args p) {
         typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
         const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_ptr)zl + piece * 1024;
         auto issue_x = [&](int stage, int buf) {
-            const int soff = (256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ldx * 2;
+            const int soff = tsvd_buffer_offset((256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ldx * 2, p.x_bytes);
             buf_load128_to_lds(act_rsrc, lds0 + buf * STAGE_BYTES, x_voff, soff);
         };
         auto load_w = [&](int pair, u32x2 (&w)[TM]) {

@@ -138,7 +138,7 @@ tsvd_mid_kernel(tsvd_mid_args p) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if constexpr (VEC) {
-                xr[j] = __builtin_amdgcn_raw_buffer_load_b128(act_rsrc, x_voff, (s * 2048 + 512 * j) * (int)p.ld * 2, 0);
+                xr[j] = __builtin_amdgcn_raw_buffer_load_b128(act_rsrc, x_voff, tsvd_buffer_offset((s * 2048 + 512 * j) * (int)p.ld * 2, p.act_bytes), 0);
             } else {
                 // unconditional loads (a load under a divergent condition makes the compiler wait for
                 // it, and for the weight tiles in flight, right there), and none at all for token

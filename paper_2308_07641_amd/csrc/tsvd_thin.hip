@@ -178,7 +178,7 @@ tsvd_thin_panel_kernel(thin_args p) {
             // 587 x 99 x 82 at 29 tokens 5.4 -> 5.2 us, 325 x 122 x 576 at 1025 7.45 -> 7.15; 49 drawn feature-major calls 0.993 of the time.)
             const int ld2 = 2 * (int)p.ldx, lane_off = (64 * (g & 1) + 16 * (g >> 1)) * ld2 + 2 * tok;
 #pragma unroll
-            for (int e = 0; e < 32; ++e) raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, lane_off, (block * 128 + 32 * (e >> 4) + (e & 15)) * ld2, 0);
+            for (int e = 0; e < 32; ++e) raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, lane_off, tsvd_buffer_offset((block * 128 + 32 * (e >> 4) + (e & 15)) * ld2, p.x_bytes), 0);
         }
         if constexpr (SOURCE == THIN_CONV || SOURCE == THIN_FEATURE_MAJOR) {
 #pragma unroll

@@ -285,7 +285,7 @@ def test_thin_panels_gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom,
 @pytest.mark.parametrize("N,B,pad", [(1153, 17, 0), (1157, 23, 3), (1279, 33, 0), (1280, 40, 1), (129, 50, 0), (8, 17, 0), (1, 19, 5), (4097, 30, 2)])
 def test_columns_of_feature_major_x(tsvd, N, B, pad, switches):
     """Feature-major bf16 x read in chunks of eight tokens: rows at odd elements, a last chunk that ends with x, features one beyond a block, the last rows of
-    a block, one row.  What stands beside the tokens is no number and reaches no result.  Exact."""
+    a block, one row.  What stands beside the tokens, and behind x where the rows of a whole block would be, is no number and reaches no result.  Exact."""
     import torch
     M, K = 70, 150
     print(f"case columns {N} {B} {pad} {switches}", flush=True)
@@ -297,7 +297,7 @@ def test_columns_of_feature_major_x(tsvd, N, B, pad, switches):
     h = tsvd.tsvd_pack(U, S, V)
     for k, v in {"TSVD_MID": 0, "TSVD_PANEL": 0, **switches}.items():
         tsvd.tsvd_tuning_set(k, v)
-    x = torch.full(((N - 1) * (B + pad) + B + 1,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    x = torch.full(((N + 256) * (B + pad) + B + 1,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
     view = torch.as_strided(x, (N, B), (B + pad, 1), 1).copy_(torch.from_numpy(X))
     y = tsvd.tsvd_forward(h, view)
     assert np.array_equal(y.cpu().numpy(), oracle.forward(U, S, V, X).astype(np.float32))

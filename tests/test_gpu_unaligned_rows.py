@@ -99,6 +99,29 @@ def test_what_lies_behind_y_stays(tsvd, M, N, K, B, route):  # noqa: F811
     tsvd.tsvd_free(h)
 
 
+@pytest.mark.parametrize("M,N,K,B", [(66, 8, 70, 40), (40, 1, 60, 33), (257, 251, 200, 136), (70, 129, 60, 24), (520, 64, 300, 16), (300, 100, 80, 1)])
+@pytest.mark.parametrize("route", ROUTES + MORE_ROUTES, ids=str)
+def test_what_lies_behind_x_reaches_nothing(tsvd, M, N, K, B, route):  # noqa: F811
+    """Features of a block beyond x's last row are not read: no number stands there in memory, for more rows than any kernel takes at a time.  Exact."""
+    import torch
+    i = workloads.make_integer_inputs(M, N, K, B, 0.5, "bf16", seed=M + N + K + B)
+    ref = oracle.forward(i.U, i.S, i.V, i.X)
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    for k, v in route.items():
+        tsvd.tsvd_tuning_set(k, v)
+    x = to_device(i)
+    print(f"case behind x {M} {N} {K} {B} {route}", flush=True)
+    for ld in (B, B + 8 - B % 8):                 # the last one aligned
+        held = torch.full(((N + 2304) * ld,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        view = torch.as_strided(held, (N, B), (ld, 1)).copy_(x)
+        assert np.array_equal(tsvd.tsvd_forward(h, view).cpu().numpy(), ref)
+    held = torch.full(((B + 256) * N,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    held[:B * N] = x.t().flatten()
+    y = tsvd.tsvd_forward_io(h, held[:B * N].view(B, N), x_layout=tsvd.TSVD_TOKEN_MAJOR, y_layout=tsvd.TSVD_TOKEN_MAJOR)
+    assert np.array_equal(y.cpu().numpy().T, ref)
+    tsvd.tsvd_free(h)
+
+
 @pytest.mark.parametrize("form,co,k,groups", [(0, 33, 3, 1), (1, 21, 3, 1), (2, 40, 3, 1), (3, 9, 5, 1), (0, 12, 5, 12)])
 @pytest.mark.parametrize("tiles", [0, 1, 2])
 def test_what_lies_behind_a_convolution_stays(tsvd, form, co, k, groups, tiles):  # noqa: F811
