@@ -262,6 +262,7 @@ tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_
     float* ones = reinterpret_cast<float*>(smem + 8 * STEP_BYTES);
     int* ready = reinterpret_cast<int*>(ones + 16 * TN);
     const split_tile tile = tile_of<PLACED>(extra);
+    if (PLACED && !tile.exists) return;                      // (before the first request: there are no codes or records at such a tile's place)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rw = wave % RW, kg = wave / RW, i = lane & 15, g = lane >> 4;
     const int b0 = tile.token * 16 * TN, strip0 = (tile.row * RW + rw) * TM;
@@ -365,7 +366,6 @@ tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_
 
     u32x2 wa[BPS][TM], wb[BPS][TM];
     load_w(min(from, nsteps - 1), wa);
-    if (PLACED && !tile.exists) return;
     if (count > 0) issue(from, 0);
     __syncthreads();                                         // (the words are zero)
     for (int s = 0; s < count; s += 2) {
@@ -443,6 +443,7 @@ tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x
     split_x xs = {};
     if constexpr (!PLACED) xs = extra;
     const split_tile tile = tile_of<PLACED>(extra);
+    if (PLACED && !tile.exists) return;                      // (before the first request: there are no codes or records at such a tile's place)
     constexpr int KG = 8, TM = 8, DEPTH = TN == 1 ? 3 : 2;
     constexpr bool DIRECT = !STAGE2;
     constexpr int NQ = DIRECT ? TN : KG, NF = 8 * TN / NQ;
@@ -549,7 +550,6 @@ tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x
         ask(kg, d0);
         ask(kg + KG, d1);
         if constexpr (DEPTH == 3) ask(kg + 2 * KG, d2);
-        if (PLACED && !tile.exists) return;
         for (int blk = kg; blk < nrun; blk += KG * DEPTH) {
             block(blk, d0);
             block(blk + KG, d1);
