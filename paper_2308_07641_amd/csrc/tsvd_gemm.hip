@@ -1478,8 +1478,12 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
         unsigned char* zplanes = xplanes + ((xp_bytes + 255) & ~(size_t)255);
         const int mask = tsvd_stage_mask();
         hipError_t e = hipSuccess;
-        const bool own_x = tsvd_fp6_split_makes_x(g.split_v, sets * pairs_n) && env_cfg("TSVD_SPLIT_X", 1) != 0;
-        if ((mask & 1) && !own_x)
+        // (feature-major bf16 is read in chunks of eight values; fewer in all: by the pass that reads pairs)
+        const bool no_chunk = !g.x_f32 && !g.x_token_major && (hd.N - 1) * g.ldx + g.B < 8;
+        const bool own_x = !no_chunk && tsvd_fp6_split_makes_x(g.split_v, sets * pairs_n) && env_cfg("TSVD_SPLIT_X", 1) != 0;
+        if ((mask & 1) && no_chunk)
+            if ((e = tsvd_fp6_launch_planes(true, static_cast<const uint16_t*>(g.x), (long long)g.ldx, (int)hd.N, (int)g.B, pairs_n, pairs_n, g.B, xplanes, stream)) != hipSuccess) return e;
+        if ((mask & 1) && !no_chunk && !own_x)
             if ((e = tsvd_fp6_split_planes(g.x, g.x_f32 != 0, g.x_token_major != 0, g.ldx, (int)hd.N, (int)g.B, pairs_n, xplanes, stream)) != hipSuccess) return e;
         if (mask & 2) {
             gemm_args a4 = a1;

@@ -302,3 +302,20 @@ def test_columns_of_feature_major_x(tsvd, N, B, pad, switches):
     y = tsvd.tsvd_forward(h, view)
     assert np.array_equal(y.cpu().numpy(), oracle.forward(U, S, V, X).astype(np.float32))
     tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("v,u,own_x", [(9, 9, 1), (10, 10, 1), (10, 18, 0), (20, 20, 1)])
+@pytest.mark.parametrize("N,B,ld", [(1, 2, 2), (1, 7, 7), (2, 3, 4), (3, 2, 2), (1, 3, 4000), (1, 8, 8), (2, 4, 4), (4, 2, 2)])
+def test_split_tiles_of_fewer_values_than_a_chunk(tsvd, N, B, ld, v, u, own_x):
+    """Feature-major bf16 x of fewer than the eight values that the split tiles read at a time, and of eight.  Exact."""
+    import torch
+    M, K = 40, 70
+    print(f"case fewer than a chunk {N} {B} {ld} {v} {u} {own_x}", flush=True)
+    i = workloads.make_integer_inputs(M, N, K, B, 0.3, "bf16", seed=N + B)
+    h = tsvd.tsvd_pack(i.U, i.S, i.V)
+    for name, value in {"TSVD_GEMM_MIN_B": 2, "TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_SPLIT_V": v, "TSVD_SPLIT_U": u, "TSVD_SPLIT_X": own_x, "TSVD_REALIGN": 0}.items():
+        tsvd.tsvd_tuning_set(name, value)
+    held = torch.full(((N - 1) * ld + B + 64,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    x = torch.as_strided(held, (N, B), (ld, 1)).copy_(to_device(i))
+    assert np.array_equal(tsvd.tsvd_forward(h, x).cpu().numpy(), oracle.forward(i.U, i.S, i.V, i.X))
+    tsvd.tsvd_free(h)
