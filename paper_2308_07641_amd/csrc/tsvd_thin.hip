@@ -53,10 +53,6 @@ struct thin_args {
 
 // THIN_CONV whose V takes rows of three taps side by side, of images of four columns and more: a row is one load of four elements.
 constexpr int THIN_CONV_ROWS = 3;
-// THIN_FEATURE_MAJOR in chunks of eight tokens, transposed in LDS (tsvd_request_columns), where a wavefront makes more than one record: 3712 x 1804 x 807 at 185 tokens
-// 18.3 -> 14.5 us, 2303 x 1152 x 577 at 439 15.7 -> 13.7, 1071 x 4096 x 177 at 1984 32.2 -> 28.2.  A single record is there sooner by element loads: 320 x 340 x 114 at
-// 123 tokens 6.3 against 6.5 us, 312 x 512 x 356 at 3367 9.0 against 9.2.
-constexpr int THIN_COLUMNS = 4;
 
 template <int TN, int RB, int SOURCE, bool CHUNKED>
 __global__ void __launch_bounds__(512, 2)
@@ -112,8 +108,7 @@ tsvd_thin_panel_kernel(thin_args p) {
                 for (int b = dy; b < 64; b += p.kv1) conv_outside |= 1ull << b;
         __syncthreads();
     }
-    u32x4 chunks[4];                         // THIN_COLUMNS: what the next record is made of
-    auto make_record = [&](int block, int tile, unsigned char* rec, auto read) __attribute__((always_inline)) {
+    auto make_record = [&](int block, int tile, unsigned char* rec) __attribute__((always_inline)) {
         int tok = min(b0 + 16 * tile + i, p.B - 1);
         const int k0 = block * 128 + 64 * (g & 1) + 16 * (g >> 1);
         asm volatile("" : "+v"(tok));                                // (what follows from it is formed here, not kept in registers over the MFMAs)
@@ -171,20 +166,23 @@ tsvd_thin_panel_kernel(thin_args p) {
             }
         } else if constexpr (SOURCE == THIN_TOKEN_MAJOR) {
             tsvd_gather_row(p.x + (size_t)tok * p.ldx, k0, p.N, block * 128 + 128 <= p.N, v);
-        } else if constexpr (SOURCE == THIN_COLUMNS) {
-            tsvd_columns_of(chunks, p.ldx, p.N, p.B, block, b0 + 16 * tile, lane, rec, v);     // (through the record's own place)
         } else {
-            // Rows at scalar offsets, those beyond N beyond the buffer.  (With an address and a test of its own for each value, three vector operations:
-            // 587 x 99 x 82 at 29 tokens 5.4 -> 5.2 us, 325 x 122 x 576 at 1025 7.45 -> 7.15; 49 drawn feature-major calls 0.993 of the time.)
-            const int ld2 = 2 * (int)p.ldx, lane_off = (64 * (g & 1) + 16 * (g >> 1)) * ld2 + 2 * tok;
+            // Rows at scalar offsets, those beyond N at the buffer's end: 587 x 99 x 82 at 29 tokens 5.4 -> 5.2 us against an address and a test for each value.
+            // They are formed here: the compiler kept the products of all 32 rows in scalar registers over the whole kernel, of which it has 102, and spilled up to 94
+            // of others in panels of several chunks (576 x 640 x 356 at 7947 tokens 15.8 -> 14.9 us, 2164 x 1579 x 428 at 9285 61.7 -> 60.5, 896 x 1203 x 913 at 6592 30.5 -> 29.9).
+            // Chunks of eight tokens, transposed in LDS, as the split tiles read them, are of no use here since: 192 x 4961 x 82 at 7561 40.8 against 34.5 us, 384 x 1535 x 218 at 845 11.6
+            // against 10.8; on 51 feature-major calls 0.98 of the time without, two of them longer (916 x 4224 x 448 at 589 19.1 -> 19.5, 233 x 5661 x 881 at 261 19.1 -> 19.3).
+            int ld2 = 2 * (int)p.ldx;
+            asm volatile("" : "+s"(ld2));
+            const int lane_off = (64 * (g & 1) + 16 * (g >> 1)) * ld2 + 2 * tok;
 #pragma unroll
-            for (int e = 0; e < 32; ++e) raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, lane_off, tsvd_buffer_offset((block * 128 + 32 * (e >> 4) + (e & 15)) * ld2, p.x_bytes), 0);
+            for (int e = 0; e < 32; ++e)
+                raw[e] = __builtin_amdgcn_raw_buffer_load_b16(x_rsrc, lane_off, tsvd_buffer_offset((block * 128 + 32 * (e >> 4) + (e & 15)) * ld2, p.x_bytes), 0);
         }
         if constexpr (SOURCE == THIN_CONV || SOURCE == THIN_FEATURE_MAJOR) {
 #pragma unroll
             for (int e = 0; e < 32; ++e) v[e] = __uint_as_float((uint32_t)raw[e] << 16);
         }
-        read();                                              // (what the record is made of is in registers)
         tsvd_planes_of_32(v, rec, lane);
     };
 
@@ -275,27 +273,24 @@ tsvd_thin_panel_kernel(thin_args p) {
                 nb = 0;
             }
         };
-        // Blocks first, first + step, ... below end of the chunk at c0.  (THIN_COLUMNS: a record's chunks are requested before the one ahead of it is made: its
-        // conversion takes about as long as the trip.)
-        auto records = [&](int c0, int first, int step, int end, int tile, unsigned char* rec) __attribute__((always_inline)) {
-            auto request = [&](int q) { tsvd_request_columns(p.x, p.ldx, p.N, p.B, c0 + q, b0 + 16 * tile, lane, chunks); };
-            if (SOURCE == THIN_COLUMNS && first < end) request(first);
-            for (int q = first; q < end; q += step) make_record(c0 + q, tile, rec + (q * TN + tile) * FP6_REC_BYTES, [&] {
-                if (SOURCE == THIN_COLUMNS && q + step < end) request(q + step);
-            });
-        };
         auto make = [&](int c0) __attribute__((always_inline)) {
             const int blocks = min(p.chunk, p.nvb - c0);
             unsigned char* rec = xrec + (c0 / p.chunk & (p.buffers - 1)) * p.chunk * TN * FP6_REC_BYTES;
             // Beside the multiplication of a chunk: wavefronts of fewer rank blocks first make as many records as take its time, a fifth of them, then all
             // in turn.  (Records of a convolution's single elements are bound by the address unit, whoever makes them: 315 -> 320 us with this on 228 x 12800 x 388.)
-            int each = 0;
-            const int side = wave / TN, tile = wave % TN, busy = (p.nub % NW + TN - 1 - tile) / TN, idle = NW / TN - busy;
-            if (CHUNKED && SOURCE != THIN_CONV && c0 > 0 && busy > 0 && idle > 0) {
-                each = min(blocks * TN / 5, blocks / idle);
-                if (side >= busy) records(c0, side - busy, idle, idle * each, tile, rec);
+            constexpr int SIDES = NW / TN;
+            const int side = wave / TN, tile = wave % TN, busy = (p.nub % NW + TN - 1 - tile) / TN, idle = SIDES - busy;
+            const int own = CHUNKED && SOURCE != THIN_CONV && c0 > 0 && busy > 0 && idle > 0 ? idle * min(blocks * TN / 5, blocks / idle) : 0;
+            const int rest = own + (own ? SIDES - 1 - side : side);
+            bool first = own > 0 && side >= busy;
+            for (int q = first ? side - busy : rest; q < blocks;) {
+                make_record(c0 + q, tile, rec + (q * TN + tile) * FP6_REC_BYTES);
+                q += first ? idle : SIDES;
+                if (first && q >= own) {
+                    first = false;
+                    q = rest;
+                }
             }
-            records(c0, idle * each + (each ? NW / TN - 1 - side : side), NW / TN, blocks, tile, rec);
         };
         make(0);
         __syncthreads();
@@ -456,8 +451,6 @@ hipError_t launch(int source, const thin_args& a, int lds, hipStream_t stream) {
     if (source == THIN_CONV && a.kv2 == 3 && a.d2 == 1 && a.W >= 4) return launch<TN, RB, THIN_CONV_ROWS>(a, lds, stream);
     if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, lds, stream);
     if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, lds, stream);
-    // (element loads reach rows at 32-bit offsets)
-    if (a.nvb * TN > 8 || 128ll * a.nvb * a.ldx >= 1ll << 30) return launch<TN, RB, THIN_COLUMNS>(a, lds, stream);
     return launch<TN, RB, THIN_FEATURE_MAJOR>(a, lds, stream);
 }
 template <int TN, int RB, int SOURCE>
@@ -472,7 +465,6 @@ template <int TN, int RB>
 hipError_t init() {
     hipError_t e;
     if ((e = init<TN, RB, THIN_FEATURE_MAJOR>()) != hipSuccess || (e = init<TN, RB, THIN_TOKEN_MAJOR>()) != hipSuccess) return e;
-    if ((e = init<TN, RB, THIN_COLUMNS>()) != hipSuccess) return e;
     if ((e = init<TN, RB, THIN_CONV>()) != hipSuccess) return e;
     return init<TN, RB, THIN_CONV_ROWS>();
 }
@@ -508,7 +500,7 @@ int tsvd_thin_chunk(long long K, long long N, int tiles, bool conv) {
 
 hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t stream) {
     const tsvd_blob_header& hd = *g.hd;
-    if ((g.source == THIN_FEATURE_MAJOR && tsvd_thin_x_bytes(g) < 16) || tsvd_thin_x_bytes(g) >= (1ull << 30) || (size_t)hd.Mp * hd.Kp / 4 >= (1ull << 31) || (size_t)hd.Kp * hd.Np / 4 >= (1ull << 31))
+    if (tsvd_thin_x_bytes(g) >= (1ull << 30) || (size_t)hd.Mp * hd.Kp / 4 >= (1ull << 31) || (size_t)hd.Kp * hd.Np / 4 >= (1ull << 31))
         return hipErrorNotSupported;
     thin_args a;
     a.tiles_v = reinterpret_cast<const uint32_t*>(g.blob + hd.off_V);
@@ -523,7 +515,7 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
     a.x_bytes = (unsigned)tsvd_thin_x_bytes(g);
     a.N = (int)hd.N;
     a.B = (int)g.B;
-    a.ldx = g.ldx;
+    a.ldx = g.source == THIN_FEATURE_MAJOR && hd.N == 1 ? g.B : g.ldx;       // (a single row: its distance to the next is any number)
     a.images = g.images; a.H = g.H; a.W = g.W; a.kv1 = g.kv1; a.kv2 = g.kv2; a.Hv = g.Hv; a.Wv = g.Wv;
     a.s1 = g.s1; a.s2 = g.s2; a.p1 = g.p1; a.p2 = g.p2; a.d1 = g.d1; a.d2 = g.d2;
     a.S = reinterpret_cast<const float*>(g.blob + hd.off_S);
@@ -554,6 +546,7 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
         if (best == 2) break;
     }
     const bool conv = g.source == THIN_CONV;
+    if (g.source == THIN_FEATURE_MAJOR && 128ll * a.nvb * a.ldx >= 1ll << 30) return hipErrorNotSupported;     // (element loads reach rows, those beyond N too, at 32-bit offsets)
     if (conv && g.kv1 * g.kv2 > MAX_TAPS) return hipErrorNotSupported;
     a.chunk = tsvd_thin_chunk(hd.K, hd.N, tiles, conv);
     if (a.chunk == 0) return hipErrorNotSupported;
