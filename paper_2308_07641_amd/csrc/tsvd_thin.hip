@@ -63,8 +63,11 @@ tsvd_thin_panel_kernel(thin_args p) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
     // workgroups go to the eight XCDs in turn; with p.runs each XCD takes a run of neighbouring panels, so that the lines that
     // panels share (32 or 64 bytes of a feature-major row each) are fetched into one L2
-    const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, more = gridDim.x & 7;
-    const int b0 = (p.runs ? xcd * per + min(xcd, more) + (blockIdx.x >> 3) : blockIdx.x) * 16 * TN;
+    // (the workgroups of a panel lie a round of panels apart.  As a second dimension of the grid they cost launches without any 0.1 us: 512 x 128 x 97, rows of
+    // tokens, at 4166 8.82 -> 8.91, now 8.71)
+    const int panels = (p.B + 16 * TN - 1) / (16 * TN), slice = p.slices > 1 ? (int)blockIdx.x / panels : 0, panel = blockIdx.x - slice * panels;
+    const int xcd = panel & 7, per = panels >> 3, more = panels & 7;
+    const int b0 = (p.runs ? xcd * per + min(xcd, more) + (panel >> 3) : panel) * 16 * TN;
     unsigned char* xrec = smem;
     unsigned char* zrec = smem + p.buffers * p.chunk * TN * FP6_REC_BYTES;
     const int* ktab = reinterpret_cast<const int*>(zrec + p.nub * TN * FP6_REC_BYTES);   // THIN_CONV: byte offset of index k in the images
@@ -297,7 +300,7 @@ tsvd_thin_panel_kernel(thin_args p) {
         auto chunks = [&](auto make_first) __attribute__((always_inline)) {
             for (int c0 = 0; c0 < p.nvb; c0 += p.chunk) {
                 const int blocks = min(p.chunk, p.nvb - c0);
-                const bool more = (CHUNKED || SOURCE == THIN_TOKEN_MAJOR) && c0 + p.chunk < p.nvb;       // (x as a whole: no code for more, but rows of tokens were 1.5 % slower without)
+                const bool more = CHUNKED && c0 + p.chunk < p.nvb;       // (x as a whole: no code for more)
                 if (decltype(make_first)::value && more) make(c0 + p.chunk);
                 const unsigned char* rec = xrec + (c0 / p.chunk & (p.buffers - 1)) * p.chunk * TN * FP6_REC_BYTES;
                 words w0[8];                                  // (not kept over the making of records: the registers are needed there)
@@ -336,7 +339,7 @@ tsvd_thin_panel_kernel(thin_args p) {
         constexpr int TM = decltype(tm_c)::value;
         const int units = (p.M + 16 * TM - 1) / (16 * TM);
         // units are dealt to the wavefronts of all slices of the panel
-        const int first = wave + NW * blockIdx.y, stride = NW * gridDim.y;
+        const int first = wave + NW * slice, stride = NW * p.slices;
         int nu = first, nb = 0;                               // the next fetch: unit, block
         const int last_unit = first + (units - 1 - first) / stride * stride;
         auto next = [&](words (&w)[TM]) {
@@ -441,7 +444,7 @@ template <int TN, int RB, int SOURCE, bool CHUNKED>
 auto kernel() { return tsvd_thin_panel_kernel<TN, RB, SOURCE, CHUNKED>; }
 template <int TN, int RB, int SOURCE>
 hipError_t launch(const thin_args& a, int lds, hipStream_t stream) {
-    const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN)), (unsigned)a.slices), block(512);
+    const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN)) * (unsigned)a.slices), block(512);
     if (a.buffers == 2) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true>()), grid, block, lds, stream, a);
     else hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false>()), grid, block, lds, stream, a);
     return hipGetLastError();
