@@ -60,6 +60,13 @@ tsvd_status tsvd_tuning_forward_stages(const tsvd_handle* h, const void* x_dev, 
  * -1 where the batched kernels are not used.  Returns 0 on success. */
 int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* shape_v, int* shape_u);
 
+/* Whether B tokens that take the single-token kernels run both stages in one launch (1) or in two (0). */
+int tsvd_tuning_one_launch(const tsvd_handle* h, long long B);
+
+/* Whether the split tiles that a call of B tokens takes (stage V, stage U) are dealt to the XCDs in groups.  Returns 0 on success, 1 where a
+ * call takes no split tiles. */
+int tsvd_tuning_tiles_by_xcd(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u);
+
 /* Copies the phase timestamps ([workgroups][16] 100 MHz ticks) of the last launch of a handle packed with
  * TSVD_CLOCKS = 1 to the host.  Returns 0 on success. */
 int tsvd_tuning_read_clocks(const tsvd_handle* h, long long* out, int workgroups);

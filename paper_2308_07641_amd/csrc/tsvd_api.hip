@@ -164,6 +164,16 @@ int pow2_floor(int64_t v) {
     return r;
 }
 
+// What decides whether tokens side by side run in one launch (tsvd_gemv_fused_fits), the rest zero.
+tsvd_gemv_fused_args gemv_fused_sizes(const tsvd_blob_header& hd, int tokens) {
+    tsvd_gemv_fused_args f;
+    std::memset(&f, 0, sizeof f);
+    f.strips_v = (int)((hd.K + 127) / 128 * 8); f.nkt_v = (int)(hd.Np / 256);
+    f.strips_u = (int)((hd.M + 15) / 16); f.nkt_u = (int)(hd.Kp / 256);
+    f.N = (int)hd.N; f.Np = (int)hd.Np; f.Kp = (int)hd.Kp; f.M = (int)hd.M;
+    f.tokens = tokens;
+    return f;
+}
 // One token through the tsvd_gemv kernels; returns false if the shape does not fit them.
 // tokens: each on workgroups of its own, x_token and y_token elements from one to the next
 bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t ldx, int tokens, int64_t x_token, void* y, int64_t ldy,
@@ -175,14 +185,12 @@ bool try_gemv(const tsvd_handle* h, const void* x, tsvd_dtype x_dtype, int64_t l
     const bool vec = ldx == 1 && hd.N % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (tokens == 1 || x_token % 4 == 0);
     if (mask == 7 && !h->dense_u && env_int("TSVD_GEMV_FUSED", 1) != 0) {
         // a small V: both stages in one launch
-        tsvd_gemv_fused_args f;
-        std::memset(&f, 0, sizeof f);
-        f.tiles_v = h->blob + hd.off_V; f.strips_v = (int)((hd.K + 127) / 128 * 8); f.nkt_v = (int)(hd.Np / 256);
-        f.tiles_u = h->blob + hd.off_U; f.strips_u = (int)((hd.M + 15) / 16); f.nkt_u = (int)(hd.Kp / 256);
-        f.N = (int)hd.N; f.Np = (int)hd.Np; f.Kp = (int)hd.Kp; f.M = (int)hd.M;
+        tsvd_gemv_fused_args f = gemv_fused_sizes(hd, tokens);
+        f.tiles_v = h->blob + hd.off_V;
+        f.tiles_u = h->blob + hd.off_U;
         f.x = x; f.x_is_bf16 = x_dtype == TSVD_BF16; f.ldx = ldx;
         f.x_vec = vec;
-        f.tokens = tokens; f.x_token = x_token; f.y_token = y_token;
+        f.x_token = x_token; f.y_token = y_token;
         f.S = reinterpret_cast<const float*>(h->blob + hd.off_S);
         f.bound_V = h->bound_V;
         f.y = y; f.ldy = ldy; f.bias = oo.bias; f.out_bf16 = oo.out_bf16;
@@ -298,12 +306,13 @@ bool z_as_fp32(const tsvd_handle* h, int64_t B, tsvd_dtype x_dtype) {
     return x_dtype == TSVD_BF16 && B >= 2 && B <= 16 && !tsvd_tuning_any() && !h->dense_u && gemv_serves(h) && (double)B * code_bytes(h) <= 60.0e6;
 }
 // Small factors on five planes, 1 to 16 tokens alike (a token's result does not depend on how many stand beside it): up to 512 ranks and 1 MB of code
-// words, and not where one workgroup does a token fastest.  Measured against side by side on 30 such factors: 2 to 8 tokens 0.87 of the time,
-// 16 tokens 0.80; at 640 to 2500 ranks one token would take 1.04 .. 1.2 times as long.  One token, 36 factors of 250 .. 2000 rows, 200 .. 1000 columns, 200 and
-// 500 ranks: against the one workgroup of up to 768 padded rows 1.00 .. 1.40 (0.94 once) of its time, beyond, against two launches, 0.92 .. 1.11 (1.04 on the
-// average: what two tokens and more gain is paid for here).  The error against 64 bits is 5e-8 to 1.3e-7 of the norm of y, side by side 1e-7 to 4e-6;
+// words, and not the smallest (the last lines).  Measured against side by side on 30 such factors: 2 to 8 tokens 0.87 of the time,
+// 16 tokens 0.80; at 640 to 2500 ranks one token would take 1.04 .. 1.2 times as long.  One token beyond 768 padded rows is no faster here: two launches, where the
+// single-token kernels have one since V is small (36 factors of 769 to 8000 rows: 4.1 to 8.1 us there, 7.4 to 8.1 here, 0.64 of the time on the average).  It stays for its bits,
+// the same beside any number of tokens, and its error: against 64 bits 5e-8 to 1.3e-7 of the norm of y, side by side 1e-7 to 4e-6;
 // and on rows that avoid features 20 to 30000 times the rest, or where such features cancel, a tenth to a thousandth of that of the integers side by
-// side, whose grid is 2^-31 of the largest sum that could be.
+// side, whose grid is 2^-31 of the largest sum that could be.  (The factors of up to 768 padded rows and 64 tiles a stage, where one workgroup took a token
+// fastest when the line was drawn, keep the single-token kernels and with them their bits.)
 bool five_planes(const tsvd_handle* h) {
     const tsvd_blob_header& hd = h->hd;
     return !h->dense_u && hd.Kp <= 512 && code_bytes(h) <= 1.0e6 && (!tsvd_gemv_one_workgroup(hd.Mp, hd.Kp, hd.Np) || hd.Mp > 768);
@@ -938,6 +947,22 @@ extern "C" int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* s
             if (tsvd_gemm_use_fp6_v(h->hd.Mp, h->hd.Kp, h->hd.Np, B, h->cu_count, true)) *shape_v = 40;
         }
     }
+    return 0;
+}
+
+extern "C" int tsvd_tuning_one_launch(const tsvd_handle* h, long long B) {
+    if (!h || B < 1 || !gemv_serves(h) || h->dense_u || env_int("TSVD_GEMV_FUSED", 1) == 0) return 0;
+    return tsvd_gemv_fused_fits(gemv_fused_sizes(h->hd, (int)std::min<long long>(gemv_tokens(h, B), B)), h->cu_count);
+}
+
+extern "C" int tsvd_tuning_tiles_by_xcd(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u) {
+    if (!h || !v || !u || B < 1 || !use_gemm(h, B, x_dtype)) return 1;
+    const tsvd_batch_plan plan = batch_plan(batch_call(h, B, x_dtype, false, false, false, false, true, true));
+    if (!plan.split) return 1;
+    const long long nvb = (h->hd.N + 127) / 128, nub = (h->hd.K + 127) / 128, sets = x_dtype == TSVD_F32 ? 2 : 1;
+    const bool own_x = tsvd_fp6_split_makes_x(plan.split_v, (int)std::min(sets * nvb, 1ll << 20)) && env_int("TSVD_SPLIT_X", 1) != 0;
+    *v = plan.split_v && !own_x && tsvd_fp6_split_placed(plan.split_v, {128 * nub, B, sets * nvb, nvb, h->cu_count});
+    *u = plan.split_u && tsvd_fp6_split_placed(plan.split_u, {h->hd.M, B, sets * nub, nub, h->cu_count});
     return 0;
 }
 

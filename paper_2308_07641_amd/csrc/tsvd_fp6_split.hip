@@ -432,8 +432,8 @@ tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_
 // ---- tiles of 128 rows: a block of the contraction for a wavefront ----------------------------------
 // With one group of rows no wavefront reads what another one uses, so nothing is staged and no barrier stands in the loop: wavefront w takes the blocks
 // w, w + 8, ..., its operands (planes of a record, 24 bytes a lane and plane, in the order of the record) go from the L2s to registers, DEPTH blocks
-// ahead, and stage V makes the planes of x in registers where it makes them itself (X; every row tile makes them again).  The partial sums of the eight
-// wavefronts meet in LDS.
+// ahead, and stage V makes the planes of x in registers where it makes them itself (X; every row tile makes them again.  Feature-major bf16 passes through 4 KiB
+// of LDS of the wavefront there, where the sums meet later: a barrier behind the loop).  The partial sums of the eight wavefronts meet in LDS.
 // Measured on MI355X against the same tiles on records staged in LDS (a step of 16 records for every barrier; in a launch of two or three steps each one
 // waited a round trip of about 1 us for the next): 3072 x 768 x 1536 fp32 at 197 tokens 20.4 -> 18.1 us, 256 x 489 x 256 fp32 at 256 13.2 -> 9.6,
 // 7415 x 4199 x 4465 bf16 at 125 32.3 -> 27.5; 40 drawn fp32 and 60 bf16 calls of 30 to 2500 tokens that take these tiles 0.73 to 1.0 of the time.
@@ -625,9 +625,13 @@ hipError_t init_shape() {
 // gcd(token tiles, 8) of the token tiles, and (token tiles) / 8 of the row tiles.  16384 x 4096 x 8192 at 256 tokens (an XCD's codes of stage U 16.8 -> 4.2 MB, planes
 // 1.3 -> 5; of stage V 8.4 -> 2.1 MB, planes 0.3 -> 1.2) 73.5 -> 68.7 us, 3072 x 768 x 1536 fp32 at 197 18.1 -> 17.1, 275 x 1257 x 597 fp32 at 418 19.7 -> 17.3;
 // on 66 drawn calls 0.88 to 1.0 of the time (one 1.03).  Launches of several rounds: 0.97 to 1.04, 1.01 on the average.  A saving below half a megabyte: nothing.
-bool place_of(long long row_tiles, long long token_tiles, double code_bytes, double act_bytes, split_place* p, dim3* grid) {
+bool place_of(int shape, const split_sizes& s, split_place* p, dim3* grid) {
+    const long long rows_tile = shape / 8 * 128, tokens_tile = (shape & 7) * 16;
+    const long long row_tiles = (s.rows + rows_tile - 1) / rows_tile, token_tiles = (s.B + tokens_tile - 1) / tokens_tile;
+    // (bytes of what the launch reads: 2 bits a code, a record of 4864 bytes for 16 tokens and 128 indices)
+    const double code_bytes = (double)s.rows * 32.0 * s.code_blocks, act_bytes = (double)s.blocks * ((s.B + 15) / 16) * FP6_REC_BYTES;
     *grid = dim3((unsigned)token_tiles, (unsigned)row_tiles);
-    if (row_tiles * token_tiles > 256) return false;
+    if (row_tiles * token_tiles > s.cus) return false;
     int d = 8;
     while (token_tiles % d) d /= 2;
     const double plain = code_bytes * std::min(1.0, (double)token_tiles / 8) + act_bytes / d;
@@ -636,7 +640,7 @@ bool place_of(long long row_tiles, long long token_tiles, double code_bytes, dou
     for (int log2 = 0; log2 <= 3; ++log2) {
         const long long rows = (row_tiles + (1 << log2) - 1) >> log2, groups = 8 >> log2, tiles = (token_tiles + groups - 1) / groups;
         const double bytes = code_bytes / (1 << log2) + act_bytes / (double)groups;
-        if (rows * tiles > 32 || bytes >= best) continue;
+        if (rows * tiles > s.cus / 8 || bytes >= best) continue;
         best = bytes;
         found = true;
         *p = {log2, (int)row_tiles, (int)token_tiles};
@@ -645,9 +649,8 @@ bool place_of(long long row_tiles, long long token_tiles, double code_bytes, dou
     return found;
 }
 template <int RW, int TN>
-hipError_t launch_shape(bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, hipStream_t stream) {
-    const unsigned token_tiles = (unsigned)((a.bvalid + 16 * TN - 1) / (16 * TN)), row_tiles = (unsigned)((a.rows_need + RW * 128 - 1) / (RW * 128));
-    dim3 grid(token_tiles, row_tiles);
+hipError_t launch_shape(bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, long long cus, hipStream_t stream) {
+    dim3 grid((unsigned)((a.bvalid + 16 * TN - 1) / (16 * TN)), (unsigned)((a.rows_need + RW * 128 - 1) / (RW * 128)));
     const dim3 block(512);
 #define SPLIT_LAUNCH(STAGE2, EX, X, PLACED, extra) hipLaunchKernelGGL((kernel<RW, TN, STAGE2, EX, X, PLACED>()), grid, block, (split_lds<RW, TN, X>), stream, a, extra)
 #define SPLIT_STAGE(PLACED, extra)                                  \
@@ -659,12 +662,9 @@ hipError_t launch_shape(bool stage2, const gemm_args& a, int ex, const split_x* 
         else SPLIT_LAUNCH(true, 0, 0, PLACED, extra);               \
     } while (0)
     split_place place;
-    // (bytes of what the launch reads: 2 bits a code, a record of 4864 bytes for 16 tokens and 128 indices)
     if (!stage2 && x && f32) SPLIT_LAUNCH(false, 0, 2, false, *x);
     else if (!stage2 && x) SPLIT_LAUNCH(false, 0, 1, false, *x);
-    else if (place_of(row_tiles, token_tiles, (double)a.rows_need * 32.0 * (a.code_blocks ? a.code_blocks : a.npairs),
-                      (double)a.npairs * ((a.bvalid + 15) / 16) * FP6_REC_BYTES, &place, &grid))
-        SPLIT_STAGE(true, place);
+    else if (place_of(8 * RW + TN, {a.rows_need, a.bvalid, a.npairs, a.code_blocks ? a.code_blocks : a.npairs, cus}, &place, &grid)) SPLIT_STAGE(true, place);
     else SPLIT_STAGE(false, split_x{});
 #undef SPLIT_STAGE
 #undef SPLIT_LAUNCH
@@ -682,24 +682,29 @@ hipError_t tsvd_fp6_split_init() {
 }
 
 // shape: rows / 128 of a tile * 8 + token tiles of 16
-static hipError_t launch_any(int shape, bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, hipStream_t stream) {
+static hipError_t launch_any(int shape, bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, long long cus, hipStream_t stream) {
     switch (shape) {
-        case 20: return launch_shape<2, 4>(stage2, a, ex, x, f32, stream);
-        case 18: return launch_shape<2, 2>(stage2, a, ex, x, f32, stream);
-        case 10: return launch_shape<1, 2>(stage2, a, ex, x, f32, stream);
-        case 9: return launch_shape<1, 1>(stage2, a, ex, x, f32, stream);
+        case 20: return launch_shape<2, 4>(stage2, a, ex, x, f32, cus, stream);
+        case 18: return launch_shape<2, 2>(stage2, a, ex, x, f32, cus, stream);
+        case 10: return launch_shape<1, 2>(stage2, a, ex, x, f32, cus, stream);
+        case 9: return launch_shape<1, 1>(stage2, a, ex, x, f32, cus, stream);
         default: return hipErrorInvalidValue;
     }
 }
-hipError_t tsvd_fp6_split_launch(int shape, bool stage2, const gemm_args& a, int ex, hipStream_t stream) {
-    return launch_any(shape, stage2, a, ex, nullptr, false, stream);
+hipError_t tsvd_fp6_split_launch(int shape, bool stage2, const gemm_args& a, int ex, long long cus, hipStream_t stream) {
+    return launch_any(shape, stage2, a, ex, nullptr, false, cus, stream);
+}
+bool tsvd_fp6_split_placed(int shape, const split_sizes& s) {
+    split_place place;
+    dim3 grid;
+    return place_of(shape, s, &place, &grid);
 }
 // Two steps of 16 records hold all of x of a token tile.
 bool tsvd_fp6_split_makes_x(int shape, int blocks) { return shape != 0 && blocks * (shape & 7) <= 32; }
 hipError_t tsvd_fp6_split_launch_x(int shape, const gemm_args& a, const void* x, bool f32, bool token_major, long long ld, int N, hipStream_t stream) {
     if (!f32 && !token_major && (N - 1) * ld + a.bvalid < 8) return hipErrorInvalidValue;
     const split_x xs = {x, ld, token_major, N};
-    return launch_any(shape, false, a, 0, &xs, f32, stream);
+    return launch_any(shape, false, a, 0, &xs, f32, 0, stream);
 }
 
 hipError_t tsvd_fp6_split_planes(const void* x, bool f32, bool token_major, long long ld, int N, int B, int blocks, unsigned char* planes,

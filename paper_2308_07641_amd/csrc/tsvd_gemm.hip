@@ -1496,7 +1496,7 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
             a4.two_sets = g.x_f32 ? pairs_k : 0;
             a4.colmax = nullptr;
             e = own_x ? tsvd_fp6_split_launch_x(g.split_v, a4, g.x, g.x_f32 != 0, g.x_token_major != 0, g.ldx, (int)hd.N, stream)
-                : g.split_v ? tsvd_fp6_split_launch(g.split_v, false, a4, 0, stream) : tsvd_fp6_launch_direct(a4, hd.Kp, g.cu_count, stream);
+                : g.split_v ? tsvd_fp6_split_launch(g.split_v, false, a4, 0, g.cu_count, stream) : tsvd_fp6_launch_direct(a4, hd.Kp, g.cu_count, stream);
             if (e != hipSuccess) return e;
         }
         if (mask & 4) {
@@ -1507,7 +1507,7 @@ hipError_t tsvd_forward_gemm(const tsvd_gemm_problem& g, hipStream_t stream) {
             a3.code_blocks = g.x_f32 ? pairs_k : 0;
             a3.colmax = nullptr;
             const int ex = out_variant(a3.bias, a3.out_bf16, a3.out_token_major);
-            e = g.split_u ? tsvd_fp6_split_launch(g.split_u, true, a3, ex, stream) : tsvd_fp6_launch(true, a3, hd.Mp, Bp, ex, g.cu_count, stream);
+            e = g.split_u ? tsvd_fp6_split_launch(g.split_u, true, a3, ex, g.cu_count, stream) : tsvd_fp6_launch(true, a3, hd.Mp, Bp, ex, g.cu_count, stream);
         }
         return e;
     }

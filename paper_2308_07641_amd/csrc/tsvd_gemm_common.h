@@ -294,9 +294,8 @@ hipError_t tsvd_fp6_split_init();
 hipError_t tsvd_fp6_split_planes(const void* x, bool f32, bool token_major, long long ld, int N, int B, int blocks, unsigned char* planes,
                                  hipStream_t stream);
 // one stage (a.act = planes in a layout of a.plane_blocks per token group; stage V: a.out = planes of z, a.ld_out per token group)
-hipError_t tsvd_fp6_split_launch(int shape, bool stage2, const gemm_args& a, int ex, hipStream_t stream);
-// stage V making the planes of x itself (a.act is not read): whether a shape can for that many blocks (fp32: both sets), and the launch
-bool tsvd_fp6_split_makes_x(int shape, int blocks);
+hipError_t tsvd_fp6_split_launch(int shape, bool stage2, const gemm_args& a, int ex, long long cus, hipStream_t stream);
+// stage V making the planes of x itself (a.act is not read), where tsvd_fp6_split_makes_x
 hipError_t tsvd_fp6_split_launch_x(int shape, const gemm_args& a, const void* x, bool f32, bool token_major, long long ld, int N, hipStream_t stream);
 // the token-panel launch on fp4 codes x fp6 planes
 hipError_t tsvd_fp6_launch_panel(const panel_args& pa, int ex, hipStream_t stream);

@@ -97,6 +97,12 @@ size_t tsvd_gemv_dense_lds(long long Kp);
 hipError_t tsvd_gemv_dense_init();
 hipError_t tsvd_launch_gemv_dense(const tsvd_gemv_dense_args& a, hipStream_t stream);
 void tsvd_internal_dense_from_blob(const void* blob, void* out);   // tsvd_pack.cpp: recodes U's tiles of a host blob
+// Rows and 128-index blocks (fp32: of both sets of planes; code_blocks: of the codes) that a launch of split tiles multiplies, and its tokens.
+struct split_sizes {
+    long long rows, B, blocks, code_blocks, cus;
+};
+bool tsvd_fp6_split_placed(int shape, const split_sizes& s);   // tsvd_fp6_split.hip: whether its tiles are dealt to the XCDs in groups
+bool tsvd_fp6_split_makes_x(int shape, int blocks);          // ... and whether stage V of a shape can make the planes of x itself, for that many blocks (fp32: both sets)
 bool tsvd_gemv_one_workgroup(long long Mp, long long Kp, long long Np);   // at most 64 tiles per stage, four a wavefront
 bool tsvd_gemv_fused_fits(const tsvd_gemv_fused_args& a, int cus);
 hipError_t tsvd_launch_gemv_fused(const tsvd_gemv_fused_args& a, int cus, hipStream_t stream);

@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 CALLS = [
     # M, N, K, B: one tile per stage; one rank, one row, one column; ends beside a strip, a tile and a block of 128 ranks
     (16, 256, 16, 1), (1, 1, 1, 1), (17, 255, 127, 3), (33, 257, 129, 2), (65, 130, 256, 16),
-    # columns of V split over 1, 2, 4, 8 and 16 wavefronts; rounds of strips; four thousand columns
-    (300, 200, 640, 1), (300, 500, 320, 2), (300, 1000, 250, 1), (300, 2000, 128, 4), (500, 4096, 96, 1), (500, 4095, 90, 2),
+    # columns of V of a wavefront and of two; rounds of strips; the most columns
+    (300, 200, 640, 1), (300, 500, 320, 2), (300, 1000, 250, 1), (300, 2000, 128, 4), (500, 3072, 96, 1), (500, 3071, 90, 2),
     # the most tiles of V, ranks beyond 1024 (two for a thread), rows that need several strips a workgroup, and all of a device's workgroups
     (700, 256, 1500, 1), (700, 250, 1536, 2), (5000, 300, 600, 1), (16384, 250, 500, 1), (12000, 100, 1025, 1), (3000, 500, 600, 16)]
 
@@ -28,6 +28,7 @@ def test_bits_of_the_two_launches(tsvd, M, N, K, B, x_dtype):  # noqa: F811
         i = make(M, N, K, B, 0.5, 0.02, x_dtype, seed=M + K) if make is workloads.make_inputs else make(M, N, K, B, 0.5, x_dtype, seed=M + K)
         h = tsvd.tsvd_pack(i.U, i.S, i.V)
         x = to_device(i)
+        assert tsvd.tsvd_tuning_one_launch(h, B)              # (else both calls would take the two launches)
         bias = torch.arange(M, dtype=torch.float32, device="cuda:0") % 7
         rows = torch.full((B, N + 3), float("nan"), dtype=x.dtype, device="cuda:0")      # rows at odd elements, what lies between them is no number
         rows[:, 1:1 + N] = x.t()

@@ -231,9 +231,10 @@ def test_blocks_of_a_pair(tsvd, M, N, K, B, v, u, own_x, x_dtype):
 
 
 @pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("M,N,K,B,v,u", [(700, 5000, 2600, 300, 9, 9), (1900, 4500, 2100, 130, 10, 10), (2600, 4300, 2300, 200, 18, 18), (2050, 8300, 1100, 513, 20, 20),
-                                         (4100, 4200, 1030, 40, 18, 9)])
-def test_tiles_by_xcd(tsvd, M, N, K, B, v, u, x_dtype):
+@pytest.mark.parametrize("M,N,K,B,v,u,placed", [
+    (700, 5000, 2600, 300, 9, 9, (False, True)), (700, 5000, 1300, 150, 9, 9, (True, False)), (1900, 4500, 2100, 130, 10, 10, (True, True)), (2600, 4300, 2300, 200, 18, 18, (True, True)),
+    (2050, 8300, 1100, 513, 20, 20, (True, True)), (4100, 8300, 2100, 72, 18, 9, (True, True))])
+def test_tiles_by_xcd(tsvd, M, N, K, B, v, u, placed, x_dtype):
     """Launches of one round whose tiles are dealt to the XCDs in groups that do not divide evenly: every tile is computed, those beyond the matrix write
     nothing (the call's own workspace ends where the planes of z do)."""
     import torch
@@ -243,7 +244,9 @@ def test_tiles_by_xcd(tsvd, M, N, K, B, v, u, x_dtype):
     h = tsvd.tsvd_pack(i.U, i.S, i.V)
     for name, value in {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_SPLIT_V": v, "TSVD_SPLIT_U": u, "TSVD_SPLIT_X": 0}.items():
         tsvd.tsvd_tuning_set(name, value)
-    need = tsvd.tsvd_workspace_bytes(h, B, tsvd.TSVD_BF16 if x_dtype == "bf16" else tsvd.TSVD_F32)
+    dtype = tsvd.TSVD_BF16 if x_dtype == "bf16" else tsvd.TSVD_F32
+    assert tsvd.tsvd_tuning_tiles_by_xcd(h, B, dtype) == placed
+    need = tsvd.tsvd_workspace_bytes(h, B, dtype)
     guarded = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda:0")
     y = tsvd.tsvd_forward(h, to_device(i), workspace=guarded[:need])
     assert np.array_equal(y.cpu().numpy(), oracle.forward(i.U, i.S, i.V, i.X))
