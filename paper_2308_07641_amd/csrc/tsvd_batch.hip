@@ -34,8 +34,9 @@ double planes_cost(const sizes& s, int v) {
     if (tsvd_fp6_split_makes_x(v, (int)std::min<long long>(s.sets * s.nvb, 1 << 20))) return 0;      // stage V makes them
     return 4.9 + 8.4 * (double)(s.nvb * up(s.B, 16) * s.sets) / 4096;
 }
-// (Shapes 9 and 10 are faster since: tsvd_fp6_own_kernel.  On 136 calls the shapes that these factors take are 1.2 % slower than the best of all 16 pairs of them,
-// those of new factors 1.1 %; and lower estimates would take calls from kernels that hold x exactly.)
+// (Fitted to kernels with a barrier for each step of 16 records.  All four shapes are faster since: tsvd_fp6_own_kernel for 9 and 10, tsvd_fp6_pair_kernel for 18 and 20.
+// On 136 calls the shapes that these factors take are 1.2 % slower than the best of all 16 pairs of them, those of new factors for 9 and 10 1.1 %; and lower estimates
+// would take calls from kernels that hold x exactly.)
 struct split_factors {
     int shape;
     double v0, v_round, v_step, v_x, u0, u_round, u_step;
@@ -79,6 +80,8 @@ double split_u_cost(const sizes& s, const split_factors* f) {
 }
 
 // ---- thin panels ----------------------------------------------------------------------------------
+// (Fitted to one workgroup for each panel and to loads by element: several workgroups where panels are few, and rows of three taps in one load, are faster
+// since and not in these numbers.)
 double thin_cost(const tsvd_batch_call& c, int tiles) {
     const long long nvb = up(c.N, 128), nub = up(c.K, 128), panels = up(c.B, 16 * tiles);
     const double r = (double)up(panels, c.cus), busy = (double)std::min(panels, c.cus) / (double)c.cus;

@@ -93,9 +93,11 @@ template <int K1, int STEP, int ROW, bool VEC>
 __global__ void __launch_bounds__(256, K1 == 7 && STEP == 1 ? 3 : 2)
 tsvd_depthwise_kernel(depthwise_args p) {
     constexpr int COLS = 16 / STEP, NR = K1 + (STEP - 1) * STEP, ADV = STEP * STEP;      // of a tile: columns, input rows, input rows to the next
-    // Rows in registers, and tiles until the slots repeat.  As few as keep a row's latency behind a tile or two: every further row is requested by all wavefronts
-    // before the first product, and the loop is unrolled over the slots.  (Three rows ahead with stride 1, 16 or 20 slots with stride 2: 2 % slower
-    // with rows by 8, 663 channels of 7 x 7, 3 x 3, stride 2, 2 images 6.3 -> 9.9 us.)
+    // Rows in registers, and tiles until the slots repeat: as few as pay, since every further row is requested by all wavefronts before the first product, and the
+    // loop is unrolled over the slots.  With stride 1 a row is requested two tiles before the one that needs it first (in rows of fewer than four elements: by that tile itself).
+    // With stride 2 a tile requests four rows and needs one of them at once (3 x 3 and 7 x 7; 5 x 5 three), so it waits for what it has just asked for, and the SIMD's
+    // other wavefronts cover that.  (Three rows ahead with stride 1, 16 or 20 slots with stride 2: 2 % slower with rows by 8, 663 channels of 7 x 7, 3 x 3, stride 2, 2 images
+    // 6.3 -> 9.9 us.  12 slots for 5 x 5 with stride 2, whose rows then come a tile ahead: 0.96 to 1.03 of the time of 8 on 14 geometries, 0.995 on the average.)
     constexpr int RING = STEP == 1 ? NR + (ROW == 1 ? 0 : 2) : NR > 8 ? 12 : 8, PERIOD = STEP == 1 ? RING : RING / ADV;
     const tsvd_depthwise_problem& g = p.g;
     __shared__ u32x2 weight[64];                      // of a tap its three parts (bf16: the first two, the last); the last entry is zero

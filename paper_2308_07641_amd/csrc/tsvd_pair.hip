@@ -40,7 +40,7 @@ constexpr int PAIR_MAX_N = 2048;
 // The order of the contraction index is free as long as both operands share it: lane group g of a wavefront takes the
 // indices 8 t + 2 g, 8 t + 2 g + 1 of its share with load t, so a load is 16 bytes per lane and touches 16 row segments of
 // 64 bytes.  Bound by the latency of the loads and of the chain of MFMAs (64 cycles each): small tiles on many
-// workgroups while n is small (n = 256: 136 workgroups of 16 MFMAs per wavefront, 5.2 us; on eight wavefronts of 8 MFMAs 5.9 against 5.6 us; the Gram matrix of
+// workgroups while n is small (n = 256: 136 workgroups with a tile, of 160, and 16 MFMAs per wavefront, 5.2 us; on eight wavefronts of 8 MFMAs 5.9 against 5.6 us; the Gram matrix of
 // 512 rows 6.2 us on four, 5.7 us on eight), 32 x 32 tiles, which read half as much per product, beyond.
 //
 // GRAM (first launch): P is R by its rows (TR = false) or columns (TR), any pitch; rows beyond n and indices beyond L read

@@ -291,7 +291,7 @@ def test_activation_scale_extremes_batched(tsvd):
 @pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("M,N,K", [(256, 256, 512), (1, 1, 1), (37, 29, 61), (500, 300, 250), (1000, 700, 200), (100, 1000, 260)])
 def test_small_single_token_fused_launch(tsvd, M, N, K, x_dtype, fused):
-    """Small matrices run both stages in one launch of one workgroup ("1"); the two-launch kernels
+    """Small matrices run both stages in one launch, every workgroup computing all of z ("1"); the two-launch kernels
     must give the same exact results on them ("0")."""
     tsvd.tsvd_tuning_set("TSVD_GEMV_FUSED", int(fused))
     i = workloads.make_integer_inputs(M, N, K, 1, 0.5, x_dtype, seed=3 * M + N + K)

@@ -101,9 +101,11 @@ def test_leading_singular_pair(tsvd, M, N):
         assert np.max(np.abs(sign * u - ur[:, 0])) < 1e-8 and np.max(np.abs(sign * v - vr[0, :])) < 1e-8
 
 
-@pytest.mark.parametrize("M,N", [(1, 1), (1, 70), (70, 1), (64, 64), (65, 63), (129, 200), (384, 400), (385, 385), (500, 420)])
+@pytest.mark.parametrize("M,N", [(1, 1), (1, 70), (70, 1), (64, 64), (65, 63), (129, 200), (384, 400), (385, 385), (500, 420),
+                                 (257, 300), (320, 321), (330, 321), (513, 513), (576, 600), (640, 641), (641, 700)])
 def test_leading_singular_pair_by_squarings_at_tile_edges(tsvd, M, N):
-    """Sizes around the tiles of the squaring kernels (16 and 32 rows, padding to 64, the change at 384), both orientations;
+    """Sizes around the tiles of the squaring kernels (16 and 32 rows, padding to 64, the change at 384; the most tiles that are dealt to the XCDs by groups of
+    rows, up to 320 with the smaller ones and 640 with the larger, and one more), both orientations;
     a rank-one matrix (done after one squaring) and a pair of equal leading singular values (never of rank one: the pair must
     still be a singular pair)."""
     rng = np.random.default_rng(100 * M + N)
