@@ -227,7 +227,7 @@ tsvd_gemm_kernel(gemm_args p) {
     auto load_x = [&](int stage) {
         const int k0 = stage_k0(stage);
         if constexpr (FAST) {
-            const int soff = tsvd_buffer_offset(k0 * (int)p.ld * 2, p.act_bytes);
+            const int soff = STAGE2 ? k0 * (int)p.ld * 2 : tsvd_buffer_offset(k0 * (int)p.ld * 2, p.act_bytes);      // (z has all rows)
 #pragma unroll
             for (int c = 0; c < CPT; ++c) xreg[c] = buf_load128(act_rsrc, x_voff[c], soff);
         } else {
@@ -376,7 +376,7 @@ tsvd_gemm_pipe_kernel(gemm_args p) {
         for (int b = 0; b < TN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     auto issue_x = [&](int stage, int buf) {
-        const int soff = tsvd_buffer_offset((256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2, p.act_bytes);
+        const int at = (256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2, soff = STAGE2 ? at : tsvd_buffer_offset(at, p.act_bytes);      // (z has all rows)
 #pragma unroll
         for (int c = 0; c < SPW; ++c)
             buf_load128_to_lds(act_rsrc, lds0 + buf * STAGE_BYTES + c * NW * 1024, x_voff[c], soff);
@@ -613,7 +613,7 @@ tsvd_gemm_ring_kernel(gemm_args p) {
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
                 const int stage = 2 * pair + st;
-                const int soff = tsvd_buffer_offset((256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2, p.act_bytes);
+                const int at = (256 * (stage >> 2) + 128 * ((stage >> 1) & 1) + 32 * (stage & 1)) * (int)p.ld * 2, soff = STAGE2 ? at : tsvd_buffer_offset(at, p.act_bytes);      // (z has all rows)
 #pragma unroll
                 for (int c = 0; c < SPW; ++c)
                     if (part < 0 || (((s * 2 + st) * SPW + c) & 3) == part)
