@@ -6,8 +6,11 @@
 // output and rank less the zeros).  w is fp32: it enters as the sum of three bf16 parts, which hold its 24 bits exactly, so products are
 // exact and sums are fp32 as before.
 //
-// The 16 columns of the B operand are strips: R output rows of one image, as many strips as it takes to fill the chip (images times
-// segments of the plane).  A lane's B operand is eight columns of its strip's next row, straight from global memory (16 bytes where
+// The 16 columns of the B operand are strips: R output rows of a column of tiles of one image, as many strips as it takes to fill the chip (images times
+// segments of the plane times columns of tiles).  Strips side by side stand in lanes side by side, so that a wavefront's request for a row is
+// whole rows of a few images rather than 64 bytes of sixteen, and its stores too: the requests' lines bound the kernel more than its matrix instructions (with sixteen images
+// or segments in a wavefront 123 channels of 56 x 56, 5 x 5, 59 images 27.0 us, now 22.6; 558 of 3 x 3, 10 images 23.0 -> 20.2; 201 of 28 x 28, 7 x 7, stride 2, 49 images 14.1 -> 12.5;
+// 53 drawn geometries 0.975 of the time, none longer).  A lane's B operand is eight columns of its strip's next row, straight from global memory (16 bytes where
 // rows are aligned); the last k1 rows stay in registers, each output row needs stride1 new ones, fetched one output row ahead.
 // The banded matrices are the same for every strip and column tile of a channel: the four wavefronts of a workgroup make them
 // together, then each keeps all of them in registers.
@@ -16,8 +19,8 @@
 // scale that is not finite all outputs of the channel.  Every such output is itself not finite: a lane that has stored one computes its
 // outputs again on the factors, tap by tap, zeros skipped, where only the outputs are touched whose taps hold the value.
 //
-// Measured on MI355X: 96 channels of 56 x 56, 7 x 7 at rank 5, 32 images, bf16: 14.4 us (68 on the factors): 6.7 of them matrix instructions, about 3.5 the latency of the
-// first loads and the bands, 2 the launch; 640 of 28 x 28, 5 x 5, stride 2, 8 images 7.8, 217 of 28 x 28, 7 x 7, 32 images 11.3 (16.6 and 14.5 with rows in loads of
+// Measured on MI355X: 96 channels of 56 x 56, 7 x 7 at rank 5, 32 images, bf16: 13.6 us (68 on the factors): 6.7 of them matrix instructions, about 3.5 the latency of the
+// first loads and the bands, 2 the launch; 640 of 28 x 28, 5 x 5, stride 2, 8 images 7.8, 217 of 28 x 28, 7 x 7, 32 images 11.3 (then 16.6 and 14.5 with rows in loads of
 // two elements and more of them ahead).  60 random geometries of 64 to 768 channels: 1.04 to 41 times the speed of the kernel on the factors.
 #include "tsvd_depthwise.h"
 
@@ -35,7 +38,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 struct depthwise_args {
     tsvd_depthwise_problem g;
-    int R, segments, strips, col_tiles, tasks;       // output rows per strip, strips per image, all; column tiles; wavefront tasks per channel
+    int R, segments, col_tiles, strips;              // output rows of a strip, strips to a column of tiles, columns of tiles; strips of all images
     unsigned plane_bytes;                            // of one channel of x
 };
 
@@ -53,8 +56,8 @@ __device__ __forceinline__ void outputs_on_factors(const depthwise_args& p, int 
     int all = -1;
     asm volatile("" : "+s"(all));
     const int lane = __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
-    const int i = lane & 15, q = lane >> 4, m = blockIdx.y, group = m / g.mg, task = blockIdx.x * 4 + wave;
-    const int ct = task % p.col_tiles, strip = task / p.col_tiles * 16 + i, img = strip / p.segments, row0 = (strip - img * p.segments) * p.R;
+    const int i = lane & 15, q = lane >> 4, m = blockIdx.y, group = m / g.mg, strip = (blockIdx.x * 4 + wave) * 16 + i;
+    const int rest = strip / p.col_tiles, ct = strip - rest * p.col_tiles, img = rest / p.segments, row0 = (rest - img * p.segments) * p.R;
     if (strip >= p.strips) return;
     const int ox = ct * (16 / STEP) + 4 * (STEP == 1 ? q : q & 1), oend = min(ox + 4, g.Wo), yend = min(row0 + p.R, g.Ho);
     const uint16_t* plane = g.x + ((size_t)group * g.images + img) * g.H * g.W;
@@ -104,14 +107,13 @@ tsvd_depthwise_kernel(depthwise_args p) {
     __shared__ __align__(16) unsigned char bands[NR * 3 * 1024];
     float* const terms = reinterpret_cast<float*>(bands);      // before the bands: U S V per rank and tap
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, q = lane >> 4;
-    const int m = blockIdx.y, group = m / g.mg, task = blockIdx.x * 4 + wave;
-    const bool active = task < p.tasks;
+    const int m = blockIdx.y, group = m / g.mg;
     const int scalar_wave = __builtin_amdgcn_readfirstlane(wave);    // (for the outputs that are computed again)
 
     // ---- this lane's strip and columns; the rows of the first output
-    const int ct = task % p.col_tiles, strip = task / p.col_tiles * 16 + i, img = strip / p.segments, row0 = (strip - img * p.segments) * p.R;
+    const int strip = (blockIdx.x * 4 + wave) * 16 + i, rest = strip / p.col_tiles, ct = strip - rest * p.col_tiles, img = rest / p.segments, row0 = (rest - img * p.segments) * p.R;
     const int first = ct * 16 - g.p2, c0 = first & ~7;       // window of the tile: columns c0 .. c0 + 31, (COLS - 1) STEP + k2 + 7 <= 29 of them used
-    const bool strip_ok = active && strip < p.strips;
+    const bool strip_ok = strip < p.strips;
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.x) + (size_t)group * (p.plane_bytes / 2), 0, (int)p.plane_bytes, 0x00020000);
     const int iy_first = row0 * STEP - g.p1, base = 2 * img * g.H * g.W, pitch = 2 * g.W;
     constexpr unsigned NONE = 0x40000000u;                  // beyond the buffer (below 2^30 bytes): loads give zero
@@ -196,7 +198,7 @@ tsvd_depthwise_kernel(depthwise_args p) {
         weight[threadIdx.x] = u32x2{part[0] | part[1] << 16, part[2]};
     }
     __syncthreads();
-    const int from_c0 = first - c0;                   // (the same for every tile: a tile starts at a multiple of 16 columns)
+    const int from_c0 = -g.p2 & 7;                    // first - c0 (a tile starts at a multiple of 16 columns)
     for (int f = wave; f < NR; f += 4) {
         const int dy = f - i / COLS * STEP;
         const int at = (unsigned)dy < (unsigned)K1 ? dy * g.k2 : 63, first_dx = 8 * q - from_c0 - i % COLS * STEP;   // window column of element 0, from the output's first
@@ -213,7 +215,7 @@ tsvd_depthwise_kernel(depthwise_args p) {
         for (int s = 0; s < 3; ++s) *reinterpret_cast<u32x4*>(bands + (f * 3 + s) * 1024 + lane * 16) = part[s];
     }
     __syncthreads();
-    if (!active) return;
+    if ((int)(blockIdx.x * 4 + scalar_wave) * 16 >= p.strips) return;
     bf16x8 band[NR][3];
 #pragma unroll
     for (int f = 0; f < NR; ++f)
@@ -305,15 +307,15 @@ hipError_t tsvd_depthwise_launch(const tsvd_depthwise_problem& g, hipStream_t st
     long long best = -1;
     for (int n = 1; n <= std::min(g.Ho, 64); ++n) {
         const int R = (g.Ho + n - 1) / n, segments = (g.Ho + R - 1) / R;
-        const long long strips = (long long)g.images * segments, tasks = (strips + 15) / 16 * a.col_tiles, blocks = (tasks + 3) / 4 * channels;
+        const long long strips = (long long)g.images * segments * a.col_tiles, blocks = (strips + 63) / 64 * channels;
         const long long work = (long long)((R + g.s1 - 1) / g.s1) * 3 * (g.k1 + (g.s1 - 1) * g.s1);
         const long long cost = (blocks + g.cu_count - 1) / g.cu_count * (work + 4 * g.k1 + 60) + work;
         if (best < 0 || cost < best) {
             best = cost;
-            a.R = R; a.segments = segments; a.strips = (int)strips; a.tasks = (int)tasks;
+            a.R = R; a.segments = segments; a.strips = (int)strips;
         }
     }
-    const dim3 grid((unsigned)((a.tasks + 3) / 4), (unsigned)channels);
+    const dim3 grid((unsigned)((a.strips + 63) / 64), (unsigned)channels);
     const uintptr_t at = reinterpret_cast<uintptr_t>(g.x);
     const int row = g.W % 8 == 0 && at % 16 == 0 ? 8 : g.W >= 4 ? 4 : 1;
     if (g.s1 == 1) {
