@@ -5,11 +5,22 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#define TSVD_PAIR_MAX_SQUARINGS 48
+
 // What the device reports about the squarings of one pair.
 struct tsvd_pair_state {
     int last;            // index of the squared matrix that is numerically of rank one, -1 while there is none
     int missed;          // pairs since it was last cleared whose squarings were not enough
     int needed;          // most squarings that a pair since it was last cleared should have had
+};
+// ... and what pairs leave to the next one of the same sequence (tsvd_pair_sequence): the shifts s and traces t of X_{k+1} = ((X_k - s_k) / t_k)^2, and the second
+// eigenvalue of the X_{count} that the pair ended with.
+struct tsvd_pair_shifts {
+    tsvd_pair_state state;
+    int count;
+    double second;       // 0: not known
+    double first;        // s_0 of the pair that is being squared
+    double s[TSVD_PAIR_MAX_SQUARINGS + 1], t[TSVD_PAIR_MAX_SQUARINGS + 1];
 };
 
 struct tsvd_pair_plan {
@@ -20,21 +31,24 @@ struct tsvd_pair_plan {
     double* v0;          // [N] start vector
     double* s;           // [n] start vector on the shorter side (v0 itself where that is the columns)
     tsvd_pair_state* state;
+    bool sequence;       // state is that of a tsvd_pair_shifts
     double *u, *v;       // [M], [N]: the pair, not normalised
 };
-
-#define TSVD_PAIR_MAX_SQUARINGS 48
 
 // Whether the squarings are the faster method for an M x N matrix (the others take Lanczos steps).
 bool tsvd_pair_squares(int64_t M, int64_t N);
 size_t tsvd_pair_bytes(int64_t M, int64_t N);
 // Lays the plan out in `mem` (tsvd_pair_bytes, 256-byte aligned) and enqueues the start vector.
 void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* plan, hipStream_t stream);
-// Gram matrix of R [M][N] and its squarings `from` .. `to` - 1 (from = 0 computes the Gram matrix first).
-void tsvd_pair_square(const tsvd_pair_plan& plan, const double* R, int from, int to, hipStream_t stream);
+// Makes the pairs taken with the plan a sequence: each one's leading value is the second of the one before, or above it, as that of a residual is when the
+// pair, or a matrix of rank one near it, is taken away (the k-th singular value of A is at most the (k - 1)-th of A less a matrix of rank one).
+void tsvd_pair_sequence(tsvd_pair_plan* plan, tsvd_pair_shifts* shifts);
+// Gram matrix of R [M][N] and its squarings `from` .. `to` - 1 (from = 0 computes the Gram matrix first).  shifted (in a sequence, from = 0, of `to` squarings in all): the
+// squarings are shifted by what the pair before left.
+void tsvd_pair_square(const tsvd_pair_plan& plan, const double* R, int from, int to, bool shifted, hipStream_t stream);
 // plan.u and plan.v from the last squared matrix; `count` squarings were enqueued in total.  any_rank: it need not be of rank one (where
-// tsvd_pair_any_rank).
-void tsvd_pair_vectors(const tsvd_pair_plan& plan, const double* R, int count, bool any_rank, hipStream_t stream);
+// tsvd_pair_any_rank).  shifted: as they were enqueued.
+void tsvd_pair_vectors(const tsvd_pair_plan& plan, const double* R, int count, bool any_rank, bool shifted, hipStream_t stream);
 bool tsvd_pair_any_rank(const tsvd_pair_plan& plan);
 // Squarings after which that is likely to do for a matrix of which nothing is known (sixteen where they have to lead to rank one); the
 // device then says what it wants (tsvd_pair_state).

@@ -502,20 +502,25 @@ tsvd_residual_kernel(const double* __restrict__ W, const int8_t* __restrict__ U,
 // a wavefront per row, four columns per lane (one 4-byte load of V serves them and hits L1 for three of the four
 // wavefronts).  part[m * gridDim.x + blockIdx.x] = sum of squares of that piece, in host memory: the host adds them (a
 // copy back to the host after the launch would cost more than the launch); with them goes what the device has to report.
-struct transition_report {
-    tsvd_pair_state pair;
+struct transition_state {
+    tsvd_pair_shifts pair;
     int failed;              // ternarizations without a result
+};
+struct transition_report {
+    int missed, needed;      // of the pairs' squarings (tsvd_pair_state)
+    int failed;
+    int resolved;            // the last pair left its second eigenvalue
 };
 static_assert(sizeof(transition_report) % 8 == 0, "doubles follow it");
 __global__ void __launch_bounds__(256)
 tsvd_residual_rows_kernel(const double* __restrict__ W, const int8_t* __restrict__ Ut, int mp, const double* __restrict__ S,
                           const int8_t* __restrict__ V, int np, int M, int N, int K, double* __restrict__ R, double* __restrict__ part,
-                          transition_report* __restrict__ seen, transition_report* __restrict__ told) {
+                          transition_state* __restrict__ seen, transition_report* __restrict__ told) {
     extern __shared__ __align__(16) unsigned char smem[];
     double* us = reinterpret_cast<double*>(smem);               // [4][K]
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-        told[0] = seen[0];
-        seen[0].pair.missed = seen[0].pair.needed = 0;          // (of one iteration each)
+        told[0] = {seen->pair.state.missed, seen->pair.state.needed, seen->failed, seen->pair.second > 0.0};
+        seen->pair.state.missed = seen->pair.state.needed = 0;  // (of one iteration each)
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.y * 4, m = m0 + wave, n = blockIdx.x * 256 + 4 * lane;
     for (int k = threadIdx.x; k < K; k += 256) {
@@ -936,12 +941,12 @@ extern "C" tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M
         int count = 0;
         for (tsvd_pair_state state = {-1, 0, 0}; count < limit && state.last < 0;) {
             const int to = std::min(limit, count == 0 ? 16 : count + 8);
-            tsvd_pair_square(plan, R_dev, count, to, s);
+            tsvd_pair_square(plan, R_dev, count, to, false, s);
             count = to;
             if (hipMemcpyAsync(&state, plan.state, sizeof state, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
                 return TSVD_EDEVICE;
         }
-        tsvd_pair_vectors(plan, R_dev, count, false, s);
+        tsvd_pair_vectors(plan, R_dev, count, false, false, s);
         tsvd_pair_normalise(plan, count, u_dev, v_dev, sigma_dev, steps_dev, s);
         return hipGetLastError() == hipSuccess ? TSVD_OK : TSVD_EDEVICE;
     }
@@ -1063,7 +1068,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     const size_t at_G = reserve((size_t)max_rank * max_rank * 8);
     const size_t at_factor = reserve((size_t)CHOL_DOUBLES * 8);
     const size_t at_part = reserve((size_t)q * M * 8);
-    const size_t at_report = reserve(sizeof(transition_report));
+    const size_t at_report = reserve(sizeof(transition_state));
     const size_t at_u = reserve((size_t)M * 8), at_v = reserve((size_t)N * 8), at_sigma = reserve(8);
     const size_t bytes_svd = tsvd_leading_singular_pair_workspace(M, N), at_svd = reserve(bytes_svd);
     // what the host reads after an iteration (two in turn, written by the device): the report, and the residual's sums of squares
@@ -1077,7 +1082,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         if (base) (void)hipFree(base);
     };
     if (hipMalloc(reinterpret_cast<void**>(&base), total) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&pinned), 2 * told_bytes + sizeof(tsvd_pair_state), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&pinned), 2 * told_bytes + sizeof(tsvd_pair_shifts), hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&event[0], hipEventDisableTiming) != hipSuccess || hipEventCreateWithFlags(&event[1], hipEventDisableTiming) != hipSuccess) {
         release();
         (void)hipGetLastError();
@@ -1093,7 +1098,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     double* G = reinterpret_cast<double*>(base + at_G);                      // [max_rank][max_rank], grown row by row
     double* factor = reinterpret_cast<double*>(base + at_factor);
     double* part = reinterpret_cast<double*>(base + at_part);
-    transition_report* rep = reinterpret_cast<transition_report*>(base + at_report);
+    transition_state* rep = reinterpret_cast<transition_state*>(base + at_report);
     double* u = reinterpret_cast<double*>(base + at_u);
     double* v = reinterpret_cast<double*>(base + at_v);
     double* sigma = reinterpret_cast<double*>(base + at_sigma);
@@ -1124,12 +1129,12 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         return true;
     };
     ok(hipMemsetAsync(Ut, 0, at_S - at_Ut, s));                              // the padding of the factors
-    ok(hipMemsetAsync(rep, 0, sizeof(transition_report), s));
+    ok(hipMemsetAsync(rep, 0, sizeof(transition_state), s));
     ok(hipMemsetAsync(factor, 0, (size_t)CHOL_DOUBLES * 8, s));
     tsvd_pair_plan plan;
     if (squares) {
         tsvd_pair_prepare(M, N, base + at_svd, &plan, s);
-        plan.state = &rep->pair;
+        tsvd_pair_sequence(&plan, &rep->pair);
         u = plan.u;
         v = plan.v;
     }
@@ -1146,24 +1151,34 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     bool first_pair = false;                                                 // in the plan already
     int least = 1;                                                           // squarings that iterations before `least_until` get
     int64_t least_until = 0;
+    // From the second iteration on pairs are shifted (tsvd_pair_square), two squarings fewer at first.  Where the pair before left no second eigenvalue, or too
+    // little came of the shifts, the iteration is taken without; for good after the second time that it had to be taken again.
+    bool resolved = false, by_shifts[2] = {false, false};
+    int shifted = 0, shifted_least = 3, misses = 0;                          // squarings of a shifted pair
     if (any_rank && st == TSVD_OK) {
-        tsvd_pair_state* state = reinterpret_cast<tsvd_pair_state*>(pinned + 2 * told_bytes);
+        tsvd_pair_shifts* left = reinterpret_cast<tsvd_pair_shifts*>(pinned + 2 * told_bytes);
+        tsvd_pair_state* state = &left->state;
         for (int from = 0, step = 0;;) {
-            tsvd_pair_square(plan, R, from, squarings, s);
-            tsvd_pair_vectors(plan, R, squarings, true, s);
-            if (!ok(hipMemcpyAsync(state, &rep->pair, sizeof *state, hipMemcpyDeviceToHost, s)) || !ok(hipStreamSynchronize(s))) break;
+            tsvd_pair_square(plan, R, from, squarings, false, s);
+            tsvd_pair_vectors(plan, R, squarings, true, false, s);
+            if (!ok(hipMemcpyAsync(left, &rep->pair, sizeof *left, hipMemcpyDeviceToHost, s)) || !ok(hipStreamSynchronize(s))) break;
             from = squarings;
             first_pair = state->missed == 0 || squarings == TSVD_PAIR_MAX_SQUARINGS;
             squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, first_pair ? std::max(1, state->needed) : std::max(squarings + step + 1, state->needed));
+            resolved = left->second > 0.0;
             if (first_pair) break;
             step += 4;                                                       // (equal values beside others: the estimate stays short)
-            if (!ok(hipMemsetAsync(&rep->pair.missed, 0, 2 * sizeof(int), s))) break;       // (and what it needed)
+            if (!ok(hipMemsetAsync(&rep->pair.state.missed, 0, 2 * sizeof(int), s))) break;       // (and what it needed)
         }
     }
     double wnorm2 = 0.0;
     if (wait_for(0)) wnorm2 = rnorm2;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
-    auto enqueue = [&](int64_t i, int64_t first, int64_t take) {
+    auto enqueue = [&](int64_t i, int64_t first, int64_t take, bool again) {
+        const bool shift = any_rank && i > 1 && resolved && !again && misses < 2;
+        if (shifted == 0) shifted = std::max(6, squarings - 2);
+        const int count = shift ? shifted : squarings;
+        by_shifts[i & 1] = shift;
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
         // that triple removed, ... (the last iteration takes what still fits below max_rank)
         const double* src = R;
@@ -1174,8 +1189,8 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         for (int64_t j = 0; j < take; ++j) {
             if (squares) {
                 if (!first_pair) {
-                    tsvd_pair_square(plan, src, 0, squarings, s);
-                    tsvd_pair_vectors(plan, src, squarings, any_rank, s);
+                    tsvd_pair_square(plan, src, 0, count, shift, s);
+                    tsvd_pair_vectors(plan, src, count, any_rank, shift, s);
                 }
                 first_pair = false;
                 if (j + 1 < take) tsvd_pair_deflate(plan, Rwork, s);
@@ -1207,23 +1222,29 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     int64_t K = 0, i = 1, ahead = 0;                                         // ahead: components enqueued
     int64_t take = std::min<int64_t>(q, max_rank);
     if (st == TSVD_OK && wnorm2 > 0.0) {
-        enqueue(1, 0, take);
+        enqueue(1, 0, take, false);
         ahead = take;
         while (st == TSVD_OK) {
             const int64_t next = std::min<int64_t>(q, max_rank - ahead);
-            if (squares && next > 0) enqueue(i + 1, ahead, next);
+            if (squares && next > 0) enqueue(i + 1, ahead, next, false);
             if (st != TSVD_OK || !wait_for(i)) break;
-            if (seen.pair.missed != 0 && seen.pair.needed < TSVD_PAIR_MAX_SQUARINGS) {
+            resolved = seen.resolved != 0;
+            if (seen.missed != 0 && (by_shifts[i & 1] || seen.needed < TSVD_PAIR_MAX_SQUARINGS)) {
                 // some pair needed more squarings: back to the residual before this iteration, with more of them, and for a while
                 // with one more than were too few (spectra on the edge of two counts missed every eighth iteration)
-                if (any_rank && i > 1) {
-                    least = std::min(seen.pair.needed, squarings + 1);
-                    least_until = i + 16;
+                if (by_shifts[i & 1]) {
+                    ++misses;
+                    shifted = shifted_least = std::min(TSVD_PAIR_MAX_SQUARINGS, shifted + 1);
+                } else {
+                    if (any_rank && i > 1) {
+                        least = std::min(seen.needed, squarings + 1);
+                        least_until = i + 16;
+                    }
+                    squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, seen.needed + (any_rank ? 0 : 8));
                 }
-                squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, seen.pair.needed + (any_rank ? 0 : 8));
-                if (!ok(hipStreamSynchronize(s)) || !ok(hipMemsetAsync(rep, 0, sizeof(transition_report), s))) break;
+                if (!ok(hipStreamSynchronize(s)) || !ok(hipMemsetAsync(rep, 0, sizeof(transition_state), s))) break;
                 residual(i - 1, K);
-                enqueue(i, K, take);
+                enqueue(i, K, take, true);
                 ahead = K + take;
                 continue;
             }
@@ -1231,14 +1252,15 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
                 st = TSVD_EVALUE;           // no ternary vector within theta: the components of an unfinished iteration are dropped
                 break;
             }
-            squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(i < least_until ? least : 1, seen.pair.needed) : std::max(16, seen.pair.needed + 2));
+            if (by_shifts[i & 1]) shifted = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(shifted_least, seen.needed));
+            else squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(i < least_until ? least : 1, seen.needed) : std::max(16, seen.needed + 2));
             const double err = std::sqrt(rnorm2 / wnorm2);
             if (errors_host)
                 for (int64_t r = K; r < K + take; ++r) errors_host[r] = err;      // (one error per iteration, repeated for its components)
             K += take;
             *rank_out = K;
             if (err <= tol || next <= 0) break;
-            if (!squares) enqueue(i + 1, ahead, next);
+            if (!squares) enqueue(i + 1, ahead, next, false);
             take = next;
             ahead += next;
             ++i;

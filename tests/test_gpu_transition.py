@@ -413,6 +413,35 @@ def test_transition_with_many_close_singular_values(tsvd, M, N):
     assert np.max(np.abs(np.array(errs) - np.array(eo))) <= 1e-9
 
 
+SHIFT_SPECTRA = {
+    "steps": 1.0 - 0.025 * np.arange(24),                                    # shifts that hold from the second pair on
+    "fall": 3.0 ** -np.arange(24),                                           # the second eigenvalue is lost beside the first: no shift
+    "shelf": np.concatenate([[1.0, 0.97, 0.94, 0.91], 0.2 - 0.004 * np.arange(20)]),   # a shift that lies above the next leading value
+}
+
+
+@pytest.mark.parametrize("q", [1, 3])
+@pytest.mark.parametrize("spectrum", list(SHIFT_SPECTRA))
+@pytest.mark.parametrize("M,N,seed", [(65, 64, 1), (150, 129, 2), (96, 400, 3), (400, 385, 4)])
+def test_pairs_squared_with_shifts_follow_the_oracle(tsvd, M, N, seed, spectrum, q):
+    """Nine components: each pair's squarings are shifted by what the pair before left, at sizes on both sides of a tile of either kind, with contractions shorter
+    than a workgroup's, where that value holds, is not known and is too large."""
+    rng = np.random.default_rng(seed)
+    r = 24
+    W = (np.linalg.qr(rng.standard_normal((M, r)))[0] * SHIFT_SPECTRA[spectrum]) @ np.linalg.qr(rng.standard_normal((N, r)))[0].T
+    rank, theta = 9, 0.65
+    Uo, So, Vo, eo = tr.transition(W, theta, q=q, max_rank=rank)
+    print(f"case shifts {M} {N} {spectrum} {q}", flush=True)
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(W), theta, 0.0, rank, q=q)
+    assert status == 0
+    U, S, V = U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy()
+    for k in range(rank):
+        sign = 1 if np.array_equal(U[:, k], Uo[:, k]) else -1
+        assert np.array_equal(sign * U[:, k], Uo[:, k]) and np.array_equal(sign * V[k, :], Vo[k, :]), k
+    assert np.max(np.abs(S - So)) <= 1e-8 * np.max(np.abs(So))
+    assert abs(errs[-1] - eo[-1]) <= 1e-9
+
+
 @pytest.mark.parametrize("spectrum", ["close", "equal"])
 def test_clustered_spectra_cost_little_more_than_others(tsvd, spectrum):
     """Singular values within 1e-6 of each other, and groups of 32 equal ones: the leading pair needs up to all of the squarings, an iteration that got
