@@ -12,6 +12,8 @@ struct tsvd_pair_state {
     int last;            // index of the squared matrix that is numerically of rank one, -1 while there is none
     int missed;          // pairs since it was last cleared whose squarings were not enough
     int needed;          // most squarings that a pair since it was last cleared should have had
+    int shifted_missed, shifted_needed;      // the same of pairs whose squarings were shifted
+    int far;             // pairs whose second eigenvalue came out below 2^-30 of the first: with little more between them it is lost in rounding
 };
 // ... and what pairs leave to the next one of the same sequence (tsvd_pair_sequence): the shifts s and traces t of X_{k+1} = ((X_k - s_k) / t_k)^2, and the second
 // eigenvalue of the X_{count} that the pair ended with.

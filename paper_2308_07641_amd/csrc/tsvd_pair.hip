@@ -305,8 +305,8 @@ tsvd_pair_start_kernel(double* __restrict__ v0, int N, tsvd_pair_state* state) {
     if (k < N) v0[k] = 1.0 + 0.5 * sin(1.0 + 0.7 * (double)k);
     if (k == 0) {
         state->last = -1;
-        state->missed = 0;
-        state->needed = 0;
+        state->missed = state->shifted_missed = 0;
+        state->needed = state->shifted_needed = state->far = 0;
     }
 }
 
@@ -442,14 +442,15 @@ tsvd_pair_tail_kernel(tsvd_pair_plan p, int count, int shifted) {
         // `over`: each squaring doubles the bits between the first pivot and the seventeenth, which are to become fifty; what is missed at the last
         // count that is tried is taken as it is (equal singular values: any vector of theirs will do).
         // (squarings with shifts: one fewer leaves two and a half to four times the pivots)
-        int want = r > 12 ? count + 1 : last >= 0 ? last + 1 : r <= (shifted && count <= 6 ? 3 : 5) ? max(count - 1, 1) : count;
+        int want = r > 12 ? count + 1 : last >= 0 ? last + 1 : r <= (shifted ? 3 : 5) ? max(count - 1, 1) : count;
         if (over && r == TAIL_RANK) {
             constexpr int LAST = TSVD_PAIR_MAX_SQUARINGS - 1;
             const double bits = log2(tol * 0x1p50 / row_j[TAIL_RANK]);      // (not above 0: pivots that are equal, as far as they are compared)
             want = count >= LAST ? TSVD_PAIR_MAX_SQUARINGS : bits > 0x1p-40 ? min(LAST, count + max(1, (int)ceil(log2(50.0 / bits)))) : LAST;
         }
-        if (over) ++p.state->missed;
-        p.state->needed = max(p.state->needed, want);
+        int* const report = shifted ? &p.state->shifted_missed : &p.state->missed;
+        if (over) ++report[0];
+        report[1] = max(report[1], want);
     }
     // ---- S = L^T L: a wavefront's share from its own 64 rows, then one wavefront
     f64x4 S = {0.0, 0.0, 0.0, 0.0};
@@ -500,6 +501,7 @@ tsvd_pair_tail_kernel(tsvd_pair_plan p, int count, int shifted) {
             if (lane == 0) {
                 shifts->second = !over && rest > 0x1p-46 * first ? fmin(rest, first) : 0.0;
                 shifts->count = last >= 0 ? last : count;
+                if (!(rest > 0x1p-30 * first)) ++p.state->far;
             }
         }
         square(1.0);

@@ -507,9 +507,9 @@ struct transition_state {
     int failed;              // ternarizations without a result
 };
 struct transition_report {
-    int missed, needed;      // of the pairs' squarings (tsvd_pair_state)
+    int missed, needed, shifted_missed, shifted_needed;      // of the pairs' squarings (tsvd_pair_state)
     int failed;
-    int resolved;            // the last pair left its second eigenvalue
+    int resolved;            // all pairs have left their second eigenvalue, and none was far below the first
 };
 static_assert(sizeof(transition_report) % 8 == 0, "doubles follow it");
 __global__ void __launch_bounds__(256)
@@ -519,8 +519,9 @@ tsvd_residual_rows_kernel(const double* __restrict__ W, const int8_t* __restrict
     extern __shared__ __align__(16) unsigned char smem[];
     double* us = reinterpret_cast<double*>(smem);               // [4][K]
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-        told[0] = {seen->pair.state.missed, seen->pair.state.needed, seen->failed, seen->pair.second > 0.0};
-        seen->pair.state.missed = seen->pair.state.needed = 0;  // (of one iteration each)
+        tsvd_pair_state& of = seen->pair.state;
+        told[0] = {of.missed, of.needed, of.shifted_missed, of.shifted_needed, seen->failed, of.far == 0 && seen->pair.second > 0.0};
+        of.missed = of.needed = of.shifted_missed = of.shifted_needed = of.far = 0;      // (of one iteration each)
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m0 = blockIdx.y * 4, m = m0 + wave, n = blockIdx.x * 256 + 4 * lane;
     for (int k = threadIdx.x; k < K; k += 256) {
@@ -939,7 +940,7 @@ extern "C" tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M
         tsvd_pair_prepare(M, N, workspace, &plan, s);
         const int limit = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(1, (int)max_steps));
         int count = 0;
-        for (tsvd_pair_state state = {-1, 0, 0}; count < limit && state.last < 0;) {
+        for (tsvd_pair_state state = {-1, 0, 0, 0, 0, 0}; count < limit && state.last < 0;) {
             const int to = std::min(limit, count == 0 ? 16 : count + 8);
             tsvd_pair_square(plan, R_dev, count, to, false, s);
             count = to;
@@ -1134,7 +1135,8 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     tsvd_pair_plan plan;
     if (squares) {
         tsvd_pair_prepare(M, N, base + at_svd, &plan, s);
-        tsvd_pair_sequence(&plan, &rep->pair);
+        plan.state = &rep->pair.state;
+        if (q == 1) tsvd_pair_sequence(&plan, &rep->pair);
         u = plan.u;
         v = plan.v;
     }
@@ -1151,9 +1153,10 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     bool first_pair = false;                                                 // in the plan already
     int least = 1;                                                           // squarings that iterations before `least_until` get
     int64_t least_until = 0;
-    // From the second iteration on pairs are shifted (tsvd_pair_square), two squarings fewer at first.  Where the pair before left no second eigenvalue, or too
-    // little came of the shifts, the iteration is taken without; for good after the second time that it had to be taken again.
-    bool resolved = false, by_shifts[2] = {false, false};
+    // With q = 1 pairs are shifted from the second iteration on (tsvd_pair_square), two squarings fewer at first.  Not where the last iteration known had a second eigenvalue far
+    // below its first, which the pair behind may then miss, nor after the second iteration that had to be taken again for the shifts.  (With more pairs an iteration one that
+    // misses takes all of them again: Laplace matrices gained 0.94, four an iteration, a linear spectrum took 1.5 times as long.)
+    bool resolved = false;
     int shifted = 0, shifted_least = 3, misses = 0;                          // squarings of a shifted pair
     if (any_rank && st == TSVD_OK) {
         tsvd_pair_shifts* left = reinterpret_cast<tsvd_pair_shifts*>(pinned + 2 * told_bytes);
@@ -1165,20 +1168,19 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
             from = squarings;
             first_pair = state->missed == 0 || squarings == TSVD_PAIR_MAX_SQUARINGS;
             squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, first_pair ? std::max(1, state->needed) : std::max(squarings + step + 1, state->needed));
-            resolved = left->second > 0.0;
+            resolved = left->second > 0.0 && state->far == 0;
             if (first_pair) break;
             step += 4;                                                       // (equal values beside others: the estimate stays short)
-            if (!ok(hipMemsetAsync(&rep->pair.state.missed, 0, 2 * sizeof(int), s))) break;       // (and what it needed)
+            if (!ok(hipMemsetAsync(&rep->pair.state.missed, 0, 5 * sizeof(int), s))) break;       // (and what it needed)
         }
     }
     double wnorm2 = 0.0;
     if (wait_for(0)) wnorm2 = rnorm2;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
     auto enqueue = [&](int64_t i, int64_t first, int64_t take, bool again) {
-        const bool shift = any_rank && i > 1 && resolved && !again && misses < 2;
+        const bool by_shifts = any_rank && q == 1 && i > 1 && resolved && !again && misses < 2;
         if (shifted == 0) shifted = std::max(6, squarings - 2);
-        const int count = shift ? shifted : squarings;
-        by_shifts[i & 1] = shift;
+        const int count = by_shifts ? shifted : squarings;
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
         // that triple removed, ... (the last iteration takes what still fits below max_rank)
         const double* src = R;
@@ -1189,8 +1191,8 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         for (int64_t j = 0; j < take; ++j) {
             if (squares) {
                 if (!first_pair) {
-                    tsvd_pair_square(plan, src, 0, count, shift, s);
-                    tsvd_pair_vectors(plan, src, count, any_rank, shift, s);
+                    tsvd_pair_square(plan, src, 0, count, by_shifts, s);
+                    tsvd_pair_vectors(plan, src, count, any_rank, by_shifts, s);
                 }
                 first_pair = false;
                 if (j + 1 < take) tsvd_pair_deflate(plan, Rwork, s);
@@ -1229,13 +1231,15 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
             if (squares && next > 0) enqueue(i + 1, ahead, next, false);
             if (st != TSVD_OK || !wait_for(i)) break;
             resolved = seen.resolved != 0;
-            if (seen.missed != 0 && (by_shifts[i & 1] || seen.needed < TSVD_PAIR_MAX_SQUARINGS)) {
+            const bool missed = seen.missed != 0 && seen.needed < TSVD_PAIR_MAX_SQUARINGS;
+            if (missed || seen.shifted_missed != 0) {
                 // some pair needed more squarings: back to the residual before this iteration, with more of them, and for a while
                 // with one more than were too few (spectra on the edge of two counts missed every eighth iteration)
-                if (by_shifts[i & 1]) {
+                if (seen.shifted_missed != 0) {
                     ++misses;
                     shifted = shifted_least = std::min(TSVD_PAIR_MAX_SQUARINGS, shifted + 1);
-                } else {
+                }
+                if (missed) {
                     if (any_rank && i > 1) {
                         least = std::min(seen.needed, squarings + 1);
                         least_until = i + 16;
@@ -1252,8 +1256,8 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
                 st = TSVD_EVALUE;           // no ternary vector within theta: the components of an unfinished iteration are dropped
                 break;
             }
-            if (by_shifts[i & 1]) shifted = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(shifted_least, seen.needed));
-            else squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(i < least_until ? least : 1, seen.needed) : std::max(16, seen.needed + 2));
+            if (seen.shifted_needed > 0) shifted = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(shifted_least, seen.shifted_needed));
+            if (seen.needed > 0 || !any_rank) squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(i < least_until ? least : 1, seen.needed) : std::max(16, seen.needed + 2));
             const double err = std::sqrt(rnorm2 / wnorm2);
             if (errors_host)
                 for (int64_t r = K; r < K + take; ++r) errors_host[r] = err;      // (one error per iteration, repeated for its components)
