@@ -77,7 +77,8 @@ tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M, int64_t N
  * pseudo-inverse of Eq. (3) selects (tsvd_fit_scales, started from zero, gives that one).
  * Returns TSVD_EVALUE if some leading vector has no ternary vector within theta (the paper's
  * algorithm raises an error there); the components found so far are kept in *rank_out.
- * max_rank <= 2048, M, N <= 8192.  Allocates and frees its own device scratch. */
+ * max_rank <= 2048, M, N <= 8192.  Allocates its own device and pinned scratch; up to four pieces of at most 64 MiB of device and
+ * 1 MiB of pinned memory each are kept for later calls (of any thread, stream and device), until tsvd_transition_release. */
 tsvd_status tsvd_transition(const double* W_dev, int64_t M, int64_t N, double theta, double tol, int64_t max_rank,
                             int8_t* U_dev, double* S_dev, int8_t* V_dev, int64_t* rank_out, double* errors_host,
                             void* stream);
@@ -91,6 +92,9 @@ tsvd_status tsvd_transition(const double* W_dev, int64_t M, int64_t N, double th
  * 1 <= q <= min(M, N, max_rank); everything else as for tsvd_transition, which is this call with q = 1. */
 tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t N, double theta, double tol, int64_t max_rank, int64_t q,
                               int8_t* U_dev, double* S_dev, int8_t* V_dev, int64_t* rank_out, double* errors_host, void* stream);
+
+/* Frees the scratch that finished calls of tsvd_transition and tsvd_transition_q left for later ones.  Calls that are running keep theirs. */
+void tsvd_transition_release(void);
 
 #ifdef __cplusplus
 }

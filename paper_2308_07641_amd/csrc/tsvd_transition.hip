@@ -15,6 +15,7 @@
 
 #include "../../include/tsvd_transition.h"
 #include "tsvd_pair.h"
+#include "tsvd_scratch.h"
 #include "tsvd_wave.h"
 
 #define TERN_MAX_N 8192
@@ -23,6 +24,12 @@
 namespace {
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// (never destroyed: the runtime may be gone by then, and takes the memory with it)
+tsvd_scratch_pool& scratch_pool() {
+    static tsvd_scratch_pool* pool = new tsvd_scratch_pool;
+    return *pool;
+}
 
 // Sum over the 256 threads of a workgroup, in a fixed order (tree in LDS); result in every thread.
 __device__ __forceinline__ double block_sum256(double v, double* red) {
@@ -1074,21 +1081,10 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     const size_t bytes_svd = tsvd_leading_singular_pair_workspace(M, N), at_svd = reserve(bytes_svd);
     // what the host reads after an iteration (two in turn, written by the device): the report, and the residual's sums of squares
     const size_t told_bytes = round256(sizeof(transition_report) + (size_t)M * pieces * 8);
-    uint8_t *base = nullptr, *pinned = nullptr;
-    hipEvent_t event[2] = {nullptr, nullptr};
-    auto release = [&] {
-        for (hipEvent_t e : event)
-            if (e) (void)hipEventDestroy(e);
-        if (pinned) (void)hipHostFree(pinned);
-        if (base) (void)hipFree(base);
-    };
-    if (hipMalloc(reinterpret_cast<void**>(&base), total) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&pinned), 2 * told_bytes + sizeof(tsvd_pair_shifts), hipHostMallocDefault) != hipSuccess ||
-        hipEventCreateWithFlags(&event[0], hipEventDisableTiming) != hipSuccess || hipEventCreateWithFlags(&event[1], hipEventDisableTiming) != hipSuccess) {
-        release();
-        (void)hipGetLastError();
-        return TSVD_EDEVICE;
-    }
+    tsvd_scratch scratch;
+    if (!scratch_pool().take(total, 2 * told_bytes + sizeof(tsvd_pair_shifts), &scratch)) return TSVD_EDEVICE;
+    uint8_t *const base = scratch.base, *const pinned = scratch.pinned;
+    hipEvent_t* const event = scratch.event;
     double* R = reinterpret_cast<double*>(base + at_R);
     double* Rwork = reinterpret_cast<double*>(base + at_Rwork);
     int8_t* Ut = reinterpret_cast<int8_t*>(base + at_Ut);                    // [max_rank][mp]
@@ -1274,7 +1270,9 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     if (st == TSVD_OK || st == TSVD_EVALUE)
         hipLaunchKernelGGL(tsvd_emit_kernel, dim3(256), dim3(256), 0, s, Ut, mp, Vs, np, scales[kept % 3], (int)M, (int)N, (int)*rank_out, (int)max_rank, U_dev, V_dev,
                            S_dev);
-    (void)hipStreamSynchronize(s);
-    release();
+    const bool done = hipStreamSynchronize(s) == hipSuccess;
+    scratch_pool().give(scratch, done);
     return st;
 }
+
+extern "C" void tsvd_transition_release(void) { scratch_pool().release(); }

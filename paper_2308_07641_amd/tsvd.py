@@ -58,6 +58,7 @@ _PROTOTYPES = {
     "tsvd_leading_singular_pair_workspace": (_sz, [_i64, _i64]),
     "tsvd_leading_singular_pair": (ctypes.c_int, [_vp, _i64, _i64, ctypes.c_int32, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "tsvd_transition": (ctypes.c_int, [_vp, _i64, _i64, ctypes.c_double, ctypes.c_double, _i64, _vp, _vp, _vp, _pi64, _vp, _vp]),
+    "tsvd_transition_release": (None, []),
     "tsvd_transition_q": (ctypes.c_int, [_vp, _i64, _i64, ctypes.c_double, ctypes.c_double, _i64, _i64, _vp, _vp, _vp, _pi64, _vp, _vp]),
     "tsvd_conv2d_workspace_bytes": (_sz, [_vp, _vp, _i64, _i64, _i64]),
     "tsvd_conv2d_forward": (ctypes.c_int, [_vp, _vp, _vp, _i64, _i64, _i64, _vp, _vp, ctypes.c_int, _vp, _sz, _vp]),
@@ -409,6 +410,11 @@ def tsvd_transition(W, theta: float, tol: float, max_rank: int, stream=None, q: 
     if status != 0 and not (status == 2 and K > 0):
         _check(status, "tsvd_transition")
     return U[:, :K].contiguous(), S[:K].clone(), V[:K, :].contiguous(), errors[:K].tolist(), status
+
+
+def tsvd_transition_release() -> None:
+    """Frees the scratch that finished transitions left for later ones."""
+    load_library().tsvd_transition_release()
 
 
 # ---- convolution forms (include/tsvd_conv.h)

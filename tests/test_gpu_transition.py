@@ -380,6 +380,44 @@ def test_transition_on_a_laplace_matrix(tsvd):
     assert 0.25 < r < 0.33
 
 
+def test_transition_scratch_is_reused_by_calls_of_any_size_thread_and_stream(tsvd):
+    """Scratch that other sizes left behind, threads with streams of their own at the same time, more of them than pieces are kept, and calls after the
+    scratch was given back: every result is the one of a call on fresh scratch."""
+    import threading
+    import torch
+    rng = np.random.default_rng(21)
+    cases = [(96, 80, 5, 1), (40, 130, 6, 2), (300, 64, 4, 1), (130, 129, 5, 3), (20, 70, 3, 1), (1500, 900, 2, 1)]
+    Ws = [_dev(rng.laplace(size=c[:2])) for c in cases]
+    def run(i, stream=None):
+        M, N, rank, q = cases[i]
+        U, S, V, errs, status = tsvd.tsvd_transition(Ws[i], 0.65, 0.0, rank, stream=stream, q=q)
+        (stream or torch.cuda.current_stream()).synchronize()
+        return U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy(), errs, status
+    def same(a, b):
+        return all(np.array_equal(x, y) for x, y in zip(a, b))
+    want = []
+    for i in range(len(cases)):
+        tsvd.tsvd_transition_release()
+        want.append(run(i))
+    print("case transition scratch", flush=True)
+    for i in [0, 3, 1, 5, 0, 2, 4, 3, 5, 1]:
+        assert same(run(i), want[i]), i
+    got = {}
+    def work(t):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for i in range(len(cases)):
+                got[t, i] = run((i + t) % len(cases), stream)
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(got) == 36 and all(same(r, want[(i + t) % len(cases)]) for (t, i), r in got.items())
+    tsvd.tsvd_transition_release()
+    assert same(run(1), want[1])
+
+
 def test_transition_of_equal_singular_values(tsvd):
     """A Hadamard matrix: all singular values equal, so no number of squarings leaves a matrix of low rank and any vector will do; the
     pair taken is a unit vector and a column (or row), which is ternary, and every component removes one of 32."""
