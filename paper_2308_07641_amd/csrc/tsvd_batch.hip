@@ -134,6 +134,34 @@ double panel_cost(const tsvd_batch_call& c) {
     return 0.95 * r * (7.5 + 2.3 * (double)nvb + 1.8 * (double)(up(strips, 8) * nub) + (double)strips * (c.y_token_major ? 1.9 : 0.83));
 }
 
+// fp32 activations run on planes whatever the shapes, so theirs are chosen by factors of their own up to 1024 tokens, fitted to the kernels as they are (kernel traces of 180 calls, 90 of them
+// fp32, each with all shapes: 10 to 17 % rms; the shapes taken are 0.6 % slower than the best of each stage, those of the factors above 5 %: those know neither that wavefronts take blocks of
+// their own nor what y costs).  Beyond, where rounds of many workgroups follow each other, they take split tiles too often (3520 x 2156 x 6144 at 6540 tokens 631 -> 758 us, 768 x 911 x 512 at 10040
+// 69 -> 74).  1898 x 1344 x 1120 at 211 tokens 22.4 -> 17.2 us, 4655 x 1408 x 114 at 23 17.4 -> 12.2, 455 x 1052 x 263 at 896 19.6 -> 13.5.
+struct own_factors {
+    int shape;
+    double v0, v_round, v_step, v_made, planes, planes_each, u0, u_round, u_step, u_mb;
+};
+constexpr own_factors f32_table[] = {
+    {9, 2.06, 1.18, 1.09, 1.21, 5.4, 6.3, 1.33, 1.02, 1.19, 0.086},
+    {10, 0.88, 3.70, 0.83, 1.13, 3.7, 7.2, 1.11, 1.08, 0.94, 0.183},
+    {18, 0.0, 4.19, 2.24, 1.30, 5.1, 7.8, 1.80, 1.44, 2.64, 0.259},
+    {20, 0.0, 5.59, 1.79, 1.41, 5.3, 7.9, 1.07, 4.41, 2.03, 0.194},
+};
+// rounds of workgroups, and what the slowest wavefront of one multiplies: blocks of its own times token tiles (128 rows), steps of four records (256 rows)
+double own_v_cost(const sizes& s, const own_factors& f) {
+    const long long n = s.sets * s.nvb, tiles = f.shape & 7;
+    const double r = rounds(s, f.shape, s.nub), steps = f.shape < 16 ? (double)(up(n, 8) * tiles) : (double)up(up(n * tiles, 4), 4);
+    const bool makes = tsvd_fp6_split_makes_x(f.shape, (int)std::min<long long>(n, 1 << 20));
+    return f.v0 + r * (f.v_round + f.v_step * steps) +
+           (makes ? r * f.v_made * (double)(up(s.nvb * tiles, 8) * s.sets) : f.planes + f.planes_each * (double)(s.nvb * up(s.B, 16) * s.sets) / 4096);
+}
+double own_u_cost(const sizes& s, const own_factors& f, bool out_bf16) {
+    const long long n = s.sets * s.nub, tiles = f.shape & 7;
+    const double r = rounds(s, f.shape, up(s.M, 128)), steps = f.shape < 16 ? (double)(up(n, 8) * tiles) : (double)up(up(n * tiles, 4), 4);
+    return f.u0 + r * (f.u_round + f.u_step * steps) + f.u_mb * (double)s.M * (double)s.B * (out_bf16 ? 2e-6 : 4e-6);
+}
+
 // The shapes of the plane path's stages, 0 each for the tiles of tsvd_fp6.hip.
 struct tiles_choice {
     int v, u;
@@ -143,6 +171,15 @@ tiles_choice choose_tiles(const tsvd_batch_call& c) {
     const sizes s = {c.M, c.N, c.B, c.cus, up(c.N, 128), up(c.K, 128), c.f32 ? 2 : 1};
     double best_v = split_v_cost(s, nullptr), best_u = split_u_cost(s, nullptr);
     tiles_choice t = {0, 0, 0, best_v + best_u};
+    if (c.f32 && c.B <= 1024) {
+        for (const own_factors& f : f32_table) {
+            const double cv = own_v_cost(s, f), cu = own_u_cost(s, f, c.out_bf16);
+            if (cv < best_v) best_v = cv, t.v = f.shape;
+            if (cu < best_u) best_u = cu, t.u = f.shape;
+        }
+        t.time = best_v + best_u;
+        return t;
+    }
     for (const split_factors& f : split_table) {
         const double cv = split_v_cost(s, &f), cu = split_u_cost(s, &f);
         if (cv < best_v) best_v = cv, t.v = f.shape;
