@@ -10,6 +10,8 @@
 // Eight wavefronts.  Planes of x are made block by block (a wavefront per record: gather, convert); wavefront w multiplies the
 // rank blocks w, w + 8, ... of stage V (128 rows x the panel; its result lanes are stage U's operand lanes, see tsvd_panel_fp6_kernel)
 // and writes their planes of z beside those of x; then stage U runs in units of 16 UTM rows, no barrier between them.
+// Where stage V's rank blocks do not go round, wavefronts share some: each a part of the contraction, sums added in LDS (3 x 3 from 310 channels, rank 119, two images of 28 x 28: 18.1 -> 14.2 us;
+// 5 x 5 from 198, rank 213, twelve of 28 x 28: 101 -> 90; 3456 x 7104 x 193, rows of tokens, at 2801 40.3 -> 36.3; 512 x 1536 x 1280 at 13568 84.1 -> 81.6; 110 drawn calls of which 40 share 0.987 of the time).
 // Where x does not fit beside z its blocks pass through in chunks, two in LDS: four of the wavefronts multiply the one before
 // they make their records of the next, the other four after, so that on every SIMD matrix and vector instructions overlap.
 // Code words go from the L2s to registers, one fetch ahead across rank blocks and units (those of the next unit are in
@@ -40,6 +42,7 @@ struct thin_args {
     const uint16_t* x;
     unsigned x_bytes;                        // below 2^31
     int N, B, chunk, buffers;        // blocks of x per chunk, chunks in LDS (1: all of x, or 2)
+    unsigned char whole, shared, parts;      // SHARED: of stage V's last rank blocks the first `whole` a wavefront each, `shared` more 1 << parts wavefronts each (thin_shares)
     long long ldx;
     int images, H, W, kv1, kv2, Hv, Wv, s1, s2, p1, p2, d1, d2;
     const float* S;
@@ -50,11 +53,19 @@ struct thin_args {
     int runs;                                // neighbouring panels on one XCD
     int slices;                              // workgroups of a panel, each with the whole z and its part of y's rows
 };
+// (Another line of arguments is 0.3 us a call: the first load of each comes from memory.)
+static_assert(sizeof(thin_args) == 192, "three lines");
+
+// bytes of LDS for records of x, and then for the sums of the wavefronts that share a block
+__host__ __device__ inline int thin_x_bytes(const thin_args& p, int tiles, bool shared) {
+    const int records = p.buffers * p.chunk * tiles * FP6_REC_BYTES, sums = shared ? p.shared * ((1 << p.parts) - 1) * tiles * 8192 : 0;
+    return records > sums ? records : sums;
+}
 
 // THIN_CONV whose V takes rows of three taps side by side, of images of four columns and more: a row is one load of four elements.
 constexpr int THIN_CONV_ROWS = 3;
 
-template <int TN, int RB, int SOURCE, bool CHUNKED>
+template <int TN, int RB, int SOURCE, bool CHUNKED, bool SHARED>
 __global__ void __launch_bounds__(512, 2)
 tsvd_thin_panel_kernel(thin_args p) {
     constexpr int NW = 8;
@@ -69,7 +80,7 @@ tsvd_thin_panel_kernel(thin_args p) {
     const int xcd = panel & 7, per = panels >> 3, more = panels & 7;
     const int b0 = (p.runs ? xcd * per + min(xcd, more) + (panel >> 3) : panel) * 16 * TN;
     unsigned char* xrec = smem;
-    unsigned char* zrec = smem + p.buffers * p.chunk * TN * FP6_REC_BYTES;
+    unsigned char* zrec = smem + thin_x_bytes(p, TN, SHARED);
     const int* ktab = reinterpret_cast<const int*>(zrec + p.nub * TN * FP6_REC_BYTES);   // THIN_CONV: byte offset of index k in the images
     const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles_v), 0, p.tile_v_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t u_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.tiles_u), 0, p.tile_u_bytes, 0x00020000);
@@ -264,16 +275,23 @@ tsvd_thin_panel_kernel(thin_args p) {
                 for (int b = 0; b < TN; ++b) acc[r][a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
         const int gg = i >> 2, vv = i & 3;
         const int voff = ((4 * (gg & 1) + (gg >> 1)) * p.nkt_v) * 1024 + (g * 16 + vv) * 16;
-        const int ranks = wave < p.nub ? (p.nub - 1 - wave) / NW + 1 : 0;      // rank blocks of this wavefront
-        int nc = 0, nr = 0, nb = 0;                           // the next fetch: first block of the chunk, rank block, block of the chunk
+        // this wavefront's last rank block, and its part of the block's contraction
+        const int mine = wave - p.whole;
+        const bool helps = SHARED && mine >= 0;
+        const int part = helps ? mine >> (p.shared - 1) : 0, last_rank = NW * (RB - 1) + (helps ? p.whole + (mine & (p.shared - 1)) : wave);
+        const bool has_last = SHARED ? !helps || part >> p.parts == 0 : last_rank < p.nub;
+        const int ranks_most = wave < p.nub ? (p.nub - 1 - wave) / NW + 1 : 0;
+        int nc = 0, nr = 0, nb = 0, ranks = ranks_most, from = 0, to = 0;     // the next fetch: first block of the chunk, rank block, block of the chunk; rank blocks, and blocks of the last one's
         auto next = [&](words (&w)[8]) {
+            const bool last = SHARED && (RB == 1 || nr == RB - 1);
+            const int rank = last ? last_rank : wave + NW * nr;
 #pragma unroll
             for (int a = 0; a < 8; ++a)
-                w[a] = fetch(v_rsrc, voff, (8 * (wave + NW * nr) + 2 * (a >> 2)) * p.nkt_v * 1024 + 4 * (a & 3) * 16, nc + nb);
-            if (nb + PER < min(p.chunk, p.nvb - nc)) nb += PER;
+                w[a] = fetch(v_rsrc, voff, (8 * rank + 2 * (a >> 2)) * p.nkt_v * 1024 + 4 * (a & 3) * 16, nc + nb);
+            if (nb + PER < (last ? to : min(p.chunk, p.nvb - nc))) nb += PER;
             else if (nr + 1 < ranks) {                        // (at the end: the last fetch again)
                 ++nr;
-                nb = 0;
+                nb = SHARED && nr == RB - 1 ? from : 0;
             }
         };
         auto make = [&](int c0) __attribute__((always_inline)) {
@@ -282,8 +300,10 @@ tsvd_thin_panel_kernel(thin_args p) {
             // Beside the multiplication of a chunk: wavefronts of fewer rank blocks first make as many records as take its time, a fifth of them, then all
             // in turn.  (Records of a convolution's single elements are bound by the address unit, whoever makes them: 315 -> 320 us with this on 228 x 12800 x 388.)
             constexpr int SIDES = NW / TN;
-            const int side = wave / TN, tile = wave % TN, busy = (p.nub % NW + TN - 1 - tile) / TN, idle = SIDES - busy;
-            const int own = CHUNKED && SOURCE != THIN_CONV && c0 > 0 && busy > 0 && idle > 0 ? idle * min(blocks * TN / 5, blocks / idle) : 0;
+            const int side = wave / TN, tile = wave % TN, heavy = !SHARED ? p.nub % NW : p.whole ? p.whole : p.shared << p.parts;
+            const int busy = (heavy + TN - 1 - tile) / TN, idle = SIDES - busy, part_of = SHARED ? blocks * TN >> p.parts : 0;
+            const int spare = SHARED && !p.whole ? part_of : blocks * TN - part_of;      // by how much the others multiply less
+            const int own = CHUNKED && SOURCE != THIN_CONV && c0 > 0 && busy > 0 && idle > 0 ? idle * min(spare / 5, blocks / idle) : 0;
             const int rest = own + (own ? SIDES - 1 - side : side);
             bool first = own > 0 && side >= busy;
             for (int q = first ? side - busy : rest; q < blocks;) {
@@ -306,20 +326,52 @@ tsvd_thin_panel_kernel(thin_args p) {
                 words w0[8];                                  // (not kept over the making of records: the registers are needed there)
                 nc = c0;
                 nr = nb = 0;
+                if (SHARED) to = blocks;
+                if (SHARED) from = 0;
+                if (helps) {                                  // (whole fetches, of two blocks each)
+                    const int fetches = (blocks + PER - 1) / PER;
+                    from = PER * (fetches * part >> p.parts);
+                    to = min(blocks, PER * (fetches * (part + 1) >> p.parts));
+                }
+                if constexpr (SHARED) {
+                    ranks = RB - 1 + (has_last && from < to ? 1 : 0);
+                    if (RB == 1) nb = from;
+                }
                 if (ranks > 0) next(w0);
 #pragma unroll
                 for (int r = 0; r < RB; ++r)
-                    if (r < ranks) run(std::integral_constant<int, 8>{}, rec, blocks, w0, next, acc[r]);
+                    if (r < ranks) {
+                        if (SHARED && r == RB - 1) run(std::integral_constant<int, 8>{}, rec + from * TN * FP6_REC_BYTES, to - from, w0, next, acc[r]);
+                        else run(std::integral_constant<int, 8>{}, rec, blocks, w0, next, acc[r]);
+                    }
                 if (!decltype(make_first)::value && more) make(c0 + p.chunk);
                 if (more) __syncthreads();
             }
         };
         if (CHUNKED && wave >= NW / 2) chunks(std::true_type{});
         else chunks(std::false_type{});
+        if constexpr (SHARED) {                               // the parts' sums meet where the records of x were
+            __syncthreads();
+            f32x4* sums = reinterpret_cast<f32x4*>(smem) + lane;
+            if (has_last && part > 0) {
+#pragma unroll
+                for (int a = 0; a < 8; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) sums[((mine - p.shared) * 8 * TN + a * TN + b) * 64] = acc[RB - 1][a][b];
+            }
+            __syncthreads();
+            if (helps && part == 0) {
+                for (int q = 0; q + 1 < 1 << p.parts; ++q)
+#pragma unroll
+                    for (int a = 0; a < 8; ++a)
+#pragma unroll
+                        for (int b = 0; b < TN; ++b) acc[RB - 1][a][b] += sums[((mine + q * p.shared) * 8 * TN + a * TN + b) * 64];
+            }
+        }
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
-            const int rank = wave + NW * r;
-            if (rank >= p.nub) break;
+            const int rank = r == RB - 1 ? last_rank : wave + NW * r;
+            if (r == RB - 1 && (!has_last || part > 0)) break;
             f32x4 sv[8];
 #pragma unroll
             for (int a = 0; a < 8; ++a)       // z = S (V x) / 4: the codes of either stage multiply as +-2
@@ -438,27 +490,31 @@ tsvd_thin_panel_kernel(thin_args p) {
     else stage_u(std::integral_constant<int, 2>{});
 }
 
+inline bool thin_rows_of_taps(int source, const thin_args& a) { return source == THIN_CONV && a.kv2 == 3 && a.d2 == 1 && a.W >= 4; }
+
 constexpr int LDS_BYTES = 160 * 1024, MAX_TAPS = 48;
 
-template <int TN, int RB, int SOURCE, bool CHUNKED>
-auto kernel() { return tsvd_thin_panel_kernel<TN, RB, SOURCE, CHUNKED>; }
+template <int TN, int RB, int SOURCE, bool CHUNKED, bool SHARED>
+auto kernel() { return tsvd_thin_panel_kernel<TN, RB, SOURCE, CHUNKED, SHARED>; }
 template <int TN, int RB, int SOURCE>
-hipError_t launch(const thin_args& a, int lds, hipStream_t stream) {
+hipError_t launch(const thin_args& a, bool shared, int lds, hipStream_t stream) {
     const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN)) * (unsigned)a.slices), block(512);
-    if (a.buffers == 2) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true>()), grid, block, lds, stream, a);
-    else hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false>()), grid, block, lds, stream, a);
+    if (a.buffers == 2 && shared) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true, true>()), grid, block, lds, stream, a);
+    else if (a.buffers == 2) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true, false>()), grid, block, lds, stream, a);
+    else if (shared) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false, true>()), grid, block, lds, stream, a);
+    else hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false, false>()), grid, block, lds, stream, a);
     return hipGetLastError();
 }
 template <int TN, int RB>
-hipError_t launch(int source, const thin_args& a, int lds, hipStream_t stream) {
-    if (source == THIN_CONV && a.kv2 == 3 && a.d2 == 1 && a.W >= 4) return launch<TN, RB, THIN_CONV_ROWS>(a, lds, stream);
-    if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, lds, stream);
-    if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, lds, stream);
-    return launch<TN, RB, THIN_FEATURE_MAJOR>(a, lds, stream);
+hipError_t launch(int source, const thin_args& a, bool shared, int lds, hipStream_t stream) {
+    if (thin_rows_of_taps(source, a)) return launch<TN, RB, THIN_CONV_ROWS>(a, shared, lds, stream);
+    if (source == THIN_CONV) return launch<TN, RB, THIN_CONV>(a, shared, lds, stream);
+    if (source == THIN_TOKEN_MAJOR) return launch<TN, RB, THIN_TOKEN_MAJOR>(a, shared, lds, stream);
+    return launch<TN, RB, THIN_FEATURE_MAJOR>(a, shared, lds, stream);
 }
 template <int TN, int RB, int SOURCE>
 hipError_t init() {
-    for (const auto k : {kernel<TN, RB, SOURCE, false>(), kernel<TN, RB, SOURCE, true>()}) {
+    for (const auto k : {kernel<TN, RB, SOURCE, false, false>(), kernel<TN, RB, SOURCE, true, false>(), kernel<TN, RB, SOURCE, false, true>(), kernel<TN, RB, SOURCE, true, true>()}) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
     }
@@ -499,6 +555,20 @@ int tsvd_thin_chunk(long long K, long long N, int tiles, bool conv) {
     if (most < 2) return 0;
     const long long chunks = (nvb + most - 1) / most;
     return (int)std::min(most, ((nvb + chunks - 1) / chunks + 1) & ~1ll);
+}
+
+// Stage V's last `left` rank blocks (1 to 8): where one or two are left several wavefronts share each, a part of its contraction everyone; of five or six the first four stay
+// whole, one on each SIMD, and the other four wavefronts share the rest.  Of three, four or seven no SIMD has less than without, and shared they cost 3 to 6 % (3 x 3 from 69 channels, rank 412).
+// The sums meet behind two more barriers, 0.3 us: worth it from three blocks that the longest part is shorter by, six where a SIMD has a whole one beside (85 channels, rank 704: 12.4 -> 12.7 us).
+// Rows of taps in chunks are dear to make: with two rank blocks the six others make them all in the time that these two take (491 channels, rank 147: 36.2 -> 37.7 shared).
+static bool thin_shares(thin_args& a, int tiles, int left, int room, bool rows_of_taps) {
+    a.whole = left > 4 ? 4 : 0;
+    a.shared = left - a.whole;
+    a.parts = 0;
+    if (a.shared > 2 || (rows_of_taps && a.buffers == 2 && a.nub == 2)) return false;
+    while (a.shared << (a.parts + 1) <= 8 - a.whole && 2 << a.parts <= (a.chunk + 1) / 2) ++a.parts;
+    const int sums = a.shared * ((1 << a.parts) - 1) * tiles * 8192, longest = (a.nvb + (1 << a.parts) - 1) >> a.parts;
+    return sums <= room && (a.nvb - longest) * tiles >= (a.whole ? 6 : 3);
 }
 
 hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t stream) {
@@ -554,9 +624,11 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
     a.chunk = tsvd_thin_chunk(hd.K, hd.N, tiles, conv);
     if (a.chunk == 0) return hipErrorNotSupported;
     a.buffers = a.chunk < a.nvb ? 2 : 1;
-    const int lds = (a.buffers * a.chunk + a.nub) * tiles * FP6_REC_BYTES + (conv ? a.nvb * 512 : 0), rb = (a.nub + 7) / 8;
-    if (tiles == 1 && rb == 1) return launch<1, 1>(g.source, a, lds, stream);
-    if (tiles == 1 && rb == 2) return launch<1, 2>(g.source, a, lds, stream);
-    if (tiles == 2 && rb == 1) return launch<2, 1>(g.source, a, lds, stream);
+    const int rb = (a.nub + 7) / 8;
+    const bool shared = thin_shares(a, tiles, (a.nub + 7) % 8 + 1, LDS_BYTES - a.nub * tiles * FP6_REC_BYTES - (conv ? a.nvb * 512 : 0), thin_rows_of_taps(g.source, a));
+    const int lds = thin_x_bytes(a, tiles, shared) + a.nub * tiles * FP6_REC_BYTES + (conv ? a.nvb * 512 : 0);
+    if (tiles == 1 && rb == 1) return launch<1, 1>(g.source, a, shared, lds, stream);
+    if (tiles == 1 && rb == 2) return launch<1, 2>(g.source, a, shared, lds, stream);
+    if (tiles == 2 && rb == 1) return launch<2, 1>(g.source, a, shared, lds, stream);
     return hipErrorNotSupported;
 }

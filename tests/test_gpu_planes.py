@@ -208,6 +208,16 @@ def test_thin_panels_of_several_workgroups(tsvd, M, N, K, B, tiles):
     _check(tsvd, M, N, K, B, "bf16", {"TSVD_THIN": tiles})
 
 
+@pytest.mark.parametrize("M,N,K,B", [(70, 300, 128, 33), (70, 513, 129, 40), (40, 900, 256, 17), (50, 2000, 60, 35), (40, 1030, 640, 31), (70, 1500, 700, 33), (30, 5000, 100, 50), (30, 4700, 250, 40),
+                                     (30, 4100, 620, 33), (60, 1030, 1100, 20), (60, 4000, 1280, 18), (30, 2100, 1664, 35), (30, 3000, 1700, 33)])
+@pytest.mark.parametrize("tiles", [1, 2])
+def test_thin_panels_share_rank_blocks(tsvd, M, N, K, B, tiles):
+    """One, two, five and six rank blocks that do not go round, alone or behind eight that do: two to eight wavefronts share a block's contraction, some with nothing of
+    it where there is little or in the last chunk; x as a whole and in chunks.  (The bound is that of test_thin_panels: sums of fp32 in another order.)"""
+    print(f"case thin shares {M} {N} {K} {B} {tiles}", flush=True)
+    _check(tsvd, M, N, K, B, "bf16", {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_THIN": tiles, "TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 9})
+
+
 @pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("own_x", [0, 1])
 @pytest.mark.parametrize("v,u", [(9, 9), (10, 10)])
