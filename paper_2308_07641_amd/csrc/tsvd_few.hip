@@ -99,6 +99,26 @@ __device__ __forceinline__ double row_sum(const unsigned char* strip, int row, i
 }
 __device__ __forceinline__ bool in_fp32(float z) { return fabsf(z) <= 3.402823466e38f; }        // (false for NaN)
 
+// The arguments of either kernel.  They are passed one by one, and the first fourteen words come preloaded in registers: a load from the others takes 0.3 us, and
+// everything waited for it in either launch (16384 x 4096 x 8192 at 16 tokens 16.65 -> 16.2 us, 428 x 949 x 320 at 7 6.75 -> 6.25, 10543 x 726 x 138 at 12
+// 8.55 -> 8.0; of 25 drawn calls of 2 to 16 tokens the 13 that come here take 0.92 to 0.98 of the time).
+struct tsvd_few_v_args {
+    const unsigned char* tiles;
+    const uint16_t* x;
+    const float* S;
+    unsigned char* planes;
+    int nkt, ld, N, B, blocks, z_planes;
+};
+struct tsvd_few_u_args {
+    const unsigned char *tiles, *planes;
+    void* y;
+    const float* bias;
+    long long ld;
+    int nkt, blocks, strips, B, M;
+    int strips_wg, rows_log2, token_major, out_bf16;         // one word: tsvd_few_u_form
+};
+unsigned tsvd_few_u_form(const tsvd_few_args& a, int waves) { return (unsigned)a.strips_wg | (unsigned)a.rows_log2 << 8 | (a.token_major ? 1u << 16 : 0u) | (a.out_bf16 ? 1u << 17 : 0u) | (unsigned)waves << 20; }
+
 }  // namespace
 
 // Stage V.  Workgroup (b, t) of kw wavefronts: SW strips, tokens 16 t ...; wavefront q: tile columns q, q + kw, ...
@@ -110,7 +130,8 @@ __device__ __forceinline__ bool in_fp32(float z) { return fabsf(z) <= 3.40282346
 // NARROW: eight tokens at most: half of the chunks (the other columns of the products hold what stands there, and nobody reads them).
 template <bool TOKENS, bool NARROW, int KWL, int SW>
 __global__ void __launch_bounds__(64 << KWL)
-tsvd_few_v_kernel(tsvd_few_args p) {
+tsvd_few_v_kernel(const unsigned char* p_tiles, const uint16_t* p_x, const float* p_S, unsigned char* p_planes, int p_nkt, int p_ld, int p_N, int p_B, int p_blocks, int p_z_planes) {
+    const tsvd_few_v_args p = {p_tiles, p_x, p_S, p_planes, p_nkt, p_ld, p_N, p_B, p_blocks, p_z_planes};
     constexpr int kw = 1 << KWL;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -292,12 +313,13 @@ tsvd_few_v_kernel(tsvd_few_args p) {
 // Stage U.  The records of two blocks (256 rank positions) in registers, 25 or 32 each; a block's next record is requested when its products are issued.
 template <int PLANES, int KWL, int SW>
 __global__ void __launch_bounds__(1024)
-tsvd_few_u_kernel(tsvd_few_args p) {
+tsvd_few_u_kernel(const unsigned char* p_tiles, const unsigned char* p_planes, const float* p_bias, int p_nkt, int p_blocks, int p_strips, int p_B, int p_M, unsigned p_form, void* p_y, long long p_ld) {
+    tsvd_few_u_args p = {p_tiles, p_planes, nullptr, p_bias, 0, p_nkt, p_blocks, p_strips, p_B, p_M, (int)(p_form & 31), (int)(p_form >> 8 & 31), (int)(p_form >> 16 & 1), (int)(p_form >> 17 & 1)};
     constexpr int kw = 1 << KWL;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, g = lane >> 4, q = wave & (kw - 1), rw = wave >> KWL;
-    const int tok0 = blockIdx.y * 16, threads = blockDim.x, rows = p.strips_wg * 16, row0 = blockIdx.x * rows;
+    const int tok0 = blockIdx.y * 16, threads = (int)(p_form >> 20) * 64, rows = p.strips_wg * 16, row0 = blockIdx.x * rows;
     const int strip0 = blockIdx.x * p.strips_wg + rw * SW, strip_bytes = p.nkt * 1024;
     const unsigned char* z = p.planes + (size_t)blockIdx.y * p.blocks * record_bytes(PLANES) + (16 * g + min(i, p.B - 1 - tok0)) * 16;
     const unsigned char* z_scales = z + 6 * 1024 - (16 * g + min(i, p.B - 1 - tok0)) * 12;       // (four planes)
@@ -349,6 +371,9 @@ tsvd_few_u_kernel(tsvd_few_args p) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < SW; ++s) w[s] = load_w(s, q);        // (q < nkt: there are no more wavefronts side by side than columns)
+    p.y = p_y;
+    p.ld = p_ld;
+    asm volatile("" : "+s"(p.y), "+s"(p.ld));               // (not preloaded: read behind the first requests)
     auto column = [&](int T, auto last) {
         uint32_t second[SW][2];
 #pragma unroll
@@ -410,10 +435,10 @@ hipError_t launch(const tsvd_few_args& a, stage st, dim3 grid, int waves, hipStr
     constexpr int S2 = SW < 2 ? 2 : SW;
     const dim3 block((unsigned)waves * 64);
     const unsigned lds = (unsigned)(st == STAGE_U ? lds_parts(waves, SW) : lds_v(waves, SW, a.strips_wg));
-    if (st == STAGE_U) (a.z_planes == 4 ? tsvd_few_u_kernel<4, KWL, SW> : tsvd_few_u_kernel<5, KWL, SW>)<<<grid, block, lds, stream>>>(a);
+    if (st == STAGE_U) (a.z_planes == 4 ? tsvd_few_u_kernel<4, KWL, SW> : tsvd_few_u_kernel<5, KWL, SW>)<<<grid, block, lds, stream>>>(a.tiles, a.planes, a.bias, a.nkt, a.blocks, a.strips, a.B, a.M, tsvd_few_u_form(a, waves), a.y, a.ld);
     else if (SW == 1) return hipErrorInvalidValue;          // (planes are made of pairs of strips)
     else (a.token_major ? a.B <= 8 ? tsvd_few_v_kernel<true, true, KWL, S2> : tsvd_few_v_kernel<true, false, KWL, S2>
-                        : a.B <= 8 ? tsvd_few_v_kernel<false, true, KWL, S2> : tsvd_few_v_kernel<false, false, KWL, S2>)<<<grid, block, lds, stream>>>(a);
+                        : a.B <= 8 ? tsvd_few_v_kernel<false, true, KWL, S2> : tsvd_few_v_kernel<false, false, KWL, S2>)<<<grid, block, lds, stream>>>(a.tiles, a.x, a.S, a.planes, a.nkt, (int)a.ld, a.N, a.B, a.blocks, a.z_planes);
     return hipGetLastError();
 }
 template <int KWL>
