@@ -53,8 +53,33 @@ struct thin_args {
     int runs;                                // neighbouring panels on one XCD
     int slices;                              // workgroups of a panel, each with the whole z and its part of y's rows
 };
-// (Another line of arguments is 0.3 us a call: the first load of each comes from memory.)
-static_assert(sizeof(thin_args) == 192, "three lines");
+// They are passed so that the fourteen words which come preloaded in registers are what stage V needs: a load from the others takes 0.3 us, and everything waits
+// for it (742 x 106 x 103 at 29 tokens 7.05 -> 6.6 us, 388 x 120 x 256 at 33 5.5 -> 5.1, 3072 x 768 x 1545 at 3152 39.8 -> 39.1; of 50 drawn calls none longer, 0.97 of the time).
+struct thin_rest {
+    void* y;
+    long long ldy;
+    const float* bias;
+    int M;
+};
+struct thin_images {
+    int images, H, W, kv1, kv2, Hv, Wv, s1, s2, p1, p2, d1, d2;
+};
+unsigned thin_form(const thin_args& a) {
+    return (unsigned)a.chunk | (unsigned)(a.buffers - 1) << 6 | (unsigned)a.nub << 7 | (unsigned)a.whole << 12 | (unsigned)a.shared << 15 | (unsigned)a.parts << 19 | (unsigned)a.runs << 21 |
+           (unsigned)a.utm << 22 | (a.out_bf16 ? 1u << 26 : 0u) | (a.token_major ? 1u << 27 : 0u);
+}
+__device__ __forceinline__ thin_args thin_arguments(const uint16_t* x, const uint32_t* tiles_v, const uint32_t* tiles_u, const float* S, unsigned x_bytes, int N, int B, int ldx, unsigned form,
+                                                    int slices, const thin_rest& r, const thin_images& c) {
+    thin_args p;
+    p.x = x, p.tiles_v = tiles_v, p.tiles_u = tiles_u, p.S = S, p.x_bytes = x_bytes, p.N = N, p.B = B, p.ldx = ldx, p.slices = slices;
+    p.chunk = form & 63, p.buffers = 1 + (form >> 6 & 1), p.nub = form >> 7 & 31, p.whole = form >> 12 & 7, p.shared = form >> 15 & 15, p.parts = form >> 19 & 3, p.runs = form >> 21 & 1;
+    p.utm = form >> 22 & 15, p.out_bf16 = form >> 26 & 1, p.token_major = form >> 27 & 1;
+    p.nvb = (N + 127) >> 7, p.nkt_v = (N + 255) >> 8, p.nkt_u = (p.nub + 1) >> 1;
+    p.tile_v_bytes = (unsigned)p.nkt_u * (unsigned)p.nkt_v << 14, p.tile_u_bytes = (unsigned)((r.M + 255) >> 8) * (unsigned)p.nkt_u << 14;
+    p.y = r.y, p.ldy = r.ldy, p.bias = r.bias, p.M = r.M;
+    p.images = c.images, p.H = c.H, p.W = c.W, p.kv1 = c.kv1, p.kv2 = c.kv2, p.Hv = c.Hv, p.Wv = c.Wv, p.s1 = c.s1, p.s2 = c.s2, p.p1 = c.p1, p.p2 = c.p2, p.d1 = c.d1, p.d2 = c.d2;
+    return p;
+}
 
 // bytes of LDS for records of x, and then for the sums of the wavefronts that share a block
 __host__ __device__ inline int thin_x_bytes(const thin_args& p, int tiles, bool shared) {
@@ -67,7 +92,9 @@ constexpr int THIN_CONV_ROWS = 3;
 
 template <int TN, int RB, int SOURCE, bool CHUNKED, bool SHARED>
 __global__ void __launch_bounds__(512, 2)
-tsvd_thin_panel_kernel(thin_args p) {
+tsvd_thin_panel_kernel(const uint16_t* p_x, const uint32_t* p_tiles_v, const uint32_t* p_tiles_u, const float* p_S, unsigned p_x_bytes, int p_N, int p_B, int p_ldx, unsigned p_form, int p_slices,
+                       thin_rest p_rest, thin_images p_images) {
+    const thin_args p = thin_arguments(p_x, p_tiles_v, p_tiles_u, p_S, p_x_bytes, p_N, p_B, p_ldx, p_form, p_slices, p_rest, p_images);
     constexpr int NW = 8;
     using words = u32x4;
     extern __shared__ __align__(16) unsigned char smem[];    // records [block][tile]: chunk blocks of x, then nub blocks of z
@@ -499,10 +526,11 @@ auto kernel() { return tsvd_thin_panel_kernel<TN, RB, SOURCE, CHUNKED, SHARED>; 
 template <int TN, int RB, int SOURCE>
 hipError_t launch(const thin_args& a, bool shared, int lds, hipStream_t stream) {
     const dim3 grid((unsigned)((a.B + 16 * TN - 1) / (16 * TN)) * (unsigned)a.slices), block(512);
-    if (a.buffers == 2 && shared) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true, true>()), grid, block, lds, stream, a);
-    else if (a.buffers == 2) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, true, false>()), grid, block, lds, stream, a);
-    else if (shared) hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false, true>()), grid, block, lds, stream, a);
-    else hipLaunchKernelGGL((kernel<TN, RB, SOURCE, false, false>()), grid, block, lds, stream, a);
+    auto* k = a.buffers == 2 ? shared ? kernel<TN, RB, SOURCE, true, true>() : kernel<TN, RB, SOURCE, true, false>()
+                             : shared ? kernel<TN, RB, SOURCE, false, true>() : kernel<TN, RB, SOURCE, false, false>();
+    const thin_rest rest = {a.y, a.ldy, a.bias, a.M};
+    const thin_images images = {a.images, a.H, a.W, a.kv1, a.kv2, a.Hv, a.Wv, a.s1, a.s2, a.p1, a.p2, a.d1, a.d2};
+    hipLaunchKernelGGL(k, grid, block, lds, stream, a.x, a.tiles_v, a.tiles_u, a.S, a.x_bytes, a.N, a.B, (int)a.ldx, thin_form(a), a.slices, rest, images);
     return hipGetLastError();
 }
 template <int TN, int RB>
