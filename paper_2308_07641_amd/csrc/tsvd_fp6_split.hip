@@ -71,11 +71,11 @@ struct split_x {
     long long ld;
     int token_major, N;
 };
-// Which tiles an XCD works on (workgroups go to the eight of them in turn: a grid of 8 x tiles x rows): 1 << row_log2 groups of gridDim.z row tiles, times
-// 8 >> row_log2 groups of gridDim.y token tiles, one pair of groups for each, so that its L2 fetches a part of the codes and a part of the
+// Which tiles an XCD works on (workgroups go to the eight of them in turn: a grid of 8 x tiles x rows): 1 << row_log2 groups of group_rows row tiles, times
+// 8 >> row_log2 groups of group_tiles token tiles, one pair of groups for each, so that its L2 fetches a part of the codes and a part of the
 // planes.  (Launches without such groups, a grid of token tiles x row tiles, are kernels of their own: the choice by an argument cost each of them 0.15 us.)
 struct split_place {
-    int row_log2, row_tiles, token_tiles;
+    int row_log2, row_tiles, token_tiles, group_tiles, group_rows;          // group_tiles, group_rows: gridDim.y, gridDim.z
 };
 // Workgroups without a tile get the last one and end behind their first requests, which stay inside the codes and records with it.  (Where they ended before those, the
 // compiler read half of the arguments behind that branch: 3072 x 768 x 1536 fp32 at 197 tokens 16.95 -> 17.15 us.)
@@ -86,12 +86,31 @@ struct split_tile {
 template <bool PLACED, typename Extra>
 __device__ __forceinline__ split_tile tile_of(const Extra& p) {
     if constexpr (PLACED) {
-        const int row = (blockIdx.x & ((1 << p.row_log2) - 1)) * gridDim.z + blockIdx.z, token = (blockIdx.x >> p.row_log2) * gridDim.y + blockIdx.y;
+        const int row = (blockIdx.x & ((1 << p.row_log2) - 1)) * p.group_rows + blockIdx.z, token = (blockIdx.x >> p.row_log2) * p.group_tiles + blockIdx.y;
         return {min(token, p.token_tiles - 1), min(row, p.row_tiles - 1), row < p.row_tiles && token < p.token_tiles};
     } else {
         return {(int)blockIdx.x, (int)blockIdx.y, true};
     }
 }
+
+// The arguments of a stage.  Its first requests need fourteen words, which come preloaded in registers; a load from the others takes 0.3 us, and everything waits for it
+// (3072 x 768 x 1536 fp32 at 197 tokens 17.1 -> 16.6 us, 741 x 1024 x 413 fp32 at 102 11.8 -> 11.3, 1051 x 2539 x 559 at 256 13.6 -> 13.2; none of 50 drawn calls longer).  extra: words of split_x (its x stands at `act` then, N at act_bytes) or of split_place.
+#define SPLIT_ARGUMENTS const uint32_t *p_tiles, const void *p_act, unsigned p_tile_bytes, unsigned p_act_bytes, int p_nkt, int p_npairs, int p_code_blocks, int p_plane_blocks, int p_bvalid, \
+                        unsigned p_extra0, unsigned p_extra1, unsigned p_extra2, gemm_args p_rest
+#define SPLIT_STRUCT split_stage(p_tiles, p_act, p_tile_bytes, p_act_bytes, p_nkt, p_npairs, p_code_blocks, p_plane_blocks, p_bvalid, p_rest)
+__device__ __forceinline__ gemm_args split_stage(const uint32_t* tiles, const void* act, unsigned tile_bytes, unsigned act_bytes, int nkt, int npairs, int code_blocks, int plane_blocks, int bvalid,
+                                                 const gemm_args& rest) {
+    gemm_args p = rest;
+    p.tiles = tiles, p.act = static_cast<const uint16_t*>(act), p.tile_bytes = tile_bytes, p.act_bytes = act_bytes;
+    p.nkt = nkt, p.npairs = npairs, p.code_blocks = code_blocks, p.plane_blocks = plane_blocks, p.bvalid = bvalid;
+    return p;
+}
+__device__ __forceinline__ split_x split_x_of(const void* x, unsigned N, unsigned ld_low, unsigned ld_high, unsigned token_major) {
+    return {x, (long long)((unsigned long long)ld_high << 32 | ld_low), (int)token_major, (int)N};
+}
+__device__ __forceinline__ split_place split_place_of(unsigned e0, unsigned e1) { return {(int)(e1 & 3), (int)(e0 & 0xFFFF), (int)(e0 >> 16), (int)(e1 >> 2 & 0x7FFF), (int)(e1 >> 17)}; }
+// (what the ends of a stage need, read behind its first requests: its lines are near when they are wanted)
+__device__ __forceinline__ void split_touch(const gemm_args& p) { asm volatile("" ::"s"(p.S), "s"(p.out), "s"(p.rows_valid), "s"(p.rows_need)); }
 
 // z = S (V x) / 4 (the codes of either stage multiply as +-2) of rank block kb and the token tile from tok on, whose result blocks are sum -> its record.
 __device__ __forceinline__ void finish_z(const gemm_args& p, f32x4 (&sum)[8], int kb, int tok, int lane) {
@@ -117,7 +136,9 @@ __device__ __forceinline__ void finish_z(const gemm_args& p, f32x4 (&sum)[8], in
 // 328 23.3 -> 21.6, 13446 x 128 x 8569 fp32 at 781 296 -> 272 (each with a stage U of pairs where that has 256 rows).
 template <int RW, int TN, int X>
 __global__ void __launch_bounds__(512, 1)
-tsvd_fp6_panel_kernel(gemm_args p, split_x xs) {
+tsvd_fp6_panel_kernel(SPLIT_ARGUMENTS) {
+    const gemm_args p = SPLIT_STRUCT;
+    const split_x xs = split_x_of(p_act, p_act_bytes, p_extra0, p_extra1, p_extra2);
     constexpr int KG = 8 / RW, BPS = 16 / (KG * TN), TM = 8, RECS = KG * BPS * TN;
     static_assert(RECS == 16 && BPS >= 1, "16 records per step");
     constexpr int CHUNK = TN * FP6_REC_BYTES, STEP_BYTES = RECS * FP6_REC_BYTES;   // a chunk: a block's TN records
@@ -254,7 +275,8 @@ tsvd_fp6_panel_kernel(gemm_args p, split_x xs) {
 // decoding and the operand reads between them.
 template <int TN, bool STAGE2, int EX, bool PLACED>
 __global__ void __launch_bounds__(512, 1)
-tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x> extra) {
+tsvd_fp6_pair_kernel(SPLIT_ARGUMENTS) {
+    const gemm_args p = SPLIT_STRUCT;
     constexpr int RW = 2, KG = 4, TM = 8, BPS = 4 / TN;
     constexpr bool DIRECT = !STAGE2;
     constexpr int CHUNK = TN * FP6_REC_BYTES, PIECES = (CHUNK + 1023) / 1024, STEP_BYTES = BPS * CHUNK;
@@ -263,7 +285,7 @@ tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_
     extern __shared__ __align__(16) unsigned char smem[];    // [pair][2] steps, then 16 TN ones, then a word for each wavefront
     float* ones = reinterpret_cast<float*>(smem + 8 * STEP_BYTES);
     int* ready = reinterpret_cast<int*>(ones + 16 * TN);
-    const split_tile tile = tile_of<PLACED>(extra);
+    const split_tile tile = tile_of<PLACED>(split_place_of(p_extra0, p_extra1));
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rw = wave % RW, kg = wave / RW, i = lane & 15, g = lane >> 4;
     const int b0 = tile.token * 16 * TN, strip0 = (tile.row * RW + rw) * TM;
@@ -369,6 +391,7 @@ tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_
     load_w(min(from, nsteps - 1), wa);
     if (PLACED && !tile.exists) return;
     if (count > 0) issue(from, 0);
+    split_touch(p);
     __syncthreads();                                         // (the words are zero)
     for (int s = 0; s < count; s += 2) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -441,10 +464,10 @@ tsvd_fp6_pair_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_
 // 7415 x 4199 x 4465 bf16 at 125 32.3 -> 27.5; 40 drawn fp32 and 60 bf16 calls of 30 to 2500 tokens that take these tiles 0.73 to 1.0 of the time.
 template <int TN, bool STAGE2, int EX, int X, bool PLACED>
 __global__ void __launch_bounds__(512, 1)
-tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x> extra) {
-    split_x xs = {};
-    if constexpr (!PLACED) xs = extra;
-    const split_tile tile = tile_of<PLACED>(extra);
+tsvd_fp6_own_kernel(SPLIT_ARGUMENTS) {
+    const gemm_args p = SPLIT_STRUCT;
+    const split_x xs = split_x_of(p_act, p_act_bytes, p_extra0, p_extra1, p_extra2);
+    const split_tile tile = tile_of<PLACED>(split_place_of(p_extra0, p_extra1));
     constexpr int KG = 8, TM = 8, DEPTH = TN == 1 ? 3 : 2;
     constexpr bool DIRECT = !STAGE2;
     constexpr int NQ = DIRECT ? TN : KG, NF = 8 * TN / NQ;
@@ -551,6 +574,7 @@ tsvd_fp6_own_kernel(gemm_args p, std::conditional_t<PLACED, split_place, split_x
         ask(kg, d0);
         ask(kg + KG, d1);
         if constexpr (DEPTH == 3) ask(kg + 2 * KG, d2);
+        split_touch(p);
         if (PLACED && !tile.exists) return;
         for (int blk = kg; blk < nrun; blk += KG * DEPTH) {
             block(blk, d0);
@@ -645,7 +669,7 @@ bool place_of(int shape, const split_sizes& s, split_place* p, dim3* grid) {
         if (rows * tiles > s.cus / 8 || bytes >= best) continue;
         best = bytes;
         found = true;
-        *p = {log2, (int)row_tiles, (int)token_tiles};
+        *p = {log2, (int)row_tiles, (int)token_tiles, (int)tiles, (int)rows};
         *grid = dim3(8, (unsigned)tiles, (unsigned)rows);
     }
     return found;
@@ -654,20 +678,30 @@ template <int RW, int TN>
 hipError_t launch_shape(bool stage2, const gemm_args& a, int ex, const split_x* x, bool f32, long long cus, hipStream_t stream) {
     dim3 grid((unsigned)((a.bvalid + 16 * TN - 1) / (16 * TN)), (unsigned)((a.rows_need + RW * 128 - 1) / (RW * 128)));
     const dim3 block(512);
-#define SPLIT_LAUNCH(STAGE2, EX, X, PLACED, extra) hipLaunchKernelGGL((kernel<RW, TN, STAGE2, EX, X, PLACED>()), grid, block, (split_lds<RW, TN, X>), stream, a, extra)
-#define SPLIT_STAGE(PLACED, extra)                                  \
-    do {                                                            \
-        if (!stage2) SPLIT_LAUNCH(false, 0, 0, PLACED, extra);      \
-        else if (ex == 3) SPLIT_LAUNCH(true, 3, 0, PLACED, extra);  \
-        else if (ex == 2) SPLIT_LAUNCH(true, 2, 0, PLACED, extra);  \
-        else if (ex == 1) SPLIT_LAUNCH(true, 1, 0, PLACED, extra);  \
-        else SPLIT_LAUNCH(true, 0, 0, PLACED, extra);               \
+#define SPLIT_LAUNCH(STAGE2, EX, X, PLACED)                                                                                                                                                  \
+    hipLaunchKernelGGL((kernel<RW, TN, STAGE2, EX, X, PLACED>()), grid, block, (split_lds<RW, TN, X>), stream, a.tiles, X ? x->x : static_cast<const void*>(a.act), a.tile_bytes, \
+                       X ? (unsigned)x->N : a.act_bytes, a.nkt, a.npairs, a.code_blocks, a.plane_blocks, a.bvalid, extra[0], extra[1], extra[2], a)
+#define SPLIT_STAGE(PLACED)                                  \
+    do {                                                     \
+        if (!stage2) SPLIT_LAUNCH(false, 0, 0, PLACED);      \
+        else if (ex == 3) SPLIT_LAUNCH(true, 3, 0, PLACED);  \
+        else if (ex == 2) SPLIT_LAUNCH(true, 2, 0, PLACED);  \
+        else if (ex == 1) SPLIT_LAUNCH(true, 1, 0, PLACED);  \
+        else SPLIT_LAUNCH(true, 0, 0, PLACED);               \
     } while (0)
     split_place place;
-    if (!stage2 && x && f32) SPLIT_LAUNCH(false, 0, 2, false, *x);
-    else if (!stage2 && x) SPLIT_LAUNCH(false, 0, 1, false, *x);
-    else if (place_of(8 * RW + TN, {a.rows_need, a.bvalid, a.npairs, a.code_blocks ? a.code_blocks : a.npairs, cus}, &place, &grid)) SPLIT_STAGE(true, place);
-    else SPLIT_STAGE(false, split_x{});
+    unsigned extra[3] = {0, 0, 0};
+    if (!stage2 && x) {
+        extra[0] = (unsigned)x->ld, extra[1] = (unsigned)((unsigned long long)x->ld >> 32), extra[2] = (unsigned)x->token_major;
+        if (f32) SPLIT_LAUNCH(false, 0, 2, false);
+        else SPLIT_LAUNCH(false, 0, 1, false);
+    } else if (place_of(8 * RW + TN, {a.rows_need, a.bvalid, a.npairs, a.code_blocks ? a.code_blocks : a.npairs, cus}, &place, &grid)) {
+        extra[0] = (unsigned)place.row_tiles | (unsigned)place.token_tiles << 16;
+        extra[1] = (unsigned)place.row_log2 | (unsigned)place.group_tiles << 2 | (unsigned)place.group_rows << 17;
+        SPLIT_STAGE(true);
+    } else {
+        SPLIT_STAGE(false);
+    }
 #undef SPLIT_STAGE
 #undef SPLIT_LAUNCH
     return hipGetLastError();
