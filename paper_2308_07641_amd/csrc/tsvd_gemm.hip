@@ -524,12 +524,24 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
+// What the first requests need are the arguments that come preloaded in registers; a load from the others takes 0.3 us, and everything waits for it (3072 x 768 x 1536 at 512 tokens 15.53 -> 15.4 us, 342 x 597 x 1080 at 1901 12.6 -> 12.3).
 // KG > 1 splits the contraction over KG groups of WM x WN wavefronts: a ring slot then holds KG
 // pairs, group kg multiplies pair KG * P + kg, and the groups' accumulators are added through LDS
 // at the end.  Same tile and same bytes moved, KG times the wavefronts to hide waits with.
 template <int WM, int WN, int TM, int TN, bool STAGE2, int NPB, bool FUSEMAX, int KG, int EX = 0>
 __global__ void __launch_bounds__(64 * WM * WN * KG)
-tsvd_gemm_ring_kernel(gemm_args p) {
+tsvd_gemm_ring_kernel(const uint32_t* p_tiles, const uint16_t* p_act, unsigned p_act_bytes, unsigned p_tile_bytes, int p_nkt, int p_npairs, int p_ld, int p_last_steps, const float* p_colpart,
+                      int p_Bp, gemm_args p_rest) {
+    gemm_args p = p_rest;
+    p.tiles = p_tiles, p.act = p_act, p.act_bytes = p_act_bytes, p.tile_bytes = p_tile_bytes;
+    p.nkt = p_nkt, p.npairs = p_npairs, p.ld = p_ld, p.last_steps = p_last_steps & 7, p.Bp = p_Bp;
+    if constexpr (STAGE2) p.colmax = const_cast<float*>(p_colpart);
+    else p.colpart = p_colpart;
+    p.clocks = nullptr;
+    if (p_last_steps & 8) {
+        p.clocks = p_rest.clocks;
+        asm volatile("" : "+s"(p.clocks));           // (read here and by nobody else)
+    }
     constexpr int NWG = WM * WN, NW = NWG * KG, THREADS = 64 * NW;
     constexpr int BT = WN * TN * 16;                 // tokens per workgroup tile
     constexpr int ROWB = BT * 2;                     // bytes per LDS row
@@ -719,6 +731,7 @@ tsvd_gemm_ring_kernel(gemm_args p) {
         if (threadIdx.x < BT) cmax = load_column_max<STAGE2>(p, b0 + threadIdx.x);
 #pragma unroll
     for (int j = 0; j < NPB - 1; ++j) issue(j, j, -1);
+    asm volatile("" ::"s"(p.S), "s"(p.out), "s"(p.bvalid), "s"(p.rows_valid));       // (the ends' lines are near when they are wanted)
     tick(1);
     if (NPB - 2 <= lasts) wait_vmcnt<(NPB - 2) * OPS>();   // slot 0 has landed (this wavefront's part)
     else wait_vmcnt<0>();
@@ -1215,14 +1228,18 @@ hipError_t launch_ring(const gemm_args& a, long long rows, int Bp, hipStream_t s
     constexpr size_t lds = ring_lds_bytes<WM, WN, TM, TN, NPB, KG>();
     if (rows % MT) return hipErrorInvalidValue;      // (96-row tiles: the rule asks for them only when they divide the rows)
     const dim3 grid((a.bvalid + BT - 1) / BT, (unsigned)((a.rows_need + MT - 1) / MT)), block(64 * WM * WN * KG);
+#define RING_LAUNCH(STAGE, FUSE, EX)                                                                                                                                                    \
+    hipLaunchKernelGGL((tsvd_gemm_ring_kernel<WM, WN, TM, TN, STAGE, NPB, FUSE, KG, EX>), grid, block, lds, stream, a.tiles, a.act, a.act_bytes, a.tile_bytes, a.nkt, a.npairs, \
+                       (int)a.ld, a.last_steps | (a.clocks ? 8 : 0), STAGE ? static_cast<const float*>(a.colmax) : a.colpart, a.Bp, a)
     if constexpr (STAGE2) {
         const int ex = out_variant(a.bias, a.out_bf16, a.out_token_major);
-        if (ex == 2) hipLaunchKernelGGL((tsvd_gemm_ring_kernel<WM, WN, TM, TN, true, NPB, false, KG, 2>), grid, block, lds, stream, a);
-        if (ex == 1) hipLaunchKernelGGL((tsvd_gemm_ring_kernel<WM, WN, TM, TN, true, NPB, false, KG, 1>), grid, block, lds, stream, a);
-        if (ex == 3) hipLaunchKernelGGL((tsvd_gemm_ring_kernel<WM, WN, TM, TN, true, NPB, false, KG, 3>), grid, block, lds, stream, a);
+        if (ex == 2) RING_LAUNCH(true, false, 2);
+        if (ex == 1) RING_LAUNCH(true, false, 1);
+        if (ex == 3) RING_LAUNCH(true, false, 3);
         if (ex != 0) return hipGetLastError();
     }
-    hipLaunchKernelGGL((tsvd_gemm_ring_kernel<WM, WN, TM, TN, STAGE2, NPB, FUSEMAX, KG>), grid, block, lds, stream, a);
+    RING_LAUNCH(STAGE2, FUSEMAX, 0);
+#undef RING_LAUNCH
     return hipGetLastError();
 }
 template <int WM, int WN, int TM, int TN, int NPB, int KG>
