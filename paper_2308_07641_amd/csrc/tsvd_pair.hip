@@ -379,7 +379,7 @@ tsvd_pair_tail_kernel(tsvd_pair_plan p, int count, int shifted) {
     double* L = reinterpret_cast<double*>(tail_lds);         // [threads][TAIL_PITCH]
     __shared__ double row_j[TAIL_RANK + 1], y[TAIL_RANK], tot[TAIL_MAX_N / 64], part[TAIL_MAX_N / 64][256];
     __shared__ uint32_t keys[TAIL_MAX_N / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6, i = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = p.np >> 6, i = lane & 15, g = lane >> 4;
     const int last = p.state->last;
     const double* X = p.X[(last >= 0 ? last : count) & 1];
     double d = tid < p.n ? p.diag[(last >= 0 ? last : count) & 1][tid] : -1.0;

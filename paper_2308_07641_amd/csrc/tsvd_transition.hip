@@ -72,7 +72,7 @@ tsvd_ternarize_kernel(ternarize_args p) {
     __shared__ int qmin;
     __shared__ double threshold;
     const ternarize_job& job = p.job[blockIdx.y];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), T = blockDim.x, nw = T >> 6, n = job.n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), T = min(p.npow2, TERN_THREADS), nw = T >> 6, n = job.n;
     const double* xr = job.x + (size_t)blockIdx.x * job.ldx;
     int8_t* tr = job.t + (size_t)blockIdx.x * job.ldt;
     if (tid == 0) qmin = 0x7FFFFFFF;
@@ -258,7 +258,7 @@ tsvd_system_kernel(const int8_t* __restrict__ Ut, int mp, const int8_t* __restri
 // and a system of up to PCG_LDS_K unknowns runs with G in LDS on as few wavefronts as it has rows.  Larger systems
 // re-read G from L2 on 1024 threads, the columns of a row split over 1024 / K groups of threads.
 #define PCG_LDS_K 96
-__device__ __forceinline__ void solve_pcg(unsigned char* smem, const double* __restrict__ G, long long ldg, double* __restrict__ d, int K,
+__device__ __forceinline__ void solve_pcg(unsigned char* smem, int T, const double* __restrict__ G, long long ldg, double* __restrict__ d, int K,
                                           double* __restrict__ s, const double* __restrict__ s0, int* __restrict__ iters,
                                           const double* __restrict__ part, int fresh, int M) {
     double* xs = reinterpret_cast<double*>(smem);   // [K] solution
@@ -269,7 +269,7 @@ __device__ __forceinline__ void solve_pcg(unsigned char* smem, const double* __r
     double* sub = dg + K;                           // [1024] partial products of a row
     double* Gl = sub + 1024;                        // [K][K], K <= PCG_LDS_K
     __shared__ double red[2][2][16];
-    const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = T >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = T >> 6;
     int flip = 0;
     auto sum2 = [&](double a, double b, double& sa, double& sb) {      // sums over the workgroup, fixed order, in every thread
         a = wave_sum(a);
@@ -390,7 +390,7 @@ __global__ void __launch_bounds__(1024)
 tsvd_pcg_kernel(const double* __restrict__ G, long long ldg, double* __restrict__ d, int K, double* __restrict__ s,
                 const double* __restrict__ s0, int* __restrict__ iters, const double* __restrict__ part, int fresh, int M) {
     extern __shared__ __align__(16) unsigned char smem[];
-    solve_pcg(smem, G, ldg, d, K, s, s0, iters, part, fresh, M);
+    solve_pcg(smem, (int)blockDim.x, G, ldg, d, K, s, s0, iters, part, fresh, M);
 }
 
 // ---- Eq. (3), the solve while Algorithm 2 has at most 64 components: one row of the triangular factor more per component ----
@@ -478,7 +478,7 @@ tsvd_scales_kernel(const double* __restrict__ G, long long ldg, double* __restri
         }
     }
     __syncthreads();
-    if (singular) solve_pcg(smem, G, ldg, d, K, s, s0, nullptr, part, fresh, M);
+    if (singular) solve_pcg(smem, 256, G, ldg, d, K, s, s0, nullptr, part, fresh, M);
 }
 
 // ---- residual: R = W - U diag(S) V and partial sums of |R|_F^2 ----------------------------------
@@ -557,7 +557,7 @@ tsvd_residual_rows_kernel(const double* __restrict__ W, const int8_t* __restrict
             ss += rv * rv;
         }
     ss = wave_sum(ss);
-    if (lane == 0) part[(size_t)m * gridDim.x + blockIdx.x] = ss;
+    if (lane == 0) part[(size_t)m * ((N + 255) >> 8) + blockIdx.x] = ss;
 }
 
 // The result of Algorithm 2 from its component-major scratch: U [M][max_rank] (zero from K on), V [K][N], S [max_rank] (zero from K on).
