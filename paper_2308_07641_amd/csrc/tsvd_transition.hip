@@ -1150,7 +1150,9 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     int least = 1;                                                           // squarings that iterations before `least_until` get
     int64_t least_until = 0;
     // With q = 1 pairs are shifted from the second iteration on (tsvd_pair_square), two squarings fewer at first.  Not where the last iteration known had a second eigenvalue far
-    // below its first, which the pair behind may then miss, nor after the second iteration that had to be taken again for the shifts.  (With more pairs an iteration one that
+    // below its first, which the pair behind may then miss, nor after the second iteration that had to be taken again for the shifts.  Nor where there are fewer than 128 values: their gaps
+    // vary more from one pair to the next, and an iteration taken again costs as much as thirty shifted ones save (188 x 112, 8 components: 0.65 -> 0.75 ms with them, 192 x 125, 40: 3.10 -> 3.26;
+    // 512 x 128, 15: 1.23 -> 1.09; 18 of 128 values and more 0.78 to 0.95 of the time).  (With more pairs an iteration one that
     // misses takes all of them again: Laplace matrices gained 0.94, four an iteration, a linear spectrum took 1.5 times as long.)
     bool resolved = false;
     int shifted = 0, shifted_least = 3, misses = 0;                          // squarings of a shifted pair
@@ -1174,7 +1176,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     if (wait_for(0)) wnorm2 = rnorm2;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
     auto enqueue = [&](int64_t i, int64_t first, int64_t take, bool again) {
-        const bool by_shifts = any_rank && q == 1 && i > 1 && resolved && !again && misses < 2;
+        const bool by_shifts = any_rank && q == 1 && std::min(M, N) >= 128 && i > 1 && resolved && !again && misses < 2;
         if (shifted == 0) shifted = std::max(6, squarings - 2);
         const int count = by_shifts ? shifted : squarings;
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
