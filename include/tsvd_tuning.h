@@ -67,6 +67,10 @@ int tsvd_tuning_one_launch(const tsvd_handle* h, long long B);
  * call takes no split tiles. */
 int tsvd_tuning_tiles_by_xcd(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u);
 
+/* Of the last tsvd_transition or tsvd_transition_q of this thread: iterations whose squarings were shifted and that were kept, and those that were
+ * taken again because the shifts did not hold. */
+void tsvd_tuning_transition_shifts(int* kept, int* again);
+
 /* Copies the phase timestamps ([workgroups][16] 100 MHz ticks) of the last launch of a handle packed with
  * TSVD_CLOCKS = 1 to the host.  Returns 0 on success. */
 int tsvd_tuning_read_clocks(const tsvd_handle* h, long long* out, int workgroups);

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/tsvd_transition.h"
+#include "../../include/tsvd_tuning.h"
 #include "tsvd_pair.h"
 #include "tsvd_scratch.h"
 #include "tsvd_wave.h"
@@ -1044,6 +1045,11 @@ hipError_t tsvd_transition_init() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(tsvd_gkl_finish_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
 }
 
+namespace {
+// of this thread's last transition, for tsvd_tuning_transition_shifts
+thread_local int shifts_kept = 0, shifts_again = 0;
+}  // namespace
+
 extern "C" tsvd_status tsvd_transition(const double* W_dev, int64_t M, int64_t N, double theta, double tol, int64_t max_rank,
                                        int8_t* U_dev, double* S_dev, int8_t* V_dev, int64_t* rank_out, double* errors_host,
                                        void* stream) {
@@ -1058,6 +1064,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         return TSVD_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     *rank_out = 0;
+    shifts_kept = shifts_again = 0;
     const bool squares = tsvd_pair_squares(M, N);
     const int mp = (int)((M + 15) & ~15), np = (int)((N + 15) & ~15);       // pitches of the component-major factors
     const int pieces = (int)((N + 255) / 256);                              // pieces of a row of the residual
@@ -1149,13 +1156,21 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     bool first_pair = false;                                                 // in the plan already
     int least = 1;                                                           // squarings that iterations before `least_until` get
     int64_t least_until = 0;
-    // With q = 1 pairs are shifted from the second iteration on (tsvd_pair_square), two squarings fewer at first.  Not where the last iteration known had a second eigenvalue far
-    // below its first, which the pair behind may then miss, nor after the second iteration that had to be taken again for the shifts.  Nor where there are fewer than 128 values: their gaps
-    // vary more from one pair to the next, and an iteration taken again costs as much as thirty shifted ones save (188 x 112, 8 components: 0.65 -> 0.75 ms with them, 192 x 125, 40: 3.10 -> 3.26;
-    // 512 x 128, 15: 1.23 -> 1.09; 18 of 128 values and more 0.78 to 0.95 of the time).  (With more pairs an iteration one that
-    // misses takes all of them again: Laplace matrices gained 0.94, four an iteration, a linear spectrum took 1.5 times as long.)
+    // With q = 1 pairs are shifted from the second iteration on (tsvd_pair_square), two squarings fewer than without.  One that has to be taken again costs itself, the one behind it and a
+    // wait, what 20 to 40 shifted ones save, so shifts are left to where they hold:
+    //   - eight to eleven squarings.  With fewer the spectrum falls: there is little to save, and shifted pairs could need more than others;  with more it has clusters, whose squarings
+    //     end by themselves without shifts;
+    //   - a second eigenvalue that the last iteration known has not lost beside the first, and more than three directions left in it: behind fewer a step down may lie, from where
+    //     the shifts reach too little;
+    //   - 128 values and more: the gaps of fewer vary more from one pair to the next (188 x 112, 8 components: 0.65 -> 0.75 ms with shifts, 192 x 125, 40: 3.10 -> 3.26; 512 x 128, 15: 1.23 -> 1.09);
+    //   - after one that was taken again only where PAYS_FROM components are left, never after the second.
+    // Of 980 random spectra (128 to 768 values, 6 to 40 components) none takes more than 1.05 of the time that it takes without shifts: Laplace, normal, ternary and linear ones 0.89 on
+    // the average, groups of equal values 0.97, values above a bulk 0.955, exponentials and low rank with noise 0.98, power laws and close values 1.00.  (With shifts from six squarings on, and as few as three of them, 0.05 of these spectra took
+    // 1.15 to 1.6 of it: power laws 1.11 on the average, values above a bulk 1.08, groups 1.05.)  (With more pairs an iteration one that misses takes all of them
+    // again: Laplace matrices gained 0.94, four an iteration, a linear spectrum took 1.5 times as long.)
+    constexpr int SHIFTS_FROM = 8, SHIFTS_TO = 11, PAYS_FROM = 24;
     bool resolved = false;
-    int shifted = 0, shifted_least = 3, misses = 0;                          // squarings of a shifted pair
+    int shifted[2] = {0, 0};                                                 // squarings of iteration i, where they are shifted, in [i & 1]
     if (any_rank && st == TSVD_OK) {
         tsvd_pair_shifts* left = reinterpret_cast<tsvd_pair_shifts*>(pinned + 2 * told_bytes);
         tsvd_pair_state* state = &left->state;
@@ -1176,9 +1191,10 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     if (wait_for(0)) wnorm2 = rnorm2;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
     auto enqueue = [&](int64_t i, int64_t first, int64_t take, bool again) {
-        const bool by_shifts = any_rank && q == 1 && std::min(M, N) >= 128 && i > 1 && resolved && !again && misses < 2;
-        if (shifted == 0) shifted = std::max(6, squarings - 2);
-        const int count = by_shifts ? shifted : squarings;
+        const bool by_shifts = any_rank && q == 1 && std::min(M, N) >= 128 && i > 1 && resolved && !again && squarings >= SHIFTS_FROM && squarings <= SHIFTS_TO &&
+                               (shifts_again == 0 || (shifts_again == 1 && max_rank - first >= PAYS_FROM));
+        const int count = by_shifts ? squarings - 2 : squarings;
+        shifted[i & 1] = by_shifts ? count : 0;
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
         // that triple removed, ... (the last iteration takes what still fits below max_rank)
         const double* src = R;
@@ -1234,8 +1250,8 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
                 // some pair needed more squarings: back to the residual before this iteration, with more of them, and for a while
                 // with one more than were too few (spectra on the edge of two counts missed every eighth iteration)
                 if (seen.shifted_missed != 0) {
-                    ++misses;
-                    shifted = shifted_least = std::min(TSVD_PAIR_MAX_SQUARINGS, shifted + 1);
+                    ++shifts_again;
+                    squarings = std::max(squarings, std::min(seen.shifted_needed + 1, tsvd_pair_first_squarings(plan)));      // (without shifts; not known where many are alike)
                 }
                 if (missed) {
                     if (any_rank && i > 1) {
@@ -1254,7 +1270,11 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
                 st = TSVD_EVALUE;           // no ternary vector within theta: the components of an unfinished iteration are dropped
                 break;
             }
-            if (seen.shifted_needed > 0) shifted = std::min(TSVD_PAIR_MAX_SQUARINGS, std::max(shifted_least, seen.shifted_needed));
+            if (const int had = shifted[i & 1]; had > 0) {
+                ++shifts_kept;
+                if (seen.shifted_needed < had) resolved = false;             // (few directions left: a step down may lie ahead)
+                squarings = std::max(squarings, std::min(TSVD_PAIR_MAX_SQUARINGS, seen.shifted_needed + 2));
+            }
             if (seen.needed > 0 || !any_rank) squarings = std::min(TSVD_PAIR_MAX_SQUARINGS, any_rank ? std::max(i < least_until ? least : 1, seen.needed) : std::max(16, seen.needed + 2));
             const double err = std::sqrt(rnorm2 / wnorm2);
             if (errors_host)
@@ -1275,6 +1295,11 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     const bool done = hipStreamSynchronize(s) == hipSuccess;
     scratch_pool().give(scratch, done);
     return st;
+}
+
+extern "C" void tsvd_tuning_transition_shifts(int* kept, int* again) {
+    *kept = shifts_kept;
+    *again = shifts_again;
 }
 
 extern "C" void tsvd_transition_release(void) { scratch_pool().release(); }

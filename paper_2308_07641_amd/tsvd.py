@@ -50,6 +50,7 @@ _PROTOTYPES = {
     "tsvd_tuning_tile_shapes": (ctypes.c_int, [_vp, ctypes.c_longlong, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "tsvd_tuning_one_launch": (ctypes.c_int, [_vp, ctypes.c_longlong]),
     "tsvd_tuning_tiles_by_xcd": (ctypes.c_int, [_vp, ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
+    "tsvd_tuning_transition_shifts": (None, [ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "tsvd_tuning_read_clocks": (ctypes.c_int, [_vp, _vp, ctypes.c_int]),
     "tsvd_ternarize": (ctypes.c_int, [_vp, _i64, _i64, _i64, ctypes.c_double, _vp, _i64, _vp, _vp]),
     "tsvd_fit_scales_workspace": (_sz, [_i64]),
@@ -313,6 +314,13 @@ def tsvd_tuning_tiles_by_xcd(h: Handle, B: int, x_dtype: int):
     if load_library().tsvd_tuning_tiles_by_xcd(h.ptr, B, x_dtype, ctypes.byref(v), ctypes.byref(u)) != 0:
         raise ValueError("tsvd_tuning_tiles_by_xcd: the call takes no split tiles")
     return bool(v.value), bool(u.value)
+
+
+def tsvd_tuning_transition_shifts():
+    """(iterations of this thread's last transition whose squarings were shifted and kept, iterations taken again for their shifts)"""
+    kept, again = ctypes.c_int(0), ctypes.c_int(0)
+    load_library().tsvd_tuning_transition_shifts(ctypes.byref(kept), ctypes.byref(again))
+    return kept.value, again.value
 
 
 def tsvd_tuning_read_clocks(h: Handle, workgroups: int) -> np.ndarray:

@@ -451,6 +451,34 @@ def test_transition_with_many_close_singular_values(tsvd, M, N):
     assert np.max(np.abs(np.array(errs) - np.array(eo))) <= 1e-9
 
 
+def _of_spectrum(M, N, s, seed):
+    rng = np.random.default_rng(seed)
+    return (np.linalg.qr(rng.standard_normal((M, len(s))))[0] * s) @ np.linalg.qr(rng.standard_normal((N, len(s))))[0].T
+
+
+UNSHIFTED_SPECTRA = {
+    "power 1/2": (1.0 + np.arange(120)) ** -0.5,
+    "power 1": (1.0 + np.arange(120)) ** -1.0,
+    "power 2": (1.0 + np.arange(120)) ** -2.0,
+    "halves": 0.5 ** np.arange(60),
+    "thirds": 3.0 ** -np.arange(24),
+    "groups": 0.9 ** (np.arange(120) // 8),                                  # jumps from one direction to eight more
+    "shelf": np.concatenate([1 - 0.01 * np.arange(4), 0.2 * (1 - 0.002 * np.arange(100))]),
+}
+
+
+@pytest.mark.parametrize("spectrum", list(UNSHIFTED_SPECTRA))
+@pytest.mark.parametrize("M,N,seed", [(150, 129, 2), (129, 300, 3), (385, 400, 5), (400, 385, 6)])
+def test_shifted_squarings_are_not_taken_again_where_a_spectrum_falls(tsvd, M, N, seed, spectrum):
+    """Falling and stepped spectra: an iteration whose shifts do not hold costs two and more, a third of a call of a few components, so none may be lost where the
+    pairs before tell that there is little to gain."""
+    print(f"case fall {M} {N} {spectrum}", flush=True)
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(_of_spectrum(M, N, UNSHIFTED_SPECTRA[spectrum], seed)), 0.65, 0.0, 12)
+    kept, again = tsvd.tsvd_tuning_transition_shifts()
+    assert status == 0 and U.shape[1] == 12
+    assert again == 0, (kept, again)
+
+
 SHIFT_SPECTRA = {
     "steps": 1.0 - 0.025 * np.arange(24),                                    # shifts that hold from the second pair on
     "fall": 3.0 ** -np.arange(24),                                           # the second eigenvalue is lost beside the first: no shift
