@@ -15,6 +15,7 @@
 
 #include "../../include/tsvd_transition.h"
 #include "../../include/tsvd_tuning.h"
+#include "tsvd_kernels.h"
 #include "tsvd_pair.h"
 #include "tsvd_scratch.h"
 #include "tsvd_wave.h"
@@ -1169,6 +1170,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     // 1.15 to 1.6 of it: power laws 1.11 on the average, values above a bulk 1.08, groups 1.05.)  (With more pairs an iteration one that misses takes all of them
     // again: Laplace matrices gained 0.94, four an iteration, a linear spectrum took 1.5 times as long.)
     constexpr int SHIFTS_FROM = 8, SHIFTS_TO = 11, PAYS_FROM = 24;
+    const int forced = tsvd_tune("TSVD_TRANSITION_SHIFTED", 0);
     bool resolved = false;
     int shifted[2] = {0, 0};                                                 // squarings of iteration i, where they are shifted, in [i & 1]
     if (any_rank && st == TSVD_OK) {
@@ -1191,9 +1193,9 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     if (wait_for(0)) wnorm2 = rnorm2;
     // Iteration i: components first .. first + take - 1 from the residual of the one before.
     auto enqueue = [&](int64_t i, int64_t first, int64_t take, bool again) {
-        const bool by_shifts = any_rank && q == 1 && std::min(M, N) >= 128 && i > 1 && resolved && !again && squarings >= SHIFTS_FROM && squarings <= SHIFTS_TO &&
-                               (shifts_again == 0 || (shifts_again == 1 && max_rank - first >= PAYS_FROM));
-        const int count = by_shifts ? squarings - 2 : squarings;
+        const bool by_shifts = any_rank && q == 1 && std::min(M, N) >= 128 && i > 1 && resolved && !again &&
+                               (forced > 0 || (squarings >= SHIFTS_FROM && squarings <= SHIFTS_TO)) && (shifts_again == 0 || (shifts_again == 1 && max_rank - first >= PAYS_FROM));
+        const int count = !by_shifts ? squarings : forced > 0 ? std::min(forced, TSVD_PAIR_MAX_SQUARINGS) : squarings - 2;
         shifted[i & 1] = by_shifts ? count : 0;
         // the top q singular triples of the residual, one after the other: the leading triple of R, then of R with
         // that triple removed, ... (the last iteration takes what still fits below max_rank)

@@ -456,6 +456,60 @@ def _of_spectrum(M, N, s, seed):
     return (np.linalg.qr(rng.standard_normal((M, len(s))))[0] * s) @ np.linalg.qr(rng.standard_normal((N, len(s))))[0].T
 
 
+def _follows_the_oracle(tsvd, W, theta, rank, q):
+    """A transition against the oracle; (kept, taken again) of its shifted iterations"""
+    Uo, So, Vo, eo = tr.transition(W, theta, q=q, max_rank=rank)
+    U, S, V, errs, status = tsvd.tsvd_transition(_dev(W), theta, 0.0, rank, q=q)
+    shifts = tsvd.tsvd_tuning_transition_shifts()
+    assert status == 0
+    U, S, V = U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy()
+    for k in range(rank):
+        sign = 1 if np.array_equal(U[:, k], Uo[:, k]) else -1
+        assert np.array_equal(sign * U[:, k], Uo[:, k]) and np.array_equal(sign * V[k, :], Vo[k, :]), k
+    assert np.max(np.abs(S - So)) <= 1e-8 * np.max(np.abs(So))
+    assert abs(errs[-1] - eo[-1]) <= 1e-9
+    return shifts
+
+
+SHIFT_SPECTRA = {
+    "steps": 1.0 - 0.006 * np.arange(60),                                    # shifts that hold from the second pair on
+    "fall": 3.0 ** -np.arange(24),                                           # the second eigenvalue is lost beside the first: no shift
+    "shelf": np.concatenate([1.0 - 0.006 * np.arange(4), 0.2 - 0.002 * np.arange(60)]),      # a step down behind a few
+}
+SHIFT_SIZES = [(150, 129, 2), (128, 128, 1), (129, 300, 3), (200, 384, 4), (385, 400, 5), (400, 385, 6)]
+
+
+@pytest.mark.parametrize("spectrum", list(SHIFT_SPECTRA))
+@pytest.mark.parametrize("M,N,seed", SHIFT_SIZES + [(127, 300, 7), (300, 127, 8)])
+def test_pairs_squared_with_shifts_follow_the_oracle(tsvd, M, N, seed, spectrum):
+    """Nine components, at the smallest shorter side that is shifted and the largest that is not, and on both sides of the one where tiles of 32 begin, either side the
+    shorter: where the pair before leaves a shift, leaves none, and where there is a step between the two."""
+    print(f"case shifts {M} {N} {spectrum}", flush=True)
+    kept, again = _follows_the_oracle(tsvd, _of_spectrum(M, N, SHIFT_SPECTRA[spectrum], seed), 0.65, 9, 1)
+    assert again == 0
+    assert kept >= 4 if spectrum == "steps" and min(M, N) >= 128 else kept == 0 or (spectrum == "shelf" and min(M, N) >= 128), kept
+
+
+@pytest.mark.parametrize("M,N,seed", [(150, 129, 2), (129, 300, 3), (400, 385, 6)])
+def test_three_pairs_an_iteration_are_not_shifted(tsvd, M, N, seed):
+    print(f"case shifts {M} {N}, three an iteration", flush=True)
+    assert _follows_the_oracle(tsvd, _of_spectrum(M, N, SHIFT_SPECTRA["steps"], seed), 0.65, 9, 3) == (0, 0)
+
+
+@pytest.mark.parametrize("M,N,seed,spectrum,squarings", [size + ("steps", 3) for size in SHIFT_SIZES] + [(150, 129, 2, "squares", 8)])
+def test_iterations_whose_shifts_do_not_hold_are_taken_again(tsvd, M, N, seed, spectrum, squarings):
+    """Shifts where the rule takes none: too few squarings leave more than sixteen directions, and of a spectrum that falls like 1 / k^2 a pair's leading value lies below what
+    the one before led to expect, so that none counts.  The device tells both, and they are done again without."""
+    s = SHIFT_SPECTRA["steps"] if spectrum == "steps" else (1.0 + np.arange(60)) ** -2.0
+    print(f"case shifts do not hold {M} {N} {spectrum} {squarings}", flush=True)
+    try:
+        tsvd.tsvd_tuning_set("TSVD_TRANSITION_SHIFTED", squarings)
+        kept, again = _follows_the_oracle(tsvd, _of_spectrum(M, N, s, seed), 0.65, 9, 1)
+    finally:
+        tsvd.tsvd_tuning_reset()
+    assert again >= 1, (kept, again)
+
+
 UNSHIFTED_SPECTRA = {
     "power 1/2": (1.0 + np.arange(120)) ** -0.5,
     "power 1": (1.0 + np.arange(120)) ** -1.0,
@@ -477,35 +531,6 @@ def test_shifted_squarings_are_not_taken_again_where_a_spectrum_falls(tsvd, M, N
     kept, again = tsvd.tsvd_tuning_transition_shifts()
     assert status == 0 and U.shape[1] == 12
     assert again == 0, (kept, again)
-
-
-SHIFT_SPECTRA = {
-    "steps": 1.0 - 0.025 * np.arange(24),                                    # shifts that hold from the second pair on
-    "fall": 3.0 ** -np.arange(24),                                           # the second eigenvalue is lost beside the first: no shift
-    "shelf": np.concatenate([[1.0, 0.97, 0.94, 0.91], 0.2 - 0.004 * np.arange(20)]),   # a shift that lies above the next leading value
-}
-
-
-@pytest.mark.parametrize("q", [1, 3])
-@pytest.mark.parametrize("spectrum", list(SHIFT_SPECTRA))
-@pytest.mark.parametrize("M,N,seed", [(65, 64, 1), (150, 129, 2), (96, 400, 3), (400, 385, 4)])
-def test_pairs_squared_with_shifts_follow_the_oracle(tsvd, M, N, seed, spectrum, q):
-    """Nine components: each pair's squarings are shifted by what the pair before left, at sizes on both sides of a tile of either kind, with contractions shorter
-    than a workgroup's, where that value holds, is not known and is too large."""
-    rng = np.random.default_rng(seed)
-    r = 24
-    W = (np.linalg.qr(rng.standard_normal((M, r)))[0] * SHIFT_SPECTRA[spectrum]) @ np.linalg.qr(rng.standard_normal((N, r)))[0].T
-    rank, theta = 9, 0.65
-    Uo, So, Vo, eo = tr.transition(W, theta, q=q, max_rank=rank)
-    print(f"case shifts {M} {N} {spectrum} {q}", flush=True)
-    U, S, V, errs, status = tsvd.tsvd_transition(_dev(W), theta, 0.0, rank, q=q)
-    assert status == 0
-    U, S, V = U.cpu().numpy(), S.cpu().numpy(), V.cpu().numpy()
-    for k in range(rank):
-        sign = 1 if np.array_equal(U[:, k], Uo[:, k]) else -1
-        assert np.array_equal(sign * U[:, k], Uo[:, k]) and np.array_equal(sign * V[k, :], Vo[k, :]), k
-    assert np.max(np.abs(S - So)) <= 1e-8 * np.max(np.abs(So))
-    assert abs(errs[-1] - eo[-1]) <= 1e-9
 
 
 @pytest.mark.parametrize("spectrum", ["close", "equal"])
