@@ -1,16 +1,17 @@
 // Scratch of calls that allocate their own: device memory, pinned host memory and two events, kept between calls.
 //
 // Allocating and freeing cost such a call 0.15 to 0.4 ms (hipMalloc 25 to 55 us, hipHostMalloc 20, hipFree 30 to 40, hipHostFree 70 to 230 and more where other memory is mapped), as
-// much as three to five components of a transition.  Up to four idle pieces are kept, each of at most 64 MiB of device and 1 MiB of pinned memory; larger ones are freed by the call
-// that allocated them.  A piece belongs to one call from take() to give(), and give() comes behind a wait for the stream that used it, so
-// calls of several threads, streams and devices never share one.  Idle pieces are given back by release(), and where an allocation fails.
+// much as three to five components of a transition.  Up to four idle pieces are kept, each of at most 64 MiB of device and 1 MiB of pinned memory; for a fifth the one
+// that has been idle longest is freed.  A piece belongs to one call from take() to give(), and give() comes behind a wait for the stream that used it, so
+// calls of several threads, streams and devices never share one.  Idle pieces are given back by release(), and where an allocation fails.  Nothing here throws.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
 
 #include <mutex>
-#include <vector>
+#include <new>
+#include <utility>
 
 struct tsvd_scratch {
     int device = -1;
@@ -20,9 +21,11 @@ struct tsvd_scratch {
 };
 
 class tsvd_scratch_pool {
-    static constexpr size_t MAX_IDLE = 4, MAX_BYTES = (size_t)64 << 20, MAX_PINNED = (size_t)1 << 20;
+    static constexpr int MAX_IDLE = 4;
+    static constexpr size_t MAX_BYTES = (size_t)64 << 20, MAX_PINNED = (size_t)1 << 20;
     std::mutex m;
-    std::vector<tsvd_scratch> idle;
+    tsvd_scratch idle[MAX_IDLE];                             // the first `count`, longest idle first
+    int count = 0;
 
     static void free_piece(tsvd_scratch& s) {
         for (hipEvent_t e : s.event)
@@ -31,16 +34,21 @@ class tsvd_scratch_pool {
         if (s.base) (void)hipFree(s.base);
         s = tsvd_scratch();
     }
-    static bool allocate(tsvd_scratch& s) {
-        if (hipMalloc(reinterpret_cast<void**>(&s.base), s.bytes) == hipSuccess &&
-            hipHostMalloc(reinterpret_cast<void**>(&s.pinned), s.pinned_bytes, hipHostMallocDefault) == hipSuccess &&
-            hipEventCreateWithFlags(&s.event[0], hipEventDisableTiming) == hipSuccess && hipEventCreateWithFlags(&s.event[1], hipEventDisableTiming) == hipSuccess)
-            return true;
+    static hipError_t allocate(tsvd_scratch& s) {
+        hipError_t e = hipMalloc(reinterpret_cast<void**>(&s.base), s.bytes);
+        if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&s.pinned), s.pinned_bytes, hipHostMallocDefault);
+        for (int k = 0; e == hipSuccess && k < 2; ++k) e = hipEventCreateWithFlags(&s.event[k], hipEventDisableTiming);
+        if (e == hipSuccess) return e;
         const tsvd_scratch wanted = s;
         free_piece(s);
         s.device = wanted.device, s.bytes = wanted.bytes, s.pinned_bytes = wanted.pinned_bytes;
         (void)hipGetLastError();
-        return false;
+        return e;
+    }
+    tsvd_scratch remove(int at) {                            // (under the lock)
+        const tsvd_scratch s = idle[at];
+        for (--count; at < count; ++at) idle[at] = idle[at + 1];
+        return s;
     }
 
 public:
@@ -50,13 +58,11 @@ public:
         if (hipGetDevice(&device) != hipSuccess) return false;
         {
             std::lock_guard<std::mutex> lock(m);
-            size_t best = idle.size();
-            for (size_t i = 0; i < idle.size(); ++i)
-                if (idle[i].device == device && idle[i].bytes >= bytes && idle[i].pinned_bytes >= pinned_bytes && (best == idle.size() || idle[i].bytes < idle[best].bytes))
-                    best = i;
-            if (best < idle.size()) {
-                *s = idle[best];
-                idle.erase(idle.begin() + (ptrdiff_t)best);
+            int best = -1;
+            for (int i = 0; i < count; ++i)
+                if (idle[i].device == device && idle[i].bytes >= bytes && idle[i].pinned_bytes >= pinned_bytes && (best < 0 || idle[i].bytes < idle[best].bytes)) best = i;
+            if (best >= 0) {
+                *s = remove(best);
                 return true;
             }
         }
@@ -64,33 +70,37 @@ public:
         s->device = device;
         s->bytes = (bytes + (1 << 20) - 1) >> 20 << 20;
         s->pinned_bytes = (pinned_bytes + (1 << 16) - 1) >> 16 << 16;
-        if (allocate(*s)) return true;
+        if (allocate(*s) == hipSuccess) return true;
         release();
-        return allocate(*s);
+        return allocate(*s) == hipSuccess;
     }
     // done: nothing enqueued uses the piece any more.
     void give(tsvd_scratch& s, bool done) {
-        if (done && s.bytes <= MAX_BYTES && s.pinned_bytes <= MAX_PINNED) {
-            std::lock_guard<std::mutex> lock(m);
-            if (idle.size() < MAX_IDLE) {
-                idle.push_back(s);
-                s = tsvd_scratch();
-                return;
-            }
-            // the smallest makes room
-            size_t least = 0;
-            for (size_t i = 1; i < idle.size(); ++i)
-                if (idle[i].bytes < idle[least].bytes) least = i;
-            if (idle[least].bytes < s.bytes) std::swap(idle[least], s);
-        }
-        free_piece(s);
-    }
-    void release() {
-        std::vector<tsvd_scratch> pieces;
+        if (!done || s.bytes > MAX_BYTES || s.pinned_bytes > MAX_PINNED) return free_piece(s);
+        tsvd_scratch out[MAX_IDLE];
+        int outs = 0;
         {
             std::lock_guard<std::mutex> lock(m);
-            pieces.swap(idle);
+            while (count == MAX_IDLE) out[outs++] = remove(0);
+            idle[count++] = s;
+            s = tsvd_scratch();
         }
-        for (tsvd_scratch& s : pieces) free_piece(s);
+        for (int i = 0; i < outs; ++i) free_piece(out[i]);
+    }
+    void release() {
+        tsvd_scratch out[MAX_IDLE];
+        int outs = 0;
+        {
+            std::lock_guard<std::mutex> lock(m);
+            while (count > 0) out[outs++] = remove(0);
+        }
+        for (int i = 0; i < outs; ++i) free_piece(out[i]);
     }
 };
+
+// The pool of the process (never destroyed: the runtime may be gone by then, and takes the memory with it).
+inline tsvd_scratch_pool& tsvd_idle_scratch() {
+    alignas(tsvd_scratch_pool) static unsigned char memory[sizeof(tsvd_scratch_pool)];
+    static tsvd_scratch_pool* const pool = new (memory) tsvd_scratch_pool;
+    return *pool;
+}

@@ -27,12 +27,6 @@ namespace {
 
 size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// (never destroyed: the runtime may be gone by then, and takes the memory with it)
-tsvd_scratch_pool& scratch_pool() {
-    static tsvd_scratch_pool* pool = new tsvd_scratch_pool;
-    return *pool;
-}
-
 // Sum over the 256 threads of a workgroup, in a fixed order (tree in LDS); result in every thread.
 __device__ __forceinline__ double block_sum256(double v, double* red) {
     red[threadIdx.x] = v;
@@ -1090,7 +1084,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     // what the host reads after an iteration (two in turn, written by the device): the report, and the residual's sums of squares
     const size_t told_bytes = round256(sizeof(transition_report) + (size_t)M * pieces * 8);
     tsvd_scratch scratch;
-    if (!scratch_pool().take(total, 2 * told_bytes + sizeof(tsvd_pair_shifts), &scratch)) return TSVD_EDEVICE;
+    if (!tsvd_idle_scratch().take(total, 2 * told_bytes + sizeof(tsvd_pair_shifts), &scratch)) return TSVD_EDEVICE;
     uint8_t *const base = scratch.base, *const pinned = scratch.pinned;
     hipEvent_t* const event = scratch.event;
     double* R = reinterpret_cast<double*>(base + at_R);
@@ -1295,7 +1289,7 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
         hipLaunchKernelGGL(tsvd_emit_kernel, dim3(256), dim3(256), 0, s, Ut, mp, Vs, np, scales[kept % 3], (int)M, (int)N, (int)*rank_out, (int)max_rank, U_dev, V_dev,
                            S_dev);
     const bool done = hipStreamSynchronize(s) == hipSuccess;
-    scratch_pool().give(scratch, done);
+    tsvd_idle_scratch().give(scratch, done);
     return st;
 }
 
@@ -1304,4 +1298,4 @@ extern "C" void tsvd_tuning_transition_shifts(int* kept, int* again) {
     *again = shifts_again;
 }
 
-extern "C" void tsvd_transition_release(void) { scratch_pool().release(); }
+extern "C" void tsvd_transition_release(void) { tsvd_idle_scratch().release(); }
