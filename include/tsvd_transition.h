@@ -77,8 +77,9 @@ tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M, int64_t N
  * pseudo-inverse of Eq. (3) selects (tsvd_fit_scales, started from zero, gives that one).
  * Returns TSVD_EVALUE if some leading vector has no ternary vector within theta (the paper's
  * algorithm raises an error there); the components found so far are kept in *rank_out.
- * max_rank <= 2048, M, N <= 8192.  Allocates its own device and pinned scratch; up to four pieces of at most 64 MiB of device and
- * 1 MiB of pinned memory each are kept for later calls (of any thread, stream and device), until tsvd_transition_release. */
+ * max_rank <= 2048, M, N <= 8192.  Allocates its own device and pinned scratch; of finished calls up to four pieces, 64 MiB
+ * of device memory in all and 1 MiB of pinned memory each, are kept for later ones (of any thread, stream and device) until tsvd_transition_release, or until an allocation of
+ * this library finds the device full.  Other allocators do not know of them: a program that is about to need all of the device calls tsvd_transition_release. */
 tsvd_status tsvd_transition(const double* W_dev, int64_t M, int64_t N, double theta, double tol, int64_t max_rank,
                             int8_t* U_dev, double* S_dev, int8_t* V_dev, int64_t* rank_out, double* errors_host,
                             void* stream);

@@ -15,6 +15,7 @@
 #include "tsvd_few.h"
 #include "tsvd_kernels.h"
 #include "tsvd_layout.h"
+#include "tsvd_scratch.h"
 #include "tsvd_thin.h"
 
 struct tsvd_handle {
@@ -571,7 +572,7 @@ extern "C" tsvd_status tsvd_pack(const int8_t* U, const float* S, const int8_t* 
             h->owns_blob = false;
         } else {
             void* d = nullptr;
-            ok = hipMalloc(&d, bytes) == hipSuccess;
+            ok = tsvd_device_malloc(&d, bytes) == hipSuccess;
             h->blob = static_cast<uint8_t*>(d);
             h->owns_blob = ok;
         }
@@ -587,7 +588,7 @@ extern "C" tsvd_status tsvd_pack(const int8_t* U, const float* S, const int8_t* 
                 const size_t sb = 256 + (size_t)h->hd.Kp * 8;
                 void* d = nullptr;
                 const unsigned one = 1u;
-                ok = hipMalloc(&d, sb) == hipSuccess;
+                ok = tsvd_device_malloc(&d, sb) == hipSuccess;
                 if (ok) {
                     h->sync = static_cast<uint8_t*>(d);
                     ok = hipMemset(d, 0, sb) == hipSuccess && hipMemcpy(d, &one, sizeof one, hipMemcpyHostToDevice) == hipSuccess;
@@ -598,7 +599,7 @@ extern "C" tsvd_status tsvd_pack(const int8_t* U, const float* S, const int8_t* 
                 const size_t db = tsvd_dense_bytes(M, K);
                 void* hostd = std::malloc(db);
                 void* d = nullptr;
-                ok = hostd && hipMalloc(&d, db) == hipSuccess;
+                ok = hostd && tsvd_device_malloc(&d, db) == hipSuccess;
                 if (ok) {
                     tsvd_internal_dense_from_blob(host, hostd);
                     h->dense_u = static_cast<uint8_t*>(d);
@@ -608,7 +609,7 @@ extern "C" tsvd_status tsvd_pack(const int8_t* U, const float* S, const int8_t* 
             }
             if (ok && env_int("TSVD_CLOCKS", 0)) {
                 void* c = nullptr;
-                if (hipMalloc(&c, TSVD_GEMV_MAX_GRID * 16 * sizeof(long long)) == hipSuccess) {
+                if (tsvd_device_malloc(&c, TSVD_GEMV_MAX_GRID * 16 * sizeof(long long)) == hipSuccess) {
                     (void)hipMemset(c, 0, TSVD_GEMV_MAX_GRID * 16 * sizeof(long long));
                     h->clocks = static_cast<long long*>(c);
                 }
@@ -723,7 +724,7 @@ extern "C" tsvd_status tsvd_forward_io(const tsvd_handle* h, const void* x_dev, 
             // does the call fall back to draining the device.
             void* d = nullptr;
             const size_t grow = std::max(need, 2 * hm->scratch_bytes);
-            if (hipMalloc(&d, grow) != hipSuccess) {
+            if (tsvd_device_malloc(&d, grow) != hipSuccess) {
                 (void)hipGetLastError();
                 return TSVD_EDEVICE;
             }

@@ -1,9 +1,10 @@
 // Scratch of calls that allocate their own: device memory, pinned host memory and two events, kept between calls.
 //
 // Allocating and freeing cost such a call 0.15 to 0.4 ms (hipMalloc 25 to 55 us, hipHostMalloc 20, hipFree 30 to 40, hipHostFree 70 to 230 and more where other memory is mapped), as
-// much as three to five components of a transition.  Up to four idle pieces are kept, each of at most 64 MiB of device and 1 MiB of pinned memory; for a fifth the one
-// that has been idle longest is freed.  A piece belongs to one call from take() to give(), and give() comes behind a wait for the stream that used it, so
-// calls of several threads, streams and devices never share one.  Idle pieces are given back by release(), and where an allocation fails.  Nothing here throws.
+// much as three to five components of a transition.  Up to four idle pieces of 64 MiB of device memory in all, and 1 MiB of pinned memory each, are kept; where that is not enough for the piece that
+// comes back, those that have been idle longest are freed.  A piece belongs to one call from take() to give(), and give() comes behind a wait for the stream that used it, so
+// calls of several threads, streams and devices never share one.  Idle pieces are given back by release(), and where the device has no memory left for this library (tsvd_device_malloc);
+// other allocators of the process do not know of them.  Nothing here throws.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
@@ -26,6 +27,7 @@ class tsvd_scratch_pool {
     std::mutex m;
     tsvd_scratch idle[MAX_IDLE];                             // the first `count`, longest idle first
     int count = 0;
+    size_t idle_bytes = 0;
 
     static void free_piece(tsvd_scratch& s) {
         for (hipEvent_t e : s.event)
@@ -48,6 +50,7 @@ class tsvd_scratch_pool {
     tsvd_scratch remove(int at) {                            // (under the lock)
         const tsvd_scratch s = idle[at];
         for (--count; at < count; ++at) idle[at] = idle[at + 1];
+        idle_bytes -= s.bytes;
         return s;
     }
 
@@ -70,7 +73,8 @@ public:
         s->device = device;
         s->bytes = (bytes + (1 << 20) - 1) >> 20 << 20;
         s->pinned_bytes = (pinned_bytes + (1 << 16) - 1) >> 16 << 16;
-        if (allocate(*s) == hipSuccess) return true;
+        const hipError_t e = allocate(*s);
+        if (e != hipErrorOutOfMemory) return e == hipSuccess;
         release();
         return allocate(*s) == hipSuccess;
     }
@@ -81,8 +85,9 @@ public:
         int outs = 0;
         {
             std::lock_guard<std::mutex> lock(m);
-            while (count == MAX_IDLE) out[outs++] = remove(0);
+            while (count == MAX_IDLE || idle_bytes + s.bytes > MAX_BYTES) out[outs++] = remove(0);
             idle[count++] = s;
+            idle_bytes += s.bytes;
             s = tsvd_scratch();
         }
         for (int i = 0; i < outs; ++i) free_piece(out[i]);
@@ -103,4 +108,13 @@ inline tsvd_scratch_pool& tsvd_idle_scratch() {
     alignas(tsvd_scratch_pool) static unsigned char memory[sizeof(tsvd_scratch_pool)];
     static tsvd_scratch_pool* const pool = new (memory) tsvd_scratch_pool;
     return *pool;
+}
+
+// hipMalloc for the library's other memory: idle scratch is no reason to fail.  (Other errors are left alone: under another stream's capture nothing may be freed either.)
+inline hipError_t tsvd_device_malloc(void** p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    tsvd_idle_scratch().release();
+    return hipMalloc(p, bytes);
 }

@@ -910,7 +910,13 @@ extern "C" tsvd_status tsvd_residual(const double* W_dev, const int8_t* U_dev, i
     double* partial = nullptr;
     if (norm2_dev) {
         // (the partial sums use the output matrix's own stream order: a scratch array per call)
-        if (hipMallocAsync(reinterpret_cast<void**>(&partial), (size_t)M * 8, s) != hipSuccess) return TSVD_EDEVICE;
+        hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&partial), (size_t)M * 8, s);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            tsvd_idle_scratch().release();
+            e = hipMallocAsync(reinterpret_cast<void**>(&partial), (size_t)M * 8, s);
+        }
+        if (e != hipSuccess) return TSVD_EDEVICE;
     }
     hipLaunchKernelGGL(tsvd_residual_kernel, dim3((unsigned)M), dim3(256), (size_t)K * 8, s, W_dev, U_dev, (long long)ldu, S_dev,
                        V_dev, (int)K, (int)N, R_dev, partial);

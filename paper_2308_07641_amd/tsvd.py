@@ -421,7 +421,7 @@ def tsvd_transition(W, theta: float, tol: float, max_rank: int, stream=None, q: 
 
 
 def tsvd_transition_release() -> None:
-    """Frees the scratch that finished transitions left for later ones."""
+    """Frees the scratch that finished transitions left for later ones (64 MiB at most, which torch's allocator does not know of)."""
     load_library().tsvd_transition_release()
 
 

@@ -89,7 +89,12 @@ static int keeps_and_gives_back() {
     CHECK(used == 16 * MiB && events == 8);                                  // four at most
     CHECK(pool.take(65 * MiB, 1, &s[0]));
     pool.give(s[0], true);
-    CHECK(used <= 64 * MiB);                                                 // none above 64 MiB
+    CHECK(used == 16 * MiB);                                                 // none above 64 MiB
+    for (int i = 0; i < 3; ++i) CHECK(pool.take((size_t)(20 + 10 * i) * MiB, 1, &s[i]));
+    for (int i = 0; i < 3; ++i) pool.give(s[i], true);
+    CHECK(used == 40 * MiB);                                                 // nor more than that in all: the last one
+    CHECK(pool.take(30 * MiB, 1, &s[0]) && s[0].bytes == 40 * MiB);
+    pool.give(s[0], true);
     CHECK(pool.take(MiB, 2 * MiB, &s[0]));
     pool.give(s[0], true);
     CHECK(pinned_used <= 4 * MiB);
@@ -112,8 +117,41 @@ static int works_without_heap() {
     return 0;
 }
 
+// Idle scratch is no reason for an allocation of the library to fail; other errors than a full device are handed on, and nothing is freed for them.
+static int is_no_reason_to_fail() {
+    tsvd_scratch_pool& pool = tsvd_idle_scratch();
+    tsvd_scratch s;
+    void* p = nullptr;
+    limit = 100 * MiB;
+    CHECK(pool.take(60 * MiB, 1, &s));
+    pool.give(s, true);
+    CHECK(used == 60 * MiB);
+    CHECK(tsvd_device_malloc(&p, 70 * MiB) == hipSuccess && used == 70 * MiB);
+    CHECK(hipFree(p) == hipSuccess);
+    CHECK(pool.take(60 * MiB, 1, &s));
+    pool.give(s, true);
+    tsvd_scratch t;
+    CHECK(pool.take(80 * MiB, 1, &t) && used == 80 * MiB);                   // nor for one of its own
+    pool.give(t, true);
+    CHECK(used == 0);
+    CHECK(pool.take(60 * MiB, 1, &s));
+    pool.give(s, true);
+    CHECK(tsvd_device_malloc(&p, 101 * MiB) == hipErrorOutOfMemory && used == 0);
+    CHECK(pool.take(60 * MiB, 1, &s));
+    pool.give(s, true);
+    refuse = hipErrorStreamCaptureUnsupported;
+    frees = mallocs = 0;
+    CHECK(tsvd_device_malloc(&p, MiB) == refuse && mallocs == 1 && frees == 0);
+    CHECK(!pool.take(80 * MiB, 1, &t) && mallocs == 2 && frees == 0);
+    refuse = hipSuccess;
+    limit = (size_t)-1;
+    pool.release();
+    CHECK(used == 0 && pinned_used == 0 && events == 0);
+    return 0;
+}
+
 int main() {
-    if (keeps_and_gives_back() || works_without_heap()) return 1;
+    if (keeps_and_gives_back() || works_without_heap() || is_no_reason_to_fail()) return 1;
     std::printf("scratch driver: ok\n");
     return 0;
 }
