@@ -79,7 +79,8 @@ tsvd_status tsvd_leading_singular_pair(const double* R_dev, int64_t M, int64_t N
  * algorithm raises an error there); the components found so far are kept in *rank_out.
  * max_rank <= 2048, M, N <= 8192.  Allocates its own device and pinned scratch; of finished calls up to four pieces, 64 MiB
  * of device memory in all and 1 MiB of pinned memory each, are kept for later ones (of any thread, stream and device) until tsvd_transition_release, or until an allocation of
- * this library finds the device full.  Other allocators do not know of them: a program that is about to need all of the device calls tsvd_transition_release. */
+ * this library finds the device full.  Other allocators do not know of them: a program that is about to need all of the device calls tsvd_transition_release.
+ * Waits for the stream; a stream that is being captured is refused (TSVD_EDEVICE) with nothing enqueued. */
 tsvd_status tsvd_transition(const double* W_dev, int64_t M, int64_t N, double theta, double tol, int64_t max_rank,
                             int8_t* U_dev, double* S_dev, int8_t* V_dev, int64_t* rank_out, double* errors_host,
                             void* stream);

@@ -1066,6 +1066,12 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     hipStream_t s = static_cast<hipStream_t>(stream);
     *rank_out = 0;
     shifts_kept = shifts_again = 0;
+    // The host waits for what is enqueued, so there is nothing to capture; refused before anything is, or a graph could be left with work on scratch that belongs to the next call.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return TSVD_EDEVICE;
+    }
     const bool squares = tsvd_pair_squares(M, N);
     const int mp = (int)((M + 15) & ~15), np = (int)((N + 15) & ~15);       // pitches of the component-major factors
     const int pieces = (int)((N + 255) / 256);                              // pieces of a row of the residual

@@ -418,6 +418,35 @@ def test_transition_scratch_is_reused_by_calls_of_any_size_thread_and_stream(tsv
     assert same(run(1), want[1])
 
 
+def test_transition_is_refused_under_capture(tsvd):
+    """The host waits for the device, so a transition cannot be captured: with scratch at hand or without it is refused before anything is enqueued, the capture stays
+    whole, and the graph's replays are those of its other work."""
+    import torch
+    W = _dev(np.random.default_rng(22).laplace(size=(140, 130)))
+    want = [t.clone() for t in tsvd.tsvd_transition(W, 0.65, 0.0, 6)[:3]]
+    x = torch.zeros(1000, device="cuda:0")
+    for fresh in (False, True):
+        if fresh:
+            tsvd.tsvd_transition_release()
+        print(f"case transition under capture, {'no ' if fresh else ''}scratch at hand", flush=True)
+        out = (torch.zeros((140, 6), dtype=torch.int8, device="cuda:0"), torch.zeros((6,), dtype=torch.float64, device="cuda:0"), torch.zeros((6, 130), dtype=torch.int8, device="cuda:0"))
+        import ctypes
+        rank = ctypes.c_int64(-1)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            x.add_(1.0)
+            st = tsvd.load_library().tsvd_transition_q(W.data_ptr(), 140, 130, 0.65, 0.0, 6, 1, out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(), ctypes.byref(rank), None,
+                                                       torch.cuda.current_stream().cuda_stream)
+        assert st == 4 and rank.value == 0
+        x.zero_()
+        for replay in range(3):
+            graph.replay()
+            got = tsvd.tsvd_transition(W, 0.65, 0.0, 6)
+            assert all(torch.equal(a, b) for a, b in zip(got, want)), replay
+            assert torch.equal(x, torch.full_like(x, replay + 1.0)) and all(int(t.abs().sum()) == 0 for t in out)
+
+
 def test_transition_of_equal_singular_values(tsvd):
     """A Hadamard matrix: all singular values equal, so no number of squarings leaves a matrix of low rank and any vector will do; the
     pair taken is a unit vector and a column (or row), which is ternary, and every component removes one of 32."""
