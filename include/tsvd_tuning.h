@@ -68,6 +68,13 @@ int tsvd_tuning_one_launch(const tsvd_handle* h, long long B);
  * call takes no split tiles. */
 int tsvd_tuning_tiles_by_xcd(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u);
 
+/* How wavefronts of a thin panel of `tiles` tiles of 16 tokens share the rank blocks of stage V that do not go round, for a rank of K and a contraction of N (gathers: of a convolution's
+ * taps, rows_of_taps: three side by side in one load): 0 not at all, else 10 x the blocks that are shared + the wavefronts that share each, + 100 where x passes in chunks; -1 without such panels. */
+int tsvd_tuning_thin_shares(int64_t K, int64_t N, int tiles, int gathers, int rows_of_taps);
+
+/* The last launch of thin panels by this thread since this was last asked: 1000 x tiles + what tsvd_tuning_thin_shares says; 0 where there was none. */
+int tsvd_tuning_thin_last(void);
+
 /* Of the last tsvd_transition or tsvd_transition_q of this thread: iterations whose squarings were shifted and that were kept, and those that were
  * taken again because the shifts did not hold. */
 void tsvd_tuning_transition_shifts(int* kept, int* again);

@@ -26,6 +26,7 @@
 // What bounds them: the matrix instructions of the panels' last round, and the code words that every workgroup pulls from its L2.  By
 // counters the matrix pipes are busy 0.43 of the compute units' cycles in the first and 0.28 in the second (which has 196 panels, and six rank blocks
 // in stage V for eight wavefronts).
+#include "../../include/tsvd_tuning.h"
 #include "tsvd_thin.h"
 
 #include <algorithm>
@@ -588,15 +589,39 @@ int tsvd_thin_chunk(long long K, long long N, int tiles, bool conv) {
 // Stage V's last `left` rank blocks (1 to 8): where one or two are left several wavefronts share each, a part of its contraction everyone; of five or six the first four stay
 // whole, one on each SIMD, and the other four wavefronts share the rest.  Of three, four or seven no SIMD has less than without, and shared they cost 3 to 6 % (3 x 3 from 69 channels, rank 412).
 // The sums meet behind two more barriers, 0.3 us: worth it from three blocks that the longest part is shorter by, six where a SIMD has a whole one beside (85 channels, rank 704: 12.4 -> 12.7 us).
-// Rows of taps in chunks are dear to make: with two rank blocks the six others make them all in the time that these two take (491 channels, rank 147: 36.2 -> 37.7 shared).
-static bool thin_shares(thin_args& a, int tiles, int left, int room, bool rows_of_taps) {
+// Rows of taps in chunks are dear to make: with two rank blocks the six others make them all in the time that these two take (491 channels, rank 147: 36.2 -> 37.7 shared).  The last two of ten in chunks
+// of eight blocks leave each of the eight wavefronts a single fetch, and nobody who makes records first (310 channels, rank 1250, 3136 positions: 29.3 -> 30.3 us shared, 4096 features as rows of tokens 41.1 -> 41.7;
+// in chunks of ten, 350 channels, 34.4 -> 33.4).
+static bool thin_shares(thin_args& a, int tiles, bool conv, bool rows_of_taps) {
+    const int left = (a.nub + 7) % 8 + 1, room = LDS_BYTES - a.nub * tiles * FP6_REC_BYTES - (conv ? a.nvb * 512 : 0);
     a.whole = left > 4 ? 4 : 0;
     a.shared = left - a.whole;
     a.parts = 0;
-    if (a.shared > 2 || (rows_of_taps && a.buffers == 2 && a.nub == 2)) return false;
+    if (a.shared > 2 || (a.buffers == 2 && a.shared == 2 && (a.nub == 2 ? rows_of_taps : a.nub == 10 && a.chunk <= 8))) return false;
     while (a.shared << (a.parts + 1) <= 8 - a.whole && 2 << a.parts <= (a.chunk + 1) / 2) ++a.parts;
     const int sums = a.shared * ((1 << a.parts) - 1) * tiles * 8192, longest = (a.nvb + (1 << a.parts) - 1) >> a.parts;
     return sums <= room && (a.nvb - longest) * tiles >= (a.whole ? 6 : 3);
+}
+static void thin_blocks(thin_args& a, long long K, long long N, int tiles, bool conv) {
+    a.nvb = (int)((N + 127) / 128);
+    a.nub = (int)((K + 127) / 128);
+    a.chunk = tsvd_thin_chunk(K, N, tiles, conv);
+    a.buffers = a.chunk < a.nvb ? 2 : 1;
+}
+
+static int thin_shares_code(const thin_args& a) { return 100 * (a.buffers - 1) + 10 * a.shared + (1 << a.parts); }
+static thread_local int thin_last = 0;       // for tsvd_tuning_thin_last
+
+extern "C" int tsvd_tuning_thin_last(void) {
+    const int last = thin_last;
+    thin_last = 0;
+    return last;
+}
+extern "C" int tsvd_tuning_thin_shares(int64_t K, int64_t N, int tiles, int gathers, int rows_of_taps) {
+    thin_args a;
+    thin_blocks(a, K, N, tiles, gathers != 0);
+    if (a.chunk == 0) return -1;
+    return thin_shares(a, tiles, gathers != 0, rows_of_taps != 0) ? thin_shares_code(a) : 0;
 }
 
 hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t stream) {
@@ -610,8 +635,6 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
     a.tile_u_bytes = (unsigned)((size_t)hd.Mp * hd.Kp / 4);
     a.nkt_v = (int)(hd.Np / 256);
     a.nkt_u = (int)(hd.Kp / 256);
-    a.nvb = (int)((hd.N + 127) / 128);
-    a.nub = (int)((hd.K + 127) / 128);
     a.x = g.x;
     a.x_bytes = (unsigned)tsvd_thin_x_bytes(g);
     a.N = (int)hd.N;
@@ -647,13 +670,13 @@ hipError_t tsvd_thin_launch(const tsvd_thin_problem& g, int tiles, hipStream_t s
         if (best == 2) break;
     }
     const bool conv = g.source == THIN_CONV;
+    thin_blocks(a, hd.K, hd.N, tiles, conv);
     if (g.source == THIN_FEATURE_MAJOR && 128ll * a.nvb * a.ldx >= 1ll << 30) return hipErrorNotSupported;     // (element loads reach rows, those beyond N too, at 32-bit offsets)
     if (conv && g.kv1 * g.kv2 > MAX_TAPS) return hipErrorNotSupported;
-    a.chunk = tsvd_thin_chunk(hd.K, hd.N, tiles, conv);
     if (a.chunk == 0) return hipErrorNotSupported;
-    a.buffers = a.chunk < a.nvb ? 2 : 1;
     const int rb = (a.nub + 7) / 8;
-    const bool shared = thin_shares(a, tiles, (a.nub + 7) % 8 + 1, LDS_BYTES - a.nub * tiles * FP6_REC_BYTES - (conv ? a.nvb * 512 : 0), thin_rows_of_taps(g.source, a));
+    const bool shared = thin_shares(a, tiles, conv, thin_rows_of_taps(g.source, a));
+    thin_last = 1000 * tiles + (shared ? thin_shares_code(a) : 0);
     const int lds = thin_x_bytes(a, tiles, shared) + a.nub * tiles * FP6_REC_BYTES + (conv ? a.nvb * 512 : 0);
     if (tiles == 1 && rb == 1) return launch<1, 1>(g.source, a, shared, lds, stream);
     if (tiles == 1 && rb == 2) return launch<1, 2>(g.source, a, shared, lds, stream);

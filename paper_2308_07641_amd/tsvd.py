@@ -50,6 +50,8 @@ _PROTOTYPES = {
     "tsvd_tuning_tile_shapes": (ctypes.c_int, [_vp, ctypes.c_longlong, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "tsvd_tuning_one_launch": (ctypes.c_int, [_vp, ctypes.c_longlong]),
     "tsvd_tuning_tiles_by_xcd": (ctypes.c_int, [_vp, ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
+    "tsvd_tuning_thin_shares": (ctypes.c_int, [_i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int]),
+    "tsvd_tuning_thin_last": (ctypes.c_int, []),
     "tsvd_tuning_transition_shifts": (None, [ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "tsvd_tuning_read_clocks": (ctypes.c_int, [_vp, _vp, ctypes.c_int]),
     "tsvd_ternarize": (ctypes.c_int, [_vp, _i64, _i64, _i64, ctypes.c_double, _vp, _i64, _vp, _vp]),
@@ -314,6 +316,14 @@ def tsvd_tuning_tiles_by_xcd(h: Handle, B: int, x_dtype: int):
     if load_library().tsvd_tuning_tiles_by_xcd(h.ptr, B, x_dtype, ctypes.byref(v), ctypes.byref(u)) != 0:
         raise ValueError("tsvd_tuning_tiles_by_xcd: the call takes no split tiles")
     return bool(v.value), bool(u.value)
+
+
+def tsvd_tuning_thin_shares(K: int, N: int, tiles: int, gathers: bool = False, rows_of_taps: bool = False) -> int:
+    return int(load_library().tsvd_tuning_thin_shares(K, N, tiles, int(gathers), int(rows_of_taps)))
+
+
+def tsvd_tuning_thin_last() -> int:
+    return int(load_library().tsvd_tuning_thin_last())
 
 
 def tsvd_tuning_transition_shifts():

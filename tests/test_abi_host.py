@@ -45,6 +45,17 @@ def test_tuning_switches_are_explicit_and_the_library_ignores_the_environment(mo
     assert "getenv" not in src
 
 
+@pytest.mark.parametrize("tiles,ranks,blocks,taps,shares", [
+    (1, 1, 5, False, 0), (1, 1, 6, False, 12), (1, 1, 7, False, 14), (1, 1, 15, True, 18), (1, 1, 33, False, 114), (1, 2, 32, False, 124), (1, 2, 30, True, 0),
+    (1, 3, 40, False, 0), (1, 4, 40, False, 0), (1, 5, 7, False, 0), (1, 5, 8, True, 14), (1, 6, 11, False, 0), (1, 6, 12, False, 22), (1, 6, 26, True, 122), (1, 7, 40, False, 0),
+    (1, 9, 25, False, 114), (1, 10, 23, False, 24), (1, 10, 24, False, 0), (1, 10, 25, False, 124), (1, 10, 22, True, 0), (1, 10, 32, True, 0), (1, 10, 35, True, 124),
+    (1, 17, 4, False, -1), (2, 2, 15, False, 122), (2, 6, 11, True, 122), (2, 9, 4, False, -1)])
+def test_thin_panels_share_rank_blocks_where_it_pays(tiles, ranks, blocks, taps, shares):
+    """Blocks of 128 ranks that several wavefronts share (10 x blocks + wavefronts of each, + 100 where x passes in chunks), on both sides of the rule's lines: the
+    last two of ten blocks were shared in chunks of eight, which made such calls up to 1.03 times as long."""
+    assert tsvd.tsvd_tuning_thin_shares(128 * ranks - 30, 128 * blocks - 50, tiles, taps, taps) == shares
+
+
 def test_strerror_covers_all_codes():
     texts = [tsvd.tsvd_strerror(s) for s in range(7)]
     assert texts[0] == "ok" and len(set(texts)) == 7
