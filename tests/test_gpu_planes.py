@@ -208,14 +208,21 @@ def test_thin_panels_of_several_workgroups(tsvd, M, N, K, B, tiles):
     _check(tsvd, M, N, K, B, "bf16", {"TSVD_THIN": tiles})
 
 
-@pytest.mark.parametrize("M,N,K,B", [(70, 300, 128, 33), (70, 513, 129, 40), (40, 900, 256, 17), (50, 2000, 60, 35), (40, 1030, 640, 31), (70, 1500, 700, 33), (30, 5000, 100, 50), (30, 4700, 250, 40),
-                                     (30, 4100, 620, 33), (60, 1030, 1100, 20), (60, 4000, 1280, 18), (30, 2100, 1664, 35), (30, 3000, 1700, 33)])
-@pytest.mark.parametrize("tiles", [1, 2])
-def test_thin_panels_share_rank_blocks(tsvd, M, N, K, B, tiles):
+@pytest.mark.parametrize("M,N,K,B,tiles,shares", [
+    (70, 700, 128, 33, 1, 12), (40, 900, 100, 17, 1, 14), (50, 2000, 60, 35, 1, 18), (30, 4300, 100, 50, 1, 114), (30, 5600, 128, 40, 1, 118), (70, 700, 129, 40, 1, 22),
+    (40, 900, 256, 17, 1, 24), (30, 4200, 250, 40, 1, 124), (40, 1030, 640, 31, 1, 14), (30, 3800, 600, 33, 1, 114), (70, 1600, 700, 33, 1, 22), (30, 3700, 760, 20, 1, 122),
+    (60, 1030, 1100, 20, 1, 14), (60, 2000, 1025, 20, 1, 18), (30, 3300, 1100, 18, 1, 114), (60, 900, 1250, 35, 1, 24), (60, 3200, 1280, 18, 1, 124), (30, 2100, 1664, 35, 1, 14),
+    (30, 2800, 1600, 33, 1, 114), (30, 1600, 1700, 33, 1, 22), (30, 3000, 1790, 33, 1, 122), (60, 3000, 1280, 18, 1, 0),
+    (40, 600, 128, 33, 2, 12), (40, 1000, 100, 50, 2, 14), (50, 1900, 60, 35, 2, 18), (30, 2100, 100, 40, 2, 112), (70, 520, 256, 40, 2, 22), (40, 900, 250, 65, 2, 24),
+    (30, 2000, 200, 33, 2, 122), (40, 760, 600, 31, 2, 12), (40, 900, 640, 33, 2, 14), (30, 1600, 620, 33, 2, 112), (70, 800, 700, 33, 2, 22), (30, 1500, 760, 40, 2, 122)])
+def test_thin_panels_share_rank_blocks(tsvd, M, N, K, B, tiles, shares):
     """One, two, five and six rank blocks that do not go round, alone or behind eight that do: two to eight wavefronts share a block's contraction, some with nothing of
-    it where there is little or in the last chunk; x as a whole and in chunks.  (The bound is that of test_thin_panels: sums of fp32 in another order.)"""
+    it where there is little or in the last chunk; x as a whole and in chunks (`shares`: 10 x blocks + wavefronts of each, + 100 in chunks; these are the kernels that
+    run).  (The bound is that of test_thin_panels: sums of fp32 in another order.)"""
     print(f"case thin shares {M} {N} {K} {B} {tiles}", flush=True)
+    tsvd.tsvd_tuning_thin_last()
     _check(tsvd, M, N, K, B, "bf16", {"TSVD_MID": 0, "TSVD_PANEL": 0, "TSVD_THIN": tiles, "TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 9})
+    assert tsvd.tsvd_tuning_thin_last() == 1000 * tiles + shares
 
 
 @pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
@@ -264,15 +271,7 @@ def test_tiles_by_xcd(tsvd, M, N, K, B, v, u, placed, x_dtype):
     tsvd.tsvd_free(h)
 
 
-@pytest.mark.parametrize("tiles", [1, 2])
-@pytest.mark.parametrize("form,ci,co,k1,K,H,W,geom", [
-    (0, 5, 7, 3, 60, 6, 4, ((1, 1), (1, 1), (1, 1))), (0, 5, 7, 3, 60, 6, 3, ((1, 1), (1, 1), (1, 1))), (0, 43, 9, 3, 150, 5, 9, ((2, 3), (4, 5), (2, 1))),
-    (0, 20, 9, 5, 150, 7, 11, ((1, 2), (0, 3), (1, 1))), (2, 90, 3, 2, 300, 6, 5, ((1, 1), (1, 2), (1, 1))), (0, 20, 9, 3, 150, 7, 11, ((1, 1), (2, 2), (1, 2))),
-    (0, 300, 5, 3, 150, 5, 7, ((1, 1), (1, 1), (1, 1))), (0, 460, 5, 3, 777, 5, 5, ((1, 1), (1, 1), (1, 1))), (0, 460, 5, 3, 1100, 5, 5, ((1, 1), (0, 1), (1, 1)))])
-def test_thin_panels_gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom, tiles):
-    """Rows of three taps in loads of four elements: images as wide as a load and narrower (which take element loads, as dilated rows do), taps that
-    begin more than a load before or behind a row, kernels of more and fewer rows, x at an odd element; and x in chunks that wavefronts of
-    fewer rank blocks make more records of.  Exact."""
+def _gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom, tiles, shares=None):
     import torch
     from oracle import conv as oc
     k2, images = 3, 5
@@ -288,9 +287,32 @@ def test_thin_panels_gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom,
     tsvd.tsvd_tuning_set("TSVD_THIN", tiles)
     xd = torch.full((x.size + 9,), float("nan"), dtype=torch.bfloat16, device="cuda:0")        # (nothing from beside x may reach y)
     xd = xd[1:1 + x.size].view(ci, images, H, W).copy_(torch.from_numpy(x.transpose(1, 0, 2, 3)))
+    tsvd.tsvd_tuning_thin_last()
     y = tsvd.tsvd_conv2d_forward(h, form, ci, co, k1, k2, xd, *geom)
+    assert shares is None or tsvd.tsvd_tuning_thin_last() == 1000 * tiles + shares
     assert torch.equal(y.cpu(), torch.from_numpy(np.ascontiguousarray(ref.transpose(1, 0, 2, 3))).to(y.dtype))
     tsvd.tsvd_free(h)
+
+
+@pytest.mark.parametrize("tiles", [1, 2])
+@pytest.mark.parametrize("form,ci,co,k1,K,H,W,geom", [
+    (0, 5, 7, 3, 60, 6, 4, ((1, 1), (1, 1), (1, 1))), (0, 5, 7, 3, 60, 6, 3, ((1, 1), (1, 1), (1, 1))), (0, 43, 9, 3, 150, 5, 9, ((2, 3), (4, 5), (2, 1))),
+    (0, 20, 9, 5, 150, 7, 11, ((1, 2), (0, 3), (1, 1))), (2, 90, 3, 2, 300, 6, 5, ((1, 1), (1, 2), (1, 1))), (0, 20, 9, 3, 150, 7, 11, ((1, 1), (2, 2), (1, 2))),
+    (0, 300, 5, 3, 150, 5, 7, ((1, 1), (1, 1), (1, 1))), (0, 460, 5, 3, 777, 5, 5, ((1, 1), (1, 1), (1, 1))), (0, 460, 5, 3, 1100, 5, 5, ((1, 1), (0, 1), (1, 1)))])
+def test_thin_panels_gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom, tiles):
+    """Rows of three taps in loads of four elements: images as wide as a load and narrower (which take element loads, as dilated rows do), taps that
+    begin more than a load before or behind a row, kernels of more and fewer rows, x at an odd element; and x in chunks that wavefronts of
+    fewer rank blocks make more records of.  Exact."""
+    _gather_rows_of_three(tsvd, form, ci, co, k1, K, H, W, geom, tiles)
+
+
+@pytest.mark.parametrize("ci,co,K,H,W,tiles,shares", [
+    (430, 5, 100, 5, 7, 1, 114), (120, 9, 640, 6, 5, 1, 14), (380, 5, 600, 5, 7, 1, 114), (180, 9, 700, 7, 5, 1, 22), (380, 5, 768, 5, 7, 1, 122), (150, 9, 1100, 5, 9, 1, 14),
+    (340, 5, 1030, 5, 7, 1, 114), (150, 9, 1250, 6, 6, 1, 24), (360, 5, 1280, 5, 7, 1, 124), (290, 5, 1600, 5, 5, 1, 114), (270, 5, 1700, 5, 7, 1, 122),
+    (240, 9, 128, 5, 7, 2, 112), (110, 9, 200, 6, 9, 2, 24), (200, 9, 600, 5, 7, 2, 112), (256, 5, 768, 7, 7, 2, 122), (256, 33, 700, 5, 8, 2, 122), (320, 5, 256, 5, 7, 2, 0)])
+def test_thin_panels_gather_rows_of_three_and_share_rank_blocks(tsvd, ci, co, K, H, W, tiles, shares):
+    """The same where rank blocks are shared (as test_thin_panels_share_rank_blocks has it), and where two are not because of the rows."""
+    _gather_rows_of_three(tsvd, 0, ci, co, 3, K, H, W, ((1, 1), (1, 1), (1, 1)), tiles, shares)
 
 
 @pytest.mark.parametrize("switches", [{"TSVD_THIN": 1}, {"TSVD_THIN": 2}, {"TSVD_SPLIT_V": 9, "TSVD_SPLIT_U": 10}, {"TSVD_SPLIT_V": 10, "TSVD_SPLIT_U": 10, "TSVD_SPLIT_X": 1},
