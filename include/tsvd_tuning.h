@@ -64,6 +64,10 @@ int tsvd_tuning_tile_shapes(const tsvd_handle* h, long long B, int* shape_v, int
 /* Whether B tokens that take the single-token kernels run both stages in one launch (1) or in two (0). */
 int tsvd_tuning_one_launch(const tsvd_handle* h, long long B);
 
+/* The tiles of the plane path's stages (V, U) that a call of B tokens of feature-major x takes, as TSVD_SPLIT_V has them, 0: those that are not split.  Returns 0 on success, 1 where a
+ * call takes none of them. */
+int tsvd_tuning_split_tiles(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u);
+
 /* Whether the split tiles that a call of B tokens takes (stage V, stage U) are dealt to the XCDs in groups.  Returns 0 on success, 1 where a
  * call takes no split tiles. */
 int tsvd_tuning_tiles_by_xcd(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u);

@@ -956,6 +956,14 @@ extern "C" int tsvd_tuning_one_launch(const tsvd_handle* h, long long B) {
     return tsvd_gemv_fused_fits(gemv_fused_sizes(h->hd, (int)std::min<long long>(gemv_tokens(h, B), B)), h->cu_count);
 }
 
+extern "C" int tsvd_tuning_split_tiles(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u) {
+    if (!h || !v || !u || B < 1 || !use_gemm(h, B, x_dtype)) return 1;
+    const tsvd_batch_plan plan = batch_plan(batch_call(h, B, x_dtype, false, false, false, false, true, true));
+    if (!plan.split) return 1;
+    *v = plan.split_v, *u = plan.split_u;
+    return 0;
+}
+
 extern "C" int tsvd_tuning_tiles_by_xcd(const tsvd_handle* h, long long B, tsvd_dtype x_dtype, int* v, int* u) {
     if (!h || !v || !u || B < 1 || !use_gemm(h, B, x_dtype)) return 1;
     const tsvd_batch_plan plan = batch_plan(batch_call(h, B, x_dtype, false, false, false, false, true, true));

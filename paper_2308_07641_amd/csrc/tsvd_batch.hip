@@ -137,7 +137,8 @@ double panel_cost(const tsvd_batch_call& c) {
 // fp32 activations run on planes whatever the shapes, so theirs are chosen by factors of their own up to 1024 tokens, fitted to the kernels as they are (kernel traces of 180 calls, 90 of them
 // fp32, each with all shapes: 10 to 17 % rms; the shapes taken are 0.6 % slower than the best of each stage, those of the factors above 5 %: those know neither that wavefronts take blocks of
 // their own nor what y costs).  Beyond, where rounds of many workgroups follow each other, they take split tiles too often (3520 x 2156 x 6144 at 6540 tokens 631 -> 758 us, 768 x 911 x 512 at 10040
-// 69 -> 74).  1898 x 1344 x 1120 at 211 tokens 22.4 -> 17.2 us, 4655 x 1408 x 114 at 23 17.4 -> 12.2, 455 x 1052 x 263 at 896 19.6 -> 13.5.
+// 69 -> 74).  1898 x 1344 x 1120 at 211 tokens 22.4 -> 17.2 us, 4655 x 1408 x 114 at 23 17.4 -> 12.2, 455 x 1052 x 263 at 896 19.6 -> 13.5;
+// 172 calls of 17 to 1024 tokens 0.96 of the time on the average, one of them longer (3072 x 768 x 1536 at 333, between two tiles' lines, 21.3 -> 22.0).
 struct own_factors {
     int shape;
     double v0, v_round, v_step, v_made, planes, planes_each, u0, u_round, u_step, u_mb;

@@ -49,6 +49,7 @@ _PROTOTYPES = {
                                                   _vp, _sz, _vp, ctypes.c_int]),
     "tsvd_tuning_tile_shapes": (ctypes.c_int, [_vp, ctypes.c_longlong, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "tsvd_tuning_one_launch": (ctypes.c_int, [_vp, ctypes.c_longlong]),
+    "tsvd_tuning_split_tiles": (ctypes.c_int, [_vp, ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "tsvd_tuning_tiles_by_xcd": (ctypes.c_int, [_vp, ctypes.c_longlong, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "tsvd_tuning_thin_shares": (ctypes.c_int, [_i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int]),
     "tsvd_tuning_thin_last": (ctypes.c_int, []),
@@ -309,6 +310,13 @@ def tsvd_tuning_tile_shapes(h: Handle, B: int):
 
 def tsvd_tuning_one_launch(h: Handle, B: int) -> bool:
     return bool(load_library().tsvd_tuning_one_launch(h.ptr, B))
+
+
+def tsvd_tuning_split_tiles(h: Handle, B: int, x_dtype: int):
+    v, u = ctypes.c_int(0), ctypes.c_int(0)
+    if load_library().tsvd_tuning_split_tiles(h.ptr, B, x_dtype, ctypes.byref(v), ctypes.byref(u)) != 0:
+        raise ValueError("tsvd_tuning_split_tiles: the call takes none of the plane path's tiles")
+    return v.value, u.value
 
 
 def tsvd_tuning_tiles_by_xcd(h: Handle, B: int, x_dtype: int):

@@ -225,6 +225,20 @@ def test_thin_panels_share_rank_blocks(tsvd, M, N, K, B, tiles, shares):
     assert tsvd.tsvd_tuning_thin_last() == 1000 * tiles + shares
 
 
+@pytest.mark.parametrize("M,N,K,B,v,u", [
+    (300, 260, 200, 17, 9, 9), (700, 600, 500, 700, 9, 10), (1500, 300, 200, 700, 9, 0), (200, 2000, 1500, 511, 10, 9), (2000, 1200, 700, 700, 10, 18), (2000, 1200, 700, 1000, 10, 0),
+    (130, 500, 1800, 700, 18, 9), (3000, 1500, 1500, 700, 18, 0), (3000, 1500, 1500, 1000, 18, 20), (600, 300, 3000, 700, 20, 9), (600, 300, 3000, 1000, 20, 10),
+    (700, 600, 500, 1024, 9, 10), (700, 600, 500, 1025, 10, 10), (130, 500, 1800, 1024, 18, 9), (130, 500, 1800, 1025, 20, 9)])
+def test_fp32_calls_choose_their_tiles(tsvd, M, N, K, B, v, u):
+    """Calls of fp32 activations without switches: each tile of either stage as the estimates choose it (on 256 compute units), and both sides of the 1024 tokens where
+    the other factors begin."""
+    print(f"case fp32 choice {M} {N} {K} {B}", flush=True)
+    h = tsvd.tsvd_pack(np.zeros((M, K), np.int8), np.ones(K, np.float32), np.zeros((K, N), np.int8))
+    assert tsvd.tsvd_tuning_split_tiles(h, B, tsvd.TSVD_F32) == (v, u)
+    tsvd.tsvd_free(h)
+    _check(tsvd, M, N, K, B, "f32", {})
+
+
 @pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("own_x", [0, 1])
 @pytest.mark.parametrize("v,u", [(9, 9), (10, 10)])
