@@ -1165,17 +1165,18 @@ extern "C" tsvd_status tsvd_transition_q(const double* W_dev, int64_t M, int64_t
     int64_t least_until = 0;
     // With q = 1 pairs are shifted from the second iteration on (tsvd_pair_square), two squarings fewer than without.  One that has to be taken again costs itself, the one behind it and a
     // wait, what 20 to 40 shifted ones save, so shifts are left to where they hold:
-    //   - eight to eleven squarings.  With fewer the spectrum falls: there is little to save, and shifted pairs could need more than others;  with more it has clusters, whose squarings
+    //   - eight to ten squarings.  With fewer the spectrum falls: there is little to save, and shifted pairs could need more than others.  With eleven the edge, 2 % below the second eigenvalue,
+    //     leaves more directions above it than plain squarings do (700 x 600, values from 1 down to a half: 6.8 -> 7.2 ms), and where more are needed there are clusters, whose squarings
     //     end by themselves without shifts;
     //   - a second eigenvalue that the last iteration known has not lost beside the first, and more than three directions left in it: behind fewer a step down may lie, from where
     //     the shifts reach too little;
     //   - 128 values and more: the gaps of fewer vary more from one pair to the next (188 x 112, 8 components: 0.65 -> 0.75 ms with shifts, 192 x 125, 40: 3.10 -> 3.26; 512 x 128, 15: 1.23 -> 1.09);
     //   - after one that was taken again only where PAYS_FROM components are left, never after the second.
-    // Of 980 random spectra (128 to 768 values, 6 to 40 components) none takes more than 1.05 of the time that it takes without shifts: Laplace, normal, ternary and linear ones 0.89 on
-    // the average, groups of equal values 0.97, values above a bulk 0.955, exponentials and low rank with noise 0.98, power laws and close values 1.00.  (With shifts from six squarings on, and as few as three of them, 0.05 of these spectra took
-    // 1.15 to 1.6 of it: power laws 1.11 on the average, values above a bulk 1.08, groups 1.05.)  (With more pairs an iteration one that misses takes all of them
-    // again: Laplace matrices gained 0.94, four an iteration, a linear spectrum took 1.5 times as long.)
-    constexpr int SHIFTS_FROM = 8, SHIFTS_TO = 11, PAYS_FROM = 24;
+    // Of 1380 random spectra (128 to 768 values, 6 to 40 components) three take more than 1.05 of the time that they take without shifts, up to 1.10: Laplace, normal, ternary and linear
+    // ones 0.89 on the average, groups of equal values 0.97, values above a bulk 0.955, exponentials and low rank with noise 0.98, power laws and close values 1.00.  (With shifts from six squarings on, and as few as
+    // three of them, 0.05 of such spectra took 1.15 to 1.6 of it: power laws 1.11 on the average, values above a bulk 1.08, groups 1.05.)  (With more pairs an iteration one that misses
+    // takes all of them again: Laplace matrices gained 0.94, four an iteration, a linear spectrum took 1.5 times as long.)
+    constexpr int SHIFTS_FROM = 8, SHIFTS_TO = 10, PAYS_FROM = 24;
     const int forced = tsvd_tune("TSVD_TRANSITION_SHIFTED", 0);
     bool resolved = false;
     int shifted[2] = {0, 0};                                                 // squarings of iteration i, where they are shifted, in [i & 1]
