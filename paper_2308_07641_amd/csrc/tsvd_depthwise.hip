@@ -9,8 +9,8 @@
 // The 16 columns of the B operand are strips: R output rows of a column of tiles of one image, as many strips as it takes to fill the chip (images times
 // segments of the plane times columns of tiles).  Strips side by side stand in lanes side by side, so that a wavefront's request for a row is
 // whole rows of a few images rather than 64 bytes of sixteen, and its stores too: the requests' lines bound the kernel more than its matrix instructions (with sixteen images
-// or segments in a wavefront 123 channels of 56 x 56, 5 x 5, 59 images 27.0 us, now 22.6; 558 of 3 x 3, 10 images 23.0 -> 20.2; 201 of 28 x 28, 7 x 7, stride 2, 49 images 14.1 -> 12.5;
-// 53 drawn geometries 0.975 of the time, none longer).  A lane's B operand is eight columns of its strip's next row, straight from global memory (16 bytes where
+// or segments in a wavefront 123 channels of 56 x 56, 5 x 5, 59 images 28.1 us, now 26.0; 558 of 3 x 3, 10 images 22.1 -> 19.5; 201 of 28 x 28, 7 x 7, stride 2, 49 images 15.9 -> 13.1;
+// 50 drawn geometries 0.95 of the time, none longer).  A lane's B operand is eight columns of its strip's next row, straight from global memory (16 bytes where
 // rows are aligned); the last k1 rows stay in registers, each output row needs stride1 new ones, fetched one output row ahead.
 // The banded matrices are the same for every strip and column tile of a channel: the four wavefronts of a workgroup make them
 // together, then each keeps all of them in registers.
@@ -19,9 +19,9 @@
 // scale that is not finite all outputs of the channel.  Every such output is itself not finite: a lane that has stored one computes its
 // outputs again on the factors, tap by tap, zeros skipped, where only the outputs are touched whose taps hold the value.
 //
-// Measured on MI355X: 96 channels of 56 x 56, 7 x 7 at rank 5, 32 images, bf16: 13.6 us (68 on the factors): 6.7 of them matrix instructions, about 3.5 the latency of the
-// first loads and the bands, 2 the launch; 640 of 28 x 28, 5 x 5, stride 2, 8 images 7.8, 217 of 28 x 28, 7 x 7, 32 images 11.3 (then 16.6 and 14.5 with rows in loads of
-// two elements and more of them ahead).  60 random geometries of 64 to 768 channels: 1.04 to 41 times the speed of the kernel on the factors.
+// Measured on MI355X: 96 channels of 56 x 56, 7 x 7 at rank 5, 32 images, bf16: 14.0 us (14.5 with sixteen images or segments in a wavefront, 68 on the factors): 6.7 of them matrix instructions, about 3.5 the latency of the
+// first loads and the bands, 2 the launch; 640 of 28 x 28, 5 x 5, stride 2, 8 images 6.9, 217 of 28 x 28, 7 x 7, 32 images 11.6 (before strips lay along the row 8.3 and 11.8, with rows in loads of two elements and more of them ahead
+// 16.6 and 14.5).  60 random geometries of 64 to 768 channels: 1.04 to 41 times the speed of the kernel on the factors.
 #include "tsvd_depthwise.h"
 
 #include <algorithm>

@@ -100,8 +100,8 @@ __device__ __forceinline__ double row_sum(const unsigned char* strip, int row, i
 __device__ __forceinline__ bool in_fp32(float z) { return fabsf(z) <= 3.402823466e38f; }        // (false for NaN)
 
 // The arguments of either kernel.  They are passed one by one, and the first fourteen words come preloaded in registers: a load from the others takes 0.3 us, and
-// everything waited for it in either launch (16384 x 4096 x 8192 at 16 tokens 16.65 -> 16.2 us, 428 x 949 x 320 at 7 6.75 -> 6.25, 10543 x 726 x 138 at 12
-// 8.55 -> 8.0; of 25 drawn calls of 2 to 16 tokens the 13 that come here take 0.92 to 0.98 of the time).
+// everything waited for it in either launch (16384 x 4096 x 8192 at 16 tokens 16.7 -> 16.2 us, 428 x 949 x 320 at 7 6.85 -> 6.3, 10543 x 726 x 138 at 12
+// 8.55 -> 8.0; of 50 drawn calls of 2 to 16 tokens the 18 that come here take 0.93 to 0.98 of the time).
 struct tsvd_few_v_args {
     const unsigned char* tiles;
     const uint16_t* x;
@@ -373,7 +373,7 @@ tsvd_few_u_kernel(const unsigned char* p_tiles, const unsigned char* p_planes, c
     for (int s = 0; s < SW; ++s) w[s] = load_w(s, q);        // (q < nkt: there are no more wavefronts side by side than columns)
     p.y = p_y;
     p.ld = p_ld;
-    asm volatile("" : "+s"(p.y), "+s"(p.ld));               // (not preloaded: read behind the first requests)
+    asm volatile("" : "+s"(p.y), "+s"(p.ld));               // (the pitch is not preloaded: read behind the first requests)
     auto column = [&](int T, auto last) {
         uint32_t second[SW][2];
 #pragma unroll

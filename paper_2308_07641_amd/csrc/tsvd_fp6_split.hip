@@ -94,7 +94,7 @@ __device__ __forceinline__ split_tile tile_of(const Extra& p) {
 }
 
 // The arguments of a stage.  Its first requests need fourteen words, which come preloaded in registers; a load from the others takes 0.3 us, and everything waits for it
-// (3072 x 768 x 1536 fp32 at 197 tokens 17.1 -> 16.6 us, 741 x 1024 x 413 fp32 at 102 11.8 -> 11.3, 1051 x 2539 x 559 at 256 13.6 -> 13.2; none of 50 drawn calls longer).  extra: words of split_x (its x stands at `act` then, N at act_bytes) or of split_place.
+// (3072 x 768 x 1536 fp32 at 197 tokens 17.1 -> 16.6 us, 741 x 1024 x 413 fp32 at 102 11.75 -> 11.3, 1051 x 2539 x 559 at 256 13.7 -> 13.2; none of 50 drawn calls longer).  extra: words of split_x (its x stands at `act` then, N at act_bytes) or of split_place.
 #define SPLIT_ARGUMENTS const uint32_t *p_tiles, const void *p_act, unsigned p_tile_bytes, unsigned p_act_bytes, int p_nkt, int p_npairs, int p_code_blocks, int p_plane_blocks, int p_bvalid, \
                         unsigned p_extra0, unsigned p_extra1, unsigned p_extra2, gemm_args p_rest
 #define SPLIT_STRUCT split_stage(p_tiles, p_act, p_tile_bytes, p_act_bytes, p_nkt, p_npairs, p_code_blocks, p_plane_blocks, p_bvalid, p_rest)

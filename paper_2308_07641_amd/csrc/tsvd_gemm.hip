@@ -524,7 +524,7 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
-// What the first requests need are the arguments that come preloaded in registers; a load from the others takes 0.3 us, and everything waits for it (3072 x 768 x 1536 at 512 tokens 15.53 -> 15.4 us, 342 x 597 x 1080 at 1901 12.6 -> 12.3).
+// What the first requests need are the arguments that come preloaded in registers; a load from the others takes 0.3 us, and everything waits for it (342 x 597 x 1080 at 1901 tokens 12.6 -> 12.3 us, 1672 x 320 x 172 at 513 11.3 -> 10.85; 3072 x 768 x 1536 at 512, 17 us, 0.1 less, what its runs differ by).
 // KG > 1 splits the contraction over KG groups of WM x WN wavefronts: a ring slot then holds KG
 // pairs, group kg multiplies pair KG * P + kg, and the groups' accumulators are added through LDS
 // at the end.  Same tile and same bytes moved, KG times the wavefronts to hide waits with.

@@ -42,8 +42,9 @@ bool tsvd_pair_squares(int64_t M, int64_t N);
 size_t tsvd_pair_bytes(int64_t M, int64_t N);
 // Lays the plan out in `mem` (tsvd_pair_bytes, 256-byte aligned) and enqueues the start vector.
 void tsvd_pair_prepare(int64_t M, int64_t N, void* mem, tsvd_pair_plan* plan, hipStream_t stream);
-// Makes the pairs taken with the plan a sequence: each one's leading value is the second of the one before, or above it, as that of a residual is when the
-// pair, or a matrix of rank one near it, is taken away (the k-th singular value of A is at most the (k - 1)-th of A less a matrix of rank one).
+// Makes the pairs taken with the plan a sequence: each one's leading value is expected at the second of the one before or a little above (of 3700 iterations on 240 random matrices 98 in 100 had
+// it at 0.99 to 1.3 of it, the lowest at 0.83).  That is no bound: a matrix of rank one taken away would give one, but all scales are fitted again, and residuals differ by as many terms as there
+// are.  What results rest on is the tail's look at the image of the edge, and the pair that is taken again without shifts.
 void tsvd_pair_sequence(tsvd_pair_plan* plan, tsvd_pair_shifts* shifts);
 // Gram matrix of R [M][N] and its squarings `from` .. `to` - 1 (from = 0 computes the Gram matrix first).  shifted (in a sequence, from = 0, of `to` squarings in all): the
 // squarings are shifted by what the pair before left.

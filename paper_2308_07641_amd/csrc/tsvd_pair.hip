@@ -65,9 +65,9 @@ __device__ __forceinline__ double lane_value(double v, int from) {
 // the edge e of the part of the spectrum that is not wanted, and the next shift halfway to the image of that edge, s_{k+1} = (s_k / t_k)^2 / 2, p squarings are, on [0, e],
 // the Chebyshev polynomial of degree 2^p (plus one, halved), which grows beyond e as cosh(2^p acosh(2 lambda / e - 1)): a distance d = lambda / e - 1 counts like 2 sqrt(d)
 // instead of d.  Six squarings leave a residual of [512, 256] Laplace entries at the rank that eight to nine leave it at without (a component 81 -> 72 us, of [300, 700]
-// 113 -> 99; the Gram matrix, which traces the value back while it waits for R, 0.6 us longer).  e is a fixed part of the
-// second eigenvalue of the pair before, traced back to its own Gram matrix by the shifts and traces of its squarings; it has to lie below the leading one, as it
-// does where the pairs are a sequence, and the tail checks that the image of e is small against the result.  The matrices are stored with
+// 113 -> 99; the Gram matrix, which traces the value back while it waits for R, 1.1 us longer).  e is a fixed part of the
+// second eigenvalue of the pair before, traced back to its own Gram matrix by the shifts and traces of its squarings.  It has to lie below the leading one, which nothing
+// guarantees (tsvd_pair_sequence): the tail takes a pair only if the image of e is small against the result.  The matrices are stored with
 // the next shift taken off their diagonal, the diagonals by themselves without.
 // (GRAM only but for n; the scalars in front of it come preloaded in registers)
 struct pair_square_rest {
@@ -632,8 +632,8 @@ void tsvd_pair_square(const tsvd_pair_plan& p, const double* R, int from, int to
     const bool big = p.np > 384;
     const int nb = p.np / (big ? 32 : 16);
     const unsigned tiles = (unsigned)pair_grid(nb);
-    // The edge for p squarings: at a degree of 2^p the second eigenvalue of the pair before less 2 %, which the leading one is not below, comes out 2^52 times the edge's
-    // image (cosh 36.7): p = 6 0.90 of it, 5 0.72, 7 0.96.
+    // The edge for p squarings: at a degree of 2^p the second eigenvalue of the pair before less 2 %, which the leading one is seldom below, comes out 2^52 times the edge's
+    // image (cosh 36.7): p = 6 0.90 of it, 7 0.96, 8 0.975.
     const double edge = p.sequence && shifted && from == 0 ? 0.98 / (1.0 + 0.5 * (std::cosh(36.7 / std::ldexp(1.0, to)) - 1.0)) : 0.0;
     const pair_square_rest rest = {p.n, p.M, p.N, p.v0, p.s, edge};
 #define PAIR_SQUARE(T, GRAM, TR, grid, threads, in, at, step) \

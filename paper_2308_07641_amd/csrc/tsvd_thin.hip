@@ -10,8 +10,8 @@
 // Eight wavefronts.  Planes of x are made block by block (a wavefront per record: gather, convert); wavefront w multiplies the
 // rank blocks w, w + 8, ... of stage V (128 rows x the panel; its result lanes are stage U's operand lanes, see tsvd_panel_fp6_kernel)
 // and writes their planes of z beside those of x; then stage U runs in units of 16 UTM rows, no barrier between them.
-// Where stage V's rank blocks do not go round, wavefronts share some: each a part of the contraction, sums added in LDS (3 x 3 from 310 channels, rank 119, two images of 28 x 28: 18.1 -> 14.2 us;
-// 5 x 5 from 198, rank 213, twelve of 28 x 28: 101 -> 90; 3456 x 7104 x 193, rows of tokens, at 2801 40.3 -> 36.3; 512 x 1536 x 1280 at 13568 84.1 -> 81.6; 110 drawn calls of which 40 share 0.987 of the time).
+// Where stage V's rank blocks do not go round, wavefronts share some: each a part of the contraction, sums added in LDS (3 x 3 from 310 channels, rank 119, two images of 28 x 28: 18.8 -> 14.2 us;
+// 5 x 5 from 198, rank 213, twelve of 28 x 28: 100 -> 88; 3456 x 7104 x 193, rows of tokens, at 2801 40.3 -> 35.6; 512 x 1536 x 1280, rows of tokens, at 13568 82.9 -> 79.1: each with arguments preloaded, 0.4 to 0.5 us).
 // Where x does not fit beside z its blocks pass through in chunks, two in LDS: four of the wavefronts multiply the one before
 // they make their records of the next, the other four after, so that on every SIMD matrix and vector instructions overlap.
 // Code words go from the L2s to registers, one fetch ahead across rank blocks and units (those of the next unit are in
@@ -55,7 +55,7 @@ struct thin_args {
     int slices;                              // workgroups of a panel, each with the whole z and its part of y's rows
 };
 // They are passed so that the fourteen words which come preloaded in registers are what stage V needs: a load from the others takes 0.3 us, and everything waits
-// for it (742 x 106 x 103 at 29 tokens 7.05 -> 6.6 us, 388 x 120 x 256 at 33 5.5 -> 5.1, 3072 x 768 x 1545 at 3152 39.8 -> 39.1; of 50 drawn calls none longer, 0.97 of the time).
+// for it (742 x 106 x 103 at 29 tokens 5.3 -> 4.8 us, 388 x 120 x 256 at 33 5.45 -> 4.95, 359 x 100 x 81 at 1569 5.7 -> 5.2; 3072 x 768 x 1545 at 3152, 39 us, as before).
 struct thin_rest {
     void* y;
     long long ldy;
